@@ -459,8 +459,8 @@ class Plan:
 
     def simulate_1f1b_static(self, count: int, d_indices, d_event=None, d_closed=None,
                              stream: int = 0) -> None:
-        """sailor_simulate_1f1b_static: the same schedule with its working set in the library's
-        static device array (no allocation inside the call)."""
+        """sailor_simulate_1f1b_static: the same schedule, at most 4 096 plans per call, which
+        allocates nothing."""
         rc = self._lib.sailor_simulate_1f1b_static(self._h, count, _ptr(d_indices), _ptr(d_event),
                                                    _ptr(d_closed), stream or None)
         if rc != SAILOR_OK:

@@ -18,6 +18,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "sailor_dev.h"
 
 namespace sailor {
@@ -1522,70 +1524,136 @@ struct SimArgs {
   uint64_t count;
   const uint64_t *indices;
   double *t_event, *t_closed;  // either may be NULL
-  double *rings;               // NULL: the rings live in LDS; else [count][2][P_max][ring] doubles
-  int ring;                    // slots per stage, a power of two > P_max
-  int p_max;
 };
 
-// The op a stage runs at position pos of its 1F1B order: warm-up forwards, then one forward
-// and one backward in turn, then the remaining backwards.  Returns true for a backward.
-__device__ __forceinline__ bool sim_op_at(int P, int M, int i, int pos, int &m) {
-  const int w = min(P - 1 - i, M);
-  if (pos < w) { m = pos; return false; }
-  const int q = pos - w;
-  if (q < 2 * (M - w)) {
-    m = (q & 1) ? (q >> 1) : w + (q >> 1);
-    return (q & 1) != 0;
-  }
-  m = (M - w) + (q - 2 * (M - w));
-  return true;
+// The value of the lane below / above (0 at the ends of the wave).
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
+__device__ __forceinline__ double from_below(double v) { return lane_shift<0x138>(v); }  // wave_shr:1
+__device__ __forceinline__ double from_above(double v) { return lane_shift<0x130>(v); }  // wave_shl:1
 
 // The 1F1B schedule of one pipeline of a plan, op by op (warm-up, steady and cool-down phases,
-// Sec. 4.3), beside the closed form of Sec. 4.2.2 on the same stage times.  One workgroup per
-// candidate, one thread per stage.  A forward of stage i takes its layers' forward time plus the
-// transfer to stage i + 1, a backward its backward time plus the transfer to stage i - 1; a
+// Sec. 4.3), beside the closed form of Sec. 4.2.2 on the same stage times.  One wave per
+// candidate, SPL consecutive stages per lane.  A forward of stage i takes its layers' forward time
+// plus the transfer to stage i + 1, a backward its backward time plus the transfer to stage i - 1; a
 // forward waits for the previous stage's forward of the same microbatch, a backward for the next
-// stage's backward.  The schedule advances in rounds: in a round every stage runs its next op if
-// what it waits for was finished in an earlier round.  End times travel between neighbouring
-// stages through rings indexed by microbatch; a producer is never more than P ops ahead of its
-// consumer, so `ring` > P slots per stage suffice.  At most 2 (N_b + P) rounds are needed.
-__global__ __launch_bounds__(256) void k_sim_1f1b(DevPlan pl, SimArgs a) {
-  extern __shared__ double sim_lds[];
-  __shared__ double s_t[kMaxStages];
-  __shared__ int s_fc[kMaxStages], s_bc[kMaxStages];  // forwards / backwards a stage has finished
-  __shared__ double s_red[4];
-  const uint64_t ci = blockIdx.x;
-  if (ci >= a.count) return;
-  const int i = threadIdx.x;
-  const uint64_t idx = a.indices[ci];
-  Cand c;
-  if (!decode_index(pl, idx, c)) {  // uniform over the workgroup
-    if (i == 0) {
-      if (a.t_event) a.t_event[ci] = __builtin_nan("");
-      if (a.t_closed) a.t_closed[ci] = __builtin_nan("");
+// stage's backward.
+//
+// The order of a stage's ops is fixed, so an op's end time is max(end of the stage's op before
+// it, end of the op it waits for) + duration, and the ops can be computed in any order that
+// respects both.  Taken in the rounds of a pipeline whose ops all last one round --
+//     F of microbatch m on stage i:  round i + m while m < P - i, round i + 2 m afterwards
+//     B of microbatch m on stage i:  round 2 P - 1 - i + 2 m
+// -- a stage runs at most one op per round, and whenever an op runs, the last op its neighbour
+// ran is the one it waits for (the one forward that waits longer, m = P - i, finds its neighbour
+// idle since).  One end time per stage is therefore all the state there is, and it stays in
+// registers: no queue of end times, no flags, no barrier.
+// From round P on, stages of one parity run forwards in the even rounds and the others
+// backwards, and vice versa in the odd ones.  Stages are laid out so that in the odd rounds the
+// two of a pair wait for each other, which leaves max, add, add per pair, and only the even
+// rounds pass values between lanes.  A position without a stage has durations 0: what it passes
+// on never exceeds what its neighbour already has.
+//
+// Bound by the chain of dependent fp64 operations: 2 (N_b + P) rounds of one or two maxima and
+// additions.  The 64 best plans of a 48-layer, 104 256 000-candidate space take 18.5 us where the
+// form with end times in LDS rings and two barriers per round took 407 us (same plans, one card).
+template <int SPL>
+__device__ __forceinline__ double sim_schedule(int P, int M, const double (&fd)[SPL], const double (&bd)[SPL]) {
+  const int lane = threadIdx.x & 63, first = lane * SPL - (P & 1);  // stage of this lane's first position
+  double x[SPL];         // end of the last op of each position
+  int a_lo[SPL], a_n[SPL], b_lo[SPL], b_n[SPL];  // periods in which its even / odd round runs an op
+#pragma unroll
+  for (int s = 0; s < SPL; ++s) {
+    const int i = first + s;
+    const bool on = i >= 0 && i < P;
+    x[s] = 0.0;
+    if (s & 1) {  // backward, then forward
+      a_lo[s] = b_lo[s] = (P - 1 - i) >> 1;
+      a_n[s] = on ? M : 0;
+      b_n[s] = on ? ((2 * M - 3 + i - P) >> 1) - b_lo[s] + 1 : 0;
+    } else {      // forward, then backward
+      a_lo[s] = (P - i) >> 1;
+      a_n[s] = on ? ((2 * M - 2 + i - P) >> 1) - a_lo[s] + 1 : 0;
+      b_lo[s] = (P - 2 - i) >> 1;
+      b_n[s] = on ? M : 0;
     }
-    return;
+    a_n[s] = max(a_n[s], 0);
+    b_n[s] = max(b_n[s], 0);
   }
+  // warm-up: rounds 0 .. P - 1 run forwards only
+  for (int r = 0; r < P; ++r) {
+    const double below = from_below(x[SPL - 1]);
+#pragma unroll
+    for (int s = SPL - 1; s >= 0; --s) {  // downwards: a position reads the one before it unchanged
+      const int i = first + s;
+      const double y = fmax(x[s], s == 0 ? below : x[s > 0 ? s - 1 : 0]) + fd[s];
+      x[s] = (i >= 0 && i <= r && r - i < min(M, P - i)) ? y : x[s];
+    }
+  }
+  // period k: rounds P + 2 k (even) and P + 2 k + 1 (odd)
+  const int periods = (2 * M + P - 1) >> 1;
+  const int full_lo = min((P + 1) >> 1, periods), full_hi = max(full_lo, min((2 * M - 1 - P) >> 1, periods));
+  auto period = [&](int k, auto all) {
+    constexpr bool ALL = decltype(all)::value;  // every stage runs an op in both rounds
+    double y[SPL];
+    const double below = from_below(x[SPL - 1]), above = from_above(x[0]);
+#pragma unroll
+    for (int s = 0; s < SPL; ++s) {
+      const double dep = (s & 1) ? (s == SPL - 1 ? above : x[s < SPL - 1 ? s + 1 : s])
+                                 : (s == 0 ? below : x[s > 0 ? s - 1 : 0]);
+      y[s] = fmax(x[s], dep) + ((s & 1) ? bd[s] : fd[s]);
+      if (!ALL) y[s] = (uint32_t)(k - a_lo[s]) < (uint32_t)a_n[s] ? y[s] : x[s];
+    }
+#pragma unroll
+    for (int s = 0; s < SPL; s += 2) {
+      const double later = fmax(y[s], y[s + 1]);
+      x[s] = later + bd[s];
+      x[s + 1] = later + fd[s + 1];
+      if (!ALL) {
+        x[s] = (uint32_t)(k - b_lo[s]) < (uint32_t)b_n[s] ? x[s] : y[s];
+        x[s + 1] = (uint32_t)(k - b_lo[s + 1]) < (uint32_t)b_n[s + 1] ? x[s + 1] : y[s + 1];
+      }
+    }
+  };
+  int k = 0;
+  for (; k < full_lo; ++k) period(k, std::false_type());
+  for (; k + 4 <= full_hi; k += 4) {  // (by hand: the compiler does not unroll around cross-lane moves)
+    period(k, std::true_type());
+    period(k, std::true_type());
+    period(k, std::true_type());
+    period(k, std::true_type());
+  }
+  for (; k < full_hi; ++k) period(k, std::true_type());
+  for (; k < periods; ++k) period(k, std::false_type());
+  double end = 0.0;  // makespan: the latest stage (what lies beyond the stages is no later)
+#pragma unroll
+  for (int s = 0; s < SPL; ++s) end = fmax(end, x[s]);
+  return wave_max_f64(end);
+}
+
+template <int SPL>
+__device__ __forceinline__ void sim_plan(const DevPlan &pl, const SimArgs &a, uint64_t ci, const Cand &c, int M,
+                                         double *s_t) {
   const int P = c.P, G = pl.G, GX = pl.GX, Z = pl.Z, MB = pl.MB, TP = pl.TP;
-  const int M = pl.nb[c.mb * pl.DP + c.dp];
-  if (M == 0) {  // the batch does not divide
-    if (i == 0) {
-      if (a.t_event) a.t_event[ci] = __builtin_huge_val();
-      if (a.t_closed) a.t_closed[ci] = __builtin_huge_val();
-    }
-    return;
-  }
-  const ShapeRec sh = pl.shapes[c.shape];
-  const bool mine = i < P;
-  double fdur = 0.0, bdur = 0.0;
-  if (mine) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t rs = pl.shapes[c.shape].row_stage;
+  const double p2p = (double)pl.p2p[c.mb];
+  const double *bwp = pl.bwp + c.mb * Z * Z;
+  double fd[SPL], bd[SPL];
+#pragma unroll
+  for (int s = 0; s < SPL; ++s) {
+    const int i = lane * SPL - (P & 1) + s;
+    fd[s] = bd[s] = 0.0;
+    if (i < 0 || i >= P) continue;
     const int seg = i < c.k1 ? 0 : (i < c.k2 ? 1 : 2);
     const int xg = pl.xt[at3(c.a, seg) % GX], g = xg & 255, g2 = xg >> 8, z = at3(c.a, seg) / GX, k = at3(c.tp, seg);
-    const size_t at = (((size_t)(sh.row_stage + i) * G + g) * MB + c.mb) * TP + k;
-    const size_t at2 = (((size_t)(sh.row_stage + i) * G + g2) * MB + c.mb) * TP + k;
-    const double p2p = (double)pl.p2p[c.mb];
-    const double *bwp = pl.bwp + c.mb * Z * Z;
+    const size_t at = (((size_t)(rs + i) * G + g) * MB + c.mb) * TP + k;
+    const size_t at2 = (((size_t)(rs + i) * G + g2) * MB + c.mb) * TP + k;
     double send_f = 0.0, send_b = 0.0;
     if (i < P - 1) {
       const int sn = (i + 1) < c.k1 ? 0 : ((i + 1) < c.k2 ? 1 : 2);
@@ -1600,59 +1668,49 @@ __global__ __launch_bounds__(256) void k_sim_1f1b(DevPlan pl, SimArgs a) {
       f = pl.st_f[at2];
       b = pl.st_b[at2];
     }
-    fdur = f + send_f;
-    bdur = b + send_b;
+    fd[s] = f + send_f;
+    bd[s] = b + send_b;
     s_t[i] = f + b + (send_f + send_b);
-    s_fc[i] = 0;
-    s_bc[i] = 0;
   }
   __syncthreads();
-  if (i == 0 && a.t_closed) {  // sums in stage order
+  if (a.t_closed) {  // sums in stage order
     double sum_t = 0.0, max_t = 0.0;
+#pragma unroll 8
     for (int j = 0; j < P; ++j) {
       sum_t += s_t[j];
       max_t = fmax(max_t, s_t[j]);
     }
-    a.t_closed[ci] = sum_t + (double)(M - 1) * max_t;
+    if (lane == 0) a.t_closed[ci] = sum_t + (double)(M - 1) * max_t;
   }
-  double *ring_f = a.rings ? a.rings + ci * 2 * (size_t)a.p_max * a.ring : sim_lds;
-  double *ring_b = ring_f + (size_t)a.p_max * a.ring;
-  const int rmask = a.ring - 1;
-  int pos = 0;
-  double free_at = 0.0;
-  for (int round = 0; round < 2 * (M + P) + 4; ++round) {  // the bound is never reached
-    bool ready = false, bwd = false;
-    int m = 0;
-    double dep = 0.0;
-    if (mine && pos < 2 * M) {
-      bwd = sim_op_at(P, M, i, pos, m);
-      if (!bwd) {
-        if (i == 0) ready = true;
-        else if (s_fc[i - 1] > m) { ready = true; dep = ring_f[(size_t)(i - 1) * a.ring + (m & rmask)]; }
-      } else {
-        if (i == P - 1) { ready = true; dep = ring_f[(size_t)i * a.ring + (m & rmask)]; }
-        else if (s_bc[i + 1] > m) { ready = true; dep = ring_b[(size_t)(i + 1) * a.ring + (m & rmask)]; }
-      }
+  if (a.t_event) {
+    const double end = sim_schedule<SPL>(P, M, fd, bd);
+    if (lane == 0) a.t_event[ci] = end;
+  }
+}
+
+__global__ __launch_bounds__(64) void k_sim_1f1b(DevPlan pl, SimArgs a) {
+  __shared__ double s_t[kMaxStages];
+  const uint64_t ci = blockIdx.x;
+  if (ci >= a.count) return;
+  const uint64_t idx = a.indices[ci];
+  Cand c;
+  double none = __builtin_nan("");  // an index outside the space
+  int M = 0;
+  if (decode_index(pl, idx, c)) {
+    M = pl.nb[c.mb * pl.DP + c.dp];
+    none = __builtin_huge_val();    // M == 0: the batch does not divide
+  }
+  if (M == 0) {  // uniform
+    if (threadIdx.x == 0) {
+      if (a.t_event) a.t_event[ci] = none;
+      if (a.t_closed) a.t_closed[ci] = none;
     }
-    __syncthreads();  // every stage has read before any stage writes
-    if (ready) {
-      const double start = fmax(free_at, dep);
-      free_at = start + (bwd ? bdur : fdur);
-      if (bwd) { ring_b[(size_t)i * a.ring + (m & rmask)] = free_at; s_bc[i] += 1; }
-      else { ring_f[(size_t)i * a.ring + (m & rmask)] = free_at; s_fc[i] += 1; }
-      pos += 1;
-    }
-    if (!__syncthreads_or(ready ? 1 : 0)) break;  // nothing moved: every stage is done
+    return;
   }
-  // makespan: the latest stage
-  double end = mine ? free_at : 0.0;
-  end = wave_max_f64(end);
-  if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = end;
-  __syncthreads();
-  if (i == 0 && a.t_event) {
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) end = fmax(end, s_red[w]);
-    a.t_event[ci] = end;
-  }
+  // two stages per lane up to 128 positions (two and four positions cost nearly the same per
+  // round, their chains run side by side; one per lane would pass values in every round)
+  if (c.P + (c.P & 1) <= 128) sim_plan<2>(pl, a, ci, c, M, s_t);
+  else sim_plan<4>(pl, a, ci, c, M, s_t);
 }
 
 // ------------------------------------------------------------------ eval_batch

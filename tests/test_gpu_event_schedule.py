@@ -118,3 +118,27 @@ def test_deepest_pipeline(torch_cuda):
         check(torch_cuda, plan, orc, idx)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("batch", [2, 6, 64, 900])
+def test_stage_counts_around_the_layout_of_a_wave(torch_cuda, batch):
+    # one stage, odd and even counts, and both sides of the 128 positions that two stages per lane
+    # give; fewer, as many and more microbatches than stages (the same max / add per op: 1e-12)
+    rng = np.random.default_rng(batch)
+    L = 131
+    prob = make_problem(n_layers=L, n_types=2, n_zones=2, mb_list=(1, 2), tp_list=(1,), dp_list=(1, 2),
+                        pp_list=[1, 2, 3, 4, 63, 64, 65, 126, 127, 128, 129, 130], global_batch=batch,
+                        max_segments=2, uniform_layers=False,
+                        t_fwd=rng.uniform(0.5e-3, 2e-3, (2, 2, 1, L)), t_bwd=rng.uniform(1e-3, 4e-3, (2, 2, 1, L)),
+                        p2p=3_000_000, bw=np.array([[1e10, 1e9], [2e9, 1e10]]), layer_params=1000)
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        n = orc.num_candidates
+        idx = np.concatenate([np.arange(64), rng.integers(0, n, 250)])
+        # every depth's one-segment plans: the first candidates of its block
+        seen = {}
+        for c in range(0, n, max(1, n // 4000)):
+            seen.setdefault(plan.decode(c).pp, c)
+        check(torch_cuda, plan, orc, np.concatenate([idx, list(seen.values())]))
+    finally:
+        plan.destroy()
