@@ -41,6 +41,7 @@ constexpr double kSplitAbove = 0.9, kSplitAboveMean = 1.5, kSplitTo = 0.7, kSpli
 constexpr uint32_t kRankOneWorkgroup = 128;  // largest k whose final ranking runs as one workgroup
 constexpr uint32_t kEvalUnitTarget = 16384;  // candidates per workgroup of the range evaluation
 constexpr unsigned kEvalRowsThreads = 512;
+constexpr uint64_t kPlaceWorkgroups = 1024;  // workgroups a list of placements is spread over, if it is long enough
 constexpr size_t kEvalRowsMaxLds = 64 * 1024;  // above this the range form evaluates lane by lane
 constexpr size_t kScanMaxLds = 160 * 1024;     // a scan workgroup stages its records within the LDS of a compute unit
 #define HIP_TRY(expr)                                                              \
@@ -964,6 +965,8 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   d.n_bw_coef = p->n_bw_coef;
   if (p->n_bw_coef > 0) CREATE_TRY(ar.upload(&d.bw_poly, p->bw_poly, (size_t)Z * Z * p->n_bw_coef));
   CREATE_TRY(ar.alloc(&d.bwp, (size_t)MB * Z * Z));
+  CREATE_TRY(ar.alloc(&d.xsec, (size_t)MB * Z * Z));
+  if (!d.mixed) CREATE_TRY(ar.alloc(&d.list_tables, list_copy_words(d)));  // (not for problems with pairs of types)
   CREATE_TRY(ar.alloc(&d.tsec_f, (size_t)MB * Z * Z));
   CREATE_TRY(ar.alloc(&d.egs_f, (size_t)Z * Z));
   CREATE_TRY(ar.alloc(&d.price_f, GX));
@@ -974,6 +977,12 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   CREATE_TRY(ar.alloc(&d.nb, (size_t)MB * DP));
   CREATE_TRY(ar.alloc(&d.divis, MB));
   CREATE_TRY(ar.alloc(&d.st_params, RS));
+  // a stage record does not straddle cache lines (128 bytes): the evaluators of listed plans
+  // fetch one per stage from anywhere in the table, and lines are what that costs
+  d.row_w = 2u * (uint32_t)G + 2u;
+  if (d.row_w <= 16u) while (d.row_w & (d.row_w - 1u)) ++d.row_w;
+  else d.row_w = (d.row_w + 15u) & ~15u;
+  CREATE_TRY(ar.alloc(&d.st_row, RS * MB * TP * d.row_w));
   CREATE_TRY(ar.alloc(&d.st_c, RS * G * MB * TP));
   CREATE_TRY(ar.alloc(&d.st_f, RS * G * MB * TP));
   CREATE_TRY(ar.alloc(&d.st_b, RS * G * MB * TP));
@@ -1014,6 +1023,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
   k_quota_table<<<quota_grid(d), 256>>>(d, d.avail, nullptr, 0u);
   k_small_tables<<<1, 256>>>(d);
+  if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
   k_shape_agg<<<(unsigned)NS, 256>>>(d);
   CREATE_TRY(hipGetLastError());
@@ -1418,6 +1428,17 @@ static sailor_status search_setup(sailor_plan *pl, int beam) {
   return SAILOR_OK;
 }
 
+// A workgroup takes up to 64 plans; fewer when the list is too short to give every compute unit
+// four workgroups that way (short lists are bound by the latency of one workgroup's passes).
+static void launch_placements(const sailor_plan *pl, PlaceArgs a, hipStream_t st) {
+  const uint64_t share = (a.count + kPlaceWorkgroups - 1) / kPlaceWorkgroups;
+  a.per_wg = (uint32_t)std::min<uint64_t>(kPlaceMaxPlans, std::max<uint64_t>(1, share));
+  const unsigned grid = (unsigned)((a.count + a.per_wg - 1) / a.per_wg);
+  const size_t lds = place_lds_bytes(pl->dev, a.per_wg);
+  if (a.pools_b) k_eval_placements<true><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+  else k_eval_placements<false><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+}
+
 sailor_status sailor_eval_placements(sailor_plan *pl, uint64_t count, const int32_t *d_desc,
                                      const int32_t *d_pools, const int32_t *d_pools_b,
                                      const int32_t *d_tps, uint32_t pool_stride,
@@ -1445,7 +1466,7 @@ sailor_status sailor_eval_placements(sailor_plan *pl, uint64_t count, const int3
   a.has_bound = (constraint && constraint->has_bound) ? 1 : 0;
   a.bound = a.has_bound ? constraint->bound : 0.0;
   a.T = d_time; a.C = d_cost; a.mem = d_mem; a.mask = d_mask;
-  k_eval_placements<<<(unsigned)((count + kPlaceWaves - 1) / kPlaceWaves), kPlaceWaves * 64, 0, st>>>(pl->dev, a);
+  launch_placements(pl, a, st);
   HIP_TRY(hipGetLastError());
   return SAILOR_OK;
 }
@@ -1478,7 +1499,8 @@ sailor_status sailor_eval_replica_placements(sailor_plan *pl, uint64_t count, co
   a.has_bound = (constraint && constraint->has_bound) ? 1 : 0;
   a.bound = a.has_bound ? constraint->bound : 0.0;
   a.T = d_time; a.C = d_cost; a.mem = d_mem; a.mask = d_mask;
-  k_eval_replicas<<<(unsigned)((count + kPlaceWaves - 1) / kPlaceWaves), kPlaceWaves * 64, 0, st>>>(pl->dev, a);
+  k_eval_replicas<<<(unsigned)((count + kReplicaWaves - 1) / kReplicaWaves), kReplicaWaves * 64,
+                    replica_lds_bytes(pl->dev), st>>>(pl->dev, a);
   HIP_TRY(hipGetLastError());
   return SAILOR_OK;
 }
@@ -1546,7 +1568,11 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   // the winner once more through the simulator, for its memory footprint and its mask
   PlaceArgs pa{};
   pa.count = 1;
-  pa.one = pl->search_final;
+  pa.desc = pl->search_final->desc;  // (device addresses: nothing is read here)
+  pa.pools = pl->search_final->pools;
+  pa.pools_b = opt->allow_split ? pl->search_final->pools_b : nullptr;
+  pa.tps = pl->search_final->tps;
+  pa.pool_stride = sizeof pl->search_final->pools / sizeof pl->search_final->pools[0];
   pa.pps = pl->d_search_pps;
   pa.n_pp = a.n_pp;
   pa.objective = (int)objective;
@@ -1556,7 +1582,7 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   pa.C = pl->search_eval + 1;
   pa.mem = reinterpret_cast<uint64_t *>(pl->search_eval + 2);
   pa.mask = reinterpret_cast<uint32_t *>(pl->search_eval + 3);
-  k_eval_placements<<<1, kPlaceWaves * 64, 0, st>>>(pl->dev, pa);
+  launch_placements(pl, pa, st);
   HIP_TRY(hipGetLastError());
   SubResult fin;
   double ev[4];

@@ -88,6 +88,7 @@ struct DevPlan {
   int n_blocks, n_shapes, n_units, n_row_stages, P_max;
   int pst;                 // 1: segments 2 and 3 carry their own tp digit
   int otp;                 // radix of those digits: TP, or 1 when all segments share one tp
+  uint32_t row_w;          // words of a stage record (see st_row)
   int W_max;               // most GPUs one replica can take from a pool: P_max * largest tp
   uint32_t inner;          // MB*TP*DP*ZG candidates per (shape, outer digits)
   uint64_t stride3;        // index stride of segment 3's relative pool: inner*(ZG-1)*otp
@@ -118,7 +119,8 @@ struct DevPlan {
   int n_bw_coef;               // 0: constant link bandwidth
   const double *bw_poly;       // [Z][Z][n_bw_coef] bandwidth over log2(message bytes)
   double *bwp;                 // [MB][Z][Z] bandwidth seen by one activation transfer
-  float *tsec_f;               // [MB][Z][Z] seconds of one activation transfer a -> b
+  double *xsec;                // [MB][Z][Z] seconds of one activation transfer a -> b
+  float *tsec_f;               // the same, rounded once
   float *egs_f;                // [Z][Z] egress both ways
   float *price_f;              // [GX] (a pair: the mean)
   float *xb_f;                 // [MB] (B/mb) * p2p bytes
@@ -131,6 +133,11 @@ struct DevPlan {
   const int32_t *st_n;         // layers
   const int32_t *st_first;     // first layer
   uint64_t *st_params;         // parameters incl. embedding / head
+  // one record per stage, microbatch size and TP degree, of row_w words: compute seconds per
+  // type [G], update seconds per type [G], bytes of weights, gradients and optimizer state of
+  // the shard (as an integer), bytes of its gradient buffer
+  double *st_row;              // [rs][MB][TP][row_w]
+  double *list_tables;         // the small tables of the evaluators of listed plans, as they lie in LDS
   double *st_c;                // [rs][G][MB][TP] sum of fwd + bwd layer times
   double *st_f, *st_b;         // [rs][G][MB][TP] the two sums apart (event-by-event schedule)
   double *st_u;                // [rs][G][TP] sum of update times

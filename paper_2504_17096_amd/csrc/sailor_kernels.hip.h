@@ -32,6 +32,9 @@ __device__ __forceinline__ float wave_min(float v) {
   return v;
 }
 
+// 24-bit multiply (full rate, unlike the 32-bit one), for table offsets
+__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return __umul24(a, b); }
+
 __device__ __forceinline__ size_t agg_slot(const DevPlan &pl, uint32_t shape, int tp, int seg) {
   return ((size_t)shape * pl.TP + tp) * 3 + seg;
 }
@@ -69,6 +72,7 @@ __global__ void k_small_tables(DevPlan pl) {
     for (int m = 0; m < pl.MB; ++m) {
       const double bytes = (double)pl.p2p[m], bwv = link_bw(pl, a, b, bytes);
       pl.bwp[m * Z * Z + i] = bwv;
+      pl.xsec[m * Z * Z + i] = bytes / bwv;
       pl.tsec_f[m * Z * Z + i] = (float)(bytes / bwv);
     }
     double e = 0.0;
@@ -125,6 +129,8 @@ struct StageArgs {
 
 // Per stage of every partition row: parameters, summed layer times per (type, mb, tp).
 __global__ void k_stage_tables(DevPlan pl, StageArgs a) {
+  __shared__ uint64_t s_params;
+  __shared__ double s_upd[kMaxTypes * kMaxTP];
   const int rs = blockIdx.x;
   const int n = pl.st_n[rs], first = pl.st_first[rs];
   const int G = pl.G, MB = pl.MB, TP = pl.TP;
@@ -134,7 +140,9 @@ __global__ void k_stage_tables(DevPlan pl, StageArgs a) {
     if (a.st_flags[rs] & 1) p += a.embed;
     if (a.st_flags[rs] & 2) p += a.head;
     pl.st_params[rs] = p;
+    s_params = p;
   }
+  double *const row = pl.st_row + (size_t)rs * MB * TP * pl.row_w;  // [MB][TP][row_w]
   const int Lc = a.uniform ? 1 : a.L;
   for (int i = threadIdx.x; i < G * MB * TP; i += blockDim.x) {
     double f = 0.0, b = 0.0;
@@ -146,6 +154,7 @@ __global__ void k_stage_tables(DevPlan pl, StageArgs a) {
       for (int l = first; l < first + n; ++l) { f += rf[l]; b += rb[l]; }
     }
     pl.st_c[(size_t)rs * G * MB * TP + i] = f + b;
+    row[(size_t)(i % (MB * TP)) * pl.row_w + i / (MB * TP)] = f + b;
     pl.st_f[(size_t)rs * G * MB * TP + i] = f;
     pl.st_b[(size_t)rs * G * MB * TP + i] = b;
   }
@@ -158,6 +167,16 @@ __global__ void k_stage_tables(DevPlan pl, StageArgs a) {
       for (int l = first; l < first + n; ++l) u += ru[l];
     }
     pl.st_u[(size_t)rs * G * TP + i] = u;
+    s_upd[i] = u;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < MB * TP; i += blockDim.x) {
+    const int k = i % TP;
+    const uint64_t shard = (s_params + (uint64_t)pl.tpv[k] - 1) / (uint64_t)pl.tpv[k];
+    double *const r = row + (size_t)i * pl.row_w + G;
+    for (int g = 0; g < G; ++g) r[g] = s_upd[g * TP + k];
+    r[G] = __longlong_as_double((long long)(shard * (uint64_t)pl.bpp));
+    r[G + 1] = (double)shard * (double)pl.gb;
   }
 }
 
@@ -1821,9 +1840,6 @@ struct PoolInfo {   // per pool, staged in LDS (a pair of types: the tighter of 
   uint64_t pad;     // (32 bytes: the index is a shift)
 };
 static_assert(sizeof(PoolInfo) == 32, "one pool per 32 bytes of LDS");
-
-// 24-bit multiply (full rate, unlike the 32-bit one): every product below is a table offset
-__device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return __umul24(a, b); }
 
 // A segment record of the range evaluation, kept in LDS as two 16-byte halves in arrays of
 // their own: the records a wave reads together then lie 16 bytes apart, not 32, and collide

@@ -733,14 +733,121 @@ __global__ __launch_bounds__(256) void k_search_pick(const SubResult *results, u
 
 // ------------------------------------------------------------------ listed placements
 
+// The problem's small tables in LDS: every stage of every listed plan reads a dozen of these
+// words, at addresses that differ from lane to lane.  They are laid out once per plan in device
+// memory (k_list_tables), so that a workgroup copies them in one go -- a dozen loops, one per
+// table, cost a trip to memory each, 5 us in front of every workgroup.
+struct ListTables {
+  double *xsec;      // [MB][Z][Z] seconds of one activation transfer
+  double *bw;        // [Z][Z]
+  double *egress;    // [Z][Z] (zeros without egress prices)
+  double *price;     // [G]
+  double *ring;      // [DP] 2 (D - 1) / D
+  double *tpd;       // [TP]
+  uint64_t *cap, *res;  // [G]
+  uint64_t *act;     // [MB][TP]
+  int32_t *nb;       // [MB][DP]
+  int32_t *dpv, *tpv, *node;  // [DP], [TP], [G]
+  uint32_t *zg;      // [ZGr] zone | type << 8 of a pool
+  int32_t *avail;    // [ZGr] (not part of the copy: it changes between calls)
+};
+
+__host__ __device__ inline size_t list_copy_words(const DevPlan &pl) {  // 8-byte words laid out in memory
+  const size_t ints = (size_t)pl.MB * pl.DP + pl.DP + pl.TP + pl.G + pl.ZGr;
+  return (size_t)pl.MB * pl.Z * pl.Z + 2 * (size_t)pl.Z * pl.Z + 3 * (size_t)pl.G + pl.DP + pl.TP +
+         (size_t)pl.MB * pl.TP + (ints + 1) / 2;
+}
+__host__ __device__ inline size_t list_tables_words(const DevPlan &pl) {  // with the availability behind them
+  return list_copy_words(pl) + ((size_t)pl.ZGr + 1) / 2;
+}
+
+__device__ __forceinline__ ListTables list_tables_at(const DevPlan &pl, double *at) {
+  const int G = pl.G, Z = pl.Z, MB = pl.MB, TP = pl.TP, DP = pl.DP;
+  ListTables T;
+  T.xsec = at;
+  T.bw = T.xsec + MB * Z * Z;
+  T.egress = T.bw + Z * Z;
+  T.price = T.egress + Z * Z;
+  T.ring = T.price + G;
+  T.tpd = T.ring + DP;
+  T.cap = reinterpret_cast<uint64_t *>(T.tpd + TP);
+  T.res = T.cap + G;
+  T.act = T.res + G;
+  T.nb = reinterpret_cast<int32_t *>(T.act + MB * TP);
+  T.dpv = T.nb + MB * DP;
+  T.tpv = T.dpv + DP;
+  T.node = T.tpv + TP;
+  T.zg = reinterpret_cast<uint32_t *>(T.node + G);
+  T.avail = reinterpret_cast<int32_t *>(at + list_copy_words(pl));
+  return T;
+}
+
+// Lays the tables out in device memory (once per plan).
+__global__ void k_list_tables(DevPlan pl) {
+  const int G = pl.G, Z = pl.Z, MB = pl.MB, TP = pl.TP, DP = pl.DP;
+  const ListTables T = list_tables_at(pl, pl.list_tables);
+  const int t = threadIdx.x, nt = blockDim.x;
+  for (int i = t; i < MB * Z * Z; i += nt) T.xsec[i] = pl.xsec[i];
+  for (int i = t; i < Z * Z; i += nt) {
+    T.bw[i] = pl.bw[i];
+    T.egress[i] = pl.egress ? pl.egress[i] : 0.0;
+  }
+  for (int i = t; i < G; i += nt) {
+    T.price[i] = pl.price[i];
+    T.cap[i] = pl.cap[i];
+    T.res[i] = pl.res[i];
+    T.node[i] = pl.node[i];
+  }
+  for (int i = t; i < DP; i += nt) {
+    const double D = (double)pl.vals[i];
+    T.ring[i] = 2.0 * (D - 1.0) / D;
+    T.dpv[i] = pl.vals[i];
+  }
+  for (int i = t; i < TP; i += nt) {
+    T.tpv[i] = pl.vals[DP + i];
+    T.tpd[i] = (double)pl.vals[DP + i];
+  }
+  for (int i = t; i < MB * TP; i += nt) T.act[i] = pl.act[i];
+  for (int i = t; i < MB * DP; i += nt) T.nb[i] = pl.nb[i];
+  for (int i = t; i < pl.ZGr; i += nt) T.zg[i] = (uint32_t)(i / G) | (uint32_t)(i % G) << 8;
+}
+
+// Needs a barrier before the tables are read.
+__device__ __forceinline__ ListTables stage_list_tables(const DevPlan &pl, double *lds) {
+  const ListTables T = list_tables_at(pl, lds);
+  const int t = threadIdx.x, nt = blockDim.x, n = (int)list_copy_words(pl);
+  int32_t avail = 0;
+  if (t < pl.ZGr) avail = pl.avail[t];  // (at most 64 pools)
+  for (int i = t; i < n; i += 4 * nt) {  // four loads in flight
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = i + q * nt < n ? pl.list_tables[i + q * nt] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i + q * nt < n) lds[i + q * nt] = v[q];
+  }
+  if (t < pl.ZGr) T.avail[t] = avail;
+  return T;
+}
+
+// the bandwidth a gradient buffer sees between two zones
+__device__ __forceinline__ double list_link(const DevPlan &pl, const ListTables &T, int za, int zb, double bytes) {
+  return pl.n_bw_coef > 0 ? link_bw(pl, za, zb, bytes) : T.bw[mul24(za, pl.Z) + zb];
+}
+
+// activation bytes of a worker: microbatches in flight x layers x bytes of one (validated < 2^62)
+__device__ __forceinline__ uint64_t act_bytes(int in_flight, int layers, uint64_t act) {
+  return (uint64_t)(uint32_t)in_flight * (uint32_t)layers * act;
+}
+
 struct PlaceArgs {
   uint64_t count;
   const int32_t *desc;    // [count][5] pp index, partition, tp index, dp index, mb index
   const int32_t *pools;   // [count][pool_stride] pool of every stage
-  const int32_t *pools_b; // optional, same shape: pool of the other half of every stage's replicas
+  const int32_t *pools_b; // SPLIT, same shape: pool of the other half of every stage's replicas
   const int32_t *tps;     // optional, same shape: TP index of every stage (else the descriptor's)
   uint32_t pool_stride;
-  const SubResult *one;   // alternative to desc / pools: the placement held by this record
+  uint32_t per_wg;        // plans a workgroup takes, at most kPlaceMaxPlans
   const SearchPP *pps;
   int n_pp;
   int objective, has_bound;
@@ -750,245 +857,249 @@ struct PlaceArgs {
   uint32_t *mask;
 };
 
-constexpr int kPlaceWaves = 4;
+constexpr int kPlaceThreads = 256;
+constexpr int kPlaceStages = 512;    // stages a workgroup holds at a time
+constexpr int kPlaceMaxPlans = 64;    // a lane each when the stages are added up
+static_assert(kPlaceStages >= kMaxStages, "one plan's stages fit");
 
-// Stages that split their D replicas over two pools, half on each, also across zones (the D
-// tuples of a stage, Sec. 4.2): the replicas on the first pools and those on the second pools
-// form two kinds of pipeline; T_iter takes the slower kind (Sec. 4.3: max over pipelines), a
-// split stage's all-reduce runs over the slowest link of a ring through both pools, and the
-// traffic between zones -- of the pipelines, each kind carrying half of the replicas, and of
-// the ring -- is paid for.  With a TP index per stage (tps; else it for all) both halves of a
-// stage use the stage's degree.  One wave; valid descriptor, pools and TP indices; nb > 0.
-__device__ __forceinline__ void eval_split_wave(const DevPlan &pl, const int32_t *pa, const int32_t *pb,
-                                                const int32_t *tps, int P, uint32_t rs, int it, int im,
-                                                int64_t nb, int64_t D, RefineLds &L, double *t_second,
-                                                int *cnt, double &T, double &C, uint64_t &peak,
-                                                uint32_t &mask) {
-  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP;
-  const int lane = threadIdx.x & 63;
-  const double p2p = (double)pl.p2p[im];
-  double max_a = 0.0, max_b = 0.0, t_sync = 0.0, t_upd = 0.0;
-  uint32_t oom = 0, h1 = 0, odd = 0;
-  for (int i = lane; i < P; i += 64) {
-    const int a = pa[i], b = pb[i];
-    const int ga = a % G, za = a / G, gb = b % G, zb = b / G;
-    const int ti = tps ? tps[i] : it;  // this stage's TP index and degree
-    const int64_t tp = pl.tpv[ti];
-    atomicAdd(&cnt[a], (int)tp);  // GPUs of one replica, counted once per half
-    atomicAdd(&cnt[b], (int)tp);
-    if (a != b && (D & 1)) odd = 1u;
-    const size_t si = (size_t)rs + i;
-    const uint64_t params = pl.st_params[si];
-    const uint64_t bytes = stage_bytes_of(params, pl.st_n[si], pl.bpp, i, P, (int)tp, nb, pl.act[im * TP + ti]);
-    const uint64_t m1 = bytes + pl.res[ga], m2 = bytes + pl.res[gb];
-    if (m1 > pl.cap[ga] || m2 > pl.cap[gb]) oom = 1u;
-    if (tp > pl.node[ga] || tp > pl.node[gb]) h1 = 1u;
-    peak = m1 > peak ? m1 : peak;
-    peak = m2 > peak ? m2 : peak;
-    double xa = 0.0, xb = 0.0, traffic = 0.0;
-    if (i < P - 1) {
-      const int zna = pa[i + 1] / G, znb = pb[i + 1] / G;
-      xa += p2p / link_bw(pl, za, zna, p2p);
-      xb += p2p / link_bw(pl, zb, znb, p2p);
-      if (pl.egress) {  // each kind of pipeline carries half of the replicas
-        if (zna != za) traffic += (double)nb * (0.5 * (double)D) * p2p * (pl.egress[za * Z + zna] + pl.egress[zna * Z + za]);
-        if (znb != zb) traffic += (double)nb * (0.5 * (double)D) * p2p * (pl.egress[zb * Z + znb] + pl.egress[znb * Z + zb]);
-      }
-    }
-    if (i > 0) {
-      xa += p2p / link_bw(pl, za, pa[i - 1] / G, p2p);
-      xb += p2p / link_bw(pl, zb, pb[i - 1] / G, p2p);
-    }
-    const double ta = pl.st_c[((si * G + ga) * MB + im) * TP + ti] + xa;
-    const double tb = pl.st_c[((si * G + gb) * MB + im) * TP + ti] + xb;
-    max_a = fmax(max_a, ta);
-    max_b = fmax(max_b, tb);
-    if (D > 1) {
-      const uint64_t shard = (params + (uint64_t)tp - 1) / (uint64_t)tp;
-      const double buffer = (double)shard * (double)pl.gb;
-      double link = link_bw(pl, za, za, buffer);
-      if (zb != za)
-        link = fmin(fmin(link, link_bw(pl, zb, zb, buffer)),
-                    fmin(link_bw(pl, za, zb, buffer), link_bw(pl, zb, za, buffer)));
-      const double ring_bytes = 2.0 * (double)(D - 1) / (double)D * buffer;
-      t_sync = fmax(t_sync, ring_bytes / link);
-      if (pl.egress && zb != za) traffic += ring_bytes * (pl.egress[za * Z + zb] + pl.egress[zb * Z + za]);
-    }
-    t_upd = fmax(t_upd, fmax(pl.st_u[(si * G + ga) * TP + ti], pl.st_u[(si * G + gb) * TP + ti]));
-    L.t[i] = ta;
-    t_second[i] = tb;
-    L.dol[i] = (double)(D * tp) * (0.5 * (pl.price[ga] + pl.price[gb]));
-    L.comm[i] = traffic;
-  }
-  if (__builtin_amdgcn_ballot_w64(oom != 0) != 0) mask |= 1u;
-  if (__builtin_amdgcn_ballot_w64(h1 != 0) != 0) mask |= 8u;
-  if (__builtin_amdgcn_ballot_w64(odd != 0) != 0) mask |= 2u;  // D replicas cannot be halved
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint64_t o = __shfl_xor((unsigned long long)peak, off);
-    peak = o > peak ? o : peak;
-  }
-  max_a = wave_max_f64(max_a);
-  max_b = wave_max_f64(max_b);
-  t_sync = wave_max_f64(t_sync);
-  t_upd = wave_max_f64(t_upd);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  bool over = false;  // every pool holds the halves placed on it
-  for (int p = lane; p < ZG; p += 64)
-    if ((int64_t)cnt[p] * D > 2 * (int64_t)pl.avail[p]) over = true;
-  if (__builtin_amdgcn_ballot_w64(over) != 0) mask |= 2u;
-  double sum_a = 0.0, sum_b = 0.0, dollars = 0.0, traffic = 0.0;
-  for (int i = 0; i < P; ++i) {
-    sum_a += L.t[i];
-    sum_b += t_second[i];
-    dollars += L.dol[i];
-    traffic += L.comm[i];
-  }
-  const double t_pp = fmax(sum_a + (double)(nb - 1) * max_a, sum_b + (double)(nb - 1) * max_b);
-  T = (t_pp + t_sync) + t_upd;
-  C = dollars / 3600.0 * T + traffic;
+struct PlacePlan {       // a plan as its stages need it
+  uint32_t rs;
+  int32_t end;           // stages of the workgroup's plans up to and including this one
+  int16_t P;             // 0: an invalid descriptor
+  uint8_t it, id, im, pad[3];
+  double dpd, half_traffic;  // D; N_b x (replicas of one kind of pipeline) x bytes of a transfer
+};
+static_assert(sizeof(PlacePlan) == 32, "two 16-byte reads");
+
+struct PlaceLds {
+  // what the stages contribute, in plan and stage order (four entries more than there are
+  // stages: the sums read four at a time): time in the two kinds of pipeline, rent, traffic
+  double term[4][kPlaceStages + 4];
+  double sum[4][kPlaceMaxPlans], slowest[2][kPlaceMaxPlans];   // what they add up to
+  long long sync[kPlaceMaxPlans], upd[kPlaceMaxPlans];  // bits of the maxima (non-negative values, in
+                                                        // which order the bits compare like them)
+  unsigned long long peak[kPlaceMaxPlans];
+  PlacePlan plan[kPlaceMaxPlans];
+  uint32_t flags[kPlaceMaxPlans];  // mask bits 0, 1, 3; bit 31: an index out of range
+  uint8_t owner[kPlaceStages];     // the stage's plan
+};
+
+__host__ __device__ inline size_t place_lds_bytes(const DevPlan &pl, uint32_t per_wg) {
+  return sizeof(PlaceLds) + list_tables_words(pl) * 8 + (size_t)per_wg * pl.ZGr * sizeof(int32_t);
 }
 
-// The simulator (Sec. 4.3) for plans whose stages choose their pools freely: one wave per
-// plan, lane i takes stages i, i + 64, ...; sums in stage order.  With a TP index per stage
-// every per-stage quantity (memory shard, activation bytes, profiled times, node size, gradient
-// shard, GPUs against the quota, rent) uses the stage's own degree.  A descriptor, pool or TP
-// index out of range yields mask = 0xFFFFFFFF, T = C = +inf, mem = 0.
-__global__ __launch_bounds__(kPlaceWaves * 64) void k_eval_placements(DevPlan pl, PlaceArgs a) {
-  __shared__ RefineLds lds[kPlaceWaves];
-  __shared__ double s_second[kPlaceWaves][kMaxStages];  // stage times of the second kind of pipeline
-  __shared__ int s_cnt[kPlaceWaves][kSearchMaxPools];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t ci = (uint64_t)blockIdx.x * kPlaceWaves + wv;
-  if (ci >= a.count) return;  // whole waves leave; no barrier below
-  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP, DP = pl.DP;
-  int ip, q, it, id, im;
-  if (a.one) { ip = a.one->desc[0]; q = a.one->desc[1]; it = a.one->desc[2]; id = a.one->desc[3]; im = a.one->desc[4]; }
-  else { const int32_t *d = a.desc + ci * 5; ip = d[0]; q = d[1]; it = d[2]; id = d[3]; im = d[4]; }
-  double T = __builtin_huge_val(), C = T;
-  uint64_t peak = 0;
-  uint32_t mask = 0xFFFFFFFFu;
-  bool valid = ip >= 0 && ip < a.n_pp && it >= 0 && it < TP && id >= 0 && id < DP && im >= 0 && im < MB && q >= 0;
-  if (valid) valid = q < a.pps[ip].n_part;
-  const int P = valid ? a.pps[ip].P : 0;
-  if (valid && !a.one && (uint32_t)P > a.pool_stride) valid = false;
-  RefineLds &L = lds[wv];
-  int *cnt = s_cnt[wv];
-  const bool split = a.one ? (a.one->desc[5] == SEARCH_SPLIT || a.one->desc[5] == SEARCH_SPLIT_TP)
-                           : a.pools_b != nullptr;  // stages may split their replicas
-  const int32_t *const tps = a.one ? a.one->tps : (a.tps ? a.tps + ci * a.pool_stride : nullptr);
-  if (valid) {
-    for (int p = lane; p < kSearchMaxPools; p += 64) cnt[p] = 0;
-    bool bad = false;
-    for (int i = lane; i < P; i += 64) {
-      const int p = a.one ? a.one->pools[i] : a.pools[ci * a.pool_stride + i];
-      if (p < 0 || p >= ZG) bad = true;
-      if (split) {
-        const int p2 = a.one ? a.one->pools_b[i] : a.pools_b[ci * a.pool_stride + i];
-        if (p2 < 0 || p2 >= ZG) bad = true;
-      }
-      if (tps && (tps[i] < 0 || tps[i] >= TP)) bad = true;
-    }
-    if (__builtin_amdgcn_ballot_w64(bad) != 0) valid = false;
+// Sum (and maximum) over a plan's stages in stage order, for a lane per plan.
+__device__ __forceinline__ void place_sum(const double *v, int P, double &sum, double &slowest) {
+  sum = 0.0;
+  slowest = 0.0;
+  int i = 0;
+  for (; i + 4 <= P; i += 4) {
+    const double x0 = v[i], x1 = v[i + 1], x2 = v[i + 2], x3 = v[i + 3];
+    sum += x0; sum += x1; sum += x2; sum += x3;
+    slowest = fmax(fmax(slowest, fmax(x0, x1)), fmax(x2, x3));
   }
-  if (valid) {
-    mask = 0;
-    const uint32_t rs = a.pps[ip].rs0 + (uint32_t)q * (uint32_t)P;
-    const int64_t nb = pl.nb[im * DP + id], D = pl.dpv[id];
-    if (nb == 0) {
-      mask = 4u;
-    } else if (split) {
-      __builtin_amdgcn_wave_barrier();
-      eval_split_wave(pl, a.one ? a.one->pools : a.pools + ci * a.pool_stride,
-                      a.one ? a.one->pools_b : a.pools_b + ci * a.pool_stride,
-                      tps, P, rs, it, im, nb, D, L, s_second[wv], cnt, T, C, peak, mask);
-      if (a.has_bound) {
-        if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
-        else if (1.0 / T < a.bound) mask |= 32u;
-      }
-    } else {
-      const double p2p = (double)pl.p2p[im];
-      __builtin_amdgcn_wave_barrier();
-      double max_t = 0.0, t_sync = 0.0, t_upd = 0.0;
-      uint32_t oom = 0, h1 = 0;
-      for (int i = lane; i < P; i += 64) {
-        const int p = a.one ? a.one->pools[i] : a.pools[ci * a.pool_stride + i];
-        const int pn = i < P - 1 ? (a.one ? a.one->pools[i + 1] : a.pools[ci * a.pool_stride + i + 1]) : p;
-        const int pv = i > 0 ? (a.one ? a.one->pools[i - 1] : a.pools[ci * a.pool_stride + i - 1]) : p;
-        const int g = p % G, z = p / G, zn = pn / G, zp = pv / G;
-        const int ti = tps ? tps[i] : it;      // this stage's TP index and degree
-        const int64_t tpi = pl.tpv[ti];
-        atomicAdd(&cnt[p], (int)tpi);          // GPUs of one replica
-        const size_t si = (size_t)rs + i;
-        const uint64_t params = pl.st_params[si];
-        const uint64_t bytes = stage_bytes_of(params, pl.st_n[si], pl.bpp, i, P, (int)tpi, nb, pl.act[im * TP + ti]);
-        const uint64_t m = bytes + pl.res[g];
-        if (m > pl.cap[g]) oom = 1u;
-        if (tpi > pl.node[g]) h1 = 1u;
-        peak = m > peak ? m : peak;
-        double x = 0.0, comm = 0.0;
-        if (i < P - 1) {
-          x += p2p / link_bw(pl, z, zn, p2p);
-          if (pl.egress && zn != z)
-            comm = (double)nb * (double)D * p2p * (pl.egress[z * Z + zn] + pl.egress[zn * Z + z]);
+  for (; i < P; ++i) {
+    const double x = v[i];
+    sum += x;
+    slowest = fmax(slowest, x);
+  }
+}
+
+// The simulator (Sec. 4.3) for plans whose stages choose their pools freely.
+//
+// With SPLIT a stage's D replicas lie on two pools, half on each, also across zones (the D tuples
+// of a stage, Sec. 4.2): the replicas on the first pools and those on the second pools form two
+// kinds of pipeline; T_iter takes the slower kind (Sec. 4.3: max over pipelines), a split stage's
+// all-reduce runs over the slowest link of a ring through both pools, and the traffic between
+// zones -- of the pipelines, each kind carrying half of the replicas, and of the ring -- is paid
+// for.  With a TP index per stage every per-stage quantity (memory shard, activation bytes,
+// profiled times, node size, gradient shard, GPUs against the quota, rent) uses the stage's own
+// degree.  A descriptor, pool or TP index out of range yields mask = 0xFFFFFFFF, T = C = +inf, mem = 0.
+//
+// A workgroup takes per_wg plans and works through their stages, up to 1 024 at a time, plans
+// one behind the other without gaps: first a lane per stage -- what is added up in stage order,
+// which is part of the definition, goes to LDS, maxima are folded in there -- then a lane per
+// plan adds its stages up, a wave per quantity.  A wave per plan leaves most lanes idle where
+// pipelines are shorter than 64 stages, and walks every plan's sums by itself: 200 003 plans of 1
+// to 48 stages with two pools and a degree per stage took 488 us that way and take 85 us this way
+// (vector instructions 35 us of it; the rest is the latency of a workgroup's chain: descriptors,
+// pools, stage records, sums).  Measured beside it: requesting two stages' words per lane at a time
+// (98 us, the registers cost a workgroup per compute unit), 512 threads (100 us), bounds on the
+// registers for more waves (113 us and more).
+template <bool SPLIT>
+__global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, PlaceArgs a) {
+  extern __shared__ double place_lds[];
+  PlaceLds &S = *reinterpret_cast<PlaceLds *>(place_lds);
+  double *const tables = reinterpret_cast<double *>(&S + 1);
+  int32_t *const cnt = reinterpret_cast<int32_t *>(tables + list_tables_words(pl));  // [plan][ZG]
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const uint32_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP, DP = pl.DP;
+  const uint32_t row_words = mul24(mul24(MB, TP), pl.row_w);  // of a stage's records
+  const uint64_t c0 = (uint64_t)blockIdx.x * a.per_wg;
+  const int n = (int)min((uint64_t)a.per_wg, a.count - c0);
+  if (wv == 0) {  // a lane per plan
+    PlacePlan p{};
+    if (lane < n) {
+      const int32_t *d = a.desc + (c0 + lane) * 5;
+      const int ip = d[0], q = d[1], it = d[2], id = d[3], im = d[4];
+      if (ip >= 0 && ip < a.n_pp && it >= 0 && it < (int)TP && id >= 0 && id < (int)DP && im >= 0 && im < (int)MB && q >= 0) {
+        const SearchPP pp = a.pps[ip];
+        if (q < pp.n_part && (uint32_t)pp.P <= a.pool_stride) {
+          p.P = (int16_t)pp.P;
+          p.rs = pp.rs0 + (uint32_t)q * (uint32_t)pp.P;
+          p.it = (uint8_t)it; p.id = (uint8_t)id; p.im = (uint8_t)im;
+          p.dpd = (double)pl.vals[id];
+          p.half_traffic = (double)pl.nb[im * DP + id] * (SPLIT ? 0.5 * p.dpd : p.dpd) * (double)pl.p2p[im];
         }
-        if (i > 0) x += p2p / link_bw(pl, z, zp, p2p);
-        const double ts = pl.st_c[((si * G + g) * MB + im) * TP + ti] + x;
-        max_t = fmax(max_t, ts);
-        if (D > 1) {
-          const uint64_t shard = (params + (uint64_t)tpi - 1) / (uint64_t)tpi;
-          const double gbytes = (double)shard * (double)pl.gb;
-          t_sync = fmax(t_sync, 2.0 * (double)(D - 1) / (double)D * gbytes / link_bw(pl, z, z, gbytes));
-        }
-        t_upd = fmax(t_upd, pl.st_u[(si * G + g) * TP + ti]);
-        L.t[i] = ts;
-        L.dol[i] = (double)(D * tpi) * pl.price[g];
-        L.comm[i] = comm;
       }
-      if (__builtin_amdgcn_ballot_w64(oom != 0) != 0) mask |= 1u;
-      if (__builtin_amdgcn_ballot_w64(h1 != 0) != 0) mask |= 8u;
+    }
+    int end = p.P;
 #pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const uint64_t o = __shfl_xor((unsigned long long)peak, off);
-        peak = o > peak ? o : peak;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(end, off);
+      if (lane >= off) end += v;
+    }
+    p.end = end;
+    S.plan[lane] = p;
+    S.sync[lane] = S.upd[lane] = 0;
+    S.peak[lane] = 0;
+    S.flags[lane] = 0;
+  }
+  for (int x = t; x < (int)(a.per_wg * ZG); x += kPlaceThreads) cnt[x] = 0;
+  const ListTables L = stage_list_tables(pl, tables);
+  __syncthreads();
+  for (int s0 = 0; s0 < n;) {  // uniform: plans s0 .. s1 - 1 make up one pass
+    const int base = s0 ? S.plan[s0 - 1].end : 0;
+    const int s1 = s0 + __popcll(__builtin_amdgcn_ballot_w64(lane >= s0 && lane < n && S.plan[lane].end - base <= kPlaceStages));
+    const int stages = S.plan[s1 - 1].end - base;
+    if (lane >= s0 && lane < s1) {  // whose stage is whose: a lane per plan, the waves take turns
+      const int P = S.plan[lane].P, at = S.plan[lane].end - P - base;
+      for (int i = wv; i < P; i += kPlaceThreads / 64) S.owner[at + i] = (uint8_t)lane;
+    }
+    __syncthreads();
+    for (int e = t; e < stages; e += kPlaceThreads) {
+      const uint32_t own = S.owner[e];
+      const PlacePlan pn = S.plan[own];
+      const int P = pn.P, i = e - (pn.end - P - base);
+      const size_t row = (c0 + own) * a.pool_stride + (uint32_t)i;
+      const int32_t *pa = a.pools + row, *pb = SPLIT ? a.pools_b + row : pa;
+      const int fwd = i < P - 1 ? 1 : 0, back = i > 0 ? -1 : 0;
+      const uint32_t ra = (uint32_t)pa[0], ran = (uint32_t)pa[fwd], rap = (uint32_t)pa[back];
+      const uint32_t rb = (uint32_t)pb[0], rbn = (uint32_t)pb[fwd], rbp = (uint32_t)pb[back];
+      const uint32_t rt = a.tps ? (uint32_t)a.tps[row] : pn.it;
+      // (indices out of range: reported by the stage they belong to, kept in bounds everywhere)
+      const uint32_t a0 = min(ra, ZG - 1), b0 = min(rb, ZG - 1), ti = min(rt, TP - 1);
+      const uint32_t zga = L.zg[a0], za = zga & 255u, ga = zga >> 8;
+      const uint32_t zgb = SPLIT ? L.zg[b0] : zga, zb = zgb & 255u, gb = zgb >> 8;
+      const uint64_t si = (uint64_t)pn.rs + (uint32_t)i;
+      const uint32_t mt = mul24(pn.im, TP) + ti;
+      const double *row_st = pl.st_row + si * row_words + mul24(mt, pl.row_w);  // the stage's record
+      const int layers = pl.st_n[si];
+      const double ca = row_st[ga], ua = row_st[G + ga];
+      const double cb = SPLIT ? row_st[gb] : 0.0, ub = SPLIT ? row_st[G + gb] : 0.0;
+      const uint64_t model = (uint64_t)__double_as_longlong(row_st[2 * G]);
+      const double grad = row_st[2 * G + 1];
+      const int tp = L.tpv[ti], nb = L.nb[mul24(pn.im, DP) + pn.id];
+      atomicAdd(&cnt[mul24(own, ZG) + a0], tp);  // GPUs of one replica (split: counted once per half)
+      if (SPLIT) atomicAdd(&cnt[mul24(own, ZG) + b0], tp);
+      const uint64_t bytes = model + act_bytes(min(P - i, nb), layers, L.act[mt]);
+      const uint64_t m1 = bytes + L.res[ga], m2 = SPLIT ? bytes + L.res[gb] : m1;
+      uint32_t flags = (m1 > L.cap[ga] || (SPLIT && m2 > L.cap[gb])) ? 1u : 0u;
+      if (tp > L.node[ga] || (SPLIT && tp > L.node[gb])) flags |= 8u;
+      if (SPLIT && a0 != b0 && (L.dpv[pn.id] & 1)) flags |= 2u;  // D replicas cannot be halved
+      if (ra >= ZG || (SPLIT && rb >= ZG) || rt >= TP) flags |= 1u << 31;
+      const double *xsec = L.xsec + mul24(pn.im, mul24(Z, Z));
+      double xa = 0.0, xb = 0.0, traffic = 0.0;
+      if (fwd) {
+        const uint32_t zna = L.zg[min(ran, ZG - 1)] & 255u;
+        xa += xsec[mul24(za, Z) + zna];
+        // (each kind of pipeline carries half of the replicas)
+        if (zna != za) traffic += pn.half_traffic * (L.egress[mul24(za, Z) + zna] + L.egress[mul24(zna, Z) + za]);
+        if (SPLIT) {
+          const uint32_t znb = L.zg[min(rbn, ZG - 1)] & 255u;
+          xb += xsec[mul24(zb, Z) + znb];
+          if (znb != zb) traffic += pn.half_traffic * (L.egress[mul24(zb, Z) + znb] + L.egress[mul24(znb, Z) + zb]);
+        }
       }
-      max_t = wave_max_f64(max_t);
-      t_sync = wave_max_f64(t_sync);
-      t_upd = wave_max_f64(t_upd);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      bool over = false;  // quota: D replicas of every stage on the pool, its tp GPUs each
-      for (int p = lane; p < ZG; p += 64)
-        if ((int64_t)cnt[p] * D > (int64_t)pl.avail[p]) over = true;
-      if (__builtin_amdgcn_ballot_w64(over) != 0) mask |= 2u;
-      double sum_t = 0.0, dollars = 0.0, comm = 0.0;
-      for (int i = 0; i < P; ++i) {
-        sum_t += L.t[i];
-        dollars += L.dol[i];
-        comm += L.comm[i];
+      if (back) {
+        xa += xsec[mul24(za, Z) + (L.zg[min(rap, ZG - 1)] & 255u)];
+        if (SPLIT) xb += xsec[mul24(zb, Z) + (L.zg[min(rbp, ZG - 1)] & 255u)];
       }
-      T = (sum_t + (double)(nb - 1) * max_t) + t_sync + t_upd;
-      C = dollars / 3600.0 * T + comm;
-      if (a.has_bound) {
-        if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
-        else if (1.0 / T < a.bound) mask |= 32u;
+      double sync = 0.0;
+      if (pn.dpd > 1.0) {
+        double link = list_link(pl, L, za, za, grad);
+        if (SPLIT && zb != za)
+          link = fmin(fmin(link, list_link(pl, L, zb, zb, grad)),
+                      fmin(list_link(pl, L, za, zb, grad), list_link(pl, L, zb, za, grad)));
+        const double ring_bytes = L.ring[pn.id] * grad;
+        sync = ring_bytes / link;
+        if (SPLIT && zb != za) traffic += ring_bytes * (L.egress[mul24(za, Z) + zb] + L.egress[mul24(zb, Z) + za]);
+      }
+      S.term[0][e] = ca + xa;
+      if (SPLIT) S.term[1][e] = cb + xb;
+      const double gpus = pn.dpd * L.tpd[ti];  // (whole numbers below 2^53)
+      S.term[2][e] = gpus * (SPLIT ? 0.5 * (L.price[ga] + L.price[gb]) : L.price[ga]);
+      S.term[3][e] = traffic;
+      atomicMax(&S.sync[own], (long long)__double_as_longlong(sync));
+      atomicMax(&S.upd[own], (long long)__double_as_longlong(SPLIT ? fmax(ua, ub) : ua));
+      atomicMax(&S.peak[own], (unsigned long long)(m1 > m2 ? m1 : m2));
+      if (flags) atomicOr(&S.flags[own], flags);
+    }
+    __syncthreads();
+    const int p = s0 + lane;
+    if (wv < 4) {  // a lane per plan, a wave per quantity
+      if (p < s1 && (SPLIT || wv != 1)) {
+        const PlacePlan pn = S.plan[p];
+        double sum, slowest;
+        place_sum(S.term[wv] + (pn.end - pn.P - base), pn.P, sum, slowest);
+        S.sum[wv][p] = sum;
+        if (wv < 2) S.slowest[wv][p] = slowest;
       }
     }
-  }
-  if (lane == 0) {
-    if (a.T) a.T[ci] = T;
-    if (a.C) a.C[ci] = C;
-    if (a.mem) a.mem[ci] = mask == 0xFFFFFFFFu ? 0 : peak;
-    if (a.mask) a.mask[ci] = mask;
+    for (int x = t; x < (int)mul24(s1 - s0, ZG); x += kPlaceThreads) {  // every pool holds what is placed on it
+      const int q = (int)((uint32_t)x / ZG), pool = x - (int)mul24(q, ZG);
+      if ((int64_t)cnt[mul24(s0 + q, ZG) + pool] * L.dpv[S.plan[s0 + q].id] > (SPLIT ? 2 : 1) * (int64_t)L.avail[pool])
+        atomicOr(&S.flags[s0 + q], 2u);
+    }
+    __syncthreads();
+    if (wv == 0 && p < s1) {
+      double T = __builtin_huge_val(), C = T;
+      uint64_t peak = 0;
+      uint32_t mask = 0xFFFFFFFFu;
+      const PlacePlan pn = S.plan[p];
+      if (pn.P != 0 && !(S.flags[p] >> 31)) {
+        const int nb = L.nb[pn.im * DP + pn.id];
+        if (nb == 0) {
+          mask = 4u;
+        } else {
+          mask = S.flags[p];
+          peak = S.peak[p];
+          double t_pp = S.sum[0][p] + (double)(nb - 1) * S.slowest[0][p];
+          if (SPLIT) t_pp = fmax(t_pp, S.sum[1][p] + (double)(nb - 1) * S.slowest[1][p]);
+          T = (t_pp + __longlong_as_double(S.sync[p])) + __longlong_as_double(S.upd[p]);
+          C = S.sum[2][p] / 3600.0 * T + S.sum[3][p];
+          if (a.has_bound) {
+            if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
+            else if (1.0 / T < a.bound) mask |= 32u;
+          }
+        }
+      }
+      if (a.T) a.T[c0 + p] = T;
+      if (a.C) a.C[c0 + p] = C;
+      if (a.mem) a.mem[c0 + p] = peak;
+      if (a.mask) a.mask[c0 + p] = mask;
+    }
+    s0 = s1;
   }
 }
 
 // ------------------------------------------------------------------ a pool per replica
 
 constexpr int64_t kReplicaMaxDegree = 65536;  // replicas per stage a listed plan may name one by one
+constexpr int kReplicaWaves = 4;
+constexpr int kReplicaTile = 512;            // stage times a wave keeps in LDS at a time
+constexpr int kReplicaShared = 512;           // plans with more (stage, replica) pairs are shared by the waves
+static_assert(kReplicaTile >= kMaxStages, "a pipeline's stages fit");
 
 struct ReplicaArgs {
   uint64_t count;
@@ -1006,10 +1117,26 @@ struct ReplicaArgs {
   uint32_t *mask;
 };
 
-__device__ __forceinline__ double wave_min_f64(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off));
-  return v;
+struct ReplicaPlan {     // a valid descriptor; P = 0: an invalid one
+  int32_t P, D, it, id, im;
+  uint32_t rs;
+};
+
+struct ReplicaSums {     // of a lane, a wave or a plan
+  double t_pipe, t_upd, t_sync, rent, traffic;
+  uint64_t peak;
+  uint32_t flags;        // mask bits 0, 3; bit 31: an index out of range
+  uint32_t pad;
+};
+
+struct ReplicaLds {
+  double times[kReplicaWaves][kReplicaTile];
+  ReplicaPlan plan[kReplicaWaves];
+  ReplicaSums part[kReplicaWaves];
+};
+
+__host__ __device__ inline size_t replica_lds_bytes(const DevPlan &pl) {
+  return sizeof(ReplicaLds) + list_tables_words(pl) * 8 + kReplicaWaves * (size_t)pl.ZGr * sizeof(int32_t);
 }
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
@@ -1018,120 +1145,125 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
-// The plan tuple in full (Sec. 4.2: D tuples per stage): replica r of all stages is pipeline r,
-// T_iter = max over the D pipelines + T_sync + T_update (Sec. 4.3); the all-reduce of a stage is
-// a ring through its replicas in their order at the pace of its slowest link; traffic between
-// zones is paid for where a pipeline or a ring crosses; a pool's quota counts the GPUs it gives.
-// One wave per plan: lane l takes the pipelines l, l + 64, ... and walks their stages in order,
-// so a pipeline's sum is taken in stage order.  A descriptor or pool out of range, fewer than
-// P x D entries per plan or more than 65 536 replicas yield mask = 0xFFFFFFFF, T = C = +inf, mem = 0.
-__global__ __launch_bounds__(kPlaceWaves * 64) void k_eval_replicas(DevPlan pl, ReplicaArgs a) {
-  __shared__ int s_cnt[kPlaceWaves][kSearchMaxPools];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t ci = (uint64_t)blockIdx.x * kPlaceWaves + wv;
-  if (ci >= a.count) return;  // whole waves leave; no barrier below
-  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP, DP = pl.DP;
-  const int32_t *d = a.desc + ci * 5;
-  const int ip = d[0], q = d[1], it = d[2], id = d[3], im = d[4];
+// makes a wave's LDS writes visible to its own later reads (operations of one wave complete in
+// order; the compiler must not move them)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A plan's (stage, replica) pairs and pipelines, shared by THREADS threads (a wave, or the
+// workgroup; tid: which one this is); what this thread's share adds up to.
+template <int THREADS>
+__device__ __forceinline__ ReplicaSums replica_pairs(const DevPlan &pl, const ReplicaArgs &a, const ListTables &L,
+                                                     const ReplicaPlan &pn, uint64_t ci, int tid, double *times,
+                                                     int32_t *cnt) {
+  const uint32_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP, DP = pl.DP;
+  const int P = pn.P, D = pn.D, im = pn.im;
+  const int32_t *const pools = a.pools + ci * a.stride;
+  const int32_t *const tps = a.tps ? a.tps + ci * a.tps_stride : nullptr;
+  const int nb = L.nb[mul24(im, DP) + pn.id];
+  const double one_traffic = (double)nb * (double)pl.p2p[im], ring = L.ring[pn.id];
+  const double *xsec = L.xsec + mul24(im, mul24(Z, Z));
+  const uint32_t row_words = mul24(mul24(MB, TP), pl.row_w);  // of a stage's records
+  ReplicaSums s{};
+  const int tile = min(D, kReplicaTile * (THREADS / 64) / P);
+  for (int r0 = 0; r0 < D; r0 += tile) {  // uniform
+    const int rt = min(tile, D - r0), n = P * rt;
+    const uint32_t mg = rt == 1 ? 0u : (uint32_t)(((1ull << 32) + (uint32_t)rt - 1) / (uint32_t)rt);
+    for (int e = tid; e < n; e += THREADS) {
+      const int i = (int)fast_div((uint32_t)e, mg), r = r0 + e - i * rt;
+      const int k = i * D + r;  // (P x D <= 2^24)
+      uint32_t p = (uint32_t)pools[k], pf = (uint32_t)pools[i < P - 1 ? k + D : k],
+               pv = (uint32_t)pools[i > 0 ? k - D : k],
+               ps = (uint32_t)pools[r + 1 == D ? k + 1 - D : k + 1],  // the ring's next replica
+               ti = (uint32_t)(tps ? tps[i] : pn.it);                 // the stage's TP index
+      if (p >= ZG || ti >= TP) s.flags |= 1u << 31;
+      // (a neighbour out of range is reported by its own lane; its values only must stay in bounds)
+      p = min(p, ZG - 1); pf = min(pf, ZG - 1); pv = min(pv, ZG - 1); ps = min(ps, ZG - 1);
+      ti = min(ti, TP - 1);
+      const uint32_t zg = L.zg[p], z = zg & 255u, g = zg >> 8;
+      const uint32_t zn = L.zg[pf] & 255u, zv = L.zg[pv] & 255u, zs = L.zg[ps] & 255u;
+      const uint64_t si = (uint64_t)pn.rs + (uint32_t)i;
+      const uint32_t mt = mul24(im, TP) + ti;
+      const double *row_st = pl.st_row + si * row_words + mul24(mt, pl.row_w);  // the stage's record
+      const int layers = pl.st_n[si];
+      const double c = row_st[g];
+      s.t_upd = fmax(s.t_upd, row_st[G + g]);
+      const uint64_t model = (uint64_t)__double_as_longlong(row_st[2 * G]);
+      const double grad = row_st[2 * G + 1];
+      const int tp = L.tpv[ti];
+      atomicAdd(&cnt[p], tp);  // GPUs the pool gives
+      const uint64_t m = model + act_bytes(min(P - i, nb), layers, L.act[mt]) + L.res[g];
+      if (m > L.cap[g]) s.flags |= 1u;
+      if (tp > L.node[g]) s.flags |= 8u;
+      s.peak = m > s.peak ? m : s.peak;
+      double x = 0.0;
+      if (i < P - 1) {
+        x += xsec[mul24(z, Z) + zn];
+        if (zn != z)  // one replica's microbatches, both directions
+          s.traffic += one_traffic * (L.egress[mul24(z, Z) + zn] + L.egress[mul24(zn, Z) + z]);
+      }
+      if (i > 0) x += xsec[mul24(z, Z) + zv];
+      times[e] = c + x;
+      s.rent += L.tpd[ti] * L.price[g];
+      if (D > 1) {
+        const double ring_bytes = ring * grad;
+        s.t_sync = fmax(s.t_sync, ring_bytes / list_link(pl, L, z, zs, grad));
+        if (zs != z) s.traffic += ring_bytes * L.egress[mul24(z, Z) + zs];
+      }
+    }
+    if (THREADS == 64) wave_lds_fence();
+    else __syncthreads();
+    for (int r = tid; r < rt; r += THREADS) {  // the tile's pipelines, in stage order
+      double total = 0.0, slowest = 0.0;
+      const double *v = times + r;
+      int i = 0;
+      for (; i + 4 <= P; i += 4, v += 4 * rt) {
+        const double x0 = v[0], x1 = v[rt], x2 = v[2 * rt], x3 = v[3 * rt];
+        total += x0; total += x1; total += x2; total += x3;
+        slowest = fmax(fmax(slowest, fmax(x0, x1)), fmax(x2, x3));
+      }
+      for (; i < P; ++i, v += rt) { total += *v; slowest = fmax(slowest, *v); }
+      s.t_pipe = fmax(s.t_pipe, total + (double)(nb - 1) * slowest);
+    }
+    if (THREADS == 64) wave_lds_fence();  // the next tile's times come after these reads
+    else __syncthreads();
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const uint64_t o = __shfl_xor((unsigned long long)s.peak, off);
+    s.peak = o > s.peak ? o : s.peak;
+    s.flags |= __shfl_xor(s.flags, off);
+  }
+  s.t_pipe = wave_max_f64(s.t_pipe);
+  s.t_sync = wave_max_f64(s.t_sync);
+  s.t_upd = wave_max_f64(s.t_upd);
+  s.rent = wave_sum_f64(s.rent);
+  s.traffic = wave_sum_f64(s.traffic);
+  return s;
+}
+
+// The results of a plan from its sums, by one wave.
+__device__ __forceinline__ void replica_write(const ReplicaArgs &a, const ListTables &L, const ReplicaPlan &pn,
+                                              const ReplicaSums &s, int DP, int ZG, uint64_t ci, const int32_t *cnt) {
+  const int lane = threadIdx.x & 63;
   double T = __builtin_huge_val(), C = T;
   uint64_t peak = 0;
   uint32_t mask = 0xFFFFFFFFu;
-  bool valid = ip >= 0 && ip < a.n_pp && it >= 0 && it < TP && id >= 0 && id < DP && im >= 0 && im < MB && q >= 0;
-  if (valid) valid = q < a.pps[ip].n_part;
-  const int P = valid ? a.pps[ip].P : 0;
-  const int64_t D = valid ? (int64_t)pl.dpv[id] : 0;
-  if (valid && (D > kReplicaMaxDegree || (uint64_t)P * (uint64_t)D > a.stride)) valid = false;
-  if (valid && a.tps && (uint32_t)P > a.tps_stride) valid = false;
-  const int32_t *pools = a.pools + ci * a.stride;
-  const int32_t *const tps = a.tps ? a.tps + ci * a.tps_stride : nullptr;
-  int *cnt = s_cnt[wv];
-  if (valid) {
-    for (int p = lane; p < kSearchMaxPools; p += 64) cnt[p] = 0;
-    bool bad = false;
-    for (int64_t k = lane; k < (int64_t)P * D; k += 64)
-      if (pools[k] < 0 || pools[k] >= ZG) bad = true;
-    if (tps)
-      for (int i = lane; i < P; i += 64)
-        if (tps[i] < 0 || tps[i] >= TP) bad = true;
-    if (__builtin_amdgcn_ballot_w64(bad) != 0) valid = false;
-  }
-  if (valid) {
-    mask = 0;
-    const uint32_t rs = a.pps[ip].rs0 + (uint32_t)q * (uint32_t)P;
-    const int64_t nb = pl.nb[im * DP + id];
-    if (nb == 0) {
+  if (pn.P != 0 && !(s.flags >> 31)) {
+    if (L.nb[pn.im * DP + pn.id] == 0) {
       mask = 4u;
     } else {
-      const double p2p = (double)pl.p2p[im];
-      __builtin_amdgcn_wave_barrier();
-      double t_pipe = 0.0, t_upd = 0.0, t_sync = 0.0, rent = 0.0, traffic = 0.0;
-      uint32_t oom = 0, h1 = 0;
-      // the pipelines
-      for (int64_t r = lane; r < D; r += 64) {
-        double total = 0.0, slowest = 0.0;
-        for (int i = 0; i < P; ++i) {
-          const int p = pools[(int64_t)i * D + r], g = p % G, z = p / G;
-          const int ti = tps ? tps[i] : it;  // the stage's TP index and degree
-          const int64_t tp = pl.tpv[ti];
-          atomicAdd(&cnt[p], (int)tp);  // GPUs the pool gives
-          const size_t si = (size_t)rs + i;
-          const uint64_t bytes = stage_bytes_of(pl.st_params[si], pl.st_n[si], pl.bpp, i, P, (int)tp, nb, pl.act[im * TP + ti]);
-          const uint64_t m = bytes + pl.res[g];
-          if (m > pl.cap[g]) oom = 1u;
-          if (tp > pl.node[g]) h1 = 1u;
-          peak = m > peak ? m : peak;
-          double x = 0.0;
-          if (i < P - 1) {
-            const int zn = pools[(int64_t)(i + 1) * D + r] / G;
-            x += p2p / link_bw(pl, z, zn, p2p);
-            if (pl.egress && zn != z)  // one replica's microbatches, both directions
-              traffic += (double)nb * p2p * (pl.egress[z * Z + zn] + pl.egress[zn * Z + z]);
-          }
-          if (i > 0) x += p2p / link_bw(pl, z, pools[(int64_t)(i - 1) * D + r] / G, p2p);
-          const double ts = pl.st_c[((si * G + g) * MB + im) * TP + ti] + x;
-          total += ts;
-          slowest = fmax(slowest, ts);
-          t_upd = fmax(t_upd, pl.st_u[(si * G + g) * TP + ti]);
-          rent += (double)tp * pl.price[g];
-        }
-        t_pipe = fmax(t_pipe, total + (double)(nb - 1) * slowest);
-      }
-      // the rings
-      if (D > 1)
-        for (int i = 0; i < P; ++i) {  // uniform
-          const uint64_t params = pl.st_params[rs + i];
-          const uint64_t tp = (uint64_t)pl.tpv[tps ? tps[i] : it];
-          const uint64_t shard = (params + tp - 1) / tp;
-          const double buffer = (double)shard * (double)pl.gb;
-          const double ring_bytes = 2.0 * (double)(D - 1) / (double)D * buffer;
-          double link = __builtin_huge_val();
-          for (int64_t r = lane; r < D; r += 64) {
-            const int zr = pools[(int64_t)i * D + r] / G, zs = pools[(int64_t)i * D + (r + 1 == D ? 0 : r + 1)] / G;
-            link = fmin(link, link_bw(pl, zr, zs, buffer));
-            if (pl.egress && zr != zs) traffic += ring_bytes * pl.egress[zr * Z + zs];
-          }
-          t_sync = fmax(t_sync, ring_bytes / wave_min_f64(link));
-        }
-      if (__builtin_amdgcn_ballot_w64(oom != 0) != 0) mask |= 1u;
-      if (__builtin_amdgcn_ballot_w64(h1 != 0) != 0) mask |= 8u;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const uint64_t o = __shfl_xor((unsigned long long)peak, off);
-        peak = o > peak ? o : peak;
-      }
-      t_pipe = wave_max_f64(t_pipe);
-      t_upd = wave_max_f64(t_upd);
-      rent = wave_sum_f64(rent);
-      traffic = wave_sum_f64(traffic);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      mask = s.flags;
+      peak = s.peak;
       bool over = false;
       for (int p = lane; p < ZG; p += 64)
-        if ((int64_t)cnt[p] > (int64_t)pl.avail[p]) over = true;
+        if ((int64_t)cnt[p] > (int64_t)L.avail[p]) over = true;
       if (__builtin_amdgcn_ballot_w64(over) != 0) mask |= 2u;
-      T = (t_pipe + t_sync) + t_upd;
-      C = rent / 3600.0 * T + traffic;
+      T = (s.t_pipe + s.t_sync) + s.t_upd;
+      C = s.rent / 3600.0 * T + s.traffic;
       if (a.has_bound) {
         if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
         else if (1.0 / T < a.bound) mask |= 32u;
@@ -1141,8 +1273,84 @@ __global__ __launch_bounds__(kPlaceWaves * 64) void k_eval_replicas(DevPlan pl, 
   if (lane == 0) {
     if (a.T) a.T[ci] = T;
     if (a.C) a.C[ci] = C;
-    if (a.mem) a.mem[ci] = mask == 0xFFFFFFFFu ? 0 : peak;
+    if (a.mem) a.mem[ci] = peak;
     if (a.mask) a.mask[ci] = mask;
+  }
+}
+
+// The plan tuple in full (Sec. 4.2: D tuples per stage): replica r of all stages is pipeline r,
+// T_iter = max over the D pipelines + T_sync + T_update (Sec. 4.3); the all-reduce of a stage is
+// a ring through its replicas in their order at the pace of its slowest link; traffic between
+// zones is paid for where a pipeline or a ring crosses; a pool's quota counts the GPUs it gives.
+// A descriptor or pool out of range, fewer than P x D entries per plan or more than 65 536
+// replicas yield mask = 0xFFFFFFFF, T = C = +inf, mem = 0.
+//
+// Four plans per workgroup.  A lane per (stage, replica) in the order of the list -- neighbouring
+// lanes read neighbouring entries -- leaves the stage times in LDS, then a lane per pipeline adds
+// its stages up in stage order.  The slowest link of a ring needs no pass of its own:
+// bytes / min(link) = max(bytes / link), division being monotone.  A wave takes a plan of up to
+// 512 pairs; a larger one, of which one can hold as many pairs as hundreds of small plans, is
+// shared by the four waves.  With a lane per pipeline that fetched stage after stage (most lanes
+// idle at D < 64, a chain of memory trips per stage) 10 007 plans of 1-48 stages and 1-32 replicas
+// took 225 us; they take 45 us now, half of the workgroups being done after 12 us: what is left is
+// the chain of trips in front of a plan and the workgroups that hold several large plans.
+__global__ __launch_bounds__(kReplicaWaves * 64) void k_eval_replicas(DevPlan pl, ReplicaArgs a) {
+  extern __shared__ double rep_lds[];
+  ReplicaLds &S = *reinterpret_cast<ReplicaLds *>(rep_lds);
+  double *const tables = reinterpret_cast<double *>(&S + 1);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int ZG = pl.ZGr, DP = pl.DP;
+  int32_t *const cnts = reinterpret_cast<int32_t *>(tables + list_tables_words(pl));
+  const uint64_t c0 = (uint64_t)blockIdx.x * kReplicaWaves, ci = c0 + wv;
+  ReplicaPlan pn{};
+  if (ci < a.count) {
+    const int32_t *d = a.desc + ci * 5;
+    const int ip = d[0], q = d[1], it = d[2], id = d[3], im = d[4];
+    if (ip >= 0 && ip < a.n_pp && it >= 0 && it < pl.TP && id >= 0 && id < DP && im >= 0 && im < pl.MB && q >= 0) {
+      const SearchPP pp = a.pps[ip];
+      const int64_t D = pl.vals[id];
+      if (q < pp.n_part && D <= kReplicaMaxDegree && (uint64_t)pp.P * (uint64_t)D <= a.stride &&
+          !(a.tps && (uint32_t)pp.P > a.tps_stride)) {
+        pn.P = pp.P;
+        pn.D = (int32_t)D;
+        pn.it = it; pn.id = id; pn.im = im;
+        pn.rs = pp.rs0 + (uint32_t)q * (uint32_t)pp.P;
+      }
+    }
+  }
+  if (lane == 0) S.plan[wv] = pn;
+  for (int p = threadIdx.x; p < kReplicaWaves * ZG; p += kReplicaWaves * 64) cnts[p] = 0;
+  const ListTables L = stage_list_tables(pl, tables);
+  __syncthreads();
+  const bool own = pn.P * pn.D <= kReplicaShared;
+  if (own && ci < a.count) {  // uniform over the wave
+    ReplicaSums s{};
+    if (pn.P != 0) s = replica_pairs<64>(pl, a, L, pn, ci, lane, S.times[wv], cnts + wv * ZG);
+    wave_lds_fence();
+    replica_write(a, L, pn, s, DP, ZG, ci, cnts + wv * ZG);
+  }
+  for (int w = 0; w < kReplicaWaves; ++w) {  // uniform over the workgroup
+    const ReplicaPlan big = S.plan[w];
+    if (big.P * big.D <= kReplicaShared) continue;
+    __syncthreads();  // the waves' times and sums are free
+    const ReplicaSums s = replica_pairs<kReplicaWaves * 64>(pl, a, L, big, c0 + w, (int)threadIdx.x, S.times[0], cnts + w * ZG);
+    if (lane == 0) S.part[wv] = s;
+    __syncthreads();
+    if (wv == w) {
+      ReplicaSums all = S.part[0];
+#pragma unroll
+      for (int x = 1; x < kReplicaWaves; ++x) {
+        const ReplicaSums &o = S.part[x];
+        all.t_pipe = fmax(all.t_pipe, o.t_pipe);
+        all.t_upd = fmax(all.t_upd, o.t_upd);
+        all.t_sync = fmax(all.t_sync, o.t_sync);
+        all.rent += o.rent;
+        all.traffic += o.traffic;
+        all.peak = o.peak > all.peak ? o.peak : all.peak;
+        all.flags |= o.flags;
+      }
+      replica_write(a, L, big, all, DP, ZG, c0 + w, cnts + w * ZG);
+    }
   }
 }
 

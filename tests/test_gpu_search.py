@@ -938,3 +938,58 @@ def test_a_beam_wider_than_one_pass_of_the_workgroup(torch_cuda):
                          orc.search_beam(300, MAX_THROUGHPUT, allow_split=True, max_runs=3), MAX_THROUGHPUT, orc)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("count", [1, 63, 65, 130])
+def test_listed_plans_at_the_edges_of_the_evaluators_passes(torch_cuda, count):
+    # one plan; one fewer and one more than a workgroup's 64; pipelines of 1 to 256 stages beside each
+    # other (a pass holds 512 stages), 1 to 70 replicas (up to 512 (stage, replica) pairs a wave takes a
+    # plan, beyond that the workgroup, in tiles): fp64 sums in the oracle's order, 1e-12
+    torch = torch_cuda
+    rng = np.random.default_rng(count)
+    L = 256
+    prob = make_problem(n_layers=L, n_types=3, n_zones=2, mb_list=(1, 2), tp_list=(1, 2), dp_list=(1, 2, 3, 8, 70),
+                        pp_list=[1, 2, 7, 64, 65, 255, 256], global_batch=1680, uniform_layers=False,
+                        partitions={255: [[2] + [1] * 254], 7: [[37, 37, 37, 37, 36, 36, 36]]},
+                        t_fwd=rng.uniform(0.5e-3, 2e-3, (3, 2, 2, L)), t_bwd=rng.uniform(1e-3, 4e-3, (3, 2, 2, L)),
+                        t_upd=rng.uniform(1e-5, 3e-5, (3, 2, L)),
+                        layer_params=rng.integers(1_000_000, 3_000_000, L).astype(np.uint64),
+                        act=rng.integers(1_000_000, 9_000_000, (2, 2)).astype(np.uint64), p2p=2_000_000,
+                        cap=np.array([40, 20, 8], np.uint64) * np.uint64(1 << 30), avail=np.full((2, 3), 9000),
+                        bw=np.array([[1e10, 1e9], [2e9, 1e10]]), egress=np.array([[0, 2e-11], [3e-11, 0]]),
+                        price=np.array([3.0, 1.5, 1.0]))
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        P_max, D_max, zg = 256, 70, 6
+        desc = np.stack([rng.integers(0, 7, count), np.zeros(count, int), rng.integers(0, 2, count),
+                         rng.integers(0, 5, count), rng.integers(0, 2, count)], 1).astype(np.int32)
+        if count == 1:
+            desc[0] = (6, 0, 0, 4, 0)  # the deepest pipeline with the most replicas
+        pa, pb = rng.integers(0, zg, (2, count, P_max)).astype(np.int32)
+        tps = rng.integers(0, 2, (count, P_max)).astype(np.int32)
+        reps = rng.integers(0, zg, (count, P_max * D_max)).astype(np.int32)
+        dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0")
+        out = {"d_time": torch.empty(count, dtype=torch.float64, device="cuda:0"),
+               "d_cost": torch.empty(count, dtype=torch.float64, device="cuda:0"),
+               "d_mem": torch.empty(count, dtype=torch.int64, device="cuda:0"),
+               "d_mask": torch.empty(count, dtype=torch.int32, device="cuda:0")}
+
+        def check(want):
+            torch.cuda.synchronize()
+            t, c, m, k = (out[f].cpu().numpy() for f in ("d_time", "d_cost", "d_mem", "d_mask"))
+            for i, e in enumerate(want):
+                assert k[i] == e.mask and m[i] == e.peak_mem, (i, desc[i])
+                assert t[i] == pytest.approx(e.iter_time, rel=1e-12) and c[i] == pytest.approx(e.cost, rel=1e-12)
+
+        P = [int(prob.pp_values[d[0]]) for d in desc]
+        D = [int(prob.dp_values[d[3]]) for d in desc]
+        plan.eval_placements(count, dev(desc), dev(pa), P_max, **out)
+        check([orc.eval_assignment(d[0], d[1], d[3], d[4], d[2], pa[i, :P[i]]) for i, d in enumerate(desc)])
+        plan.eval_placements(count, dev(desc), dev(pa), P_max, d_pools_b=dev(pb), d_tps=dev(tps), **out)
+        check([orc.eval_split_assignment_tp(d[0], d[1], d[3], d[4], tps[i, :P[i]], pa[i, :P[i]], pb[i, :P[i]])
+               for i, d in enumerate(desc)])
+        plan.eval_replica_placements(count, dev(desc), dev(reps), P_max * D_max, **out)
+        check([orc.eval_replica_assignment(d[0], d[1], d[3], d[4], d[2], reps[i, :P[i] * D[i]].reshape(P[i], D[i]))
+               for i, d in enumerate(desc)])
+    finally:
+        plan.destroy()
