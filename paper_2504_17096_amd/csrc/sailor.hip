@@ -41,6 +41,8 @@ constexpr double kSplitAbove = 0.9, kSplitAboveMean = 1.5, kSplitTo = 0.7, kSpli
 constexpr uint32_t kRankOneWorkgroup = 128;  // largest k whose final ranking runs as one workgroup
 constexpr uint32_t kEvalUnitTarget = 16384;  // candidates per workgroup of the range evaluation
 constexpr unsigned kEvalRowsThreads = 512;
+constexpr uint32_t kSearchWorkgroups = 1024, kRootWorkgroups = 1024;  // of the search's two kernels
+constexpr size_t kSearchLds = 80 * 1024;       // LDS of a search workgroup: two fit a compute unit
 constexpr uint64_t kPlaceWorkgroups = 1024;  // workgroups a list of placements is spread over, if it is long enough
 constexpr size_t kEvalRowsMaxLds = 64 * 1024;  // above this the range form evaluates lane by lane
 constexpr size_t kScanMaxLds = 160 * 1024;     // a scan workgroup stages its records within the LDS of a compute unit
@@ -150,11 +152,13 @@ struct sailor_plan {
   std::vector<SearchPP> search_pps;
   const SearchPP *d_search_pps = nullptr;
   uint32_t n_sub = 0, n_sub_t = 0;  // sub-problems with TP in them / with a TP degree per stage
-  uint8_t *search_states = nullptr;
-  uint32_t search_wgs = 0, search_state_stride = 0, search_path_stride = 0;
-  int search_beam_cap = 0;  // beam width the frontier buffers hold
+  double *search_states = nullptr;    // frontiers and histories that do not fit LDS (wide beams), and
+  uint32_t *search_history = nullptr; // how many words of them there are
+  size_t search_states_cap = 0, search_history_cap = 0;
+  uint32_t *search_list = nullptr, *search_counters = nullptr;
+  unsigned long long *search_root_expanded = nullptr;
   SubResult *search_results = nullptr, *search_final = nullptr;
-  double *search_eval = nullptr;  // T, C, then (as 64-bit words) mem and mask of the winner
+  bool search_dirty = true;           // the counters are not zero
   uint32_t cnt_phase = 0;      // which of the two counter sets the next call uses
   bool counters_dirty = false; // a failed call may have left either set in any state
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};  // start, scan end, end, scan start
@@ -544,6 +548,28 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
   else launch_units_m<MODE, false>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
 }
 
+template <int MODE>
+void launch_search(const sailor_plan *pl, const SearchArgs &a, unsigned root_wgs, size_t root_words, unsigned wgs,
+                          size_t lds, hipStream_t st) {
+  k_search_root<MODE><<<root_wgs, kRootWaves * 64, root_words * 8 * kRootWaves, st>>>(pl->dev, a, (uint32_t)root_words);
+  k_search_beam<MODE><<<wgs, kSearchThreads, lds, st>>>(pl->dev, a);
+}
+
+// Waits for the sequence number in host-mapped memory rather than for the dispatch to
+// retire; the stream is asked now and then, so that a failed launch cannot hang the wait.
+sailor_status wait_for_result(const sailor_plan *pl, hipStream_t st) {
+  const volatile uint32_t *flag = &static_cast<ResultHeader *>(pl->h_result)->seq;
+  for (uint32_t spins = 1; *flag != pl->seq; ++spins) {
+    if ((spins & 0x3FFu) != 0) continue;
+    const hipError_t q = hipStreamQuery(st);
+    if (q == hipErrorNotReady) continue;
+    HIP_TRY(q);
+    if (*flag != pl->seq) return SAILOR_EDEVICE;  // the stream drained without a result
+  }
+  __atomic_thread_fence(__ATOMIC_ACQUIRE);
+  return SAILOR_OK;
+}
+
 // Shared by best_plan (k = 0: tolerance rule) and topk.
 sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
                                  const sailor_constraint *con, uint32_t k, hipStream_t st,
@@ -631,17 +657,8 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     }
     if (t_all) HIP_TRY(hipEventRecord(pl->ev[2], st));
     HIP_TRY(hipGetLastError());
-    // Wait for the sequence number in host-mapped memory rather than for the dispatch to
-    // retire; the stream is asked now and then, so that a failed launch cannot hang the wait.
-    const volatile uint32_t *flag = &static_cast<ResultHeader *>(pl->h_result)->seq;
-    for (uint32_t spins = 1; *flag != pl->seq; ++spins) {
-      if ((spins & 0x3FFu) != 0) continue;
-      const hipError_t q = hipStreamQuery(st);
-      if (q == hipErrorNotReady) continue;
-      HIP_TRY(q);
-      if (*flag != pl->seq) return SAILOR_EDEVICE;  // the stream drained without a result
-    }
-    __atomic_thread_fence(__ATOMIC_ACQUIRE);
+    const sailor_status waited = wait_for_result(pl, st);
+    if (waited != SAILOR_OK) return waited;
     *hdr = *static_cast<ResultHeader *>(pl->h_result);
     return SAILOR_OK;
   };
@@ -1360,9 +1377,8 @@ sailor_status sailor_simulate_1f1b_static(sailor_plan *pl, uint64_t count, const
 }
 
 // tables of the search and of the placement evaluation (once per plan)
-// (beam = 0: the tables only; beam > 0: also the search's buffers, its frontiers sized for the
-// widest beam asked for so far)
-static sailor_status search_setup(sailor_plan *pl, int beam) {
+// (search: also the search's buffers)
+static sailor_status search_setup(sailor_plan *pl, bool search) {
   if (!pl->d_search_pps) {
     pl->search_pps.clear();
     uint32_t sub = 0, sub_t = 0;
@@ -1390,40 +1406,27 @@ static sailor_status search_setup(sailor_plan *pl, int beam) {
     if (pl->arena.upload(&pl->d_search_pps, pl->search_pps.data(), pl->search_pps.size()) != hipSuccess)
       return SAILOR_ENOMEM;
   }
-  if (beam > 0 && !pl->search_results) {
+  if (search && !pl->search_results) {
     SubResult *res = nullptr, *fin = nullptr;
-    double *ev = nullptr;
-    if (pl->arena.alloc(&res, (size_t)pl->n_sub) != hipSuccess || pl->arena.alloc(&fin, 1) != hipSuccess ||
-        pl->arena.alloc(&ev, 4) != hipSuccess) {
-      pl->arena.free_one(res);
-      pl->arena.free_one(fin);
-      pl->arena.free_one(ev);
+    DeviceArena &ar = pl->arena;
+    if (ar.alloc(&res, (size_t)std::min(pl->n_sub, kSearchWorkgroups)) != hipSuccess || ar.alloc(&fin, 1) != hipSuccess ||
+        ar.alloc(&pl->search_list, (size_t)pl->n_sub) != hipSuccess ||
+        ar.alloc(&pl->search_counters, pl->search_pps.size() + 1) != hipSuccess ||
+        ar.alloc(&pl->search_root_expanded, (size_t)kRootWorkgroups) != hipSuccess) {
+      for (void *p : {(void *)res, (void *)fin, (void *)pl->search_list, (void *)pl->search_counters,
+                      (void *)pl->search_root_expanded})
+        if (p) ar.free_one(p);
+      pl->search_list = pl->search_counters = nullptr;
+      pl->search_root_expanded = nullptr;
       return SAILOR_ENOMEM;
     }
     if (hipMemset(fin, 0, sizeof(SubResult)) != hipSuccess) {  // (read by the winner's re-evaluation
-      pl->arena.free_one(res);                                 // also when nothing was found)
-      pl->arena.free_one(fin);
-      pl->arena.free_one(ev);
+      ar.free_one(res);                                        // also when nothing was found)
+      ar.free_one(fin);
       return SAILOR_EDEVICE;
     }
     pl->search_results = res;
     pl->search_final = fin;
-    pl->search_eval = ev;
-  }
-  if (beam > pl->search_beam_cap) {
-    // (no search is in flight on these buffers: every call waits for its own kernels)
-    pl->arena.free_one(pl->search_states);
-    pl->search_states = nullptr;
-    pl->search_beam_cap = 0;
-    pl->search_wgs = std::min<uint32_t>(pl->n_sub, 2048u);
-    pl->search_path_stride = ((uint32_t)pl->dev.P_max + 7u) & ~7u;
-    pl->search_state_stride = kStateBytes + 3 * pl->search_path_stride;  // pools, second pools, TP indices
-    const size_t bytes = (size_t)pl->search_wgs * 2 * (size_t)beam * pl->search_state_stride;
-    if (pl->arena.alloc(&pl->search_states, bytes) != hipSuccess) {
-      pl->search_states = nullptr;
-      return SAILOR_ENOMEM;
-    }
-    pl->search_beam_cap = beam;
   }
   return SAILOR_OK;
 }
@@ -1454,7 +1457,7 @@ sailor_status sailor_eval_placements(sailor_plan *pl, uint64_t count, const int3
   HIP_TRY(hipSetDevice(pl->device));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   sailor_status rc;
-  try { rc = search_setup(pl, 0); } catch (...) { rc = SAILOR_ENOMEM; }
+  try { rc = search_setup(pl, false); } catch (...) { rc = SAILOR_ENOMEM; }
   if (rc != SAILOR_OK) return rc;
   rc = refresh_avail(pl, st);
   if (rc != SAILOR_OK) return rc;
@@ -1487,7 +1490,7 @@ sailor_status sailor_eval_replica_placements(sailor_plan *pl, uint64_t count, co
   HIP_TRY(hipSetDevice(pl->device));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   sailor_status rc;
-  try { rc = search_setup(pl, 0); } catch (...) { rc = SAILOR_ENOMEM; }
+  try { rc = search_setup(pl, false); } catch (...) { rc = SAILOR_ENOMEM; }
   if (rc != SAILOR_OK) return rc;
   rc = refresh_avail(pl, st);
   if (rc != SAILOR_OK) return rc;
@@ -1527,7 +1530,7 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   if (rc != SAILOR_OK) return rc;
   HIP_TRY(hipSetDevice(pl->device));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  try { rc = search_setup(pl, opt->beam_width); } catch (...) { rc = SAILOR_ENOMEM; }
+  try { rc = search_setup(pl, true); } catch (...) { rc = SAILOR_ENOMEM; }
   if (rc != SAILOR_OK) return rc;
   SearchArgs a{};
   a.objective = (int)objective;
@@ -1552,25 +1555,73 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   }
   rc = refresh_avail(pl, st);
   if (rc != SAILOR_OK) return rc;
+  const bool split = opt->allow_split != 0, stp = opt->stage_tp != 0;
+  const size_t W = (size_t)a.W, ZG = (size_t)pl->dev.ZGr, TPn = stp ? (size_t)pl->dev.TP : 1;
   a.pps = pl->d_search_pps;
   a.n_pp = (int)pl->search_pps.size();
-  a.n_sub = opt->stage_tp ? pl->n_sub_t : pl->n_sub;
-  a.states = pl->search_states;
-  a.state_stride = pl->search_state_stride;
-  a.path_stride = pl->search_path_stride;
+  a.n_sub = stp ? pl->n_sub_t : pl->n_sub;
+  a.list = pl->search_list;
+  a.counters = pl->search_counters;
+  a.root_expanded = pl->search_root_expanded;
   a.results = pl->search_results;
-  const unsigned wgs = std::min<uint32_t>(pl->search_wgs, a.n_sub);
-  if (opt->allow_split && opt->stage_tp) k_search_beam<SEARCH_SPLIT_TP><<<wgs, kSearchThreads, 0, st>>>(pl->dev, a);
-  else if (opt->allow_split) k_search_beam<SEARCH_SPLIT><<<wgs, kSearchThreads, 0, st>>>(pl->dev, a);
-  else if (opt->stage_tp) k_search_beam<SEARCH_STAGE_TP><<<wgs, kSearchThreads, 0, st>>>(pl->dev, a);
-  else k_search_beam<SEARCH_PLAIN><<<wgs, kSearchThreads, 0, st>>>(pl->dev, a);
-  k_search_pick<<<1, 256, 0, st>>>(pl->search_results, a.n_sub, pl->search_final);
+  // a power of two that holds what a level can have, and twice the beam
+  size_t buf = 64;
+  while (buf < kSearchBuf && buf < std::max(2 * W, W * ZG * (split ? TPn : 1))) buf *= 2;
+  a.buf = (uint32_t)buf;
+  // split stages: about 16 KiB of tables for a block of states
+  a.block = (uint32_t)std::max<size_t>(1, std::min(W, 1024 / (TPn * ZG)));
+  // Frontiers and history stay in LDS as long as two workgroups fit a compute unit; wide beams keep the
+  // history, then the frontiers too, in device memory.
+  const unsigned wgs = std::min(a.n_sub, kSearchWorkgroups);
+  SearchLds layout;
+  auto lds_bytes = [&]() { return search_carve(pl->dev, split, stp, false, a, nullptr, layout) * 8; };
+  size_t lds = lds_bytes();
+  if (lds > kSearchLds) {
+    const size_t words = (size_t)kSearchWorkgroups * W * pl->dev.P_max;
+    if (words > pl->search_history_cap) {
+      // (no search is in flight on these buffers: every call waits for its own kernels)
+      pl->arena.free_one(pl->search_history);
+      pl->search_history = nullptr;
+      pl->search_history_cap = 0;
+      if (pl->arena.alloc(&pl->search_history, words) != hipSuccess) return SAILOR_ENOMEM;
+      pl->search_history_cap = words;
+    }
+    a.history = pl->search_history;
+    lds = lds_bytes();
+  }
+  if (lds > kSearchLds) {
+    const size_t words = (size_t)kSearchWorkgroups * 2 * W * search_state_words(true, (int)ZG);
+    if (words > pl->search_states_cap) {
+      pl->arena.free_one(pl->search_states);
+      pl->search_states = nullptr;
+      pl->search_states_cap = 0;
+      if (pl->arena.alloc(&pl->search_states, words) != hipSuccess) return SAILOR_ENOMEM;
+      pl->search_states_cap = words;
+    }
+    a.states = pl->search_states;
+    lds = lds_bytes();
+  }
+  const size_t root_words = search_carve(pl->dev, split, stp, true, a, nullptr, layout);
+  if (lds > kScanMaxLds || root_words * 8 * kRootWaves > kScanMaxLds) return SAILOR_EINVAL;
+  if (pl->search_dirty)  // (the last kernel of a search leaves the counters at zero)
+    HIP_TRY(hipMemsetAsync(pl->search_counters, 0, ((size_t)a.n_pp + 1) * sizeof(uint32_t), st));
+  pl->search_dirty = true;  // until this search has succeeded
+  const unsigned root_wgs = std::min<unsigned>(kRootWorkgroups, (a.n_sub + kRootWaves - 1) / kRootWaves);
+  if (split && stp) launch_search<SEARCH_SPLIT_TP>(pl, a, root_wgs, root_words, wgs, lds, st);
+  else if (split) launch_search<SEARCH_SPLIT>(pl, a, root_wgs, root_words, wgs, lds, st);
+  else if (stp) launch_search<SEARCH_STAGE_TP>(pl, a, root_wgs, root_words, wgs, lds, st);
+  else launch_search<SEARCH_PLAIN>(pl, a, root_wgs, root_words, wgs, lds, st);
+  // what the host reads is written to the mapped result area (the flat space's results, if any, have
+  // been read): the winner, then its T, C, mem and mask
+  SubResult *const d_fin = reinterpret_cast<SubResult *>(pl->d_out);
+  double *const d_ev = reinterpret_cast<double *>(d_fin + 1);
+  k_search_pick<<<1, 1024, 0, st>>>(a, wgs, root_wgs, pl->search_final, d_fin);
   // the winner once more through the simulator, for its memory footprint and its mask
   PlaceArgs pa{};
   pa.count = 1;
   pa.desc = pl->search_final->desc;  // (device addresses: nothing is read here)
   pa.pools = pl->search_final->pools;
-  pa.pools_b = opt->allow_split ? pl->search_final->pools_b : nullptr;
+  pa.pools_b = split ? pl->search_final->pools_b : nullptr;
   pa.tps = pl->search_final->tps;
   pa.pool_stride = sizeof pl->search_final->pools / sizeof pl->search_final->pools[0];
   pa.pps = pl->d_search_pps;
@@ -1578,17 +1629,19 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   pa.objective = (int)objective;
   pa.has_bound = has_bound;
   pa.bound = bound;
-  pa.T = pl->search_eval;
-  pa.C = pl->search_eval + 1;
-  pa.mem = reinterpret_cast<uint64_t *>(pl->search_eval + 2);
-  pa.mask = reinterpret_cast<uint32_t *>(pl->search_eval + 3);
+  pa.T = d_ev;
+  pa.C = d_ev + 1;
+  pa.mem = reinterpret_cast<uint64_t *>(d_ev + 2);
+  pa.mask = reinterpret_cast<uint32_t *>(d_ev + 3);
+  pa.hdr = pl->d_hdr;
+  pa.seq = ++pl->seq;
   launch_placements(pl, pa, st);
   HIP_TRY(hipGetLastError());
-  SubResult fin;
-  double ev[4];
-  HIP_TRY(hipMemcpyAsync(&fin, pl->search_final, sizeof fin, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(ev, pl->search_eval, sizeof ev, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  rc = wait_for_result(pl, st);
+  if (rc != SAILOR_OK) return rc;
+  pl->search_dirty = false;
+  const SubResult &fin = *reinterpret_cast<const SubResult *>(static_cast<char *>(pl->h_result) + sizeof(ResultHeader));
+  const double *ev = reinterpret_cast<const double *>(&fin + 1);
   std::memset(out, 0, sizeof *out);
   for (int i = 0; i < SAILOR_MAX_STAGES; ++i) out->pool[i] = out->pool_b[i] = out->stage_tp_index[i] = -1;
   out->exact = fin.truncated ? 0 : 1;

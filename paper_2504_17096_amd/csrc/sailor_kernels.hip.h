@@ -189,6 +189,19 @@ __device__ __forceinline__ uint64_t stage_bytes_of(uint64_t params, int32_t laye
   return shard * (uint64_t)bpp + (uint64_t)inflight * (uint64_t)layers * act;
 }
 
+// activation bytes of a worker: microbatches in flight x layers x bytes of one (validated < 2^62)
+__device__ __forceinline__ uint64_t act_bytes(int in_flight, int layers, uint64_t act) {
+  return (uint64_t)(uint32_t)in_flight * (uint32_t)layers * act;
+}
+
+// makes a wave's LDS writes visible to its own later reads (operations of one wave complete in
+// order; the compiler must not move them)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ uint64_t stage_bytes(const DevPlan &pl, uint32_t rs, int i, int P,
                                                 int tp, int64_t nb, uint64_t act) {
   return stage_bytes_of(pl.st_params[rs + i], pl.st_n[rs + i], pl.bpp, i, P, tp, nb, act);

@@ -15,13 +15,25 @@
 // TP degree (a, t) -- tp_ij of Sec. 4.2.2 taken per stage; TP then leaves the sub-problem and a
 // pool's quota is counted in GPUs of one replica.
 //
-//   k_search_beam        the level-by-level expansion, one workgroup per sub-problem
-//   k_search_pick        smallest (key, sub-problem) over the sub-problems' winners
-//   k_eval_placements    the simulator of Sec. 4.3 for listed placements, one wave each, fp64
+//   k_search_root        first level of every sub-problem, a wave each: the ones that survive it
+//                        go to a list, the deepest pipelines to be taken first
+//   k_search_beam        the level-by-level expansion, one workgroup per surviving sub-problem
+//   k_search_pick        smallest (key, sub-problem) over the workgroups' winners
+//   k_eval_placements    the simulator of Sec. 4.3 for listed placements, fp64
 //   k_eval_replicas      the same for plans in which every replica of every stage names its pool
 //
 // All arithmetic is fp64 in a fixed order (sums in stage order), so that which extension is
 // dropped or kept does not depend on how the work is spread over lanes.
+//
+// What bounds it: the levels of one deep sub-problem follow one another (48 for 48 stages),
+// while all of a search's candidates together are little work for the chip (6 to 30 million of
+// them).  So a level is kept short: frontier, tables and history stay in LDS, the next level's
+// inputs are requested a level ahead, appending candidates takes no barrier, the W smallest come
+// from a histogram and a count of predecessors instead of a sort of everything, and a wide choice
+// (second pool, TP degree) is first reduced to the best of each (state, pool).  On the 48-layer,
+// 20-pool problem a search with beam 64 takes 0.85 ms where states in device memory, paths copied
+// level by level and a bitonic sort of every level took 2.9 ms; with two pools and a TP degree per
+// stage (1 600 choices, beam 8) 1.15 ms against 9.3 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -30,11 +42,14 @@
 
 namespace sailor {
 
-constexpr int kSearchThreads = 256;
+constexpr int kSearchThreads = 512;
 constexpr int kSearchMaxBeam = 1024;   // longest frontier a sub-problem keeps (half of kSearchBuf at most)
-constexpr int kSearchBuf = 2048;       // extensions buffered between two sorts
-constexpr int kSearchMaxStages = 255;  // placements count stages per pool in a byte
+constexpr int kSearchBuf = 2048;       // most candidates buffered between two selections
+constexpr int kSearchBins = 512;
+constexpr int kSearchMaxStages = 255;  // placements count runs in a byte
 constexpr int kSearchMaxPools = 64;
+constexpr int kRootWaves = 4;
+static_assert(kMaxTP * (2 * kMaxTypes + 16) <= kSearchThreads, "a thread per word of a level's records");
 
 struct SearchPP {      // one pipeline depth
   int32_t P;
@@ -47,21 +62,26 @@ struct SearchPP {      // one pipeline depth
 
 enum : int { SEARCH_PLAIN = 0, SEARCH_SPLIT = 1, SEARCH_STAGE_TP = 2, SEARCH_SPLIT_TP = 3 };
 
-struct SState {        // placement of stages 0 .. j; kStateBytes, followed by the paths (a byte per stage)
+struct SPart {         // one kind of pipeline of a placement of stages 0 .. j
   double sum;          // times of the closed stages 0 .. j-1
   double maxt;         // slowest closed stage
   double c_open;       // compute time of stage j (its forward transfer is not known yet)
   double xb_open;      // its backward transfer to stage j-1
-  double sum_b, maxt_b, c_open_b, xb_open_b;  // with split stages: the pipelines through the second pools
+};
+
+template <bool SPLIT>
+struct SState {        // placement of stages 0 .. j, followed by its pool counts (uint16_t per pool):
+                       // stages placed on each pool (split stages: halves of stages; a TP degree per
+                       // stage: GPUs of one replica)
   double msync, mupd, dol, comm;
-  uint16_t cnt[kSearchMaxPools];  // stages placed on each pool (split stages: halves of stages; a
-                                  // TP degree per stage: GPUs of one replica)
+  SPart part[SPLIT ? 2 : 1];  // with split stages: the pipelines through the first / second pools
   uint8_t pool, pool_b, runs, tpi, pad[4];  // tpi: the open stage's TP index (TP per stage)
 };
-constexpr uint32_t kStateBytes = sizeof(SState);
-static_assert(kStateBytes == 232, "twelve doubles, the pool counts, pools, runs and TP index");
+__host__ __device__ inline uint32_t search_state_words(bool split, int ZG) {  // 8-byte words
+  return (uint32_t)((split ? sizeof(SState<true>) : sizeof(SState<false>)) / 8) + (uint32_t)(ZG + 3) / 4;
+}
 
-struct SubResult {     // winner of one sub-problem (or of the whole search)
+struct SubResult {     // winner of a workgroup's sub-problems (or of the whole search)
   double key, T, C;
   uint32_t found, truncated;
   unsigned long long expanded;
@@ -78,44 +98,444 @@ struct SearchArgs {
   const SearchPP *pps;
   int n_pp;
   uint32_t n_sub;
-  uint8_t *states;        // [workgroups][2][W] states of state_stride bytes
-  uint32_t state_stride;  // kStateBytes + three paths of path_stride bytes (pools, second pools, TP indices)
-  uint32_t path_stride;   // the deepest pipeline, rounded up to 8
-  SubResult *results;     // [n_sub]
+  uint32_t *list;         // [n_sub] surviving sub-problems, those of a depth together
+  uint32_t *counters;     // [n_pp] how many per depth, [1] how many were taken
+  unsigned long long *root_expanded;  // [k_search_root's workgroups]
+  uint32_t buf;           // candidates buffered, at most kSearchBuf
+  uint32_t block;         // split stages: states whose tables are in LDS at a time
+  double *states;         // [workgroups][2][W] states, or NULL: they are in LDS
+  uint32_t *history;      // [workgroups][P_max][W], or NULL: it is in LDS
+  SubResult *results;     // [workgroups]
 };
 
 struct SBound { double T, C; };
-
-// Lower bounds of T_iter and C_iter over the completions of a placement whose stage j is open;
-// the plan's own values when j = P - 1 (then every S term is zero).
-__device__ __forceinline__ SBound search_bounds(double sum, double maxt, double c_open, double xb_open,
-                                                double msync, double mupd, double dol, double comm,
-                                                double Ssum, double Smax, double Ssync, double Supd,
-                                                double Sdol, double nbm1) {
-  const double t_open = c_open + xb_open;
-  const double tsum = (sum + t_open) + Ssum;
-  const double tmax = fmax(fmax(maxt, t_open), Smax);
-  SBound b;
-  b.T = ((tsum + nbm1 * tmax) + fmax(msync, Ssync)) + fmax(mupd, Supd);
-  b.C = (dol + Sdol) / 3600.0 * b.T + comm;
-  return b;
-}
 
 __device__ __forceinline__ bool key_id_less(unsigned long long ka, uint32_t ia, unsigned long long kb,
                                             uint32_t ib) {
   return ka < kb || (ka == kb && ia < ib);
 }
 
-// Ascending bitonic sort of (key, id) pairs in LDS; m = the power of two >= n, entries
-// n .. m-1 are filled with the largest pair first.
+// ---- tables in LDS ----
+
+struct SearchLds {
+  // of the sub-problem
+  double *S;            // [5][P_max] what lies behind stage i: sum, max, sync, upd, $
+  double *smin;         // [4][P_max] cheapest admissible choice of every stage
+  double *xfer, *comm;  // [Z][Z] transfer seconds; price of a boundary (split: of one kind of pipeline)
+  double *ring_price;   // [Z][Z] split: egress both ways
+  double *link;         // [Z] a zone's own link; split: [Z][Z] slowest link of a ring through both
+  double *price, *dtp;  // [G]; [TPn] D * tp
+  int32_t *cap;         // [ZG] what a pool can host, in the units of the pool counts
+  uint32_t *zg;         // [ZG] zone | type << 8
+  int32_t *width;       // [TPn] what a stage (half a stage) takes from a pool
+  // of a level, two of each: the next level's are filled while this one's are used
+  double *raw;          // [2][TPn][row_w] the stage's records (DevPlan::st_row)
+  double *sync;         // [2][TPn][Z]; split: [TPn][Z][Z] seconds of the stage's all-reduce
+  double *ring;         // [2][TPn] bytes it moves over every link
+  uint32_t *fit;        // [2][TPn] bit g: the stage fits type g
+  // split, for a block of states: bounds of the two kinds of pipeline by (TP, pool), pools that
+  // can take one half / both halves, the maxima a choice is folded into
+  double *pa, *pb;      // [block][TPn][ZG]
+  unsigned long long *half, *whole;  // [block][TPn]
+  double *mx;           // [block][2]
+  // the candidates
+  unsigned long long *key;  // [buf]
+  unsigned long long *okey; // [gather]
+  uint32_t *id, *oid, *rank, *sel;  // [buf], [gather], [gather], [W]
+  uint32_t *hist;       // [kSearchBins]
+  double *states;
+  uint32_t *history;
+};
+
+__host__ __device__ inline uint32_t search_gather(uint32_t W, uint32_t buf) { return W + 256u < buf ? W + 256u : buf; }
+
+// Lays the tables out from base on (NULL: only counts); returns the 8-byte words they take.
+__host__ __device__ inline size_t search_carve(const DevPlan &pl, bool split, bool stp, bool root, const SearchArgs &a,
+                                               double *base, SearchLds &L) {
+  const size_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, TPn = stp ? pl.TP : 1, P = pl.P_max, two = root ? 1 : 2;
+  size_t at = 0;
+  auto words = [&](size_t n) { double *p = base + at; at += n; return p; };
+  auto ints = [&](size_t n) { return reinterpret_cast<uint32_t *>(words((n + 1) / 2)); };
+  L.S = words(5 * P);
+  L.smin = words(4 * P);
+  L.xfer = words(root ? 0 : Z * Z);
+  L.comm = words(root ? 0 : Z * Z);
+  L.ring_price = words(split ? Z * Z : 0);
+  L.link = words(split ? Z * Z : Z);
+  L.price = words(G);
+  L.dtp = words(TPn);
+  L.cap = reinterpret_cast<int32_t *>(ints(ZG));
+  L.zg = ints(ZG);
+  L.width = reinterpret_cast<int32_t *>(ints(TPn));
+  L.raw = words(two * TPn * pl.row_w);
+  L.sync = words(two * TPn * (split ? Z * Z : Z));
+  L.ring = words(two * TPn);
+  L.fit = ints(two * TPn);
+  if (root) return at;
+  L.pa = words(split ? a.block * TPn * ZG : 0);
+  L.pb = words(split ? a.block * TPn * ZG : 0);
+  L.half = reinterpret_cast<unsigned long long *>(words(split ? a.block * TPn : 0));
+  L.whole = reinterpret_cast<unsigned long long *>(words(split ? a.block * TPn : 0));
+  L.mx = words(split ? a.block * 2 : 0);
+  const size_t gather = search_gather((uint32_t)a.W, a.buf);
+  L.key = reinterpret_cast<unsigned long long *>(words(a.buf));
+  L.okey = reinterpret_cast<unsigned long long *>(words(gather));
+  L.id = ints(a.buf);
+  L.oid = ints(gather);
+  L.rank = ints(gather);
+  L.sel = ints(a.W);
+  L.hist = ints(kSearchBins);
+  L.states = words(a.states ? 0 : 2 * (size_t)a.W * search_state_words(split, (int)ZG));
+  L.history = ints(a.history ? 0 : (size_t)a.W * P);
+  return at;
+}
+
+// for fast_div
+__device__ __forceinline__ uint32_t search_magic(int d) {
+  return d == 1 ? 0u : (uint32_t)(((1ull << 32) + (uint32_t)d - 1) / (uint32_t)d);
+}
+
+struct SearchSub {     // a sub-problem
+  int ip, q, it, id, im, P, nb;
+  int64_t D;
+  uint32_t rs;
+  double nbm1, ringf;  // N_b - 1; 2 (D - 1) / D
+};
+
+template <bool STP>
+__device__ __forceinline__ SearchSub search_sub(const DevPlan &pl, const SearchArgs &a, uint32_t sid) {
+  SearchSub s;
+  s.ip = 0;
+  for (int i = 1; i < a.n_pp; ++i)
+    if (sid >= (STP ? a.pps[i].sub_off_t : a.pps[i].sub_off)) s.ip = i;
+  const SearchPP pp = a.pps[s.ip];
+  uint32_t rem = sid - (STP ? pp.sub_off_t : pp.sub_off);
+  s.im = (int)(rem % (uint32_t)pl.MB); rem /= (uint32_t)pl.MB;
+  s.id = (int)(rem % (uint32_t)pl.DP); rem /= (uint32_t)pl.DP;
+  s.it = STP ? 0 : (int)(rem % (uint32_t)pl.TP);  // (TP per stage: not part of the sub-problem)
+  s.q = STP ? (int)rem : (int)(rem / (uint32_t)pl.TP);
+  s.P = pp.P;
+  s.rs = pp.rs0 + (uint32_t)s.q * (uint32_t)pp.P;
+  s.nb = pl.nb[s.im * pl.DP + s.id];
+  s.D = pl.vals[s.id];
+  s.nbm1 = (double)(s.nb - 1);
+  s.ringf = 2.0 * (double)(s.D - 1) / (double)s.D;
+  return s;
+}
+
+// First record of stage i (at the sub-problem's TP, or at every one from the first on).
+template <bool STP>
+__device__ __forceinline__ const double *search_row(const DevPlan &pl, const SearchSub &s, int i) {
+  return pl.st_row + ((size_t)(s.rs + (uint32_t)i) * pl.MB * pl.TP + (size_t)s.im * pl.TP + (STP ? 0 : s.it)) * pl.row_w;
+}
+
+// The sub-problem's tables, by nt threads (tid: which one this is); false: some stage fits no
+// pool (known to the thread that looked at it).  A barrier (or fence) before S is accumulated.
+template <int MODE, bool ROOT>
+__device__ __forceinline__ bool search_tables(const DevPlan &pl, const SearchSub &s, const SearchLds &L, int tid, int nt) {
+  constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
+  constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
+  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, TP = pl.TP, TPn = STP ? TP : 1;
+  const double D = (double)s.D;
+  for (int i = tid; i < Z * Z; i += nt) {
+    const int z = i / Z, y = i - z * Z;
+    double both = 0.0;
+    if (pl.egress && z != y) both = pl.egress[z * Z + y] + pl.egress[y * Z + z];
+    if (!ROOT) {
+      L.xfer[i] = pl.xsec[s.im * Z * Z + i];
+      L.comm[i] = z == y ? 0.0 : (double)s.nb * (SPLIT ? 0.5 * D : D) * (double)pl.p2p[s.im] * both;
+    }
+    if (SPLIT) {
+      L.ring_price[i] = both;
+      double link = pl.bw[z * Z + z];
+      if (y != z) link = fmin(fmin(link, pl.bw[y * Z + y]), fmin(pl.bw[z * Z + y], pl.bw[y * Z + z]));
+      L.link[i] = link;
+    } else if (z == y) {
+      L.link[z] = pl.bw[z * Z + z];
+    }
+  }
+  for (int p = tid; p < ZG; p += nt) {
+    const int64_t per = STP ? s.D : (int64_t)pl.vals[pl.DP + s.it] * s.D;
+    L.cap[p] = (int32_t)((SPLIT ? 2 : 1) * (int64_t)pl.avail[p] / per);
+    const uint32_t z = fast_div((uint32_t)p, pl.mg_g);
+    L.zg[p] = z | ((uint32_t)p - z * (uint32_t)G) << 8;
+  }
+  for (int g = tid; g < G; g += nt) L.price[g] = pl.price[g];
+  for (int k = tid; k < TPn; k += nt) {
+    const int tp = pl.vals[pl.DP + (STP ? k : s.it)];
+    L.dtp[k] = (double)(s.D * (int64_t)tp);
+    L.width[k] = STP ? tp : 1;
+  }
+  bool fine = true;
+  for (int i = tid; i < s.P; i += nt) {  // the cheapest admissible (type, TP) of stage i
+    const double *row = search_row<STP>(pl, s, i);
+    const int layers = pl.st_n[s.rs + i];
+    double cmin = __builtin_huge_val(), umin = cmin, dmin = cmin, smin = cmin;
+    bool any = false;
+    for (int k = 0; k < TPn; ++k, row += pl.row_w) {
+      const int kk = STP ? k : s.it, tpk = pl.vals[pl.DP + kk];
+      const uint64_t bytes = (uint64_t)__double_as_longlong(row[2 * G]) +
+                             act_bytes(min(s.P - i, s.nb), layers, pl.act[s.im * TP + kk]);
+      bool fits_some = false;
+      for (int g = 0; g < G; ++g) {
+        if (!(bytes + pl.res[g] <= pl.cap[g] && tpk <= pl.node[g])) continue;
+        fits_some = true;
+        cmin = fmin(cmin, row[g]);
+        umin = fmin(umin, row[G + g]);
+        dmin = fmin(dmin, (double)(s.D * (int64_t)tpk) * pl.price[g]);
+      }
+      if (!fits_some) continue;
+      any = true;
+      // (the all-reduce is fastest over the fastest link, division being monotone)
+      double sync = 0.0;
+      if (s.D > 1) {
+        double fastest = 0.0;
+        for (int z = 0; z < Z; ++z) fastest = fmax(fastest, pl.bw[z * Z + z]);
+        sync = s.ringf * row[2 * G + 1] / fastest;
+      }
+      smin = fmin(smin, sync);
+    }
+    const int P = pl.P_max;
+    L.smin[i] = cmin; L.smin[P + i] = smin; L.smin[2 * P + i] = umin; L.smin[3 * P + i] = dmin;
+    fine = fine && any;
+  }
+  return fine;
+}
+
+// What lies behind every stage, accumulated from the last stage backwards: lanes 0 .. 4 of a
+// wave take a quantity each.
+__device__ __forceinline__ void search_suffix(const DevPlan &pl, const SearchSub &s, const SearchLds &L, int lane) {
+  if (lane >= 5) return;
+  const int P = pl.P_max;
+  const double *v = L.smin + (lane == 0 || lane == 1 ? 0 : lane - 1) * P;
+  double *o = L.S + lane * P, x = 0.0;
+  o[s.P - 1] = 0.0;
+  for (int i = s.P - 2; i >= 0; --i) {
+    const double y = v[i + 1];
+    x = (lane == 0 || lane == 4) ? x + y : fmax(x, y);
+    o[i] = x;
+  }
+}
+
+// What follows from a level's records (which must be visible): all-reduce seconds, fits.
+template <int MODE>
+__device__ __forceinline__ void search_level(const DevPlan &pl, const SearchSub &s, const SearchLds &L, int j, int b, int tid,
+                                             int nt) {
+  constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
+  constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
+  const int G = pl.G, Z = pl.Z, TP = pl.TP, TPn = STP ? TP : 1, NS = SPLIT ? Z * Z : Z;
+  const double *raw = L.raw + (size_t)b * TPn * pl.row_w;
+  for (int i = tid; i < TPn * NS; i += nt) {
+    const int k = i / NS, z = i - k * NS;
+    const double ring = s.D > 1 ? s.ringf * raw[k * pl.row_w + 2 * G + 1] : 0.0;
+    L.sync[b * TPn * NS + i] = s.D > 1 ? ring / L.link[z] : 0.0;
+    if (z == 0) L.ring[b * TPn + k] = ring;
+  }
+  const int layers = pl.st_n[s.rs + j];
+  for (int k = tid; k < TPn; k += nt) {
+    const int kk = STP ? k : s.it, tpk = pl.vals[pl.DP + kk];
+    const uint64_t bytes = (uint64_t)__double_as_longlong(raw[k * pl.row_w + 2 * G]) +
+                           act_bytes(min(s.P - j, s.nb), layers, pl.act[s.im * TP + kk]);
+    uint32_t m = 0;
+    for (int g = 0; g < G; ++g)
+      if (bytes + pl.res[g] <= pl.cap[g] && tpk <= pl.node[g]) m |= 1u << g;
+    L.fit[b * TPn + k] = m;
+  }
+}
+
+// ---- one choice ----
+
+struct SAcc {          // what a placement carries besides its pool counts
+  SPart part[2];
+  double msync, mupd, dol, comm;
+};
+
+// One kind of pipeline goes on from pool zone pz to a stage of compute time c in zone z (no
+// stage before it for par = NULL).  The order of the operations is part of the definition: sums in
+// stage order, a closed stage's transfers forward then backward.
+__device__ __forceinline__ SPart search_close(const SPart *par, int pz, int z, int Z, double c, const double *xfer) {
+  SPart o;
+  o.c_open = c;
+  if (!par) {
+    o.sum = o.maxt = o.xb_open = 0.0;
+  } else {
+    const double closed = par->c_open + (xfer[pz * Z + z] + par->xb_open);
+    o.sum = par->sum + closed;
+    o.maxt = fmax(par->maxt, closed);
+    o.xb_open = xfer[z * Z + pz];
+  }
+  return o;
+}
+
+// Lower bound of a kind of pipeline's time over the completions.
+__device__ __forceinline__ double search_pipe(const SPart &o, double Ssum, double Smax, double nbm1) {
+  const double t_open = o.c_open + o.xb_open;
+  return ((o.sum + t_open) + Ssum) + nbm1 * fmax(fmax(o.maxt, t_open), Smax);
+}
+
+// Stage j on pool a (split stages: half of its replicas on pool b, else b = a) at TP index k (a
+// TP degree per stage; else 0) behind the placement par (NULL for j = 0): may it be placed, and
+// what the placement then carries.
+template <int MODE>
+__device__ __forceinline__ bool search_step(const DevPlan &pl, const SearchLds &L, const SearchSub &s,
+                                            const SState<MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP> *par, int tb,
+                                            int a, int b, int k, int max_runs, SAcc &o, int &runs) {
+  constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
+  constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
+  const int G = pl.G, Z = pl.Z, TPn = STP ? pl.TP : 1;
+  const uint32_t zga = L.zg[a], zgb = SPLIT ? L.zg[b] : zga;
+  const int za = zga & 255u, ga = zga >> 8, zb = zgb & 255u, gb = zgb >> 8;
+  const uint32_t fit = L.fit[tb * TPn + k];
+  const int width = STP ? L.width[k] : 1;
+  const uint16_t *cnt = reinterpret_cast<const uint16_t *>(par + 1);
+  const int ca = par ? (int)cnt[a] : 0;
+  bool ok = ((fit >> ga) & 1u) != 0;
+  if (!SPLIT) {
+    ok = ok && ca + width <= L.cap[a];
+  } else {
+    ok = ok && ((fit >> gb) & 1u) != 0;
+    if (a == b) ok = ok && ca + 2 * width <= L.cap[a];
+    else ok = ok && (s.D & 1) == 0 && ca + width <= L.cap[a] && (par ? (int)cnt[b] : 0) + width <= L.cap[b];
+  }
+  runs = par ? par->runs + ((a != par->pool || (SPLIT && b != par->pool_b) || (STP && k != par->tpi)) ? 1 : 0) : 1;
+  if (max_runs != 0 && runs > max_runs) ok = false;
+  if (!ok) return false;
+  const double *raw = L.raw + (size_t)(tb * TPn + k) * pl.row_w;
+  const int pza = par ? (int)(L.zg[par->pool] & 255u) : 0, pzb = SPLIT && par ? (int)(L.zg[par->pool_b] & 255u) : 0;
+  o.part[0] = search_close(par ? &par->part[0] : nullptr, pza, za, Z, raw[ga], L.xfer);
+  if (SPLIT) o.part[1] = search_close(par ? &par->part[SPLIT ? 1 : 0] : nullptr, pzb, zb, Z, raw[gb], L.xfer);
+  // the stage by itself: all-reduce over the slowest link of a ring through both pools, the
+  // slower update, the mean rent, the ring's traffic between the zones
+  const double sync = SPLIT ? L.sync[(tb * TPn + k) * Z * Z + za * Z + zb] : L.sync[(tb * TPn + k) * Z + za];
+  const double upd = SPLIT ? fmax(raw[G + ga], raw[G + gb]) : raw[G + ga];
+  const double dol = L.dtp[k] * (SPLIT ? 0.5 * (L.price[ga] + L.price[gb]) : L.price[ga]);
+  const double ring = SPLIT && zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
+  if (!par) {
+    o.msync = sync; o.mupd = upd; o.dol = dol; o.comm = ring;
+  } else {
+    o.msync = fmax(par->msync, sync);
+    o.mupd = fmax(par->mupd, upd);
+    o.dol = par->dol + dol;
+    double comm = par->comm;
+    if (pza != za) comm += L.comm[pza * Z + za];
+    if (SPLIT && pzb != zb) comm += L.comm[pzb * Z + zb];
+    o.comm = SPLIT ? comm + ring : comm;
+  }
+  return true;
+}
+
+// Lower bounds of T_iter and C_iter over the completions of a placement whose stage j is open
+// (the plan's own values when j = P - 1, where every S term is zero); with split stages the
+// slower of the two kinds of pipeline counts (Sec. 4.3).
+template <bool SPLIT>
+__device__ __forceinline__ SBound search_bound(const SAcc &o, const double *S, int P_max, int j, double nbm1) {
+  double pipe = search_pipe(o.part[0], S[j], S[P_max + j], nbm1);
+  if (SPLIT) pipe = fmax(pipe, search_pipe(o.part[1], S[j], S[P_max + j], nbm1));
+  SBound b;
+  b.T = (pipe + fmax(o.msync, S[2 * P_max + j])) + fmax(o.mupd, S[3 * P_max + j]);
+  b.C = (o.dol + S[4 * P_max + j]) / 3600.0 * b.T + o.comm;
+  return b;
+}
+
+// Whether a bound is dropped, and its sort key (non-negative: its bits order like the value).
+__device__ __forceinline__ bool search_keep(const SearchArgs &a, const SBound &b, unsigned long long &kbits) {
+  const double key = a.objective == 0 ? b.T : b.C;
+  bool drop = false;
+  if (a.has_bound) drop = a.objective == 0 ? b.C > a.bound : 1.0 / b.T < a.bound;
+  if (a.has_inc && key > a.inc) drop = true;
+  kbits = (unsigned long long)__double_as_longlong(key);
+  return !drop;
+}
+
+// ---- the first level of every sub-problem ----
+
+// One wave per sub-problem.  Most sub-problems end here: their batch does not divide, a stage fits
+// nowhere, or no placement of the first stage survives its bound.
+template <int MODE>
+__global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, SearchArgs a, uint32_t wave_words) {
+  constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
+  constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
+  extern __shared__ double search_lds[];
+  __shared__ unsigned long long s_exp[kRootWaves];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int ZG = pl.ZGr, TPn = STP ? pl.TP : 1, NCH = SPLIT ? ZG * ZG * TPn : ZG * TPn;
+  SearchLds L;
+  search_carve(pl, SPLIT, STP, true, a, search_lds + wv * wave_words, L);
+  unsigned long long expanded = 0;
+  for (uint32_t sid = blockIdx.x * kRootWaves + wv; sid < a.n_sub; sid += gridDim.x * kRootWaves) {
+    const SearchSub s = search_sub<STP>(pl, a, sid);
+    if (s.nb == 0) continue;  // (uniform over the wave, like what follows)
+    wave_lds_fence();         // the tables are reused
+    for (int i = lane; i < TPn * (int)pl.row_w; i += 64) L.raw[i] = search_row<STP>(pl, s, 0)[i];
+    const bool fine = search_tables<MODE, true>(pl, s, L, lane, 64);
+    if (__builtin_amdgcn_ballot_w64(!fine) != 0) continue;
+    wave_lds_fence();
+    search_suffix(pl, s, L, lane);
+    search_level<MODE>(pl, s, L, 0, 0, lane, 64);
+    wave_lds_fence();
+    bool alive = false;
+    uint32_t mine = 0;
+    for (int c = lane; c < NCH; c += 64) {
+      const int k = STP ? c % TPn : 0, pools = STP ? c / TPn : c;
+      const int pa = SPLIT ? pools / ZG : pools, pb = SPLIT ? pools - pa * ZG : pa;
+      SAcc o;
+      int runs;
+      if (!search_step<MODE>(pl, L, s, nullptr, 0, pa, pb, k, a.max_runs, o, runs)) continue;
+      ++mine;
+      unsigned long long kbits;
+      alive = search_keep(a, search_bound<SPLIT>(o, L.S, pl.P_max, 0, s.nbm1), kbits) || alive;
+    }
+    if (__builtin_amdgcn_ballot_w64(alive) != 0) {  // (counted again, with its other levels, by k_search_beam)
+      if (lane == 0)
+        a.list[(STP ? a.pps[s.ip].sub_off_t : a.pps[s.ip].sub_off) + atomicAdd(&a.counters[s.ip], 1u)] = sid;
+    } else {
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
+      expanded += mine;
+    }
+  }
+  if (lane == 0) s_exp[wv] = expanded;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kRootWaves; ++w) expanded += s_exp[w];
+    a.root_expanded[blockIdx.x] = expanded;
+  }
+}
+
+// ---- the W smallest ----
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_move(double v) {  // lanes without a source keep their own value
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t l = (uint32_t)b, h = (uint32_t)(b >> 32);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)l, (int)l, CTRL, ROWS, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)h, (int)h, CTRL, ROWS, 0xF, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Minimum / maximum over a wave, in its last lane.
+template <bool MIN>
+__device__ __forceinline__ double wave_extreme_last(double v) {
+  auto f = [](double x, double y) { return MIN ? fmin(x, y) : fmax(x, y); };
+  v = f(v, lane_move<0x111, 0xF>(v));  // row_shr:1, 2, 4, 8: within rows of 16 lanes
+  v = f(v, lane_move<0x112, 0xF>(v));
+  v = f(v, lane_move<0x114, 0xF>(v));
+  v = f(v, lane_move<0x118, 0xF>(v));
+  v = f(v, lane_move<0x142, 0xA>(v));  // row_bcast:15, 31: across rows
+  v = f(v, lane_move<0x143, 0xC>(v));
+  return v;
+}
+
+// Ascending bitonic sort of (key, id) pairs in LDS; m = the power of two >= n; entries
+// n .. m-1 (which must exist) are filled with the largest pair first.
 __device__ __forceinline__ void search_sort(unsigned long long *key, uint32_t *id, int n) {
   int m = 1;
   while (m < n) m <<= 1;
-  for (int i = n + (int)threadIdx.x; i < m; i += blockDim.x) { key[i] = ~0ull; id[i] = ~0u; }
+  for (int i = n + (int)threadIdx.x; i < m; i += kSearchThreads) { key[i] = ~0ull; id[i] = ~0u; }
   __syncthreads();
   for (int k = 2; k <= m; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < m; i += blockDim.x) {
+      for (int i = threadIdx.x; i < m; i += kSearchThreads) {
         const int x = i ^ j;
         if (x > i) {
           const bool up = (i & k) == 0;
@@ -129,455 +549,360 @@ __device__ __forceinline__ void search_sort(unsigned long long *key, uint32_t *i
     }
 }
 
-struct SearchTables {  // LDS of a search workgroup: the sub-problem's and the level's tables
-  double S[5][kSearchMaxStages + 1];   // what lies behind stage i: sum, max, sync, upd, $
-  double xfer[kMaxZones][kMaxZones], comm[kMaxZones][kMaxZones];
-  double comm_half[kMaxZones][kMaxZones];  // traffic of one kind of pipeline (half of the replicas)
-  double bw[kMaxZones][kMaxZones], ring_price[kMaxZones][kMaxZones];
-  double l_c[kMaxTypes], l_upd[kMaxTypes], l_dol[kMaxTypes], l_price[kMaxTypes], l_sync[kMaxZones];
-  double l_ring;                       // bytes the level's stage's ring all-reduce moves over every link
-  double smin[4][kSearchMaxStages + 1];  // cheapest admissible choice of every stage
-  int cap[kSearchMaxPools];            // stages a pool can host
-  int cap_half[kSearchMaxPools];       // halves of stages
-  uint32_t l_fit;                      // bit g: the level's stage fits type g
-  int dp_even;
-  double dtp;                          // D * tp
-  // a TP degree per stage: the level's stage on every type / zone at every degree
-  double l_c3[kMaxTypes][kMaxTP], l_upd3[kMaxTypes][kMaxTP], l_dol3[kMaxTypes][kMaxTP];
-  double l_sync3[kMaxZones][kMaxTP];
-  uint32_t l_fit3[kMaxTP];             // bit g: the level's stage fits type g at this degree
-  int tpv[kMaxTP];
-  int cap_gpus[kSearchMaxPools];       // GPUs one replica can take from a pool
-  // ... and two pools per stage as well
-  double l_ring3[kMaxTP];              // the level's stage's ring bytes at every degree
-  int cap_half_gpus[kSearchMaxPools];  // GPUs of one replica, counted once per half of a stage
-  long long dp;                        // D
+struct SelectShared {
+  double ext[2 * (kSearchThreads / 64)];
+  unsigned long long lo, hi;
+  uint32_t bin, below, upto, n;
 };
 
-struct SAcc {          // what a placement carries besides its pool counts
-  double sum, maxt, c_open, xb_open, sum_b, maxt_b, c_open_b, xb_open_b, msync, mupd, dol, comm;
-};
-
-// Stage j on pool a (split stages: half of its replicas on pool b, else b = a) at TP index k (a
-// TP degree per stage; else the sub-problem's) behind the placement par (none for j = 0): may
-// it be placed, and what the placement then carries.  The order of the operations is part of
-// the definition: sums in stage order, a closed stage's transfers forward then backward.
-template <int MODE>
-__device__ __forceinline__ bool search_step(const SearchTables &T, const SState *par, int j, int a, int b,
-                                            int k, int G, int max_runs, SAcc &o, int &runs) {
-  constexpr bool SPLIT = MODE == SEARCH_SPLIT;
-  if (MODE == SEARCH_SPLIT_TP) {
-    const int ga = a % G, za = a / G, gb = b % G, zb = b / G, width = T.tpv[k];
-    bool ok = ((T.l_fit3[k] >> ga) & 1u) != 0 && ((T.l_fit3[k] >> gb) & 1u) != 0;
-    const int ca = par ? (int)par->cnt[a] : 0, cb = par ? (int)par->cnt[b] : 0;
-    if (a == b) ok = ok && ca + 2 * width <= T.cap_half_gpus[a];
-    else ok = ok && T.dp_even && ca + width <= T.cap_half_gpus[a] && cb + width <= T.cap_half_gpus[b];
-    runs = par ? par->runs + ((a != par->pool || b != par->pool_b || k != par->tpi) ? 1 : 0) : 1;
-    if (max_runs != 0 && runs > max_runs) ok = false;
-    if (!ok) return false;
-    double link = T.bw[za][za];
-    if (zb != za) link = fmin(fmin(link, T.bw[zb][zb]), fmin(T.bw[za][zb], T.bw[zb][za]));
-    const double sync = T.l_ring3[k] / link;
-    const double upd = fmax(T.l_upd3[ga][k], T.l_upd3[gb][k]);
-    const double dol = (double)(T.dp * (long long)width) * (0.5 * (T.l_price[ga] + T.l_price[gb]));
-    const double ring = zb != za ? T.l_ring3[k] * T.ring_price[za][zb] : 0.0;
-    o.c_open = T.l_c3[ga][k];
-    o.c_open_b = T.l_c3[gb][k];
-    if (!par) {
-      o.sum = o.maxt = o.xb_open = o.sum_b = o.maxt_b = o.xb_open_b = 0.0;
-      o.msync = sync; o.mupd = upd; o.dol = dol; o.comm = ring;
-    } else {
-      const int pza = par->pool / G, pzb = par->pool_b / G;
-      const double ta = par->c_open + (T.xfer[pza][za] + par->xb_open);  // forward, then backward
-      const double tb = par->c_open_b + (T.xfer[pzb][zb] + par->xb_open_b);
-      o.sum = par->sum + ta;
-      o.maxt = fmax(par->maxt, ta);
-      o.sum_b = par->sum_b + tb;
-      o.maxt_b = fmax(par->maxt_b, tb);
-      o.xb_open = T.xfer[za][pza];
-      o.xb_open_b = T.xfer[zb][pzb];
-      o.msync = fmax(par->msync, sync);
-      o.mupd = fmax(par->mupd, upd);
-      o.dol = par->dol + dol;
-      double comm = par->comm;
-      if (pza != za) comm += T.comm_half[pza][za];
-      if (pzb != zb) comm += T.comm_half[pzb][zb];
-      o.comm = comm + ring;
+// The m pairs of (okey, oid), ranked by counting each one's predecessors -- by_id: in the order
+// of their ids -- back to the first places of (key, id), as far as they rank below W.
+__device__ __forceinline__ void search_place(const SearchLds &L, int m, int W, bool by_id) {
+  const int t = threadIdx.x;
+  int np = 64;
+  while (np < m) np <<= 1;
+  if (np <= kSearchThreads) {  // several threads share a pair
+    const int q = t & (np - 1), row = t / np, rows = kSearchThreads / np;
+    if (q < m) {
+      const unsigned long long mk = by_id ? 0 : L.okey[q];
+      const uint32_t mi = L.oid[q];
+      uint32_t before = 0;
+#pragma unroll 4
+      for (int x = row; x < m; x += rows) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
+      if (before) atomicAdd(&L.rank[q], before);
     }
-    return true;
-  }
-  if (MODE == SEARCH_STAGE_TP) {
-    const int g = a % G, z = a / G, t = k;
-    bool ok = ((T.l_fit3[t] >> g) & 1u) != 0;
-    const int used = par ? (int)par->cnt[a] : 0;
-    ok = ok && used + T.tpv[t] <= T.cap_gpus[a];
-    runs = par ? par->runs + ((a != par->pool || t != par->tpi) ? 1 : 0) : 1;
-    if (max_runs != 0 && runs > max_runs) ok = false;
-    if (!ok) return false;
-    o.c_open = T.l_c3[g][t];
-    if (!par) {
-      o.sum = 0.0; o.maxt = 0.0; o.xb_open = 0.0; o.msync = T.l_sync3[z][t]; o.mupd = T.l_upd3[g][t];
-      o.dol = T.l_dol3[g][t]; o.comm = 0.0;
-    } else {
-      const int pz = par->pool / G;
-      const double t_closed = par->c_open + (T.xfer[pz][z] + par->xb_open);  // forward, then backward
-      o.sum = par->sum + t_closed;
-      o.maxt = fmax(par->maxt, t_closed);
-      o.xb_open = T.xfer[z][pz];
-      o.msync = fmax(par->msync, T.l_sync3[z][t]);
-      o.mupd = fmax(par->mupd, T.l_upd3[g][t]);
-      o.dol = par->dol + T.l_dol3[g][t];
-      o.comm = pz != z ? par->comm + T.comm[pz][z] : par->comm;
-    }
-    o.sum_b = o.maxt_b = o.c_open_b = o.xb_open_b = 0.0;
-    return true;
-  }
-  const int ga = a % G, za = a / G, gb = b % G, zb = b / G;
-  bool ok = ((T.l_fit >> ga) & 1u) != 0 && ((T.l_fit >> gb) & 1u) != 0;
-  const int ca = par ? (int)par->cnt[a] : 0, cb = par ? (int)par->cnt[b] : 0;
-  if (!SPLIT) ok = ok && ca + 1 <= T.cap[a];
-  else if (a == b) ok = ok && ca + 2 <= T.cap_half[a];
-  else ok = ok && T.dp_even && ca + 1 <= T.cap_half[a] && cb + 1 <= T.cap_half[b];
-  runs = par ? par->runs + ((a != par->pool || (SPLIT && b != par->pool_b)) ? 1 : 0) : 1;
-  if (max_runs != 0 && runs > max_runs) ok = false;
-  if (!ok) return false;
-  if (!SPLIT) {
-    o.c_open = T.l_c[ga];
-    if (!par) {
-      o.sum = 0.0; o.maxt = 0.0; o.xb_open = 0.0; o.msync = T.l_sync[za]; o.mupd = T.l_upd[ga];
-      o.dol = T.l_dol[ga]; o.comm = 0.0;
-    } else {
-      const int pz = par->pool / G;
-      const double t_closed = par->c_open + (T.xfer[pz][za] + par->xb_open);  // forward, then backward
-      o.sum = par->sum + t_closed;
-      o.maxt = fmax(par->maxt, t_closed);
-      o.xb_open = T.xfer[za][pz];
-      o.msync = fmax(par->msync, T.l_sync[za]);
-      o.mupd = fmax(par->mupd, T.l_upd[ga]);
-      o.dol = par->dol + T.l_dol[ga];
-      o.comm = pz != za ? par->comm + T.comm[pz][za] : par->comm;
-    }
-    o.sum_b = o.maxt_b = o.c_open_b = o.xb_open_b = 0.0;
-    return true;
-  }
-  // the stage by itself: all-reduce over the slowest link of a ring through both pools, the
-  // slower update, the mean rent, the ring's traffic between the zones
-  double link = T.bw[za][za];
-  if (zb != za) link = fmin(fmin(link, T.bw[zb][zb]), fmin(T.bw[za][zb], T.bw[zb][za]));
-  const double sync = T.l_ring / link;
-  const double upd = fmax(T.l_upd[ga], T.l_upd[gb]);
-  const double dol = T.dtp * (0.5 * (T.l_price[ga] + T.l_price[gb]));
-  const double ring = zb != za ? T.l_ring * T.ring_price[za][zb] : 0.0;
-  o.c_open = T.l_c[ga];
-  o.c_open_b = T.l_c[gb];
-  if (!par) {
-    o.sum = o.maxt = o.xb_open = o.sum_b = o.maxt_b = o.xb_open_b = 0.0;
-    o.msync = sync; o.mupd = upd; o.dol = dol; o.comm = ring;
   } else {
-    const int pza = par->pool / G, pzb = par->pool_b / G;
-    const double ta = par->c_open + (T.xfer[pza][za] + par->xb_open);
-    const double tb = par->c_open_b + (T.xfer[pzb][zb] + par->xb_open_b);
-    o.sum = par->sum + ta;
-    o.maxt = fmax(par->maxt, ta);
-    o.sum_b = par->sum_b + tb;
-    o.maxt_b = fmax(par->maxt_b, tb);
-    o.xb_open = T.xfer[za][pza];
-    o.xb_open_b = T.xfer[zb][pzb];
-    o.msync = fmax(par->msync, sync);
-    o.mupd = fmax(par->mupd, upd);
-    o.dol = par->dol + dol;
-    double comm = par->comm;
-    if (pza != za) comm += T.comm_half[pza][za];
-    if (pzb != zb) comm += T.comm_half[pzb][zb];
-    o.comm = comm + ring;
+    for (int q = t; q < m; q += kSearchThreads) {
+      const unsigned long long mk = by_id ? 0 : L.okey[q];
+      const uint32_t mi = L.oid[q];
+      uint32_t before = 0;
+#pragma unroll 4
+      for (int x = 0; x < m; ++x) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
+      L.rank[q] = before;
+    }
   }
-  return true;
+  __syncthreads();
+  for (int q = t; q < m; q += kSearchThreads) {
+    const uint32_t r = L.rank[q];
+    if (r < (uint32_t)W) { L.key[r] = L.okey[q]; L.id[r] = L.oid[q]; }
+  }
+  __syncthreads();
 }
 
-// Bounds of a placement whose stage j is open; with split stages the slower of the two kinds
-// of pipeline counts (Sec. 4.3).
-template <int MODE>
-__device__ __forceinline__ SBound search_bound_of(const SearchTables &T, const SAcc &o, int j, double nbm1) {
-  if (MODE != SEARCH_SPLIT && MODE != SEARCH_SPLIT_TP)
-    return search_bounds(o.sum, o.maxt, o.c_open, o.xb_open, o.msync, o.mupd, o.dol, o.comm, T.S[0][j],
-                         T.S[1][j], T.S[2][j], T.S[3][j], T.S[4][j], nbm1);
-  const double ta = o.c_open + o.xb_open, tb = o.c_open_b + o.xb_open_b;
-  const double pa = ((o.sum + ta) + T.S[0][j]) + nbm1 * fmax(fmax(o.maxt, ta), T.S[1][j]);
-  const double pb = ((o.sum_b + tb) + T.S[0][j]) + nbm1 * fmax(fmax(o.maxt_b, tb), T.S[1][j]);
-  SBound b;
-  b.T = (fmax(pa, pb) + fmax(o.msync, T.S[2][j])) + fmax(o.mupd, T.S[3][j]);
-  b.C = (o.dol + T.S[4][j]) / 3600.0 * b.T + o.comm;
-  return b;
+// Brings the W smallest of the n > W (key, id) pairs to the front of the buffer, in ascending
+// order.  A histogram over the range of the keys finds the bin the W-th lies in (again within that
+// bin while too many share it); what lies in it or before it is ranked.  The buffer must be
+// visible; it is again on return.
+__device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &sh, int n, int W, int gather) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  double lo = __builtin_huge_val(), hi = 0.0;
+  for (int e = t; e < n; e += kSearchThreads) {
+    const double x = __longlong_as_double((long long)L.key[e]);
+    lo = fmin(lo, x);
+    hi = fmax(hi, x);
+  }
+  lo = wave_extreme_last<true>(lo);
+  hi = wave_extreme_last<false>(hi);
+  if (lane == 63) { sh.ext[2 * wv] = lo; sh.ext[2 * wv + 1] = hi; }
+  for (int x = t; x < kSearchBins; x += kSearchThreads) L.hist[x] = 0;
+  __syncthreads();
+  lo = sh.ext[0]; hi = sh.ext[1];
+  for (int w = 1; w < kSearchThreads / 64; ++w) { lo = fmin(lo, sh.ext[2 * w]); hi = fmax(hi, sh.ext[2 * w + 1]); }
+  int below = 0;  // pairs under lo
+  for (int round = 0;; ++round) {  // uniform
+    const double scale = hi > lo ? (double)kSearchBins / (hi - lo) : 0.0;
+    auto bin_of = [&](double x) { return min((int)((x - lo) * scale), kSearchBins - 1); };
+    for (int e = t; e < n; e += kSearchThreads) {
+      const double x = __longlong_as_double((long long)L.key[e]);
+      if (x >= lo && x <= hi) atomicAdd(&L.hist[bin_of(x)], 1u);
+    }
+    if (t == 0) { sh.n = 0; sh.lo = ~0ull; sh.hi = 0; }
+    __syncthreads();
+    if (wv == 0) {  // the bin of the W-th
+      constexpr int kPer = kSearchBins / 64;
+      uint32_t h[kPer], sum = 0;
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) { h[q] = L.hist[lane * kPer + q]; sum += h[q]; }
+      uint32_t incl = sum;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+      }
+      uint32_t excl = (uint32_t)below + incl - sum;
+      if (excl < (uint32_t)W && (uint32_t)W <= excl + sum) {
+        int b = 0;
+#pragma unroll
+        for (int q = 0; q < kPer - 1; ++q)
+          if (b == q && excl + h[q] < (uint32_t)W) { excl += h[q]; b = q + 1; }
+        uint32_t hb = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) hb = b == q ? h[q] : hb;
+        sh.bin = (uint32_t)(lane * kPer + b);
+        sh.below = excl;
+        sh.upto = excl + hb;
+      }
+    }
+    __syncthreads();
+    const int bin = (int)sh.bin, m = (int)sh.upto;
+    if (m <= gather) {
+      for (int e = t; e < n; e += kSearchThreads) {
+        const unsigned long long kb = L.key[e];
+        const double x = __longlong_as_double((long long)kb);
+        if (x < lo || (x <= hi && bin_of(x) <= bin)) {
+          const uint32_t at = atomicAdd(&sh.n, 1u);
+          L.okey[at] = kb;
+          L.oid[at] = L.id[e];
+        }
+      }
+      for (int x = t; x < m; x += kSearchThreads) L.rank[x] = 0;
+      __syncthreads();
+      search_place(L, m, W, false);
+      return;
+    }
+    if (scale == 0.0 || round == 3) break;  // (equal keys, or a range the bins do not separate)
+    for (int e = t; e < n; e += kSearchThreads) {
+      const unsigned long long kb = L.key[e];
+      const double x = __longlong_as_double((long long)kb);
+      if (x >= lo && x <= hi && bin_of(x) == bin) { atomicMin(&sh.lo, kb); atomicMax(&sh.hi, kb); }
+    }
+    for (int x = t; x < kSearchBins; x += kSearchThreads) L.hist[x] = 0;
+    below = (int)sh.below;
+    __syncthreads();
+    lo = __longlong_as_double((long long)sh.lo);
+    hi = __longlong_as_double((long long)sh.hi);
+    __syncthreads();  // (read before the next round resets them)
+  }
+  search_sort(L.key, L.id, n);
 }
+
+// ---- the levels ----
 
 template <int MODE>
 __global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, SearchArgs a) {
-  constexpr bool BOTH = MODE == SEARCH_SPLIT_TP;
-  constexpr bool SPLIT = MODE == SEARCH_SPLIT || BOTH;     // two pools per stage
-  constexpr bool STP = MODE == SEARCH_STAGE_TP || BOTH;    // a TP degree per stage
-  __shared__ SearchTables T;
-  __shared__ unsigned long long b_key[kSearchBuf];
-  __shared__ uint32_t b_id[kSearchBuf];
-  __shared__ uint32_t s_wave[kSearchThreads / 64];
-  __shared__ int s_nbuf, s_bad;
+  constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;   // two pools per stage
+  constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;  // a TP degree per stage
+  using State = SState<SPLIT>;
+  extern __shared__ double search_lds[];
+  __shared__ SelectShared sh;
+  // candidates buffered (items; choices behind them) and kept in all; two sets, used by levels in turn
+  __shared__ uint32_t s_n[2], s_m[2], s_kept[2], s_next;
+  __shared__ unsigned long long s_expanded;
   __shared__ unsigned long long s_bk[kSearchThreads / 64];
   __shared__ uint32_t s_bi[kSearchThreads / 64];
-  __shared__ unsigned long long s_expanded;
-  __shared__ unsigned char s_fit3[kMaxTypes][kMaxTP];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP, DP = pl.DP;
-  // choices per stage: a pool; a pair (a, b) = a * ZG + b; a pool and a TP index (a, t) = a * TP + t;
-  // a pair and a TP index ((a * ZG + b) * TP + t)
-  const int NCH = BOTH ? ZG * ZG * TP : (SPLIT ? ZG * ZG : (STP ? ZG * TP : ZG));
-  // a choice c -> first pool, second pool (= the first without split stages), TP index
-  auto choice = [&](int c, int it0, int &ca, int &cb, int &ck) {
-    ck = STP ? c % TP : it0;
-    const int pools = STP ? c / TP : c;
-    ca = SPLIT ? pools / ZG : pools;
+  const int ZG = pl.ZGr, Z = pl.Z, G = pl.G, TPn = STP ? pl.TP : 1, W = a.W, P_max = pl.P_max;
+  // a choice: (a, k), or with split stages (a, b, k); an item: the choices that differ in the
+  // inner digit only (k, or b), of which the best stands for all at first
+  const int NCH = SPLIT ? ZG * ZG * TPn : ZG * TPn, ITEMS = SPLIT ? ZG * TPn : ZG, INNER = SPLIT ? ZG : TPn;
+  SearchLds L;
+  search_carve(pl, SPLIT, STP, false, a, search_lds, L);
+  const uint32_t mg_items = search_magic(ITEMS), mg_zg = search_magic(ZG), mg_tpn = search_magic(TPn), mg_inner = search_magic(INNER);
+  const int gather = (int)search_gather((uint32_t)W, a.buf), buf = (int)a.buf;
+  const uint32_t sw = search_state_words(SPLIT, ZG);
+  double *const states = a.states ? a.states + (size_t)blockIdx.x * 2 * W * sw : L.states;
+  uint32_t *const history = a.history ? a.history + (size_t)blockIdx.x * P_max * W : L.history;
+  SubResult *const res = a.results + blockIdx.x;
+  const bool need_c = a.objective != 0 || a.has_bound != 0;
+  unsigned long long wg_key = ~0ull;  // the workgroup's best so far
+  uint32_t wg_sid = ~0u, wg_trunc = 0;
+  unsigned long long my_total = 0;    // placements this thread generated
+  uint32_t n_alive = 0;
+  for (int i = 0; i < a.n_pp; ++i) n_alive += a.counters[i];
+  auto state_at = [&](int frontier, int r) { return reinterpret_cast<State *>(states + ((size_t)frontier * W + r) * sw); };
+  // a candidate's state, pools and TP index from its number r * NCH + (a, k) / (a, b, k)
+  auto choice = [&](uint32_t cand, int &r, int &ca, int &cb, int &ck) {
+    r = (int)(cand / (uint32_t)NCH);
+    const int c = (int)cand - r * NCH, pools = STP ? (int)fast_div((uint32_t)c, mg_tpn) : c;  // c < 2^15
+    ck = STP ? c - pools * TPn : 0;
+    ca = SPLIT ? (int)fast_div((uint32_t)pools, mg_zg) : pools;
     cb = SPLIT ? pools - ca * ZG : ca;
   };
-  uint8_t *const buf0 = a.states + (size_t)blockIdx.x * 2 * a.W * a.state_stride;
-  uint8_t *const buf1 = buf0 + (size_t)a.W * a.state_stride;
+  if (t == 0) s_expanded = 0;
 
-  for (uint32_t sid = blockIdx.x; sid < a.n_sub; sid += gridDim.x) {  // uniform
-    __syncthreads();  // the shared tables are reused
-    int ip = 0;
-    for (int i = 1; i < a.n_pp; ++i)
-      if (sid >= (STP ? a.pps[i].sub_off_t : a.pps[i].sub_off)) ip = i;
-    const SearchPP pp = a.pps[ip];
-    uint32_t rem = sid - (STP ? pp.sub_off_t : pp.sub_off);
-    const int im = (int)(rem % (uint32_t)MB); rem /= (uint32_t)MB;
-    const int id = (int)(rem % (uint32_t)DP); rem /= (uint32_t)DP;
-    const int it = STP ? 0 : (int)(rem % (uint32_t)TP);  // (TP per stage: not part of the sub-problem)
-    const int q = STP ? (int)rem : (int)(rem / (uint32_t)TP);
-    const int P = pp.P;
-    const uint32_t rs = pp.rs0 + (uint32_t)q * (uint32_t)P;
-    SubResult *res = a.results + sid;
-    const int64_t nb = pl.nb[im * DP + id];
-    const int64_t D = pl.dpv[id];
-    const int tp = pl.tpv[it];
-    if (t == 0) {
-      res->found = 0; res->truncated = 0; res->expanded = 0; res->sid = sid; res->P = (uint32_t)P;
-      res->desc[0] = ip; res->desc[1] = q; res->desc[2] = it; res->desc[3] = id; res->desc[4] = im;
-      res->desc[5] = MODE;
-      s_bad = 0;
-      s_expanded = 0;
-      T.dp_even = (D % 2 == 0) ? 1 : 0;
-      T.dtp = (double)(D * tp);
-      T.dp = (long long)D;
-    }
+  for (;;) {  // sub-problems, the deepest pipelines first (uniform; ends when the list is used up)
+    __syncthreads();  // the tables are reused
+    if (t == 0) s_next = atomicAdd(&a.counters[a.n_pp], 1u);
     __syncthreads();
-    if (nb == 0) continue;              // the batch does not divide (uniform)
-    const double p2p = (double)pl.p2p[im];
-    const double nbm1 = (double)(nb - 1);
-    // tables of the sub-problem
-    for (int i = t; i < Z * Z; i += blockDim.x) {
-      const int z = i / Z, y = i - z * Z;
-      T.xfer[z][y] = p2p / pl.bw[z * Z + y];
-      T.bw[z][y] = pl.bw[z * Z + y];
-      double cm = 0.0, ch = 0.0, rp = 0.0;
-      if (pl.egress && z != y) {
-        const double both = pl.egress[z * Z + y] + pl.egress[y * Z + z];
-        cm = (double)nb * (double)D * p2p * both;
-        ch = (double)nb * (0.5 * (double)D) * p2p * both;
-        rp = both;
-      }
-      T.comm[z][y] = cm;
-      T.comm_half[z][y] = ch;
-      T.ring_price[z][y] = rp;
-    }
-    for (int p = t; p < ZG; p += blockDim.x) {
-      T.cap[p] = (int)((int64_t)pl.avail[p] / ((int64_t)tp * D));
-      T.cap_half[p] = (int)(2 * (int64_t)pl.avail[p] / ((int64_t)tp * D));
-      T.cap_gpus[p] = (int)((int64_t)pl.avail[p] / D);
-      T.cap_half_gpus[p] = (int)(2 * (int64_t)pl.avail[p] / D);
-    }
-    if (t < TP) T.tpv[t] = pl.tpv[t];
-    if (STP) {
-      for (int i = t; i < P; i += blockDim.x) {  // the cheapest admissible (type, TP) of stage i
-        const uint64_t params = pl.st_params[rs + i];
-        double cmin = __builtin_huge_val(), umin = cmin, dmin = cmin, smin = cmin;
-        bool any = false;
-        for (int k = 0; k < TP; ++k) {
-          const int tpk = pl.tpv[k];
-          const uint64_t bytes = stage_bytes_of(params, pl.st_n[rs + i], pl.bpp, i, P, tpk, nb, pl.act[im * TP + k]);
-          const uint64_t shard = (params + (uint64_t)tpk - 1) / (uint64_t)tpk;
-          bool fits_some = false;
-          for (int g = 0; g < G; ++g) {
-            if (!(bytes + pl.res[g] <= pl.cap[g] && tpk <= pl.node[g])) continue;
-            fits_some = true;
-            cmin = fmin(cmin, pl.st_c[(((size_t)(rs + i) * G + g) * MB + im) * TP + k]);
-            umin = fmin(umin, pl.st_u[((size_t)(rs + i) * G + g) * TP + k]);
-            dmin = fmin(dmin, (double)(D * tpk) * pl.price[g]);
-          }
-          if (!fits_some) continue;
-          any = true;
-          for (int z = 0; z < Z; ++z) {
-            double sync = 0.0;
-            if (D > 1) {
-              const double grad = (double)shard * (double)pl.gb;
-              sync = 2.0 * (double)(D - 1) / (double)D * grad / pl.bw[z * Z + z];
-            }
-            smin = fmin(smin, sync);
-          }
-        }
-        T.smin[0][i] = cmin; T.smin[1][i] = smin; T.smin[2][i] = umin; T.smin[3][i] = dmin;
-        if (!any) s_bad = 1;  // (benign race: every writer stores 1)
-      }
-    } else
-    for (int i = t; i < P; i += blockDim.x) {  // the cheapest admissible choice of stage i
-      const uint64_t params = pl.st_params[rs + i];
-      const uint64_t bytes = stage_bytes_of(params, pl.st_n[rs + i], pl.bpp, i, P, tp, nb, pl.act[im * TP + it]);
-      const uint64_t shard = (params + (uint64_t)tp - 1) / (uint64_t)tp;
-      double cmin = __builtin_huge_val(), umin = cmin, dmin = cmin, smin = cmin;
-      bool any = false;
-      for (int g = 0; g < G; ++g) {
-        if (!(bytes + pl.res[g] <= pl.cap[g] && tp <= pl.node[g])) continue;
-        any = true;
-        cmin = fmin(cmin, pl.st_c[(((size_t)(rs + i) * G + g) * MB + im) * TP + it]);
-        umin = fmin(umin, pl.st_u[((size_t)(rs + i) * G + g) * TP + it]);
-        dmin = fmin(dmin, (double)(D * tp) * pl.price[g]);
-      }
-      for (int z = 0; z < Z; ++z) {
-        double sync = 0.0;
-        if (D > 1) {
-          const double grad = (double)shard * (double)pl.gb;
-          sync = 2.0 * (double)(D - 1) / (double)D * grad / pl.bw[z * Z + z];
-        }
-        smin = fmin(smin, sync);
-      }
-      T.smin[0][i] = cmin; T.smin[1][i] = smin; T.smin[2][i] = umin; T.smin[3][i] = dmin;
-      if (!any) s_bad = 1;  // (benign race: every writer stores 1)
-    }
+    uint32_t turn = s_next;
+    if (turn >= n_alive) break;
+    int ip = a.n_pp - 1;
+    for (; ip > 0 && turn >= a.counters[ip]; --ip) turn -= a.counters[ip];
+    const uint32_t sid = a.list[(STP ? a.pps[ip].sub_off_t : a.pps[ip].sub_off) + turn];
+    const SearchSub s = search_sub<STP>(pl, a, sid);
+    const int P = s.P;
+    const int n_raw = TPn * (int)pl.row_w;
+    for (int i = t; i < n_raw; i += kSearchThreads) L.raw[i] = search_row<STP>(pl, s, 0)[i];
+    search_tables<MODE, false>(pl, s, L, t, kSearchThreads);
+    if (t == 0) s_n[0] = s_m[0] = s_kept[0] = 0;
     __syncthreads();
-    if (s_bad) continue;  // some stage fits no pool (uniform)
-    if (t == 0) {  // what lies behind stage i, accumulated from the last stage backwards
-      T.S[0][P - 1] = T.S[1][P - 1] = T.S[2][P - 1] = T.S[3][P - 1] = T.S[4][P - 1] = 0.0;
-      for (int i = P - 2; i >= 0; --i) {
-        T.S[0][i] = T.S[0][i + 1] + T.smin[0][i + 1];
-        T.S[1][i] = fmax(T.S[1][i + 1], T.smin[0][i + 1]);
-        T.S[2][i] = fmax(T.S[2][i + 1], T.smin[1][i + 1]);
-        T.S[3][i] = fmax(T.S[3][i + 1], T.smin[2][i + 1]);
-        T.S[4][i] = T.S[4][i + 1] + T.smin[3][i + 1];
-      }
-    }
+    if (wv == kSearchThreads / 64 - 1) search_suffix(pl, s, L, lane);
+    search_level<MODE>(pl, s, L, 0, 0, t, kSearchThreads);
     int n_cur = 1;  // frontier length; level 0 extends one empty placement
     bool truncated = false;
     for (int j = 0; j < P; ++j) {  // place stage j (uniform loop)
-      uint8_t *const cur = (j & 1) ? buf1 : buf0, *const nxt = (j & 1) ? buf0 : buf1;
-      __syncthreads();
-      // the level's tables: stage j on every type / zone
-      if (STP) {
-        if (t < G * TP) {  // (type g, TP index k)
-          const int g = t / TP, k = t - g * TP, tpk = pl.tpv[k];
-          const uint64_t params = pl.st_params[rs + j];
-          const uint64_t bytes = stage_bytes_of(params, pl.st_n[rs + j], pl.bpp, j, P, tpk, nb, pl.act[im * TP + k]);
-          T.l_c3[g][k] = pl.st_c[(((size_t)(rs + j) * G + g) * MB + im) * TP + k];
-          T.l_upd3[g][k] = pl.st_u[((size_t)(rs + j) * G + g) * TP + k];
-          T.l_dol3[g][k] = (double)(D * tpk) * pl.price[g];
-          if (k == 0) T.l_price[g] = pl.price[g];
-          s_fit3[g][k] = (bytes + pl.res[g] <= pl.cap[g] && tpk <= pl.node[g]) ? 1 : 0;
-        } else if (t >= 128 && t < 128 + Z * TP) {  // (zone z, TP index k)
-          const int z = (t - 128) / TP, k = (t - 128) - z * TP, tpk = pl.tpv[k];
-          const uint64_t params = pl.st_params[rs + j];
-          const uint64_t shard = (params + (uint64_t)tpk - 1) / (uint64_t)tpk;
-          double sync = 0.0, ring = 0.0;
-          if (D > 1) {
-            const double grad = (double)shard * (double)pl.gb;
-            sync = 2.0 * (double)(D - 1) / (double)D * grad / pl.bw[z * Z + z];
-            ring = 2.0 * (double)(D - 1) / (double)D * grad;
-          }
-          T.l_sync3[z][k] = sync;
-          if (z == 0) T.l_ring3[k] = ring;
-        }
-        __syncthreads();
-        if (t < TP) {
-          uint32_t m = 0;
-          for (int g = 0; g < G; ++g) m |= (uint32_t)s_fit3[g][t] << g;
-          T.l_fit3[t] = m;
-        }
-      } else if (t < G) {
-        const uint64_t params = pl.st_params[rs + j];
-        const uint64_t bytes = stage_bytes_of(params, pl.st_n[rs + j], pl.bpp, j, P, tp, nb, pl.act[im * TP + it]);
-        T.l_c[t] = pl.st_c[(((size_t)(rs + j) * G + t) * MB + im) * TP + it];
-        T.l_upd[t] = pl.st_u[((size_t)(rs + j) * G + t) * TP + it];
-        T.l_dol[t] = (double)(D * tp) * pl.price[t];
-        T.l_price[t] = pl.price[t];
-        const bool fits = bytes + pl.res[t] <= pl.cap[t] && tp <= pl.node[t];
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(fits);
-        if (t == 0) T.l_fit = (uint32_t)m;
-      } else if (t >= 64 && t < 64 + Z) {
-        const int z = t - 64;
-        const uint64_t params = pl.st_params[rs + j];
-        const uint64_t shard = (params + (uint64_t)tp - 1) / (uint64_t)tp;
-        double sync = 0.0, ring = 0.0;
-        if (D > 1) {
-          const double grad = (double)shard * (double)pl.gb;
-          sync = 2.0 * (double)(D - 1) / (double)D * grad / pl.bw[z * Z + z];
-          ring = 2.0 * (double)(D - 1) / (double)D * grad;
-        }
-        T.l_sync[z] = sync;
-        if (z == 0) T.l_ring = ring;
-      }
-      if (t == 0) s_nbuf = 0;
-      __syncthreads();
+      const int tb = j & 1, cur = j & 1, nxt = cur ^ 1;
       const bool last = j == P - 1;
-      const int n_total = n_cur * NCH;
+      __syncthreads();
+      if (t == 0) s_n[nxt] = s_m[nxt] = s_kept[nxt] = 0;
+      uint32_t *counter = &s_n[cur];
+      // the next level's records, requested now and stored when this level's candidates are in
+      double ahead = 0.0;
+      if (!last && t < n_raw) ahead = search_row<STP>(pl, s, j + 1)[t];
+      const double S0 = L.S[j], S1 = L.S[P_max + j], S2 = L.S[2 * P_max + j], S3 = L.S[3 * P_max + j], S4 = L.S[4 * P_max + j];
       unsigned long long best_k = ~0ull;  // last level: this thread's smallest (key, id)
       uint32_t best_i = ~0u;
-      uint32_t my_expanded = 0;
-      for (int row = 0; row * kSearchThreads < n_total; ++row) {  // uniform
-        const int cand = row * kSearchThreads + t;
-        bool keep = false;
-        unsigned long long kbits = 0;
-        if (cand < n_total) {
-          const int r = cand / NCH, c = cand - r * NCH;
-          int pa, pb, pk;
-          choice(c, it, pa, pb, pk);
-          const SState *par = j == 0 ? nullptr : reinterpret_cast<const SState *>(cur + (size_t)r * a.state_stride);
-          SAcc o;
-          int runs;
-          if (search_step<MODE>(T, par, j, pa, pb, pk, G, a.max_runs, o, runs)) {
-            my_expanded += 1;
-            const SBound b = search_bound_of<MODE>(T, o, j, nbm1);
-            const double key = a.objective == 0 ? b.T : b.C;
-            bool drop = false;
-            if (a.has_bound) drop = a.objective == 0 ? b.C > a.bound : 1.0 / b.T < a.bound;
-            if (a.has_inc && key > a.inc) drop = true;
-            keep = !drop;
-            kbits = (unsigned long long)__double_as_longlong(key);  // non-negative: orders like the value
-          }
-        }
+      unsigned long long tau = ~0ull;     // only keys up to this can be among the W smallest
+      uint32_t kept = 0, expanded = 0;
+      auto take = [&](bool keep, unsigned long long kb, uint32_t id) {  // whole waves
         if (last) {
-          if (keep && key_id_less(kbits, (uint32_t)cand, best_k, best_i)) { best_k = kbits; best_i = (uint32_t)cand; }
-          continue;
+          if (keep && key_id_less(kb, id, best_k, best_i)) { best_k = kb; best_i = id; }
+          return;
         }
-        // append the row's survivors in candidate order
+        keep = keep && kb <= tau;
         const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-        if (lane == 0) s_wave[wv] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t before = 0, row_total = 0;
-        for (int w = 0; w < kSearchThreads / 64; ++w) {
-          if (w < wv) before += s_wave[w];
-          row_total += s_wave[w];
-        }
-        int nbuf = s_nbuf;
-        if (nbuf + (int)row_total > kSearchBuf) {  // uniform: make room, only the W smallest can matter
-          __syncthreads();
-          search_sort(b_key, b_id, nbuf);
-          nbuf = min(nbuf, a.W);
-          truncated = true;
-        }
+        if (m == 0) return;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(counter, (uint32_t)__popcll(m));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
         if (keep) {
-          const int at = nbuf + (int)before + __popcll(m & ((1ull << lane) - 1ull));
-          b_key[at] = kbits;
-          b_id[at] = (uint32_t)cand;
+          at += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+          L.key[at] = kb;
+          L.id[at] = id;
         }
+      };
+      // room for n more candidates; otherwise the W smallest stay and bound the others
+      auto make_room = [&](int n) {  // uniform; a barrier in any case
         __syncthreads();
-        if (t == 0) s_nbuf = nbuf + (int)row_total;
-        __syncthreads();
+        int used = (int)*counter;
+        if (buf - used < n) {
+          search_select(L, sh, used, W, gather);
+          used = W;
+          tau = L.key[W - 1];
+          if (t == 0) *counter = (uint32_t)W;
+          __syncthreads();
+        }
+        return buf - used;
+      };
+      const int n_items = n_cur * ITEMS;
+      int room = buf, block0 = -1, block1 = 0;
+      for (int i0 = 0; i0 < n_items;) {  // uniform
+        int i1 = n_items;
+        if (!last) {
+          if (i0) room = make_room(min(n_items - i0, buf - W));
+          i1 = min(i1, i0 + room);
+        }
+        if (SPLIT) {
+          if (i0 >= block1 * ITEMS) {  // the next states' tables
+            if (block0 >= 0) __syncthreads();
+            block0 = block1;
+            block1 = min(n_cur, block0 + (int)a.block);
+            const int nb = block1 - block0;
+            for (int x = t; x < 2 * nb * ITEMS; x += kSearchThreads) {
+              const int second = x >= nb * ITEMS ? 1 : 0, y = x - second * nb * ITEMS;
+              const int rl = (int)fast_div((uint32_t)y, mg_items), rem = y - rl * ITEMS, k = (int)fast_div((uint32_t)rem, mg_zg),
+                        p = rem - k * ZG;
+              const uint32_t zg = L.zg[p];
+              const int z = zg & 255u, g = zg >> 8;
+              const State *par = j == 0 ? nullptr : state_at(cur, block0 + rl);
+              const int pz = par ? (int)(L.zg[second ? par->pool_b : par->pool] & 255u) : 0;
+              const SPart o = search_close(par ? &par->part[second && SPLIT ? 1 : 0] : nullptr, pz, z, Z,
+                                           L.raw[(tb * TPn + k) * pl.row_w + g], L.xfer);
+              (second ? L.pb : L.pa)[y] = search_pipe(o, S0, S1, s.nbm1);
+            }
+            for (int y = wv; y < nb * TPn; y += kSearchThreads / 64) {  // a wave, its lanes the pools
+              const int rl = (int)fast_div((uint32_t)y, mg_tpn), k = y - rl * TPn, width = L.width[k];
+              const State *par = j == 0 ? nullptr : state_at(cur, block0 + rl);
+              const int used = par && lane < ZG ? (int)reinterpret_cast<const uint16_t *>(par + 1)[lane] : 0;
+              const bool fits = lane < ZG && ((L.fit[tb * TPn + k] >> (L.zg[lane < ZG ? lane : 0] >> 8)) & 1u) != 0;
+              const unsigned long long h = __builtin_amdgcn_ballot_w64(fits && used + width <= L.cap[lane < ZG ? lane : 0]);
+              const unsigned long long w2 = __builtin_amdgcn_ballot_w64(fits && used + 2 * width <= L.cap[lane < ZG ? lane : 0]);
+              if (lane == 0) { L.half[y] = (s.D & 1) ? 0 : h; L.whole[y] = w2; }
+              if (lane == 0 && k == 0) {
+                L.mx[2 * rl] = par ? fmax(par->msync, S2) : fmax(0.0, S2);
+                L.mx[2 * rl + 1] = par ? fmax(par->mupd, S3) : fmax(0.0, S3);
+              }
+            }
+            __syncthreads();
+          }
+          i1 = min(i1, block1 * ITEMS);
+        }
+        for (int x0 = i0; x0 < i1; x0 += kSearchThreads) {  // uniform
+          const int x = x0 + t;
+          bool keep = false;
+          unsigned long long bk = ~0ull;
+          uint32_t bi = ~0u;
+          if (x < i1) {
+            const int r = (int)fast_div((uint32_t)x, mg_items), rem = x - r * ITEMS;  // (x < 2^19, ITEMS < 2^10)
+            const State *par = j == 0 ? nullptr : state_at(cur, r);
+            if (SPLIT) {
+              const int pa = (int)fast_div((uint32_t)rem, mg_tpn), k = rem - pa * TPn, y = (r - block0) * TPn + k;
+              const uint32_t zga = L.zg[pa];
+              const int za = zga & 255u, ga = zga >> 8;
+              const unsigned long long half = L.half[y], whole = L.whole[y];
+              const double ta = L.pa[y * ZG + pa], mx0 = L.mx[2 * (r - block0)], mx1 = L.mx[2 * (r - block0) + 1];
+              const double *raw = L.raw + (size_t)(tb * TPn + k) * pl.row_w, *sync = L.sync + (tb * TPn + k) * Z * Z + za * Z;
+              const double ua = fmax(mx1, raw[G + ga]);
+              // the second pools this state and first pool admit
+              unsigned long long cand = ((half >> pa) & 1ull) ? half & ~(1ull << pa) : 0ull;
+              cand |= whole & (1ull << pa);
+              if (a.max_runs != 0 && par && par->runs >= a.max_runs)
+                cand &= (par->runs == a.max_runs && pa == par->pool && (!STP || k == par->tpi)) ? 1ull << par->pool_b : 0ull;
+              expanded += (uint32_t)__popcll(cand);
+              const uint32_t id0 = (uint32_t)(r * NCH + pa * ZG * TPn + k);
+              while (cand) {
+                const int pb = __builtin_ctzll(cand);
+                cand &= cand - 1;
+                const uint32_t zgb = L.zg[pb];
+                const int zb = zgb & 255u, gb = zgb >> 8;
+                SBound b;
+                b.T = (fmax(ta, L.pb[y * ZG + pb]) + fmax(mx0, sync[zb])) + fmax(ua, raw[G + gb]);
+                b.C = 0.0;
+                if (need_c) {
+                  const double dol = L.dtp[k] * (0.5 * (L.price[ga] + L.price[gb]));
+                  const double ring = zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
+                  double rent = dol, comm = ring;
+                  if (par) {
+                    const int pza = L.zg[par->pool] & 255u, pzb = L.zg[par->pool_b] & 255u;
+                    rent = par->dol + dol;
+                    comm = par->comm;
+                    if (pza != za) comm += L.comm[pza * Z + za];
+                    if (pzb != zb) comm += L.comm[pzb * Z + zb];
+                    comm = comm + ring;
+                  }
+                  b.C = (rent + S4) / 3600.0 * b.T + comm;
+                }
+                unsigned long long kb;
+                if (search_keep(a, b, kb)) {
+                  ++kept;
+                  keep = true;
+                  if (kb < bk) { bk = kb; bi = id0 + (uint32_t)(pb * TPn); }
+                }
+              }
+            } else {
+              const int pa = rem;
+              for (int k = 0; k < TPn; ++k) {
+                SAcc o;
+                int runs;
+                if (!search_step<MODE>(pl, L, s, par, tb, pa, pa, k, a.max_runs, o, runs)) continue;
+                ++expanded;
+                SBound b;
+                b.T = (search_pipe(o.part[0], S0, S1, s.nbm1) + fmax(o.msync, S2)) + fmax(o.mupd, S3);
+                b.C = need_c ? (o.dol + S4) / 3600.0 * b.T + o.comm : 0.0;
+                unsigned long long kb;
+                if (search_keep(a, b, kb)) {
+                  ++kept;
+                  keep = true;
+                  if (kb < bk) { bk = kb; bi = (uint32_t)(r * NCH + pa * TPn + k); }
+                }
+              }
+            }
+          }
+          take(keep, bk, bi);
+        }
+        i0 = i1;
       }
-      atomicAdd(&s_expanded, (unsigned long long)my_expanded);
+      my_total += expanded;
       if (last) {
         // the smallest (key, id) of the workgroup
 #pragma unroll
@@ -591,144 +916,186 @@ __global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, Sear
         best_k = s_bk[0]; best_i = s_bi[0];
         for (int w = 1; w < kSearchThreads / 64; ++w)
           if (key_id_less(s_bk[w], s_bi[w], best_k, best_i)) { best_k = s_bk[w]; best_i = s_bi[w]; }
-        if (best_i != ~0u) {  // uniform
-          const int r = (int)best_i / NCH, c = (int)best_i - r * NCH;
-          int pa, pb, pk;
-          choice(c, it, pa, pb, pk);
-          const uint8_t *par_path = cur + (size_t)r * a.state_stride + kStateBytes;
-          for (int i = t; i < P - 1; i += blockDim.x) {
-            res->pools[i] = par_path[i];
-            res->pools_b[i] = SPLIT ? par_path[a.path_stride + i] : par_path[i];
-            res->tps[i] = STP ? par_path[2 * a.path_stride + i] : it;
-          }
+        if (best_i != ~0u && key_id_less(best_k, sid, wg_key, wg_sid)) {  // uniform
+          wg_key = best_k;
+          wg_sid = sid;
           if (t == 0) {
-            const SState *par = j == 0 ? nullptr : reinterpret_cast<const SState *>(cur + (size_t)r * a.state_stride);
+            int r, pa, pb, pk;
+            choice(best_i, r, pa, pb, pk);
             SAcc o;
             int runs;
-            search_step<MODE>(T, par, j, pa, pb, pk, G, a.max_runs, o, runs);
-            const SBound b = search_bound_of<MODE>(T, o, j, nbm1);
-            res->pools[P - 1] = pa;
-            res->pools_b[P - 1] = pb;
-            res->tps[P - 1] = pk;
-            if (STP) res->desc[2] = P > 1 ? (int)par_path[2 * a.path_stride] : pk;  // stage 0's
+            search_step<MODE>(pl, L, s, j == 0 ? nullptr : state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs);
+            const SBound b = search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1);
             res->T = b.T;
             res->C = b.C;
             res->key = a.objective == 0 ? b.T : b.C;
-            res->found = 1;
+            res->sid = sid;
+            res->P = (uint32_t)P;
+            res->desc[0] = s.ip; res->desc[1] = s.q; res->desc[3] = s.id; res->desc[4] = s.im; res->desc[5] = MODE;
+            uint32_t cand = best_i;
+            for (int i = P - 1; i >= 0; --i) {  // back through the levels
+              choice(cand, r, pa, pb, pk);
+              res->pools[i] = pa;
+              res->pools_b[i] = pb;
+              res->tps[i] = STP ? pk : s.it;
+              if (i > 0) cand = history[(size_t)(i - 1) * W + r];
+            }
+            res->desc[2] = STP ? pk : s.it;  // stage 0's
           }
         }
         break;
       }
+      // how many were kept in all
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) kept += __shfl_xor(kept, off);
+      if (lane == 0 && kept) atomicAdd(&s_kept[cur], kept);
       __syncthreads();
-      int n_next = s_nbuf;
-      if (n_next > a.W) {  // uniform: keep the W smallest bounds, in that order
-        search_sort(b_key, b_id, n_next);
-        n_next = a.W;
-        truncated = true;
+      kept = s_kept[cur];
+      int n = (int)s_n[cur];
+      if (t < n_raw) L.raw[(tb ^ 1) * n_raw + t] = ahead;
+      if (kept == 0) break;  // uniform
+      const bool cut = kept > (uint32_t)W;
+      truncated = truncated || cut;
+      bool sorted = false;
+      if (n > W) {
+        search_select(L, sh, n, W, gather);
+        n = W;
+        sorted = INNER == 1;
       }
-      if (n_next == 0) break;  // uniform
+      if (INNER > 1) {  // the choices behind the best items, one by one
+        for (int x = t; x < n; x += kSearchThreads) L.sel[x] = L.id[x];
+        const int n_all = n * INNER;
+        tau = ~0ull;
+        counter = &s_m[cur];
+        int room2 = buf;
+        __syncthreads();
+        for (int x0 = 0; x0 < n_all;) {  // uniform
+          if (x0) room2 = make_room(min(n_all - x0, buf - W));
+          const int x1 = min(n_all, x0 + room2);
+          for (int y0 = x0; y0 < x1; y0 += kSearchThreads) {
+            const int y = y0 + t;
+            bool keep = false;
+            unsigned long long kb = ~0ull;
+            uint32_t id = 0;
+            if (y < x1) {
+              const int e = (int)fast_div((uint32_t)y, mg_inner), in = y - e * INNER;
+              int r, pa, pb, pk;
+              choice(L.sel[e], r, pa, pb, pk);
+              if (SPLIT) pb = in;
+              else pk = in;
+              id = (uint32_t)(r * NCH + (SPLIT ? (pa * ZG + pb) * TPn + pk : pa * TPn + pk));
+              SAcc o;
+              int runs;
+              if (search_step<MODE>(pl, L, s, j == 0 ? nullptr : state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs))
+                keep = search_keep(a, search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1), kb);
+            }
+            take(keep, kb, id);
+          }
+          x0 = x1;
+        }
+        __syncthreads();
+        n = (int)s_m[cur];
+        if (n > W) {
+          search_select(L, sh, n, W, gather);
+          n = W;
+          sorted = true;
+        }
+      }
+      // a cut frontier: ascending bounds (as a selection leaves them); else the order of generation
+      if (!sorted) {
+        for (int x = t; x < n; x += kSearchThreads) { L.okey[x] = L.key[x]; L.oid[x] = L.id[x]; L.rank[x] = 0; }
+        __syncthreads();
+        search_place(L, n, W, !cut);
+      }
       // write the next frontier
-      for (int k = t; k < n_next; k += blockDim.x) {
-        const int cand = (int)b_id[k];
-        const int r = cand / NCH, c = cand - r * NCH;
-        int pa, pb, pk;
-        choice(c, it, pa, pb, pk);
-        uint8_t *const out = nxt + (size_t)k * a.state_stride;
-        const SState *par = j == 0 ? nullptr : reinterpret_cast<const SState *>(cur + (size_t)r * a.state_stride);
+      for (int k = t; k < n; k += kSearchThreads) {
+        const uint32_t cand = L.id[k];
+        int r, pa, pb, pk;
+        choice(cand, r, pa, pb, pk);
+        const State *par = j == 0 ? nullptr : state_at(cur, r);
+        State *const out = state_at(nxt, k);
         SAcc o;
         int runs;
-        search_step<MODE>(T, par, j, pa, pb, pk, G, a.max_runs, o, runs);
-        SState st;
-        if (par) {
-          st = *par;
-          const uint8_t *par_path = cur + (size_t)r * a.state_stride + kStateBytes;
-          for (int i = 0; i < j; ++i) {
-            out[kStateBytes + i] = par_path[i];
-            if (SPLIT) out[kStateBytes + a.path_stride + i] = par_path[a.path_stride + i];
-            if (STP) out[kStateBytes + 2 * a.path_stride + i] = par_path[2 * a.path_stride + i];
-          }
-        } else {
-          for (int x = 0; x < kSearchMaxPools; ++x) st.cnt[x] = 0;
-        }
-        st.sum = o.sum; st.maxt = o.maxt; st.c_open = o.c_open; st.xb_open = o.xb_open;
-        st.sum_b = o.sum_b; st.maxt_b = o.maxt_b; st.c_open_b = o.c_open_b; st.xb_open_b = o.xb_open_b;
+        search_step<MODE>(pl, L, s, par, tb, pa, pb, pk, a.max_runs, o, runs);
+        State st;
         st.msync = o.msync; st.mupd = o.mupd; st.dol = o.dol; st.comm = o.comm;
-        if (BOTH) {
-          st.cnt[pa] = (uint16_t)(st.cnt[pa] + T.tpv[pk]);
-          st.cnt[pb] = (uint16_t)(st.cnt[pb] + T.tpv[pk]);
-        } else if (STP) {
-          st.cnt[pa] = (uint16_t)(st.cnt[pa] + T.tpv[pk]);
-        } else if (!SPLIT) {
-          st.cnt[pa] = (uint16_t)(st.cnt[pa] + 1);
-        } else {
-          st.cnt[pa] = (uint16_t)(st.cnt[pa] + 1);
-          st.cnt[pb] = (uint16_t)(st.cnt[pb] + 1);
-        }
-        st.pool = (uint8_t)pa;
-        st.pool_b = (uint8_t)pb;
-        st.tpi = (uint8_t)pk;
-        st.runs = (uint8_t)runs;
+        st.part[0] = o.part[0];
+        if (SPLIT) st.part[SPLIT ? 1 : 0] = o.part[1];
+        st.pool = (uint8_t)pa; st.pool_b = (uint8_t)pb; st.runs = (uint8_t)runs; st.tpi = (uint8_t)pk;
         for (int x = 0; x < 4; ++x) st.pad[x] = 0;
-        *reinterpret_cast<SState *>(out) = st;
-        out[kStateBytes + j] = (uint8_t)pa;
-        if (SPLIT) out[kStateBytes + a.path_stride + j] = (uint8_t)pb;
-        if (STP) out[kStateBytes + 2 * a.path_stride + j] = (uint8_t)pk;
+        *out = st;
+        uint16_t *const cnt = reinterpret_cast<uint16_t *>(out + 1);
+        unsigned long long *const cw = reinterpret_cast<unsigned long long *>(out + 1);
+        for (int x = 0; x < (ZG + 3) / 4; ++x) cw[x] = par ? reinterpret_cast<const unsigned long long *>(par + 1)[x] : 0;
+        cnt[pa] = (uint16_t)(cnt[pa] + L.width[pk]);
+        if (SPLIT) cnt[pb] = (uint16_t)(cnt[pb] + L.width[pk]);
+        history[(size_t)j * W + k] = cand;
       }
-      n_cur = n_next;
+      search_level<MODE>(pl, s, L, j + 1, tb ^ 1, t, kSearchThreads);
+      n_cur = n;
     }
-    __syncthreads();
-    if (t == 0) {
-      res->truncated = truncated ? 1u : 0u;
-      res->expanded = s_expanded;
-    }
+    if (truncated) wg_trunc = 1;
+  }
+  atomicAdd(&s_expanded, my_total);
+  __syncthreads();
+  if (t == 0) {
+    res->found = wg_sid != ~0u ? 1u : 0u;
+    res->truncated = wg_trunc;
+    res->expanded = s_expanded;
   }
 }
 
-// Smallest (key, sub-problem) over the sub-problems' winners; also the totals.
-__global__ __launch_bounds__(256) void k_search_pick(const SubResult *results, uint32_t n_sub, SubResult *out) {
-  __shared__ unsigned long long s_k[4], s_e[4];
-  __shared__ uint32_t s_i[4], s_t[4];
+// Smallest (key, sub-problem) over the workgroups' winners; also the totals.  Leaves the winner
+// in host-mapped memory as well and the counters ready for the next search.
+__global__ __launch_bounds__(1024) void k_search_pick(SearchArgs a, uint32_t n_wgs, uint32_t n_root, SubResult *out,
+                                                      SubResult *host_out) {
+  __shared__ unsigned long long s_k[16], s_e[16];
+  __shared__ uint32_t s_i[16], s_t[16], s_at[16];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   unsigned long long bk = ~0ull, expanded = 0;
-  uint32_t bi = ~0u, trunc = 0;
-  for (uint32_t i = t; i < n_sub; i += blockDim.x) {
-    const SubResult &r = results[i];
+  uint32_t bi = ~0u, trunc = 0, at = 0;
+  for (uint32_t i = t; i < n_root; i += blockDim.x) expanded += a.root_expanded[i];
+  for (uint32_t i = t; i < n_wgs; i += blockDim.x) {
+    const SubResult &r = a.results[i];
     expanded += r.expanded;
     trunc |= r.truncated;
     if (r.found) {
       const unsigned long long k = (unsigned long long)__double_as_longlong(r.key);
-      if (key_id_less(k, i, bk, bi)) { bk = k; bi = i; }
+      if (key_id_less(k, r.sid, bk, bi)) { bk = k; bi = r.sid; at = i; }
     }
   }
+  for (int i = t; i <= a.n_pp; i += blockDim.x) a.counters[i] = 0;
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const unsigned long long ok = __shfl_xor(bk, off);
-    const uint32_t oi = __shfl_xor(bi, off);
-    if (key_id_less(ok, oi, bk, bi)) { bk = ok; bi = oi; }
+    const uint32_t oi = __shfl_xor(bi, off), oa = __shfl_xor(at, off);
+    if (key_id_less(ok, oi, bk, bi)) { bk = ok; bi = oi; at = oa; }
     expanded += __shfl_xor(expanded, off);
     trunc |= __shfl_xor(trunc, off);
   }
-  if (lane == 0) { s_k[wv] = bk; s_i[wv] = bi; s_e[wv] = expanded; s_t[wv] = trunc; }
+  if (lane == 0) { s_k[wv] = bk; s_i[wv] = bi; s_e[wv] = expanded; s_t[wv] = trunc; s_at[wv] = at; }
+  __syncthreads();
+  bk = s_k[0]; bi = s_i[0]; at = s_at[0]; expanded = s_e[0]; trunc = s_t[0];
+  for (int w = 1; w < 16; ++w) {
+    if (key_id_less(s_k[w], s_i[w], bk, bi)) { bk = s_k[w]; bi = s_i[w]; at = s_at[w]; }
+    expanded += s_e[w];
+    trunc |= s_t[w];
+  }
+  if (bi != ~0u) {
+    const unsigned long long *src = reinterpret_cast<const unsigned long long *>(a.results + at);
+    unsigned long long *dst = reinterpret_cast<unsigned long long *>(out), *hst = reinterpret_cast<unsigned long long *>(host_out);
+    for (uint32_t w = t; w < sizeof(SubResult) / 8; w += blockDim.x) {
+      const unsigned long long v = src[w];
+      dst[w] = v;
+      hst[w] = v;
+    }
+  }
   __syncthreads();
   if (t == 0) {
-    for (int w = 1; w < 4; ++w) {
-      if (key_id_less(s_k[w], s_i[w], bk, bi)) { bk = s_k[w]; bi = s_i[w]; }
-      expanded += s_e[w];
-      trunc |= s_t[w];
-    }
-    s_i[0] = bi; s_e[0] = expanded; s_t[0] = trunc;
+    host_out->found = bi != ~0u ? 1u : 0u;
+    host_out->truncated = trunc;
+    host_out->expanded = expanded;
   }
-  __syncthreads();
-  bi = s_i[0];
-  if (bi == ~0u) {
-    if (t == 0) { out->found = 0; out->truncated = s_t[0]; out->expanded = s_e[0]; out->P = 0; }
-    return;
-  }
-  const unsigned long long *src = reinterpret_cast<const unsigned long long *>(results + bi);
-  unsigned long long *dst = reinterpret_cast<unsigned long long *>(out);
-  for (uint32_t w = t; w < sizeof(SubResult) / 8; w += blockDim.x) dst[w] = src[w];
-  __syncthreads();
-  if (t == 0) { out->truncated = s_t[0]; out->expanded = s_e[0]; }
 }
 
 // ------------------------------------------------------------------ listed placements
@@ -835,11 +1202,6 @@ __device__ __forceinline__ double list_link(const DevPlan &pl, const ListTables 
   return pl.n_bw_coef > 0 ? link_bw(pl, za, zb, bytes) : T.bw[mul24(za, pl.Z) + zb];
 }
 
-// activation bytes of a worker: microbatches in flight x layers x bytes of one (validated < 2^62)
-__device__ __forceinline__ uint64_t act_bytes(int in_flight, int layers, uint64_t act) {
-  return (uint64_t)(uint32_t)in_flight * (uint32_t)layers * act;
-}
-
 struct PlaceArgs {
   uint64_t count;
   const int32_t *desc;    // [count][5] pp index, partition, tp index, dp index, mb index
@@ -855,6 +1217,8 @@ struct PlaceArgs {
   double *T, *C;
   uint64_t *mem;
   uint32_t *mask;
+  ResultHeader *hdr;      // optional, one workgroup: seq goes to hdr->seq when the results are in place
+  uint32_t seq;
 };
 
 constexpr int kPlaceThreads = 256;
@@ -1091,6 +1455,9 @@ __global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, P
     }
     s0 = s1;
   }
+  if (a.hdr && wv == 0) {  // (one plan: lane 0 wrote its results)
+    if (lane == 0) publish(a.hdr, a.seq);
+  }
 }
 
 // ------------------------------------------------------------------ a pool per replica
@@ -1143,14 +1510,6 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
   return v;
-}
-
-// makes a wave's LDS writes visible to its own later reads (operations of one wave complete in
-// order; the compiler must not move them)
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // A plan's (stage, replica) pairs and pipelines, shared by THREADS threads (a wave, or the
