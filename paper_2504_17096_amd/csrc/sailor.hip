@@ -552,7 +552,8 @@ template <int MODE>
 void launch_search(const sailor_plan *pl, const SearchArgs &a, unsigned root_wgs, size_t root_words, unsigned wgs,
                           size_t lds, hipStream_t st) {
   k_search_root<MODE><<<root_wgs, kRootWaves * 64, root_words * 8 * kRootWaves, st>>>(pl->dev, a, (uint32_t)root_words);
-  k_search_beam<MODE><<<wgs, kSearchThreads, lds, st>>>(pl->dev, a);
+  if (a.states) k_search_beam<MODE, false><<<wgs, kSearchThreads, lds, st>>>(pl->dev, a);
+  else k_search_beam<MODE, true><<<wgs, kSearchThreads, lds, st>>>(pl->dev, a);
 }
 
 // Waits for the sequence number in host-mapped memory rather than for the dispatch to
@@ -1564,10 +1565,8 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   a.counters = pl->search_counters;
   a.root_expanded = pl->search_root_expanded;
   a.results = pl->search_results;
-  // a power of two that holds what a level can have, and twice the beam
-  size_t buf = 64;
-  while (buf < kSearchBuf && buf < std::max(2 * W, W * ZG * (split ? TPn : 1))) buf *= 2;
-  a.buf = (uint32_t)buf;
+  // room for what a level can have, and for twice the beam
+  a.buf = (uint32_t)std::min<size_t>(kSearchBuf, std::max(2 * W, W * ZG * std::max<size_t>(TPn, 1)));
   // split stages: about 16 KiB of tables for a block of states
   a.block = (uint32_t)std::max<size_t>(1, std::min(W, 1024 / (TPn * ZG)));
   // Frontiers and history stay in LDS as long as two workgroups fit a compute unit; wide beams keep the

@@ -31,9 +31,9 @@
 // inputs are requested a level ahead, appending candidates takes no barrier, the W smallest come
 // from a histogram and a count of predecessors instead of a sort of everything, and a wide choice
 // (second pool, TP degree) is first reduced to the best of each (state, pool).  On the 48-layer,
-// 20-pool problem a search with beam 64 takes 0.85 ms where states in device memory, paths copied
+// 20-pool problem a search with beam 64 takes 0.63 ms where states in device memory, paths copied
 // level by level and a bitonic sort of every level took 2.9 ms; with two pools and a TP degree per
-// stage (1 600 choices, beam 8) 1.15 ms against 9.3 ms.
+// stage (1 600 choices, beam 8) 1.06 ms against 9.3 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -42,14 +42,15 @@
 
 namespace sailor {
 
+// threads of a search workgroup (256: 0.70 / 1.18 ms on the two searches named above, 1 024: 0.74 / 1.29)
 constexpr int kSearchThreads = 512;
 constexpr int kSearchMaxBeam = 1024;   // longest frontier a sub-problem keeps (half of kSearchBuf at most)
 constexpr int kSearchBuf = 2048;       // most candidates buffered between two selections
-constexpr int kSearchBins = 512;
+constexpr int kSearchBins = 256;
+constexpr int kSelectKeep = kSearchBuf / kSearchThreads;  // of them per thread
 constexpr int kSearchMaxStages = 255;  // placements count runs in a byte
 constexpr int kSearchMaxPools = 64;
 constexpr int kRootWaves = 4;
-static_assert(kMaxTP * (2 * kMaxTypes + 16) <= kSearchThreads, "a thread per word of a level's records");
 
 struct SearchPP {      // one pipeline depth
   int32_t P;
@@ -75,7 +76,8 @@ struct SState {        // placement of stages 0 .. j, followed by its pool count
                        // stage: GPUs of one replica)
   double msync, mupd, dol, comm;
   SPart part[SPLIT ? 2 : 1];  // with split stages: the pipelines through the first / second pools
-  uint8_t pool, pool_b, runs, tpi, pad[4];  // tpi: the open stage's TP index (TP per stage)
+  uint8_t pool, pool_b, runs, tpi;          // tpi: the open stage's TP index (TP per stage)
+  uint8_t zone, zone_b, pad[2];             // of the pools
 };
 __host__ __device__ inline uint32_t search_state_words(bool split, int ZG) {  // 8-byte words
   return (uint32_t)((split ? sizeof(SState<true>) : sizeof(SState<false>)) / 8) + (uint32_t)(ZG + 3) / 4;
@@ -125,62 +127,77 @@ struct SearchLds {
   double *ring_price;   // [Z][Z] split: egress both ways
   double *link;         // [Z] a zone's own link; split: [Z][Z] slowest link of a ring through both
   double *price, *dtp;  // [G]; [TPn] D * tp
+  unsigned long long *act;   // [TPn] activation bytes of a layer and microbatch
+  long long *room;      // [G] memory without what is reserved
+  int32_t *node;        // [G]
   int32_t *cap;         // [ZG] what a pool can host, in the units of the pool counts
   uint32_t *zg;         // [ZG] zone | type << 8
   int32_t *width;       // [TPn] what a stage (half a stage) takes from a pool
   // of a level, two of each: the next level's are filled while this one's are used
   double *raw;          // [2][TPn][row_w] the stage's records (DevPlan::st_row)
-  double *sync;         // [2][TPn][Z]; split: [TPn][Z][Z] seconds of the stage's all-reduce
+  double *sync;         // [2][TPn][Z]; split: [TPn][Z][ZP] (first zone, second pool; ZP: ZG made even)
+                        // seconds of the stage's all-reduce
+  double *upd;          // split: [2][TPn][ZP] update seconds by pool
   double *ring;         // [2][TPn] bytes it moves over every link
   uint32_t *fit;        // [2][TPn] bit g: the stage fits type g
   // split, for a block of states: bounds of the two kinds of pipeline by (TP, pool), pools that
   // can take one half / both halves, the maxima a choice is folded into
-  double *pa, *pb;      // [block][TPn][ZG]
+  double *pa, *pb;      // [block][TPn][ZP]
   unsigned long long *half, *whole;  // [block][TPn]
   double *mx;           // [block][2]
   // the candidates
   unsigned long long *key;  // [buf]
   unsigned long long *okey; // [gather]
-  uint32_t *id, *oid, *rank, *sel;  // [buf], [gather], [gather], [W]
+  uint32_t *id, *oid, *rank, *sel;  // [buf], [gather], [gather], [W]: a candidate is numbered by its
+                        // state << 16 | choice, which orders like the order of generation
   uint32_t *hist;       // [kSearchBins]
   double *states;
-  uint32_t *history;
+  uint32_t *history;    // [P_max][W] the candidates the frontiers are made of
 };
 
-__host__ __device__ inline uint32_t search_gather(uint32_t W, uint32_t buf) { return W + 256u < buf ? W + 256u : buf; }
+__host__ __device__ inline uint32_t search_gather(uint32_t W, uint32_t buf) { return W + 128u < buf ? W + 128u : buf; }
 
 // Lays the tables out from base on (NULL: only counts); returns the 8-byte words they take.
 __host__ __device__ inline size_t search_carve(const DevPlan &pl, bool split, bool stp, bool root, const SearchArgs &a,
                                                double *base, SearchLds &L) {
-  const size_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, TPn = stp ? pl.TP : 1, P = pl.P_max, two = root ? 1 : 2;
+  const size_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, ZP = ZG + (ZG & 1), TPn = stp ? pl.TP : 1, P = pl.P_max, two = root ? 1 : 2;
   size_t at = 0;
   auto words = [&](size_t n) { double *p = base + at; at += n; return p; };
   auto ints = [&](size_t n) { return reinterpret_cast<uint32_t *>(words((n + 1) / 2)); };
   L.S = words(5 * P);
-  L.smin = words(4 * P);
+  if (root) L.smin = words(4 * P);
   L.xfer = words(root ? 0 : Z * Z);
   L.comm = words(root ? 0 : Z * Z);
   L.ring_price = words(split ? Z * Z : 0);
   L.link = words(split ? Z * Z : Z);
   L.price = words(G);
   L.dtp = words(TPn);
+  L.act = reinterpret_cast<unsigned long long *>(words(TPn));
+  L.room = reinterpret_cast<long long *>(words(G));
+  L.node = reinterpret_cast<int32_t *>(ints(G));
   L.cap = reinterpret_cast<int32_t *>(ints(ZG));
   L.zg = ints(ZG);
   L.width = reinterpret_cast<int32_t *>(ints(TPn));
   L.raw = words(two * TPn * pl.row_w);
-  L.sync = words(two * TPn * (split ? Z * Z : Z));
+  at += at & 1;  // (rows that are read in pairs)
+  L.sync = words(two * TPn * (split ? Z * ZP : Z));
+  L.upd = words(split ? two * TPn * ZP : 0);
   L.ring = words(two * TPn);
   L.fit = ints(two * TPn);
   if (root) return at;
-  L.pa = words(split ? a.block * TPn * ZG : 0);
-  L.pb = words(split ? a.block * TPn * ZG : 0);
+  at += at & 1;
+  L.pa = words(split ? a.block * TPn * ZP : 0);
+  L.pb = words(split ? a.block * TPn * ZP : 0);
   L.half = reinterpret_cast<unsigned long long *>(words(split ? a.block * TPn : 0));
   L.whole = reinterpret_cast<unsigned long long *>(words(split ? a.block * TPn : 0));
   L.mx = words(split ? a.block * 2 : 0);
   const size_t gather = search_gather((uint32_t)a.W, a.buf);
+  L.smin = words(0);  // (needed before there are candidates)
+  const size_t from = at;
   L.key = reinterpret_cast<unsigned long long *>(words(a.buf));
-  L.okey = reinterpret_cast<unsigned long long *>(words(gather));
   L.id = ints(a.buf);
+  if (at < from + 4 * P) at = from + 4 * P;
+  L.okey = reinterpret_cast<unsigned long long *>(words(gather));
   L.oid = ints(gather);
   L.rank = ints(gather);
   L.sel = ints(a.W);
@@ -260,11 +277,16 @@ __device__ __forceinline__ bool search_tables(const DevPlan &pl, const SearchSub
     const uint32_t z = fast_div((uint32_t)p, pl.mg_g);
     L.zg[p] = z | ((uint32_t)p - z * (uint32_t)G) << 8;
   }
-  for (int g = tid; g < G; g += nt) L.price[g] = pl.price[g];
+  for (int g = tid; g < G; g += nt) {
+    L.price[g] = pl.price[g];
+    L.room[g] = (long long)pl.cap[g] - (long long)pl.res[g];  // (both below 2^62)
+    L.node[g] = pl.node[g];
+  }
   for (int k = tid; k < TPn; k += nt) {
     const int tp = pl.vals[pl.DP + (STP ? k : s.it)];
     L.dtp[k] = (double)(s.D * (int64_t)tp);
     L.width[k] = STP ? tp : 1;
+    L.act[k] = pl.act[s.im * TP + (STP ? k : s.it)];
   }
   bool fine = true;
   for (int i = tid; i < s.P; i += nt) {  // the cheapest admissible (type, TP) of stage i
@@ -317,28 +339,31 @@ __device__ __forceinline__ void search_suffix(const DevPlan &pl, const SearchSub
   }
 }
 
-// What follows from a level's records (which must be visible): all-reduce seconds, fits.
+// What follows from a level's records (which must be visible): all-reduce seconds, fits.  layers:
+// of the level's stage; tp1: the sub-problem's TP degree.
 template <int MODE>
-__device__ __forceinline__ void search_level(const DevPlan &pl, const SearchSub &s, const SearchLds &L, int j, int b, int tid,
-                                             int nt) {
+__device__ __forceinline__ void search_level(const DevPlan &pl, const SearchSub &s, const SearchLds &L, int j, int layers,
+                                             int tp1, int b, int tid, int nt) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
-  const int G = pl.G, Z = pl.Z, TP = pl.TP, TPn = STP ? TP : 1, NS = SPLIT ? Z * Z : Z;
+  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, TPn = STP ? pl.TP : 1, NS = SPLIT ? Z * (ZG + (ZG & 1)) : Z;
   const double *raw = L.raw + (size_t)b * TPn * pl.row_w;
   for (int i = tid; i < TPn * NS; i += nt) {
-    const int k = i / NS, z = i - k * NS;
+    const int k = i / NS, z = i - k * NS;  // split: first zone * ZP + second pool
     const double ring = s.D > 1 ? s.ringf * raw[k * pl.row_w + 2 * G + 1] : 0.0;
-    L.sync[b * TPn * NS + i] = s.D > 1 ? ring / L.link[z] : 0.0;
+    const int ZP = ZG + (ZG & 1), pb = SPLIT ? min(z % ZP, ZG - 1) : 0;
+    const uint32_t zgb = L.zg[pb];
+    L.sync[b * TPn * NS + i] = s.D > 1 ? ring / L.link[SPLIT ? z / ZP * Z + (int)(zgb & 255u) : z] : 0.0;
     if (z == 0) L.ring[b * TPn + k] = ring;
+    if (SPLIT && z < ZP) L.upd[(b * TPn + k) * ZP + z] = raw[k * pl.row_w + G + (zgb >> 8)];
   }
-  const int layers = pl.st_n[s.rs + j];
   for (int k = tid; k < TPn; k += nt) {
-    const int kk = STP ? k : s.it, tpk = pl.vals[pl.DP + kk];
+    const int tpk = STP ? L.width[k] : tp1;
     const uint64_t bytes = (uint64_t)__double_as_longlong(raw[k * pl.row_w + 2 * G]) +
-                           act_bytes(min(s.P - j, s.nb), layers, pl.act[s.im * TP + kk]);
+                           act_bytes(min(s.P - j, s.nb), layers, L.act[k]);
     uint32_t m = 0;
     for (int g = 0; g < G; ++g)
-      if (bytes + pl.res[g] <= pl.cap[g] && tpk <= pl.node[g]) m |= 1u << g;
+      if ((long long)bytes <= L.room[g] && tpk <= L.node[g]) m |= 1u << g;
     L.fit[b * TPn + k] = m;
   }
 }
@@ -350,13 +375,13 @@ struct SAcc {          // what a placement carries besides its pool counts
   double msync, mupd, dol, comm;
 };
 
-// One kind of pipeline goes on from pool zone pz to a stage of compute time c in zone z (no
-// stage before it for par = NULL).  The order of the operations is part of the definition: sums in
+// One kind of pipeline goes on from pool zone pz to a stage of compute time c in zone z (first: no
+// stage before it, par is not read).  The order of the operations is part of the definition: sums in
 // stage order, a closed stage's transfers forward then backward.
-__device__ __forceinline__ SPart search_close(const SPart *par, int pz, int z, int Z, double c, const double *xfer) {
+__device__ __forceinline__ SPart search_close(bool first, const SPart *par, int pz, int z, int Z, double c, const double *xfer) {
   SPart o;
   o.c_open = c;
-  if (!par) {
+  if (first) {
     o.sum = o.maxt = o.xb_open = 0.0;
   } else {
     const double closed = par->c_open + (xfer[pz * Z + z] + par->xb_open);
@@ -374,11 +399,11 @@ __device__ __forceinline__ double search_pipe(const SPart &o, double Ssum, doubl
 }
 
 // Stage j on pool a (split stages: half of its replicas on pool b, else b = a) at TP index k (a
-// TP degree per stage; else 0) behind the placement par (NULL for j = 0): may it be placed, and
-// what the placement then carries.
+// TP degree per stage; else 0) behind the placement par (first: j = 0, there is none): may it be
+// placed, and what the placement then carries.
 template <int MODE>
 __device__ __forceinline__ bool search_step(const DevPlan &pl, const SearchLds &L, const SearchSub &s,
-                                            const SState<MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP> *par, int tb,
+                                            bool first, const SState<MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP> *par, int tb,
                                             int a, int b, int k, int max_runs, SAcc &o, int &runs) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
@@ -388,29 +413,29 @@ __device__ __forceinline__ bool search_step(const DevPlan &pl, const SearchLds &
   const uint32_t fit = L.fit[tb * TPn + k];
   const int width = STP ? L.width[k] : 1;
   const uint16_t *cnt = reinterpret_cast<const uint16_t *>(par + 1);
-  const int ca = par ? (int)cnt[a] : 0;
+  const int ca = first ? 0 : (int)cnt[a];
   bool ok = ((fit >> ga) & 1u) != 0;
   if (!SPLIT) {
     ok = ok && ca + width <= L.cap[a];
   } else {
     ok = ok && ((fit >> gb) & 1u) != 0;
     if (a == b) ok = ok && ca + 2 * width <= L.cap[a];
-    else ok = ok && (s.D & 1) == 0 && ca + width <= L.cap[a] && (par ? (int)cnt[b] : 0) + width <= L.cap[b];
+    else ok = ok && (s.D & 1) == 0 && ca + width <= L.cap[a] && (first ? 0 : (int)cnt[b]) + width <= L.cap[b];
   }
-  runs = par ? par->runs + ((a != par->pool || (SPLIT && b != par->pool_b) || (STP && k != par->tpi)) ? 1 : 0) : 1;
+  runs = first ? 1 : par->runs + ((a != par->pool || (SPLIT && b != par->pool_b) || (STP && k != par->tpi)) ? 1 : 0);
   if (max_runs != 0 && runs > max_runs) ok = false;
   if (!ok) return false;
   const double *raw = L.raw + (size_t)(tb * TPn + k) * pl.row_w;
-  const int pza = par ? (int)(L.zg[par->pool] & 255u) : 0, pzb = SPLIT && par ? (int)(L.zg[par->pool_b] & 255u) : 0;
-  o.part[0] = search_close(par ? &par->part[0] : nullptr, pza, za, Z, raw[ga], L.xfer);
-  if (SPLIT) o.part[1] = search_close(par ? &par->part[SPLIT ? 1 : 0] : nullptr, pzb, zb, Z, raw[gb], L.xfer);
+  const int pza = first ? 0 : (int)par->zone, pzb = SPLIT && !first ? (int)par->zone_b : 0;
+  o.part[0] = search_close(first, &par->part[0], pza, za, Z, raw[ga], L.xfer);
+  if (SPLIT) o.part[1] = search_close(first, &par->part[SPLIT ? 1 : 0], pzb, zb, Z, raw[gb], L.xfer);
   // the stage by itself: all-reduce over the slowest link of a ring through both pools, the
   // slower update, the mean rent, the ring's traffic between the zones
-  const double sync = SPLIT ? L.sync[(tb * TPn + k) * Z * Z + za * Z + zb] : L.sync[(tb * TPn + k) * Z + za];
+  const double sync = SPLIT ? L.sync[((tb * TPn + k) * Z + za) * (pl.ZGr + (pl.ZGr & 1)) + b] : L.sync[(tb * TPn + k) * Z + za];
   const double upd = SPLIT ? fmax(raw[G + ga], raw[G + gb]) : raw[G + ga];
   const double dol = L.dtp[k] * (SPLIT ? 0.5 * (L.price[ga] + L.price[gb]) : L.price[ga]);
   const double ring = SPLIT && zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
-  if (!par) {
+  if (first) {
     o.msync = sync; o.mupd = upd; o.dol = dol; o.comm = ring;
   } else {
     o.msync = fmax(par->msync, sync);
@@ -471,7 +496,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
     if (__builtin_amdgcn_ballot_w64(!fine) != 0) continue;
     wave_lds_fence();
     search_suffix(pl, s, L, lane);
-    search_level<MODE>(pl, s, L, 0, 0, lane, 64);
+    search_level<MODE>(pl, s, L, 0, pl.st_n[s.rs], pl.vals[pl.DP + s.it], 0, lane, 64);
     wave_lds_fence();
     bool alive = false;
     uint32_t mine = 0;
@@ -480,7 +505,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
       const int pa = SPLIT ? pools / ZG : pools, pb = SPLIT ? pools - pa * ZG : pa;
       SAcc o;
       int runs;
-      if (!search_step<MODE>(pl, L, s, nullptr, 0, pa, pb, k, a.max_runs, o, runs)) continue;
+      if (!search_step<MODE>(pl, L, s, true, nullptr, 0, pa, pb, k, a.max_runs, o, runs)) continue;
       ++mine;
       unsigned long long kbits;
       alive = search_keep(a, search_bound<SPLIT>(o, L.S, pl.P_max, 0, s.nbm1), kbits) || alive;
@@ -526,33 +551,10 @@ __device__ __forceinline__ double wave_extreme_last(double v) {
   return v;
 }
 
-// Ascending bitonic sort of (key, id) pairs in LDS; m = the power of two >= n; entries
-// n .. m-1 (which must exist) are filled with the largest pair first.
-__device__ __forceinline__ void search_sort(unsigned long long *key, uint32_t *id, int n) {
-  int m = 1;
-  while (m < n) m <<= 1;
-  for (int i = n + (int)threadIdx.x; i < m; i += kSearchThreads) { key[i] = ~0ull; id[i] = ~0u; }
-  __syncthreads();
-  for (int k = 2; k <= m; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < m; i += kSearchThreads) {
-        const int x = i ^ j;
-        if (x > i) {
-          const bool up = (i & k) == 0;
-          const unsigned long long ki = key[i], kx = key[x];
-          const uint32_t ii = id[i], ix = id[x];
-          const bool swap = up ? key_id_less(kx, ix, ki, ii) : key_id_less(ki, ii, kx, ix);
-          if (swap) { key[i] = kx; key[x] = ki; id[i] = ix; id[x] = ii; }
-        }
-      }
-      __syncthreads();
-    }
-}
-
 struct SelectShared {
   double ext[2 * (kSearchThreads / 64)];
   unsigned long long lo, hi;
-  uint32_t bin, below, upto, n;
+  uint32_t n;
 };
 
 // The m pairs of (okey, oid), ranked by counting each one's predecessors -- by_id: in the order
@@ -567,7 +569,7 @@ __device__ __forceinline__ void search_place(const SearchLds &L, int m, int W, b
       const unsigned long long mk = by_id ? 0 : L.okey[q];
       const uint32_t mi = L.oid[q];
       uint32_t before = 0;
-#pragma unroll 4
+#pragma unroll 8
       for (int x = row; x < m; x += rows) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
       if (before) atomicAdd(&L.rank[q], before);
     }
@@ -576,7 +578,7 @@ __device__ __forceinline__ void search_place(const SearchLds &L, int m, int W, b
       const unsigned long long mk = by_id ? 0 : L.okey[q];
       const uint32_t mi = L.oid[q];
       uint32_t before = 0;
-#pragma unroll 4
+#pragma unroll 8
       for (int x = 0; x < m; ++x) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
       L.rank[q] = before;
     }
@@ -595,9 +597,19 @@ __device__ __forceinline__ void search_place(const SearchLds &L, int m, int W, b
 // visible; it is again on return.
 __device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &sh, int n, int W, int gather) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  // this thread's pairs (requested together: places beyond n read the last pair and do not count)
+  unsigned long long kk[kSelectKeep];
+  uint32_t ii[kSelectKeep];
+#pragma unroll
+  for (int q = 0; q < kSelectKeep; ++q) {
+    const int e = min(t + q * kSearchThreads, n - 1);
+    kk[q] = L.key[e];
+    ii[q] = L.id[e];
+  }
   double lo = __builtin_huge_val(), hi = 0.0;
-  for (int e = t; e < n; e += kSearchThreads) {
-    const double x = __longlong_as_double((long long)L.key[e]);
+#pragma unroll
+  for (int q = 0; q < kSelectKeep; ++q) {  // (the last pair again changes neither)
+    const double x = __longlong_as_double((long long)kk[q]);
     lo = fmin(lo, x);
     hi = fmax(hi, x);
   }
@@ -605,102 +617,126 @@ __device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &
   hi = wave_extreme_last<false>(hi);
   if (lane == 63) { sh.ext[2 * wv] = lo; sh.ext[2 * wv + 1] = hi; }
   for (int x = t; x < kSearchBins; x += kSearchThreads) L.hist[x] = 0;
+  for (int x = t; x < gather; x += kSearchThreads) L.rank[x] = 0;
   __syncthreads();
   lo = sh.ext[0]; hi = sh.ext[1];
+#pragma unroll
   for (int w = 1; w < kSearchThreads / 64; ++w) { lo = fmin(lo, sh.ext[2 * w]); hi = fmax(hi, sh.ext[2 * w + 1]); }
   int below = 0;  // pairs under lo
   for (int round = 0;; ++round) {  // uniform
     const double scale = hi > lo ? (double)kSearchBins / (hi - lo) : 0.0;
     auto bin_of = [&](double x) { return min((int)((x - lo) * scale), kSearchBins - 1); };
-    for (int e = t; e < n; e += kSearchThreads) {
-      const double x = __longlong_as_double((long long)L.key[e]);
-      if (x >= lo && x <= hi) atomicAdd(&L.hist[bin_of(x)], 1u);
+#pragma unroll
+    for (int q = 0; q < kSelectKeep; ++q) {
+      const double x = __longlong_as_double((long long)kk[q]);
+      if (t + q * kSearchThreads < n && x >= lo && x <= hi) atomicAdd(&L.hist[bin_of(x)], 1u);
     }
     if (t == 0) { sh.n = 0; sh.lo = ~0ull; sh.hi = 0; }
     __syncthreads();
-    if (wv == 0) {  // the bin of the W-th
-      constexpr int kPer = kSearchBins / 64;
-      uint32_t h[kPer], sum = 0;
+    // the bin of the W-th (every wave for itself)
+    constexpr int kPer = kSearchBins / 64;
+    uint32_t h[kPer], sum = 0;
 #pragma unroll
-      for (int q = 0; q < kPer; ++q) { h[q] = L.hist[lane * kPer + q]; sum += h[q]; }
-      uint32_t incl = sum;
+    for (int q = 0; q < kPer; ++q) { h[q] = L.hist[lane * kPer + q]; sum += h[q]; }
+    uint32_t incl = sum;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_up(incl, off);
-        if (lane >= off) incl += v;
-      }
-      uint32_t excl = (uint32_t)below + incl - sum;
-      if (excl < (uint32_t)W && (uint32_t)W <= excl + sum) {
-        int b = 0;
-#pragma unroll
-        for (int q = 0; q < kPer - 1; ++q)
-          if (b == q && excl + h[q] < (uint32_t)W) { excl += h[q]; b = q + 1; }
-        uint32_t hb = 0;
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) hb = b == q ? h[q] : hb;
-        sh.bin = (uint32_t)(lane * kPer + b);
-        sh.below = excl;
-        sh.upto = excl + hb;
-      }
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
     }
-    __syncthreads();
-    const int bin = (int)sh.bin, m = (int)sh.upto;
+    uint32_t excl = (uint32_t)below + incl - sum;
+    const unsigned long long here = __builtin_amdgcn_ballot_w64(excl < (uint32_t)W && (uint32_t)W <= excl + sum);
+    const int owner = __builtin_ctzll(here);
+    int b = 0;
+#pragma unroll
+    for (int q = 0; q < kPer - 1; ++q)
+      if (b == q && excl + h[q] < (uint32_t)W) { excl += h[q]; b = q + 1; }
+    uint32_t hb = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) hb = b == q ? h[q] : hb;
+    const int bin = __builtin_amdgcn_readlane(lane * kPer + b, owner), under = __builtin_amdgcn_readlane((int)excl, owner),
+              m = under + __builtin_amdgcn_readlane((int)hb, owner);
     if (m <= gather) {
-      for (int e = t; e < n; e += kSearchThreads) {
-        const unsigned long long kb = L.key[e];
-        const double x = __longlong_as_double((long long)kb);
-        if (x < lo || (x <= hi && bin_of(x) <= bin)) {
-          const uint32_t at = atomicAdd(&sh.n, 1u);
-          L.okey[at] = kb;
-          L.oid[at] = L.id[e];
-        }
+      unsigned long long mask[kSelectKeep];  // one reservation per wave
+      uint32_t total = 0;
+#pragma unroll
+      for (int q = 0; q < kSelectKeep; ++q) {
+        const double x = __longlong_as_double((long long)kk[q]);
+        mask[q] = __builtin_amdgcn_ballot_w64(t + q * kSearchThreads < n && (x < lo || (x <= hi && bin_of(x) <= bin)));
+        total += (uint32_t)__popcll(mask[q]);
       }
-      for (int x = t; x < m; x += kSearchThreads) L.rank[x] = 0;
+      uint32_t at = 0;
+      if (lane == 0 && total) at = atomicAdd(&sh.n, total);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+      for (int q = 0; q < kSelectKeep; ++q) {
+        const uint32_t mine = at + (uint32_t)__popcll(mask[q] & ((1ull << lane) - 1ull));
+        if ((mask[q] >> lane) & 1ull) { L.okey[mine] = kk[q]; L.oid[mine] = ii[q]; }
+        at += (uint32_t)__popcll(mask[q]);
+      }
       __syncthreads();
       search_place(L, m, W, false);
       return;
     }
     if (scale == 0.0 || round == 3) break;  // (equal keys, or a range the bins do not separate)
-    for (int e = t; e < n; e += kSearchThreads) {
-      const unsigned long long kb = L.key[e];
-      const double x = __longlong_as_double((long long)kb);
-      if (x >= lo && x <= hi && bin_of(x) == bin) { atomicMin(&sh.lo, kb); atomicMax(&sh.hi, kb); }
+#pragma unroll
+    for (int q = 0; q < kSelectKeep; ++q) {
+      const double x = __longlong_as_double((long long)kk[q]);
+      if (t + q * kSearchThreads < n && x >= lo && x <= hi && bin_of(x) == bin) { atomicMin(&sh.lo, kk[q]); atomicMax(&sh.hi, kk[q]); }
     }
+    __syncthreads();  // (every wave has read the histogram)
     for (int x = t; x < kSearchBins; x += kSearchThreads) L.hist[x] = 0;
-    below = (int)sh.below;
-    __syncthreads();
+    below = under;
     lo = __longlong_as_double((long long)sh.lo);
     hi = __longlong_as_double((long long)sh.hi);
     __syncthreads();  // (read before the next round resets them)
   }
-  search_sort(L.key, L.id, n);
+  // many equal keys: every pair against every other
+#pragma unroll
+  for (int q = 0; q < kSelectKeep; ++q) {
+    if (t + q * kSearchThreads < n) {
+      uint32_t before = 0;
+      for (int x = 0; x < n; ++x) before += key_id_less(L.key[x], L.id[x], kk[q], ii[q]) ? 1u : 0u;
+      if (before < (uint32_t)W) { L.okey[before] = kk[q]; L.oid[before] = ii[q]; }
+    }
+  }
+  __syncthreads();
+  for (int x = t; x < W; x += kSearchThreads) { L.key[x] = L.okey[x]; L.id[x] = L.oid[x]; }
+  __syncthreads();
 }
 
 // ---- the levels ----
 
-template <int MODE>
-__global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, SearchArgs a) {
+// One workgroup per surviving sub-problem.
+//
+// A choice is (a, k), or with split stages (a, b, k).  An item is the choices that differ in the
+// inner digit only (b, or k): a level first looks at items, by the best choice of each; only where
+// there is an inner digit, the choices behind the best W items are looked at one by one -- the W
+// smallest choices lie in the W items with the smallest bests.
+// (Two waves per SIMD for split stages, four else: with four, the wider code spills to memory, 1.19 ms
+// against 1.05; with two, the narrower loses a workgroup per compute unit, 0.72 ms against 0.62.)
+// LDSF: the frontiers are in LDS (else in device memory, for wide beams).
+template <int MODE, bool LDSF>
+__global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_beam(DevPlan pl, SearchArgs a) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;   // two pools per stage
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;  // a TP degree per stage
   using State = SState<SPLIT>;
   extern __shared__ double search_lds[];
   __shared__ SelectShared sh;
   // candidates buffered (items; choices behind them) and kept in all; two sets, used by levels in turn
-  __shared__ uint32_t s_n[2], s_m[2], s_kept[2], s_next;
+  __shared__ uint32_t s_n[2][2], s_kept[2], s_next;
   __shared__ unsigned long long s_expanded;
   __shared__ unsigned long long s_bk[kSearchThreads / 64];
   __shared__ uint32_t s_bi[kSearchThreads / 64];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int ZG = pl.ZGr, Z = pl.Z, G = pl.G, TPn = STP ? pl.TP : 1, W = a.W, P_max = pl.P_max;
-  // a choice: (a, k), or with split stages (a, b, k); an item: the choices that differ in the
-  // inner digit only (k, or b), of which the best stands for all at first
-  const int NCH = SPLIT ? ZG * ZG * TPn : ZG * TPn, ITEMS = SPLIT ? ZG * TPn : ZG, INNER = SPLIT ? ZG : TPn;
+  const int ITEMS = SPLIT ? ZG * TPn : ZG, INNER = SPLIT ? ZG : TPn, ZP = ZG + (ZG & 1);
   SearchLds L;
   search_carve(pl, SPLIT, STP, false, a, search_lds, L);
   const uint32_t mg_items = search_magic(ITEMS), mg_zg = search_magic(ZG), mg_tpn = search_magic(TPn), mg_inner = search_magic(INNER);
   const int gather = (int)search_gather((uint32_t)W, a.buf), buf = (int)a.buf;
   const uint32_t sw = search_state_words(SPLIT, ZG);
-  double *const states = a.states ? a.states + (size_t)blockIdx.x * 2 * W * sw : L.states;
+  double *const states = LDSF ? L.states : a.states + (size_t)blockIdx.x * 2 * W * sw;
   uint32_t *const history = a.history ? a.history + (size_t)blockIdx.x * P_max * W : L.history;
   SubResult *const res = a.results + blockIdx.x;
   const bool need_c = a.objective != 0 || a.has_bound != 0;
@@ -710,13 +746,13 @@ __global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, Sear
   uint32_t n_alive = 0;
   for (int i = 0; i < a.n_pp; ++i) n_alive += a.counters[i];
   auto state_at = [&](int frontier, int r) { return reinterpret_cast<State *>(states + ((size_t)frontier * W + r) * sw); };
-  // a candidate's state, pools and TP index from its number r * NCH + (a, k) / (a, b, k)
+  auto number = [&](int r, int pa, int pb, int k) { return (uint32_t)(r << 16 | (SPLIT ? (pa * ZG + pb) * TPn + k : pa * TPn + k)); };
   auto choice = [&](uint32_t cand, int &r, int &ca, int &cb, int &ck) {
-    r = (int)(cand / (uint32_t)NCH);
-    const int c = (int)cand - r * NCH, pools = STP ? (int)fast_div((uint32_t)c, mg_tpn) : c;  // c < 2^15
-    ck = STP ? c - pools * TPn : 0;
-    ca = SPLIT ? (int)fast_div((uint32_t)pools, mg_zg) : pools;
-    cb = SPLIT ? pools - ca * ZG : ca;
+    r = (int)(cand >> 16);
+    const uint32_t c = cand & 0xFFFFu, pools = STP ? fast_div(c, mg_tpn) : c;
+    ck = STP ? (int)(c - pools * (uint32_t)TPn) : 0;
+    ca = SPLIT ? (int)fast_div(pools, mg_zg) : (int)pools;
+    cb = SPLIT ? (int)pools - ca * ZG : ca;
   };
   if (t == 0) s_expanded = 0;
 
@@ -734,173 +770,256 @@ __global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, Sear
     const int n_raw = TPn * (int)pl.row_w;
     for (int i = t; i < n_raw; i += kSearchThreads) L.raw[i] = search_row<STP>(pl, s, 0)[i];
     search_tables<MODE, false>(pl, s, L, t, kSearchThreads);
-    if (t == 0) s_n[0] = s_m[0] = s_kept[0] = 0;
+    if (t == 0) s_n[0][0] = s_n[0][1] = s_kept[0] = 0;
     __syncthreads();
     if (wv == kSearchThreads / 64 - 1) search_suffix(pl, s, L, lane);
-    search_level<MODE>(pl, s, L, 0, 0, t, kSearchThreads);
+    const int tp1 = pl.vals[pl.DP + s.it];
+    search_level<MODE>(pl, s, L, 0, pl.st_n[s.rs], tp1, 0, t, kSearchThreads);
     int n_cur = 1;  // frontier length; level 0 extends one empty placement
     bool truncated = false;
     for (int j = 0; j < P; ++j) {  // place stage j (uniform loop)
       const int tb = j & 1, cur = j & 1, nxt = cur ^ 1;
-      const bool last = j == P - 1;
+      const bool last = j == P - 1, first = j == 0;
       __syncthreads();
-      if (t == 0) s_n[nxt] = s_m[nxt] = s_kept[nxt] = 0;
-      uint32_t *counter = &s_n[cur];
+      if (t == 0) s_n[nxt][0] = s_n[nxt][1] = s_kept[nxt] = 0;
       // the next level's records, requested now and stored when this level's candidates are in
       double ahead = 0.0;
-      if (!last && t < n_raw) ahead = search_row<STP>(pl, s, j + 1)[t];
+      int layers = 0;
+      if (!last) {
+        layers = pl.st_n[s.rs + j + 1];
+        if (t < n_raw) ahead = search_row<STP>(pl, s, j + 1)[t];
+      }
       const double S0 = L.S[j], S1 = L.S[P_max + j], S2 = L.S[2 * P_max + j], S3 = L.S[3 * P_max + j], S4 = L.S[4 * P_max + j];
       unsigned long long best_k = ~0ull;  // last level: this thread's smallest (key, id)
       uint32_t best_i = ~0u;
-      unsigned long long tau = ~0ull;     // only keys up to this can be among the W smallest
       uint32_t kept = 0, expanded = 0;
-      auto take = [&](bool keep, unsigned long long kb, uint32_t id) {  // whole waves
-        if (last) {
-          if (keep && key_id_less(kb, id, best_k, best_i)) { best_k = kb; best_i = id; }
-          return;
+      bool cut = false, sorted = false;
+      int n = 0, block0 = 0, block1 = 0;
+      for (int phase = 0; phase < (INNER > 1 && !last ? 2 : 1); ++phase) {  // items; the choices behind the best
+        uint32_t *const counter = &s_n[cur][phase];
+        unsigned long long tau = ~0ull;     // only keys up to this can be among the W smallest
+        const int n_all = phase == 0 ? n_cur * ITEMS : n * INNER;
+        int used = 0;
+        for (int i0 = 0;;) {  // uniform
+          int i1 = last ? n_all : min(n_all, i0 + buf - used);
+          if (SPLIT && phase == 0) {
+            if (i0 >= block1 * ITEMS) {  // the next states' tables
+              if (block1 > 0) __syncthreads();
+              block0 = block1;
+              block1 = min(n_cur, block0 + (int)a.block);
+              const int nb = block1 - block0;
+              for (int x = t; x < 2 * nb * ITEMS; x += kSearchThreads) {
+                const int second = x >= nb * ITEMS ? 1 : 0, y = x - second * nb * ITEMS;
+                const int rl = (int)fast_div((uint32_t)y, mg_items), rem = y - rl * ITEMS, k = (int)fast_div((uint32_t)rem, mg_zg),
+                          p = rem - k * ZG;
+                const uint32_t zg = L.zg[p];
+                const State *par = state_at(cur, block0 + rl);
+                const int pz = first ? 0 : (int)(second ? par->zone_b : par->zone);
+                const SPart o = search_close(first, &par->part[second && SPLIT ? 1 : 0], pz, (int)(zg & 255u), Z,
+                                             L.raw[(tb * TPn + k) * pl.row_w + (zg >> 8)], L.xfer);
+                const double pipe = search_pipe(o, S0, S1, s.nbm1);
+                double *const row = (second ? L.pb : L.pa) + (rl * TPn + k) * ZP;
+                row[p] = pipe;
+                if (p == ZG - 1 && ZP != ZG) row[ZG] = pipe;  // (read, not used)
+              }
+              for (int y = wv; y < nb * TPn; y += kSearchThreads / 64) {  // a wave, its lanes the pools
+                const int rl = (int)fast_div((uint32_t)y, mg_tpn), k = y - rl * TPn, width = L.width[k], p = lane < ZG ? lane : 0;
+                const State *par = state_at(cur, block0 + rl);
+                const int count = first ? 0 : (int)reinterpret_cast<const uint16_t *>(par + 1)[p];
+                const bool fits = lane < ZG && ((L.fit[tb * TPn + k] >> (L.zg[p] >> 8)) & 1u) != 0;
+                const unsigned long long h = __builtin_amdgcn_ballot_w64(fits && count + width <= L.cap[p]);
+                const unsigned long long w2 = __builtin_amdgcn_ballot_w64(fits && count + 2 * width <= L.cap[p]);
+                if (lane == 0) { L.half[y] = (s.D & 1) ? 0 : h; L.whole[y] = w2; }
+                if (lane == 0 && k == 0) {
+                  L.mx[2 * rl] = first ? fmax(0.0, S2) : fmax(par->msync, S2);
+                  L.mx[2 * rl + 1] = first ? fmax(0.0, S3) : fmax(par->mupd, S3);
+                }
+              }
+              __syncthreads();
+            }
+            i1 = min(i1, block1 * ITEMS);
+          }
+          for (int x0 = i0; x0 < i1; x0 += kSearchThreads) {  // uniform
+            const int x = x0 + t;
+            unsigned long long bk = ~0ull;  // (no bound has this pattern)
+            uint32_t bi = ~0u;
+            if (x < i1 && phase == 1) {
+              const int e = (int)fast_div((uint32_t)x, mg_inner), in = x - e * INNER;
+              int r, pa, pb, pk;
+              choice(L.sel[e], r, pa, pb, pk);
+              if (SPLIT) pb = in;
+              else pk = in;
+              SAcc o;
+              int runs;
+              unsigned long long kb;
+              if (search_step<MODE>(pl, L, s, first, state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs) &&
+                  search_keep(a, search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1), kb)) {
+                bk = kb;
+                bi = number(r, pa, pb, pk);
+              }
+            } else if (x < i1) {
+              const int r = (int)fast_div((uint32_t)x, mg_items), rem = x - r * ITEMS;  // (x < 2^19, ITEMS < 2^10)
+              const State *par = state_at(cur, r);
+              if (SPLIT) {
+                const int pa = (int)fast_div((uint32_t)rem, mg_tpn), k = rem - pa * TPn, y = (r - block0) * TPn + k;
+                const uint32_t zga = L.zg[pa];
+                const int za = zga & 255u, ga = zga >> 8;
+                const unsigned long long half = L.half[y], whole = L.whole[y];
+                const double ta = L.pa[y * ZP + pa], mx0 = L.mx[2 * (r - block0)], mx1 = L.mx[2 * (r - block0) + 1];
+                const double *row_b = L.pb + y * ZP, *sync = L.sync + ((tb * TPn + k) * Z + za) * ZP, *upd = L.upd + (tb * TPn + k) * ZP;
+                const double ua = fmax(mx1, upd[pa]);
+                // the second pools this state and first pool admit
+                unsigned long long cand = ((half >> pa) & 1ull) ? half & ~(1ull << pa) : 0ull;
+                cand |= whole & (1ull << pa);
+                if (a.max_runs != 0 && !first && par->runs >= a.max_runs)
+                  cand &= (par->runs == a.max_runs && pa == par->pool && (!STP || k == par->tpi)) ? 1ull << par->pool_b : 0ull;
+                expanded += (uint32_t)__popcll(cand);
+                int best_b = 0;
+                if (!need_c) {
+                  // (a bound of +inf, which no incumbent drops, must not look like none)
+                  double best_t = __builtin_huge_val();
+                  int none = -1;
+                  const double inc = a.has_inc ? a.inc : __builtin_huge_val();
+                  uint32_t c_lo = (uint32_t)cand, c_hi = (uint32_t)(cand >> 32);
+#pragma unroll 2
+                  for (int pb = 0; pb < ZP; pb += 2) {
+                    const double2 rb = *reinterpret_cast<const double2 *>(row_b + pb), sy = *reinterpret_cast<const double2 *>(sync + pb),
+                                  up = *reinterpret_cast<const double2 *>(upd + pb);
+                    const double T0 = (fmax(ta, rb.x) + fmax(mx0, sy.x)) + fmax(ua, up.x);
+                    const double T1 = (fmax(ta, rb.y) + fmax(mx0, sy.y)) + fmax(ua, up.y);
+                    const uint32_t word = pb < 32 ? c_lo : c_hi;
+                    const bool f0 = ((word >> (pb & 31)) & 1u) != 0 && T0 <= inc, f1 = ((word >> (pb & 31)) & 2u) != 0 && T1 <= inc;
+                    kept += (f0 ? 1u : 0u) + (f1 ? 1u : 0u);
+                    const bool b0 = f0 && (T0 < best_t || none < 0);
+                    best_t = b0 ? T0 : best_t;
+                    none = b0 ? pb : none;
+                    const bool b1 = f1 && (T1 < best_t || none < 0);
+                    best_t = b1 ? T1 : best_t;
+                    none = b1 ? pb + 1 : none;
+                  }
+                  if (none >= 0) { bk = (unsigned long long)__double_as_longlong(best_t); best_b = none; }
+                } else {
+                  for (; cand; cand &= cand - 1) {
+                    const int pb = __builtin_ctzll(cand);
+                    const uint32_t zgb = L.zg[pb];
+                    const int zb = zgb & 255u, gb = zgb >> 8;
+                    SBound b;
+                    b.T = (fmax(ta, row_b[pb]) + fmax(mx0, sync[pb])) + fmax(ua, upd[pb]);
+                    double rent = L.dtp[k] * (0.5 * (L.price[ga] + L.price[gb])), comm = 0.0;
+                    const double ring = zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
+                    if (!first) {
+                      rent = par->dol + rent;
+                      comm = par->comm;
+                      if (par->zone != za) comm += L.comm[par->zone * Z + za];
+                      if (par->zone_b != zb) comm += L.comm[par->zone_b * Z + zb];
+                    }
+                    b.C = (rent + S4) / 3600.0 * b.T + (comm + ring);
+                    unsigned long long kb;
+                    if (search_keep(a, b, kb)) {
+                      ++kept;
+                      if (kb < bk) { bk = kb; best_b = pb; }
+                    }
+                  }
+                }
+                bi = number(r, pa, best_b, k);
+              } else {
+                const int pa = rem;
+                const uint32_t zga = L.zg[pa];
+                const int z = zga & 255u, g = zga >> 8;
+                const int count = first ? 0 : (int)reinterpret_cast<const uint16_t *>(par + 1)[pa], cap = L.cap[pa];
+                SPart o;
+                o.sum = o.maxt = o.xb_open = 0.0;
+                double msync = S2, mupd = S3;
+                if (!first) {
+                  o = search_close(false, &par->part[0], par->zone, z, Z, 0.0, L.xfer);
+                  msync = fmax(par->msync, S2);
+                  mupd = fmax(par->mupd, S3);
+                }
+                int best_b = 0;
+                for (int k = 0; k < TPn; ++k) {
+                  const int width = STP ? L.width[k] : 1;
+                  bool ok = ((L.fit[tb * TPn + k] >> g) & 1u) != 0 && count + width <= cap;
+                  if (a.max_runs != 0 && !first)
+                    ok = ok && par->runs + ((pa != par->pool || (STP && k != par->tpi)) ? 1 : 0) <= a.max_runs;
+                  if (!ok) continue;
+                  ++expanded;
+                  const double *raw = L.raw + (size_t)(tb * TPn + k) * pl.row_w;
+                  o.c_open = raw[g];
+                  SBound b;
+                  b.T = (search_pipe(o, S0, S1, s.nbm1) + fmax(msync, L.sync[(tb * TPn + k) * Z + z])) + fmax(mupd, raw[G + g]);
+                  b.C = 0.0;
+                  if (need_c) {
+                    double rent = L.dtp[k] * L.price[g], comm = 0.0;
+                    if (!first) {
+                      rent = par->dol + rent;
+                      comm = par->comm;
+                      if (par->zone != z) comm += L.comm[par->zone * Z + z];
+                    }
+                    b.C = (rent + S4) / 3600.0 * b.T + comm;
+                  }
+                  unsigned long long kb;
+                  if (search_keep(a, b, kb)) {
+                    ++kept;
+                    if (kb < bk) { bk = kb; best_b = k; }
+                  }
+                }
+                bi = number(r, pa, pa, best_b);
+              }
+            }
+            if (last) {
+              if (key_id_less(bk, bi, best_k, best_i) && bk != ~0ull) { best_k = bk; best_i = bi; }
+              continue;
+            }
+            const bool keep = bk != ~0ull && bk <= tau;
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+            if (m == 0) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(counter, (uint32_t)__popcll(m));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            if (keep) {
+              at += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+              L.key[at] = bk;
+              L.id[at] = bi;
+            }
+          }
+          i0 = i1;
+          if (last) {
+            if (i0 >= n_all) break;
+            continue;
+          }
+          const bool done = i0 >= n_all;
+          if (done && phase == 0) {  // how many were kept in all
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) kept += __shfl_xor(kept, off);
+            if (lane == 0 && kept) atomicAdd(&s_kept[cur], kept);
+          }
+          __syncthreads();
+          used = (int)*counter;
+          if (done && phase == 0) {
+            kept = s_kept[cur];
+            cut = kept > (uint32_t)W;
+            for (int i = t; i < n_raw; i += kSearchThreads) L.raw[(tb ^ 1) * n_raw + i] = i < kSearchThreads ? ahead : search_row<STP>(pl, s, j + 1)[i];
+          }
+          // the W smallest, at the end of a phase and when there is no room for what is left
+          sorted = false;
+          if (used > W && (done || buf - used < min(n_all - i0, buf - W))) {  // uniform
+            search_select(L, sh, used, W, gather);
+            used = W;
+            tau = L.key[W - 1];
+            sorted = true;
+            if (!done) {
+              if (t == 0) *counter = (uint32_t)W;
+              __syncthreads();
+            }
+          }
+          if (done) break;
         }
-        keep = keep && kb <= tau;
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-        if (m == 0) return;
-        uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(counter, (uint32_t)__popcll(m));
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-        if (keep) {
-          at += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-          L.key[at] = kb;
-          L.id[at] = id;
-        }
-      };
-      // room for n more candidates; otherwise the W smallest stay and bound the others
-      auto make_room = [&](int n) {  // uniform; a barrier in any case
-        __syncthreads();
-        int used = (int)*counter;
-        if (buf - used < n) {
-          search_select(L, sh, used, W, gather);
-          used = W;
-          tau = L.key[W - 1];
-          if (t == 0) *counter = (uint32_t)W;
+        if (last || kept == 0) break;  // uniform
+        n = used;
+        if (phase == 0 && INNER > 1) {
+          for (int x = t; x < n; x += kSearchThreads) L.sel[x] = L.id[x];
           __syncthreads();
         }
-        return buf - used;
-      };
-      const int n_items = n_cur * ITEMS;
-      int room = buf, block0 = -1, block1 = 0;
-      for (int i0 = 0; i0 < n_items;) {  // uniform
-        int i1 = n_items;
-        if (!last) {
-          if (i0) room = make_room(min(n_items - i0, buf - W));
-          i1 = min(i1, i0 + room);
-        }
-        if (SPLIT) {
-          if (i0 >= block1 * ITEMS) {  // the next states' tables
-            if (block0 >= 0) __syncthreads();
-            block0 = block1;
-            block1 = min(n_cur, block0 + (int)a.block);
-            const int nb = block1 - block0;
-            for (int x = t; x < 2 * nb * ITEMS; x += kSearchThreads) {
-              const int second = x >= nb * ITEMS ? 1 : 0, y = x - second * nb * ITEMS;
-              const int rl = (int)fast_div((uint32_t)y, mg_items), rem = y - rl * ITEMS, k = (int)fast_div((uint32_t)rem, mg_zg),
-                        p = rem - k * ZG;
-              const uint32_t zg = L.zg[p];
-              const int z = zg & 255u, g = zg >> 8;
-              const State *par = j == 0 ? nullptr : state_at(cur, block0 + rl);
-              const int pz = par ? (int)(L.zg[second ? par->pool_b : par->pool] & 255u) : 0;
-              const SPart o = search_close(par ? &par->part[second && SPLIT ? 1 : 0] : nullptr, pz, z, Z,
-                                           L.raw[(tb * TPn + k) * pl.row_w + g], L.xfer);
-              (second ? L.pb : L.pa)[y] = search_pipe(o, S0, S1, s.nbm1);
-            }
-            for (int y = wv; y < nb * TPn; y += kSearchThreads / 64) {  // a wave, its lanes the pools
-              const int rl = (int)fast_div((uint32_t)y, mg_tpn), k = y - rl * TPn, width = L.width[k];
-              const State *par = j == 0 ? nullptr : state_at(cur, block0 + rl);
-              const int used = par && lane < ZG ? (int)reinterpret_cast<const uint16_t *>(par + 1)[lane] : 0;
-              const bool fits = lane < ZG && ((L.fit[tb * TPn + k] >> (L.zg[lane < ZG ? lane : 0] >> 8)) & 1u) != 0;
-              const unsigned long long h = __builtin_amdgcn_ballot_w64(fits && used + width <= L.cap[lane < ZG ? lane : 0]);
-              const unsigned long long w2 = __builtin_amdgcn_ballot_w64(fits && used + 2 * width <= L.cap[lane < ZG ? lane : 0]);
-              if (lane == 0) { L.half[y] = (s.D & 1) ? 0 : h; L.whole[y] = w2; }
-              if (lane == 0 && k == 0) {
-                L.mx[2 * rl] = par ? fmax(par->msync, S2) : fmax(0.0, S2);
-                L.mx[2 * rl + 1] = par ? fmax(par->mupd, S3) : fmax(0.0, S3);
-              }
-            }
-            __syncthreads();
-          }
-          i1 = min(i1, block1 * ITEMS);
-        }
-        for (int x0 = i0; x0 < i1; x0 += kSearchThreads) {  // uniform
-          const int x = x0 + t;
-          bool keep = false;
-          unsigned long long bk = ~0ull;
-          uint32_t bi = ~0u;
-          if (x < i1) {
-            const int r = (int)fast_div((uint32_t)x, mg_items), rem = x - r * ITEMS;  // (x < 2^19, ITEMS < 2^10)
-            const State *par = j == 0 ? nullptr : state_at(cur, r);
-            if (SPLIT) {
-              const int pa = (int)fast_div((uint32_t)rem, mg_tpn), k = rem - pa * TPn, y = (r - block0) * TPn + k;
-              const uint32_t zga = L.zg[pa];
-              const int za = zga & 255u, ga = zga >> 8;
-              const unsigned long long half = L.half[y], whole = L.whole[y];
-              const double ta = L.pa[y * ZG + pa], mx0 = L.mx[2 * (r - block0)], mx1 = L.mx[2 * (r - block0) + 1];
-              const double *raw = L.raw + (size_t)(tb * TPn + k) * pl.row_w, *sync = L.sync + (tb * TPn + k) * Z * Z + za * Z;
-              const double ua = fmax(mx1, raw[G + ga]);
-              // the second pools this state and first pool admit
-              unsigned long long cand = ((half >> pa) & 1ull) ? half & ~(1ull << pa) : 0ull;
-              cand |= whole & (1ull << pa);
-              if (a.max_runs != 0 && par && par->runs >= a.max_runs)
-                cand &= (par->runs == a.max_runs && pa == par->pool && (!STP || k == par->tpi)) ? 1ull << par->pool_b : 0ull;
-              expanded += (uint32_t)__popcll(cand);
-              const uint32_t id0 = (uint32_t)(r * NCH + pa * ZG * TPn + k);
-              while (cand) {
-                const int pb = __builtin_ctzll(cand);
-                cand &= cand - 1;
-                const uint32_t zgb = L.zg[pb];
-                const int zb = zgb & 255u, gb = zgb >> 8;
-                SBound b;
-                b.T = (fmax(ta, L.pb[y * ZG + pb]) + fmax(mx0, sync[zb])) + fmax(ua, raw[G + gb]);
-                b.C = 0.0;
-                if (need_c) {
-                  const double dol = L.dtp[k] * (0.5 * (L.price[ga] + L.price[gb]));
-                  const double ring = zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
-                  double rent = dol, comm = ring;
-                  if (par) {
-                    const int pza = L.zg[par->pool] & 255u, pzb = L.zg[par->pool_b] & 255u;
-                    rent = par->dol + dol;
-                    comm = par->comm;
-                    if (pza != za) comm += L.comm[pza * Z + za];
-                    if (pzb != zb) comm += L.comm[pzb * Z + zb];
-                    comm = comm + ring;
-                  }
-                  b.C = (rent + S4) / 3600.0 * b.T + comm;
-                }
-                unsigned long long kb;
-                if (search_keep(a, b, kb)) {
-                  ++kept;
-                  keep = true;
-                  if (kb < bk) { bk = kb; bi = id0 + (uint32_t)(pb * TPn); }
-                }
-              }
-            } else {
-              const int pa = rem;
-              for (int k = 0; k < TPn; ++k) {
-                SAcc o;
-                int runs;
-                if (!search_step<MODE>(pl, L, s, par, tb, pa, pa, k, a.max_runs, o, runs)) continue;
-                ++expanded;
-                SBound b;
-                b.T = (search_pipe(o.part[0], S0, S1, s.nbm1) + fmax(o.msync, S2)) + fmax(o.mupd, S3);
-                b.C = need_c ? (o.dol + S4) / 3600.0 * b.T + o.comm : 0.0;
-                unsigned long long kb;
-                if (search_keep(a, b, kb)) {
-                  ++kept;
-                  keep = true;
-                  if (kb < bk) { bk = kb; bi = (uint32_t)(r * NCH + pa * TPn + k); }
-                }
-              }
-            }
-          }
-          take(keep, bk, bi);
-        }
-        i0 = i1;
       }
       my_total += expanded;
       if (last) {
@@ -924,7 +1043,7 @@ __global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, Sear
             choice(best_i, r, pa, pb, pk);
             SAcc o;
             int runs;
-            search_step<MODE>(pl, L, s, j == 0 ? nullptr : state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs);
+            search_step<MODE>(pl, L, s, first, state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs);
             const SBound b = search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1);
             res->T = b.T;
             res->C = b.C;
@@ -945,93 +1064,48 @@ __global__ __launch_bounds__(kSearchThreads) void k_search_beam(DevPlan pl, Sear
         }
         break;
       }
-      // how many were kept in all
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) kept += __shfl_xor(kept, off);
-      if (lane == 0 && kept) atomicAdd(&s_kept[cur], kept);
-      __syncthreads();
-      kept = s_kept[cur];
-      int n = (int)s_n[cur];
-      if (t < n_raw) L.raw[(tb ^ 1) * n_raw + t] = ahead;
       if (kept == 0) break;  // uniform
-      const bool cut = kept > (uint32_t)W;
       truncated = truncated || cut;
-      bool sorted = false;
-      if (n > W) {
-        search_select(L, sh, n, W, gather);
-        n = W;
-        sorted = INNER == 1;
-      }
-      if (INNER > 1) {  // the choices behind the best items, one by one
-        for (int x = t; x < n; x += kSearchThreads) L.sel[x] = L.id[x];
-        const int n_all = n * INNER;
-        tau = ~0ull;
-        counter = &s_m[cur];
-        int room2 = buf;
-        __syncthreads();
-        for (int x0 = 0; x0 < n_all;) {  // uniform
-          if (x0) room2 = make_room(min(n_all - x0, buf - W));
-          const int x1 = min(n_all, x0 + room2);
-          for (int y0 = x0; y0 < x1; y0 += kSearchThreads) {
-            const int y = y0 + t;
-            bool keep = false;
-            unsigned long long kb = ~0ull;
-            uint32_t id = 0;
-            if (y < x1) {
-              const int e = (int)fast_div((uint32_t)y, mg_inner), in = y - e * INNER;
-              int r, pa, pb, pk;
-              choice(L.sel[e], r, pa, pb, pk);
-              if (SPLIT) pb = in;
-              else pk = in;
-              id = (uint32_t)(r * NCH + (SPLIT ? (pa * ZG + pb) * TPn + pk : pa * TPn + pk));
-              SAcc o;
-              int runs;
-              if (search_step<MODE>(pl, L, s, j == 0 ? nullptr : state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs))
-                keep = search_keep(a, search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1), kb);
-            }
-            take(keep, kb, id);
-          }
-          x0 = x1;
-        }
-        __syncthreads();
-        n = (int)s_m[cur];
-        if (n > W) {
-          search_select(L, sh, n, W, gather);
-          n = W;
-          sorted = true;
-        }
-      }
       // a cut frontier: ascending bounds (as a selection leaves them); else the order of generation
       if (!sorted) {
         for (int x = t; x < n; x += kSearchThreads) { L.okey[x] = L.key[x]; L.oid[x] = L.id[x]; L.rank[x] = 0; }
         __syncthreads();
         search_place(L, n, W, !cut);
       }
-      // write the next frontier
-      for (int k = t; k < n; k += kSearchThreads) {
+      // write the next frontier: four lanes per state
+      for (int x = t; x < 4 * n; x += kSearchThreads) {
+        const int k = x >> 2, q = x & 3;
         const uint32_t cand = L.id[k];
         int r, pa, pb, pk;
         choice(cand, r, pa, pb, pk);
-        const State *par = j == 0 ? nullptr : state_at(cur, r);
+        const State *par = state_at(cur, r);
         State *const out = state_at(nxt, k);
+        const unsigned long long *cw = reinterpret_cast<const unsigned long long *>(par + 1);
+        unsigned long long *ow = reinterpret_cast<unsigned long long *>(out + 1);
+        const unsigned long long width = (unsigned long long)L.width[pk];
+        for (int w = q; w < (ZG + 3) / 4; w += 4) {  // the pool counts, four to a word
+          unsigned long long v = first ? 0ull : cw[w];
+          if (pa >> 2 == w) v += width << (16 * (pa & 3));
+          if (SPLIT && pb >> 2 == w) v += width << (16 * (pb & 3));
+          ow[w] = v;
+        }
         SAcc o;
         int runs;
-        search_step<MODE>(pl, L, s, par, tb, pa, pb, pk, a.max_runs, o, runs);
-        State st;
-        st.msync = o.msync; st.mupd = o.mupd; st.dol = o.dol; st.comm = o.comm;
-        st.part[0] = o.part[0];
-        if (SPLIT) st.part[SPLIT ? 1 : 0] = o.part[1];
-        st.pool = (uint8_t)pa; st.pool_b = (uint8_t)pb; st.runs = (uint8_t)runs; st.tpi = (uint8_t)pk;
-        for (int x = 0; x < 4; ++x) st.pad[x] = 0;
-        *out = st;
-        uint16_t *const cnt = reinterpret_cast<uint16_t *>(out + 1);
-        unsigned long long *const cw = reinterpret_cast<unsigned long long *>(out + 1);
-        for (int x = 0; x < (ZG + 3) / 4; ++x) cw[x] = par ? reinterpret_cast<const unsigned long long *>(par + 1)[x] : 0;
-        cnt[pa] = (uint16_t)(cnt[pa] + L.width[pk]);
-        if (SPLIT) cnt[pb] = (uint16_t)(cnt[pb] + L.width[pk]);
-        history[(size_t)j * W + k] = cand;
+        search_step<MODE>(pl, L, s, first, par, tb, pa, pb, pk, a.max_runs, o, runs);
+        if (q == 0) {
+          out->msync = o.msync; out->mupd = o.mupd; out->dol = o.dol; out->comm = o.comm;
+        } else if (q == 1) {
+          out->part[0] = o.part[0];
+        } else if (q == 2) {
+          if (SPLIT) out->part[SPLIT ? 1 : 0] = o.part[1];
+          history[(size_t)j * W + k] = cand;
+        } else {
+          const unsigned long long z = L.zg[pa] & 255u, zb = L.zg[pb] & 255u;
+          *reinterpret_cast<unsigned long long *>(&out->pool) = (unsigned long long)pa | (unsigned long long)pb << 8 |
+              (unsigned long long)(runs & 255) << 16 | (unsigned long long)pk << 24 | z << 32 | zb << 40;
+        }
       }
-      search_level<MODE>(pl, s, L, j + 1, tb ^ 1, t, kSearchThreads);
+      search_level<MODE>(pl, s, L, j + 1, layers, tp1, tb ^ 1, t, kSearchThreads);
       n_cur = n;
     }
     if (truncated) wg_trunc = 1;
