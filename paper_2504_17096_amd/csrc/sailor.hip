@@ -38,6 +38,7 @@ constexpr uint32_t kDirectManySurvivors = 8192;  // more than the select kernel 
 // a scan unit that takes more than kSplitAbove x the average load of a workgroup slot (and
 // kSplitAboveMean x the mean unit) is cut into parts of about kSplitTo x that load
 constexpr double kSplitAbove = 0.9, kSplitAboveMean = 1.5, kSplitTo = 0.7, kSplitToMean = 1.1;
+constexpr float kStagingTicks = 270.f;  // ticks (100 MHz) of a unit that its staging takes: 2.7 us
 constexpr uint32_t kRankOneWorkgroup = 128;  // largest k whose final ranking runs as one workgroup
 constexpr uint32_t kEvalUnitTarget = 16384;  // candidates per workgroup of the range evaluation
 constexpr unsigned kEvalRowsThreads = 512;
@@ -548,6 +549,13 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
   else launch_units_m<MODE, false>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
 }
 
+// One workgroup per unit, the availability ignored (plan creation).
+void launch_bounds(sailor_plan *pl, const ScanArgs &a) {
+  const dim3 grid((unsigned)pl->dev.n_units), block(pl->unit_threads);
+  if (pl->dev.mixed) k_units<MODE_BOUNDS, 0, false, true><<<grid, block, pl->lds_bytes>>>(pl->dev, a);
+  else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a);
+}
+
 template <int MODE>
 void launch_search(const sailor_plan *pl, const SearchArgs &a, unsigned root_wgs, size_t root_words, unsigned wgs,
                           size_t lds, hipStream_t st) {
@@ -1043,16 +1051,20 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
-  k_shape_agg<<<(unsigned)NS, 256>>>(d);
+  k_shape_agg<<<(unsigned)NS, kShapeAggThreads>>>(d);
   CREATE_TRY(hipGetLastError());
   CREATE_TRY(hipDeviceSynchronize());
   {
-    // Two passes over the space order the scan.  With availability ignored, a unit whose
-    // minimum is +inf holds no plan that memory, node size and batch divisibility allow,
-    // whatever the availability becomes: it is dropped for good.  Units of equal size still
-    // differ widely in cost, because invalid plans are pruned early, so a second pass
-    // records how long each remaining unit takes; they are then launched longest first,
-    // which also deals them evenly to the hardware's dispatch queues.
+    // Two passes over the space order the scan.  The first ignores the availability and records,
+    // per unit, the smallest iteration time and the smallest cost of the plans that memory, node
+    // size and batch divisibility allow: bounds that let a query pass over a unit whatever the
+    // availability becomes.  A unit that has no such plan is dropped for good.  Units of equal
+    // size still differ widely in cost, because invalid plans are pruned early, so the second
+    // pass records how long each remaining unit takes; they are launched longest first, which
+    // also deals them evenly to the hardware's dispatch queues.
+    // (Five passes did this -- which units hold a plan, how long each takes, the same once more
+    // after the cut below, either bound on its own: of the 1.1e9 plans of five zones with pairs of
+    // types 2.1 ms, now 0.9 ms.)
     size_t NU = pl->units.size();
     const size_t n_units_alloc = unit_cap;  // entries of the per-unit tables on the device
     float *d_cost = nullptr;
@@ -1063,16 +1075,20 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     ca.counters = pl->counters;
     ca.lim_s = ca.lim_l = kPosInf;
     ca.ignore_quota = 1;
-    launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
+    launch_bounds(pl, ca);
     CREATE_TRY(hipGetLastError());
-    std::vector<float> val(NU);
-    CREATE_TRY(hipMemcpy(val.data(), pl->umin_s, NU * sizeof(float), hipMemcpyDeviceToHost));
-    std::vector<UnitRec> kept;
-    for (size_t i = 0; i < NU; ++i)
-      if (val[i] < kPosInf) kept.push_back(pl->units[i]);
-    if (kept.empty()) kept.push_back(pl->units[0]);  // launches need a non-empty grid
-    pl->units.swap(kept);
-    NU = pl->units.size();
+    std::vector<float> val(NU), lb_time(NU), lb_cost(NU);
+    CREATE_TRY(hipMemcpy(lb_time.data(), pl->umin_s, NU * sizeof(float), hipMemcpyDeviceToHost));
+    CREATE_TRY(hipMemcpy(lb_cost.data(), pl->umin_l, NU * sizeof(float), hipMemcpyDeviceToHost));
+    size_t n_kept = 0;
+    for (size_t i = 0; i < NU; ++i) {
+      if (!(lb_time[i] < kPosInf) && !(n_kept == 0 && i + 1 == NU)) continue;  // launches need a non-empty grid
+      pl->units[n_kept] = pl->units[i];
+      lb_time[n_kept] = lb_time[i];
+      lb_cost[n_kept] = lb_cost[i];
+      ++n_kept;
+    }
+    pl->units.resize(NU = n_kept);
     d.n_units = (int)NU;
     UnitRec *d_units = const_cast<UnitRec *>(d.units);
     CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
@@ -1081,11 +1097,14 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
     CREATE_TRY(hipGetLastError());
     CREATE_TRY(hipMemcpy(val.data(), d_cost, NU * sizeof(float), hipMemcpyDeviceToHost));
+    ca.ignore_quota = 1;
+    ca.ucost = nullptr;
     // With the longest units first the launch ends about when the average load of a
     // workgroup slot is done, unless a unit on its own takes longer than that: such a unit is
     // cut into parts -- every part keeps the unit's records and takes a share of its lane
-    // space -- within the room the dropped units left in the tables, and the pass is timed
-    // again.  (Cutting units that are merely above the mean costs more in staging than it
+    // space -- within the room the dropped units left in the tables.  A part is taken to last its
+    // share of the unit's time beyond the staging, and its bounds are computed anew.  (Cutting
+    // units that are merely above the mean costs more in staging than it
     // gains: spaces with far more units than slots ran 4 % slower that way.)
     {
       double total = 0.0;
@@ -1106,8 +1125,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
       const size_t chunks_of_unit = ((size_t)d.MB * d.DP * (size_t)std::max(1, d.ZG - 1) + 63) / 64;
       const size_t most = std::max<size_t>(1, std::min<size_t>(255, chunks_of_unit / waves));
       size_t room = n_units_alloc - NU;
-      std::vector<UnitRec> cut;
-      cut.reserve(n_units_alloc);
+      std::vector<UnitRec> cut;  // the parts, which go behind the units that stay whole
+      std::vector<float> cut_val;
+      size_t n_whole = 0;
       for (size_t i = 0; i < NU; ++i) {
         UnitRec u = pl->units[i];
         size_t parts = 1;
@@ -1115,21 +1135,36 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
         else if (val[i] > above)
           parts = std::min<size_t>({most, (size_t)std::ceil(val[i] / target), room + 1});
         u.n_parts = (uint8_t)parts;
+        if (parts == 1) {
+          pl->units[n_whole] = u;
+          val[n_whole] = val[i];
+          lb_time[n_whole] = lb_time[i];
+          lb_cost[n_whole] = lb_cost[i];
+          ++n_whole;
+          continue;
+        }
         for (size_t c = 0; c < parts; ++c) {
           u.part = (uint8_t)c;
           cut.push_back(u);
+          cut_val.push_back(std::min(val[i], kStagingTicks) + std::max(0.f, val[i] - kStagingTicks) / (float)parts);
         }
         room -= parts - 1;
       }
-      if (cut.size() != NU) {
-        pl->units.swap(cut);
-        NU = pl->units.size();
-        d.n_units = (int)NU;
-        val.resize(NU);
-        CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
-        launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
+      if (!cut.empty()) {
+        NU = n_whole + cut.size();
+        pl->units.resize(n_whole);
+        pl->units.insert(pl->units.end(), cut.begin(), cut.end());
+        val.resize(n_whole);
+        val.insert(val.end(), cut_val.begin(), cut_val.end());
+        lb_time.resize(NU);
+        lb_cost.resize(NU);
+        d.n_units = (int)cut.size();  // the parts alone
+        CREATE_TRY(hipMemcpy(d_units, cut.data(), cut.size() * sizeof(UnitRec), hipMemcpyHostToDevice));
+        launch_bounds(pl, ca);
         CREATE_TRY(hipGetLastError());
-        CREATE_TRY(hipMemcpy(val.data(), d_cost, NU * sizeof(float), hipMemcpyDeviceToHost));
+        CREATE_TRY(hipMemcpy(&lb_time[n_whole], pl->umin_s, cut.size() * sizeof(float), hipMemcpyDeviceToHost));
+        CREATE_TRY(hipMemcpy(&lb_cost[n_whole], pl->umin_l, cut.size() * sizeof(float), hipMemcpyDeviceToHost));
+        d.n_units = (int)NU;
       }
     }
     std::vector<uint32_t> order(NU);
@@ -1140,19 +1175,14 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     for (size_t i = 0; i < NU; ++i) sorted[i] = pl->units[order[i]];
     pl->units.swap(sorted);
     CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
-    // Per unit (in its final order), the smallest iteration time and the smallest cost over the
-    // plans that do not depend on the availability: bounds that let a query pass over a unit.
-    ca.ignore_quota = 1;
-    ca.ucost = nullptr;
-    launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
-    CREATE_TRY(hipMemcpy(pl->lb_time, pl->umin_s, NU * sizeof(float), hipMemcpyDeviceToDevice));
-    launch_units<MODE_SCAN>(pl, SAILOR_MIN_COST, 0, ca, nullptr, nullptr, nullptr);
-    CREATE_TRY(hipMemcpy(pl->lb_cost, pl->umin_s, NU * sizeof(float), hipMemcpyDeviceToDevice));
-    CREATE_TRY(hipGetLastError());
-    // ... and the units sorted by either bound: the host then knows how many units a limit
-    // leaves alive, and the device which
+    // the bounds in the units' final order, and the units sorted by either bound: the host then
+    // knows how many units a limit leaves alive, and the device which
+    const std::vector<uint32_t> final_order = order;
     for (int which = 0; which < 2; ++which) {
-      CREATE_TRY(hipMemcpy(val.data(), which ? pl->lb_cost : pl->lb_time, NU * sizeof(float), hipMemcpyDeviceToHost));
+      const std::vector<float> &lb = which ? lb_cost : lb_time;
+      for (size_t i = 0; i < NU; ++i) val[i] = lb[final_order[i]];
+      CREATE_TRY(hipMemcpy(which ? pl->lb_cost : pl->lb_time, val.data(), NU * sizeof(float), hipMemcpyHostToDevice));
+      for (size_t i = 0; i < NU; ++i) order[i] = (uint32_t)i;
       std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return val[x] < val[y]; });
       std::vector<float> &sorted_lb = which ? pl->lb_cost_sorted : pl->lb_time_sorted;
       sorted_lb.resize(NU);

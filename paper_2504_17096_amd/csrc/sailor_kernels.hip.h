@@ -202,27 +202,33 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ uint64_t stage_bytes(const DevPlan &pl, uint32_t rs, int i, int P,
-                                                int tp, int64_t nb, uint64_t act) {
-  return stage_bytes_of(pl.st_params[rs + i], pl.st_n[rs + i], pl.bpp, i, P, tp, nb, act);
-}
-
 // Segment aggregates of one shape: everything of a segment that does not depend on
-// the pool it is placed on.
-__global__ void k_shape_agg(DevPlan pl) {
+// the pool it is placed on.  One workgroup per shape; a thread per (degree, segment, ...) entry
+// walks the segment's stages.  Bound by the latency of those walks: what a stage contributes is
+// read ready-made from its record (st_row; the shard sizes were 64-bit divisions per entry and
+// stage), the walks are unrolled so that their loads are in flight together, and eight waves per
+// shape shorten them.
+constexpr int kShapeAggThreads = 512;
+__global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
   const uint32_t shp = blockIdx.x;
   const ShapeRec sh = pl.shapes[shp];
   const int G = pl.G, GX = pl.GX, MB = pl.MB, TP = pl.TP, DP = pl.DP, P = sh.P;
   const int t = threadIdx.x, nt = blockDim.x;
+  const size_t row_stride = (size_t)MB * TP * pl.row_w;          // from stage to stage
+  const double *const rows = pl.st_row + sh.row_stage * row_stride;
   // need[tp][seg][mb][dp], syncz, upd
   for (int it = t; it < TP * 3 * MB * DP; it += nt) {
     int d = it % DP, m = (it / DP) % MB, seg = (it / (DP * MB)) % 3, k = it / (DP * MB * 3);
     uint64_t mx = 0;
-    int64_t nb = pl.nb[m * DP + d];
+    const int64_t nb = pl.nb[m * DP + d];
     if (seg < sh.s && nb > 0) {
-      uint64_t act = pl.act[m * TP + k];
+      const uint64_t act = pl.act[m * TP + k];
+      const double *const shard_bytes = rows + (size_t)k * pl.row_w + 2 * G;
+#pragma unroll 4
       for (int i = sh.lo[seg]; i < sh.lo[seg] + sh.n[seg]; ++i) {
-        uint64_t b = stage_bytes(pl, sh.row_stage, i, P, pl.tpv[k], nb, act);
+        const int64_t in_flight = (int64_t)(P - i) < nb ? (int64_t)(P - i) : nb;
+        const uint64_t b = (uint64_t)__double_as_longlong(shard_bytes[i * row_stride]) +
+                           act_bytes((int)in_flight, pl.st_n[sh.row_stage + i], act);
         mx = b > mx ? b : mx;
       }
     }
@@ -231,23 +237,33 @@ __global__ void k_shape_agg(DevPlan pl) {
   for (int it = t; it < TP * 3 * pl.Z; it += nt) {
     int z = it % pl.Z, seg = (it / pl.Z) % 3, k = it / (pl.Z * 3);
     double mx = 0.0;  // seconds of the slowest stage's gradient buffer over the zone's link
-    if (seg < sh.s)
-      for (int i = sh.lo[seg]; i < sh.lo[seg] + sh.n[seg]; ++i) {
-        uint64_t shard = (pl.st_params[sh.row_stage + i] + pl.tpv[k] - 1) / (uint64_t)pl.tpv[k];
-        const double bytes = (double)shard * (double)pl.gb;
-        mx = fmax(mx, bytes / link_bw(pl, z, z, bytes));
+    if (seg < sh.s) {
+      const double *const grads = rows + (size_t)k * pl.row_w + 2 * G + 1;
+      const int lo = sh.lo[seg], hi = lo + sh.n[seg];
+      if (pl.n_bw_coef > 0) {
+        for (int i = lo; i < hi; ++i) {
+          const double bytes = grads[i * row_stride];
+          mx = fmax(mx, bytes / link_bw(pl, z, z, bytes));
+        }
+      } else {  // one bandwidth for all: the largest buffer is the slowest (division rounds monotonically)
+#pragma unroll 4
+        for (int i = lo; i < hi; ++i) mx = fmax(mx, grads[i * row_stride]);
+        mx = mx / pl.bw[z * pl.Z + z];
       }
+    }
     pl.syncz[agg_slot(pl, shp, k, seg) * pl.Z + z] = (float)mx;
   }
   for (int it = t; it < TP * 3 * GX; it += nt) {
     int g = it % GX, seg = (it / GX) % 3, k = it / (GX * 3);
     const int ga = pl.xt[g] & 255, gb = pl.xt[g] >> 8;
     double mx = 0.0;
-    if (seg < sh.s)
+    if (seg < sh.s) {
+#pragma unroll 4
       for (int i = sh.lo[seg]; i < sh.lo[seg] + sh.n[seg]; ++i) {
         mx = fmax(mx, pl.st_u[((size_t)(sh.row_stage + i) * G + ga) * TP + k]);
         mx = fmax(mx, pl.st_u[((size_t)(sh.row_stage + i) * G + gb) * TP + k]);
       }
+    }
     pl.upd[agg_slot(pl, shp, k, seg) * GX + g] = (float)mx;
   }
   for (int it = t; it < TP * 3 * GX * MB; it += nt) {
@@ -256,16 +272,20 @@ __global__ void k_shape_agg(DevPlan pl) {
     float4 v = make_float4(0.f, 0.f, kNegInf, kNegInf);
     if (seg < sh.s) {
       const int lo = sh.lo[seg], n = sh.n[seg];
-      double sum = 0.0, mxi = -__builtin_huge_val(), fst = 0.0, lst = 0.0;
-      for (int i = lo; i < lo + n; ++i) {
-        // replicas of two types: the slower one sets the stage's pace (straggler, Sec. 4.3)
-        double c = fmax(pl.st_c[(((size_t)(sh.row_stage + i) * G + ga) * MB + m) * TP + k],
-                        pl.st_c[(((size_t)(sh.row_stage + i) * G + gb) * MB + m) * TP + k]);
+      // replicas of two types: the slower one sets the stage's pace (straggler, Sec. 4.3)
+      auto stage = [&](int i) {
+        return fmax(pl.st_c[(((size_t)(sh.row_stage + i) * G + ga) * MB + m) * TP + k],
+                    pl.st_c[(((size_t)(sh.row_stage + i) * G + gb) * MB + m) * TP + k]);
+      };
+      const double fst = stage(lo), lst = stage(lo + n - 1);
+      double sum = fst, mxi = -__builtin_huge_val();
+#pragma unroll 4
+      for (int i = lo + 1; i < lo + n - 1; ++i) {
+        const double c = stage(i);
         sum += c;
-        if (i == lo) fst = c;
-        if (i == lo + n - 1) lst = c;
-        if (i > lo && i < lo + n - 1) mxi = fmax(mxi, c);
+        mxi = fmax(mxi, c);
       }
+      if (n > 1) sum += lst;
       v = make_float4((float)sum, (float)fst, (float)lst, (float)mxi);
     }
     pl.ta[(agg_slot(pl, shp, k, seg) * GX + g) * MB + m] = v;
@@ -468,7 +488,10 @@ __device__ __forceinline__ uint32_t joint_quota_bits(const DevPlan &pl, int n_se
   return bits;
 }
 
-enum { MODE_SCAN = 0, MODE_COLLECT = 1 };
+// SCAN: a unit's smallest key over the candidates strictly / loosely within the constraint.
+// COLLECT: a unit's candidates under a threshold.  BOUNDS (plan creation, no constraint): a unit's
+// smallest iteration time and smallest cost, in the places of SCAN's two minima.
+enum { MODE_SCAN = 0, MODE_COLLECT = 1, MODE_BOUNDS = 2 };
 
 struct ScanArgs {
   float *umin_s, *umin_l;   // [n_units] minima over strictly / loosely constrained candidates
@@ -537,9 +560,12 @@ __device__ __forceinline__ void visit(const ScanArgs &a, float T, float C, bool 
                                       uint64_t idx, uint32_t shape, float &ms, float &ml) {
   const float key = OBJ == 0 ? T : C;
   const float con = OBJ == 0 ? C : T;
-  if (MODE == MODE_SCAN) {
+  if (MODE != MODE_COLLECT) {
     const float kf = feas ? key : kPosInf;
-    if (HASB) {
+    if (MODE == MODE_BOUNDS) {
+      ms = fminf(ms, kf);
+      ml = fminf(ml, feas ? con : kPosInf);
+    } else if (HASB) {
       ms = fminf(ms, con <= a.lim_s ? kf : kPosInf);
       ml = fminf(ml, con <= a.lim_l ? kf : kPosInf);
     } else {
@@ -876,7 +902,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   }
   any_all &= 7u;
   if (any_all != (1u << S) - 1u) {  // uniform over the workgroup
-    if (MODE == MODE_SCAN && t == 0) {
+    if (MODE != MODE_COLLECT && t == 0) {
       a.umin_s[uidx] = kPosInf;
       a.umin_l[uidx] = kPosInf;
       if (a.unit_gen) {
@@ -898,8 +924,8 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   else if (S == 2) unit_body<2, MODE, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, ms, ml);
   else unit_body<3, MODE, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, ms, ml);
 
-  if (MODE == MODE_SCAN) {
-    if (!HASB) ml = ms;
+  if (MODE != MODE_COLLECT) {
+    if (!HASB && MODE != MODE_BOUNDS) ml = ms;
     ms = wave_min(ms);
     ml = wave_min(ml);
     if ((t & 63) == 0) { red[0][t >> 6] = ms; red[1][t >> 6] = ml; }
@@ -915,7 +941,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
         a.unit_gen[uidx] = a.cur_gen;
         a.unit_seq[uidx] = a.call_seq;  // evaluated by this call
       }
-      unit_publish(a, uidx, ms, ml);
+      if (MODE == MODE_SCAN) unit_publish(a, uidx, ms, ml);
       if (a.ucost) a.ucost[uidx] = (float)(wall_clock64() - t_begin);
     }
   }
@@ -926,7 +952,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
 template <int MODE, int OBJ, bool HASB, bool MIXED>
 __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a) {
   extern __shared__ uint4 lds_raw[];
-  if (MODE == MODE_SCAN) {
+  if (MODE != MODE_COLLECT) {
     unit_work<MODE, OBJ, HASB, MIXED>(pl, a, blockIdx.x, 0, 1u, lds_raw);
   } else if (!a.ulist) {
     unit_work<MODE, OBJ, HASB, MIXED>(pl, a, blockIdx.x / a.n_sub, (int)(blockIdx.x % a.n_sub), a.n_sub,
