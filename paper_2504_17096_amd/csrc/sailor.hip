@@ -90,6 +90,77 @@ struct DeviceArena {  // every device allocation of a plan, freed together
   }
 };
 
+// The tables a plan keeps for its lifetime, as one allocation with one upload.  Pointers are
+// announced first and set by commit(): inputs (copied from host memory that must live until then),
+// zero-filled tables, uninitialised ones, each on a 256-byte boundary.  (Sixty allocations, twenty
+// copies of 20 to 40 us each and as many frees were 1.6 ms of the 5.1 ms that a new job on 1.1e9
+// plans took.)
+class TableSlab {
+ public:
+  template <typename T>
+  void input(const T **out, const T *src, size_t n) { add(kInput, out, src, n * sizeof(T)); }
+  template <typename T>
+  void zeroed(T **out, size_t n) { add(kZeroed, out, nullptr, n * sizeof(T)); }
+  template <typename T>
+  void table(T **out, size_t n) { add(kTable, out, nullptr, n * sizeof(T)); }
+  hipError_t commit(DeviceArena &arena) {
+    size_t end[3], at = 0;
+    for (int kind : {kInput, kZeroed, kTable}) {
+      for (Entry &e : entries_)
+        if (e.kind == kind) {
+          e.at = at;
+          at += (std::max<size_t>(e.bytes, 1) + 255) & ~(size_t)255;
+        }
+      end[kind] = at;
+    }
+    char *base = nullptr;
+    hipError_t err = arena.alloc(&base, at);
+    if (err != hipSuccess) return err;
+    std::vector<char> staging(end[kInput]);
+    for (const Entry &e : entries_) {
+      void *p = base + e.at;
+      std::memcpy(e.out, &p, sizeof p);
+      if (e.kind == kInput && e.bytes) std::memcpy(&staging[e.at], e.src, e.bytes);
+    }
+    if (!staging.empty()) err = hipMemcpy(base, staging.data(), staging.size(), hipMemcpyHostToDevice);
+    if (err == hipSuccess && end[kZeroed] > end[kInput])
+      err = hipMemset(base + end[kInput], 0, end[kZeroed] - end[kInput]);
+    return err;
+  }
+
+ private:
+  enum Kind { kInput, kZeroed, kTable };
+  struct Entry {
+    Kind kind;
+    void *out;  // where the pointer goes
+    const void *src;
+    size_t bytes, at;
+  };
+  void add(Kind kind, void *out, const void *src, size_t bytes) { entries_.push_back({kind, out, src, bytes, 0}); }
+  std::vector<Entry> entries_;
+};
+
+// The positions 0 .. n - 1 in ascending (descending) order of non-negative values, equal ones in
+// the order they come in: three counting passes over the values' bits.
+std::vector<uint32_t> order_by(const float *values, size_t n, bool descending) {
+  constexpr int kBits = 11, kBins = 1 << kBits;
+  std::vector<uint32_t> from(n), to(n), keys(n);
+  for (size_t i = 0; i < n; ++i) {
+    const uint32_t bits = __builtin_bit_cast(uint32_t, values[i]) & 0x7fffffffu;
+    keys[i] = descending ? 0x7fffffffu - bits : bits;
+    from[i] = (uint32_t)i;
+  }
+  for (int shift = 0; shift < 32; shift += kBits) {
+    uint32_t at[kBins] = {};
+    for (uint32_t k : keys) ++at[(k >> shift) & (kBins - 1)];
+    uint32_t sum = 0;
+    for (uint32_t &a : at) { const uint32_t c = a; a = sum; sum += c; }
+    for (uint32_t i : from) to[at[(keys[i] >> shift) & (kBins - 1)]++] = i;
+    from.swap(to);
+  }
+  return from;
+}
+
 }  // namespace
 
 struct sailor_plan {
@@ -110,7 +181,7 @@ struct sailor_plan {
   ResultHeader last_hdr{};         // of the last successful selection
   bool have_hdr = false;
   int32_t *d_avail = nullptr;
-  int32_t *h_avail = nullptr;      // pinned staging of the availability table
+  int32_t *h_avail = nullptr;      // pinned staging of the availability table (behind h_result)
   const int32_t *h_avail_dev = nullptr;  // the same memory as the device addresses it
   bool avail_dirty = false;        // h_avail is newer than the device copy
   bool upload_pending = false;     // an asynchronous upload from h_avail was enqueued
@@ -403,11 +474,15 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
   }
   // Largest units first, so that the small ones fill the tail of the launch (the order is
   // refined by a timed pass once the tables are on the device).
-  auto unit_cost = [&](const UnitRec &u) {  // candidates of the unit
-    return innerp * (uint64_t)u.o_cnt * (u.s == 3 ? (uint64_t)(ZG - 1) : 1u);
-  };
-  std::stable_sort(pl->units.begin(), pl->units.end(),
-                   [&](const UnitRec &a, const UnitRec &b) { return unit_cost(a) > unit_cost(b); });
+  {
+    std::vector<float> cost;  // candidates of the unit / innerp: whole numbers below 2^24
+    cost.reserve(pl->units.size());
+    for (const UnitRec &u : pl->units) cost.push_back((float)((uint32_t)u.o_cnt * (u.s == 3 ? (uint32_t)(ZG - 1) : 1u)));
+    std::vector<UnitRec> sorted;
+    sorted.reserve(pl->units.size());
+    for (uint32_t i : order_by(cost.data(), cost.size(), true)) sorted.push_back(pl->units[i]);
+    pl->units.swap(sorted);
+  }
   // Waves per workgroup: the lanes of a unit cover MB*DP*ZG triples in chunks of 64; pick
   // the wave count (2..8) that leaves the fewest idle wave slots in the last round.
   const uint64_t chunks = (innerp + 63) / 64;
@@ -838,7 +913,6 @@ sailor_status sailor_plan_destroy(sailor_plan *pl) {
   (void)hipSetDevice(pl->device);
   pl->arena.release();
   if (pl->h_result) (void)hipHostFree(pl->h_result);
-  if (pl->h_avail) (void)hipHostFree(pl->h_avail);
   if (pl->ev_upload) (void)hipEventDestroy(pl->ev_upload);
   for (hipEvent_t e : pl->ev)
     if (e) (void)hipEventDestroy(e);
@@ -915,135 +989,118 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   } while (0)
 
   CREATE_TRY(hipGetDevice(&pl->device));
-  DeviceArena &ar = pl->arena;
+  TableSlab slab;
   const int G = d.G, GX = d.GX, Z = d.Z, ZG = d.ZG, ZGr = d.ZGr, MB = d.MB, TP = d.TP, DP = d.DP,
             L = p->n_layers;
   const size_t Lc = p->uniform_layers ? 1 : (size_t)L;
   const size_t RS = (size_t)d.n_row_stages, NS = pl->shapes.size();
 
   // inputs, copied as they are
-  CREATE_TRY(ar.alloc(&pl->d_avail, ZGr));
-  CREATE_TRY(hipMemcpy(pl->d_avail, p->avail, ZGr * sizeof(int32_t), hipMemcpyHostToDevice));
-  d.avail = pl->d_avail;
-  CREATE_TRY(hipHostMalloc(reinterpret_cast<void **>(&pl->h_avail), ZGr * sizeof(int32_t), 0));
-  {
-    void *dev_view = nullptr;
-    CREATE_TRY(hipHostGetDevicePointer(&dev_view, pl->h_avail, 0));
-    pl->h_avail_dev = static_cast<const int32_t *>(dev_view);
-  }
+  slab.input(&d.avail, p->avail, ZGr);
   CREATE_TRY(hipEventCreateWithFlags(&pl->ev_upload, hipEventDisableTiming));
   d.P_max = 0;
   for (int ip = 0; ip < p->n_pp; ++ip) d.P_max = std::max(d.P_max, (int)p->pp_values[ip]);
   d.W_max = d.P_max * p->tp_values[TP - 1];
-  CREATE_TRY(ar.alloc(&d.qw, (size_t)(d.W_max + 1) * ZG));
-  if (d.mixed) CREATE_TRY(ar.alloc(&d.qh, (size_t)(2 * d.W_max + 1) * ZGr));
-  CREATE_TRY(ar.alloc(&d.row_gen, 1));
-  CREATE_TRY(hipMemset(d.row_gen, 0, sizeof(uint32_t)));
-  CREATE_TRY(ar.alloc(&d.h1m, ZG));
-  CREATE_TRY(ar.alloc(&d.isect, (size_t)2 * ZG));
-  {
-    std::vector<uint16_t> xt;
-    for (int a = 0; a < G; ++a) xt.push_back((uint16_t)(a | (a << 8)));
-    if (d.mixed)
-      for (int a = 0; a < G; ++a)
-        for (int b = a + 1; b < G; ++b) xt.push_back((uint16_t)(a | (b << 8)));
-    pl->xt = xt;
-    CREATE_TRY(ar.upload(&d.xt, xt.data(), xt.size()));
-  }
-  {
-    std::vector<int32_t> vals(p->dp_values, p->dp_values + DP);
-    vals.insert(vals.end(), p->tp_values, p->tp_values + TP);
-    CREATE_TRY(ar.upload(&d.vals, vals.data(), vals.size()));
-  }
-  CREATE_TRY(ar.upload(&d.cap, p->mem_capacity, G));
-  CREATE_TRY(ar.upload(&d.res, p->mem_reserved, G));
-  CREATE_TRY(ar.upload(&d.node, p->gpus_per_node, G));
-  CREATE_TRY(ar.upload(&d.price, p->price_per_hour, G));
-  CREATE_TRY(ar.upload(&d.bw, p->bandwidth, (size_t)Z * Z));
-  if (p->egress_per_byte) CREATE_TRY(ar.upload(&d.egress, p->egress_per_byte, (size_t)Z * Z));
-  CREATE_TRY(ar.upload(&d.act, p->act_store_bytes, (size_t)MB * TP));
-  CREATE_TRY(ar.upload(&d.p2p, p->p2p_bytes, MB));
+  slab.table(&d.qw, (size_t)(d.W_max + 1) * ZG);
+  if (d.mixed) slab.table(&d.qh, (size_t)(2 * d.W_max + 1) * ZGr);
+  slab.zeroed(&d.row_gen, 1);
+  slab.table(&d.h1m, ZG);
+  slab.table(&d.isect, (size_t)2 * ZG);
+  for (int a = 0; a < G; ++a) pl->xt.push_back((uint16_t)(a | (a << 8)));
+  if (d.mixed)
+    for (int a = 0; a < G; ++a)
+      for (int b = a + 1; b < G; ++b) pl->xt.push_back((uint16_t)(a | (b << 8)));
+  slab.input(&d.xt, pl->xt.data(), pl->xt.size());
+  std::vector<int32_t> vals(p->dp_values, p->dp_values + DP);
+  vals.insert(vals.end(), p->tp_values, p->tp_values + TP);
+  slab.input(&d.vals, vals.data(), vals.size());
+  slab.input(&d.cap, p->mem_capacity, G);
+  slab.input(&d.res, p->mem_reserved, G);
+  slab.input(&d.node, p->gpus_per_node, G);
+  slab.input(&d.price, p->price_per_hour, G);
+  slab.input(&d.bw, p->bandwidth, (size_t)Z * Z);
+  if (p->egress_per_byte) slab.input(&d.egress, p->egress_per_byte, (size_t)Z * Z);
+  slab.input(&d.act, p->act_store_bytes, (size_t)MB * TP);
+  slab.input(&d.p2p, p->p2p_bytes, MB);
   StageArgs sa{};
-  CREATE_TRY(ar.upload(&sa.layer_params, p->layer_params, L));
-  CREATE_TRY(ar.upload(&sa.t_fwd, p->t_fwd, (size_t)G * MB * TP * Lc));
-  CREATE_TRY(ar.upload(&sa.t_bwd, p->t_bwd, (size_t)G * MB * TP * Lc));
-  CREATE_TRY(ar.upload(&sa.t_upd, p->t_upd, (size_t)G * TP * Lc));
-  CREATE_TRY(ar.upload(&sa.st_flags, st_flags.data(), RS));
+  slab.input(&sa.layer_params, p->layer_params, L);
+  slab.input(&sa.t_fwd, p->t_fwd, (size_t)G * MB * TP * Lc);
+  slab.input(&sa.t_bwd, p->t_bwd, (size_t)G * MB * TP * Lc);
+  slab.input(&sa.t_upd, p->t_upd, (size_t)G * TP * Lc);
+  slab.input(&sa.st_flags, st_flags.data(), RS);
   sa.embed = p->embed_params; sa.head = p->head_params; sa.L = L; sa.uniform = p->uniform_layers ? 1 : 0;
-  CREATE_TRY(ar.upload(&d.st_n, st_n.data(), RS));
-  CREATE_TRY(ar.upload(&d.st_first, st_first.data(), RS));
-  CREATE_TRY(ar.upload(&d.shapes, pl->shapes.data(), NS));
-  CREATE_TRY(ar.upload(&d.blocks, pl->blocks.data(), pl->blocks.size()));
+  slab.input(&d.st_n, st_n.data(), RS);
+  slab.input(&d.st_first, st_first.data(), RS);
+  slab.input(&d.shapes, pl->shapes.data(), NS);
+  slab.input(&d.blocks, pl->blocks.data(), pl->blocks.size());
   // per-unit tables: one entry per unit as laid out (units dropped later leave room for the
   // parts of units that are cut); sailor_set_scan_unit_parts(n) cuts every unit into n parts
   // whatever the timing says and needs n times the room
   const long forced_parts = g_forced_unit_parts.load(std::memory_order_relaxed);
   const size_t unit_cap = pl->units.size() * (size_t)std::max(1L, forced_parts);
-  {
-    UnitRec *d_units_new = nullptr;
-    CREATE_TRY(ar.alloc(&d_units_new, unit_cap));
-    CREATE_TRY(hipMemcpy(d_units_new, pl->units.data(), pl->units.size() * sizeof(UnitRec),
-                         hipMemcpyHostToDevice));
-    d.units = d_units_new;
-  }
-  CREATE_TRY(ar.upload(&pl->d_eunits, pl->eunits.data(), pl->eunits.size()));
+  char *per_unit = nullptr;  // the tables that creation fills last, in one copy: records, bounds, orders
+  slab.table(&per_unit, unit_cap * (sizeof(UnitRec) + 4 * sizeof(float)));
+  slab.input(&pl->d_eunits, pl->eunits.data(), pl->eunits.size());
   // derived tables, filled by the set-up kernels
   d.n_bw_coef = p->n_bw_coef;
-  if (p->n_bw_coef > 0) CREATE_TRY(ar.upload(&d.bw_poly, p->bw_poly, (size_t)Z * Z * p->n_bw_coef));
-  CREATE_TRY(ar.alloc(&d.bwp, (size_t)MB * Z * Z));
-  CREATE_TRY(ar.alloc(&d.xsec, (size_t)MB * Z * Z));
-  if (!d.mixed) CREATE_TRY(ar.alloc(&d.list_tables, list_copy_words(d)));  // (not for problems with pairs of types)
-  CREATE_TRY(ar.alloc(&d.tsec_f, (size_t)MB * Z * Z));
-  CREATE_TRY(ar.alloc(&d.egs_f, (size_t)Z * Z));
-  CREATE_TRY(ar.alloc(&d.price_f, GX));
-  CREATE_TRY(ar.alloc(&d.xb_f, MB));
-  CREATE_TRY(ar.alloc(&d.cd_f, DP));
-  CREATE_TRY(ar.alloc(&d.nbm1_f, (size_t)MB * DP));
-  CREATE_TRY(ar.alloc(&d.dph_f, DP));
-  CREATE_TRY(ar.alloc(&d.nb, (size_t)MB * DP));
-  CREATE_TRY(ar.alloc(&d.divis, MB));
-  CREATE_TRY(ar.alloc(&d.st_params, RS));
+  if (p->n_bw_coef > 0) slab.input(&d.bw_poly, p->bw_poly, (size_t)Z * Z * p->n_bw_coef);
+  slab.table(&d.bwp, (size_t)MB * Z * Z);
+  slab.table(&d.xsec, (size_t)MB * Z * Z);
+  if (!d.mixed) slab.table(&d.list_tables, list_copy_words(d));  // (not for problems with pairs of types)
+  slab.table(&d.tsec_f, (size_t)MB * Z * Z);
+  slab.table(&d.egs_f, (size_t)Z * Z);
+  slab.table(&d.price_f, GX);
+  slab.table(&d.xb_f, MB);
+  slab.table(&d.cd_f, DP);
+  slab.table(&d.nbm1_f, (size_t)MB * DP);
+  slab.table(&d.dph_f, DP);
+  slab.table(&d.nb, (size_t)MB * DP);
+  slab.table(&d.divis, MB);
+  slab.table(&d.st_params, RS);
   // a stage record does not straddle cache lines (128 bytes): the evaluators of listed plans
   // fetch one per stage from anywhere in the table, and lines are what that costs
   d.row_w = 2u * (uint32_t)G + 2u;
   if (d.row_w <= 16u) while (d.row_w & (d.row_w - 1u)) ++d.row_w;
   else d.row_w = (d.row_w + 15u) & ~15u;
-  CREATE_TRY(ar.alloc(&d.st_row, RS * MB * TP * d.row_w));
-  CREATE_TRY(ar.alloc(&d.st_c, RS * G * MB * TP));
-  CREATE_TRY(ar.alloc(&d.st_f, RS * G * MB * TP));
-  CREATE_TRY(ar.alloc(&d.st_b, RS * G * MB * TP));
-  CREATE_TRY(ar.alloc(&d.st_u, RS * G * TP));
+  slab.table(&d.st_row, RS * MB * TP * d.row_w);
+  slab.table(&d.st_c, RS * G * MB * TP);
+  slab.table(&d.st_f, RS * G * MB * TP);
+  slab.table(&d.st_b, RS * G * MB * TP);
+  slab.table(&d.st_u, RS * G * TP);
   const size_t slots = NS * TP * 3;
-  CREATE_TRY(ar.alloc(&d.ta, slots * GX * MB));
-  CREATE_TRY(ar.alloc(&d.memok, slots * GX * MB));
-  CREATE_TRY(ar.alloc(&d.need, slots * MB * DP));
-  CREATE_TRY(ar.alloc(&d.syncz, slots * Z));
-  CREATE_TRY(ar.alloc(&d.upd, slots * GX));
-  // selection scratch
-  CREATE_TRY(ar.alloc(&pl->umin_s, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->umin_l, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->lb_time, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->lb_cost, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->order_time, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->order_cost, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->counters, (size_t)2 * CNT_COUNT));
-  CREATE_TRY(ar.alloc(&pl->ulist, unit_cap));
-  CREATE_TRY(ar.alloc(&pl->unit_gen, unit_cap));
-  CREATE_TRY(hipMemset(pl->unit_gen, 0, unit_cap * sizeof(uint32_t)));
-  CREATE_TRY(ar.alloc(&pl->unit_seq, unit_cap));
-  CREATE_TRY(hipMemset(pl->unit_seq, 0, unit_cap * sizeof(uint32_t)));
+  slab.table(&d.ta, slots * GX * MB);
+  slab.table(&d.memok, slots * GX * MB);
+  slab.table(&d.need, slots * MB * DP);
+  slab.table(&d.syncz, slots * Z);
+  slab.table(&d.upd, slots * GX);
+  // selection scratch (umin_l lies behind umin_s: creation reads both back in one copy)
+  slab.table(&pl->umin_s, 2 * unit_cap);
+  slab.table(&pl->counters, (size_t)2 * CNT_COUNT);
+  slab.table(&pl->ulist, unit_cap);
+  slab.zeroed(&pl->unit_gen, unit_cap);
+  slab.zeroed(&pl->unit_seq, unit_cap);
   pl->ubits_stride = (uint32_t)(unit_lds_records(ZG, MB) + (size_t)ZG);
-  CREATE_TRY(ar.alloc(&pl->ubits, unit_cap * (size_t)pl->ubits_stride));
-  CREATE_TRY(ar.alloc(&pl->surv, (size_t)pl->surv_cap));
-  CREATE_TRY(ar.alloc(&pl->ref, (size_t)pl->ref_cap));
-  CREATE_TRY(ar.alloc(&pl->staged, (size_t)SAILOR_MAX_K));
-  const size_t res_bytes = sizeof(ResultHeader) + 8 + (size_t)SAILOR_MAX_K * sizeof(RefRec);
-  CREATE_TRY(hipHostMalloc(&pl->h_result, res_bytes, hipHostMallocMapped));
+  slab.table(&pl->ubits, unit_cap * (size_t)pl->ubits_stride);
+  slab.table(&pl->staged, (size_t)SAILOR_MAX_K);
+  CREATE_TRY(slab.commit(pl->arena));
+  CREATE_TRY(pl->arena.alloc(&pl->surv, (size_t)pl->surv_cap));  // (these two can be replaced on their own)
+  CREATE_TRY(pl->arena.alloc(&pl->ref, (size_t)pl->ref_cap));
+  pl->d_avail = const_cast<int32_t *>(d.avail);
+  pl->umin_l = pl->umin_s + unit_cap;
+  d.units = reinterpret_cast<UnitRec *>(per_unit);
+  pl->lb_time = reinterpret_cast<float *>(per_unit + unit_cap * sizeof(UnitRec));
+  pl->lb_cost = pl->lb_time + unit_cap;
+  pl->order_time = reinterpret_cast<uint32_t *>(pl->lb_cost + unit_cap);
+  pl->order_cost = pl->order_time + unit_cap;
+  const size_t res_bytes = (sizeof(ResultHeader) + 8 + (size_t)SAILOR_MAX_K * sizeof(RefRec) + 127) & ~(size_t)127;
+  CREATE_TRY(hipHostMalloc(&pl->h_result, res_bytes + (size_t)ZGr * sizeof(int32_t), hipHostMallocMapped));
   std::memset(pl->h_result, 0, res_bytes);
   void *d_res = nullptr;
   CREATE_TRY(hipHostGetDevicePointer(&d_res, pl->h_result, 0));
   pl->d_hdr = static_cast<ResultHeader *>(d_res);
   pl->d_out = reinterpret_cast<RefRec *>(static_cast<char *>(d_res) + sizeof(ResultHeader));
+  pl->h_avail = reinterpret_cast<int32_t *>(static_cast<char *>(pl->h_result) + res_bytes);
+  pl->h_avail_dev = reinterpret_cast<const int32_t *>(static_cast<char *>(d_res) + res_bytes);
   for (hipEvent_t &e : pl->ev) CREATE_TRY(hipEventCreate(&e));
 
   k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
@@ -1053,7 +1110,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
   k_shape_agg<<<(unsigned)NS, kShapeAggThreads>>>(d);
   CREATE_TRY(hipGetLastError());
-  CREATE_TRY(hipDeviceSynchronize());
   {
     // Two passes over the space order the scan.  The first ignores the availability and records,
     // per unit, the smallest iteration time and the smallest cost of the plans that memory, node
@@ -1067,8 +1123,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     // types 2.1 ms, now 0.9 ms.)
     size_t NU = pl->units.size();
     const size_t n_units_alloc = unit_cap;  // entries of the per-unit tables on the device
-    float *d_cost = nullptr;
-    CREATE_TRY(ar.alloc(&d_cost, unit_cap));
+    UnitRec *d_units = const_cast<UnitRec *>(d.units);
+    CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
+    float *d_cost = reinterpret_cast<float *>(pl->order_time);  // (filled behind this)
     ScanArgs ca{};
     ca.umin_s = pl->umin_s;
     ca.umin_l = pl->umin_l;
@@ -1077,9 +1134,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     ca.ignore_quota = 1;
     launch_bounds(pl, ca);
     CREATE_TRY(hipGetLastError());
-    std::vector<float> val(NU), lb_time(NU), lb_cost(NU);
-    CREATE_TRY(hipMemcpy(lb_time.data(), pl->umin_s, NU * sizeof(float), hipMemcpyDeviceToHost));
-    CREATE_TRY(hipMemcpy(lb_cost.data(), pl->umin_l, NU * sizeof(float), hipMemcpyDeviceToHost));
+    std::vector<float> val(NU), lb_time(unit_cap + NU);
+    CREATE_TRY(hipMemcpy(lb_time.data(), pl->umin_s, lb_time.size() * sizeof(float), hipMemcpyDeviceToHost));
+    std::vector<float> lb_cost(lb_time.begin() + (ptrdiff_t)unit_cap, lb_time.end());
     size_t n_kept = 0;
     for (size_t i = 0; i < NU; ++i) {
       if (!(lb_time[i] < kPosInf) && !(n_kept == 0 && i + 1 == NU)) continue;  // launches need a non-empty grid
@@ -1090,7 +1147,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     }
     pl->units.resize(NU = n_kept);
     d.n_units = (int)NU;
-    UnitRec *d_units = const_cast<UnitRec *>(d.units);
     CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
     ca.ignore_quota = 0;
     ca.ucost = d_cost;
@@ -1167,32 +1223,28 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
         d.n_units = (int)NU;
       }
     }
-    std::vector<uint32_t> order(NU);
-    for (size_t i = 0; i < NU; ++i) order[i] = (uint32_t)i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](uint32_t x, uint32_t y) { return val[x] > val[y]; });
-    std::vector<UnitRec> sorted(NU);
-    for (size_t i = 0; i < NU; ++i) sorted[i] = pl->units[order[i]];
-    pl->units.swap(sorted);
-    CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
     // the bounds in the units' final order, and the units sorted by either bound: the host then
     // knows how many units a limit leaves alive, and the device which
-    const std::vector<uint32_t> final_order = order;
+    const std::vector<uint32_t> final_order = order_by(val.data(), NU, true);
+    std::vector<UnitRec> sorted(NU);
+    for (size_t i = 0; i < NU; ++i) sorted[i] = pl->units[final_order[i]];
+    pl->units.swap(sorted);
+    std::vector<char> tables(unit_cap * (sizeof(UnitRec) + 4 * sizeof(float)));  // as they lie in `per_unit`
+    std::memcpy(tables.data(), pl->units.data(), NU * sizeof(UnitRec));
+    float *const words = reinterpret_cast<float *>(&tables[unit_cap * sizeof(UnitRec)]);
     for (int which = 0; which < 2; ++which) {
       const std::vector<float> &lb = which ? lb_cost : lb_time;
       for (size_t i = 0; i < NU; ++i) val[i] = lb[final_order[i]];
-      CREATE_TRY(hipMemcpy(which ? pl->lb_cost : pl->lb_time, val.data(), NU * sizeof(float), hipMemcpyHostToDevice));
-      for (size_t i = 0; i < NU; ++i) order[i] = (uint32_t)i;
-      std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return val[x] < val[y]; });
+      std::memcpy(words + which * unit_cap, val.data(), NU * sizeof(float));
+      const std::vector<uint32_t> order = order_by(val.data(), NU, false);
+      std::memcpy(words + (2 + which) * unit_cap, order.data(), NU * sizeof(uint32_t));
       std::vector<float> &sorted_lb = which ? pl->lb_cost_sorted : pl->lb_time_sorted;
       sorted_lb.resize(NU);
       for (size_t i = 0; i < NU; ++i) sorted_lb[i] = val[order[i]];
-      CREATE_TRY(hipMemcpy(which ? pl->order_cost : pl->order_time, order.data(), NU * sizeof(uint32_t),
-                           hipMemcpyHostToDevice));
     }
+    CREATE_TRY(hipMemcpy(per_unit, tables.data(), tables.size(), hipMemcpyHostToDevice));
     k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
     CREATE_TRY(hipDeviceSynchronize());
-    ar.free_one(d_cost);
   }
 #undef CREATE_TRY
   *track = nullptr;
