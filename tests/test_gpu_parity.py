@@ -777,3 +777,34 @@ def test_selection_with_every_scan_unit_cut_into_parts(torch_cuda, name, parts):
                            objective, orc, bound)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("n_dp", [1, 4, 7, 8])
+def test_scan_at_the_edges_of_its_lane_space(torch_cuda, n_dp, mixed):
+    # three mb x n_dp degrees x six pools (five with three segments; nine and eight with pairs of types)
+    # in chunks of 64 lanes, walked from the last one down: 15 to 216 of them, 54 and 60 (one short
+    # chunk), 72 (a second of eight), 126, 192 (three whole ones); waves without a chunk, plans dropped
+    # on their leading segments.  Tight, loose and no bounds; fp64 values against the oracle's, 1e-9.
+    from dataclasses import replace
+    stream = torch_cuda.cuda.current_stream().cuda_stream
+    prob = replace(W.tiny_problem(72, n_layers=8, n_zones=3, seg3_max_pp=8), global_batch=3360,
+                   dp_values=np.arange(1, n_dp + 1, dtype=np.int32))
+    prob = prob.with_mixed_types() if mixed else prob
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        t, c, _, mask = orc.eval_batch(n_threads=THREADS)
+        ok = mask == 0
+        assert ok.any()
+        for objective in (MAX_THROUGHPUT, MIN_COST):
+            val = c if objective == MAX_THROUGHPUT else 1.0 / t
+            lo, hi = float(val[ok].min()), float(val[ok].max())
+            for bound in (None, off_data(lo + 0.02 * (hi - lo)), off_data(lo + 0.6 * (hi - lo))):
+                check_result(plan.best_plan(objective=objective, bound=bound, stream=stream),
+                             orc.best(objective=objective, bound=bound, n_threads=THREADS), orc)
+                for k in (1, 64):
+                    check_topk(plan.topk(k, objective=objective, bound=bound, stream=stream),
+                               orc.topk(k, objective=objective, bound=bound, n_threads=THREADS),
+                               objective, orc, bound)
+    finally:
+        plan.destroy()
