@@ -1047,6 +1047,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&d.bwp, (size_t)MB * Z * Z);
   slab.table(&d.xsec, (size_t)MB * Z * Z);
   if (!d.mixed) slab.table(&d.list_tables, list_copy_words(d));  // (not for problems with pairs of types)
+  slab.table(&d.direct_tables, direct_copy_words(d));
   slab.table(&d.tsec_f, (size_t)MB * Z * Z);
   slab.table(&d.egs_f, (size_t)Z * Z);
   slab.table(&d.price_f, GX);
@@ -1107,6 +1108,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   k_quota_table<<<quota_grid(d), 256>>>(d, d.avail, nullptr, 0u);
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
+  k_direct_tables<<<1, 256>>>(d);
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
   k_shape_agg<<<(unsigned)NS, kShapeAggThreads>>>(d);
   CREATE_TRY(hipGetLastError());
@@ -1342,7 +1344,9 @@ sailor_status sailor_eval_batch(sailor_plan *pl, uint64_t first, uint64_t count,
     pl->scan_timed = timed;
     return SAILOR_OK;
   }
-  launch(k_eval_direct, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st,
+  const uint64_t chunks = (count + kDirectThreads - 1) / kDirectThreads;
+  launch(k_eval_direct, dim3((unsigned)std::min<uint64_t>(chunks, kDirectWorkgroups)), dim3(kDirectThreads),
+         direct_lds_bytes(pl->dev), st,
          timed ? pl->ev[3] : nullptr, timed ? pl->ev[1] : nullptr, pl->dev, a);
   HIP_TRY(hipGetLastError());
   pl->total_timed = false;

@@ -138,6 +138,7 @@ struct DevPlan {
   // the shard (as an integer), bytes of its gradient buffer
   double *st_row;              // [rs][MB][TP][row_w]
   double *list_tables;         // the small tables of the evaluators of listed plans, as they lie in LDS
+  uint32_t *direct_tables;     // the same of the evaluator of index lists
   double *st_c;                // [rs][G][MB][TP] sum of fwd + bwd layer times
   double *st_f, *st_b;         // [rs][G][MB][TP] the two sums apart (event-by-event schedule)
   double *st_u;                // [rs][G][TP] sum of update times

@@ -1189,20 +1189,25 @@ __device__ __forceinline__ void decode_in_shape(const DevPlan &pl, uint32_t shap
   c.s = sh.s;
   c.k1 = sh.k1;
   c.k2 = sh.k2;
-  const uint32_t in = (uint32_t)(rem % pl.inner);
   uint32_t o = (uint32_t)(rem / pl.inner);
-  c.mb = in % pl.MB;
-  c.tp[0] = c.tp[1] = c.tp[2] = (in / pl.MB) % pl.TP;
-  c.dp = (in / (pl.MB * pl.TP)) % pl.DP;
-  c.a[0] = in / (pl.MB * pl.TP * pl.DP);
+  uint32_t in = (uint32_t)rem - o * pl.inner;  // below 8 * 8 * 24 * 128: fast_div is exact
+  c.a[0] = (int)fast_div(in, pl.mg_mbtpdp);
+  in -= (uint32_t)(c.a[0] * pl.MB * pl.TP * pl.DP);
+  c.dp = (int)fast_div(in, pl.mg_mbtp);
+  in -= (uint32_t)(c.dp * pl.MB * pl.TP);
+  const int tp = (int)fast_div(in, pl.mg_mb);
+  c.tp[0] = c.tp[1] = c.tp[2] = tp;
+  c.mb = (int)in - tp * pl.MB;
   c.a[1] = c.a[2] = -1;
   if (c.s >= 2) {
-    c.a[1] = (c.a[0] + 1 + (int)(o % (pl.ZG - 1))) % pl.ZG;
+    c.a[1] = c.a[0] + 1 + (int)(o % (pl.ZG - 1));
+    if (c.a[1] >= pl.ZG) c.a[1] -= pl.ZG;
     o /= (pl.ZG - 1);
     if (pl.pst) { c.tp[1] = (int)(o % pl.TP); o /= pl.TP; }
   }
   if (c.s == 3) {
-    c.a[2] = (c.a[1] + 1 + (int)(o % (pl.ZG - 1))) % pl.ZG;
+    c.a[2] = c.a[1] + 1 + (int)(o % (pl.ZG - 1));
+    if (c.a[2] >= pl.ZG) c.a[2] -= pl.ZG;
     o /= (pl.ZG - 1);
     if (pl.pst) c.tp[2] = (int)o;
   }
@@ -1847,83 +1852,189 @@ struct EvalArgs {
   float bound;
 };
 
+// The small tables of the evaluator of index lists: laid out once per plan in memory
+// (k_direct_tables), copied to LDS by every workgroup in one go, the availability behind them.
+struct DirectTables {
+  uint64_t *cap, *res;        // [G]
+  float *ts;                  // [MB][Z][Z] transfer seconds
+  float *egs;                 // [Z][Z]
+  float *price;               // [GX]
+  float *xb;                  // [MB]
+  float *cd, *dph;            // [DP]
+  float *nbm1;                // [MB][DP]
+  int32_t *nb;                // [MB][DP]
+  int32_t *dp, *tp;           // [DP], [TP] the lists' values
+  int32_t *node;              // [G]
+  uint32_t *xt;               // [GX]
+  int32_t *avail;             // [ZGr]
+};
+
+__host__ __device__ inline uint32_t direct_copy_words(const DevPlan &pl) {  // 4-byte words laid out in memory
+  return (uint32_t)(4 * pl.G + pl.MB * pl.Z * pl.Z + pl.Z * pl.Z + 2 * pl.GX + pl.MB + 3 * pl.DP +
+                    2 * pl.MB * pl.DP + pl.TP + pl.G);
+}
+inline size_t direct_lds_bytes(const DevPlan &pl) {  // (13 KB at the limits of a problem)
+  return ((size_t)direct_copy_words(pl) + pl.ZGr) * sizeof(uint32_t);
+}
+
+__device__ __forceinline__ DirectTables direct_tables_at(const DevPlan &pl, uint32_t *at) {
+  DirectTables T;
+  T.cap = reinterpret_cast<uint64_t *>(at);
+  T.res = T.cap + pl.G;
+  T.ts = reinterpret_cast<float *>(at + 4 * pl.G);
+  T.egs = T.ts + pl.MB * pl.Z * pl.Z;
+  T.price = T.egs + pl.Z * pl.Z;
+  T.xb = T.price + pl.GX;
+  T.cd = T.xb + pl.MB;
+  T.dph = T.cd + pl.DP;
+  T.nbm1 = T.dph + pl.DP;
+  T.nb = reinterpret_cast<int32_t *>(T.nbm1 + pl.MB * pl.DP);
+  T.dp = T.nb + pl.MB * pl.DP;
+  T.tp = T.dp + pl.DP;
+  T.node = T.tp + pl.TP;
+  T.xt = reinterpret_cast<uint32_t *>(T.node + pl.G);
+  T.avail = reinterpret_cast<int32_t *>(T.xt + pl.GX);
+  return T;
+}
+
+// (after k_small_tables, one workgroup)
+__global__ void k_direct_tables(DevPlan pl) {
+  const DirectTables T = direct_tables_at(pl, pl.direct_tables);
+  const int t = threadIdx.x, nt = blockDim.x;
+  for (int i = t; i < pl.G; i += nt) { T.cap[i] = pl.cap[i]; T.res[i] = pl.res[i]; T.node[i] = pl.node[i]; }
+  for (int i = t; i < pl.MB * pl.Z * pl.Z; i += nt) T.ts[i] = pl.tsec_f[i];
+  for (int i = t; i < pl.Z * pl.Z; i += nt) T.egs[i] = pl.egs_f[i];
+  for (int i = t; i < pl.GX; i += nt) { T.price[i] = pl.price_f[i]; T.xt[i] = pl.xt[i]; }
+  for (int i = t; i < pl.MB; i += nt) T.xb[i] = pl.xb_f[i];
+  for (int i = t; i < pl.DP; i += nt) { T.cd[i] = pl.cd_f[i]; T.dph[i] = pl.dph_f[i]; T.dp[i] = pl.vals[i]; }
+  for (int i = t; i < pl.MB * pl.DP; i += nt) { T.nbm1[i] = pl.nbm1_f[i]; T.nb[i] = pl.nb[i]; }
+  for (int i = t; i < pl.TP; i += nt) T.tp[i] = pl.vals[pl.DP + i];
+}
+
 template <int S>
-__device__ __forceinline__ void eval_direct_s(const DevPlan &pl, const Cand &c, const ShapeRec &sh,
-                                              const LaneC &lc, float &T, float &C, uint64_t &peak,
-                                              uint32_t &mask) {
+__device__ __forceinline__ void eval_direct_s(const DevPlan &pl, const DirectTables &L, const Cand &c,
+                                              const ShapeRec &sh, const LaneC &lc, float &T, float &C,
+                                              uint64_t &peak, uint32_t &mask) {
   const int GX = pl.GX, Z = pl.Z, MB = pl.MB, DP = pl.DP;
-  const int64_t D = pl.vals[c.dp];
-  const float *ts = pl.tsec_f + c.mb * Z * Z;  // transfer seconds of this microbatch size
-  Acc acc;
-  int w[3] = {0, 0, 0};
+  const int64_t D = L.dp[c.dp];
+  const float *ts = L.ts + c.mb * Z * Z;  // transfer seconds of this microbatch size
+  // what comes from memory is requested for all segments before any of it is used
+  float4 ta[S];
+  float sync[S], upd[S];
+  uint64_t need[S];
+  int z[S], gx[S];
 #pragma unroll
   for (int j = 0; j < S; ++j) {
-    const int p = c.a[j], gx = p % GX, z = p / GX;
-    const int ga = pl.xt[gx] & 255, gb = pl.xt[gx] >> 8;
-    const int tpv = pl.vals[pl.DP + c.tp[j]];
+    z[j] = (int)fast_div((uint32_t)c.a[j], pl.mg_g);
+    gx[j] = c.a[j] - z[j] * GX;
     const size_t sl = agg_slot(pl, c.shape, c.tp[j], j);
-    const Rec r = make_rec(pl.ta[(sl * GX + gx) * MB + c.mb], pl.syncz[sl * Z + z], pl.upd[sl * GX + gx],
-                           pl.price_f[gx], ts[z * Z + z], sh.n[j], tpv, 0u);
-    const uint64_t need = pl.need[(sl * MB + c.mb) * DP + c.dp];
-    const uint64_t m = need + pl.res[ga], m2 = need + pl.res[gb];
-    if (m > pl.cap[ga] || m2 > pl.cap[gb]) mask |= 1u;
+    ta[j] = pl.ta[(sl * GX + gx[j]) * MB + c.mb];
+    sync[j] = pl.syncz[sl * Z + z[j]];
+    upd[j] = pl.upd[sl * GX + gx[j]];
+    need[j] = pl.need[(sl * MB + c.mb) * DP + c.dp];
+  }
+  Acc acc;
+  int w[S], ra[S], rb[S];  // GPUs of one replica on the pool, the real pools
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    const uint32_t x = L.xt[gx[j]];
+    const int ga = x & 255, gb = x >> 8;
+    const int tpv = L.tp[c.tp[j]];
+    const Rec r = make_rec(ta[j], sync[j], upd[j], L.price[gx[j]], ts[z[j] * Z + z[j]], sh.n[j], tpv, 0u);
+    const uint64_t m = need[j] + L.res[ga], m2 = need[j] + L.res[gb];
+    if (m > L.cap[ga] || m2 > L.cap[gb]) mask |= 1u;
     peak = m > peak ? m : peak;
     peak = m2 > peak ? m2 : peak;
-    w[j] = sh.n[j] * tpv;  // GPUs of one replica on this pool
-    if (!((pl.qw[(size_t)w[j] * pl.ZG + p] >> c.dp) & 1u)) mask |= 2u;
-    if (tpv > pl.node[ga] || tpv > pl.node[gb]) mask |= 8u;
+    w[j] = sh.n[j] * tpv;
+    ra[j] = z[j] * pl.G + ga;
+    rb[j] = z[j] * pl.G + gb;
+    // (a pair gives half of the replicas from each type, an even number of them)
+    const int64_t take = (int64_t)w[j] * D;
+    const bool fits = ga == gb ? take <= (int64_t)L.avail[ra[j]]
+                               : (D % 2 == 0 && take <= 2 * (int64_t)L.avail[ra[j]] &&
+                                  take <= 2 * (int64_t)L.avail[rb[j]]);
+    if (!fits) mask |= 2u;
+    if (tpv > L.node[ga] || tpv > L.node[gb]) mask |= 8u;
     if (j == 0) {
       acc = acc_begin(r);
     } else {
-      const int zp = c.a[j - 1] / GX;
-      acc = acc_cross(acc, r, ts[zp * Z + z], ts[z * Z + zp],
-                      pl.egs_f[zp * Z + z], sh.n[j - 1] == 1, j == 1);
+      const int zp = z[j - 1];
+      acc = acc_cross(acc, r, ts[zp * Z + z[j]], ts[z[j] * Z + zp], L.egs[zp * Z + z[j]],
+                      sh.n[j - 1] == 1, j == 1);
     }
   }
   // segments that draw on one real pool together
   if (pl.mixed) {
-    if (S >= 2 && !((joint_quota_bits(pl, S, c.a[0], c.a[1], c.a[2], w[0], w[1], w[2]) >> c.dp) & 1u))
-      mask |= 2u;
+    // half-GPUs per replica that each of the real pools named by the segments gives in all
+    if (S >= 2) {
+      auto taken = [&](int r) {
+        int h = 0;
+#pragma unroll
+        for (int k = 0; k < S; ++k) h += (ra[k] == r ? w[k] : 0) + (rb[k] == r ? w[k] : 0);
+        return h;
+      };
+#pragma unroll
+      for (int j = 0; j < S; ++j) {
+        if ((int64_t)taken(ra[j]) * D > 2 * (int64_t)L.avail[ra[j]]) mask |= 2u;
+        if ((int64_t)taken(rb[j]) * D > 2 * (int64_t)L.avail[rb[j]]) mask |= 2u;
+      }
+    }
   } else if (S == 3 && c.a[0] == c.a[2]) {
-    if ((int64_t)(w[0] + w[2]) * D > (int64_t)pl.avail[c.a[0]]) mask |= 2u;
+    if ((int64_t)(w[0] + w[2]) * D > (int64_t)L.avail[c.a[0]]) mask |= 2u;
   }
   acc_finish(acc, lc, T, C);
 }
 
-// One lane per candidate; reads the segment aggregates straight from global memory.
-__global__ __launch_bounds__(256) void k_eval_direct(DevPlan pl, EvalArgs a) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.count) return;
-  const uint64_t idx = a.indices ? a.indices[i] : a.first + i;
-  float T = kPosInf, C = kPosInf;
-  uint64_t peak = 0;
-  uint32_t mask = 0xFFFFFFFFu;
-  Cand c;
-  if (decode_index(pl, idx, c)) {
-    mask = 0;
-    const int nb = pl.nb[c.mb * pl.DP + c.dp];
-    if (nb == 0) {
-      mask = 4u;
-    } else {
-      const ShapeRec sh = pl.shapes[c.shape];
-      LaneC lc;
-      lc.nbm1 = pl.nbm1_f[c.mb * pl.DP + c.dp];
-      lc.cd = pl.cd_f[c.dp];
-      lc.dph = pl.dph_f[c.dp];
-      lc.xb = pl.xb_f[c.mb];
-      if (c.s == 1) eval_direct_s<1>(pl, c, sh, lc, T, C, peak, mask);
-      else if (c.s == 2) eval_direct_s<2>(pl, c, sh, lc, T, C, peak, mask);
-      else eval_direct_s<3>(pl, c, sh, lc, T, C, peak, mask);
-      if (a.has_bound) {
-        if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
-        else if (throughput_below(T, a.bound)) mask |= 32u;
+// One lane per candidate, grid-stride; the segment aggregates come straight from global memory.
+// Bound by gathers: every lane of a wave reads another cache line.  With the small tables in LDS
+// and quotas by arithmetic a candidate of three segments gathers 13 times (its shape, and four
+// words per segment) instead of about 50, and none of those waits for another but the shape's.
+// 1 000 003 random candidates: 51.4 -> 42.7 us (28 MB of indices and outputs; the same
+// bytes take 5 us as a copy).
+constexpr int kDirectThreads = 256;
+constexpr unsigned kDirectWorkgroups = 2048;  // eight per compute unit: all resident, one copy of the tables each
+__global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, EvalArgs a) {
+  extern __shared__ uint64_t direct_lds[];
+  uint32_t *const lds = reinterpret_cast<uint32_t *>(direct_lds);
+  const DirectTables L = direct_tables_at(pl, lds);
+  const int n_words = (int)direct_copy_words(pl);
+  for (int r = threadIdx.x; r < pl.ZGr; r += kDirectThreads) L.avail[r] = pl.avail[r];
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n_words; i += kDirectThreads) lds[i] = pl.direct_tables[i];
+  __syncthreads();
+  const uint64_t stride = (uint64_t)gridDim.x * kDirectThreads;
+  for (uint64_t i = (uint64_t)blockIdx.x * kDirectThreads + threadIdx.x; i < a.count; i += stride) {
+    const uint64_t idx = a.indices ? a.indices[i] : a.first + i;
+    float T = kPosInf, C = kPosInf;
+    uint64_t peak = 0;
+    uint32_t mask = 0xFFFFFFFFu;
+    Cand c;
+    if (decode_index(pl, idx, c)) {
+      mask = 0;
+      const int nb = L.nb[c.mb * pl.DP + c.dp];
+      if (nb == 0) {
+        mask = 4u;
+      } else {
+        const ShapeRec sh = pl.shapes[c.shape];
+        LaneC lc;
+        lc.nbm1 = L.nbm1[c.mb * pl.DP + c.dp];
+        lc.cd = L.cd[c.dp];
+        lc.dph = L.dph[c.dp];
+        lc.xb = L.xb[c.mb];
+        if (c.s == 1) eval_direct_s<1>(pl, L, c, sh, lc, T, C, peak, mask);
+        else if (c.s == 2) eval_direct_s<2>(pl, L, c, sh, lc, T, C, peak, mask);
+        else eval_direct_s<3>(pl, L, c, sh, lc, T, C, peak, mask);
+        if (a.has_bound) {
+          if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
+          else if (throughput_below(T, a.bound)) mask |= 32u;
+        }
       }
     }
+    if (a.time) a.time[i] = T;
+    if (a.cost) a.cost[i] = C;
+    if (a.mem) a.mem[i] = peak;
+    if (a.mask) a.mask[i] = mask;
   }
-  if (a.time) a.time[i] = T;
-  if (a.cost) a.cost[i] = C;
-  if (a.mem) a.mem[i] = peak;
-  if (a.mask) a.mask[i] = mask;
 }
 
 // Range form of sailor_eval_batch.  One workgroup per EvalUnit: the records of the unit's
