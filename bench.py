@@ -353,7 +353,8 @@ def main() -> int:
     best_ms = (time.perf_counter() - t0) / max(1, reps) * 1e3
 
     # the timed query once more with a budget that no plan exceeds: nothing falls to a cost
-    # bound, only invalid plans are discarded (outside the timed region)
+    # bound, plans are discarded one by one: invalid ones, and those whose leading segments already
+    # take longer than what was found (outside the timed region)
     unbound = None
     if True:
         for _ in range(3):
@@ -380,9 +381,10 @@ def main() -> int:
     plan.set_timing(0)
     del tt, cc, mm, kk
 
-    # the same kind of query where nothing can be discarded: resources never bind, nearly every
+    # the same kind of query where no constraint discards anything: resources never bind, nearly every
     # candidate is a valid plan, and the budget is one that no plan exceeds (so no piece of the
-    # space is ruled out by its cost bound either): every candidate's arithmetic is done
+    # space is ruled out by its cost bound either); what the scan may still pass over is plans
+    # whose leading segments already take longer than what their workgroup has found
     dense_prob = workloads.config4_dense()
     pd = Plan(dense_prob)
     pd.set_incremental(False)
@@ -543,7 +545,7 @@ def main() -> int:
     # pieces alive (the others fall to their cost bounds without being touched), so the pass is a
     # short, latency-bound launch; what the evaluation kernel sustains when the arithmetic has to
     # be done is in roofline_scan_no_binding_budget (validity pruning only) and roofline_dense
-    # (nothing to prune).
+    # (no plan falls to validity or to the budget).
     roof = alu_roofline(counters.get("pass_cfg4"), scan_ms, flops_per_cand * n)
     roof.update({"kernel": "k_units<COLLECT>, one pass over the pieces the budget leaves alive",
                  "pieces_evaluated": units_evaluated, "pieces_total": units_total,
