@@ -1007,12 +1007,10 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
             used = W;
             tau = L.key[W - 1];
             sorted = true;
-            if (!done) {
-              if (t == 0) *counter = (uint32_t)W;
-              __syncthreads();
-            }
+            if (!done && t == 0) *counter = (uint32_t)W;
           }
           if (done) break;
+          __syncthreads();  // every wave has read the counter (or sees it reset) before the next pass adds to it
         }
         if (last || kept == 0) break;  // uniform
         n = used;

@@ -940,6 +940,38 @@ def test_a_beam_wider_than_one_pass_of_the_workgroup(torch_cuda):
         plan.destroy()
 
 
+@pytest.mark.parametrize("objective", OBJECTIVES)
+@pytest.mark.parametrize("form", ["plain", "stage_tp", "split", "split_tp"])
+def test_levels_that_take_several_passes_of_the_buffer(torch_cuda, form, objective):
+    # 64 pools: a frontier of more than 32 states has more items than the 2 048 the buffer holds.  One
+    # run: an extension stays on its pools, so that a pass leaves fewer candidates than the beam and the
+    # next one follows without a selection; two runs, an incumbent just above the best: selections
+    # between some passes, none between others.
+    stream = torch_cuda.cuda.current_stream().cuda_stream
+    kw = {"allow_split": form.startswith("split"), "stage_tp": form.endswith("tp")}
+    prob = _tiny(9, n_layers=4, n_types=8, n_zones=8, partitions_per_pp=1)
+    plan, orc = _plan(prob), Oracle(prob)
+
+    def check(width, **more):
+        got, want = plan.search(width, objective, stream=stream, **kw, **more), orc.search_beam(width, objective, **kw, **more)
+        if form == "plain":
+            check_same(got, want, objective)
+        else:
+            {"stage_tp": check_same_tp, "split": check_same_split, "split_tp": check_same_both}[form](got, want, objective, orc)
+        return want
+
+    try:
+        best = check(128, max_runs=1)
+        key = _key(best, objective)
+        for width in (40, 128):
+            check(width, max_runs=1, incumbent=1.3 * key)
+        for width in (40,) if kw["allow_split"] else (40, 128, 500):
+            check(width, max_runs=2)
+            check(width, max_runs=2, incumbent=1.02 * key)
+    finally:
+        plan.destroy()
+
+
 @pytest.mark.parametrize("count", [1, 63, 65, 130])
 def test_listed_plans_at_the_edges_of_the_evaluators_passes(torch_cuda, count):
     # one plan; one fewer and one more than a workgroup's 64; pipelines of 1 to 256 stages beside each
