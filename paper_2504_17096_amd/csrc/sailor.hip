@@ -44,6 +44,7 @@ constexpr uint32_t kEvalUnitTarget = 16384;  // candidates per workgroup of the 
 constexpr unsigned kEvalRowsThreads = 512;
 constexpr uint32_t kSearchWorkgroups = 1024, kRootWorkgroups = 1024;  // of the search's two kernels
 constexpr size_t kSearchLds = 80 * 1024;       // LDS of a search workgroup: two fit a compute unit
+constexpr size_t kSearchMaxLds = 160 * 1024 - kSearchStaticLds;  // most dynamic LDS of one
 constexpr uint64_t kPlaceWorkgroups = 1024;  // workgroups a list of placements is spread over, if it is long enough
 constexpr size_t kEvalRowsMaxLds = 64 * 1024;  // above this the range form evaluates lane by lane
 constexpr size_t kScanMaxLds = 160 * 1024;     // a scan workgroup stages its records within the LDS of a compute unit
@@ -631,12 +632,20 @@ void launch_bounds(sailor_plan *pl, const ScanArgs &a) {
   else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a);
 }
 
+struct SearchLaunch {
+  unsigned root_wgs, root_waves;  // workgroups of the first level's kernel, waves of each
+  size_t root_words;              // LDS words of a wave
+  unsigned wgs;
+  size_t lds;
+};
+
 template <int MODE>
-void launch_search(const sailor_plan *pl, const SearchArgs &a, unsigned root_wgs, size_t root_words, unsigned wgs,
-                          size_t lds, hipStream_t st) {
-  k_search_root<MODE><<<root_wgs, kRootWaves * 64, root_words * 8 * kRootWaves, st>>>(pl->dev, a, (uint32_t)root_words);
-  if (a.states) k_search_beam<MODE, false><<<wgs, kSearchThreads, lds, st>>>(pl->dev, a);
-  else k_search_beam<MODE, true><<<wgs, kSearchThreads, lds, st>>>(pl->dev, a);
+void launch_search(const sailor_plan *pl, const SearchArgs &a, const SearchLaunch &l, hipStream_t st) {
+  k_search_root<MODE><<<l.root_wgs, l.root_waves * 64, l.root_words * 8 * l.root_waves, st>>>(pl->dev, a, (uint32_t)l.root_words);
+  // (only two pools and a degree per stage have tables that large)
+  if (a.by_zone) k_search_beam<SEARCH_SPLIT_TP, SEARCH_BY_ZONE><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
+  else if (a.states) k_search_beam<MODE, SEARCH_IN_MEMORY><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
+  else k_search_beam<MODE, SEARCH_IN_LDS><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
 }
 
 // Waits for the sequence number in host-mapped memory rather than for the dispatch to
@@ -1625,23 +1634,6 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   a.bound = bound;
   a.W = opt->beam_width;
   a.max_runs = opt->max_runs;
-  if (opt->use_incumbent == 1) {
-    a.has_inc = 1;
-    a.inc = opt->incumbent;
-  } else if (opt->use_incumbent == 2) {
-    // the best plan of the flat space (at most three contiguous runs) through the evaluator:
-    // every placement whose bound exceeds its key can be dropped
-    ResultHeader hdr;
-    rc = run_selection(pl, objective, constraint, 0, st, &hdr);
-    if (rc != SAILOR_OK) return rc;
-    if (hdr.n_found) {
-      const RefRec *rec = reinterpret_cast<const RefRec *>(static_cast<char *>(pl->h_result) + sizeof(ResultHeader));
-      a.has_inc = 1;
-      a.inc = (objective == SAILOR_MAX_THROUGHPUT ? rec[0].T : rec[0].C) * (1.0 + 1e-9);
-    }
-  }
-  rc = refresh_avail(pl, st);
-  if (rc != SAILOR_OK) return rc;
   const bool split = opt->allow_split != 0, stp = opt->stage_tp != 0;
   const size_t W = (size_t)a.W, ZG = (size_t)pl->dev.ZGr, TPn = stp ? (size_t)pl->dev.TP : 1;
   a.pps = pl->d_search_pps;
@@ -1657,7 +1649,6 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   a.block = (uint32_t)std::max<size_t>(1, std::min(W, 1024 / (TPn * ZG)));
   // Frontiers and history stay in LDS as long as two workgroups fit a compute unit; wide beams keep the
   // history, then the frontiers too, in device memory.
-  const unsigned wgs = std::min(a.n_sub, kSearchWorkgroups);
   SearchLds layout;
   auto lds_bytes = [&]() { return search_carve(pl->dev, split, stp, false, a, nullptr, layout) * 8; };
   size_t lds = lds_bytes();
@@ -1686,21 +1677,47 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
     a.states = pl->search_states;
     lds = lds_bytes();
   }
-  const size_t root_words = search_carve(pl->dev, split, stp, true, a, nullptr, layout);
-  if (lds > kScanMaxLds || root_words * 8 * kRootWaves > kScanMaxLds) return SAILOR_EINVAL;
+  if (lds > kSearchMaxLds && split && stp) {
+    a.by_zone = 1;
+    lds = lds_bytes();
+  }
+  SearchLaunch launch{};
+  launch.wgs = std::min(a.n_sub, kSearchWorkgroups);
+  launch.lds = lds;
+  launch.root_words = search_carve(pl->dev, split, stp, true, a, nullptr, layout);
+  launch.root_waves = (unsigned)std::min<size_t>(kRootWaves, kSearchMaxLds / (launch.root_words * 8));
+  launch.root_wgs = std::min<unsigned>(kRootWorkgroups, (a.n_sub + kRootWaves - 1) / kRootWaves);
+  // (cannot be: at 64 pools, 255 stages, 8 degrees and the widest beam the tables take 125 KiB, a wave's of the first level 40)
+  if (lds > kSearchMaxLds || launch.root_waves == 0) return SAILOR_EINVAL;
+  if (opt->use_incumbent == 1) {
+    a.has_inc = 1;
+    a.inc = opt->incumbent;
+  } else if (opt->use_incumbent == 2) {
+    // the best plan of the flat space (at most three contiguous runs) through the evaluator:
+    // every placement whose bound exceeds its key can be dropped
+    ResultHeader hdr;
+    rc = run_selection(pl, objective, constraint, 0, st, &hdr);
+    if (rc != SAILOR_OK) return rc;
+    if (hdr.n_found) {
+      const RefRec *rec = reinterpret_cast<const RefRec *>(static_cast<char *>(pl->h_result) + sizeof(ResultHeader));
+      a.has_inc = 1;
+      a.inc = (objective == SAILOR_MAX_THROUGHPUT ? rec[0].T : rec[0].C) * (1.0 + 1e-9);
+    }
+  }
+  rc = refresh_avail(pl, st);
+  if (rc != SAILOR_OK) return rc;
   if (pl->search_dirty)  // (the last kernel of a search leaves the counters at zero)
     HIP_TRY(hipMemsetAsync(pl->search_counters, 0, ((size_t)a.n_pp + 1) * sizeof(uint32_t), st));
   pl->search_dirty = true;  // until this search has succeeded
-  const unsigned root_wgs = std::min<unsigned>(kRootWorkgroups, (a.n_sub + kRootWaves - 1) / kRootWaves);
-  if (split && stp) launch_search<SEARCH_SPLIT_TP>(pl, a, root_wgs, root_words, wgs, lds, st);
-  else if (split) launch_search<SEARCH_SPLIT>(pl, a, root_wgs, root_words, wgs, lds, st);
-  else if (stp) launch_search<SEARCH_STAGE_TP>(pl, a, root_wgs, root_words, wgs, lds, st);
-  else launch_search<SEARCH_PLAIN>(pl, a, root_wgs, root_words, wgs, lds, st);
+  if (split && stp) launch_search<SEARCH_SPLIT_TP>(pl, a, launch, st);
+  else if (split) launch_search<SEARCH_SPLIT>(pl, a, launch, st);
+  else if (stp) launch_search<SEARCH_STAGE_TP>(pl, a, launch, st);
+  else launch_search<SEARCH_PLAIN>(pl, a, launch, st);
   // what the host reads is written to the mapped result area (the flat space's results, if any, have
   // been read): the winner, then its T, C, mem and mask
   SubResult *const d_fin = reinterpret_cast<SubResult *>(pl->d_out);
   double *const d_ev = reinterpret_cast<double *>(d_fin + 1);
-  k_search_pick<<<1, 1024, 0, st>>>(a, wgs, root_wgs, pl->search_final, d_fin);
+  k_search_pick<<<1, 1024, 0, st>>>(a, launch.wgs, launch.root_wgs, pl->search_final, d_fin);
   // the winner once more through the simulator, for its memory footprint and its mask
   PlaceArgs pa{};
   pa.count = 1;

@@ -50,7 +50,8 @@ constexpr int kSearchBins = 256;
 constexpr int kSelectKeep = kSearchBuf / kSearchThreads;  // of them per thread
 constexpr int kSearchMaxStages = 255;  // placements count runs in a byte
 constexpr int kSearchMaxPools = 64;
-constexpr int kRootWaves = 4;
+constexpr int kRootWaves = 4;            // of a k_search_root workgroup, if their tables fit
+constexpr size_t kSearchStaticLds = 1024;  // left to the search kernels' static LDS
 
 struct SearchPP {      // one pipeline depth
   int32_t P;
@@ -62,6 +63,12 @@ struct SearchPP {      // one pipeline depth
 };
 
 enum : int { SEARCH_PLAIN = 0, SEARCH_SPLIT = 1, SEARCH_STAGE_TP = 2, SEARCH_SPLIT_TP = 3 };
+
+// Forms of k_search_beam: frontiers in LDS; in device memory (wide beams); the same, and with two
+// pools and a TP degree per stage all-reduce seconds by (first zone, second zone) instead of (first
+// zone, second pool), for problems whose degrees x zones x pools of them do not fit LDS twice (16 zones
+// of 4 types at 8 degrees: 131 KB; by zone 33 KB).
+enum : int { SEARCH_IN_LDS = 0, SEARCH_IN_MEMORY = 1, SEARCH_BY_ZONE = 2 };
 
 struct SPart {         // one kind of pipeline of a placement of stages 0 .. j
   double sum;          // times of the closed stages 0 .. j-1
@@ -105,6 +112,7 @@ struct SearchArgs {
   unsigned long long *root_expanded;  // [k_search_root's workgroups]
   uint32_t buf;           // candidates buffered, at most kSearchBuf
   uint32_t block;         // split stages: states whose tables are in LDS at a time
+  uint32_t by_zone;       // split stages: k_search_beam keeps all-reduce seconds by pairs of zones
   double *states;         // [workgroups][2][W] states, or NULL: they are in LDS
   uint32_t *history;      // [workgroups][P_max][W], or NULL: it is in LDS
   SubResult *results;     // [workgroups]
@@ -135,8 +143,8 @@ struct SearchLds {
   int32_t *width;       // [TPn] what a stage (half a stage) takes from a pool
   // of a level, two of each: the next level's are filled while this one's are used
   double *raw;          // [2][TPn][row_w] the stage's records (DevPlan::st_row)
-  double *sync;         // [2][TPn][Z]; split: [TPn][Z][ZP] (first zone, second pool; ZP: ZG made even)
-                        // seconds of the stage's all-reduce
+  double *sync;         // [2][TPn][Z]; split: [TPn][Z][ZP] (first zone, second pool; ZP: ZG made even) or,
+                        // by zone, [TPn][Z][Z]: seconds of the stage's all-reduce
   double *upd;          // split: [2][TPn][ZP] update seconds by pool
   double *ring;         // [2][TPn] bytes it moves over every link
   uint32_t *fit;        // [2][TPn] bit g: the stage fits type g
@@ -161,6 +169,7 @@ __host__ __device__ inline uint32_t search_gather(uint32_t W, uint32_t buf) { re
 __host__ __device__ inline size_t search_carve(const DevPlan &pl, bool split, bool stp, bool root, const SearchArgs &a,
                                                double *base, SearchLds &L) {
   const size_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, ZP = ZG + (ZG & 1), TPn = stp ? pl.TP : 1, P = pl.P_max, two = root ? 1 : 2;
+  const size_t sync_row = root || a.by_zone ? Z : ZP;
   size_t at = 0;
   auto words = [&](size_t n) { double *p = base + at; at += n; return p; };
   auto ints = [&](size_t n) { return reinterpret_cast<uint32_t *>(words((n + 1) / 2)); };
@@ -180,8 +189,9 @@ __host__ __device__ inline size_t search_carve(const DevPlan &pl, bool split, bo
   L.width = reinterpret_cast<int32_t *>(ints(TPn));
   L.raw = words(two * TPn * pl.row_w);
   at += at & 1;  // (rows that are read in pairs)
-  L.sync = words(two * TPn * (split ? Z * ZP : Z));
-  L.upd = words(split ? two * TPn * ZP : 0);
+  L.sync = words(two * TPn * (split ? Z * sync_row : Z));
+  at += at & 1;
+  L.upd = words(split && !root ? two * TPn * ZP : 0);
   L.ring = words(two * TPn);
   L.fit = ints(two * TPn);
   if (root) return at;
@@ -339,23 +349,34 @@ __device__ __forceinline__ void search_suffix(const DevPlan &pl, const SearchSub
   }
 }
 
-// What follows from a level's records (which must be visible): all-reduce seconds, fits.  layers:
-// of the level's stage; tp1: the sub-problem's TP degree.
-template <int MODE>
+// What follows from a level's records (which must be visible): all-reduce seconds (ZONES: by pairs of
+// zones), update seconds (not for the root), fits.  layers: of the level's stage; tp1: the
+// sub-problem's TP degree.
+template <int MODE, bool ROOT, bool ZONES>
 __device__ __forceinline__ void search_level(const DevPlan &pl, const SearchSub &s, const SearchLds &L, int j, int layers,
                                              int tp1, int b, int tid, int nt) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
-  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, TPn = STP ? pl.TP : 1, NS = SPLIT ? Z * (ZG + (ZG & 1)) : Z;
+  const int G = pl.G, Z = pl.Z, ZG = pl.ZGr, TPn = STP ? pl.TP : 1, ZP = ZG + (ZG & 1);
+  const int NS = SPLIT ? Z * (ZONES ? Z : ZP) : Z;
   const double *raw = L.raw + (size_t)b * TPn * pl.row_w;
   for (int i = tid; i < TPn * NS; i += nt) {
-    const int k = i / NS, z = i - k * NS;  // split: first zone * ZP + second pool
+    const int k = i / NS, z = i - k * NS;  // split: first zone * ZP + second pool, or first zone * Z + second zone
     const double ring = s.D > 1 ? s.ringf * raw[k * pl.row_w + 2 * G + 1] : 0.0;
-    const int ZP = ZG + (ZG & 1), pb = SPLIT ? min(z % ZP, ZG - 1) : 0;
-    const uint32_t zgb = L.zg[pb];
-    L.sync[b * TPn * NS + i] = s.D > 1 ? ring / L.link[SPLIT ? z / ZP * Z + (int)(zgb & 255u) : z] : 0.0;
+    if (!SPLIT || ZONES) {
+      L.sync[b * TPn * NS + i] = s.D > 1 ? ring / L.link[z] : 0.0;
+    } else {
+      const uint32_t zgb = L.zg[min(z % ZP, ZG - 1)];
+      L.sync[b * TPn * NS + i] = s.D > 1 ? ring / L.link[z / ZP * Z + (int)(zgb & 255u)] : 0.0;
+      if (!ROOT && z < ZP) L.upd[(b * TPn + k) * ZP + z] = raw[k * pl.row_w + G + (zgb >> 8)];
+    }
     if (z == 0) L.ring[b * TPn + k] = ring;
-    if (SPLIT && z < ZP) L.upd[(b * TPn + k) * ZP + z] = raw[k * pl.row_w + G + (zgb >> 8)];
+  }
+  if (SPLIT && ZONES && !ROOT) {
+    for (int i = tid; i < TPn * ZP; i += nt) {
+      const int k = i / ZP, p = i - k * ZP;
+      L.upd[b * TPn * ZP + i] = raw[k * pl.row_w + G + (L.zg[min(p, ZG - 1)] >> 8)];
+    }
   }
   for (int k = tid; k < TPn; k += nt) {
     const int tpk = STP ? L.width[k] : tp1;
@@ -400,8 +421,8 @@ __device__ __forceinline__ double search_pipe(const SPart &o, double Ssum, doubl
 
 // Stage j on pool a (split stages: half of its replicas on pool b, else b = a) at TP index k (a
 // TP degree per stage; else 0) behind the placement par (first: j = 0, there is none): may it be
-// placed, and what the placement then carries.
-template <int MODE>
+// placed, and what the placement then carries.  ZONES: all-reduce seconds are kept by pairs of zones.
+template <int MODE, bool ZONES>
 __device__ __forceinline__ bool search_step(const DevPlan &pl, const SearchLds &L, const SearchSub &s,
                                             bool first, const SState<MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP> *par, int tb,
                                             int a, int b, int k, int max_runs, SAcc &o, int &runs) {
@@ -431,7 +452,10 @@ __device__ __forceinline__ bool search_step(const DevPlan &pl, const SearchLds &
   if (SPLIT) o.part[1] = search_close(first, &par->part[SPLIT ? 1 : 0], pzb, zb, Z, raw[gb], L.xfer);
   // the stage by itself: all-reduce over the slowest link of a ring through both pools, the
   // slower update, the mean rent, the ring's traffic between the zones
-  const double sync = SPLIT ? L.sync[((tb * TPn + k) * Z + za) * (pl.ZGr + (pl.ZGr & 1)) + b] : L.sync[(tb * TPn + k) * Z + za];
+  double sync;
+  if (!SPLIT) sync = L.sync[(tb * TPn + k) * Z + za];
+  else if (ZONES) sync = L.sync[((tb * TPn + k) * Z + za) * Z + zb];
+  else sync = L.sync[((tb * TPn + k) * Z + za) * (pl.ZGr + (pl.ZGr & 1)) + b];
   const double upd = SPLIT ? fmax(raw[G + ga], raw[G + gb]) : raw[G + ga];
   const double dol = L.dtp[k] * (SPLIT ? 0.5 * (L.price[ga] + L.price[gb]) : L.price[ga]);
   const double ring = SPLIT && zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
@@ -474,20 +498,21 @@ __device__ __forceinline__ bool search_keep(const SearchArgs &a, const SBound &b
 
 // ---- the first level of every sub-problem ----
 
-// One wave per sub-problem.  Most sub-problems end here: their batch does not divide, a stage fits
-// nowhere, or no placement of the first stage survives its bound.
+// One wave per sub-problem, kRootWaves per workgroup or as many as have room for their tables.  Most
+// sub-problems end here: their batch does not divide, a stage fits nowhere, or no placement of the
+// first stage survives its bound.
 template <int MODE>
 __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, SearchArgs a, uint32_t wave_words) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
   extern __shared__ double search_lds[];
   __shared__ unsigned long long s_exp[kRootWaves];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n_waves = (int)(blockDim.x >> 6);
   const int ZG = pl.ZGr, TPn = STP ? pl.TP : 1, NCH = SPLIT ? ZG * ZG * TPn : ZG * TPn;
   SearchLds L;
   search_carve(pl, SPLIT, STP, true, a, search_lds + wv * wave_words, L);
   unsigned long long expanded = 0;
-  for (uint32_t sid = blockIdx.x * kRootWaves + wv; sid < a.n_sub; sid += gridDim.x * kRootWaves) {
+  for (uint32_t sid = blockIdx.x * n_waves + wv; sid < a.n_sub; sid += gridDim.x * n_waves) {
     const SearchSub s = search_sub<STP>(pl, a, sid);
     if (s.nb == 0) continue;  // (uniform over the wave, like what follows)
     wave_lds_fence();         // the tables are reused
@@ -496,7 +521,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
     if (__builtin_amdgcn_ballot_w64(!fine) != 0) continue;
     wave_lds_fence();
     search_suffix(pl, s, L, lane);
-    search_level<MODE>(pl, s, L, 0, pl.st_n[s.rs], pl.vals[pl.DP + s.it], 0, lane, 64);
+    search_level<MODE, true, true>(pl, s, L, 0, pl.st_n[s.rs], pl.vals[pl.DP + s.it], 0, lane, 64);
     wave_lds_fence();
     bool alive = false;
     uint32_t mine = 0;
@@ -505,7 +530,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
       const int pa = SPLIT ? pools / ZG : pools, pb = SPLIT ? pools - pa * ZG : pa;
       SAcc o;
       int runs;
-      if (!search_step<MODE>(pl, L, s, true, nullptr, 0, pa, pb, k, a.max_runs, o, runs)) continue;
+      if (!search_step<MODE, true>(pl, L, s, true, nullptr, 0, pa, pb, k, a.max_runs, o, runs)) continue;
       ++mine;
       unsigned long long kbits;
       alive = search_keep(a, search_bound<SPLIT>(o, L.S, pl.P_max, 0, s.nbm1), kbits) || alive;
@@ -522,7 +547,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
   if (lane == 0) s_exp[wv] = expanded;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kRootWaves; ++w) expanded += s_exp[w];
+    for (int w = 1; w < n_waves; ++w) expanded += s_exp[w];
     a.root_expanded[blockIdx.x] = expanded;
   }
 }
@@ -715,11 +740,12 @@ __device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &
 // smallest choices lie in the W items with the smallest bests.
 // (Two waves per SIMD for split stages, four else: with four, the wider code spills to memory, 1.19 ms
 // against 1.05; with two, the narrower loses a workgroup per compute unit, 0.72 ms against 0.62.)
-// LDSF: the frontiers are in LDS (else in device memory, for wide beams).
-template <int MODE, bool LDSF>
+// FORM: where the frontiers are, and how all-reduce seconds are kept.
+template <int MODE, int FORM>
 __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_beam(DevPlan pl, SearchArgs a) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;   // two pools per stage
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;  // a TP degree per stage
+  constexpr bool LDSF = FORM == SEARCH_IN_LDS, ZONES = FORM == SEARCH_BY_ZONE;
   using State = SState<SPLIT>;
   extern __shared__ double search_lds[];
   __shared__ SelectShared sh;
@@ -728,6 +754,8 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
   __shared__ unsigned long long s_expanded;
   __shared__ unsigned long long s_bk[kSearchThreads / 64];
   __shared__ uint32_t s_bi[kSearchThreads / 64];
+  static_assert(sizeof sh + sizeof s_n + sizeof s_kept + sizeof s_next + sizeof s_expanded + sizeof s_bk + sizeof s_bi + 64 <=
+                kSearchStaticLds, "what dynamic LDS leaves room for");
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int ZG = pl.ZGr, Z = pl.Z, G = pl.G, TPn = STP ? pl.TP : 1, W = a.W, P_max = pl.P_max;
   const int ITEMS = SPLIT ? ZG * TPn : ZG, INNER = SPLIT ? ZG : TPn, ZP = ZG + (ZG & 1);
@@ -774,7 +802,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
     __syncthreads();
     if (wv == kSearchThreads / 64 - 1) search_suffix(pl, s, L, lane);
     const int tp1 = pl.vals[pl.DP + s.it];
-    search_level<MODE>(pl, s, L, 0, pl.st_n[s.rs], tp1, 0, t, kSearchThreads);
+    search_level<MODE, false, ZONES>(pl, s, L, 0, pl.st_n[s.rs], tp1, 0, t, kSearchThreads);
     int n_cur = 1;  // frontier length; level 0 extends one empty placement
     bool truncated = false;
     for (int j = 0; j < P; ++j) {  // place stage j (uniform loop)
@@ -852,7 +880,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
               SAcc o;
               int runs;
               unsigned long long kb;
-              if (search_step<MODE>(pl, L, s, first, state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs) &&
+              if (search_step<MODE, ZONES>(pl, L, s, first, state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs) &&
                   search_keep(a, search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1), kb)) {
                 bk = kb;
                 bi = number(r, pa, pb, pk);
@@ -866,7 +894,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
                 const int za = zga & 255u, ga = zga >> 8;
                 const unsigned long long half = L.half[y], whole = L.whole[y];
                 const double ta = L.pa[y * ZP + pa], mx0 = L.mx[2 * (r - block0)], mx1 = L.mx[2 * (r - block0) + 1];
-                const double *row_b = L.pb + y * ZP, *sync = L.sync + ((tb * TPn + k) * Z + za) * ZP, *upd = L.upd + (tb * TPn + k) * ZP;
+                const double *row_b = L.pb + y * ZP, *sync = L.sync + ((tb * TPn + k) * Z + za) * (ZONES ? Z : ZP), *upd = L.upd + (tb * TPn + k) * ZP;
                 const double ua = fmax(mx1, upd[pa]);
                 // the second pools this state and first pool admit
                 unsigned long long cand = ((half >> pa) & 1ull) ? half & ~(1ull << pa) : 0ull;
@@ -883,8 +911,14 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
                   uint32_t c_lo = (uint32_t)cand, c_hi = (uint32_t)(cand >> 32);
 #pragma unroll 2
                   for (int pb = 0; pb < ZP; pb += 2) {
-                    const double2 rb = *reinterpret_cast<const double2 *>(row_b + pb), sy = *reinterpret_cast<const double2 *>(sync + pb),
-                                  up = *reinterpret_cast<const double2 *>(upd + pb);
+                    const double2 rb = *reinterpret_cast<const double2 *>(row_b + pb), up = *reinterpret_cast<const double2 *>(upd + pb);
+                    double2 sy;
+                    if (ZONES) {
+                      sy.x = sync[fast_div((uint32_t)pb, pl.mg_g)];
+                      sy.y = sync[fast_div((uint32_t)min(pb + 1, ZG - 1), pl.mg_g)];
+                    } else {
+                      sy = *reinterpret_cast<const double2 *>(sync + pb);
+                    }
                     const double T0 = (fmax(ta, rb.x) + fmax(mx0, sy.x)) + fmax(ua, up.x);
                     const double T1 = (fmax(ta, rb.y) + fmax(mx0, sy.y)) + fmax(ua, up.y);
                     const uint32_t word = pb < 32 ? c_lo : c_hi;
@@ -904,7 +938,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
                     const uint32_t zgb = L.zg[pb];
                     const int zb = zgb & 255u, gb = zgb >> 8;
                     SBound b;
-                    b.T = (fmax(ta, row_b[pb]) + fmax(mx0, sync[pb])) + fmax(ua, upd[pb]);
+                    b.T = (fmax(ta, row_b[pb]) + fmax(mx0, sync[ZONES ? zb : pb])) + fmax(ua, upd[pb]);
                     double rent = L.dtp[k] * (0.5 * (L.price[ga] + L.price[gb])), comm = 0.0;
                     const double ring = zb != za ? L.ring[tb * TPn + k] * L.ring_price[za * Z + zb] : 0.0;
                     if (!first) {
@@ -1041,7 +1075,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
             choice(best_i, r, pa, pb, pk);
             SAcc o;
             int runs;
-            search_step<MODE>(pl, L, s, first, state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs);
+            search_step<MODE, ZONES>(pl, L, s, first, state_at(cur, r), tb, pa, pb, pk, a.max_runs, o, runs);
             const SBound b = search_bound<SPLIT>(o, L.S, P_max, j, s.nbm1);
             res->T = b.T;
             res->C = b.C;
@@ -1089,7 +1123,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
         }
         SAcc o;
         int runs;
-        search_step<MODE>(pl, L, s, first, par, tb, pa, pb, pk, a.max_runs, o, runs);
+        search_step<MODE, ZONES>(pl, L, s, first, par, tb, pa, pb, pk, a.max_runs, o, runs);
         if (q == 0) {
           out->msync = o.msync; out->mupd = o.mupd; out->dol = o.dol; out->comm = o.comm;
         } else if (q == 1) {
@@ -1103,7 +1137,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
               (unsigned long long)(runs & 255) << 16 | (unsigned long long)pk << 24 | z << 32 | zb << 40;
         }
       }
-      search_level<MODE>(pl, s, L, j + 1, layers, tp1, tb ^ 1, t, kSearchThreads);
+      search_level<MODE, false, ZONES>(pl, s, L, j + 1, layers, tp1, tb ^ 1, t, kSearchThreads);
       n_cur = n;
     }
     if (truncated) wg_trunc = 1;

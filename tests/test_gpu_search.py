@@ -972,6 +972,52 @@ def test_levels_that_take_several_passes_of_the_buffer(torch_cuda, form, objecti
         plan.destroy()
 
 
+def many_zones(n_zones, n_types, n_tp, depths, n_layers):
+    rng = np.random.default_rng(n_zones * 100 + n_tp)
+    G, Z, L = n_types, n_zones, n_layers
+    bw = rng.uniform(0.5e9, 2e9, (Z, Z))
+    np.fill_diagonal(bw, rng.uniform(5e9, 1e10, Z))
+    return make_problem(n_layers=L, n_types=G, n_zones=Z, mb_list=(1,), tp_list=tuple(range(1, n_tp + 1)), dp_list=(2,),
+                        pp_list=depths, global_batch=8, t_fwd=rng.uniform(0.5e-3, 3e-3, (G, 1, n_tp, 1)),
+                        t_bwd=rng.uniform(1e-3, 5e-3, (G, 1, n_tp, 1)), t_upd=rng.uniform(1e-4, 3e-4, (G, n_tp, 1)),
+                        layer_params=180_000_000 // L, act=rng.integers(1_000_000, 4_000_000, (1, n_tp)).astype(np.uint64),
+                        p2p=3_000_000, cap=rng.integers(2, 8, G).astype(np.uint64) * np.uint64(1 << 30),
+                        node=rng.integers(2, 9, G), price=rng.uniform(0.5, 4.0, G), avail=rng.integers(1, 8, (Z, G)),
+                        bw=bw, egress=rng.uniform(1e-11, 5e-11, (Z, Z)))
+
+
+@pytest.mark.parametrize("n_zones, n_types, n_tp, width, depths, n_layers", [
+    (8, 8, 8, 4, [1, 3], 6), (12, 4, 8, 3, [1, 3], 6), (16, 4, 4, 4, [1, 3], 6),
+    (16, 4, 8, 1, [1, 3], 6), (16, 4, 8, 4, [1, 3], 6),
+    (16, 4, 8, 4, [2, 255], 255),  # the deepest pipeline's tables
+    (15, 3, 8, 1024, [2], 6),      # an odd number of pools, the widest beam
+])
+def test_two_pools_and_a_tp_per_stage_on_many_zones(torch_cuda, n_zones, n_types, n_tp, width, depths, n_layers):
+    # all-reduce seconds by degree, zone and pool: the tables of four first-level waves, or of a
+    # level and the next, exceed the LDS of a compute unit
+    stream = torch_cuda.cuda.current_stream().cuda_stream
+    kw = dict(allow_split=True, stage_tp=True)
+    prob = many_zones(n_zones, n_types, n_tp, depths, n_layers)
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        if depths[-1] == 255:  # (255 stages cost more than two by far: they end at their first stage)
+            two = Oracle(many_zones(n_zones, n_types, n_tp, depths[:1], n_layers))
+            inc = 1.5 * two.search_beam(1, MIN_COST, **kw).cost
+            check_same_both(plan.search(width, MIN_COST, incumbent=inc, stream=stream, **kw),
+                            orc.search_beam(width, MIN_COST, incumbent=inc, **kw), MIN_COST, orc)
+            return
+        for objective in OBJECTIVES if width < 1000 else [MAX_THROUGHPUT]:
+            want = orc.search_beam(width, objective, **kw)
+            assert want is not None
+            check_same_both(plan.search(width, objective, stream=stream, **kw), want, objective, orc)
+        if width < 1000:
+            inc = 1.2 * want.cost
+            check_same_both(plan.search(width, MIN_COST, incumbent=inc, max_runs=2, stream=stream, **kw),
+                            orc.search_beam(width, MIN_COST, incumbent=inc, max_runs=2, **kw), MIN_COST, orc)
+    finally:
+        plan.destroy()
+
+
 @pytest.mark.parametrize("count", [1, 63, 65, 130])
 def test_listed_plans_at_the_edges_of_the_evaluators_passes(torch_cuda, count):
     # one plan; one fewer and one more than a workgroup's 64; pipelines of 1 to 256 stages beside each
