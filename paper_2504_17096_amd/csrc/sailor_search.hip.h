@@ -505,7 +505,7 @@ template <int MODE>
 __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, SearchArgs a, uint32_t wave_words) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;
-  extern __shared__ double search_lds[];
+  extern __shared__ __align__(16) double search_lds[];
   __shared__ unsigned long long s_exp[kRootWaves];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n_waves = (int)(blockDim.x >> 6);
   const int ZG = pl.ZGr, TPn = STP ? pl.TP : 1, NCH = SPLIT ? ZG * ZG * TPn : ZG * TPn;
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;  // a TP degree per stage
   constexpr bool LDSF = FORM == SEARCH_IN_LDS, ZONES = FORM == SEARCH_BY_ZONE;
   using State = SState<SPLIT>;
-  extern __shared__ double search_lds[];
+  extern __shared__ __align__(16) double search_lds[];  // (tables by pool are read in pairs, from even places)
   __shared__ SelectShared sh;
   // candidates buffered (items; choices behind them) and kept in all; two sets, used by levels in turn
   __shared__ uint32_t s_n[2][2], s_kept[2], s_next;
