@@ -1503,26 +1503,26 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
       return SAILOR_ENOMEM;
   }
   if (search && !pl->search_results) {
-    SubResult *res = nullptr, *fin = nullptr;
     DeviceArena &ar = pl->arena;
+    SubResult *res = nullptr, *fin = nullptr;
+    uint32_t *list = nullptr, *counters = nullptr;
+    unsigned long long *root_expanded = nullptr;
+    sailor_status rc = SAILOR_OK;
     if (ar.alloc(&res, (size_t)std::min(pl->n_sub, kSearchWorkgroups)) != hipSuccess || ar.alloc(&fin, 1) != hipSuccess ||
-        ar.alloc(&pl->search_list, (size_t)pl->n_sub) != hipSuccess ||
-        ar.alloc(&pl->search_counters, pl->search_pps.size() + 1) != hipSuccess ||
-        ar.alloc(&pl->search_root_expanded, (size_t)kRootWorkgroups) != hipSuccess) {
-      for (void *p : {(void *)res, (void *)fin, (void *)pl->search_list, (void *)pl->search_counters,
-                      (void *)pl->search_root_expanded})
-        if (p) ar.free_one(p);
-      pl->search_list = pl->search_counters = nullptr;
-      pl->search_root_expanded = nullptr;
-      return SAILOR_ENOMEM;
-    }
-    if (hipMemset(fin, 0, sizeof(SubResult)) != hipSuccess) {  // (read by the winner's re-evaluation
-      ar.free_one(res);                                        // also when nothing was found)
-      ar.free_one(fin);
-      return SAILOR_EDEVICE;
+        ar.alloc(&list, (size_t)pl->n_sub) != hipSuccess || ar.alloc(&counters, pl->search_pps.size() + 1) != hipSuccess ||
+        ar.alloc(&root_expanded, (size_t)kRootWorkgroups) != hipSuccess)
+      rc = SAILOR_ENOMEM;
+    else if (hipMemset(fin, 0, sizeof(SubResult)) != hipSuccess)  // (read by the winner's re-evaluation
+      rc = SAILOR_EDEVICE;                                        // also when nothing was found)
+    if (rc != SAILOR_OK) {
+      for (void *p : {(void *)res, (void *)fin, (void *)list, (void *)counters, (void *)root_expanded}) ar.free_one(p);
+      return rc;
     }
     pl->search_results = res;
     pl->search_final = fin;
+    pl->search_list = list;
+    pl->search_counters = counters;
+    pl->search_root_expanded = root_expanded;
   }
   return SAILOR_OK;
 }
