@@ -644,6 +644,7 @@ void launch_search(const sailor_plan *pl, const SearchArgs &a, const SearchLaunc
   k_search_root<MODE><<<l.root_wgs, l.root_waves * 64, l.root_words * 8 * l.root_waves, st>>>(pl->dev, a, (uint32_t)l.root_words);
   // (only two pools and a degree per stage have tables that large)
   if (a.by_zone) k_search_beam<SEARCH_SPLIT_TP, SEARCH_BY_ZONE><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
+  else if (a.W > kSearchNarrow) k_search_beam<MODE, SEARCH_WIDE><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
   else if (a.states) k_search_beam<MODE, SEARCH_IN_MEMORY><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
   else k_search_beam<MODE, SEARCH_IN_LDS><<<l.wgs, kSearchThreads, l.lds, st>>>(pl->dev, a);
 }
@@ -1665,7 +1666,7 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
     a.history = pl->search_history;
     lds = lds_bytes();
   }
-  if (lds > kSearchLds) {
+  if (lds > kSearchLds || a.W > kSearchNarrow) {
     const size_t words = (size_t)kSearchWorkgroups * 2 * W * search_state_words(true, (int)ZG);
     if (words > pl->search_states_cap) {
       pl->arena.free_one(pl->search_states);

@@ -29,7 +29,7 @@
 // while all of a search's candidates together are little work for the chip (6 to 30 million of
 // them).  So a level is kept short: frontier, tables and history stay in LDS, the next level's
 // inputs are requested a level ahead, appending candidates takes no barrier, the W smallest come
-// from a histogram and a count of predecessors instead of a sort of everything, and a wide choice
+// from a histogram and (up to 512 of them) a count of predecessors instead of a sort of everything, and a wide choice
 // (second pool, TP degree) is first reduced to the best of each (state, pool).  On the 48-layer,
 // 20-pool problem a search with beam 64 takes 0.63 ms where states in device memory, paths copied
 // level by level and a bitonic sort of every level took 2.9 ms; with two pools and a TP degree per
@@ -46,7 +46,7 @@ namespace sailor {
 constexpr int kSearchThreads = 512;
 constexpr int kSearchMaxBeam = 1024;   // longest frontier a sub-problem keeps (half of kSearchBuf at most)
 constexpr int kSearchBuf = 2048;       // most candidates buffered between two selections
-constexpr int kSearchBins = 256;
+constexpr int kSearchBinBits = 8, kSearchBins = 1 << kSearchBinBits;
 constexpr int kSelectKeep = kSearchBuf / kSearchThreads;  // of them per thread
 constexpr int kSearchMaxStages = 255;  // placements count runs in a byte
 constexpr int kSearchMaxPools = 64;
@@ -64,11 +64,12 @@ struct SearchPP {      // one pipeline depth
 
 enum : int { SEARCH_PLAIN = 0, SEARCH_SPLIT = 1, SEARCH_STAGE_TP = 2, SEARCH_SPLIT_TP = 3 };
 
-// Forms of k_search_beam: frontiers in LDS; in device memory (wide beams); the same, and with two
-// pools and a TP degree per stage all-reduce seconds by (first zone, second zone) instead of (first
-// zone, second pool), for problems whose degrees x zones x pools of them do not fit LDS twice (16 zones
-// of 4 types at 8 degrees: 131 KB; by zone 33 KB).
-enum : int { SEARCH_IN_LDS = 0, SEARCH_IN_MEMORY = 1, SEARCH_BY_ZONE = 2 };
+// Forms of k_search_beam: frontiers in LDS; in device memory; the same for beams above kSearchNarrow,
+// whose selections leave more pairs than can be ranked by counting; the same, and with two pools and a
+// TP degree per stage all-reduce seconds by (first zone, second zone) instead of (first zone, second
+// pool), for problems whose degrees x zones x pools of them do not fit LDS twice (16 zones of 4 types
+// at 8 degrees: 131 KB; by zone 33 KB).
+enum : int { SEARCH_IN_LDS = 0, SEARCH_IN_MEMORY = 1, SEARCH_WIDE = 2, SEARCH_BY_ZONE = 3 };
 
 struct SPart {         // one kind of pipeline of a placement of stages 0 .. j
   double sum;          // times of the closed stages 0 .. j-1
@@ -108,7 +109,7 @@ struct SearchArgs {
   int n_pp;
   uint32_t n_sub;
   uint32_t *list;         // [n_sub] surviving sub-problems, those of a depth together
-  uint32_t *counters;     // [n_pp] how many per depth, [1] how many were taken
+  uint32_t *counters;     // [n_pp] how many per depth; at [n_pp]: how many were taken
   unsigned long long *root_expanded;  // [k_search_root's workgroups]
   uint32_t buf;           // candidates buffered, at most kSearchBuf
   uint32_t block;         // split stages: states whose tables are in LDS at a time
@@ -163,7 +164,9 @@ struct SearchLds {
   uint32_t *history;    // [P_max][W] the candidates the frontiers are made of
 };
 
-__host__ __device__ inline uint32_t search_gather(uint32_t W, uint32_t buf) { return W + 128u < buf ? W + 128u : buf; }
+// most pairs a selection leaves to be ordered
+constexpr uint32_t kSearchSlack = 128;
+__host__ __device__ inline uint32_t search_gather(uint32_t W, uint32_t buf) { return W + kSearchSlack < buf ? W + kSearchSlack : buf; }
 
 // Lays the tables out from base on (NULL: only counts); returns the 8-byte words they take.
 __host__ __device__ inline size_t search_carve(const DevPlan &pl, bool split, bool stp, bool root, const SearchArgs &a,
@@ -582,80 +585,107 @@ struct SelectShared {
   uint32_t n;
 };
 
-// The m pairs of (okey, oid), ranked by counting each one's predecessors -- by_id: in the order
-// of their ids -- back to the first places of (key, id), as far as they rank below W.
+// The m pairs of (okey, oid), ranked by counting each one's predecessors (rank is zero) -- by_id: in
+// the order of their ids -- back to the first places of (key, id), as far as they rank below W.
+//
+// n^2 comparisons: up to 512 pairs no more than search_sort takes (beam 256 on 64 pools: 4.5 ms, sorted
+// 5.1), beyond that more (512 on 64 pools: 24.7 ms, sorted 12.6; 1 024 on 20 pools: 94.5 and 22.5).
+constexpr int kRankByCounting = 512;                                // most pairs
+constexpr int kSearchNarrow = kRankByCounting - (int)kSearchSlack;  // widest beam that needs no sort
 __device__ __forceinline__ void search_place(const SearchLds &L, int m, int W, bool by_id) {
   const int t = threadIdx.x;
   int np = 64;
   while (np < m) np <<= 1;
-  if (np <= kSearchThreads) {  // several threads share a pair
-    const int q = t & (np - 1), row = t / np, rows = kSearchThreads / np;
-    if (q < m) {
-      const unsigned long long mk = by_id ? 0 : L.okey[q];
-      const uint32_t mi = L.oid[q];
-      uint32_t before = 0;
+  const int q = t & (np - 1), row = t / np, rows = kSearchThreads / np;  // several threads share a pair
+  if (q < m) {
+    const unsigned long long mk = by_id ? 0 : L.okey[q];
+    const uint32_t mi = L.oid[q];
+    uint32_t before = 0;
 #pragma unroll 8
-      for (int x = row; x < m; x += rows) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
-      if (before) atomicAdd(&L.rank[q], before);
-    }
-  } else {
-    for (int q = t; q < m; q += kSearchThreads) {
-      const unsigned long long mk = by_id ? 0 : L.okey[q];
-      const uint32_t mi = L.oid[q];
-      uint32_t before = 0;
-#pragma unroll 8
-      for (int x = 0; x < m; ++x) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
-      L.rank[q] = before;
-    }
+    for (int x = row; x < m; x += rows) before += key_id_less(by_id ? 0 : L.okey[x], L.oid[x], mk, mi) ? 1u : 0u;
+    if (before) atomicAdd(&L.rank[q], before);
   }
   __syncthreads();
-  for (int q = t; q < m; q += kSearchThreads) {
-    const uint32_t r = L.rank[q];
-    if (r < (uint32_t)W) { L.key[r] = L.okey[q]; L.id[r] = L.oid[q]; }
+  if (t < m) {
+    const uint32_t r = L.rank[t];
+    if (r < (uint32_t)W) { L.key[r] = L.okey[t]; L.id[r] = L.oid[t]; }
+  }
+  __syncthreads();
+}
+static_assert(kRankByCounting <= kSearchThreads, "a thread per pair");
+
+// Ascending bitonic sort of n (key, id) pairs -- by_id: in the order of their ids.  Every exchange
+// brings the smaller pair to the lower place (the first of a merge by mirrored places), so places
+// beyond n need no pairs: what they would hold is never smaller.  Exchanges within 128 places are
+// between lanes of one wave.  The pairs must be visible; they are again on return.
+__device__ __forceinline__ void search_sort(unsigned long long *key, uint32_t *id, int n, bool by_id) {
+  int np = 2;
+  while (np < n) np <<= 1;
+#pragma unroll 1
+  for (int k = 2; k <= np; k <<= 1) {
+#pragma unroll 1
+    for (int j = k >> 1; j > 0; j >>= 1) {
+#pragma unroll 1
+      for (int p = threadIdx.x; p < np / 2; p += kSearchThreads) {
+        const int low = p & (j - 1), i = 2 * p - low, x = j == k >> 1 ? i - low + (2 * j - 1 - low) : i + j;  // i < x
+        if (x < n) {
+          const unsigned long long ki = key[i], kx = key[x];
+          const uint32_t ii = id[i], ix = id[x];
+          if (key_id_less(by_id ? 0 : kx, ix, by_id ? 0 : ki, ii)) { key[i] = kx; key[x] = ki; id[i] = ix; id[x] = ii; }
+        }
+      }
+      const int next = j > 1 ? j : 2 * k;  // places the next step's exchanges lie within
+      if (2 * j > 128 || next > 128) __syncthreads();
+      else wave_lds_fence();
+    }
   }
   __syncthreads();
 }
 
 // Brings the W smallest of the n > W (key, id) pairs to the front of the buffer, in ascending
-// order.  A histogram over the range of the keys finds the bin the W-th lies in (again within that
-// bin while too many share it); what lies in it or before it is ranked.  The buffer must be
-// visible; it is again on return.
-__device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &sh, int n, int W, int gather) {
+// order.  A histogram over the range of the keys' bits (keys are not negative) finds the bin the W-th
+// lies in, again within that bin while too many share it; among equal keys the ids take the keys'
+// place.  What lies in the bin or before it is ranked.  The buffer must be visible; it is again on
+// return.  Returns 0, or (WIDE) how many pairs (okey, oid) then holds, the W smallest among them and
+// more than search_place takes: their order is left to the caller.
+// Every round takes a range apart into at least two bins that are not empty, so there are at most 15.
+template <bool WIDE>
+__device__ __forceinline__ int search_select(const SearchLds &L, SelectShared &sh, int n, int W, int gather) {
+  constexpr unsigned long long kById = 1ull << 63;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   // this thread's pairs (requested together: places beyond n read the last pair and do not count)
-  unsigned long long kk[kSelectKeep];
+  unsigned long long x[kSelectKeep];  // the key's bits, later what takes their place
   uint32_t ii[kSelectKeep];
 #pragma unroll
   for (int q = 0; q < kSelectKeep; ++q) {
     const int e = min(t + q * kSearchThreads, n - 1);
-    kk[q] = L.key[e];
+    x[q] = L.key[e];
     ii[q] = L.id[e];
   }
-  double lo = __builtin_huge_val(), hi = 0.0;
+  double least = __builtin_huge_val(), most = 0.0;
 #pragma unroll
   for (int q = 0; q < kSelectKeep; ++q) {  // (the last pair again changes neither)
-    const double x = __longlong_as_double((long long)kk[q]);
-    lo = fmin(lo, x);
-    hi = fmax(hi, x);
+    least = fmin(least, __longlong_as_double((long long)x[q]));
+    most = fmax(most, __longlong_as_double((long long)x[q]));
   }
-  lo = wave_extreme_last<true>(lo);
-  hi = wave_extreme_last<false>(hi);
-  if (lane == 63) { sh.ext[2 * wv] = lo; sh.ext[2 * wv + 1] = hi; }
-  for (int x = t; x < kSearchBins; x += kSearchThreads) L.hist[x] = 0;
-  for (int x = t; x < gather; x += kSearchThreads) L.rank[x] = 0;
+  least = wave_extreme_last<true>(least);
+  most = wave_extreme_last<false>(most);
+  if (lane == 63) { sh.ext[2 * wv] = least; sh.ext[2 * wv + 1] = most; }
+  for (int b = t; b < kSearchBins; b += kSearchThreads) L.hist[b] = 0;
+  for (int b = t; b < gather; b += kSearchThreads) L.rank[b] = 0;
   __syncthreads();
-  lo = sh.ext[0]; hi = sh.ext[1];
+  least = sh.ext[0]; most = sh.ext[1];
 #pragma unroll
-  for (int w = 1; w < kSearchThreads / 64; ++w) { lo = fmin(lo, sh.ext[2 * w]); hi = fmax(hi, sh.ext[2 * w + 1]); }
+  for (int w = 1; w < kSearchThreads / 64; ++w) { least = fmin(least, sh.ext[2 * w]); most = fmax(most, sh.ext[2 * w + 1]); }
+  unsigned long long lo = (unsigned long long)__double_as_longlong(least), hi = (unsigned long long)__double_as_longlong(most);
   int below = 0;  // pairs under lo
-  for (int round = 0;; ++round) {  // uniform
-    const double scale = hi > lo ? (double)kSearchBins / (hi - lo) : 0.0;
-    auto bin_of = [&](double x) { return min((int)((x - lo) * scale), kSearchBins - 1); };
+  for (;;) {  // uniform
+    // (a range of 2^k values and less than twice that: 128 to 256 bins)
+    const int shift = hi - lo < kSearchBins ? 0 : 64 - kSearchBinBits - __builtin_clzll(hi - lo);
+    auto bin_of = [&](unsigned long long v) { return (int)((v - lo) >> shift); };
 #pragma unroll
-    for (int q = 0; q < kSelectKeep; ++q) {
-      const double x = __longlong_as_double((long long)kk[q]);
-      if (t + q * kSearchThreads < n && x >= lo && x <= hi) atomicAdd(&L.hist[bin_of(x)], 1u);
-    }
+    for (int q = 0; q < kSelectKeep; ++q)
+      if (t + q * kSearchThreads < n && x[q] >= lo && x[q] <= hi) atomicAdd(&L.hist[bin_of(x[q])], 1u);
     if (t == 0) { sh.n = 0; sh.lo = ~0ull; sh.hi = 0; }
     __syncthreads();
     // the bin of the W-th (every wave for itself)
@@ -686,8 +716,7 @@ __device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &
       uint32_t total = 0;
 #pragma unroll
       for (int q = 0; q < kSelectKeep; ++q) {
-        const double x = __longlong_as_double((long long)kk[q]);
-        mask[q] = __builtin_amdgcn_ballot_w64(t + q * kSearchThreads < n && (x < lo || (x <= hi && bin_of(x) <= bin)));
+        mask[q] = __builtin_amdgcn_ballot_w64(t + q * kSearchThreads < n && (x[q] < lo || (x[q] <= hi && bin_of(x[q]) <= bin)));
         total += (uint32_t)__popcll(mask[q]);
       }
       uint32_t at = 0;
@@ -696,38 +725,30 @@ __device__ __forceinline__ void search_select(const SearchLds &L, SelectShared &
 #pragma unroll
       for (int q = 0; q < kSelectKeep; ++q) {
         const uint32_t mine = at + (uint32_t)__popcll(mask[q] & ((1ull << lane) - 1ull));
-        if ((mask[q] >> lane) & 1ull) { L.okey[mine] = kk[q]; L.oid[mine] = ii[q]; }
+        if ((mask[q] >> lane) & 1ull) { L.okey[mine] = L.key[t + q * kSearchThreads]; L.oid[mine] = ii[q]; }
         at += (uint32_t)__popcll(mask[q]);
       }
       __syncthreads();
+      if (WIDE && m > kRankByCounting) return m;
       search_place(L, m, W, false);
-      return;
+      return 0;
     }
-    if (scale == 0.0 || round == 3) break;  // (equal keys, or a range the bins do not separate)
+    const bool equal = lo == hi;
+    if (equal) {  // many equal keys: by their ids, which differ
 #pragma unroll
-    for (int q = 0; q < kSelectKeep; ++q) {
-      const double x = __longlong_as_double((long long)kk[q]);
-      if (t + q * kSearchThreads < n && x >= lo && x <= hi && bin_of(x) == bin) { atomicMin(&sh.lo, kk[q]); atomicMax(&sh.hi, kk[q]); }
+      for (int q = 0; q < kSelectKeep; ++q) x[q] = x[q] == lo ? kById | ii[q] : (x[q] < lo ? 0ull : ~0ull);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kSelectKeep; ++q)
+        if (t + q * kSearchThreads < n && x[q] >= lo && x[q] <= hi && bin_of(x[q]) == bin) { atomicMin(&sh.lo, x[q]); atomicMax(&sh.hi, x[q]); }
     }
     __syncthreads();  // (every wave has read the histogram)
-    for (int x = t; x < kSearchBins; x += kSearchThreads) L.hist[x] = 0;
+    for (int e = t; e < kSearchBins; e += kSearchThreads) L.hist[e] = 0;
     below = under;
-    lo = __longlong_as_double((long long)sh.lo);
-    hi = __longlong_as_double((long long)sh.hi);
+    lo = equal ? kById : sh.lo;
+    hi = equal ? kById | 0xFFFFFFFFull : sh.hi;
     __syncthreads();  // (read before the next round resets them)
   }
-  // many equal keys: every pair against every other
-#pragma unroll
-  for (int q = 0; q < kSelectKeep; ++q) {
-    if (t + q * kSearchThreads < n) {
-      uint32_t before = 0;
-      for (int x = 0; x < n; ++x) before += key_id_less(L.key[x], L.id[x], kk[q], ii[q]) ? 1u : 0u;
-      if (before < (uint32_t)W) { L.okey[before] = kk[q]; L.oid[before] = ii[q]; }
-    }
-  }
-  __syncthreads();
-  for (int x = t; x < W; x += kSearchThreads) { L.key[x] = L.okey[x]; L.id[x] = L.oid[x]; }
-  __syncthreads();
 }
 
 // ---- the levels ----
@@ -745,7 +766,7 @@ template <int MODE, int FORM>
 __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_beam(DevPlan pl, SearchArgs a) {
   constexpr bool SPLIT = MODE == SEARCH_SPLIT || MODE == SEARCH_SPLIT_TP;   // two pools per stage
   constexpr bool STP = MODE == SEARCH_STAGE_TP || MODE == SEARCH_SPLIT_TP;  // a TP degree per stage
-  constexpr bool LDSF = FORM == SEARCH_IN_LDS, ZONES = FORM == SEARCH_BY_ZONE;
+  constexpr bool LDSF = FORM == SEARCH_IN_LDS, WIDE = FORM >= SEARCH_WIDE, ZONES = FORM == SEARCH_BY_ZONE;
   using State = SState<SPLIT>;
   extern __shared__ __align__(16) double search_lds[];  // (tables by pool are read in pairs, from even places)
   __shared__ SelectShared sh;
@@ -1035,12 +1056,24 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
             for (int i = t; i < n_raw; i += kSearchThreads) L.raw[(tb ^ 1) * n_raw + i] = i < kSearchThreads ? ahead : search_row<STP>(pl, s, j + 1)[i];
           }
           // the W smallest, at the end of a phase and when there is no room for what is left
-          sorted = false;
-          if (used > W && (done || buf - used < min(n_all - i0, buf - W))) {  // uniform
-            search_select(L, sh, used, W, gather);
+          const bool full = used > W && (done || buf - used < min(n_all - i0, buf - W));  // uniform
+          const int left = full ? search_select<WIDE>(L, sh, used, W, gather) : 0;
+          sorted = full;
+          if (WIDE) {
+            // left to sort: what a selection did not rank; a long frontier that was not cut
+            const bool whole = !full && done && phase == (INNER > 1 ? 1 : 0) && used > kRankByCounting;
+            if (left != 0) {
+              search_sort(L.okey, L.oid, left, false);
+              for (int x = t; x < W; x += kSearchThreads) { L.key[x] = L.okey[x]; L.id[x] = L.oid[x]; }
+              __syncthreads();
+            } else if (whole) {
+              search_sort(L.key, L.id, used, !cut);
+              sorted = true;
+            }
+          }
+          if (full) {
             used = W;
             tau = L.key[W - 1];
-            sorted = true;
             if (!done && t == 0) *counter = (uint32_t)W;
           }
           if (done) break;
@@ -1386,7 +1419,7 @@ __device__ __forceinline__ void place_sum(const double *v, int P, double &sum, d
 // profiled times, node size, gradient shard, GPUs against the quota, rent) uses the stage's own
 // degree.  A descriptor, pool or TP index out of range yields mask = 0xFFFFFFFF, T = C = +inf, mem = 0.
 //
-// A workgroup takes per_wg plans and works through their stages, up to 1 024 at a time, plans
+// A workgroup takes per_wg plans and works through their stages, up to kPlaceStages at a time, plans
 // one behind the other without gaps: first a lane per stage -- what is added up in stage order,
 // which is part of the definition, goes to LDS, maxima are folded in there -- then a lane per
 // plan adds its stages up, a wave per quantity.  A wave per plan leaves most lanes idle where

@@ -972,6 +972,35 @@ def test_levels_that_take_several_passes_of_the_buffer(torch_cuda, form, objecti
         plan.destroy()
 
 
+@pytest.mark.parametrize("form", ["plain", "stage_tp", "split"])
+@pytest.mark.parametrize("n_types, width", [(1, 64), (2, 64), (2, 384), (1, 385), (2, 1024)])
+def test_frontiers_of_equal_keys(torch_cuda, form, n_types, width):
+    # zones that do not differ: most bounds of a level are equal and the frontier is cut among them by
+    # the order of generation; beams up to 384 rank what a selection leaves, wider ones sort it
+    stream = torch_cuda.cuda.current_stream().cuda_stream
+    kw = {"allow_split": form == "split", "stage_tp": form == "stage_tp"}
+    if kw["allow_split"] and width > 64:
+        width = 40 if width < 1024 else 400
+    Z, G = 16, n_types
+    bw = np.full((Z, Z), 1e9)
+    np.fill_diagonal(bw, 1e10)
+    t = np.array([1.0, 1.25])[:G].reshape(G, 1, 1, 1) * np.array([1.0, 0.5]).reshape(1, 1, 2, 1)
+    prob = make_problem(n_layers=6, n_types=G, n_zones=Z, mb_list=(1,), tp_list=(1, 2), dp_list=(2,), pp_list=[3, 6],
+                        global_batch=16, t_fwd=1e-3 * t, t_bwd=2e-3 * t, t_upd=1e-4, layer_params=20_000_000, p2p=3_000_000,
+                        avail=6, bw=bw, egress=np.where(np.eye(Z) > 0, 0.0, 2e-11), price=np.array([3.0, 2.5])[:G])
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        for objective in OBJECTIVES:
+            got, want = plan.search(width, objective, stream=stream, **kw), orc.search_beam(width, objective, **kw)
+            assert want is not None and want.truncated
+            if form == "plain":
+                check_same(got, want, objective)
+            else:
+                {"stage_tp": check_same_tp, "split": check_same_split}[form](got, want, objective, orc)
+    finally:
+        plan.destroy()
+
+
 def many_zones(n_zones, n_types, n_tp, depths, n_layers):
     rng = np.random.default_rng(n_zones * 100 + n_tp)
     G, Z, L = n_types, n_zones, n_layers
