@@ -1128,8 +1128,11 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     // size and batch divisibility allow: bounds that let a query pass over a unit whatever the
     // availability becomes.  A unit that has no such plan is dropped for good.  Units of equal
     // size still differ widely in cost, because invalid plans are pruned early, so the second
-    // pass records how long each remaining unit takes; they are launched longest first, which
-    // also deals them evenly to the hardware's dispatch queues.
+    // pass records how long each remaining unit takes -- with every valid plan evaluated, since what
+    // a query can leave out depends on its objective and its bound (timed with what the fastest plan
+    // leaves out, units that are long for the cheapest one stayed whole: 144 us instead of 77 on
+    // 2.7e8 plans with pairs of types); they are launched longest first, which also deals them
+    // evenly to the hardware's dispatch queues.
     // (Five passes did this -- which units hold a plan, how long each takes, the same once more
     // after the cut below, either bound on its own: of the 1.1e9 plans of five zones with pairs of
     // types 2.1 ms, now 0.9 ms.)
@@ -1165,15 +1168,14 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
     CREATE_TRY(hipGetLastError());
     CREATE_TRY(hipMemcpy(val.data(), d_cost, NU * sizeof(float), hipMemcpyDeviceToHost));
-    ca.ignore_quota = 1;
-    ca.ucost = nullptr;
     // With the longest units first the launch ends about when the average load of a
     // workgroup slot is done, unless a unit on its own takes longer than that: such a unit is
     // cut into parts -- every part keeps the unit's records and takes a share of its lane
     // space -- within the room the dropped units left in the tables.  A part is taken to last its
-    // share of the unit's time beyond the staging, and its bounds are computed anew.  (Cutting
-    // units that are merely above the mean costs more in staging than it
-    // gains: spaces with far more units than slots ran 4 % slower that way.)
+    // share of the unit's time beyond the staging, and keeps the unit's bounds: its own would take
+    // as long as the whole pass behind them (five parts of a space of 1.1e9 plans: 150 of 3 200 us)
+    // and tell few parts apart.  (Cutting units that are merely above the mean costs more in
+    // staging than it gains: spaces with far more units than slots ran 4 % slower that way.)
     {
       double total = 0.0;
       for (size_t i = 0; i < NU; ++i) total += val[i];
@@ -1194,7 +1196,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
       const size_t most = std::max<size_t>(1, std::min<size_t>(255, chunks_of_unit / waves));
       size_t room = n_units_alloc - NU;
       std::vector<UnitRec> cut;  // the parts, which go behind the units that stay whole
-      std::vector<float> cut_val;
+      std::vector<float> cut_val, cut_time, cut_cost;
       size_t n_whole = 0;
       for (size_t i = 0; i < NU; ++i) {
         UnitRec u = pl->units[i];
@@ -1215,25 +1217,20 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
           u.part = (uint8_t)c;
           cut.push_back(u);
           cut_val.push_back(std::min(val[i], kStagingTicks) + std::max(0.f, val[i] - kStagingTicks) / (float)parts);
+          cut_time.push_back(lb_time[i]);
+          cut_cost.push_back(lb_cost[i]);
         }
         room -= parts - 1;
       }
-      if (!cut.empty()) {
-        NU = n_whole + cut.size();
-        pl->units.resize(n_whole);
-        pl->units.insert(pl->units.end(), cut.begin(), cut.end());
-        val.resize(n_whole);
-        val.insert(val.end(), cut_val.begin(), cut_val.end());
-        lb_time.resize(NU);
-        lb_cost.resize(NU);
-        d.n_units = (int)cut.size();  // the parts alone
-        CREATE_TRY(hipMemcpy(d_units, cut.data(), cut.size() * sizeof(UnitRec), hipMemcpyHostToDevice));
-        launch_bounds(pl, ca);
-        CREATE_TRY(hipGetLastError());
-        CREATE_TRY(hipMemcpy(&lb_time[n_whole], pl->umin_s, cut.size() * sizeof(float), hipMemcpyDeviceToHost));
-        CREATE_TRY(hipMemcpy(&lb_cost[n_whole], pl->umin_l, cut.size() * sizeof(float), hipMemcpyDeviceToHost));
-        d.n_units = (int)NU;
-      }
+      const auto behind = [n_whole](auto &whole, const auto &parts) {
+        whole.resize(n_whole);
+        whole.insert(whole.end(), parts.begin(), parts.end());
+      };
+      behind(pl->units, cut);
+      behind(val, cut_val);
+      behind(lb_time, cut_time);
+      behind(lb_cost, cut_cost);
+      d.n_units = (int)(NU = pl->units.size());
     }
     // the bounds in the units' final order, and the units sorted by either bound: the host then
     // knows how many units a limit leaves alive, and the device which

@@ -505,7 +505,8 @@ struct ScanArgs {
   float lim_s, lim_l;       // constraint limits (strict, loose) on cost or on time
   SurvRec *surv;
   uint32_t surv_cap;
-  float *ucost;             // SCAN, optional: ticks of the 100 MHz clock each unit took
+  float *ucost;             // SCAN, optional: ticks of the 100 MHz clock each unit took, nothing
+                            // left out for the minimum found so far
   int ignore_quota;         // SCAN at plan creation: treat every pool as large enough
   const uint32_t *ulist;    // COLLECT, optional: the units to visit and, in counters[CNT_NLIST],
                             // how many; the grid then strides over the list
@@ -660,8 +661,9 @@ __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballo
 // non-negative values round monotonically, so the bound holds for the very values that the full
 // evaluation returns, and no minimum and no kept candidate changes.  A lane is dropped when the
 // bound lies above the smallest key its workgroup has found (kept in LDS), above the threshold
-// the caller knows, or above the loose limit.  The lane space is walked from the largest
-// data-parallel degrees down: those plans are the fast ones, and what is small early prunes most.
+// the caller knows, or above the loose limit.  For the fastest plan the lane space is walked from the
+// largest data-parallel degrees down, for the cheapest from the smallest up: what is small early prunes
+// most (cheapest of 1.9e7 plans with a TP degree per segment: 59 us down, 53 up).
 // The scan is bound by vector instructions (70 of its 92 us on 9.2e8 plans with a TP degree per
 // segment); without the bound it took 107 us, and 257 us instead of 156 on 1.1e9 plans with pairs
 // of types.
@@ -701,7 +703,7 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   };
   // (one thread of the waves that improve on what the workgroup has)
   auto report = [&](float l0, float l1) {
-    if (MODE == MODE_COLLECT) return;
+    if (MODE == MODE_COLLECT || (MODE == MODE_SCAN && a.ucost)) return;
     if (wave_any(ms < l0)) {
       const float m = wave_min(ms);
       if (lane == 0) atomicMin(&s_min[0], __float_as_uint(m));
@@ -714,8 +716,8 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   if (S <= 2) {
     const int nin = MB * DP * ZG;
     const int rounds = (nin - 1 - wave * 64 + nwave * 64) / (nwave * 64);  // (0 for waves beyond the lane space)
-    for (int j = rounds - 1; j >= 0; --j) {
-      const int e0 = (wave + j * nwave) * 64;
+    for (int i = 0; i < rounds; ++i) {
+      const int e0 = (wave + (OBJ == 0 ? rounds - 1 - i : i) * nwave) * 64;
       const LaneItem it = lane_item(pl, e0 + lane, nin, ZG, pl.mg_mbzg);
       const int a1 = it.a1;
       uint32_t b0 = rbits[a1 * MB + it.mb] & it.dpbit;
@@ -763,8 +765,8 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
     int z2 = u.o_lo / G, g2 = u.o_lo % G;
     for (int a2 = u.o_lo; a2 < u.o_lo + u.o_cnt; ++a2) {
 
-      for (int j = rounds - 1; j >= 0; --j) {
-        const int e0 = (wave + j * nwave) * 64;
+      for (int i = 0; i < rounds; ++i) {
+        const int e0 = (wave + (OBJ == 0 ? rounds - 1 - i : i) * nwave) * 64;
         const LaneItem it = lane_item(pl, e0 + lane, nin, ZG - 1, pl.mg_mbzg1);
         const int a1 = it.a1 + (it.a1 >= a2 ? 1 : 0);  // skip the pool of segment 2
         const int i0 = a1 * MB + it.mb, i1 = (ZG + a2) * MB + it.mb;
