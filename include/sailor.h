@@ -107,7 +107,7 @@ enum {
   SAILOR_MAX_SHAPES = 1 << 20, /* (layer split, cut points) combinations over all pp */
   SAILOR_MAX_BW_COEF = 8, /* coefficients of a link's bandwidth polynomial */
   SAILOR_MAX_K = 4096,    /* largest k of sailor_topk */
-  SAILOR_STATIC_SCRATCH_BYTES = 8 << 20, /* (no longer used: the schedule needs no device scratch) */
+  SAILOR_STATIC_SCRATCH_BYTES = 8 << 20, /* unused: the schedule needs no device scratch (kept for programs that name it) */
   SAILOR_STATIC_MAX_PLANS = 4096         /* most plans one call of it takes */
 };
 

@@ -759,8 +759,9 @@ __device__ __forceinline__ int search_select(const SearchLds &L, SelectShared &s
 // inner digit only (b, or k): a level first looks at items, by the best choice of each; only where
 // there is an inner digit, the choices behind the best W items are looked at one by one -- the W
 // smallest choices lie in the W items with the smallest bests.
-// (Two waves per SIMD for split stages, four else: with four, the wider code spills to memory, 1.19 ms
-// against 1.05; with two, the narrower loses a workgroup per compute unit, 0.72 ms against 0.62.)
+// (Two waves per SIMD for split stages, four else.  At four, the code for split stages spills so much
+// that it takes 1.19 ms against 1.05; the other forms spill too -- 54 registers with a pool per stage,
+// 121 with a degree per stage -- but at two they lose a workgroup per compute unit, 0.72 ms against 0.62.)
 // FORM: where the frontiers are, and how all-reduce seconds are kept.
 template <int MODE, int FORM>
 __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_beam(DevPlan pl, SearchArgs a) {
