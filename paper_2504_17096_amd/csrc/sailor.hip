@@ -580,13 +580,18 @@ unsigned quota_grid(const DevPlan &d) {
 // the quota table from it.
 sailor_status refresh_avail(sailor_plan *pl, hipStream_t st) {
   if (!pl->avail_dirty) return SAILOR_OK;
-  // the kernel reads the new table from the pinned staging buffer and leaves a copy on the
-  // device (no separate upload in front of it)
   pl->avail_gen += 1;
-  k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, pl->h_avail_dev, pl->d_avail,
-                                                      pl->avail_gen);
-  HIP_TRY(hipEventRecord(pl->ev_upload, st));
-  pl->upload_pending = true;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();  // (the launch reports it)
+  const bool mapped = capturing != hipStreamCaptureStatusNone;  // replays read the table of their time
+  AvailTable table;
+  std::memcpy(table.v, pl->h_avail, pl->dev.ZGr * sizeof(int32_t));
+  k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, table, mapped ? pl->h_avail_dev : nullptr, pl->d_avail,
+                                                     pl->avail_gen);
+  if (mapped) {
+    HIP_TRY(hipEventRecord(pl->ev_upload, st));
+    pl->upload_pending = true;
+  }
   pl->avail_dirty = false;
   return SAILOR_OK;
 }
@@ -615,10 +620,10 @@ template <int MODE>
 void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const ScanArgs &a,
                   hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const unsigned n_units = (unsigned)pl->units.size();
-  const dim3 grid(MODE == MODE_SCAN ? n_units
-                  : a.direct        ? a.n_list_host * a.n_sub
-                  : a.ulist         ? std::min(n_units, kListUnits) * a.n_sub
-                                    : n_units * a.n_sub),
+  const dim3 grid(a.direct              ? a.n_list_host * a.n_sub
+                  : MODE != MODE_COLLECT ? n_units
+                  : a.ulist              ? std::min(n_units, kListUnits) * a.n_sub
+                                         : n_units * a.n_sub),
       block(pl->unit_threads);
   const size_t lds = pl->lds_bytes;
   if (pl->dev.mixed) launch_units_m<MODE, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
@@ -667,7 +672,7 @@ sailor_status wait_for_result(const sailor_plan *pl, hipStream_t st) {
 // Shared by best_plan (k = 0: tolerance rule) and topk.
 sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
                                  const sailor_constraint *con, uint32_t k, hipStream_t st,
-                                 ResultHeader *hdr_out, bool allow_direct, bool *again) {
+                                 ResultHeader *hdr_out, bool first_try, bool *again) {
   int has_bound;
   double bound;
   ScanArgs sa{};
@@ -714,10 +719,12 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   const bool t_scan = pl->timing_mode >= 1, t_all = pl->timing_mode >= 2;
 
   // collect -> [k-th smallest survivor key] -> fp64 refine -> final selection -> sync
-  auto run_tail = [&](ResultHeader *hdr) -> sailor_status {
+  // kept: the best plan's scan has kept its candidates already
+  auto run_tail = [&](ResultHeader *hdr, bool kept) -> sailor_status {
     // (a direct pass is the call's pass over the space: the scan's timing events ride on it)
-    launch_units<MODE_COLLECT>(pl, obj, has_bound, sa, st, sa.direct && t_scan ? pl->ev[3] : nullptr,
-                               sa.direct && t_scan ? pl->ev[1] : nullptr);
+    if (!kept)
+      launch_units<MODE_COLLECT>(pl, obj, has_bound, sa, st, sa.direct && t_scan ? pl->ev[3] : nullptr,
+                                 sa.direct && t_scan ? pl->ev[1] : nullptr);
     RefineArgs ra{};
     ra.surv = pl->surv;
     ra.surv_cap = pl->surv_cap;
@@ -728,21 +735,16 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     ra.has_bound = has_bound;
     ra.bound = bound;
     ra.band = 1.0f + 3.0f * kEvalEps;
-    if (!best || sa.direct) {
+    if (best) {
+      ra.band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
+      k_refine_best<<<kBestWorkgroups, kBestWaves * 64, 0, st>>>(pl->dev, ra, cnt_next, pl->d_hdr, pl->d_out, ++pl->seq);
+    } else {
       // the exact k-th smallest fp32 key among the survivors, then only its neighbourhood
-      // (best plan after a direct pass: the smallest key and its tie band -- what the collect
-      // pass behind a scan gathers in the first place)
       k_select_kth<256><<<1, 256, 0, st>>>(&pl->surv[0].key, (int)(sizeof(SurvRec) / 4),
-                                       cnt + CNT_SURV, pl->surv_cap, best ? 1u : k, cnt + CNT_TAU1,
+                                       cnt + CNT_SURV, pl->surv_cap, k, cnt + CNT_TAU1,
                                        nullptr, 0u, 0.f, nullptr, nullptr);
       ra.tau_src = cnt + CNT_TAU1;
-      if (best) ra.band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
-    }
-    k_refine<<<256, kRefineWaves * 64, 0, st>>>(pl->dev, ra);
-    if (best) {
-      k_pick_best<<<1, 1024, 0, st>>>(pl->ref, pl->ref_cap, cnt, cnt_next, (int)obj, pl->d_hdr,
-                                      pl->d_out, ++pl->seq);
-    } else {
+      k_refine<<<256, kRefineWaves * 64, 0, st>>>(pl->dev, ra);
       // few records expected (about k, plus ties): one workgroup ranks them from LDS
       const bool one = k <= kRankOneWorkgroup;
       k_rank_topk<<<one ? 1 : 64, one ? kRankLds : 256, 0, st>>>(
@@ -758,14 +760,10 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   };
 
   if (t_all) HIP_TRY(hipEventRecord(pl->ev[0], st));
-  // A query whose constraint leaves only a few units alive (their bounds are sorted on the
-  // host) needs no scan and no threshold: one pass over those units keeps every valid
-  // candidate within the loose limit, and the usual tail -- the k-th smallest key among them
-  // (the smallest, for the best plan), fp64 re-evaluation, ranking -- follows.  Not when minima are kept for later calls (this
-  // pass produces none), and not for a query that kept too many candidates the last time.
+  // A constraint often leaves only a few units alive (their bounds are sorted on the host).  Not
+  // used when minima are kept for later calls: a pass over a few units produces none.
   pl->last_direct = false;
-  if (allow_direct && has_bound && !pl->incremental &&
-      !(pl->direct_declined && pl->declined_obj == (int)obj && pl->declined_lim == sa.lim_l)) {
+  if (first_try && has_bound && !pl->incremental) {
     const bool on_cost = obj == SAILOR_MAX_THROUGHPUT;
     const std::vector<float> &sorted_lb = on_cost ? pl->lb_cost_sorted : pl->lb_time_sorted;
     const size_t n_live = (size_t)(std::upper_bound(sorted_lb.begin(), sorted_lb.end(), sa.lim_l) -
@@ -775,69 +773,67 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
       sa.n_list_host = (uint32_t)n_live;
       sa.ulist = on_cost ? pl->order_cost : pl->order_time;
       sa.n_sub = kDirectSub;
-      sa.use_tau_host = 1;
-      sa.tau_host = kPosInf;
-      rc = run_tail(hdr_out);
-      if (rc != SAILOR_OK) return rc;
-      pl->total_timed = t_all;
-      pl->scan_timed = t_scan;
-      if (hdr_out->surv_count > std::min(kDirectManySurvivors, pl->surv_cap / 2)) {
-        pl->direct_declined = true;
-        pl->declined_obj = (int)obj;
-        pl->declined_lim = sa.lim_l;
-      }
-      if (hdr_out->surv_count > pl->surv_cap || hdr_out->ref_count > pl->ref_cap) {
-        *again = true;  // more candidates than the buffers hold: the scan and its threshold decide
-        return SAILOR_OK;
-      }
-      pl->last_direct = true;
-      pl->last_direct_units = (uint32_t)n_live;
-      pl->last_incremental = false;
+    }
+  }
+  if (best && !sa.incremental && first_try) {
+    // The scan keeps the candidates near the minimum itself (ScanArgs::near_band), so one kernel
+    // is left behind it.  (Not when minima are reused: units that are not evaluated again report at
+    // once, before any running minimum exists, and would have to stage their records again.)
+    sa.near_band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
+    // (minima kept for later calls must not depend on this call's running minimum)
+    if (!pl->incremental) sa.ulb_key = obj == SAILOR_MAX_THROUGHPUT ? pl->lb_time : pl->lb_cost;
+    launch_units<MODE_BEST>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr, t_scan ? pl->ev[1] : nullptr);
+    rc = run_tail(hdr_out, true);
+    if (rc != SAILOR_OK) return rc;
+    pl->total_timed = t_all;
+    pl->scan_timed = t_scan;
+    if (hdr_out->surv_count > pl->surv_cap) {
+      *again = true;  // a running minimum admits more than the final one: the scan's minimum decides
       return SAILOR_OK;
     }
+    pl->last_direct = sa.direct != 0;
+    pl->last_direct_units = sa.n_list_host;
+    pl->cache_ok = !sa.direct;
+    pl->last_incremental = false;
+    pl->last_scan_seq = sa.call_seq;
+    return hdr_out->ref_count > pl->ref_cap ? SAILOR_ENOMEM : SAILOR_OK;
   }
-  if (best) {
-    // the scan itself lists the units that can hold a plan within the tie band of the
-    // minimum (a superset: see ScanArgs), so the collect pass visits a handful of units
-    // instead of asking every unit's workgroups
-    sa.band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
-    // (not when minima are reused: units that are not evaluated again report at once, before
-    // any running minimum exists, and nearly all of them would be listed)
-    if (!sa.incremental) {
-      sa.near_list = pl->ulist;
-      sa.near_band = sa.band;
-      // (minima kept for later calls must not depend on this call's running minimum)
-      if (!pl->incremental) sa.ulb_key = obj == SAILOR_MAX_THROUGHPUT ? pl->lb_time : pl->lb_cost;
+  // Top-k over a few units needs no scan and no threshold: one pass over them keeps every valid
+  // candidate within the loose limit, and the usual tail -- the k-th smallest key among them, fp64
+  // re-evaluation, ranking -- follows.  Not for a query that kept too many candidates the last time.
+  if (sa.direct && !(pl->direct_declined && pl->declined_obj == (int)obj && pl->declined_lim == sa.lim_l)) {
+    sa.use_tau_host = 1;
+    sa.tau_host = kPosInf;
+    rc = run_tail(hdr_out, false);
+    if (rc != SAILOR_OK) return rc;
+    pl->total_timed = t_all;
+    pl->scan_timed = t_scan;
+    if (hdr_out->surv_count > std::min(kDirectManySurvivors, pl->surv_cap / 2)) {
+      pl->direct_declined = true;
+      pl->declined_obj = (int)obj;
+      pl->declined_lim = sa.lim_l;
     }
+    if (hdr_out->surv_count > pl->surv_cap || hdr_out->ref_count > pl->ref_cap) {
+      *again = true;  // more candidates than the buffers hold: the scan and its threshold decide
+      return SAILOR_OK;
+    }
+    pl->last_direct = true;
+    pl->last_direct_units = sa.n_list_host;
+    pl->last_incremental = false;
+    return SAILOR_OK;
   }
+  sa.direct = 0;
   launch_units<MODE_SCAN>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr,
                           t_scan ? pl->ev[1] : nullptr);
-  const bool listed_by_scan = sa.near_list != nullptr;
-  sa.near_list = nullptr;
-  sa.ulb_key = nullptr;
-  if (best && listed_by_scan) {
-    sa.tau_src = cnt + CNT_GMIN;
-    sa.ulist = pl->ulist;
-    sa.n_sub = kListSub;
-  } else if (best) {
-    // the smallest strict unit minimum is the scan's minimum; the same kernel lists the units
-    // whose loose minimum lies within the tie band of it
-    k_select_kth<1024><<<1, 1024, 0, st>>>(pl->umin_s, 1, nullptr, n_units, 1u, cnt + CNT_TAU0,
-                                     pl->umin_l, n_units, sa.band, pl->ulist, cnt + CNT_NLIST);
-    sa.tau_src = cnt + CNT_TAU0;
-    sa.ulist = pl->ulist;
-    sa.n_sub = kListSub;
-  } else {
-    // an upper bound of the k-th smallest key: the k-th smallest unit minimum
-    // (the same kernel lists the units whose loose minimum lies under it)
-    sa.band = 1.0f + 3.0f * kEvalEps;
-    k_select_kth<1024><<<1, 1024, 0, st>>>(pl->umin_s, 1, nullptr, n_units, k, cnt + CNT_TAU0,
-                                     pl->umin_l, n_units, sa.band, pl->ulist, cnt + CNT_NLIST);
-    sa.tau_src = cnt + CNT_TAU0;
-    sa.ulist = pl->ulist;
-    sa.n_sub = kListSub;
-  }
-  rc = run_tail(hdr_out);
+  // an upper bound of the k-th smallest key: the k-th smallest unit minimum (the best plan's: the
+  // smallest, and its tie band).  The same kernel lists the units whose loose minimum lies under it.
+  sa.band = best ? (float)(1.0 + kTieTol) + 3.0f * kEvalEps : 1.0f + 3.0f * kEvalEps;
+  k_select_kth<1024><<<1, 1024, 0, st>>>(pl->umin_s, 1, nullptr, n_units, best ? 1u : k, cnt + CNT_TAU0,
+                                   pl->umin_l, n_units, sa.band, pl->ulist, cnt + CNT_NLIST);
+  sa.tau_src = cnt + CNT_TAU0;
+  sa.ulist = pl->ulist;
+  sa.n_sub = kListSub;
+  rc = run_tail(hdr_out, false);
   if (rc != SAILOR_OK) return rc;
   pl->total_timed = t_all;
   pl->scan_timed = t_scan;
@@ -886,7 +882,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
         cnt, (1u << CNT_SURV) | (1u << CNT_REF) | (1u << CNT_FEAS) | (1u << CNT_DONE));
     sa.count_only = 0;
     sa.tau_host = tau;
-    rc = run_tail(hdr_out);
+    rc = run_tail(hdr_out, false);
     if (rc != SAILOR_OK) return rc;
   }
   pl->cache_ok = true;  // the scan completed: every unit's minima and stamp are in place
@@ -1115,7 +1111,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   for (hipEvent_t &e : pl->ev) CREATE_TRY(hipEventCreate(&e));
 
   k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
-  k_quota_table<<<quota_grid(d), 256>>>(d, d.avail, nullptr, 0u);
+  AvailTable table;
+  std::memcpy(table.v, p->avail, ZGr * sizeof(int32_t));
+  k_quota_table<<<quota_grid(d), 256>>>(d, table, nullptr, pl->d_avail, 0u);
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_direct_tables<<<1, 256>>>(d);

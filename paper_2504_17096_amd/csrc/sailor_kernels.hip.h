@@ -5,8 +5,8 @@
 // Hot path:  k_units<SCAN>    full-space fp32 evaluation + per-unit minima, early pruning
 //            k_select_kth     radix select of the k-th smallest fp32 key
 //            k_units<COLLECT> re-evaluates the few units that can hold a winner
-//            k_refine         fp64 / exact-integer stage-by-stage re-evaluation
-//            k_pick_best / k_rank_topk   final selection
+//            k_refine, k_rank_topk   fp64 / exact-integer stage-by-stage re-evaluation, ranking
+//            k_units<BEST>, k_refine_best   the best plan: the same in two kernels
 //            k_eval_rows / k_eval_direct   per-candidate outputs for sailor_eval_batch
 //                             (index ranges / index lists)
 // Beside it: k_sim_1f1b       event-by-event 1F1B schedule of listed plans
@@ -421,12 +421,19 @@ __device__ __forceinline__ void acc_finish(const Acc &p, const LaneC &lc, float 
 // gen: the availability generation (0 while the plan is built); when an entry of qh changes,
 // row_gen[0] receives it, so that a scan can tell whether the shared-pool checks of a unit's
 // last evaluation still hold.
-__global__ void k_quota_table(DevPlan pl, const int32_t *avail, int32_t *avail_copy, uint32_t gen) {
-  // avail: the table to build from -- pl.avail, or a newer one in host-mapped memory, which
-  // is then also copied to avail_copy (= pl.avail) for the kernels that read it later; that
-  // saves a separate upload in front of this kernel
-  if (avail_copy && blockIdx.x == 0)
-    for (int r = threadIdx.x; r < pl.ZGr; r += blockDim.x) avail_copy[r] = avail[r];
+//
+// table: the availability, which travels in the kernel's arguments -- no upload in front of the
+// kernel, no trip over the bus inside it and nothing of the host's to wait for before it is used
+// again.  mapped: the same in host-mapped memory instead, for a call under stream capture (a replay
+// then reads what the host holds at the time).  Left in avail_copy (= pl.avail) for later kernels.
+struct AvailTable { int32_t v[kMaxPools]; };
+__global__ void k_quota_table(DevPlan pl, AvailTable table, const int32_t *mapped, int32_t *avail_copy, uint32_t gen) {
+  __shared__ int32_t avail[kMaxPools];
+  for (int r = threadIdx.x; r < pl.ZGr; r += blockDim.x) {
+    avail[r] = mapped ? mapped[r] : table.v[r];
+    if (blockIdx.x == 0) avail_copy[r] = avail[r];
+  }
+  __syncthreads();
   const int n = (pl.W_max + 1) * pl.ZG;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const int p = i % pl.ZG, w = i / pl.ZG;
@@ -490,8 +497,9 @@ __device__ __forceinline__ uint32_t joint_quota_bits(const DevPlan &pl, int n_se
 
 // SCAN: a unit's smallest key over the candidates strictly / loosely within the constraint.
 // COLLECT: a unit's candidates under a threshold.  BOUNDS (plan creation, no constraint): a unit's
-// smallest iteration time and smallest cost, in the places of SCAN's two minima.
-enum { MODE_SCAN = 0, MODE_COLLECT = 1, MODE_BOUNDS = 2 };
+// smallest iteration time and smallest cost, in the places of SCAN's two minima.  BEST: as SCAN, and a
+// unit that comes within the tie band of the smallest key so far keeps its candidates at once.
+enum { MODE_SCAN = 0, MODE_COLLECT = 1, MODE_BOUNDS = 2, MODE_BEST = 3 };
 
 struct ScanArgs {
   float *umin_s, *umin_l;   // [n_units] minima over strictly / loosely constrained candidates
@@ -518,21 +526,20 @@ struct ScanArgs {
                             // last evaluation keep their minima and are not evaluated again
   uint32_t *ubits;          // SCAN, with unit_gen: per unit, the validity bits of its records
   uint32_t ubits_stride;    // (and the shared-pool quota words) as last staged; words per unit
-  uint32_t *near_list;      // SCAN, optional (best plan): units whose loose minimum lies within
-  float near_band;          // near_band of the smallest strict key seen so far are appended
-                            // here (count in counters[CNT_NLIST]); the running minimum only
-                            // falls, so the list holds every unit within the band of the final one
+  float near_band;          // BEST: the tie band.  A unit whose loose minimum lies within near_band of
+                            // the smallest strict key seen so far appends its candidates up to there;
+                            // the running minimum only falls, so every candidate within the band of
+                            // the final one is among them
   const float *ulb_con;     // SCAN, optional, with a constraint: per unit, the smallest value the
                             // constrained quantity takes on any plan of the unit that memory, node
                             // size and batch allow (availability ignored; the same fp32 arithmetic,
                             // so an exact bound): a unit whose bound fails the loose limit holds
                             // nothing and is not staged at all (Sec. 4.2.1, H3, applied to a unit)
-  int direct;               // COLLECT without a scan before it: ulist names the only units whose
-  uint32_t n_list_host;     // bound meets the limit (n_list_host of them); every candidate of
-                            // theirs that is valid and within the loose limit is kept
-  const float *ulb_key;     // SCAN, optional, with near_list: the same bound for the objective;
-                            // a unit that cannot come within near_band of the running minimum
-                            // is passed over
+  int direct;               // COLLECT without a scan before it, BEST: ulist names the only units
+  uint32_t n_list_host;     // whose bound meets the limit (n_list_host of them).  COLLECT: every
+                            // candidate of theirs that is valid and within the loose limit is kept
+  const float *ulb_key;     // BEST, optional: the same bound for the objective; a unit that cannot
+                            // come within near_band of the running minimum is passed over
 };
 
 enum Counter { CNT_SURV = 0, CNT_REF = 1, CNT_FEAS = 2, CNT_GMIN = 3, CNT_TAU0 = 4, CNT_TAU1 = 5,
@@ -819,19 +826,17 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   }
 }
 
-// Records a scanned unit's minima and folds them into the global minimum (and, for the best
-// plan, the list of units near it).  One thread.
-__device__ __forceinline__ void unit_publish(const ScanArgs &a, uint32_t uidx, float ms, float ml) {
+// Folds a scanned unit's minima into the global minimum.  One thread.  Returns (best plan) the
+// threshold up to which the unit's candidates are kept, or -1 if it has none that near.
+__device__ __forceinline__ float unit_publish(const ScanArgs &a, float ms, float ml) {
   // keys are non-negative, so their bit patterns order like unsigned integers
   // (a stale read only costs a redundant atomic; most units lose and skip theirs)
   const uint32_t seen = __hip_atomic_load(&a.counters[CNT_GMIN], __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_AGENT);
   if (__float_as_uint(ms) < seen) atomicMin(&a.counters[CNT_GMIN], __float_as_uint(ms));
-  if (a.near_list && ml < kPosInf) {
-    // (a stale `seen` is larger than the true running minimum and only lengthens the list)
-    const float running = fminf(__uint_as_float(seen), ms);
-    if (ml <= running * a.near_band) a.near_list[atomicAdd(&a.counters[CNT_NLIST], 1u)] = uidx;
-  }
+  // (a stale `seen` is larger than the true running minimum: more is kept, nothing is lost)
+  const float tau = fminf(__uint_as_float(seen), ms) * a.near_band;
+  return ml < kPosInf && ml <= tau ? tau : -1.0f;
 }
 
 // LDS of a scan workgroup: the records of [3][ZG][MB] (segment, pool, mb) as two float4 arrays
@@ -850,10 +855,10 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   const unsigned long long t_begin = (MODE == MODE_SCAN && a.ucost) ? wall_clock64() : 0ull;
   const UnitRec u = pl.units[uidx];
   float tau = kPosInf, key_limit = kPosInf;
-  if (MODE == MODE_SCAN && (a.ulb_con || a.ulb_key)) {
+  if ((MODE == MODE_SCAN || MODE == MODE_BEST) && (a.ulb_con || a.ulb_key)) {
     bool dead = false;  // must come out the same in every wave of the workgroup
     if (HASB && a.ulb_con) dead = !(a.ulb_con[uidx] <= a.lim_l);
-    if (a.ulb_key && a.near_list) {
+    if (MODE == MODE_BEST && a.ulb_key) {
       // the running minimum changes while the workgroup reads it: one thread reads, all follow
       __shared__ uint32_t s_seen;
       if (threadIdx.x == 0)
@@ -863,7 +868,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
       dead = dead || a.ulb_key[uidx] > key_limit;
     }
     if (dead) {
-      if (threadIdx.x == 0) {
+      if (threadIdx.x == 0 && !(MODE == MODE_BEST && a.direct)) {
         a.umin_s[uidx] = kPosInf;
         a.umin_l[uidx] = kPosInf;
         if (a.unit_gen) a.unit_gen[uidx] = a.cur_gen;  // (not counted as evaluated: unit_seq stays)
@@ -903,7 +908,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   // or three segments is evaluated again whenever that table has changed since.
   const bool joint_changed = MIXED && MODE == MODE_SCAN && a.incremental && S >= 2 &&
                              pl.row_gen[0] > a.unit_gen[uidx];
-  const bool keep_bits = MODE == MODE_SCAN && a.ubits != nullptr;
+  const bool keep_bits = (MODE == MODE_SCAN || MODE == MODE_BEST) && a.ubits != nullptr;
   uint32_t *const ub = keep_bits ? a.ubits + (size_t)uidx * a.ubits_stride : nullptr;
   uint32_t any_here = 0;
   for (int i = t; i < S * ZG * MB; i += blockDim.x) {
@@ -958,12 +963,12 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   for (int w = 0; w < (int)(blockDim.x >> 6); ++w) any_all |= s_any[w];
   if (MODE == MODE_SCAN && a.incremental && !(any_all & 8u) && !joint_changed) {
     // every validity bit is what it was: the minima still hold (uniform over the workgroup)
-    if (t == 0) unit_publish(a, uidx, a.umin_s[uidx], a.umin_l[uidx]);
+    if (t == 0) unit_publish(a, a.umin_s[uidx], a.umin_l[uidx]);
     return;
   }
   any_all &= 7u;
   if (any_all != (1u << S) - 1u) {  // uniform over the workgroup
-    if (MODE != MODE_COLLECT && t == 0) {
+    if (MODE != MODE_COLLECT && t == 0 && !(MODE == MODE_BEST && a.direct)) {
       a.umin_s[uidx] = kPosInf;
       a.umin_l[uidx] = kPosInf;
       if (a.unit_gen) {
@@ -981,9 +986,13 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   // fast digit of the share a part keeps the same chunks ((c / waves) mod n_parts == part)
   // whatever n_sub is: the collect pass must visit exactly what the scan saw.
   const int share = sub * (int)u.n_parts + (int)u.part, n_shares = (int)u.n_parts * (int)n_sub;
-  if (S == 1) unit_body<1, MODE, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
-  else if (S == 2) unit_body<2, MODE, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
-  else unit_body<3, MODE, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
+  auto walk = [&](auto mode) {
+    constexpr int M = decltype(mode)::value;
+    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
+    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
+    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
+  };
+  walk(std::integral_constant<int, MODE>());
 
   if (MODE != MODE_COLLECT) {
     if (!HASB && MODE != MODE_BOUNDS) ml = ms;
@@ -996,24 +1005,39 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
         ms = fminf(ms, red[0][w]);
         ml = fminf(ml, red[1][w]);
       }
-      a.umin_s[uidx] = ms;
-      a.umin_l[uidx] = ml;
-      if (a.unit_gen) {
-        a.unit_gen[uidx] = a.cur_gen;
-        a.unit_seq[uidx] = a.call_seq;  // evaluated by this call
+      float keep = -1.0f;
+      if (MODE != MODE_BOUNDS) keep = unit_publish(a, ms, ml);
+      if (MODE == MODE_BEST) s_min[0] = __float_as_uint(keep);
+      if (!(MODE == MODE_BEST && a.direct)) {  // (several workgroups share a listed unit)
+        a.umin_s[uidx] = ms;
+        a.umin_l[uidx] = ml;
+        if (a.unit_gen) {
+          a.unit_gen[uidx] = a.cur_gen;
+          a.unit_seq[uidx] = a.call_seq;  // evaluated by this call
+        }
       }
-      if (MODE == MODE_SCAN) unit_publish(a, uidx, ms, ml);
       if (a.ucost) a.ucost[uidx] = (float)(wall_clock64() - t_begin);
     }
+  }
+  if (MODE == MODE_BEST) {
+    // The few units near the minimum are walked once more, their records still in LDS, instead of
+    // being listed for a kernel of their own (8 to 10 us of a query of 35 to 55): with the threshold
+    // known nearly all of it falls to the bounds.
+    __syncthreads();
+    tau = __uint_as_float(s_min[0]);
+    if (tau >= 0.0f) walk(std::integral_constant<int, MODE_COLLECT>());  // uniform
   }
 }
 
 // SCAN: one workgroup per unit.  COLLECT: n_sub workgroups share a unit; with a unit list
-// the grid strides over the list instead of covering every unit.
+// the grid strides over the list instead of covering every unit.  BEST: as SCAN, or n_sub workgroups
+// for each of a few listed units.
 template <int MODE, int OBJ, bool HASB, bool MIXED>
 __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a) {
   extern __shared__ uint4 lds_raw[];
-  if (MODE != MODE_COLLECT) {
+  if (MODE == MODE_BEST && a.direct) {
+    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, a.ulist[blockIdx.x / a.n_sub], (int)(blockIdx.x % a.n_sub), a.n_sub, lds_raw);
+  } else if (MODE != MODE_COLLECT) {
     unit_work<MODE, OBJ, HASB, MIXED>(pl, a, blockIdx.x, 0, 1u, lds_raw);
   } else if (!a.ulist) {
     unit_work<MODE, OBJ, HASB, MIXED>(pl, a, blockIdx.x / a.n_sub, (int)(blockIdx.x % a.n_sub), a.n_sub,
@@ -1448,46 +1472,98 @@ __device__ __forceinline__ void publish(ResultHeader *hdr, uint32_t seq) {
   __hip_atomic_store(&hdr->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Best plan: minimum fp64 key over valid candidates, then the lowest index within the
-// tie tolerance of it.  One workgroup; results go to host-mapped memory.
-__global__ __launch_bounds__(1024) void k_pick_best(const RefRec *ref, uint32_t ref_cap,
-                                                    const uint32_t *counters,
-                                                    uint32_t *next_counters, int objective,
-                                                    ResultHeader *hdr, RefRec *out, uint32_t seq) {
-  __shared__ double s_key[16];
-  __shared__ unsigned long long s_idx[16];
-  __shared__ uint32_t s_pos[16];
+// Best plan: fp64 re-evaluation of the survivors within the tie band of the smallest fp32 key, one
+// wave each, then the minimum fp64 key over the valid ones and the lowest index within the tie
+// tolerance of it; results go to host-mapped memory.
+//
+// There are rarely more than a few survivors, and what this costs is its chain of trips to memory
+// (count and records, shape, stages), so up to kBestAlone of them are one workgroup's: it holds the
+// results in LDS and picks at once, where a kernel of its own for the pick started with a cold L2 and
+// took 4 to 5 us more.  With more, every workgroup takes its share and the one that finishes last
+// picks.
+constexpr int kBestWaves = 8;
+constexpr uint32_t kBestAlone = 64;  // (a lane each in the selection and the pick)
+constexpr unsigned kBestWorkgroups = 64;
+
+__global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, RefineArgs a, uint32_t *next_counters,
+                                                                ResultHeader *hdr, RefRec *out, uint32_t seq) {
+  __shared__ RefineLds lds[kBestWaves];
+  __shared__ RefRec s_ref[kBestAlone];
+  __shared__ double s_key[kBestWaves];
+  __shared__ unsigned long long s_idx[kBestWaves];
+  __shared__ uint32_t s_pos[kBestWaves], s_last;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  // a thread's first record is requested together with the counters (the buffer holds
-  // ref_cap records, so the address is valid whatever the count turns out to be)
-  RefRec mine{};
-  if ((uint32_t)t < ref_cap) mine = ref[t];
-  const uint32_t n_ref = counters[CNT_REF], n_surv = counters[CNT_SURV],
-                 n_feas = counters[CNT_FEAS], gmin = counters[CNT_GMIN];
-  const uint32_t n = min(n_ref, ref_cap);
+  // a lane's survivor is requested together with the counters (the buffer holds surv_cap records,
+  // so the address is valid whatever the count turns out to be)
+  SurvRec mine{};
+  if ((uint32_t)lane < a.surv_cap) mine = a.surv[lane];
+  const uint32_t n_surv = a.counters[CNT_SURV], gmin = a.counters[CNT_GMIN];
+  const uint32_t n = min(n_surv, a.surv_cap);
+  const float tau = __uint_as_float(gmin) * a.band;
+  const bool alone = n <= kBestAlone;  // uniform over the grid
+  if (alone && blockIdx.x != 0) return;
+  auto evaluate = [&](uint64_t idx, uint32_t shape) {
+    Cand c;
+    decode_in_shape(pl, shape, idx, c);
+    RefRec r;
+    r.idx = idx;
+    r.pad = 0;
+    eval_exact_wave(pl, c, a.objective, a.has_bound, a.bound, lds[wv], r.T, r.C, r.mem, r.mask);
+    return r;
+  };
+  auto key_of = [&](const RefRec &r) { return r.mask != 0 ? __builtin_huge_val() : (a.objective == 0 ? r.T : r.C); };
+  uint32_t n_ref, n_feas = 0;
+  if (alone) {
+    const unsigned long long near = __builtin_amdgcn_ballot_w64((uint32_t)lane < n && mine.key_loose <= tau);
+    const uint32_t rank = (uint32_t)__popcll(near & ((1ull << lane) - 1ull));
+    n_ref = (uint32_t)__popcll(near);
+    for (uint32_t w = wv; w < n_ref; w += kBestWaves) {  // uniform over the wave
+      const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(((near >> lane) & 1ull) != 0 && rank == w));
+      const RefRec r = evaluate(__shfl((unsigned long long)mine.idx, from), (uint32_t)__shfl((int)mine.shape, from));
+      if (lane == 0) s_ref[w] = r;
+    }
+    __syncthreads();
+  } else {
+    for (uint32_t i = blockIdx.x * kBestWaves + wv; i < n; i += gridDim.x * kBestWaves) {
+      const SurvRec sv = a.surv[i];
+      if (!(sv.key_loose <= tau)) continue;
+      const RefRec r = evaluate(sv.idx, sv.shape);
+      if (lane == 0) {
+        const uint32_t slot = atomicAdd(&a.counters[CNT_REF], 1u);
+        if (slot < a.ref_cap) {  // (what does not fit is counted only: the host reports it)
+          a.ref[slot] = r;
+          if (r.mask == 0) atomicAdd(&a.counters[CNT_FEAS], 1u);
+        }
+      }
+    }
+    __threadfence();  // visible to the other workgroups before this one counts as done
+    __syncthreads();
+    if (t == 0) s_last = atomicAdd(&a.counters[CNT_DONE], 1u) == gridDim.x - 1 ? 1u : 0u;
+    __syncthreads();
+    if (!s_last) return;  // uniform
+    __threadfence();      // the last workgroup: see what the others stored
+    n_ref = __hip_atomic_load(&a.counters[CNT_REF], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    n_feas = __hip_atomic_load(&a.counters[CNT_FEAS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   if (t < CNT_COUNT) next_counters[t] = counter_reset_value(t);  // for the next call
+  const RefRec *const ref = alone ? s_ref : a.ref;
+  const uint32_t stored = alone ? n_ref : min(n_ref, a.ref_cap);
+  if (alone) {
+    n_feas = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((uint32_t)lane < stored && s_ref[lane].mask == 0));
+  }
   double best = __builtin_huge_val();
-  if ((uint32_t)t < n && mine.mask == 0) best = objective == 0 ? mine.T : mine.C;
-  for (uint32_t i = t + blockDim.x; i < n; i += blockDim.x)
-    if (ref[i].mask == 0) best = fmin(best, objective == 0 ? ref[i].T : ref[i].C);
+  for (uint32_t i = t; i < stored; i += kBestWaves * 64) best = fmin(best, key_of(ref[i]));
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) best = fmin(best, __shfl_xor(best, off));
   if (lane == 0) s_key[wv] = best;
   __syncthreads();
-  best = s_key[0];
 #pragma unroll
-  for (int w = 1; w < 16; ++w) best = fmin(best, s_key[w]);
+  for (int w = 0; w < kBestWaves; ++w) best = fmin(best, s_key[w]);
   const double limit = best * (1.0 + kTieTol);
   unsigned long long bi = ~0ull;
   uint32_t bp = 0;
-  if ((uint32_t)t < n && mine.mask == 0 && (objective == 0 ? mine.T : mine.C) <= limit) {
-    bi = mine.idx;
-    bp = t;
-  }
-  for (uint32_t i = t + blockDim.x; i < n; i += blockDim.x) {
-    const double key = objective == 0 ? ref[i].T : ref[i].C;
-    if (ref[i].mask == 0 && key <= limit && ref[i].idx < bi) { bi = ref[i].idx; bp = i; }
-  }
+  for (uint32_t i = t; i < stored; i += kBestWaves * 64)
+    if (ref[i].mask == 0 && key_of(ref[i]) <= limit && ref[i].idx < bi) { bi = ref[i].idx; bp = i; }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const unsigned long long oi = __shfl_xor(bi, off);
@@ -1497,13 +1573,10 @@ __global__ __launch_bounds__(1024) void k_pick_best(const RefRec *ref, uint32_t 
   if (lane == 0) { s_idx[wv] = bi; s_pos[wv] = bp; }
   __syncthreads();
   if (t == 0) {
-    for (int w = 1; w < 16; ++w)
+    for (int w = 1; w < kBestWaves; ++w)
       if (s_idx[w] < bi) { bi = s_idx[w]; bp = s_pos[w]; }
     const bool found = bi != ~0ull;
-    if (found) {
-      if (bp == 0) out[0] = mine;  // (thread 0 holds record 0)
-      else out[0] = ref[bp];
-    }
+    if (found) out[0] = ref[bp];
     hdr->n_found = found ? 1u : 0u;
     hdr->surv_count = n_surv;
     hdr->ref_count = n_ref;
