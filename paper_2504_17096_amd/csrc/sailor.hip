@@ -32,6 +32,7 @@ constexpr uint32_t kListUnits = 256;     // and the units it visits per round
 // keeps every valid candidate of those units (see run_selection_impl)
 constexpr uint32_t kDirectUnits = 128;
 constexpr uint32_t kDirectSub = 16;             // workgroups that share one of them
+constexpr uint32_t kFreshWorkgroups = 16;       // that bring the quota table up to date beside a call's first kernel
 constexpr uint32_t kDirectManySurvivors = 8192;  // more than the select kernel holds in registers
                                                 // (or than half the survivor buffer): the query
                                                 // goes back to the scan from then on
@@ -576,6 +577,12 @@ unsigned quota_grid(const DevPlan &d) {
   return (unsigned)std::min<size_t>(1024, (n + 255) / 256);
 }
 
+AvailTable avail_table(const sailor_plan *pl) {
+  AvailTable t{};
+  std::memcpy(t.v, pl->h_avail, pl->dev.ZGr * sizeof(int32_t));
+  return t;
+}
+
 // Brings a changed availability table to the device on the caller's stream and rebuilds
 // the quota table from it.
 sailor_status refresh_avail(sailor_plan *pl, hipStream_t st) {
@@ -584,10 +591,8 @@ sailor_status refresh_avail(sailor_plan *pl, hipStream_t st) {
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();  // (the launch reports it)
   const bool mapped = capturing != hipStreamCaptureStatusNone;  // replays read the table of their time
-  AvailTable table;
-  std::memcpy(table.v, pl->h_avail, pl->dev.ZGr * sizeof(int32_t));
-  k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, table, mapped ? pl->h_avail_dev : nullptr, pl->d_avail,
-                                                     pl->avail_gen);
+  k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, avail_table(pl), mapped ? pl->h_avail_dev : nullptr,
+                                                     pl->d_avail, pl->avail_gen);
   if (mapped) {
     HIP_TRY(hipEventRecord(pl->ev_upload, st));
     pl->upload_pending = true;
@@ -607,12 +612,13 @@ void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEven
 template <int MODE, bool MIXED>
 void launch_units_m(sailor_plan *pl, sailor_objective obj, int has_bound, const ScanArgs &a,
                     dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const AvailTable avail = avail_table(pl);
   if (obj == SAILOR_MAX_THROUGHPUT) {
-    if (has_bound) launch(k_units<MODE, 0, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a);
-    else launch(k_units<MODE, 0, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a);
+    if (has_bound) launch(k_units<MODE, 0, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
+    else launch(k_units<MODE, 0, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
   } else {
-    if (has_bound) launch(k_units<MODE, 1, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a);
-    else launch(k_units<MODE, 1, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a);
+    if (has_bound) launch(k_units<MODE, 1, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
+    else launch(k_units<MODE, 1, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
   }
 }
 
@@ -620,10 +626,10 @@ template <int MODE>
 void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const ScanArgs &a,
                   hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const unsigned n_units = (unsigned)pl->units.size();
-  const dim3 grid(a.direct              ? a.n_list_host * a.n_sub
-                  : MODE != MODE_COLLECT ? n_units
-                  : a.ulist              ? std::min(n_units, kListUnits) * a.n_sub
-                                         : n_units * a.n_sub),
+  const dim3 grid((a.direct               ? a.n_list_host * a.n_sub
+                   : MODE != MODE_COLLECT ? n_units
+                   : a.ulist              ? std::min(n_units, kListUnits) * a.n_sub
+                                          : n_units * a.n_sub) + a.fresh),
       block(pl->unit_threads);
   const size_t lds = pl->lds_bytes;
   if (pl->dev.mixed) launch_units_m<MODE, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
@@ -633,8 +639,8 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
 // One workgroup per unit, the availability ignored (plan creation).
 void launch_bounds(sailor_plan *pl, const ScanArgs &a) {
   const dim3 grid((unsigned)pl->dev.n_units), block(pl->unit_threads);
-  if (pl->dev.mixed) k_units<MODE_BOUNDS, 0, false, true><<<grid, block, pl->lds_bytes>>>(pl->dev, a);
-  else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a);
+  if (pl->dev.mixed) k_units<MODE_BOUNDS, 0, false, true><<<grid, block, pl->lds_bytes>>>(pl->dev, a, AvailTable{});
+  else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a, AvailTable{});
 }
 
 struct SearchLaunch {
@@ -679,8 +685,15 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   sailor_status rc = constraint_limits(obj, con, &has_bound, &bound, &sa.lim_s, &sa.lim_l);
   if (rc != SAILOR_OK) return rc;
   HIP_TRY(hipSetDevice(pl->device));
-  rc = refresh_avail(pl, st);
-  if (rc != SAILOR_OK) return rc;
+  if (pl->dev.mixed) {
+    rc = refresh_avail(pl, st);
+    if (rc != SAILOR_OK) return rc;
+  } else if (pl->avail_dirty) {  // the call's first launch brings it along (it waits for its result: never captured)
+    pl->avail_gen += 1;
+    pl->avail_dirty = false;
+    sa.fresh = kFreshWorkgroups;
+    sa.avail_copy = pl->d_avail;
+  }
   if (pl->counters_dirty) {
     k_init_counters<<<1, 64, 0, st>>>(pl->counters, 2 * CNT_COUNT);
     pl->counters_dirty = false;
@@ -725,6 +738,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     if (!kept)
       launch_units<MODE_COLLECT>(pl, obj, has_bound, sa, st, sa.direct && t_scan ? pl->ev[3] : nullptr,
                                  sa.direct && t_scan ? pl->ev[1] : nullptr);
+    sa.fresh = 0;
     RefineArgs ra{};
     ra.surv = pl->surv;
     ra.surv_cap = pl->surv_cap;
@@ -825,6 +839,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   sa.direct = 0;
   launch_units<MODE_SCAN>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr,
                           t_scan ? pl->ev[1] : nullptr);
+  sa.fresh = 0;
   // an upper bound of the k-th smallest key: the k-th smallest unit minimum (the best plan's: the
   // smallest, and its tie band).  The same kernel lists the units whose loose minimum lies under it.
   sa.band = best ? (float)(1.0 + kTieTol) + 3.0f * kEvalEps : 1.0f + 3.0f * kEvalEps;
@@ -1108,12 +1123,11 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   pl->d_out = reinterpret_cast<RefRec *>(static_cast<char *>(d_res) + sizeof(ResultHeader));
   pl->h_avail = reinterpret_cast<int32_t *>(static_cast<char *>(pl->h_result) + res_bytes);
   pl->h_avail_dev = reinterpret_cast<const int32_t *>(static_cast<char *>(d_res) + res_bytes);
+  std::memcpy(pl->h_avail, p->avail, ZGr * sizeof(int32_t));
   for (hipEvent_t &e : pl->ev) CREATE_TRY(hipEventCreate(&e));
 
   k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
-  AvailTable table;
-  std::memcpy(table.v, p->avail, ZGr * sizeof(int32_t));
-  k_quota_table<<<quota_grid(d), 256>>>(d, table, nullptr, pl->d_avail, 0u);
+  k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(pl), nullptr, pl->d_avail, 0u);
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_direct_tables<<<1, 256>>>(d);

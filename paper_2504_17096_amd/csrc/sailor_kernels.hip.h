@@ -427,6 +427,18 @@ __device__ __forceinline__ void acc_finish(const Acc &p, const LaneC &lc, float 
 // again.  mapped: the same in host-mapped memory instead, for a call under stream capture (a replay
 // then reads what the host holds at the time).  Left in avail_copy (= pl.avail) for later kernels.
 struct AvailTable { int32_t v[kMaxPools]; };
+
+// bit d: dpv[d] replicas of w >= 1 GPUs fit a pool that has `avail` (the degrees ascend)
+__device__ __forceinline__ uint32_t quota_bits(const DevPlan &pl, int32_t avail, int w) {
+  const int32_t most = (int32_t)((uint32_t)avail / (uint32_t)w);
+  uint32_t bits = 0;
+  for (int d = 0; d < pl.DP; ++d) bits |= pl.dpv[d] <= most ? 1u << d : 0u;
+  return bits;
+}
+
+__device__ __forceinline__ void quota_table(const DevPlan &pl, const int32_t *avail, uint32_t gen, uint32_t block,
+                                            uint32_t n_blocks);
+
 __global__ void k_quota_table(DevPlan pl, AvailTable table, const int32_t *mapped, int32_t *avail_copy, uint32_t gen) {
   __shared__ int32_t avail[kMaxPools];
   for (int r = threadIdx.x; r < pl.ZGr; r += blockDim.x) {
@@ -434,8 +446,14 @@ __global__ void k_quota_table(DevPlan pl, AvailTable table, const int32_t *mappe
     if (blockIdx.x == 0) avail_copy[r] = avail[r];
   }
   __syncthreads();
+  quota_table(pl, avail, gen, blockIdx.x, gridDim.x);
+}
+
+// The share of workgroup `block` of n_blocks.
+__device__ __forceinline__ void quota_table(const DevPlan &pl, const int32_t *avail, uint32_t gen, uint32_t block,
+                                            uint32_t n_blocks) {
   const int n = (pl.W_max + 1) * pl.ZG;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+  for (int i = block * blockDim.x + threadIdx.x; i < n; i += n_blocks * blockDim.x) {
     const int p = i % pl.ZG, w = i / pl.ZG;
     const int x = pl.xt[p % pl.GX], ga = x & 255, gb = x >> 8, z = p / pl.GX;
     const int64_t avail_a = avail[z * pl.G + ga], avail_b = avail[z * pl.G + gb];
@@ -450,7 +468,7 @@ __global__ void k_quota_table(DevPlan pl, AvailTable table, const int32_t *mappe
   }
   if (!pl.mixed) return;
   const int nh = (2 * pl.W_max + 1) * pl.ZGr;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nh; i += gridDim.x * blockDim.x) {
+  for (int i = block * blockDim.x + threadIdx.x; i < nh; i += n_blocks * blockDim.x) {
     const int r = i % pl.ZGr, x = i / pl.ZGr;
     const int64_t avail2 = 2 * (int64_t)avail[r];
     uint32_t bits = 0;
@@ -538,6 +556,9 @@ struct ScanArgs {
   int direct;               // COLLECT without a scan before it, BEST: ulist names the only units
   uint32_t n_list_host;     // whose bound meets the limit (n_list_host of them).  COLLECT: every
                             // candidate of theirs that is valid and within the loose limit is kept
+  uint32_t fresh;           // the availability is new and travels with this launch (plain pools only): units
+                            // take their quotas from it, and the `fresh` workgroups behind theirs
+  int32_t *avail_copy;      // bring the quota table and the device's copy up to date
   const float *ulb_key;     // BEST, optional: the same bound for the objective; a unit that cannot
                             // come within near_band of the running minimum is passed over
 };
@@ -850,8 +871,8 @@ __host__ __device__ inline size_t unit_lds_records(int ZG, int MB) {
 // needs comes from the unit record and tables that do not depend on one another, so all of
 // its global loads are in flight together and one barrier ends it.
 template <int MODE, int OBJ, bool HASB, bool MIXED>
-__device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, uint32_t uidx,
-                                          int sub, uint32_t n_sub, uint4 *lds_raw) {
+__device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, const AvailTable &avail,
+                                          uint32_t uidx, int sub, uint32_t n_sub, uint4 *lds_raw) {
   const unsigned long long t_begin = (MODE == MODE_SCAN && a.ucost) ? wall_clock64() : 0ull;
   const UnitRec u = pl.units[uidx];
   float tau = kPosInf, key_limit = kPosInf;
@@ -920,7 +941,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     const uint32_t sl = (u.shape * (uint32_t)pl.TP + (uint32_t)k) * 3u + (uint32_t)seg;
     const uint32_t gi = (sl * (uint32_t)G + (uint32_t)g) * (uint32_t)MB + mb;
     const float4 ta = pl.ta[gi];
-    uint32_t q = a.ignore_quota ? 0xFFFFFFFFu : pl.qw[w * ZG + p];
+    uint32_t q = 0xFFFFFFFFu;
+    if (!MIXED && a.fresh) q = quota_bits(pl, avail.v[p], w);
+    else if (!a.ignore_quota) q = pl.qw[w * ZG + p];
     if ((pl.h1m[p] >> k) & 1u) q = 0;  // H1: tensor parallelism stays inside a node
     const uint32_t bits = pl.memok[gi] & q & pl.divis[mb];
     rec_store(rec_lo, rec_hi, rbits, i,
@@ -937,7 +960,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   }
   if (S == 3 && !MIXED)
     for (int p = t; p < ZG; p += blockDim.x) {
-      const uint32_t q = a.ignore_quota ? 0xFFFFFFFFu : pl.qw[(w0 + w2) * ZG + p];
+      uint32_t q = 0xFFFFFFFFu;
+      if (a.fresh) q = quota_bits(pl, avail.v[p], w0 + w2);
+      else if (!a.ignore_quota) q = pl.qw[(w0 + w2) * ZG + p];
       q13[p] = q;
       if (keep_bits) {
         uint32_t *const uq = ub + a.ubits_stride - ZG;  // behind the records' bits
@@ -1032,22 +1057,33 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
 // SCAN: one workgroup per unit.  COLLECT: n_sub workgroups share a unit; with a unit list
 // the grid strides over the list instead of covering every unit.  BEST: as SCAN, or n_sub workgroups
 // for each of a few listed units.
+//
+// A new availability rides on the call's first launch (ScanArgs::fresh): a quota table made by a kernel
+// of its own in front of it cost 6 of the 44 us that a new table and its fastest plan took on 6.8e6
+// candidates.  (Not with pairs of types, whose joint quotas are looked up per plan.)
 template <int MODE, int OBJ, bool HASB, bool MIXED>
-__global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a) {
+__global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a, AvailTable avail) {
   extern __shared__ uint4 lds_raw[];
+  const uint32_t n_wgs = gridDim.x - (MIXED ? 0u : a.fresh);
+  if (!MIXED && blockIdx.x >= n_wgs) {
+    if (blockIdx.x == n_wgs)
+      for (int r = threadIdx.x; r < pl.ZGr; r += blockDim.x) a.avail_copy[r] = avail.v[r];
+    quota_table(pl, avail.v, 0u, blockIdx.x - n_wgs, a.fresh);
+    return;
+  }
   if (MODE == MODE_BEST && a.direct) {
-    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, a.ulist[blockIdx.x / a.n_sub], (int)(blockIdx.x % a.n_sub), a.n_sub, lds_raw);
+    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist[blockIdx.x / a.n_sub], (int)(blockIdx.x % a.n_sub), a.n_sub, lds_raw);
   } else if (MODE != MODE_COLLECT) {
-    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, blockIdx.x, 0, 1u, lds_raw);
+    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, blockIdx.x, 0, 1u, lds_raw);
   } else if (!a.ulist) {
-    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, blockIdx.x / a.n_sub, (int)(blockIdx.x % a.n_sub), a.n_sub,
+    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, blockIdx.x / a.n_sub, (int)(blockIdx.x % a.n_sub), a.n_sub,
                                lds_raw);
   } else {
     const uint32_t n_list = a.direct ? a.n_list_host : a.counters[CNT_NLIST];
-    const uint32_t per_round = gridDim.x / a.n_sub;
+    const uint32_t per_round = n_wgs / a.n_sub;
     const int sub = (int)(blockIdx.x % a.n_sub);
     for (uint32_t e = blockIdx.x / a.n_sub; e < n_list; e += per_round) {  // uniform
-      unit_work<MODE, OBJ, HASB, MIXED>(pl, a, a.ulist[e], sub, a.n_sub, lds_raw);
+      unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist[e], sub, a.n_sub, lds_raw);
       __syncthreads();  // the staging area is reused
     }
   }
