@@ -1053,6 +1053,11 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.input(&d.st_n, st_n.data(), RS);
   slab.input(&d.st_first, st_first.data(), RS);
   slab.input(&d.shapes, pl->shapes.data(), NS);
+  std::vector<uint32_t> shape_n;
+  shape_n.reserve(NS);
+  for (const ShapeRec &sh : pl->shapes)
+    shape_n.push_back((uint32_t)((sh.n[0] - 1) & 255) | (uint32_t)((sh.n[1] - 1) & 255) << 8 | (uint32_t)((sh.n[2] - 1) & 255) << 16);
+  slab.input(&d.shape_n, shape_n.data(), NS);
   slab.input(&d.blocks, pl->blocks.data(), pl->blocks.size());
   // per-unit tables: one entry per unit as laid out (units dropped later leave room for the
   // parts of units that are cut); sailor_set_scan_unit_parts(n) cuts every unit into n parts
@@ -1095,6 +1100,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&d.need, slots * MB * DP);
   slab.table(&d.syncz, slots * Z);
   slab.table(&d.upd, slots * GX);
+  slab.table(&d.su, slots * ZG);
   // selection scratch (umin_l lies behind umin_s: creation reads both back in one copy)
   slab.table(&pl->umin_s, 2 * unit_cap);
   slab.table(&pl->counters, (size_t)2 * CNT_COUNT);
@@ -1132,7 +1138,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_direct_tables<<<1, 256>>>(d);
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
-  k_shape_agg<<<(unsigned)NS, kShapeAggThreads>>>(d);
+  k_shape_agg<<<(unsigned)NS, kShapeAggThreads, (size_t)3 * TP * (Z + GX) * sizeof(float)>>>(d);
   CREATE_TRY(hipGetLastError());
   {
     // Two passes over the space order the scan.  The first ignores the availability and records,

@@ -144,6 +144,7 @@ struct DevPlan {
   double *st_u;                // [rs][G][TP] sum of update times
   // candidate space
   const ShapeRec *shapes;
+  const uint32_t *shape_n;     // [n_shapes] a shape's stages per segment once more, less one, a byte each
   const BlockRec *blocks;
   const UnitRec *units;
   // per-shape segment aggregates, [shape][TP][3]...  (a pair of types: every stage at the
@@ -153,6 +154,8 @@ struct DevPlan {
   uint64_t *need;              // [..][MB][DP] max over stages of model + activation bytes
   float *syncz;                // [..][Z] slowest stage: gradient bytes / intra-zone bandwidth
   float *upd;                  // [..][GX] slowest stage update
+  float2 *su;                  // [..][ZG] both by pool, for lane-dependent pools (the scan, which reads a segment
+                               // as a whole, is 3 % slower with these: 2 MB beside an L2 of 4)
 };
 
 }  // namespace sailor

@@ -210,6 +210,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // shape shorten them.
 constexpr int kShapeAggThreads = 512;
 __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
+  extern __shared__ float agg_lds[];  // [TP][3][Z], [TP][3][GX]
   const uint32_t shp = blockIdx.x;
   const ShapeRec sh = pl.shapes[shp];
   const int G = pl.G, GX = pl.GX, MB = pl.MB, TP = pl.TP, DP = pl.DP, P = sh.P;
@@ -234,6 +235,9 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
     }
     pl.need[(agg_slot(pl, shp, k, seg) * MB + m) * DP + d] = mx;
   }
+  // slowest all-reduce per zone and slowest update per type, then both by pool
+  const size_t slot0 = agg_slot(pl, shp, 0, 0);
+  float *const syncz = agg_lds, *const upd = agg_lds + TP * 3 * pl.Z;
   for (int it = t; it < TP * 3 * pl.Z; it += nt) {
     int z = it % pl.Z, seg = (it / pl.Z) % 3, k = it / (pl.Z * 3);
     double mx = 0.0;  // seconds of the slowest stage's gradient buffer over the zone's link
@@ -251,7 +255,8 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
         mx = mx / pl.bw[z * pl.Z + z];
       }
     }
-    pl.syncz[agg_slot(pl, shp, k, seg) * pl.Z + z] = (float)mx;
+    syncz[it] = (float)mx;
+    pl.syncz[slot0 * pl.Z + it] = (float)mx;
   }
   for (int it = t; it < TP * 3 * GX; it += nt) {
     int g = it % GX, seg = (it / GX) % 3, k = it / (GX * 3);
@@ -264,7 +269,8 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
         mx = fmax(mx, pl.st_u[((size_t)(sh.row_stage + i) * G + gb) * TP + k]);
       }
     }
-    pl.upd[agg_slot(pl, shp, k, seg) * GX + g] = (float)mx;
+    upd[it] = (float)mx;
+    pl.upd[slot0 * GX + it] = (float)mx;
   }
   for (int it = t; it < TP * 3 * GX * MB; it += nt) {
     int m = it % MB, g = (it / MB) % GX, seg = (it / (MB * GX)) % 3, k = it / (MB * GX * 3);
@@ -291,6 +297,10 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
     pl.ta[(agg_slot(pl, shp, k, seg) * GX + g) * MB + m] = v;
   }
   __syncthreads();
+  for (int it = t; it < TP * 3 * pl.ZG; it += nt) {
+    const int p = it % pl.ZG, ks = it / pl.ZG, seg = ks % 3, k = ks / 3, z = p / GX, g = p - z * GX;
+    pl.su[(slot0 + k * 3 + seg) * pl.ZG + p] = make_float2(syncz[ks * pl.Z + z], upd[ks * GX + g]);
+  }
   __threadfence();
   // memok bit d: largest worker of the segment fits the type's memory
   for (int it = t; it < TP * 3 * GX * MB; it += nt) {
@@ -1965,7 +1975,16 @@ struct EvalArgs {
 
 // The small tables of the evaluator of index lists: laid out once per plan in memory
 // (k_direct_tables), copied to LDS by every workgroup in one go, the availability behind them.
+struct DirectBlock {          // a block of the index space (BlockRec) as an index is decoded with it
+  uint64_t off;
+  double size, inv_size;      // candidates per shape, and 1 / that
+  uint32_t first_shape, s;
+};
+static_assert(sizeof(DirectBlock) == 32, "whole 8-byte words");
+constexpr int kDirectShapes = 2048;  // shapes whose stages fit LDS (8 KB)
+
 struct DirectTables {
+  DirectBlock *blocks;        // [n_blocks]
   uint64_t *cap, *res;        // [G]
   float *ts;                  // [MB][Z][Z] transfer seconds
   float *egs;                 // [Z][Z]
@@ -1977,22 +1996,24 @@ struct DirectTables {
   int32_t *dp, *tp;           // [DP], [TP] the lists' values
   int32_t *node;              // [G]
   uint32_t *xt;               // [GX]
-  int32_t *avail;             // [ZGr]
+  uint32_t *n;                // [n_shapes] stages - 1 per segment, a byte each (kDirectShapes of them at most)
+  uint32_t *room;             // [DP][ZGr] half-GPUs per replica that a real pool has room for (not part of the copy)
 };
 
 __host__ __device__ inline uint32_t direct_copy_words(const DevPlan &pl) {  // 4-byte words laid out in memory
-  return (uint32_t)(4 * pl.G + pl.MB * pl.Z * pl.Z + pl.Z * pl.Z + 2 * pl.GX + pl.MB + 3 * pl.DP +
-                    2 * pl.MB * pl.DP + pl.TP + pl.G);
+  return (uint32_t)(8 * pl.n_blocks + 4 * pl.G + pl.MB * pl.Z * pl.Z + pl.Z * pl.Z + 2 * pl.GX + pl.MB + 3 * pl.DP +
+                    2 * pl.MB * pl.DP + pl.TP + pl.G + (pl.n_shapes <= kDirectShapes ? pl.n_shapes : 0));
 }
-inline size_t direct_lds_bytes(const DevPlan &pl) {  // (13 KB at the limits of a problem)
-  return ((size_t)direct_copy_words(pl) + pl.ZGr) * sizeof(uint32_t);
+inline size_t direct_lds_bytes(const DevPlan &pl) {  // (57 KB at the limits of a problem)
+  return ((size_t)direct_copy_words(pl) + (size_t)pl.DP * pl.ZGr) * sizeof(uint32_t);
 }
 
 __device__ __forceinline__ DirectTables direct_tables_at(const DevPlan &pl, uint32_t *at) {
   DirectTables T;
-  T.cap = reinterpret_cast<uint64_t *>(at);
+  T.blocks = reinterpret_cast<DirectBlock *>(at);
+  T.cap = reinterpret_cast<uint64_t *>(T.blocks + pl.n_blocks);
   T.res = T.cap + pl.G;
-  T.ts = reinterpret_cast<float *>(at + 4 * pl.G);
+  T.ts = reinterpret_cast<float *>(T.res + pl.G);
   T.egs = T.ts + pl.MB * pl.Z * pl.Z;
   T.price = T.egs + pl.Z * pl.Z;
   T.xb = T.price + pl.GX;
@@ -2004,7 +2025,8 @@ __device__ __forceinline__ DirectTables direct_tables_at(const DevPlan &pl, uint
   T.tp = T.dp + pl.DP;
   T.node = T.tp + pl.TP;
   T.xt = reinterpret_cast<uint32_t *>(T.node + pl.G);
-  T.avail = reinterpret_cast<int32_t *>(T.xt + pl.GX);
+  T.n = T.xt + pl.GX;
+  T.room = T.n + (pl.n_shapes <= kDirectShapes ? pl.n_shapes : 0);
   return T;
 }
 
@@ -2012,6 +2034,13 @@ __device__ __forceinline__ DirectTables direct_tables_at(const DevPlan &pl, uint
 __global__ void k_direct_tables(DevPlan pl) {
   const DirectTables T = direct_tables_at(pl, pl.direct_tables);
   const int t = threadIdx.x, nt = blockDim.x;
+  for (int i = t; i < pl.n_blocks; i += nt) {
+    const BlockRec b = pl.blocks[i];
+    DirectBlock o;
+    o.off = b.off; o.size = (double)b.shape_size; o.inv_size = 1.0 / (double)b.shape_size;
+    o.first_shape = b.first_shape; o.s = b.s;
+    T.blocks[i] = o;
+  }
   for (int i = t; i < pl.G; i += nt) { T.cap[i] = pl.cap[i]; T.res[i] = pl.res[i]; T.node[i] = pl.node[i]; }
   for (int i = t; i < pl.MB * pl.Z * pl.Z; i += nt) T.ts[i] = pl.tsec_f[i];
   for (int i = t; i < pl.Z * pl.Z; i += nt) T.egs[i] = pl.egs_f[i];
@@ -2020,88 +2049,36 @@ __global__ void k_direct_tables(DevPlan pl) {
   for (int i = t; i < pl.DP; i += nt) { T.cd[i] = pl.cd_f[i]; T.dph[i] = pl.dph_f[i]; T.dp[i] = pl.vals[i]; }
   for (int i = t; i < pl.MB * pl.DP; i += nt) { T.nbm1[i] = pl.nbm1_f[i]; T.nb[i] = pl.nb[i]; }
   for (int i = t; i < pl.TP; i += nt) T.tp[i] = pl.vals[pl.DP + i];
+  if (pl.n_shapes <= kDirectShapes) for (int i = t; i < pl.n_shapes; i += nt) T.n[i] = pl.shape_n[i];
 }
 
-template <int S>
-__device__ __forceinline__ void eval_direct_s(const DevPlan &pl, const DirectTables &L, const Cand &c,
-                                              const ShapeRec &sh, const LaneC &lc, float &T, float &C,
-                                              uint64_t &peak, uint32_t &mask) {
-  const int GX = pl.GX, Z = pl.Z, MB = pl.MB, DP = pl.DP;
-  const int64_t D = L.dp[c.dp];
-  const float *ts = L.ts + c.mb * Z * Z;  // transfer seconds of this microbatch size
-  // what comes from memory is requested for all segments before any of it is used
-  float4 ta[S];
-  float sync[S], upd[S];
-  uint64_t need[S];
-  int z[S], gx[S];
-#pragma unroll
-  for (int j = 0; j < S; ++j) {
-    z[j] = (int)fast_div((uint32_t)c.a[j], pl.mg_g);
-    gx[j] = c.a[j] - z[j] * GX;
-    const size_t sl = agg_slot(pl, c.shape, c.tp[j], j);
-    ta[j] = pl.ta[(sl * GX + gx[j]) * MB + c.mb];
-    sync[j] = pl.syncz[sl * Z + z[j]];
-    upd[j] = pl.upd[sl * GX + gx[j]];
-    need[j] = pl.need[(sl * MB + c.mb) * DP + c.dp];
-  }
-  Acc acc;
-  int w[S], ra[S], rb[S];  // GPUs of one replica on the pool, the real pools
-#pragma unroll
-  for (int j = 0; j < S; ++j) {
-    const uint32_t x = L.xt[gx[j]];
-    const int ga = x & 255, gb = x >> 8;
-    const int tpv = L.tp[c.tp[j]];
-    const Rec r = make_rec(ta[j], sync[j], upd[j], L.price[gx[j]], ts[z[j] * Z + z[j]], sh.n[j], tpv, 0u);
-    const uint64_t m = need[j] + L.res[ga], m2 = need[j] + L.res[gb];
-    if (m > L.cap[ga] || m2 > L.cap[gb]) mask |= 1u;
-    peak = m > peak ? m : peak;
-    peak = m2 > peak ? m2 : peak;
-    w[j] = sh.n[j] * tpv;
-    ra[j] = z[j] * pl.G + ga;
-    rb[j] = z[j] * pl.G + gb;
-    // (a pair gives half of the replicas from each type, an even number of them)
-    const int64_t take = (int64_t)w[j] * D;
-    const bool fits = ga == gb ? take <= (int64_t)L.avail[ra[j]]
-                               : (D % 2 == 0 && take <= 2 * (int64_t)L.avail[ra[j]] &&
-                                  take <= 2 * (int64_t)L.avail[rb[j]]);
-    if (!fits) mask |= 2u;
-    if (tpv > L.node[ga] || tpv > L.node[gb]) mask |= 8u;
-    if (j == 0) {
-      acc = acc_begin(r);
-    } else {
-      const int zp = z[j - 1];
-      acc = acc_cross(acc, r, ts[zp * Z + z[j]], ts[z[j] * Z + zp], L.egs[zp * Z + z[j]],
-                      sh.n[j - 1] == 1, j == 1);
-    }
-  }
-  // segments that draw on one real pool together
-  if (pl.mixed) {
-    // half-GPUs per replica that each of the real pools named by the segments gives in all
-    if (S >= 2) {
-      auto taken = [&](int r) {
-        int h = 0;
-#pragma unroll
-        for (int k = 0; k < S; ++k) h += (ra[k] == r ? w[k] : 0) + (rb[k] == r ? w[k] : 0);
-        return h;
-      };
-#pragma unroll
-      for (int j = 0; j < S; ++j) {
-        if ((int64_t)taken(ra[j]) * D > 2 * (int64_t)L.avail[ra[j]]) mask |= 2u;
-        if ((int64_t)taken(rb[j]) * D > 2 * (int64_t)L.avail[rb[j]]) mask |= 2u;
-      }
-    }
-  } else if (S == 3 && c.a[0] == c.a[2]) {
-    if ((int64_t)(w[0] + w[2]) * D > (int64_t)L.avail[c.a[0]]) mask |= 2u;
-  }
-  acc_finish(acc, lc, T, C);
+// n / d for n < 2^20 and n d < 2^40 or so by a product in single precision: inv is 1 / d rounded up by two
+// units, so the product is never below a whole quotient and above the true one by less than n 2^-21 < 1
+// in units of 1 / d.  (Three full-rate instructions; 32-bit integer products run at a quarter of it.)
+__device__ __forceinline__ float float_inverse(uint32_t d) { return __uint_as_float(__float_as_uint(1.0f / (float)d) + 2u); }
+__device__ __forceinline__ uint32_t float_div(uint32_t n, float inv) { return (uint32_t)((float)n * inv); }
+
+// n / d and the remainder, whole numbers below 2^52 held as doubles, given 1 / d: the quotient of the
+// rounded product is off by one at most, and the remainder exact (one rounding, of a whole number).
+__device__ __forceinline__ double divide_by(double n, double d, double inv, double &rem) {
+  double q = trunc(n * inv), r = fma(-q, d, n);
+  const double by = r < 0.0 ? -1.0 : (r >= d ? 1.0 : 0.0);
+  rem = fma(-by, d, r);
+  return q + by;
 }
 
 // One lane per candidate, grid-stride; the segment aggregates come straight from global memory.
-// Bound by gathers: every lane of a wave reads another cache line.  With the small tables in LDS
-// and quotas by arithmetic a candidate of three segments gathers 13 times (its shape, and four
-// words per segment) instead of about 50, and none of those waits for another but the shape's.
-// 1 000 003 random candidates: 51.4 -> 42.7 us (28 MB of indices and outputs; the same
-// bytes take 5 us as a copy).
+// Bound by gathers: every lane of a wave reads another cache line, and a compute unit's address path
+// takes a cycle per lane and 8 bytes (54 000 of the kernel's 70 000 cycles; vector instructions 32 000).
+// So the small tables, the shapes' stages among them, are in LDS, a candidate of three segments gathers
+// nine times (aggregate, seconds of all-reduce and update, bytes of each segment), and no load waits for
+// another: an index is decoded from its block's record in LDS, its two 64-bit divisions by products in
+// double precision (indices from 2^52 on divide).  The lanes of a wave go through the segments together,
+// whether they have one, two or three (apart, a wave ran the code of each number it held), quotas
+// compare with what the table of degrees and pools has room for, and products are 24-bit or in single
+// precision (32-bit ones run at a quarter of the rate).
+// 1 000 003 random candidates: 42.7 -> 35.4 us (28 MB of indices and outputs; the same bytes take 5 us as
+// a copy).  Held to fewer registers for seven waves per SIMD instead of five it spills: 41.3 us.
 constexpr int kDirectThreads = 256;
 constexpr unsigned kDirectWorkgroups = 2048;  // eight per compute unit: all resident, one copy of the tables each
 __global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, EvalArgs a) {
@@ -2109,32 +2086,152 @@ __global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, Eval
   uint32_t *const lds = reinterpret_cast<uint32_t *>(direct_lds);
   const DirectTables L = direct_tables_at(pl, lds);
   const int n_words = (int)direct_copy_words(pl);
-  for (int r = threadIdx.x; r < pl.ZGr; r += kDirectThreads) L.avail[r] = pl.avail[r];
+  for (int i = threadIdx.x; i < pl.DP * pl.ZGr; i += kDirectThreads) {  // (degrees are at least 1)
+    const int d = i / pl.ZGr;
+    L.room[i] = 2u * (uint32_t)pl.avail[i - d * pl.ZGr] / (uint32_t)pl.vals[d];
+  }
 #pragma unroll 4
   for (int i = threadIdx.x; i < n_words; i += kDirectThreads) lds[i] = pl.direct_tables[i];
   __syncthreads();
+  const uint32_t GX = pl.GX, Z = pl.Z, ZG = pl.ZG, MB = pl.MB, DP = pl.DP, TP = pl.TP;
+  const uint32_t mbtp = MB * TP, mbtpdp = mbtp * DP, gxmb = GX * MB, mbdp = MB * DP, slots = 3 * TP;
+  const float inv_mb = float_inverse(MB), inv_mbtp = float_inverse(mbtp), inv_mbtpdp = float_inverse(mbtpdp),
+              inv_gx = float_inverse(GX), inv_zg1 = float_inverse(ZG > 1 ? ZG - 1 : 1), inv_tp = float_inverse(TP);
+  const bool exact_double = pl.N < (1ull << 52), in_lds = pl.n_shapes <= kDirectShapes;
+  const double inv_inner = 1.0 / (double)pl.inner;
+  int first_step = 1;  // of the search for an index's block
+  while (2 * first_step < pl.n_blocks) first_step *= 2;
   const uint64_t stride = (uint64_t)gridDim.x * kDirectThreads;
   for (uint64_t i = (uint64_t)blockIdx.x * kDirectThreads + threadIdx.x; i < a.count; i += stride) {
     const uint64_t idx = a.indices ? a.indices[i] : a.first + i;
     float T = kPosInf, C = kPosInf;
     uint64_t peak = 0;
     uint32_t mask = 0xFFFFFFFFu;
-    Cand c;
-    if (decode_index(pl, idx, c)) {
-      mask = 0;
-      const int nb = L.nb[c.mb * pl.DP + c.dp];
-      if (nb == 0) {
-        mask = 4u;
+    if (idx < pl.N) {
+      int b = 0;  // the last block that starts at or before the index (blocks are ordered and not empty)
+      for (int step = first_step; step > 0; step >>= 1) {
+        const int c = min(b + step, pl.n_blocks - 1);
+        if (L.blocks[c].off <= idx) b = c;
+      }
+      const DirectBlock blk = L.blocks[b];
+      const int S = (int)blk.s;
+      uint32_t shape, o, in;
+      const uint64_t within = idx - blk.off;
+      if (exact_double) {
+        double rem, in_d;
+        shape = blk.first_shape + (uint32_t)divide_by((double)within, blk.size, blk.inv_size, rem);
+        o = (uint32_t)divide_by(rem, (double)pl.inner, inv_inner, in_d);
+        in = (uint32_t)in_d;
       } else {
-        const ShapeRec sh = pl.shapes[c.shape];
+        const uint64_t size = pl.blocks[b].shape_size, rem = within % size;
+        shape = blk.first_shape + (uint32_t)(within / size);
+        o = (uint32_t)(rem / pl.inner);
+        in = (uint32_t)(rem - (uint64_t)o * pl.inner);
+      }
+      uint32_t p[3], k[3];  // pool and TP index of each segment
+      p[0] = float_div(in, inv_mbtpdp);
+      in -= mul24(p[0], mbtpdp);
+      const uint32_t dp = float_div(in, inv_mbtp);
+      in -= mul24(dp, mbtp);
+      k[0] = k[1] = k[2] = float_div(in, inv_mb);
+      const uint32_t mb = in - mul24(k[0], MB), md = mul24(mb, DP) + dp;
+      // the later segments' digits (o < 2^20; zero where there is no such segment, which then names
+      // the pool behind: in bounds, not used)
+      auto digit = [&](uint32_t radix, float inv) {
+        const uint32_t q = float_div(o, inv), d = o - mul24(q, radix);
+        o = q;
+        return d;
+      };
+#pragma unroll
+      for (int j = 1; j < 3; ++j) {
+        if (j >= S) { p[j] = p[0]; k[j] = k[0]; continue; }
+        p[j] = p[j - 1] + 1 + digit(ZG - 1, inv_zg1);
+        if (p[j] >= ZG) p[j] -= ZG;
+        if (pl.pst) k[j] = digit(TP, inv_tp);
+      }
+      const int nb = L.nb[md];
+      mask = nb == 0 ? 4u : 0u;
+      if (nb != 0) {
+        const uint32_t stages = in_lds ? L.n[shape] : pl.shape_n[shape];
+        float4 ta[3];
+        float2 su[3];
+        uint64_t need[3];
+        uint32_t z[3], g[3];
+        const uint32_t slot0 = shape * slots;
+        const float4 *const ta_at = pl.ta + ((uint64_t)slot0 * gxmb + mb);
+        const float2 *const su_at = pl.su + (uint64_t)slot0 * ZG;
+        const uint64_t *const need_at = pl.need + ((uint64_t)slot0 * mbdp + md);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {  // what comes from memory is requested before any of it is used
+          z[j] = float_div(p[j], inv_gx);
+          g[j] = p[j] - mul24(z[j], GX);
+          if (j >= S) continue;
+          const uint32_t sl = 3u * k[j] + (uint32_t)j;
+          ta[j] = ta_at[mul24(sl, gxmb) + mul24(g[j], MB)];
+          su[j] = su_at[mul24(sl, ZG) + p[j]];
+          need[j] = need_at[mul24(sl, mbdp)];
+        }
         LaneC lc;
-        lc.nbm1 = L.nbm1[c.mb * pl.DP + c.dp];
-        lc.cd = L.cd[c.dp];
-        lc.dph = L.dph[c.dp];
-        lc.xb = L.xb[c.mb];
-        if (c.s == 1) eval_direct_s<1>(pl, L, c, sh, lc, T, C, peak, mask);
-        else if (c.s == 2) eval_direct_s<2>(pl, L, c, sh, lc, T, C, peak, mask);
-        else eval_direct_s<3>(pl, L, c, sh, lc, T, C, peak, mask);
+        lc.nbm1 = L.nbm1[md];
+        lc.cd = L.cd[dp];
+        lc.dph = L.dph[dp];
+        lc.xb = L.xb[mb];
+        const uint32_t *room = L.room + mul24(dp, pl.ZGr);
+        const bool odd = (L.dp[dp] & 1) != 0;
+        const float *ts = L.ts + mul24(mb, mul24(Z, Z));  // transfer seconds of this microbatch size
+        const int n[3] = {(int)(stages & 255u) + 1, (int)((stages >> 8) & 255u) + 1, (int)((stages >> 16) & 255u) + 1};
+        Acc acc;
+        int w[3], ra[3], rb[3];  // GPUs of one replica on the pool, the real pools
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          w[j] = 0;
+          ra[j] = rb[j] = 0;
+          if (j >= S) continue;
+          const uint32_t x = L.xt[g[j]];
+          const int ga = x & 255, gb = x >> 8, tpv = L.tp[k[j]];
+          const Rec r = make_rec(ta[j], su[j].x, su[j].y, L.price[g[j]], ts[mul24(z[j], Z + 1)], n[j], tpv, 0u);
+          const uint64_t m = need[j] + L.res[ga];
+          if (m > L.cap[ga]) mask |= 1u;
+          peak = m > peak ? m : peak;
+          if (pl.mixed) {
+            const uint64_t m2 = need[j] + L.res[gb];
+            if (m2 > L.cap[gb]) mask |= 1u;
+            peak = m2 > peak ? m2 : peak;
+          }
+          w[j] = (int)mul24(n[j], tpv);  // (both below 2^21)
+          ra[j] = (int)mul24(z[j], pl.G) + ga;
+          rb[j] = (int)mul24(z[j], pl.G) + gb;
+          // (a pair gives half of the replicas from each type, an even number of them)
+          const uint32_t half = (uint32_t)w[j];
+          const bool fits = ga == gb ? 2u * half <= room[ra[j]] : (!odd && half <= room[ra[j]] && half <= room[rb[j]]);
+          if (!fits) mask |= 2u;
+          if (tpv > L.node[ga] || tpv > L.node[gb]) mask |= 8u;
+          if (j == 0) {
+            acc = acc_begin(r);
+          } else {
+            const uint32_t zp = z[j - 1];
+            const uint32_t ab = mul24(zp, Z) + z[j], ba = mul24(z[j], Z) + zp;
+            acc = acc_cross(acc, r, ts[ab], ts[ba], L.egs[ab], n[j - 1] == 1, j == 1);
+          }
+        }
+        // segments that draw on one real pool together
+        if (pl.mixed) {  // half-GPUs per replica that each real pool named by the segments gives in all
+          auto taken = [&](int r) {
+            int h = 0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) h += (ra[q] == r ? w[q] : 0) + (rb[q] == r ? w[q] : 0);
+            return h;
+          };
+          if (S >= 2)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              if (j >= S) continue;
+              if ((uint32_t)taken(ra[j]) > room[ra[j]] || (uint32_t)taken(rb[j]) > room[rb[j]]) mask |= 2u;
+            }
+        } else if (S == 3 && p[0] == p[2]) {
+          if (2u * (uint32_t)(w[0] + w[2]) > room[p[0]]) mask |= 2u;
+        }
+        acc_finish(acc, lc, T, C);
         if (a.has_bound) {
           if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
           else if (throughput_below(T, a.bound)) mask |= 32u;
