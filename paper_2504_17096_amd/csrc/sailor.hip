@@ -46,7 +46,8 @@ constexpr unsigned kEvalRowsThreads = 512;
 constexpr uint32_t kSearchWorkgroups = 1024, kRootWorkgroups = 1024;  // of the search's two kernels
 constexpr size_t kSearchLds = 80 * 1024;       // LDS of a search workgroup: two fit a compute unit
 constexpr size_t kSearchMaxLds = 160 * 1024 - kSearchStaticLds;  // most dynamic LDS of one
-constexpr uint64_t kPlaceWorkgroups = 1024;  // workgroups a list of placements is spread over, if it is long enough
+constexpr uint64_t kPlaceUnits = 256;      // compute units a list of placements is spread over
+constexpr uint64_t kPlaceLongest = 256;    // plans a workgroup takes at most
 constexpr size_t kEvalRowsMaxLds = 64 * 1024;  // above this the range form evaluates lane by lane
 constexpr size_t kScanMaxLds = 160 * 1024;     // a scan workgroup stages its records within the LDS of a compute unit
 #define HIP_TRY(expr)                                                              \
@@ -1543,15 +1544,21 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
   return SAILOR_OK;
 }
 
-// A workgroup takes up to 64 plans; fewer when the list is too short to give every compute unit
-// four workgroups that way (short lists are bound by the latency of one workgroup's passes).
+// Every workgroup slot of the chip takes one run of plans, so that the whole list is resident at once and
+// the tables are staged once per slot; a longer list takes several such rounds.
 static void launch_placements(const sailor_plan *pl, PlaceArgs a, hipStream_t st) {
-  const uint64_t share = (a.count + kPlaceWorkgroups - 1) / kPlaceWorkgroups;
-  a.per_wg = (uint32_t)std::min<uint64_t>(kPlaceMaxPlans, std::max<uint64_t>(1, share));
+  const uint64_t slots = kPlaceUnits * place_workgroups_per_cu(pl->dev);
+  const uint64_t rounds = (a.count + slots * kPlaceLongest - 1) / (slots * kPlaceLongest);
+  a.per_wg = (uint32_t)((a.count + slots * rounds - 1) / (slots * rounds));
   const unsigned grid = (unsigned)((a.count + a.per_wg - 1) / a.per_wg);
   const size_t lds = place_lds_bytes(pl->dev, a.per_wg);
-  if (a.pools_b) k_eval_placements<true><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
-  else k_eval_placements<false><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+  if (pl->dev.n_bw_coef > 0) {
+    if (a.pools_b) k_eval_placements<true, true><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+    else k_eval_placements<false, true><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+  } else {
+    if (a.pools_b) k_eval_placements<true, false><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+    else k_eval_placements<false, false><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
+  }
 }
 
 sailor_status sailor_eval_placements(sailor_plan *pl, uint64_t count, const int32_t *d_desc,

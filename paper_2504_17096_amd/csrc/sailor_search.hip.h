@@ -1245,13 +1245,16 @@ __global__ __launch_bounds__(1024) void k_search_pick(SearchArgs a, uint32_t n_w
 // memory (k_list_tables), so that a workgroup copies them in one go -- a dozen loops, one per
 // table, cost a trip to memory each, 5 us in front of every workgroup.
 struct ListTables {
+  ulonglong2 *mem;   // [G] a GPU's reserved bytes and its capacity
   double *xsec;      // [MB][Z][Z] seconds of one activation transfer
   double *bw;        // [Z][Z]
+  double *ring_link; // [Z][Z] slowest link of a ring through two zones (without link profiles)
   double *egress;    // [Z][Z] (zeros without egress prices)
+  double *both_ways; // [Z][Z] egress there and back, 0 inside a zone
   double *price;     // [G]
   double *ring;      // [DP] 2 (D - 1) / D
   double *tpd;       // [TP]
-  uint64_t *cap, *res;  // [G]
+  double *p2p;       // [MB] bytes of one activation transfer
   uint64_t *act;     // [MB][TP]
   int32_t *nb;       // [MB][DP]
   int32_t *dpv, *tpv, *node;  // [DP], [TP], [G]
@@ -1261,7 +1264,7 @@ struct ListTables {
 
 __host__ __device__ inline size_t list_copy_words(const DevPlan &pl) {  // 8-byte words laid out in memory
   const size_t ints = (size_t)pl.MB * pl.DP + pl.DP + pl.TP + pl.G + pl.ZGr;
-  return (size_t)pl.MB * pl.Z * pl.Z + 2 * (size_t)pl.Z * pl.Z + 3 * (size_t)pl.G + pl.DP + pl.TP +
+  return (size_t)pl.MB * pl.Z * pl.Z + 4 * (size_t)pl.Z * pl.Z + 3 * (size_t)pl.G + pl.DP + pl.TP + pl.MB +
          (size_t)pl.MB * pl.TP + (ints + 1) / 2;
 }
 __host__ __device__ inline size_t list_tables_words(const DevPlan &pl) {  // with the availability behind them
@@ -1271,15 +1274,17 @@ __host__ __device__ inline size_t list_tables_words(const DevPlan &pl) {  // wit
 __device__ __forceinline__ ListTables list_tables_at(const DevPlan &pl, double *at) {
   const int G = pl.G, Z = pl.Z, MB = pl.MB, TP = pl.TP, DP = pl.DP;
   ListTables T;
-  T.xsec = at;
+  T.mem = reinterpret_cast<ulonglong2 *>(at);  // (first: 16-byte reads)
+  T.xsec = at + 2 * G;
   T.bw = T.xsec + MB * Z * Z;
-  T.egress = T.bw + Z * Z;
-  T.price = T.egress + Z * Z;
+  T.ring_link = T.bw + Z * Z;
+  T.egress = T.ring_link + Z * Z;
+  T.both_ways = T.egress + Z * Z;
+  T.price = T.both_ways + Z * Z;
   T.ring = T.price + G;
   T.tpd = T.ring + DP;
-  T.cap = reinterpret_cast<uint64_t *>(T.tpd + TP);
-  T.res = T.cap + G;
-  T.act = T.res + G;
+  T.p2p = T.tpd + TP;
+  T.act = reinterpret_cast<uint64_t *>(T.p2p + MB);
   T.nb = reinterpret_cast<int32_t *>(T.act + MB * TP);
   T.dpv = T.nb + MB * DP;
   T.tpv = T.dpv + DP;
@@ -1296,13 +1301,15 @@ __global__ void k_list_tables(DevPlan pl) {
   const int t = threadIdx.x, nt = blockDim.x;
   for (int i = t; i < MB * Z * Z; i += nt) T.xsec[i] = pl.xsec[i];
   for (int i = t; i < Z * Z; i += nt) {
+    const int a = i / Z, b = i % Z, back = b * Z + a;
     T.bw[i] = pl.bw[i];
+    T.ring_link[i] = a == b ? pl.bw[i] : fmin(fmin(pl.bw[a * Z + a], pl.bw[b * Z + b]), fmin(pl.bw[i], pl.bw[back]));
     T.egress[i] = pl.egress ? pl.egress[i] : 0.0;
+    T.both_ways[i] = pl.egress && a != b ? pl.egress[i] + pl.egress[back] : 0.0;
   }
   for (int i = t; i < G; i += nt) {
     T.price[i] = pl.price[i];
-    T.cap[i] = pl.cap[i];
-    T.res[i] = pl.res[i];
+    T.mem[i] = make_ulonglong2(pl.res[i], pl.cap[i]);
     T.node[i] = pl.node[i];
   }
   for (int i = t; i < DP; i += nt) {
@@ -1314,6 +1321,7 @@ __global__ void k_list_tables(DevPlan pl) {
     T.tpv[i] = pl.vals[DP + i];
     T.tpd[i] = (double)pl.vals[DP + i];
   }
+  for (int i = t; i < MB; i += nt) T.p2p[i] = (double)pl.p2p[i];
   for (int i = t; i < MB * TP; i += nt) T.act[i] = pl.act[i];
   for (int i = t; i < MB * DP; i += nt) T.nb[i] = pl.nb[i];
   for (int i = t; i < pl.ZGr; i += nt) T.zg[i] = (uint32_t)(i / G) | (uint32_t)(i % G) << 8;
@@ -1349,7 +1357,7 @@ struct PlaceArgs {
   const int32_t *pools_b; // SPLIT, same shape: pool of the other half of every stage's replicas
   const int32_t *tps;     // optional, same shape: TP index of every stage (else the descriptor's)
   uint32_t pool_stride;
-  uint32_t per_wg;        // plans a workgroup takes, at most kPlaceMaxPlans
+  uint32_t per_wg;        // plans a workgroup takes, kPlacePlans at a time at most
   const SearchPP *pps;
   int n_pp;
   int objective, has_bound;
@@ -1363,33 +1371,46 @@ struct PlaceArgs {
 
 constexpr int kPlaceThreads = 256;
 constexpr int kPlaceStages = 512;    // stages a workgroup holds at a time
-constexpr int kPlaceMaxPlans = 64;    // a lane each when the stages are added up
+constexpr int kPlacePlans = 64;      // and plans: a lane each when the stages are added up
 static_assert(kPlaceStages >= kMaxStages, "one plan's stages fit");
+
+struct PlaceDesc { int32_t pp, split, it, id, im; };  // a descriptor as the list has it
 
 struct PlacePlan {       // a plan as its stages need it
   uint32_t rs;
-  int32_t end;           // stages of the workgroup's plans up to and including this one
-  int16_t P;             // 0: an invalid descriptor
-  uint8_t it, id, im, pad[3];
-  double dpd, half_traffic;  // D; N_b x (replicas of one kind of pipeline) x bytes of a transfer
+  uint16_t end, P;       // stages of the pass's plans up to and including this one; P = 0: an invalid descriptor
+  uint8_t it, id, im, pad[5];
 };
-static_assert(sizeof(PlacePlan) == 32, "two 16-byte reads");
+static_assert(sizeof(PlacePlan) == 16, "one 16-byte read");
+
+struct PlacePass { uint64_t first; int32_t plans, stages; };  // what is worked through at a time
 
 struct PlaceLds {
+  // two passes' plans: one is laid out while the other's results are written
+  PlacePlan plan[2][kPlacePlans];
+  PlacePass pass[2];
   // what the stages contribute, in plan and stage order (four entries more than there are
   // stages: the sums read four at a time): time in the two kinds of pipeline, rent, traffic
   double term[4][kPlaceStages + 4];
-  double sum[4][kPlaceMaxPlans], slowest[2][kPlaceMaxPlans];   // what they add up to
-  long long sync[kPlaceMaxPlans], upd[kPlaceMaxPlans];  // bits of the maxima (non-negative values, in
-                                                        // which order the bits compare like them)
-  unsigned long long peak[kPlaceMaxPlans];
-  PlacePlan plan[kPlaceMaxPlans];
-  uint32_t flags[kPlaceMaxPlans];  // mask bits 0, 1, 3; bit 31: an index out of range
+  double sum[4][kPlacePlans], slowest[2][kPlacePlans];   // what they add up to
+  unsigned long long sync[kPlacePlans], upd[kPlacePlans];  // bits of the maxima (non-negative values, in
+                                                           // which order the bits compare like them)
+  unsigned long long peak[kPlacePlans];
+  uint32_t flags[kPlacePlans];     // mask bits 0, 1, 3; bit 31: an index out of range
   uint8_t owner[kPlaceStages];     // the stage's plan
 };
+static_assert(sizeof(PlaceLds) % 16 == 0, "the tables behind it hold 16-byte words");
 
 __host__ __device__ inline size_t place_lds_bytes(const DevPlan &pl, uint32_t per_wg) {
-  return sizeof(PlaceLds) + list_tables_words(pl) * 8 + (size_t)per_wg * pl.ZGr * sizeof(int32_t);
+  return sizeof(PlaceLds) + list_tables_words(pl) * 8 +
+         (size_t)(per_wg < (uint32_t)kPlacePlans ? per_wg : (uint32_t)kPlacePlans) * pl.ZGr * sizeof(int32_t);
+}
+
+// Workgroups a compute unit holds at a time: its LDS is handed out in units of 1 280 bytes.
+inline uint64_t place_workgroups_per_cu(const DevPlan &pl) {
+  const size_t units = (place_lds_bytes(pl, kPlacePlans) + 1279) / 1280;
+  const size_t by_registers = pl.n_bw_coef > 0 ? 4 : 5;
+  return std::min(by_registers, std::max<size_t>(1, 128 / units));
 }
 
 // Sum (and maximum) over a plan's stages in stage order, for a lane per plan.
@@ -1409,6 +1430,42 @@ __device__ __forceinline__ void place_sum(const double *v, int P, double &sum, d
   }
 }
 
+// The maximum over a plan's stages that lie in the lane's row of 16, up to and including the lane
+// (which is stage i of its plan): reads only lanes below.
+__device__ __forceinline__ unsigned long long place_row_max(unsigned long long v, int i) {
+  auto step = [&](auto ctrl, int by) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, decltype(ctrl)::value, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), decltype(ctrl)::value, 0xF, 0xF, true);
+    const unsigned long long o = ((unsigned long long)hi << 32) | lo;  // (0 from outside the row)
+    v = i >= by && o > v ? o : v;
+  };
+  step(std::integral_constant<int, 0x111>(), 1);  // row_shr:1, 2, 4, 8
+  step(std::integral_constant<int, 0x112>(), 2);
+  step(std::integral_constant<int, 0x114>(), 4);
+  step(std::integral_constant<int, 0x118>(), 8);
+  return v;
+}
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32 |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
+__device__ __forceinline__ PlaceDesc place_desc(const PlaceArgs &a, uint64_t c, uint64_t c_end) {
+  PlaceDesc d{-1, 0, 0, 0, 0};
+  if (c < c_end) {
+    const int32_t *p = a.desc + c * 5;
+    d = PlaceDesc{p[0], p[1], p[2], p[3], p[4]};
+  }
+  return d;
+}
+
+__device__ __forceinline__ SearchPP place_depth(const PlaceArgs &a, const PlaceDesc &d) {
+  SearchPP pp{};
+  if (d.pp >= 0 && d.pp < a.n_pp) pp = a.pps[d.pp];
+  return pp;  // (n_part = 0 without a depth: no layer split is in range)
+}
+
 // The simulator (Sec. 4.3) for plans whose stages choose their pools freely.
 //
 // With SPLIT a stage's D replicas lie on two pools, half on each, also across zones (the D tuples
@@ -1420,72 +1477,113 @@ __device__ __forceinline__ void place_sum(const double *v, int P, double &sum, d
 // profiled times, node size, gradient shard, GPUs against the quota, rent) uses the stage's own
 // degree.  A descriptor, pool or TP index out of range yields mask = 0xFFFFFFFF, T = C = +inf, mem = 0.
 //
-// A workgroup takes per_wg plans and works through their stages, up to kPlaceStages at a time, plans
-// one behind the other without gaps: first a lane per stage -- what is added up in stage order,
-// which is part of the definition, goes to LDS, maxima are folded in there -- then a lane per
-// plan adds its stages up, a wave per quantity.  A wave per plan leaves most lanes idle where
-// pipelines are shorter than 64 stages, and walks every plan's sums by itself: 200 003 plans of 1
-// to 48 stages with two pools and a degree per stage took 488 us that way and take 85 us this way
-// (vector instructions 35 us of it; the rest is the latency of a workgroup's chain: descriptors,
-// pools, stage records, sums).  Measured beside it: requesting two stages' words per lane at a time
-// (98 us, the registers cost a workgroup per compute unit), 512 threads (100 us), bounds on the
-// registers for more waves (113 us and more).
-template <bool SPLIT>
+// A workgroup goes through a run of per_wg plans, as many at a time as have kPlaceStages stages
+// between them, plans one behind the other without gaps: first a lane per stage -- what is added up
+// in stage order, which is part of the definition, goes to LDS, maxima are folded in there -- then a
+// lane per plan adds its stages up, a wave per quantity.  While wave 0 writes a pass's results wave 1
+// lays out the next one's plans, whose descriptors were requested a pass earlier.
+//
+// Bound by vector instructions (31 us of the 63 below) and the latency of a pass's chain: pools, stage
+// records, sums.  200 003 plans of 1 to 48 stages with two pools and a degree per stage took 488 us with
+// a wave per plan (most lanes idle), 85 us with 64 plans a workgroup -- two passes, the second half
+// empty, 2.4 rounds of workgroups, and the LDS busy for 40 us, mostly with maxima of 64 lanes on the same
+// word -- and take 63 us this way (67 with four workgroups per compute unit, which is what the registers
+// allow where the links' profiles are evaluated in the same kernel: hence PROFILES).  Measured beside
+// it: runs half as long, in two rounds, 65 us; the bound on the registers for five workgroups instead of
+// PROFILES 80 us (spills).  Earlier: two stages' words per lane at a time 98 instead of 85 us, 512
+// threads 100 us.
+template <bool SPLIT, bool PROFILES>
 __global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, PlaceArgs a) {
-  extern __shared__ double place_lds[];
+  extern __shared__ ulonglong2 place_lds[];
   PlaceLds &S = *reinterpret_cast<PlaceLds *>(place_lds);
   double *const tables = reinterpret_cast<double *>(&S + 1);
   int32_t *const cnt = reinterpret_cast<int32_t *>(tables + list_tables_words(pl));  // [plan][ZG]
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const uint32_t G = pl.G, Z = pl.Z, ZG = pl.ZGr, MB = pl.MB, TP = pl.TP, DP = pl.DP;
   const uint32_t row_words = mul24(mul24(MB, TP), pl.row_w);  // of a stage's records
-  const uint64_t c0 = (uint64_t)blockIdx.x * a.per_wg;
-  const int n = (int)min((uint64_t)a.per_wg, a.count - c0);
-  if (wv == 0) {  // a lane per plan
-    PlacePlan p{};
-    if (lane < n) {
-      const int32_t *d = a.desc + (c0 + lane) * 5;
-      const int ip = d[0], q = d[1], it = d[2], id = d[3], im = d[4];
-      if (ip >= 0 && ip < a.n_pp && it >= 0 && it < (int)TP && id >= 0 && id < (int)DP && im >= 0 && im < (int)MB && q >= 0) {
-        const SearchPP pp = a.pps[ip];
-        if (q < pp.n_part && (uint32_t)pp.P <= a.pool_stride) {
-          p.P = (int16_t)pp.P;
-          p.rs = pp.rs0 + (uint32_t)q * (uint32_t)pp.P;
-          p.it = (uint8_t)it; p.id = (uint8_t)id; p.im = (uint8_t)im;
-          p.dpd = (double)pl.vals[id];
-          p.half_traffic = (double)pl.nb[im * DP + id] * (SPLIT ? 0.5 * p.dpd : p.dpd) * (double)pl.p2p[im];
-        }
-      }
-    }
-    int end = p.P;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(end, off);
-      if (lane >= off) end += v;
-    }
-    p.end = end;
-    S.plan[lane] = p;
-    S.sync[lane] = S.upd[lane] = 0;
-    S.peak[lane] = 0;
+  const uint64_t c_begin = (uint64_t)blockIdx.x * a.per_wg, c_end = min(a.count, c_begin + a.per_wg);
+  uint64_t next = c_begin;  // wave 1: the next pass's first plan, the descriptors from there on and their depths
+  PlaceDesc d{};
+  SearchPP pp{};
+  if (wv == 1) {
+    d = place_desc(a, next + lane, c_end);
+    pp = place_depth(a, d);
+  }
+  if (wv == 0) {
+    S.sync[lane] = S.upd[lane] = S.peak[lane] = 0;
     S.flags[lane] = 0;
   }
-  for (int x = t; x < (int)(a.per_wg * ZG); x += kPlaceThreads) cnt[x] = 0;
+  for (int x = t; x < (int)mul24(min(a.per_wg, (uint32_t)kPlacePlans), ZG); x += kPlaceThreads) cnt[x] = 0;
   const ListTables L = stage_list_tables(pl, tables);
   __syncthreads();
-  for (int s0 = 0; s0 < n;) {  // uniform: plans s0 .. s1 - 1 make up one pass
-    const int base = s0 ? S.plan[s0 - 1].end : 0;
-    const int s1 = s0 + __popcll(__builtin_amdgcn_ballot_w64(lane >= s0 && lane < n && S.plan[lane].end - base <= kPlaceStages));
-    const int stages = S.plan[s1 - 1].end - base;
-    if (lane >= s0 && lane < s1) {  // whose stage is whose: a lane per plan, the waves take turns
-      const int P = S.plan[lane].P, at = S.plan[lane].end - P - base;
-      for (int i = wv; i < P; i += kPlaceThreads / 64) S.owner[at + i] = (uint8_t)lane;
+  PlacePass done{0, 0, 0};  // the pass whose results are to be written
+  for (int b = 0;; b ^= 1) {  // uniform
+    if (wv == 1) {  // a lane per plan
+      PlacePlan p{};
+      if (d.pp >= 0 && d.split >= 0 && d.split < pp.n_part && d.it >= 0 && d.it < (int)TP && d.id >= 0 && d.id < (int)DP &&
+          d.im >= 0 && d.im < (int)MB && (uint32_t)pp.P <= a.pool_stride) {
+        p.P = (uint16_t)pp.P;
+        p.rs = pp.rs0 + (uint32_t)d.split * (uint32_t)pp.P;
+        p.it = (uint8_t)d.it; p.id = (uint8_t)d.id; p.im = (uint8_t)d.im;
+      }
+      int end = p.P;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(end, off);
+        if (lane >= off) end += v;
+      }
+      const int n = __popcll(__builtin_amdgcn_ballot_w64(next + lane < c_end && end <= kPlaceStages));
+      const int stages = __shfl(end, max(n - 1, 0));
+      if (lane < n) {
+        p.end = (uint16_t)end;
+        S.plan[b][lane] = p;
+        for (int i = end - p.P; i < end; ++i) S.owner[i] = (uint8_t)lane;
+      }
+      if (lane == 0) S.pass[b] = PlacePass{next, n, n ? stages : 0};
+      next = uniform64(next + (uint32_t)n);
+      d = place_desc(a, next + lane, c_end);
+    }
+    if (wv == 0 && lane < done.plans) {
+      double T = __builtin_huge_val(), C = T;
+      uint64_t peak = 0;
+      uint32_t mask = 0xFFFFFFFFu;
+      const PlacePlan pn = S.plan[b ^ 1][lane];
+      const uint32_t flags = S.flags[lane];
+      if (pn.P != 0 && !(flags >> 31)) {
+        const int nb = L.nb[pn.im * DP + pn.id];
+        if (nb == 0) {
+          mask = 4u;
+        } else {
+          mask = flags;
+          peak = S.peak[lane];
+          double t_pp = S.sum[0][lane] + (double)(nb - 1) * S.slowest[0][lane];
+          if (SPLIT) t_pp = fmax(t_pp, S.sum[1][lane] + (double)(nb - 1) * S.slowest[1][lane]);
+          T = (t_pp + __longlong_as_double((long long)S.sync[lane])) + __longlong_as_double((long long)S.upd[lane]);
+          C = S.sum[2][lane] / 3600.0 * T + S.sum[3][lane];
+          if (a.has_bound) {
+            if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
+            else if (1.0 / T < a.bound) mask |= 32u;
+          }
+        }
+      }
+      const uint64_t c = done.first + (uint32_t)lane;
+      if (a.T) a.T[c] = T;
+      if (a.C) a.C[c] = C;
+      if (a.mem) a.mem[c] = peak;
+      if (a.mask) a.mask[c] = mask;
+      S.sync[lane] = S.upd[lane] = S.peak[lane] = 0;
+      S.flags[lane] = 0;
     }
     __syncthreads();
-    for (int e = t; e < stages; e += kPlaceThreads) {
+    done.first = uniform64(S.pass[b].first);
+    done.plans = __builtin_amdgcn_readfirstlane(S.pass[b].plans);
+    done.stages = __builtin_amdgcn_readfirstlane(S.pass[b].stages);
+    if (done.plans == 0) break;  // uniform
+    for (int e = t; e < done.stages; e += kPlaceThreads) {
       const uint32_t own = S.owner[e];
-      const PlacePlan pn = S.plan[own];
-      const int P = pn.P, i = e - (pn.end - P - base);
-      const size_t row = (c0 + own) * a.pool_stride + (uint32_t)i;
+      const PlacePlan pn = S.plan[b][own];
+      const int P = pn.P, i = e - (pn.end - P);
+      const size_t row = (done.first + own) * a.pool_stride + (uint32_t)i;
       const int32_t *pa = a.pools + row, *pb = SPLIT ? a.pools_b + row : pa;
       const int fwd = i < P - 1 ? 1 : 0, back = i > 0 ? -1 : 0;
       const uint32_t ra = (uint32_t)pa[0], ran = (uint32_t)pa[fwd], rap = (uint32_t)pa[back];
@@ -1503,101 +1601,85 @@ __global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, P
       const double cb = SPLIT ? row_st[gb] : 0.0, ub = SPLIT ? row_st[G + gb] : 0.0;
       const uint64_t model = (uint64_t)__double_as_longlong(row_st[2 * G]);
       const double grad = row_st[2 * G + 1];
-      const int tp = L.tpv[ti], nb = L.nb[mul24(pn.im, DP) + pn.id];
+      const int tp = L.tpv[ti], nb = L.nb[mul24(pn.im, DP) + pn.id], D = L.dpv[pn.id];
+      const double dpd = (double)D;
       atomicAdd(&cnt[mul24(own, ZG) + a0], tp);  // GPUs of one replica (split: counted once per half)
       if (SPLIT) atomicAdd(&cnt[mul24(own, ZG) + b0], tp);
       const uint64_t bytes = model + act_bytes(min(P - i, nb), layers, L.act[mt]);
-      const uint64_t m1 = bytes + L.res[ga], m2 = SPLIT ? bytes + L.res[gb] : m1;
-      uint32_t flags = (m1 > L.cap[ga] || (SPLIT && m2 > L.cap[gb])) ? 1u : 0u;
+      const ulonglong2 gpu_a = L.mem[ga], gpu_b = SPLIT ? L.mem[gb] : gpu_a;
+      const uint64_t m1 = bytes + gpu_a.x, m2 = bytes + gpu_b.x;
+      uint32_t flags = (m1 > gpu_a.y || (SPLIT && m2 > gpu_b.y)) ? 1u : 0u;
       if (tp > L.node[ga] || (SPLIT && tp > L.node[gb])) flags |= 8u;
-      if (SPLIT && a0 != b0 && (L.dpv[pn.id] & 1)) flags |= 2u;  // D replicas cannot be halved
+      if (SPLIT && a0 != b0 && (D & 1)) flags |= 2u;  // D replicas cannot be halved
       if (ra >= ZG || (SPLIT && rb >= ZG) || rt >= TP) flags |= 1u << 31;
+      const uint32_t at_a = mul24(za, Z), at_b = mul24(zb, Z);  // rows of the zone tables
       const double *xsec = L.xsec + mul24(pn.im, mul24(Z, Z));
+      // N_b x replicas of one kind of pipeline (each carries half of them) x bytes of a transfer
+      const double one_way = (double)nb * (SPLIT ? 0.5 * dpd : dpd) * L.p2p[pn.im];
       double xa = 0.0, xb = 0.0, traffic = 0.0;
       if (fwd) {
         const uint32_t zna = L.zg[min(ran, ZG - 1)] & 255u;
-        xa += xsec[mul24(za, Z) + zna];
-        // (each kind of pipeline carries half of the replicas)
-        if (zna != za) traffic += pn.half_traffic * (L.egress[mul24(za, Z) + zna] + L.egress[mul24(zna, Z) + za]);
+        xa = xsec[at_a + zna];
+        traffic = one_way * L.both_ways[at_a + zna];
         if (SPLIT) {
           const uint32_t znb = L.zg[min(rbn, ZG - 1)] & 255u;
-          xb += xsec[mul24(zb, Z) + znb];
-          if (znb != zb) traffic += pn.half_traffic * (L.egress[mul24(zb, Z) + znb] + L.egress[mul24(znb, Z) + zb]);
+          xb = xsec[at_b + znb];
+          traffic += one_way * L.both_ways[at_b + znb];
         }
       }
       if (back) {
-        xa += xsec[mul24(za, Z) + (L.zg[min(rap, ZG - 1)] & 255u)];
-        if (SPLIT) xb += xsec[mul24(zb, Z) + (L.zg[min(rbp, ZG - 1)] & 255u)];
+        xa += xsec[at_a + (L.zg[min(rap, ZG - 1)] & 255u)];
+        if (SPLIT) xb += xsec[at_b + (L.zg[min(rbp, ZG - 1)] & 255u)];
       }
       double sync = 0.0;
-      if (pn.dpd > 1.0) {
-        double link = list_link(pl, L, za, za, grad);
-        if (SPLIT && zb != za)
-          link = fmin(fmin(link, list_link(pl, L, zb, zb, grad)),
-                      fmin(list_link(pl, L, za, zb, grad), list_link(pl, L, zb, za, grad)));
+      if (D > 1) {
+        double link;
+        if (PROFILES) {
+          link = link_bw(pl, za, za, grad);
+          if (SPLIT && zb != za)
+            link = fmin(fmin(link, link_bw(pl, zb, zb, grad)),
+                        fmin(link_bw(pl, za, zb, grad), link_bw(pl, zb, za, grad)));
+        } else {
+          link = L.ring_link[at_a + (SPLIT ? zb : za)];
+        }
         const double ring_bytes = L.ring[pn.id] * grad;
         sync = ring_bytes / link;
-        if (SPLIT && zb != za) traffic += ring_bytes * (L.egress[mul24(za, Z) + zb] + L.egress[mul24(zb, Z) + za]);
+        if (SPLIT) traffic += ring_bytes * L.both_ways[at_a + zb];
       }
       S.term[0][e] = ca + xa;
       if (SPLIT) S.term[1][e] = cb + xb;
-      const double gpus = pn.dpd * L.tpd[ti];  // (whole numbers below 2^53)
+      const double gpus = dpd * L.tpd[ti];  // (whole numbers below 2^53)
       S.term[2][e] = gpus * (SPLIT ? 0.5 * (L.price[ga] + L.price[gb]) : L.price[ga]);
       S.term[3][e] = traffic;
-      atomicMax(&S.sync[own], (long long)__double_as_longlong(sync));
-      atomicMax(&S.upd[own], (long long)__double_as_longlong(SPLIT ? fmax(ua, ub) : ua));
-      atomicMax(&S.peak[own], (unsigned long long)(m1 > m2 ? m1 : m2));
+      // (an LDS atomic takes a cycle per lane on the same word, and a plan's stages lie side by side)
+      const unsigned long long most_sync = place_row_max((unsigned long long)__double_as_longlong(sync), i);
+      const unsigned long long most_upd = place_row_max((unsigned long long)__double_as_longlong(SPLIT ? fmax(ua, ub) : ua), i);
+      const unsigned long long most = place_row_max(m1 > m2 ? m1 : m2, i);
+      if ((lane & 15) == 15 || i == P - 1) {
+        atomicMax(&S.sync[own], most_sync);
+        atomicMax(&S.upd[own], most_upd);
+        atomicMax(&S.peak[own], most);
+      }
       if (flags) atomicOr(&S.flags[own], flags);
     }
+    if (wv == 1) pp = place_depth(a, d);
     __syncthreads();
-    const int p = s0 + lane;
-    if (wv < 4) {  // a lane per plan, a wave per quantity
-      if (p < s1 && (SPLIT || wv != 1)) {
-        const PlacePlan pn = S.plan[p];
-        double sum, slowest;
-        place_sum(S.term[wv] + (pn.end - pn.P - base), pn.P, sum, slowest);
-        S.sum[wv][p] = sum;
-        if (wv < 2) S.slowest[wv][p] = slowest;
-      }
+    if (lane < done.plans && (SPLIT || wv != 1)) {  // a lane per plan, a wave per quantity
+      const PlacePlan pn = S.plan[b][lane];
+      double sum, slowest;
+      place_sum(S.term[wv] + (pn.end - pn.P), pn.P, sum, slowest);
+      S.sum[wv][lane] = sum;
+      if (wv < 2) S.slowest[wv][lane] = slowest;
     }
-    for (int x = t; x < (int)mul24(s1 - s0, ZG); x += kPlaceThreads) {  // every pool holds what is placed on it
+    for (int x = t; x < (int)mul24(done.plans, ZG); x += kPlaceThreads) {  // every pool holds what is placed on it
       const int q = (int)((uint32_t)x / ZG), pool = x - (int)mul24(q, ZG);
-      if ((int64_t)cnt[mul24(s0 + q, ZG) + pool] * L.dpv[S.plan[s0 + q].id] > (SPLIT ? 2 : 1) * (int64_t)L.avail[pool])
-        atomicOr(&S.flags[s0 + q], 2u);
+      if ((int64_t)cnt[x] * L.dpv[S.plan[b][q].id] > (SPLIT ? 2 : 1) * (int64_t)L.avail[pool])
+        atomicOr(&S.flags[q], 2u);
+      cnt[x] = 0;
     }
     __syncthreads();
-    if (wv == 0 && p < s1) {
-      double T = __builtin_huge_val(), C = T;
-      uint64_t peak = 0;
-      uint32_t mask = 0xFFFFFFFFu;
-      const PlacePlan pn = S.plan[p];
-      if (pn.P != 0 && !(S.flags[p] >> 31)) {
-        const int nb = L.nb[pn.im * DP + pn.id];
-        if (nb == 0) {
-          mask = 4u;
-        } else {
-          mask = S.flags[p];
-          peak = S.peak[p];
-          double t_pp = S.sum[0][p] + (double)(nb - 1) * S.slowest[0][p];
-          if (SPLIT) t_pp = fmax(t_pp, S.sum[1][p] + (double)(nb - 1) * S.slowest[1][p]);
-          T = (t_pp + __longlong_as_double(S.sync[p])) + __longlong_as_double(S.upd[p]);
-          C = S.sum[2][p] / 3600.0 * T + S.sum[3][p];
-          if (a.has_bound) {
-            if (a.objective == 0) { if (C > a.bound) mask |= 32u; }
-            else if (1.0 / T < a.bound) mask |= 32u;
-          }
-        }
-      }
-      if (a.T) a.T[c0 + p] = T;
-      if (a.C) a.C[c0 + p] = C;
-      if (a.mem) a.mem[c0 + p] = peak;
-      if (a.mask) a.mask[c0 + p] = mask;
-    }
-    s0 = s1;
   }
-  if (a.hdr && wv == 0) {  // (one plan: lane 0 wrote its results)
-    if (lane == 0) publish(a.hdr, a.seq);
-  }
+  if (a.hdr && t == 0) publish(a.hdr, a.seq);  // (one plan: this lane wrote its results)
 }
 
 // ------------------------------------------------------------------ a pool per replica
@@ -1694,15 +1776,15 @@ __device__ __forceinline__ ReplicaSums replica_pairs(const DevPlan &pl, const Re
       const double grad = row_st[2 * G + 1];
       const int tp = L.tpv[ti];
       atomicAdd(&cnt[p], tp);  // GPUs the pool gives
-      const uint64_t m = model + act_bytes(min(P - i, nb), layers, L.act[mt]) + L.res[g];
-      if (m > L.cap[g]) s.flags |= 1u;
+      const ulonglong2 gpu = L.mem[g];
+      const uint64_t m = model + act_bytes(min(P - i, nb), layers, L.act[mt]) + gpu.x;
+      if (m > gpu.y) s.flags |= 1u;
       if (tp > L.node[g]) s.flags |= 8u;
       s.peak = m > s.peak ? m : s.peak;
       double x = 0.0;
       if (i < P - 1) {
         x += xsec[mul24(z, Z) + zn];
-        if (zn != z)  // one replica's microbatches, both directions
-          s.traffic += one_traffic * (L.egress[mul24(z, Z) + zn] + L.egress[mul24(zn, Z) + z]);
+        s.traffic += one_traffic * L.both_ways[mul24(z, Z) + zn];  // one replica's microbatches
       }
       if (i > 0) x += xsec[mul24(z, Z) + zv];
       times[e] = c + x;

@@ -1100,3 +1100,46 @@ def test_listed_plans_at_the_edges_of_the_evaluators_passes(torch_cuda, count):
                for i, d in enumerate(desc)])
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("count,depths,profiles", [(90_001, (1, 2, 7), False), (330_007, (1, 2, 7), False),
+                                                   (90_001, (1, 7, 64, 256), False), (5_003, (2, 7, 64), True)])
+def test_long_lists_of_placements_give_what_short_ones_give(torch_cuda, count, depths, profiles):
+    # a workgroup's run of plans in several passes, each of 64 plans or of up to 512 stages, and (330 007)
+    # more plans than every workgroup's longest run takes at once; each plan as in a list of one plan a
+    # workgroup, bit for bit (no sum crosses plans), invalid descriptors and pools in between
+    torch = torch_cuda
+    prob = make_problem(n_layers=256, n_types=2, n_zones=2, mb_list=(1, 2), tp_list=(1, 2), dp_list=(1, 2, 8),
+                        pp_list=list(depths), global_batch=1680, partitions={7: [[37, 37, 37, 37, 36, 36, 36]]},
+                        t_fwd=1e-3, t_bwd=2e-3, t_upd=1e-5, layer_params=2_000_000, act=3_000_000, p2p=2_000_000,
+                        cap=np.array([40, 8], np.uint64) * np.uint64(1 << 30), avail=np.full((2, 2), 300),
+                        bw=np.array([[1e10, 1e9], [2e9, 1e10]]), egress=np.array([[0, 2e-11], [3e-11, 0]]),
+                        price=np.array([3.0, 1.5]))
+    if profiles:
+        prob = prob.with_bw_poly(W.bandwidth_poly(prob))
+    plan, rng, n, most = _plan(prob), np.random.default_rng(count), 211, max(depths)
+    try:
+        desc = np.stack([rng.integers(0, len(depths), n), np.zeros(n, int), rng.integers(0, 2, n),
+                         rng.integers(0, 3, n), rng.integers(0, 2, n)], 1)
+        pa, pb, tps = rng.integers(0, 4, (n, most)), rng.integers(0, 4, (n, most)), rng.integers(0, 2, (n, most))
+        desc[5, 1], desc[40, 0], pa[77, 0] = 9, 99, -1
+        dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, dtype=np.int32)).to("cuda:0")
+        d, a, b, k = dev(desc), dev(pa), dev(pb), dev(tps)
+        at = torch.from_numpy(rng.integers(0, n, count)).to("cuda:0")
+
+        def run(d, **lists):
+            m = d.shape[0]
+            out = {f: torch.empty(m, dtype=t, device="cuda:0") for f, t in
+                   (("d_time", torch.float64), ("d_cost", torch.float64), ("d_mem", torch.int64), ("d_mask", torch.int32))}
+            plan.eval_placements(m, d, pool_stride=most, bound=1.0, **lists, **out)
+            torch.cuda.synchronize()
+            return out
+
+        for lists in ({"d_pools": a}, {"d_pools": a, "d_pools_b": b, "d_tps": k}):
+            short = run(d, **lists)
+            assert (short["d_mask"] == -1).sum() >= 3 and torch.isfinite(short["d_time"]).sum() > n // 2
+            long = run(d[at].contiguous(), **{f: v[at].contiguous() for f, v in lists.items()})
+            for f in short:
+                assert torch.equal(long[f], short[f][at]), f
+    finally:
+        plan.destroy()
