@@ -172,8 +172,9 @@ struct sailor_plan {
   std::vector<ShapeRec> shapes;
   std::vector<BlockRec> blocks;
   std::vector<UnitRec> units;
-  std::vector<EvalUnit> eunits;  // range evaluation, ascending idx_lo
-  const EvalUnit *d_eunits = nullptr;
+  std::vector<EvalBlock> eblocks;  // range evaluation: a block's units (laid out on the device)
+  uint64_t n_eunits = 0;
+  EvalUnit *d_eunits = nullptr;    // ascending idx_lo
   size_t eval_lds_bytes = 0;
   std::vector<int32_t> mbv, tpv, dpv, ppv;
   std::vector<uint16_t> xt;        // real types a | b << 8 of every extended type
@@ -459,21 +460,19 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
   }
   if (pl->units.size() > (size_t)0x7fffffff / kCollectSub) return SAILOR_EINVAL;
   // units of the range evaluation: (shape, range of the outer digits), about 16 Ki
-  // candidates each, in index order
-  for (uint32_t si = 0; si < pl->shapes.size(); ++si) {
-    const ShapeRec &sh = pl->shapes[si];
-    uint64_t o_total = 1;
-    for (int j = 1; j < sh.s; ++j) o_total *= (uint64_t)(ZG - 1) * otp;
-    const uint64_t chunk = std::min<uint64_t>(
-        std::min<uint64_t>(o_total, kEvalUnitMaxOuter), std::max<uint64_t>(1, kEvalUnitTarget / inner));
-    for (uint64_t lo = 0; lo < o_total; lo += chunk) {
-      EvalUnit e{};
-      e.shape = si;
-      e.o_lo = (uint32_t)lo;
-      e.o_cnt = (uint32_t)std::min<uint64_t>(chunk, o_total - lo);
-      e.idx_lo = sh.base + lo * inner;
-      pl->eunits.push_back(e);
-    }
+  // candidates each, in index order; the shapes of a block are divided alike
+  for (const BlockRec &b : pl->blocks) {
+    EvalBlock e{};
+    e.off = b.off;
+    e.shape_size = b.shape_size;
+    e.o_total = b.shape_size / inner;
+    e.first_unit = pl->n_eunits;
+    e.first_shape = b.first_shape;
+    e.chunk = (uint32_t)std::min<uint64_t>(
+        std::min<uint64_t>(e.o_total, kEvalUnitMaxOuter), std::max<uint64_t>(1, kEvalUnitTarget / inner));
+    e.per_shape = (e.o_total + e.chunk - 1) / e.chunk;
+    pl->eblocks.push_back(e);
+    pl->n_eunits += e.per_shape * b.n_shapes;
   }
   // Largest units first, so that the small ones fill the tail of the launch (the order is
   // refined by a timed pass once the tables are on the device).
@@ -578,11 +577,12 @@ unsigned quota_grid(const DevPlan &d) {
   return (unsigned)std::min<size_t>(1024, (n + 255) / 256);
 }
 
-AvailTable avail_table(const sailor_plan *pl) {
+AvailTable avail_table(const int32_t *avail, int n) {
   AvailTable t{};
-  std::memcpy(t.v, pl->h_avail, pl->dev.ZGr * sizeof(int32_t));
+  std::memcpy(t.v, avail, n * sizeof(int32_t));
   return t;
 }
+AvailTable avail_table(const sailor_plan *pl) { return avail_table(pl->h_avail, pl->dev.ZGr); }
 
 // Brings a changed availability table to the device on the caller's stream and rebuilds
 // the quota table from it.
@@ -1067,7 +1067,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   const size_t unit_cap = pl->units.size() * (size_t)std::max(1L, forced_parts);
   char *per_unit = nullptr;  // the tables that creation fills last, in one copy: records, bounds, orders
   slab.table(&per_unit, unit_cap * (sizeof(UnitRec) + 4 * sizeof(float)));
-  slab.input(&pl->d_eunits, pl->eunits.data(), pl->eunits.size());
+  const EvalBlock *d_eblocks = nullptr;
+  slab.input(&d_eblocks, pl->eblocks.data(), pl->eblocks.size());
+  slab.table(&pl->d_eunits, (size_t)pl->n_eunits);
   // derived tables, filled by the set-up kernels
   d.n_bw_coef = p->n_bw_coef;
   if (p->n_bw_coef > 0) slab.input(&d.bw_poly, p->bw_poly, (size_t)Z * Z * p->n_bw_coef);
@@ -1112,8 +1114,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&pl->ubits, unit_cap * (size_t)pl->ubits_stride);
   slab.table(&pl->staged, (size_t)SAILOR_MAX_K);
   CREATE_TRY(slab.commit(pl->arena));
-  CREATE_TRY(pl->arena.alloc(&pl->surv, (size_t)pl->surv_cap));  // (these two can be replaced on their own)
-  CREATE_TRY(pl->arena.alloc(&pl->ref, (size_t)pl->ref_cap));
   pl->d_avail = const_cast<int32_t *>(d.avail);
   pl->umin_l = pl->umin_s + unit_cap;
   d.units = reinterpret_cast<UnitRec *>(per_unit);
@@ -1121,20 +1121,10 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   pl->lb_cost = pl->lb_time + unit_cap;
   pl->order_time = reinterpret_cast<uint32_t *>(pl->lb_cost + unit_cap);
   pl->order_cost = pl->order_time + unit_cap;
-  const size_t res_bytes = (sizeof(ResultHeader) + 8 + (size_t)SAILOR_MAX_K * sizeof(RefRec) + 127) & ~(size_t)127;
-  CREATE_TRY(hipHostMalloc(&pl->h_result, res_bytes + (size_t)ZGr * sizeof(int32_t), hipHostMallocMapped));
-  std::memset(pl->h_result, 0, res_bytes);
-  void *d_res = nullptr;
-  CREATE_TRY(hipHostGetDevicePointer(&d_res, pl->h_result, 0));
-  pl->d_hdr = static_cast<ResultHeader *>(d_res);
-  pl->d_out = reinterpret_cast<RefRec *>(static_cast<char *>(d_res) + sizeof(ResultHeader));
-  pl->h_avail = reinterpret_cast<int32_t *>(static_cast<char *>(pl->h_result) + res_bytes);
-  pl->h_avail_dev = reinterpret_cast<const int32_t *>(static_cast<char *>(d_res) + res_bytes);
-  std::memcpy(pl->h_avail, p->avail, ZGr * sizeof(int32_t));
-  for (hipEvent_t &e : pl->ev) CREATE_TRY(hipEventCreate(&e));
-
+  // (the units in front of the tables' kernels: a copy waits for what was launched before it)
+  CREATE_TRY(hipMemcpy(const_cast<UnitRec *>(d.units), pl->units.data(), pl->units.size() * sizeof(UnitRec), hipMemcpyHostToDevice));
   k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
-  k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(pl), nullptr, pl->d_avail, 0u);
+  k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(p->avail, ZGr), nullptr, pl->d_avail, 0u);
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_direct_tables<<<1, 256>>>(d);
@@ -1158,7 +1148,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     size_t NU = pl->units.size();
     const size_t n_units_alloc = unit_cap;  // entries of the per-unit tables on the device
     UnitRec *d_units = const_cast<UnitRec *>(d.units);
-    CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
     float *d_cost = reinterpret_cast<float *>(pl->order_time);  // (filled behind this)
     ScanArgs ca{};
     ca.umin_s = pl->umin_s;
@@ -1167,6 +1156,23 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     ca.lim_s = ca.lim_l = kPosInf;
     ca.ignore_quota = 1;
     launch_bounds(pl, ca);
+    CREATE_TRY(hipGetLastError());
+    // what only queries need is allocated while the pass runs
+    CREATE_TRY(pl->arena.alloc(&pl->surv, (size_t)pl->surv_cap));  // (these two can be replaced on their own)
+    CREATE_TRY(pl->arena.alloc(&pl->ref, (size_t)pl->ref_cap));
+    const size_t res_bytes = (sizeof(ResultHeader) + 8 + (size_t)SAILOR_MAX_K * sizeof(RefRec) + 127) & ~(size_t)127;
+    CREATE_TRY(hipHostMalloc(&pl->h_result, res_bytes + (size_t)ZGr * sizeof(int32_t), hipHostMallocMapped));
+    std::memset(pl->h_result, 0, res_bytes);
+    void *d_res = nullptr;
+    CREATE_TRY(hipHostGetDevicePointer(&d_res, pl->h_result, 0));
+    pl->d_hdr = static_cast<ResultHeader *>(d_res);
+    pl->d_out = reinterpret_cast<RefRec *>(static_cast<char *>(d_res) + sizeof(ResultHeader));
+    pl->h_avail = reinterpret_cast<int32_t *>(static_cast<char *>(pl->h_result) + res_bytes);
+    pl->h_avail_dev = reinterpret_cast<const int32_t *>(static_cast<char *>(d_res) + res_bytes);
+    std::memcpy(pl->h_avail, p->avail, ZGr * sizeof(int32_t));
+    for (hipEvent_t &e : pl->ev) CREATE_TRY(hipEventCreate(&e));
+    k_eval_units<<<(unsigned)std::min<uint64_t>(1024, (pl->n_eunits + 255) / 256), 256>>>(
+        d_eblocks, (int)pl->eblocks.size(), pl->n_eunits, d.inner, pl->d_eunits);
     CREATE_TRY(hipGetLastError());
     std::vector<float> val(NU), lb_time(unit_cap + NU);
     CREATE_TRY(hipMemcpy(lb_time.data(), pl->umin_s, lb_time.size() * sizeof(float), hipMemcpyDeviceToHost));
@@ -1345,24 +1351,19 @@ sailor_status sailor_eval_batch(sailor_plan *pl, uint64_t first, uint64_t count,
   const bool timed = pl->timing_mode >= 1;
   if (!d_indices && pl->eval_lds_bytes <= kEvalRowsMaxLds) {
     // the units that intersect [first, first + count)
-    auto end_of = [&](const EvalUnit &e) { return e.idx_lo + (uint64_t)e.o_cnt * pl->dev.inner; };
-    size_t lo = 0, hi = pl->eunits.size();
-    while (lo < hi) {  // first unit that ends after `first`
-      const size_t mid = (lo + hi) / 2;
-      if (end_of(pl->eunits[mid]) <= first) lo = mid + 1; else hi = mid;
-    }
-    const size_t u0 = lo;
-    hi = pl->eunits.size();
-    while (lo < hi) {  // first unit that starts at or after the end of the range
-      const size_t mid = (lo + hi) / 2;
-      if (pl->eunits[mid].idx_lo < first + count) lo = mid + 1; else hi = mid;
-    }
+    auto unit_of = [&](uint64_t index) {
+      const EvalBlock &b = *(std::upper_bound(pl->eblocks.begin(), pl->eblocks.end(), index,
+                                              [](uint64_t i, const EvalBlock &e) { return i < e.off; }) - 1);
+      const uint64_t rem = index - b.off;
+      return b.first_unit + rem / b.shape_size * b.per_shape + rem % b.shape_size / pl->dev.inner / b.chunk;
+    };
+    const uint64_t u0 = unit_of(first), n_wgs = unit_of(first + count - 1) - u0 + 1;
     if (pl->dev.mixed)
-      launch(k_eval_rows<true>, dim3((unsigned)(lo - u0)), dim3(kEvalRowsThreads), pl->eval_lds_bytes,
+      launch(k_eval_rows<true>, dim3((unsigned)n_wgs), dim3(kEvalRowsThreads), pl->eval_lds_bytes,
              st, timed ? pl->ev[3] : nullptr, timed ? pl->ev[1] : nullptr, pl->dev, a, pl->d_eunits,
              (uint32_t)u0);
     else
-      launch(k_eval_rows<false>, dim3((unsigned)(lo - u0)), dim3(kEvalRowsThreads), pl->eval_lds_bytes,
+      launch(k_eval_rows<false>, dim3((unsigned)n_wgs), dim3(kEvalRowsThreads), pl->eval_lds_bytes,
              st, timed ? pl->ev[3] : nullptr, timed ? pl->ev[1] : nullptr, pl->dev, a, pl->d_eunits,
              (uint32_t)u0);
     HIP_TRY(hipGetLastError());

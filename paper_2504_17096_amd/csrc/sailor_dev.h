@@ -59,6 +59,13 @@ struct EvalUnit {       // work of one workgroup of the range evaluation: one sh
   uint32_t pad;
 };
 
+struct EvalBlock {      // the range evaluation's units of a block's shapes, which are divided alike
+  uint64_t off, shape_size;  // first index, candidates per shape
+  uint64_t o_total;     // values of a shape's outer digits, of which a unit spans `chunk`
+  uint64_t first_unit, per_shape;
+  uint32_t first_shape, chunk;
+};
+
 struct SurvRec {        // candidate kept for the fp64 re-evaluation
   uint64_t idx;
   float key;            // fp32 key; +inf when only loosely inside the constraint
