@@ -613,7 +613,8 @@ void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEven
 template <int MODE, bool MIXED>
 void launch_units_m(sailor_plan *pl, sailor_objective obj, int has_bound, const ScanArgs &a,
                     dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  const AvailTable avail = avail_table(pl);
+  AvailArg<MODE, MIXED> avail{};
+  if constexpr (kAvailRides<MODE, MIXED>) avail = avail_table(pl);
   if (obj == SAILOR_MAX_THROUGHPUT) {
     if (has_bound) launch(k_units<MODE, 0, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
     else launch(k_units<MODE, 0, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
@@ -640,8 +641,8 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
 // One workgroup per unit, the availability ignored (plan creation).
 void launch_bounds(sailor_plan *pl, const ScanArgs &a) {
   const dim3 grid((unsigned)pl->dev.n_units), block(pl->unit_threads);
-  if (pl->dev.mixed) k_units<MODE_BOUNDS, 0, false, true><<<grid, block, pl->lds_bytes>>>(pl->dev, a, AvailTable{});
-  else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a, AvailTable{});
+  if (pl->dev.mixed) k_units<MODE_BOUNDS, 0, false, true><<<grid, block, pl->lds_bytes>>>(pl->dev, a, NoAvail{});
+  else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a, NoAvail{});
 }
 
 struct SearchLaunch {
@@ -686,7 +687,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   sailor_status rc = constraint_limits(obj, con, &has_bound, &bound, &sa.lim_s, &sa.lim_l);
   if (rc != SAILOR_OK) return rc;
   HIP_TRY(hipSetDevice(pl->device));
-  if (pl->dev.mixed) {
+  if (pl->dev.mixed || k != 0 || !first_try || pl->incremental) {
     rc = refresh_avail(pl, st);
     if (rc != SAILOR_OK) return rc;
   } else if (pl->avail_dirty) {  // the call's first launch brings it along (it waits for its result: never captured)
@@ -840,7 +841,6 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   sa.direct = 0;
   launch_units<MODE_SCAN>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr,
                           t_scan ? pl->ev[1] : nullptr);
-  sa.fresh = 0;
   // an upper bound of the k-th smallest key: the k-th smallest unit minimum (the best plan's: the
   // smallest, and its tie band).  The same kernel lists the units whose loose minimum lies under it.
   sa.band = best ? (float)(1.0 + kTieTol) + 3.0f * kEvalEps : 1.0f + 3.0f * kEvalEps;

@@ -590,7 +590,7 @@ struct ScanArgs {
   int direct;               // COLLECT without a scan before it, BEST: ulist names the only units
   uint32_t n_list_host;     // whose bound meets the limit (n_list_host of them).  COLLECT: every
                             // candidate of theirs that is valid and within the loose limit is kept
-  uint32_t fresh;           // the availability is new and travels with this launch (plain pools only): units
+  uint32_t fresh;           // BEST: the availability is new and travels with this launch (plain pools only): units
                             // take their quotas from it, and the `fresh` workgroups behind theirs
   int32_t *avail_copy;      // bring the quota table and the device's copy up to date
   const float *ulb_key;     // BEST, optional: the same bound for the objective; a unit that cannot
@@ -618,6 +618,10 @@ __global__ void k_init_counters(uint32_t *c, int n) {
 }
 
 // One candidate of the scan: update the running minima, or append it to the survivors.
+struct NoAvail {};
+template <int MODE, bool MIXED> constexpr bool kAvailRides = MODE == MODE_BEST && !MIXED;
+template <int MODE, bool MIXED> using AvailArg = std::conditional_t<kAvailRides<MODE, MIXED>, AvailTable, NoAvail>;
+
 template <int MODE, int OBJ, bool HASB>
 __device__ __forceinline__ void visit(const ScanArgs &a, float T, float C, bool feas, float tau,
                                       uint64_t idx, uint32_t shape, float &ms, float &ml) {
@@ -905,10 +909,11 @@ __host__ __device__ inline size_t unit_lds_records(int ZG, int MB) {
 // needs comes from the unit record and tables that do not depend on one another, so all of
 // its global loads are in flight together and one barrier ends it.
 template <int MODE, int OBJ, bool HASB, bool MIXED>
-__device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, const AvailTable &avail,
+__device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, const AvailArg<MODE, MIXED> &avail,
                                           uint32_t uidx, int sub, uint32_t n_sub, uint4 *lds_raw) {
   const unsigned long long t_begin = (MODE == MODE_SCAN && a.ucost) ? wall_clock64() : 0ull;
   const UnitRec u = pl.units[uidx];
+  const bool fresh = kAvailRides<MODE, MIXED> && a.fresh != 0;
   float tau = kPosInf, key_limit = kPosInf;
   if ((MODE == MODE_SCAN || MODE == MODE_BEST) && (a.ulb_con || a.ulb_key)) {
     bool dead = false;  // must come out the same in every wave of the workgroup
@@ -976,8 +981,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     const uint32_t gi = (sl * (uint32_t)G + (uint32_t)g) * (uint32_t)MB + mb;
     const float4 ta = pl.ta[gi];
     uint32_t q = 0xFFFFFFFFu;
-    if (!MIXED && a.fresh) q = quota_bits(pl, avail.v[p], w);
-    else if (!a.ignore_quota) q = pl.qw[w * ZG + p];
+    if (!a.ignore_quota && !fresh) q = pl.qw[w * ZG + p];
+    if constexpr (kAvailRides<MODE, MIXED>)
+      if (fresh) q = quota_bits(pl, avail.v[p], w);
     if ((pl.h1m[p] >> k) & 1u) q = 0;  // H1: tensor parallelism stays inside a node
     const uint32_t bits = pl.memok[gi] & q & pl.divis[mb];
     rec_store(rec_lo, rec_hi, rbits, i,
@@ -995,8 +1001,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   if (S == 3 && !MIXED)
     for (int p = t; p < ZG; p += blockDim.x) {
       uint32_t q = 0xFFFFFFFFu;
-      if (a.fresh) q = quota_bits(pl, avail.v[p], w0 + w2);
-      else if (!a.ignore_quota) q = pl.qw[(w0 + w2) * ZG + p];
+      if (!a.ignore_quota && !fresh) q = pl.qw[(w0 + w2) * ZG + p];
+      if constexpr (kAvailRides<MODE, MIXED>)
+        if (fresh) q = quota_bits(pl, avail.v[p], w0 + w2);
       q13[p] = q;
       if (keep_bits) {
         uint32_t *const uq = ub + a.ubits_stride - ZG;  // behind the records' bits
@@ -1094,16 +1101,20 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
 //
 // A new availability rides on the call's first launch (ScanArgs::fresh): a quota table made by a kernel
 // of its own in front of it cost 6 of the 44 us that a new table and its fastest plan took on 6.8e6
-// candidates.  (Not with pairs of types, whose joint quotas are looked up per plan.)
+// candidates.  Only the best plan's pass takes it along: 512 bytes of arguments and the registers of the
+// second source of quotas cost a top-64 query, in its scan and its collect pass, 2 to 3 of its 33 to 61 us.
+// (Not with pairs of types, whose joint quotas are looked up per plan.)
 template <int MODE, int OBJ, bool HASB, bool MIXED>
-__global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a, AvailTable avail) {
+__global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a, AvailArg<MODE, MIXED> avail) {
   extern __shared__ uint4 lds_raw[];
-  const uint32_t n_wgs = gridDim.x - (MIXED ? 0u : a.fresh);
-  if (!MIXED && blockIdx.x >= n_wgs) {
-    if (blockIdx.x == n_wgs)
-      for (int r = threadIdx.x; r < pl.ZGr; r += blockDim.x) a.avail_copy[r] = avail.v[r];
-    quota_table(pl, avail.v, 0u, blockIdx.x - n_wgs, a.fresh);
-    return;
+  if constexpr (kAvailRides<MODE, MIXED>) {
+    const uint32_t n_wgs = gridDim.x - a.fresh;
+    if (blockIdx.x >= n_wgs) {
+      if (blockIdx.x == n_wgs)
+        for (int r = threadIdx.x; r < pl.ZGr; r += blockDim.x) a.avail_copy[r] = avail.v[r];
+      quota_table(pl, avail.v, 0u, blockIdx.x - n_wgs, a.fresh);
+      return;
+    }
   }
   if (MODE == MODE_BEST && a.direct) {
     unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist[blockIdx.x / a.n_sub], (int)(blockIdx.x % a.n_sub), a.n_sub, lds_raw);
@@ -1114,7 +1125,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
                                lds_raw);
   } else {
     const uint32_t n_list = a.direct ? a.n_list_host : a.counters[CNT_NLIST];
-    const uint32_t per_round = n_wgs / a.n_sub;
+    const uint32_t per_round = gridDim.x / a.n_sub;
     const int sub = (int)(blockIdx.x % a.n_sub);
     for (uint32_t e = blockIdx.x / a.n_sub; e < n_list; e += per_round) {  // uniform
       unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist[e], sub, a.n_sub, lds_raw);
