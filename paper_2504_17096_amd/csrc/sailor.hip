@@ -844,8 +844,10 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   // an upper bound of the k-th smallest key: the k-th smallest unit minimum (the best plan's: the
   // smallest, and its tie band).  The same kernel lists the units whose loose minimum lies under it.
   sa.band = best ? (float)(1.0 + kTieTol) + 3.0f * kEvalEps : 1.0f + 3.0f * kEvalEps;
-  k_select_kth<1024><<<1, 1024, 0, st>>>(pl->umin_s, 1, nullptr, n_units, best ? 1u : k, cnt + CNT_TAU0,
-                                   pl->umin_l, n_units, sa.band, pl->ulist, cnt + CNT_NLIST);
+  const uint32_t k_units_min = best ? 1u : k;
+  const auto select = n_units > kKthByRankFrom && k_units_min <= kKthByRank ? k_select_kth<1024, true> : k_select_kth<1024, false>;
+  select<<<1, 1024, 0, st>>>(pl->umin_s, 1, nullptr, n_units, k_units_min, cnt + CNT_TAU0, pl->umin_l, n_units, sa.band,
+                             pl->ulist, cnt + CNT_NLIST);
   sa.tau_src = cnt + CNT_TAU0;
   sa.ulist = pl->ulist;
   sa.n_sub = kListSub;

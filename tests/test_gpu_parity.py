@@ -808,3 +808,26 @@ def test_scan_at_the_edges_of_its_lane_space(torch_cuda, n_dp, mixed):
                                objective, orc, bound)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("form", ["distinct", "ties", "scarce"])
+def test_threshold_among_more_units_than_a_workgroup_keeps(torch_cuda, form):
+    # 290 shapes x a TP degree per segment: over 8 192 units, whose k-th smallest minimum is found by rank
+    # (distinct times), by its digits (identical layers and pools: thousands of equal minima), or is not
+    # there (fewer valid units than k); k on both sides of the 64 that the ranks are taken up to
+    L, rng = 24, np.random.default_rng(3)
+    shape = (2, 1, 4, L)
+    fwd = np.full(shape, 1e-3) if form == "ties" else rng.uniform(0.5e-3, 2e-3, shape)
+    prob = make_problem(n_layers=L, n_types=2, n_zones=2, mb_list=(1,), tp_list=(1, 2, 4, 8), dp_list=(1, 2),
+                        pp_list=[1, 2, 24], max_segments=3, seg3_max_pp=24, global_batch=64, uniform_layers=False,
+                        t_fwd=fwd, t_bwd=2 * fwd, layer_params=1_000_000, act=1_000_000, p2p=1_000_000,
+                        avail=np.array([[24, 0], [0, 3]]) if form == "scarce" else np.full((2, 2), 400),
+                        bw=np.array([[1e10, 1e9], [1e9, 1e10]])).with_per_segment_tp(True)
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        n_units = 64 * 253 + 16 * 23  # three and two segments of the deepest pipeline alone
+        assert n_units > 8192 and plan.num_candidates() == orc.num_candidates
+        for k in (1, 17, 64, 65):
+            check_topk(plan.topk(k), orc.topk(k, n_threads=4), MAX_THROUGHPUT, orc)
+    finally:
+        plan.destroy()
