@@ -235,7 +235,7 @@ struct sailor_plan {
   unsigned long long *search_root_expanded = nullptr;
   SubResult *search_results = nullptr, *search_final = nullptr;
   bool search_dirty = true;           // the counters are not zero
-  uint32_t cnt_phase = 0;      // which of the two counter sets the next call uses
+  uint32_t calls = 0;          // number of the next selection; its lowest bit says which counter set it uses
   bool counters_dirty = false; // a failed call may have left either set in any state
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};  // start, scan end, end, scan start
   int timing_mode = 0;         // 0 none, 1 dominant kernel, 2 dominant kernel + whole call
@@ -697,13 +697,13 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     sa.avail_copy = pl->d_avail;
   }
   if (pl->counters_dirty) {
-    k_init_counters<<<1, 64, 0, st>>>(pl->counters, 2 * CNT_COUNT);
+    k_init_counters<<<1, 64, 0, st>>>(pl->counters, pl->calls);
     pl->counters_dirty = false;
   }
   // two counter sets: this call's set was reset by the final kernel of the previous call
-  uint32_t *cnt = pl->counters + pl->cnt_phase * CNT_COUNT;
-  uint32_t *cnt_next = pl->counters + (pl->cnt_phase ^ 1u) * CNT_COUNT;
-  pl->cnt_phase ^= 1u;
+  const uint32_t call = pl->calls++;
+  uint32_t *cnt = pl->counters + (call & 1u) * CNT_COUNT;
+  uint32_t *cnt_next = pl->counters + (~call & 1u) * CNT_COUNT;
   sa.umin_s = pl->umin_s;
   sa.umin_l = pl->umin_l;
   sa.counters = cnt;
@@ -753,7 +753,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     ra.band = 1.0f + 3.0f * kEvalEps;
     if (best) {
       ra.band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
-      k_refine_best<<<kBestWorkgroups, kBestWaves * 64, 0, st>>>(pl->dev, ra, cnt_next, pl->d_hdr, pl->d_out, ++pl->seq);
+      k_refine_best<<<kBestWorkgroups, kBestWaves * 64, 0, st>>>(pl->dev, ra, call, cnt_next, pl->d_hdr, pl->d_out, ++pl->seq);
     } else {
       // the exact k-th smallest fp32 key among the survivors, then only its neighbourhood
       k_select_kth<256><<<1, 256, 0, st>>>(&pl->surv[0].key, (int)(sizeof(SurvRec) / 4),
@@ -764,7 +764,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
       // few records expected (about k, plus ties): one workgroup ranks them from LDS
       const bool one = k <= kRankOneWorkgroup;
       k_rank_topk<<<one ? 1 : 64, one ? kRankLds : 256, 0, st>>>(
-          pl->ref, pl->ref_cap, cnt, cnt_next, (int)obj, k, pl->d_hdr, pl->d_out, pl->staged,
+          pl->ref, pl->ref_cap, cnt, call, cnt_next, (int)obj, k, pl->d_hdr, pl->d_out, pl->staged,
           cnt + CNT_DONE, ++pl->seq);
     }
     if (t_all) HIP_TRY(hipEventRecord(pl->ev[2], st));
@@ -1125,7 +1125,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   pl->order_cost = pl->order_time + unit_cap;
   // (the units in front of the tables' kernels: a copy waits for what was launched before it)
   CREATE_TRY(hipMemcpy(const_cast<UnitRec *>(d.units), pl->units.data(), pl->units.size() * sizeof(UnitRec), hipMemcpyHostToDevice));
-  k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
+  k_init_counters<<<1, 64>>>(pl->counters, pl->calls);
   k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(p->avail, ZGr), nullptr, pl->d_avail, 0u);
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
@@ -1279,7 +1279,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
       for (size_t i = 0; i < NU; ++i) sorted_lb[i] = val[order[i]];
     }
     CREATE_TRY(hipMemcpy(per_unit, tables.data(), tables.size(), hipMemcpyHostToDevice));
-    k_init_counters<<<1, 64>>>(pl->counters, 2 * CNT_COUNT);
+    k_init_counters<<<1, 64>>>(pl->counters, pl->calls);
     CREATE_TRY(hipDeviceSynchronize());
   }
 #undef CREATE_TRY

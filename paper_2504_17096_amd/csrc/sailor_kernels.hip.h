@@ -597,14 +597,18 @@ struct ScanArgs {
                             // come within near_band of the running minimum is passed over
 };
 
-enum Counter { CNT_SURV = 0, CNT_REF = 1, CNT_FEAS = 2, CNT_GMIN = 3, CNT_TAU0 = 4, CNT_TAU1 = 5,
-               CNT_NLOOSE = 6, CNT_NSTRICT = 7,  // count-only collect passes
-               CNT_NLIST = 8,                    // length of the collect pass's unit list
-               CNT_DONE = 9,                     // workgroups of the final kernel that have finished
+// Two sets, which a plan's calls use in turn; the final kernel of a call resets the next call's.
+enum Counter { CNT_SURV = 0, CNT_OWNER = 1,      // number of the call the set belongs to (read with CNT_SURV)
+               CNT_REF = 2, CNT_FEAS = 3, CNT_GMIN = 4, CNT_TAU0 = 5, CNT_TAU1 = 6,
+               CNT_NLOOSE = 7, CNT_NSTRICT = 8,  // count-only collect passes
+               CNT_NLIST = 9,                    // length of the collect pass's unit list
+               CNT_DONE = 10,                    // workgroups of the final kernel that have finished
                CNT_COUNT = 16 };
+static_assert(CNT_SURV % 2 == 0 && CNT_OWNER == CNT_SURV + 1 && CNT_COUNT % 2 == 0, "one 8-byte word");
 
-__device__ __forceinline__ uint32_t counter_reset_value(int i) {
-  const int c = i % CNT_COUNT;
+// c: a counter of the set that belongs to `call`
+__device__ __forceinline__ uint32_t counter_reset_value(int c, uint32_t call) {
+  if (c == CNT_OWNER) return call;
   return (c >= CNT_GMIN && c <= CNT_TAU1) ? 0x7f800000u : 0u;  // thresholds start at +inf
 }
 
@@ -613,8 +617,10 @@ __global__ void k_zero_counters(uint32_t *c, uint32_t mask) {
   if (threadIdx.x < CNT_COUNT && ((mask >> threadIdx.x) & 1u)) c[threadIdx.x] = 0u;
 }
 
-__global__ void k_init_counters(uint32_t *c, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) c[i] = counter_reset_value(i);
+// both sets, before `call`
+__global__ void k_init_counters(uint32_t *c, uint32_t call) {
+  for (int i = threadIdx.x; i < 2 * CNT_COUNT; i += blockDim.x)
+    c[i] = counter_reset_value(i % CNT_COUNT, call + (((uint32_t)(i / CNT_COUNT) ^ call) & 1u));
 }
 
 // One candidate of the scan: update the running minima, or append it to the survivors.
@@ -1651,12 +1657,21 @@ __device__ __forceinline__ void publish(ResultHeader *hdr, uint32_t seq) {
 // results in LDS and picks at once, where a kernel of its own for the pick started with a cold L2 and
 // took 4 to 5 us more.  With more, every workgroup takes its share and the one that finishes last
 // picks.
+//
+// In the first case the host has the result while other workgroups may not have started yet.  By then
+// the plan may be in use again, on another stream too, where nothing orders them: the next call but one
+// uses the same counters.  So a workgroup other than the first works only if the set belongs to its own
+// call.  While it does, the count is this call's, which everyone sees alike; the final kernel of the next
+// call gives the set a new owner before the call behind it can count anything; and count and owner come in
+// one load, so a late workgroup sees a small count or a foreign owner, and leaves.  (A late one touches
+// nothing else but the survivor list, whose records it reads and drops.)
 constexpr int kBestWaves = 8;
 constexpr uint32_t kBestAlone = 64;  // (a lane each in the selection and the pick)
 constexpr unsigned kBestWorkgroups = 64;
 
-__global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, RefineArgs a, uint32_t *next_counters,
-                                                                ResultHeader *hdr, RefRec *out, uint32_t seq) {
+__global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, RefineArgs a, uint32_t call,
+                                                                uint32_t *next_counters, ResultHeader *hdr,
+                                                                RefRec *out, uint32_t seq) {
   __shared__ RefineLds lds[kBestWaves];
   __shared__ RefRec s_ref[kBestAlone];
   __shared__ double s_key[kBestWaves];
@@ -1667,11 +1682,15 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
   // so the address is valid whatever the count turns out to be)
   SurvRec mine{};
   if ((uint32_t)lane < a.surv_cap) mine = a.surv[lane];
-  const uint32_t n_surv = a.counters[CNT_SURV], gmin = a.counters[CNT_GMIN];
+  const uint64_t count_owner = __hip_atomic_load(reinterpret_cast<const uint64_t *>(a.counters + CNT_SURV),
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t gmin = a.counters[CNT_GMIN];
+  const uint32_t n_surv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)count_owner),
+                 owner = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(count_owner >> 32));
   const uint32_t n = min(n_surv, a.surv_cap);
   const float tau = __uint_as_float(gmin) * a.band;
-  const bool alone = n <= kBestAlone;  // uniform over the grid
-  if (alone && blockIdx.x != 0) return;
+  const bool alone = n <= kBestAlone;  // uniform over the call's grid
+  if (blockIdx.x != 0 && (alone || owner != call)) return;
   auto evaluate = [&](uint64_t idx, uint32_t shape) {
     Cand c;
     decode_in_shape(pl, shape, idx, c);
@@ -1715,7 +1734,7 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
     n_ref = __hip_atomic_load(&a.counters[CNT_REF], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     n_feas = __hip_atomic_load(&a.counters[CNT_FEAS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (t < CNT_COUNT) next_counters[t] = counter_reset_value(t);  // for the next call
+  if (t < CNT_COUNT) next_counters[t] = counter_reset_value(t, call + 1);  // for the next call
   const RefRec *const ref = alone ? s_ref : a.ref;
   const uint32_t stored = alone ? n_ref : min(n_ref, a.ref_cap);
   if (alone) {
@@ -1768,7 +1787,7 @@ constexpr uint32_t kRankLds = 1024;  // records the one-workgroup form of k_rank
 // (scattered 40-byte stores over the bus, each behind its own fence, cost 20 us for 500
 // records).
 __global__ __launch_bounds__(kRankLds) void k_rank_topk(const RefRec *ref, uint32_t ref_cap,
-                                                        const uint32_t *counters,
+                                                        const uint32_t *counters, uint32_t call,
                                                         uint32_t *next_counters, int objective,
                                                         uint32_t k, ResultHeader *hdr, RefRec *out,
                                                         RefRec *staged, uint32_t *done,
@@ -1787,7 +1806,7 @@ __global__ __launch_bounds__(kRankLds) void k_rank_topk(const RefRec *ref, uint3
   const uint32_t f = counters[CNT_FEAS];  // valid stored records (requested with the count)
   const bool overflow = n_ref > ref_cap;  // uniform: the list is incomplete, nothing is ranked
   if (blockIdx.x == 0 && threadIdx.x < CNT_COUNT)
-    next_counters[threadIdx.x] = counter_reset_value(threadIdx.x);  // for the next call
+    next_counters[threadIdx.x] = counter_reset_value(threadIdx.x, call + 1);  // for the next call
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     hdr->n_found = overflow ? 0u : (f < k ? f : k);
     hdr->surv_count = counters[CNT_SURV];

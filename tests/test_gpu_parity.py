@@ -719,6 +719,45 @@ def test_independent_plans_serve_two_host_threads(torch_cuda):
             p.destroy()
 
 
+def test_calls_of_one_plan_move_between_streams(torch_cuda):
+    # nothing orders the streams, and a call returns while its last kernel is retiring (the more so on a
+    # GPU that another plan keeps busy): what still runs of it must leave the counters of the plan's later
+    # calls alone.  Few and many survivors in turn: up to 64 are one workgroup's, more are shared by all
+    torch = torch_cuda
+    prob = make_problem(n_layers=8, n_types=8, n_zones=2, mb_list=(1, 2), tp_list=(1, 2), dp_list=(1, 2, 4),
+                        pp_list=[1, 4], max_segments=2, layer_params=1_000_000, act=1_000_000,
+                        price=np.arange(1.0, 9.0), bw=1e10)
+    plan, orc, busy = _plan(prob), Oracle(prob), _plan(W.config2())
+    try:
+        cheapest = orc.best(MIN_COST)
+        budget = cheapest.cost * (1 + 1e-6)
+        best = {None: orc.best(), budget: orc.best(MAX_THROUGHPUT, budget)}
+        top = orc.topk(8, MIN_COST)
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        n = busy.num_candidates()
+        out = torch.empty(n, dtype=torch.float32, device="cuda:0")
+        torch.cuda.synchronize()
+        counts, rng = {None: set(), budget: set()}, np.random.default_rng(5)
+        for rep in range(300):
+            if rep % 10 == 0:
+                for _ in range(10):
+                    busy.eval_batch(0, n, d_time=out, stream=streams[2].cuda_stream)
+            st = streams[int(rng.integers(2))].cuda_stream
+            if rng.integers(4) == 0:
+                check_topk(plan.topk(8, MIN_COST, stream=st), top, MIN_COST, orc)
+                continue
+            bound = (None, budget)[int(rng.integers(2))]
+            check_result(plan.best_plan(MAX_THROUGHPUT, bound, stream=st), best[bound], orc)
+            counts[bound].add(plan.last_counts()[1:])
+        torch.cuda.synchronize()
+        # (the candidates within the tie band of the minimum do not depend on the order of the scan)
+        assert len(counts[None]) == len(counts[budget]) == 1, counts
+        assert min(counts[None])[0] > 64 >= max(counts[budget])[0] > 0
+    finally:
+        plan.destroy()
+        busy.destroy()
+
+
 def test_timing_modes_report_the_scan_and_the_whole_call(torch_cuda):
     from paper_2504_17096_amd.binding import SAILOR_EINVAL, SailorError
     stream = torch_cuda.cuda.current_stream().cuda_stream
