@@ -753,7 +753,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     ra.band = 1.0f + 3.0f * kEvalEps;
     if (best) {
       ra.band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
-      k_refine_best<<<kBestWorkgroups, kBestWaves * 64, 0, st>>>(pl->dev, ra, call, cnt_next, pl->d_hdr, pl->d_out, ++pl->seq);
+      k_refine_best<<<kBestWorkgroups, kBestWaves * 64, 0, st>>>(pl->dev, ra, cnt_next, pl->d_hdr, pl->d_out, ++pl->seq, call);
     } else {
       // the exact k-th smallest fp32 key among the survivors, then only its neighbourhood
       k_select_kth<256><<<1, 256, 0, st>>>(&pl->surv[0].key, (int)(sizeof(SurvRec) / 4),
@@ -764,7 +764,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
       // few records expected (about k, plus ties): one workgroup ranks them from LDS
       const bool one = k <= kRankOneWorkgroup;
       k_rank_topk<<<one ? 1 : 64, one ? kRankLds : 256, 0, st>>>(
-          pl->ref, pl->ref_cap, cnt, call, cnt_next, (int)obj, k, pl->d_hdr, pl->d_out, pl->staged,
+          pl->ref, pl->ref_cap, cnt, cnt_next, (int)obj, k, pl->d_hdr, pl->d_out, pl->staged,
           cnt + CNT_DONE, ++pl->seq);
     }
     if (t_all) HIP_TRY(hipEventRecord(pl->ev[2], st));

@@ -1669,9 +1669,9 @@ constexpr int kBestWaves = 8;
 constexpr uint32_t kBestAlone = 64;  // (a lane each in the selection and the pick)
 constexpr unsigned kBestWorkgroups = 64;
 
-__global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, RefineArgs a, uint32_t call,
-                                                                uint32_t *next_counters, ResultHeader *hdr,
-                                                                RefRec *out, uint32_t seq) {
+__global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, RefineArgs a, uint32_t *next_counters,
+                                                                ResultHeader *hdr, RefRec *out, uint32_t seq,
+                                                                uint32_t call) {
   __shared__ RefineLds lds[kBestWaves];
   __shared__ RefRec s_ref[kBestAlone];
   __shared__ double s_key[kBestWaves];
@@ -1734,7 +1734,7 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
     n_ref = __hip_atomic_load(&a.counters[CNT_REF], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     n_feas = __hip_atomic_load(&a.counters[CNT_FEAS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (t < CNT_COUNT) next_counters[t] = counter_reset_value(t, call + 1);  // for the next call
+  if (t < CNT_COUNT) next_counters[t] = counter_reset_value(t, owner + 1);  // for the next call
   const RefRec *const ref = alone ? s_ref : a.ref;
   const uint32_t stored = alone ? n_ref : min(n_ref, a.ref_cap);
   if (alone) {
@@ -1787,7 +1787,7 @@ constexpr uint32_t kRankLds = 1024;  // records the one-workgroup form of k_rank
 // (scattered 40-byte stores over the bus, each behind its own fence, cost 20 us for 500
 // records).
 __global__ __launch_bounds__(kRankLds) void k_rank_topk(const RefRec *ref, uint32_t ref_cap,
-                                                        const uint32_t *counters, uint32_t call,
+                                                        const uint32_t *counters,
                                                         uint32_t *next_counters, int objective,
                                                         uint32_t k, ResultHeader *hdr, RefRec *out,
                                                         RefRec *staged, uint32_t *done,
@@ -1803,7 +1803,7 @@ __global__ __launch_bounds__(kRankLds) void k_rank_topk(const RefRec *ref, uint3
   if (gridDim.x == 1 && threadIdx.x < ref_cap) mine = ref[threadIdx.x];
   const uint32_t n_ref = counters[CNT_REF];
   const uint32_t n = min(n_ref, ref_cap);
-  const uint32_t f = counters[CNT_FEAS];  // valid stored records (requested with the count)
+  const uint32_t f = counters[CNT_FEAS], call = counters[CNT_OWNER];  // valid stored records (requested with the count)
   const bool overflow = n_ref > ref_cap;  // uniform: the list is incomplete, nothing is ranked
   if (blockIdx.x == 0 && threadIdx.x < CNT_COUNT)
     next_counters[threadIdx.x] = counter_reset_value(threadIdx.x, call + 1);  // for the next call
