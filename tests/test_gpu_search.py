@@ -1143,3 +1143,43 @@ def test_long_lists_of_placements_give_what_short_ones_give(torch_cuda, count, d
                 assert torch.equal(long[f], short[f][at]), f
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("count", [1024, 1025, 1281, 32_768, 32_769, 90_001])
+def test_lists_of_placements_of_every_length_match_the_oracle(torch_cuda, count):
+    # one plan a workgroup and two; runs of one pass on four workgroups per compute unit, on five, runs of
+    # several passes: the plans of a list are drawn from a few whose values the oracle gives
+    torch = torch_cuda
+    prob = make_problem(n_layers=24, n_types=2, n_zones=3, mb_list=(1, 2), tp_list=(1, 2), dp_list=(1, 2, 8),
+                        pp_list=[1, 3, 8, 24], global_batch=64, t_fwd=1e-3, t_bwd=2e-3, t_upd=1e-5,
+                        layer_params=20_000_000, act=3_000_000, p2p=2_000_000,
+                        cap=np.array([40, 4], np.uint64) * np.uint64(1 << 30), avail=np.full((3, 2), 60),
+                        bw=np.array([[1e10, 1e9, 5e8], [2e9, 1e10, 7e8], [1e9, 3e9, 8e9]]),
+                        egress=np.array([[0, 2e-11, 1e-11], [3e-11, 0, 2e-11], [1e-11, 4e-11, 0]]),
+                        price=np.array([3.0, 1.5]))
+    plan, orc, rng, n, most, zg = _plan(prob), Oracle(prob), np.random.default_rng(count), 97, 24, 6
+    try:
+        desc = np.stack([rng.integers(0, 4, n), np.zeros(n, int), rng.integers(0, 2, n),
+                         rng.integers(0, 3, n), rng.integers(0, 2, n)], 1).astype(np.int32)
+        pa, pb = rng.integers(0, zg, (2, n, most)).astype(np.int32)
+        tps = rng.integers(0, 2, (n, most)).astype(np.int32)
+        P = [int(prob.pp_values[d[0]]) for d in desc]
+        at = rng.integers(0, n, count)
+        for split in (False, True):
+            want = [orc.eval_split_assignment_tp(d[0], d[1], d[3], d[4], tps[i, :P[i]], pa[i, :P[i]], pb[i, :P[i]])
+                    if split else orc.eval_assignment(d[0], d[1], d[3], d[4], d[2], pa[i, :P[i]])
+                    for i, d in enumerate(desc)]
+            args = [torch.from_numpy(x[at]).to("cuda:0") for x in (desc, pa, pb, tps)]
+            out = {f: torch.empty(count, dtype=t, device="cuda:0") for f, t in
+                   (("d_time", torch.float64), ("d_cost", torch.float64), ("d_mem", torch.int64), ("d_mask", torch.int32))}
+            plan.eval_placements(count, args[0], args[1], most, **out,
+                                 **({"d_pools_b": args[2], "d_tps": args[3]} if split else {}))
+            t, c, m, k = (out[f].cpu().numpy() for f in ("d_time", "d_cost", "d_mem", "d_mask"))
+            assert len({e.mask for e in want}) > 2
+            assert np.array_equal(k, np.array([e.mask for e in want])[at])
+            assert np.array_equal(m, np.array([e.peak_mem for e in want])[at])
+            # (the same sums in the same order, up to the rounding of products and quotients)
+            np.testing.assert_allclose(t, np.array([e.iter_time for e in want])[at], rtol=1e-12)
+            np.testing.assert_allclose(c, np.array([e.cost for e in want])[at], rtol=1e-12)
+    finally:
+        plan.destroy()
