@@ -1514,8 +1514,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, P
     S.flags[lane] = 0;
   }
   for (int x = t; x < (int)mul24(min(a.per_wg, (uint32_t)kPlacePlans), ZG); x += kPlaceThreads) cnt[x] = 0;
-  const ListTables L = stage_list_tables(pl, tables);
-  __syncthreads();
+  const ListTables L = stage_list_tables(pl, tables);  // (read behind the loop's first barrier)
   PlacePass done{0, 0, 0};  // the pass whose results are to be written
   for (int b = 0;; b ^= 1) {  // uniform
     if (wv == 1) {  // a lane per plan
@@ -1631,36 +1630,48 @@ __global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, P
         xa += xsec[at_a + (L.zg[min(rap, ZG - 1)] & 255u)];
         if (SPLIT) xb += xsec[at_b + (L.zg[min(rbp, ZG - 1)] & 255u)];
       }
-      double sync = 0.0;
-      if (D > 1) {
-        double link;
-        if (PROFILES) {
-          link = link_bw(pl, za, za, grad);
-          if (SPLIT && zb != za)
-            link = fmin(fmin(link, link_bw(pl, zb, zb, grad)),
-                        fmin(link_bw(pl, za, zb, grad), link_bw(pl, zb, za, grad)));
-        } else {
-          link = L.ring_link[at_a + (SPLIT ? zb : za)];
+      const double ring_bytes = D > 1 ? L.ring[pn.id] * grad : 0.0;
+      if (SPLIT) traffic += ring_bytes * L.both_ways[at_a + zb];
+      auto slowest_sync = [&] {  // of the plan's stages in the lane's row up to here
+        double sync = 0.0;
+        if (D > 1) {
+          double link;
+          if (PROFILES) {
+            link = link_bw(pl, za, za, grad);
+            if (SPLIT && zb != za)
+#pragma unroll 1
+              for (int q = 1; q < 4; ++q) link = fmin(link, link_bw(pl, q == 2 ? za : zb, q == 3 ? za : zb, grad));  // within b, there, back
+          } else {
+            link = L.ring_link[at_a + (SPLIT ? zb : za)];
+          }
+          sync = ring_bytes / link;
         }
-        const double ring_bytes = L.ring[pn.id] * grad;
-        sync = ring_bytes / link;
-        if (SPLIT) traffic += ring_bytes * L.both_ways[at_a + zb];
-      }
+        return place_row_max((unsigned long long)__double_as_longlong(sync), i);
+      };
+      // (the profiles of four links go last, one after the other: with the rest of the stage behind them
+      // they took 112 registers instead of 103.  Everywhere else the quotient is better started early.)
+      constexpr bool kLinksLast = SPLIT && PROFILES;
+      unsigned long long most_sync = 0;
+      if (!kLinksLast) most_sync = slowest_sync();
       S.term[0][e] = ca + xa;
       if (SPLIT) S.term[1][e] = cb + xb;
       const double gpus = dpd * L.tpd[ti];  // (whole numbers below 2^53)
       S.term[2][e] = gpus * (SPLIT ? 0.5 * (L.price[ga] + L.price[gb]) : L.price[ga]);
       S.term[3][e] = traffic;
       // (an LDS atomic takes a cycle per lane on the same word, and a plan's stages lie side by side)
-      const unsigned long long most_sync = place_row_max((unsigned long long)__double_as_longlong(sync), i);
       const unsigned long long most_upd = place_row_max((unsigned long long)__double_as_longlong(SPLIT ? fmax(ua, ub) : ua), i);
       const unsigned long long most = place_row_max(m1 > m2 ? m1 : m2, i);
-      if ((lane & 15) == 15 || i == P - 1) {
-        atomicMax(&S.sync[own], most_sync);
+      const bool last = (lane & 15) == 15 || i == P - 1;
+      if (last) {
+        if (!kLinksLast) atomicMax(&S.sync[own], most_sync);
         atomicMax(&S.upd[own], most_upd);
         atomicMax(&S.peak[own], most);
       }
       if (flags) atomicOr(&S.flags[own], flags);
+      if (kLinksLast) {
+        most_sync = slowest_sync();
+        if (last) atomicMax(&S.sync[own], most_sync);
+      }
     }
     if (wv == 1) pp = place_depth(a, d);
     __syncthreads();

@@ -1145,8 +1145,9 @@ def test_long_lists_of_placements_give_what_short_ones_give(torch_cuda, count, d
         plan.destroy()
 
 
-@pytest.mark.parametrize("count", [1024, 1025, 1281, 32_768, 32_769, 90_001])
-def test_lists_of_placements_of_every_length_match_the_oracle(torch_cuda, count):
+@pytest.mark.parametrize("count,profiles", [(1024, False), (1025, False), (1281, False), (32_768, False),
+                                            (32_769, False), (90_001, False), (1281, True), (70_001, True)])
+def test_lists_of_placements_of_every_length_match_the_oracle(torch_cuda, count, profiles):
     # one plan a workgroup and two; runs of one pass on four workgroups per compute unit, on five, runs of
     # several passes: the plans of a list are drawn from a few whose values the oracle gives
     torch = torch_cuda
@@ -1157,6 +1158,8 @@ def test_lists_of_placements_of_every_length_match_the_oracle(torch_cuda, count)
                         bw=np.array([[1e10, 1e9, 5e8], [2e9, 1e10, 7e8], [1e9, 3e9, 8e9]]),
                         egress=np.array([[0, 2e-11, 1e-11], [3e-11, 0, 2e-11], [1e-11, 4e-11, 0]]),
                         price=np.array([3.0, 1.5]))
+    if profiles:
+        prob = prob.with_bw_poly(W.bandwidth_poly(prob))
     plan, orc, rng, n, most, zg = _plan(prob), Oracle(prob), np.random.default_rng(count), 97, 24, 6
     try:
         desc = np.stack([rng.integers(0, 4, n), np.zeros(n, int), rng.integers(0, 2, n),
