@@ -169,6 +169,7 @@ std::vector<uint32_t> order_by(const float *values, size_t n, bool descending) {
 
 struct sailor_plan {
   DevPlan dev{};
+  DirectMem direct_mem{};
   DeviceArena arena;
   std::vector<ShapeRec> shapes;
   std::vector<BlockRec> blocks;
@@ -1061,7 +1062,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   shape_n.reserve(NS);
   for (const ShapeRec &sh : pl->shapes)
     shape_n.push_back((uint32_t)((sh.n[0] - 1) & 255) | (uint32_t)((sh.n[1] - 1) & 255) << 8 | (uint32_t)((sh.n[2] - 1) & 255) << 16);
-  slab.input(&d.shape_n, shape_n.data(), NS);
+  slab.input(&pl->direct_mem.shape_n, shape_n.data(), NS);
   slab.input(&d.blocks, pl->blocks.data(), pl->blocks.size());
   // per-unit tables: one entry per unit as laid out (units dropped later leave room for the
   // parts of units that are cut); sailor_set_scan_unit_parts(n) cuts every unit into n parts
@@ -1106,7 +1107,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&d.need, slots * MB * DP);
   slab.table(&d.syncz, slots * Z);
   slab.table(&d.upd, slots * GX);
-  slab.table(&d.su, slots * ZG);
+  slab.table(&pl->direct_mem.su, slots * ZG);
   // selection scratch (umin_l lies behind umin_s: creation reads both back in one copy)
   slab.table(&pl->umin_s, 2 * unit_cap);
   slab.table(&pl->counters, (size_t)2 * CNT_COUNT);
@@ -1130,9 +1131,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(p->avail, ZGr), nullptr, pl->d_avail, 0u);
   k_small_tables<<<1, 256>>>(d);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
-  k_direct_tables<<<1, 256>>>(d);
+  k_direct_tables<<<1, 256>>>(d, pl->direct_mem);
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
-  k_shape_agg<<<(unsigned)NS, kShapeAggThreads, (size_t)3 * TP * (Z + GX) * sizeof(float)>>>(d);
+  k_shape_agg<<<(unsigned)NS, kShapeAggThreads, (size_t)3 * TP * (Z + GX) * sizeof(float)>>>(d, pl->direct_mem);
   CREATE_TRY(hipGetLastError());
   {
     // Two passes over the space order the scan.  The first ignores the availability and records,
@@ -1377,7 +1378,7 @@ sailor_status sailor_eval_batch(sailor_plan *pl, uint64_t first, uint64_t count,
   const uint64_t chunks = (count + kDirectThreads - 1) / kDirectThreads;
   launch(k_eval_direct, dim3((unsigned)std::min<uint64_t>(chunks, kDirectWorkgroups)), dim3(kDirectThreads),
          direct_lds_bytes(pl->dev), st,
-         timed ? pl->ev[3] : nullptr, timed ? pl->ev[1] : nullptr, pl->dev, a);
+         timed ? pl->ev[3] : nullptr, timed ? pl->ev[1] : nullptr, pl->dev, a, pl->direct_mem);
   HIP_TRY(hipGetLastError());
   pl->total_timed = false;
   pl->scan_timed = timed;

@@ -161,10 +161,16 @@ struct DevPlan {
   uint64_t *need;              // [..][MB][DP] max over stages of model + activation bytes
   float *syncz;                // [..][Z] slowest stage: gradient bytes / intra-zone bandwidth
   float *upd;                  // [..][GX] slowest stage update
-  float2 *su;                  // [..][ZG] both by pool, for lane-dependent pools (the scan, which reads a segment
-                               // as a whole, is 3 % slower with these: 2 MB beside an L2 of 4)
-  const uint32_t *shape_n;     // [n_shapes] a shape's stages per segment once more, less one, a byte each
 };
 static_assert(offsetof(DevPlan, blocks) == offsetof(DevPlan, shapes) + sizeof(void *), "read with one load");
+
+// What only the evaluator of index lists reads.  (Within DevPlan, which every kernel takes, it moved the hidden
+// arguments of k_units, the workgroup's size among them, to a 64-byte line of their own: one more trip to
+// memory, the pass over a budget's few units 12.3 instead of 12.1 us.)
+struct DirectMem {
+  float2 *su;                  // [shape][TP][3][ZG] syncz and upd by pool, for lane-dependent pools (the scan, which
+                               // reads a segment as a whole, is 3 % slower with these: 2 MB beside an L2 of 4)
+  const uint32_t *shape_n;     // [n_shapes] a shape's stages per segment once more, less one, a byte each
+};
 
 }  // namespace sailor

@@ -211,7 +211,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // barrier orders it.  (A fence for the whole device behind the tables had every workgroup write its
 // die's L2 back: about 1 000 shapes with pairs of types 218 us, without it 69.)
 constexpr int kShapeAggThreads = 512;
-__global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
+__global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, DirectMem dm) {
   extern __shared__ float agg_lds[];  // [TP][3][Z], [TP][3][GX]
   const uint32_t shp = blockIdx.x;
   const ShapeRec sh = pl.shapes[shp];
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl) {
   __syncthreads();
   for (int it = t; it < TP * 3 * pl.ZG; it += nt) {
     const int p = it % pl.ZG, ks = it / pl.ZG, seg = ks % 3, k = ks / 3, z = p / GX, g = p - z * GX;
-    pl.su[(slot0 + k * 3 + seg) * pl.ZG + p] = make_float2(syncz[ks * pl.Z + z], upd[ks * GX + g]);
+    dm.su[(slot0 + k * 3 + seg) * pl.ZG + p] = make_float2(syncz[ks * pl.Z + z], upd[ks * GX + g]);
   }
   // memok bit d: largest worker of the segment fits the type's memory
   for (int it = t; it < TP * 3 * GX * MB; it += nt) {
@@ -2174,7 +2174,7 @@ __device__ __forceinline__ DirectTables direct_tables_at(const DevPlan &pl, uint
 }
 
 // (after k_small_tables, one workgroup)
-__global__ void k_direct_tables(DevPlan pl) {
+__global__ void k_direct_tables(DevPlan pl, DirectMem dm) {
   const DirectTables T = direct_tables_at(pl, pl.direct_tables);
   const int t = threadIdx.x, nt = blockDim.x;
   for (int i = t; i < pl.n_blocks; i += nt) {
@@ -2192,7 +2192,7 @@ __global__ void k_direct_tables(DevPlan pl) {
   for (int i = t; i < pl.DP; i += nt) { T.cd[i] = pl.cd_f[i]; T.dph[i] = pl.dph_f[i]; T.dp[i] = pl.vals[i]; }
   for (int i = t; i < pl.MB * pl.DP; i += nt) { T.nbm1[i] = pl.nbm1_f[i]; T.nb[i] = pl.nb[i]; }
   for (int i = t; i < pl.TP; i += nt) T.tp[i] = pl.vals[pl.DP + i];
-  if (pl.n_shapes <= kDirectShapes) for (int i = t; i < pl.n_shapes; i += nt) T.n[i] = pl.shape_n[i];
+  if (pl.n_shapes <= kDirectShapes) for (int i = t; i < pl.n_shapes; i += nt) T.n[i] = dm.shape_n[i];
 }
 
 // n / d for n < 2^20 and n d < 2^40 or so by a product in single precision: inv is 1 / d rounded up by two
@@ -2224,7 +2224,7 @@ __device__ __forceinline__ double divide_by(double n, double d, double inv, doub
 // a copy).  Held to fewer registers for seven waves per SIMD instead of five it spills: 41.3 us.
 constexpr int kDirectThreads = 256;
 constexpr unsigned kDirectWorkgroups = 2048;  // eight per compute unit: all resident, one copy of the tables each
-__global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, EvalArgs a) {
+__global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, EvalArgs a, DirectMem dm) {
   extern __shared__ uint64_t direct_lds[];
   uint32_t *const lds = reinterpret_cast<uint32_t *>(direct_lds);
   const DirectTables L = direct_tables_at(pl, lds);
@@ -2295,14 +2295,14 @@ __global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, Eval
       const int nb = L.nb[md];
       mask = nb == 0 ? 4u : 0u;
       if (nb != 0) {
-        const uint32_t stages = in_lds ? L.n[shape] : pl.shape_n[shape];
+        const uint32_t stages = in_lds ? L.n[shape] : dm.shape_n[shape];
         float4 ta[3];
         float2 su[3];
         uint64_t need[3];
         uint32_t z[3], g[3];
         const uint32_t slot0 = shape * slots;
         const float4 *const ta_at = pl.ta + ((uint64_t)slot0 * gxmb + mb);
-        const float2 *const su_at = pl.su + (uint64_t)slot0 * ZG;
+        const float2 *const su_at = dm.su + (uint64_t)slot0 * ZG;
         const uint64_t *const need_at = pl.need + ((uint64_t)slot0 * mbdp + md);
 #pragma unroll
         for (int j = 0; j < 3; ++j) {  // what comes from memory is requested before any of it is used
