@@ -209,7 +209,9 @@ sailor_status sailor_plan_destroy(sailor_plan *plan);
  * availability are kept (cf. the reuse noted under H2, Sec. 4.2.1).  The table is copied
  * before the call returns; it reaches the device, and the quota table derived from it is
  * rebuilt there, at the start of the next evaluation or selection call, on that call's
- * stream. */
+ * stream.  If that call is captured into a graph, every replay brings along the table that was
+ * set last by then, and the next call outside the graph still brings its own; replays have to
+ * have finished before the table is replaced. */
 sailor_status sailor_plan_set_avail(sailor_plan *plan, const int32_t *avail);
 
 /* Re-planning (Sec. 4.4: the planner is invoked again whenever the availability changes;

@@ -187,11 +187,9 @@ struct sailor_plan {
   ResultHeader last_hdr{};         // of the last successful selection
   bool have_hdr = false;
   int32_t *d_avail = nullptr;
-  int32_t *h_avail = nullptr;      // pinned staging of the availability table (behind h_result)
+  int32_t *h_avail = nullptr;      // the availability table, host-mapped (behind h_result)
   const int32_t *h_avail_dev = nullptr;  // the same memory as the device addresses it
   bool avail_dirty = false;        // h_avail is newer than the device copy
-  bool upload_pending = false;     // an asynchronous upload from h_avail was enqueued
-  hipEvent_t ev_upload = nullptr;
   // scratch of the selection pipeline
   float *umin_s = nullptr, *umin_l = nullptr;
   float *lb_time = nullptr, *lb_cost = nullptr;  // per unit: smallest time / cost with availability ignored
@@ -590,16 +588,16 @@ AvailTable avail_table(const sailor_plan *pl) { return avail_table(pl->h_avail, 
 // the quota table from it.
 sailor_status refresh_avail(sailor_plan *pl, hipStream_t st) {
   if (!pl->avail_dirty) return SAILOR_OK;
-  pl->avail_gen += 1;
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();  // (the launch reports it)
-  const bool mapped = capturing != hipStreamCaptureStatusNone;  // replays read the table of their time
-  k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, avail_table(pl), mapped ? pl->h_avail_dev : nullptr,
-                                                     pl->d_avail, pl->avail_gen);
-  if (mapped) {
-    HIP_TRY(hipEventRecord(pl->ev_upload, st));
-    pl->upload_pending = true;
+  if (capturing != hipStreamCaptureStatusNone) {
+    // Replays read the table of their time (the caller has them finish before it sets another).  Nothing
+    // has run yet: the table stays due for calls outside the graph.  What a replay changes counts as
+    // newer than any kept minimum.
+    k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, AvailTable{}, pl->h_avail_dev, pl->d_avail, ~0u);
+    return SAILOR_OK;
   }
+  k_quota_table<<<quota_grid(pl->dev), 256, 0, st>>>(pl->dev, avail_table(pl), nullptr, pl->d_avail, ++pl->avail_gen);
   pl->avail_dirty = false;
   return SAILOR_OK;
 }
@@ -939,7 +937,6 @@ sailor_status sailor_plan_destroy(sailor_plan *pl) {
   (void)hipSetDevice(pl->device);
   pl->arena.release();
   if (pl->h_result) (void)hipHostFree(pl->h_result);
-  if (pl->ev_upload) (void)hipEventDestroy(pl->ev_upload);
   for (hipEvent_t e : pl->ev)
     if (e) (void)hipEventDestroy(e);
   delete pl;
@@ -1023,7 +1020,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
 
   // inputs, copied as they are
   slab.input(&d.avail, p->avail, ZGr);
-  CREATE_TRY(hipEventCreateWithFlags(&pl->ev_upload, hipEventDisableTiming));
   d.P_max = 0;
   for (int ip = 0; ip < p->n_pp; ++ip) d.P_max = std::max(d.P_max, (int)p->pp_values[ip]);
   d.W_max = d.P_max * p->tp_values[TP - 1];
@@ -1308,10 +1304,6 @@ sailor_status sailor_plan_set_avail(sailor_plan *pl, const int32_t *avail) {
   for (int i = 0; i < pl->dev.ZGr; ++i)
     if (avail[i] < 0) return SAILOR_EINVAL;
   HIP_TRY(hipSetDevice(pl->device));
-  if (pl->upload_pending) {  // the staging buffer may still be read by an earlier upload
-    HIP_TRY(hipEventSynchronize(pl->ev_upload));
-    pl->upload_pending = false;
-  }
   std::memcpy(pl->h_avail, avail, pl->dev.ZGr * sizeof(int32_t));
   pl->avail_dirty = true;  // uploaded, with the quota table, by the next call on its stream
   return SAILOR_OK;

@@ -454,7 +454,7 @@ __device__ __forceinline__ void acc_finish(const Acc &p, const LaneC &lc, float 
 // replica of the plan fit the real pool for the degrees whose bit is set.
 // gen: the availability generation (0 while the plan is built); when an entry of qh changes,
 // row_gen[0] receives it, so that a scan can tell whether the shared-pool checks of a unit's
-// last evaluation still hold.
+// last evaluation still hold.  (A captured call passes the largest number: its replays come at any time.)
 //
 // table: the availability, which travels in the kernel's arguments -- no upload in front of the
 // kernel, no trip over the bus inside it and nothing of the host's to wait for before it is used

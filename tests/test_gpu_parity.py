@@ -683,6 +683,71 @@ def test_eval_batch_replays_from_a_captured_graph(torch_cuda):
         plan.destroy()
 
 
+@pytest.mark.parametrize("mixed", [False, True])
+def test_calls_captured_while_a_new_availability_is_due(torch_cuda, mixed):
+    # replays read the table that the host holds at the time; calls outside the graph see it too, before
+    # the first replay and behind a replay that has brought it to the device (kept minima included)
+    torch = torch_cuda
+    prob = W.config2()
+    if mixed:
+        prob = W.tiny_problem(77, n_layers=6, n_types=2, n_zones=2, max_segments=3, seg3_max_pp=6,
+                              partitions_per_pp=2).with_mixed_types()
+    rng = np.random.default_rng(4)
+    tables = [np.where(rng.random(prob.avail.shape) < 0.2, 0, rng.integers(1, prob.avail.max() + 1, prob.avail.shape))
+              .astype(np.int32) for _ in range(8)]
+    orcs = [Oracle(prob.with_avail(a)) for a in tables]
+    plan, kept = _plan(prob), _plan(prob)
+    kept.set_incremental(True)
+    try:
+        n, dev = orcs[0].num_candidates, "cuda:0"
+        out = [torch.zeros(n, dtype=d, device=dev) for d in (torch.float32, torch.float32, torch.int64, torch.int32)]
+        idx = torch.from_numpy(rng.integers(0, n, 4096)).to(dev)
+        ti = torch.zeros(4096, dtype=torch.float32, device=dev)
+        side = torch.cuda.Stream()
+        st = side.cuda_stream
+        side.wait_stream(torch.cuda.current_stream())
+
+        def calls():
+            for p in (plan, kept):
+                p.eval_batch(0, n, d_time=out[0], d_cost=out[1], d_mem=out[2], d_mask=out[3], stream=st)
+                p.eval_batch(0, 4096, d_indices=idx, d_time=ti, stream=st)
+
+        def best(p, orc):
+            got, want = p.best_plan(stream=st), orc.best(n_threads=THREADS)
+            assert (got is None) == (want is None)
+            if want is not None:
+                check_result(got, want, orc)
+
+        with torch.cuda.stream(side):
+            calls()
+            side.synchronize()
+            for p in (plan, kept):
+                p.set_avail(tables[0])
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                calls()
+        best(plan, orcs[0])
+        best(kept, orcs[0])
+        for table, orc in zip(tables, orcs):
+            torch.cuda.synchronize()  # the replays have finished
+            for p in (plan, kept):
+                p.set_avail(table)
+            for x in (*out, ti):
+                x.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            got = (out[0].cpu().numpy(), out[1].cpu().numpy(), out[2].cpu().numpy().view(np.uint64),
+                   out[3].cpu().numpy().view(np.uint32))
+            assert_eval_parity(got, orc.eval_batch(n_threads=THREADS))
+            assert np.array_equal(ti.cpu().numpy(), got[0][idx.cpu().numpy()])
+            best(plan, orc)
+            best(kept, orc)
+    finally:
+        plan.destroy()
+        kept.destroy()
+
+
 def test_independent_plans_serve_two_host_threads(torch_cuda):
     # one plan per thread, each on a stream of its own: the calls overlap in time (ctypes
     # releases the interpreter lock) and every one must return what the oracle selects
