@@ -748,6 +748,32 @@ def test_calls_captured_while_a_new_availability_is_due(torch_cuda, mixed):
         kept.destroy()
 
 
+@pytest.mark.parametrize("pps,n_shapes", [([2, 8, 64], 2048), ([1, 2, 8, 64], 2049)])
+def test_index_lists_where_the_shapes_leave_lds(torch_cuda, pps, n_shapes):
+    # the stages of up to 2 048 shapes lie in LDS, those of more are read from memory
+    L, rng = 64, np.random.default_rng(6)
+    shape = (2, 2, 2, L)
+    fwd = rng.uniform(0.5e-3, 2e-3, shape)
+    prob = make_problem(n_layers=L, n_types=2, n_zones=2, mb_list=(1, 2), tp_list=(1, 2), dp_list=(1, 2, 4), pp_list=pps,
+                        max_segments=3, seg3_max_pp=64, global_batch=32, uniform_layers=False, t_fwd=fwd, t_bwd=2 * fwd,
+                        t_upd=1e-5, layer_params=rng.integers(1_000_000, 90_000_000, L), act=3_000_000, p2p=2_000_000,
+                        cap=np.array([8, 3], np.uint64) * np.uint64(1 << 30), node=np.array([2, 1]),
+                        avail=np.array([[120, 60], [40, 250]]), bw=np.array([[1e10, 1e9], [2e9, 1e10]]),
+                        price=np.array([3.0, 1.5]), egress=np.array([[0, 2e-11], [1e-11, 0]]))
+    cuts = sum(1 + (p - 1) + (p - 1) * (p - 2) // 2 for p in pps)
+    assert cuts == n_shapes
+    plan, orc = _plan(prob), Oracle(prob)
+    try:
+        n = orc.num_candidates
+        assert plan.num_candidates() == n
+        idx = np.concatenate([rng.integers(0, n, 200_000), [0, n - 1]]).astype(np.uint64)
+        want = orc.eval_batch(indices=idx, n_threads=THREADS)
+        assert len(set((want[3] & 15).tolist())) > 4
+        assert_eval_parity(gpu_eval(torch_cuda, plan, 0, len(idx), indices=idx), want)
+    finally:
+        plan.destroy()
+
+
 def test_independent_plans_serve_two_host_threads(torch_cuda):
     # one plan per thread, each on a stream of its own: the calls overlap in time (ctypes
     # releases the interpreter lock) and every one must return what the oracle selects
@@ -929,9 +955,11 @@ def test_threshold_among_more_units_than_a_workgroup_keeps(torch_cuda, form):
                         bw=np.array([[1e10, 1e9], [1e9, 1e10]])).with_per_segment_tp(True)
     plan, orc = _plan(prob), Oracle(prob)
     try:
-        n_units = 64 * 253 + 16 * 23  # three and two segments of the deepest pipeline alone
-        assert n_units > 8192 and plan.num_candidates() == orc.num_candidates
+        assert plan.num_candidates() == orc.num_candidates
         for k in (1, 17, 64, 65):
             check_topk(plan.topk(k), orc.topk(k, n_threads=4), MAX_THROUGHPUT, orc)
+        # the units that the plan keeps: beyond what the digit form holds in registers, and where the values
+        # are distinct beyond what the rank form holds, too (pools without room take units away)
+        assert plan.last_scan()[1] > (8192 if form == "scarce" else 16384)
     finally:
         plan.destroy()
