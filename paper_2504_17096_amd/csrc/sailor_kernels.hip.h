@@ -209,7 +209,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // stage), the walks are unrolled so that their loads are in flight together, and eight waves per
 // shape shorten them.  What one thread writes and another reads stays within the workgroup: a
 // barrier orders it.  (A fence for the whole device behind the tables had every workgroup write its
-// die's L2 back: about 1 000 shapes with pairs of types 218 us, without it 69.)
+// die's L2 back: about 1 000 shapes with pairs of types 218 us, without it 64.)
 constexpr int kShapeAggThreads = 512;
 __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, DirectMem dm) {
   extern __shared__ float agg_lds[];  // [TP][3][Z], [TP][3][GX]
@@ -217,6 +217,12 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, Dire
   const ShapeRec sh = pl.shapes[shp];
   const int G = pl.G, GX = pl.GX, MB = pl.MB, TP = pl.TP, DP = pl.DP, P = sh.P;
   const int t = threadIdx.x, nt = blockDim.x;
+  // (first stage and number of stages, 16 bits a segment: a record indexed by lane lies in scratch memory,
+  // 48 bytes a lane, and about 1 000 shapes with pairs of types took 69 us instead of 64)
+  const uint64_t los = sh.lo[0] | (uint64_t)sh.lo[1] << 16 | (uint64_t)sh.lo[2] << 32;
+  const uint64_t ns = sh.n[0] | (uint64_t)sh.n[1] << 16 | (uint64_t)sh.n[2] << 32;
+  auto lo_of = [&](int seg) { return (int)((los >> (16 * seg)) & 0xFFFFu); };
+  auto n_of = [&](int seg) { return (int)((ns >> (16 * seg)) & 0xFFFFu); };
   const size_t row_stride = (size_t)MB * TP * pl.row_w;          // from stage to stage
   const double *const rows = pl.st_row + sh.row_stage * row_stride;
   // need[tp][seg][mb][dp], syncz, upd
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, Dire
       const uint64_t act = pl.act[m * TP + k];
       const double *const shard_bytes = rows + (size_t)k * pl.row_w + 2 * G;
 #pragma unroll 4
-      for (int i = sh.lo[seg]; i < sh.lo[seg] + sh.n[seg]; ++i) {
+      for (int i = lo_of(seg); i < lo_of(seg) + n_of(seg); ++i) {
         const int64_t in_flight = (int64_t)(P - i) < nb ? (int64_t)(P - i) : nb;
         const uint64_t b = (uint64_t)__double_as_longlong(shard_bytes[i * row_stride]) +
                            act_bytes((int)in_flight, pl.st_n[sh.row_stage + i], act);
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, Dire
     double mx = 0.0;  // seconds of the slowest stage's gradient buffer over the zone's link
     if (seg < sh.s) {
       const double *const grads = rows + (size_t)k * pl.row_w + 2 * G + 1;
-      const int lo = sh.lo[seg], hi = lo + sh.n[seg];
+      const int lo = lo_of(seg), hi = lo + n_of(seg);
       if (pl.n_bw_coef > 0) {
         for (int i = lo; i < hi; ++i) {
           const double bytes = grads[i * row_stride];
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, Dire
     double mx = 0.0;
     if (seg < sh.s) {
 #pragma unroll 4
-      for (int i = sh.lo[seg]; i < sh.lo[seg] + sh.n[seg]; ++i) {
+      for (int i = lo_of(seg); i < lo_of(seg) + n_of(seg); ++i) {
         mx = fmax(mx, pl.st_u[((size_t)(sh.row_stage + i) * G + ga) * TP + k]);
         mx = fmax(mx, pl.st_u[((size_t)(sh.row_stage + i) * G + gb) * TP + k]);
       }
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(kShapeAggThreads) void k_shape_agg(DevPlan pl, Dire
     const int ga = pl.xt[g] & 255, gb = pl.xt[g] >> 8;
     float4 v = make_float4(0.f, 0.f, kNegInf, kNegInf);
     if (seg < sh.s) {
-      const int lo = sh.lo[seg], n = sh.n[seg];
+      const int lo = lo_of(seg), n = n_of(seg);
       // replicas of two types: the slower one sets the stage's pace (straggler, Sec. 4.3)
       auto stage = [&](int i) {
         return fmax(pl.st_c[(((size_t)(sh.row_stage + i) * G + ga) * MB + m) * TP + k],
