@@ -2224,14 +2224,16 @@ __device__ __forceinline__ double divide_by(double n, double d, double inv, doub
 // So the small tables, the shapes' stages among them, are in LDS, a candidate of three segments gathers
 // nine times (aggregate, seconds of all-reduce and update, bytes of each segment), and no load waits for
 // another: an index is decoded from its block's record in LDS, its two 64-bit divisions by products in
-// double precision (indices from 2^52 on divide).  The lanes of a wave go through the segments together,
+// double precision (a space has at most 2^29 units of at most 8 x 24 x 128 x 127 plans: below 2^51).  The lanes of a wave go through the segments together,
 // whether they have one, two or three (apart, a wave ran the code of each number it held), quotas
 // compare with what the table of degrees and pools has room for, and products are 24-bit or in single
 // precision (32-bit ones run at a quarter of the rate).
 // 1 000 003 random candidates: 42.7 -> 35.4 us (28 MB of indices and outputs; the same bytes take 5 us as
 // a copy).  Held to fewer registers for seven waves per SIMD instead of five it spills: 41.3 us.
 constexpr int kDirectThreads = 256;
-constexpr unsigned kDirectWorkgroups = 2048;  // eight per compute unit: all resident, one copy of the tables each
+// (five workgroups fit a compute unit, 1 280 in all; the same time with that many, within 1 %: 1 000 003
+// candidates 35.7 us, with 1 280 35.4; 250 000 12.8 and 12.9; 30 000 6.5 and 6.6)
+constexpr unsigned kDirectWorkgroups = 2048;
 __global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, EvalArgs a, DirectMem dm) {
   extern __shared__ uint64_t direct_lds[];
   uint32_t *const lds = reinterpret_cast<uint32_t *>(direct_lds);
@@ -2248,7 +2250,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, Eval
   const uint32_t mbtp = MB * TP, mbtpdp = mbtp * DP, gxmb = GX * MB, mbdp = MB * DP, slots = 3 * TP;
   const float inv_mb = float_inverse(MB), inv_mbtp = float_inverse(mbtp), inv_mbtpdp = float_inverse(mbtpdp),
               inv_gx = float_inverse(GX), inv_zg1 = float_inverse(ZG > 1 ? ZG - 1 : 1), inv_tp = float_inverse(TP);
-  const bool exact_double = pl.N < (1ull << 52), in_lds = pl.n_shapes <= kDirectShapes;
+  const bool in_lds = pl.n_shapes <= kDirectShapes;
   const double inv_inner = 1.0 / (double)pl.inner;
   int first_step = 1;  // of the search for an index's block
   while (2 * first_step < pl.n_blocks) first_step *= 2;
@@ -2266,19 +2268,10 @@ __global__ __launch_bounds__(kDirectThreads) void k_eval_direct(DevPlan pl, Eval
       }
       const DirectBlock blk = L.blocks[b];
       const int S = (int)blk.s;
-      uint32_t shape, o, in;
       const uint64_t within = idx - blk.off;
-      if (exact_double) {
-        double rem, in_d;
-        shape = blk.first_shape + (uint32_t)divide_by((double)within, blk.size, blk.inv_size, rem);
-        o = (uint32_t)divide_by(rem, (double)pl.inner, inv_inner, in_d);
-        in = (uint32_t)in_d;
-      } else {
-        const uint64_t size = pl.blocks[b].shape_size, rem = within % size;
-        shape = blk.first_shape + (uint32_t)(within / size);
-        o = (uint32_t)(rem / pl.inner);
-        in = (uint32_t)(rem - (uint64_t)o * pl.inner);
-      }
+      double rem, in_d;
+      const uint32_t shape = blk.first_shape + (uint32_t)divide_by((double)within, blk.size, blk.inv_size, rem);
+      uint32_t o = (uint32_t)divide_by(rem, (double)pl.inner, inv_inner, in_d), in = (uint32_t)in_d;
       uint32_t p[3], k[3];  // pool and TP index of each segment
       p[0] = float_div(in, inv_mbtpdp);
       in -= mul24(p[0], mbtpdp);
