@@ -1734,6 +1734,7 @@ struct ReplicaLds {
   ReplicaPlan plan[kReplicaWaves];
   ReplicaSums part[kReplicaWaves];
 };
+static_assert(sizeof(ReplicaLds) % 16 == 0, "the tables behind it hold 16-byte words");
 
 __host__ __device__ inline size_t replica_lds_bytes(const DevPlan &pl) {
   return sizeof(ReplicaLds) + list_tables_words(pl) * 8 + kReplicaWaves * (size_t)pl.ZGr * sizeof(int32_t);
@@ -1887,7 +1888,7 @@ __device__ __forceinline__ void replica_write(const ReplicaArgs &a, const ListTa
 // took 225 us; they take 45 us now, half of the workgroups being done after 12 us: what is left is
 // the chain of trips in front of a plan and the workgroups that hold several large plans.
 __global__ __launch_bounds__(kReplicaWaves * 64) void k_eval_replicas(DevPlan pl, ReplicaArgs a) {
-  extern __shared__ double rep_lds[];
+  extern __shared__ ulonglong2 rep_lds[];
   ReplicaLds &S = *reinterpret_cast<ReplicaLds *>(rep_lds);
   double *const tables = reinterpret_cast<double *>(&S + 1);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
