@@ -1548,19 +1548,20 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
 // 7.6 us with five, 6.7 with four; 9 000: 8.7 and 8.25; 25 000: 10.65 and 10.3).  Beyond, the fifth saves a
 // second pass (33 000 plans: 11.3 us with five, 13.3 with four).
 static void launch_placements(const sailor_plan *pl, PlaceArgs a, hipStream_t st) {
-  const uint64_t per_cu = place_workgroups_per_cu(pl->dev);
+  const auto kernel = pl->dev.n_bw_coef > 0 ? (a.pools_b ? k_eval_placements<true, true> : k_eval_placements<false, true>)
+                                            : (a.pools_b ? k_eval_placements<true, false> : k_eval_placements<false, false>);
+  // (five or four by registers, fewer where the tables need the LDS.  The runtime keeps what it works out:
+  // 0.1 us a call)
+  int fit = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, (const void *)kernel, kPlaceThreads, place_lds_bytes(pl->dev, kPlacePlans)) != hipSuccess)
+    (void)hipGetLastError();
+  const uint64_t per_cu = (uint64_t)std::max(1, fit);
   const uint64_t slots = kPlaceUnits * (a.count <= kPlaceShort ? std::min<uint64_t>(4, per_cu) : per_cu);
   const uint64_t rounds = (a.count + slots * kPlaceLongest - 1) / (slots * kPlaceLongest);
   a.per_wg = (uint32_t)((a.count + slots * rounds - 1) / (slots * rounds));
   const unsigned grid = (unsigned)((a.count + a.per_wg - 1) / a.per_wg);
   const size_t lds = place_lds_bytes(pl->dev, a.per_wg);
-  if (pl->dev.n_bw_coef > 0) {
-    if (a.pools_b) k_eval_placements<true, true><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
-    else k_eval_placements<false, true><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
-  } else {
-    if (a.pools_b) k_eval_placements<true, false><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
-    else k_eval_placements<false, false><<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
-  }
+  kernel<<<grid, kPlaceThreads, lds, st>>>(pl->dev, a);
 }
 
 sailor_status sailor_eval_placements(sailor_plan *pl, uint64_t count, const int32_t *d_desc,

@@ -1406,13 +1406,6 @@ __host__ __device__ inline size_t place_lds_bytes(const DevPlan &pl, uint32_t pe
          (size_t)(per_wg < (uint32_t)kPlacePlans ? per_wg : (uint32_t)kPlacePlans) * pl.ZGr * sizeof(int32_t);
 }
 
-// Workgroups a compute unit holds at a time: its LDS is handed out in units of 1 280 bytes.
-inline uint64_t place_workgroups_per_cu(const DevPlan &pl) {
-  const size_t units = (place_lds_bytes(pl, kPlacePlans) + 1279) / 1280;
-  const size_t by_registers = pl.n_bw_coef > 0 ? 4 : 5;
-  return std::min(by_registers, std::max<size_t>(1, 128 / units));
-}
-
 // Sum (and maximum) over a plan's stages in stage order, for a lane per plan.
 __device__ __forceinline__ void place_sum(const double *v, int P, double &sum, double &slowest) {
   sum = 0.0;
