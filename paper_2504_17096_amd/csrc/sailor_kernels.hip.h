@@ -1150,7 +1150,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
 
 // The form that looks for the k-th value by rank (k_select_kth, RANK) is taken for more values than the
 // other one keeps in registers and k up to kKthByRank; beyond kKthRanked candidates it, too, takes the digits.
-constexpr uint32_t kKthByRank = 64, kKthByRankFrom = 8192, kKthRanked = 512;
+constexpr uint32_t kKthByRank = 128, kKthByRankFrom = 8192, kKthRanked = 512;
 
 // The smallest value of a wave, in every lane.
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
@@ -1179,6 +1179,9 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 // to it.  Those -- hundreds, units being dealt to lanes by their place in the launch order -- go to LDS,
 // where each counts its rank.  The 64th of the minima of 9.2e8 plans' units, and the list: 15.7 -> 9.7 us, of
 // a query of 136 -> 132.  Not below 8 192 values, which the other form keeps in registers: 1 to 5 us slower there.
+// Nor for a larger k, for which the waves name more and hundreds become thousands, which take the digits after
+// all (that query, by digits and by rank: k = 65 137.9 and 134.4 us, 128 144.0 and 143.0, 256 175.5 and 181.4,
+// 512 245.9 and 249.1).
 template <int THREADS, bool RANK = false>
 __global__ __launch_bounds__(THREADS) void k_select_kth(const float *vals, int stride_words,
                                                      const uint32_t *count, uint32_t cap,

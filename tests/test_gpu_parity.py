@@ -944,7 +944,7 @@ def test_scan_at_the_edges_of_its_lane_space(torch_cuda, n_dp, mixed):
 def test_threshold_among_more_units_than_a_workgroup_keeps(torch_cuda, form):
     # 290 shapes x a TP degree per segment: over 8 192 units, whose k-th smallest minimum is found by rank
     # (distinct times), by its digits (identical layers and pools: thousands of equal minima), or is not
-    # there (fewer valid units than k); k on both sides of the 64 that the ranks are taken up to
+    # there (fewer valid units than k); k on both sides of the 128 that the ranks are taken up to
     L, rng = 24, np.random.default_rng(3)
     shape = (2, 1, 4, L)
     fwd = np.full(shape, 1e-3) if form == "ties" else rng.uniform(0.5e-3, 2e-3, shape)
@@ -956,7 +956,7 @@ def test_threshold_among_more_units_than_a_workgroup_keeps(torch_cuda, form):
     plan, orc = _plan(prob), Oracle(prob)
     try:
         assert plan.num_candidates() == orc.num_candidates
-        for k in (1, 17, 64, 65):
+        for k in (1, 17, 64, 65, 128, 129):
             check_topk(plan.topk(k), orc.topk(k, n_threads=4), MAX_THROUGHPUT, orc)
         # the units that the plan keeps: beyond what the digit form holds in registers, and where the values
         # are distinct beyond what the rank form holds, too (pools without room take units away)
