@@ -176,6 +176,7 @@ struct sailor_plan {
   std::vector<UnitRec> units;
   std::vector<EvalBlock> eblocks;  // range evaluation: a block's units (laid out on the device)
   uint64_t n_eunits = 0;
+  uint32_t n_groups = 0;           // units of one shape and tp per segment are a group: see k_group_bounds
   EvalUnit *d_eunits = nullptr;    // ascending idx_lo
   size_t eval_lds_bytes = 0;
   std::vector<int32_t> mbv, tpv, dpv, ppv;
@@ -428,6 +429,7 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
   const uint64_t unit_target =
       std::min(kUnitTargetMax, std::max(kUnitTargetMin, pl->dev.N / kUnitsWanted));
   const uint64_t innerp = (uint64_t)p->n_mb * p->n_dp * ZG;
+  uint32_t group = 0;
   for (uint32_t si = 0; si < pl->shapes.size(); ++si) {
     const ShapeRec &sh = pl->shapes[si];
     const int n_o = sh.s >= 2 ? ZG : 1;
@@ -437,7 +439,7 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
     const int n_t1 = (pst && sh.s >= 2) ? p->n_tp : 1, n_t2 = (pst && sh.s == 3) ? p->n_tp : 1;
     for (int t2 = 0; t2 < n_t2; ++t2)
       for (int t1 = 0; t1 < n_t1; ++t1)
-        for (int t = 0; t < p->n_tp; ++t)
+        for (int t = 0; t < p->n_tp; ++t, ++group)
           for (int c = 0; c < n_chunks; ++c) {
             const int lo = (int)((int64_t)n_o * c / n_chunks),
                       hi = (int)((int64_t)n_o * (c + 1) / n_chunks);
@@ -452,6 +454,7 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
             for (int j = 0; j < 3; ++j) u.n[j] = sh.n[j];
             u.part = 0;
             u.n_parts = 1;
+            u.group = group;
             u.base = sh.base + (pst ? inner * (uint64_t)(ZG - 1) * (uint64_t)t1 +
                                           pl->dev.stride3 * (uint64_t)(ZG - 1) * (uint64_t)t2
                                     : 0u);
@@ -471,9 +474,14 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
     e.chunk = (uint32_t)std::min<uint64_t>(
         std::min<uint64_t>(e.o_total, kEvalUnitMaxOuter), std::max<uint64_t>(1, kEvalUnitTarget / inner));
     e.per_shape = (e.o_total + e.chunk - 1) / e.chunk;
+    e.first_group = pl->n_groups;
+    e.groups = (uint32_t)p->n_tp;
+    for (uint32_t j = 1; pst && j < b.s; ++j) e.groups *= (uint32_t)p->n_tp;
+    pl->n_groups += e.groups * b.n_shapes;
     pl->eblocks.push_back(e);
     pl->n_eunits += e.per_shape * b.n_shapes;
   }
+  if (pl->n_groups != group) return SAILOR_EINVAL;
   // Largest units first, so that the small ones fill the tail of the launch (the order is
   // refined by a timed pass once the tables are on the device).
   {
@@ -636,13 +644,6 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
   const size_t lds = pl->lds_bytes;
   if (pl->dev.mixed) launch_units_m<MODE, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
   else launch_units_m<MODE, false>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
-}
-
-// One workgroup per unit, the availability ignored (plan creation).
-void launch_bounds(sailor_plan *pl, const ScanArgs &a) {
-  const dim3 grid((unsigned)pl->dev.n_units), block(pl->unit_threads);
-  if (pl->dev.mixed) k_units<MODE_BOUNDS, 0, false, true><<<grid, block, pl->lds_bytes>>>(pl->dev, a, NoAvail{});
-  else k_units<MODE_BOUNDS, 0, false, false><<<grid, block, pl->lds_bytes>>>(pl->dev, a, NoAvail{});
 }
 
 struct SearchLaunch {
@@ -1104,6 +1105,11 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&d.syncz, slots * Z);
   slab.table(&d.upd, slots * GX);
   slab.table(&pl->direct_mem.su, slots * ZG);
+  float *link_min = nullptr;
+  GroupArgs ga{};
+  slab.table(&link_min, (size_t)2 * MB + 1);
+  slab.table(&ga.rows, (size_t)pl->n_groups * 2 * DP);
+  slab.table(&ga.sums, (size_t)pl->n_groups);
   // selection scratch (umin_l lies behind umin_s: creation reads both back in one copy)
   slab.table(&pl->umin_s, 2 * unit_cap);
   slab.table(&pl->counters, (size_t)2 * CNT_COUNT);
@@ -1121,30 +1127,23 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   pl->lb_cost = pl->lb_time + unit_cap;
   pl->order_time = reinterpret_cast<uint32_t *>(pl->lb_cost + unit_cap);
   pl->order_cost = pl->order_time + unit_cap;
-  // (the units in front of the tables' kernels: a copy waits for what was launched before it)
-  CREATE_TRY(hipMemcpy(const_cast<UnitRec *>(d.units), pl->units.data(), pl->units.size() * sizeof(UnitRec), hipMemcpyHostToDevice));
   k_init_counters<<<1, 64>>>(pl->counters, pl->calls);
   k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(p->avail, ZGr), nullptr, pl->d_avail, 0u);
-  k_small_tables<<<1, 256>>>(d);
+  k_small_tables<<<1, 256>>>(d, link_min);
   if (!d.mixed) k_list_tables<<<1, 256>>>(d);
   k_direct_tables<<<1, 256>>>(d, pl->direct_mem);
   k_stage_tables<<<(unsigned)RS, 128>>>(d, sa);
   k_shape_agg<<<(unsigned)NS, kShapeAggThreads, (size_t)3 * TP * (Z + GX) * sizeof(float)>>>(d, pl->direct_mem);
   CREATE_TRY(hipGetLastError());
   {
-    // Two passes over the space order the scan.  The first ignores the availability and records,
-    // per unit, the smallest iteration time and the smallest cost of the plans that memory, node
-    // size and batch divisibility allow: bounds that let a query pass over a unit whatever the
-    // availability becomes.  A unit that has no such plan is dropped for good.  Units of equal
-    // size still differ widely in cost, because invalid plans are pruned early, so the second
+    // The units' bounds, which let a query pass over a unit whatever the availability becomes.  A unit
+    // without a plan that memory, node size and batch divisibility allow is dropped for good.  Units of equal
+    // size still differ widely in cost, because invalid plans are pruned early, so a timed
     // pass records how long each remaining unit takes -- with every valid plan evaluated, since what
     // a query can leave out depends on its objective and its bound (timed with what the fastest plan
     // leaves out, units that are long for the cheapest one stayed whole: 144 us instead of 77 on
     // 2.7e8 plans with pairs of types); they are launched longest first, which also deals them
     // evenly to the hardware's dispatch queues.
-    // (Five passes did this -- which units hold a plan, how long each takes, the same once more
-    // after the cut below, either bound on its own: of the 1.1e9 plans of five zones with pairs of
-    // types 2.1 ms, now 0.9 ms.)
     size_t NU = pl->units.size();
     const size_t n_units_alloc = unit_cap;  // entries of the per-unit tables on the device
     UnitRec *d_units = const_cast<UnitRec *>(d.units);
@@ -1154,10 +1153,13 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     ca.umin_l = pl->umin_l;
     ca.counters = pl->counters;
     ca.lim_s = ca.lim_l = kPosInf;
-    ca.ignore_quota = 1;
-    launch_bounds(pl, ca);
+    ga.blocks = d_eblocks;
+    ga.n_blocks = (int)pl->eblocks.size();
+    ga.link_min = link_min;
+    // (a lane takes a microbatch size and a type per segment)
+    k_group_bounds<<<pl->n_groups, GX * GX * MB <= 256 ? 64 : kGroupThreads, group_lds_bytes(GX, MB, DP)>>>(d, ga);
     CREATE_TRY(hipGetLastError());
-    // what only queries need is allocated while the pass runs
+    // what only queries need is allocated while the set-up kernels run
     CREATE_TRY(pl->arena.alloc(&pl->surv, (size_t)pl->surv_cap));  // (these two can be replaced on their own)
     CREATE_TRY(pl->arena.alloc(&pl->ref, (size_t)pl->ref_cap));
     const size_t res_bytes = (sizeof(ResultHeader) + 8 + (size_t)SAILOR_MAX_K * sizeof(RefRec) + 127) & ~(size_t)127;
@@ -1174,21 +1176,25 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     k_eval_units<<<(unsigned)std::min<uint64_t>(1024, (pl->n_eunits + 255) / 256), 256>>>(
         d_eblocks, (int)pl->eblocks.size(), pl->n_eunits, d.inner, pl->d_eunits);
     CREATE_TRY(hipGetLastError());
-    std::vector<float> val(NU), lb_time(unit_cap + NU);
-    CREATE_TRY(hipMemcpy(lb_time.data(), pl->umin_s, lb_time.size() * sizeof(float), hipMemcpyDeviceToHost));
-    std::vector<float> lb_cost(lb_time.begin() + (ptrdiff_t)unit_cap, lb_time.end());
+    std::vector<GroupSum> sums(pl->n_groups);
+    CREATE_TRY(hipMemcpy(sums.data(), ga.sums, sums.size() * sizeof(GroupSum), hipMemcpyDeviceToHost));
+    std::vector<float> val(NU), lb_time(NU), lb_cost(NU);
     size_t n_kept = 0;
     for (size_t i = 0; i < NU; ++i) {
-      if (!(lb_time[i] < kPosInf) && !(n_kept == 0 && i + 1 == NU)) continue;  // launches need a non-empty grid
-      pl->units[n_kept] = pl->units[i];
-      lb_time[n_kept] = lb_time[i];
-      lb_cost[n_kept] = lb_cost[i];
+      const UnitRec &u = pl->units[i];
+      const GroupSum &g = sums[u.group];
+      bool holds = u.s == 1 && g.time < kPosInf;
+      for (int a2 = u.o_lo; u.s >= 2 && a2 < u.o_lo + u.o_cnt && !holds; ++a2)
+        holds = (g.seg2[(a2 % GX) >> 5] >> ((a2 % GX) & 31)) & 1u;
+      if (!holds && !(n_kept == 0 && i + 1 == NU)) continue;  // launches need a non-empty grid
+      lb_time[n_kept] = g.time;
+      lb_cost[n_kept] = g.cost;
+      pl->units[n_kept] = u;
       ++n_kept;
     }
     pl->units.resize(NU = n_kept);
     d.n_units = (int)NU;
     CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
-    ca.ignore_quota = 0;
     ca.ucost = d_cost;
     launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
     CREATE_TRY(hipGetLastError());

@@ -48,8 +48,8 @@ struct UnitRec {        // work of one workgroup of the scan: one shape, one tp 
   uint16_t o_lo, o_cnt; // n = stages per segment (copied from the shape, so that a
   uint16_t n[3];        // workgroup needs one record to start).  A unit found to run long is
   uint8_t part, n_parts;  // cut into n_parts records: record `part` takes every n_parts-th
-  uint32_t pad2;          // share of the lane space (the (mb, dp, pool 1) triples)
-};
+  uint32_t group;         // share of the lane space (the (mb, dp, pool 1) triples).  group: see
+};                        // k_group_bounds
 static_assert(sizeof(UnitRec) == 32, "one unit record per 32 bytes");
 
 struct EvalUnit {       // work of one workgroup of the range evaluation: one shape, all tp,
@@ -59,12 +59,19 @@ struct EvalUnit {       // work of one workgroup of the range evaluation: one sh
   uint32_t pad;
 };
 
-struct EvalBlock {      // the range evaluation's units of a block's shapes, which are divided alike
+struct EvalBlock {      // a block's shapes are divided alike: into units of the range evaluation
   uint64_t off, shape_size;  // first index, candidates per shape
   uint64_t o_total;     // values of a shape's outer digits, of which a unit spans `chunk`
   uint64_t first_unit, per_shape;
   uint32_t first_shape, chunk;
+  uint32_t first_group, groups;  // groups of units (k_group_bounds), how many of them a shape has
 };
+
+struct GroupSum {       // what k_group_bounds tells the host of a group of units
+  float time, cost;     // smallest over all degrees, infinite if it holds no plan
+  uint32_t seg2[4];     // the types that segment 2 has in its plans, a bit each
+};
+static_assert(kMaxPools <= 128, "a bit per type");
 
 struct SurvRec {        // candidate kept for the fp64 re-evaluation
   uint64_t idx;

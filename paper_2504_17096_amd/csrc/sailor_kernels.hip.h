@@ -1,6 +1,6 @@
 // HIP kernels of the batched plan evaluator (gfx950, wave64).
 //
-// Set-up kernels (once per plan): k_small_tables, k_stage_tables, k_shape_agg;
+// Set-up kernels (once per plan): k_small_tables, k_stage_tables, k_shape_agg, k_group_bounds;
 //            k_quota_table    again whenever the availability changes.
 // Hot path:  k_units<SCAN>    full-space fp32 evaluation + per-unit minima, early pruning
 //            k_select_kth     radix select of the k-th smallest fp32 key
@@ -30,6 +30,27 @@ __device__ __forceinline__ float wave_min(float v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v = fminf(v, __shfl_xor(v, off));
   return v;
+}
+
+// The smallest value of a wave, in every lane.
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  auto below = [&](auto ctrl) {  // (lanes without a source keep their own value)
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xF, 0xF, false));
+  };
+  below(std::integral_constant<int, 0x111>());  // row_shr:1, 2, 4, 8
+  below(std::integral_constant<int, 0x112>());
+  below(std::integral_constant<int, 0x114>());
+  below(std::integral_constant<int, 0x118>());
+  below(std::integral_constant<int, 0x142>());  // row_bcast:15, 31
+  below(std::integral_constant<int, 0x143>());
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Element j of a three-element array by selects (a lane-dependent subscript would move the
+// array to scratch memory).
+template <typename T>
+__device__ __forceinline__ int at3(const T *v, int j) {
+  return j == 0 ? (int)v[0] : (j == 1 ? (int)v[1] : (int)v[2]);
 }
 
 // 24-bit multiply (full rate, unlike the 32-bit one), for table offsets
@@ -63,10 +84,14 @@ __device__ __forceinline__ bool pool_bit(const uint64_t *mask, int p, int q) {
 
 // ------------------------------------------------------------------ set-up kernels
 
-// Reciprocal bandwidths, two-way egress, and the per-(mb, dp, tp) scalars of a plan.
-__global__ void k_small_tables(DevPlan pl) {
+// Reciprocal bandwidths, two-way egress, and the per-(mb, dp, tp) scalars of a plan.  link_min (see
+// k_group_bounds): per microbatch size the quickest transfer within a zone and between two, and behind
+// them the smallest egress between two zones.
+__global__ void k_small_tables(DevPlan pl, float *link_min) {
   const int t = threadIdx.x, nt = blockDim.x;
   const int Z = pl.Z;
+  for (int i = t; i <= 2 * pl.MB; i += nt) link_min[i] = kPosInf;
+  __syncthreads();
   for (int i = t; i < Z * Z; i += nt) {
     int a = i / Z, b = i % Z;
     for (int m = 0; m < pl.MB; ++m) {
@@ -74,10 +99,12 @@ __global__ void k_small_tables(DevPlan pl) {
       pl.bwp[m * Z * Z + i] = bwv;
       pl.xsec[m * Z * Z + i] = bytes / bwv;
       pl.tsec_f[m * Z * Z + i] = (float)(bytes / bwv);
+      atomicMin(reinterpret_cast<uint32_t *>(&link_min[2 * m + (a != b)]), __float_as_uint((float)(bytes / bwv)));
     }
     double e = 0.0;
     if (pl.egress && a != b) e = pl.egress[a * Z + b] + pl.egress[b * Z + a];
     pl.egs_f[i] = (float)e;
+    if (a != b) atomicMin(reinterpret_cast<uint32_t *>(&link_min[2 * pl.MB]), __float_as_uint((float)e));
   }
   for (int g = t; g < pl.GX; g += nt) {
     const int ga = pl.xt[g] & 255, gb = pl.xt[g] >> 8;
@@ -554,10 +581,9 @@ __device__ __forceinline__ uint32_t joint_quota_bits(const DevPlan &pl, int n_se
 }
 
 // SCAN: a unit's smallest key over the candidates strictly / loosely within the constraint.
-// COLLECT: a unit's candidates under a threshold.  BOUNDS (plan creation, no constraint): a unit's
-// smallest iteration time and smallest cost, in the places of SCAN's two minima.  BEST: as SCAN, and a
-// unit that comes within the tie band of the smallest key so far keeps its candidates at once.
-enum { MODE_SCAN = 0, MODE_COLLECT = 1, MODE_BOUNDS = 2, MODE_BEST = 3 };
+// COLLECT: a unit's candidates under a threshold.  BEST: as SCAN, and a unit that comes within the tie
+// band of the smallest key so far keeps its candidates at once.
+enum { MODE_SCAN = 0, MODE_COLLECT = 1, MODE_BEST = 2 };
 
 struct ScanArgs {
   float *umin_s, *umin_l;   // [n_units] minima over strictly / loosely constrained candidates
@@ -573,7 +599,6 @@ struct ScanArgs {
   uint32_t surv_cap;
   float *ucost;             // SCAN, optional: ticks of the 100 MHz clock each unit took, nothing
                             // left out for the minimum found so far
-  int ignore_quota;         // SCAN at plan creation: treat every pool as large enough
   const uint32_t *ulist;    // COLLECT, optional: the units to visit and, in counters[CNT_NLIST],
                             // how many; the grid then strides over the list
   uint32_t *unit_gen;       // SCAN, optional: per unit, the availability generation its minima
@@ -641,10 +666,7 @@ __device__ __forceinline__ void visit(const ScanArgs &a, float T, float C, bool 
   const float con = OBJ == 0 ? C : T;
   if (MODE != MODE_COLLECT) {
     const float kf = feas ? key : kPosInf;
-    if (MODE == MODE_BOUNDS) {
-      ms = fminf(ms, kf);
-      ml = fminf(ml, feas ? con : kPosInf);
-    } else if (HASB) {
+    if (HASB) {
       ms = fminf(ms, con <= a.lim_s ? kf : kPosInf);
       ml = fminf(ml, con <= a.lim_l ? kf : kPosInf);
     } else {
@@ -720,6 +742,134 @@ __device__ __forceinline__ LaneItem lane_item(const DevPlan &pl, int e, int n_it
 
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
+// Bounds of a group of units -- one shape, one tp per segment -- by data-parallel degree: rows[group] =
+// the smallest iteration time per degree, then the smallest cost, of plans that memory, node size and
+// batch allow, whatever the availability.  A segment's pool matters through its type and its zone.  Types
+// are gone through exhaustively; of the zones only the best case is kept: the quickest link of the right
+// kind (two neighbours of one type lie in different zones), the smallest egress, the quickest all-reduce.
+// What the scan computes for a plan goes through the same operations on inputs that are no smaller, and
+// fp32 additions, products, fused multiply-adds and maxima of non-negative values round monotonically: so
+// a row's entry is at most the fp32 value of every plan it stands for, and needs no slack.  It is infinite
+// exactly where there is no such plan.
+//
+// The types leave (types / pools)^segments of the plans, and what the segments add up to is shared by all
+// degrees: MB x types^segments sums a group, bound by vector instructions.  On 1.1e9 plans with pairs of
+// types 44 us, where a pass over every plan took 659 for one bound for all degrees.  On 1.0e8 plans as many
+// units meet the budget and the cheapest plan by either; of 3 457 within reach of the 64 fastest remain 297
+// with these bounds and 167 with exact ones.
+constexpr int kGroupThreads = 256;  // (64 where all pairs of types are few)
+
+struct GroupArgs {
+  const EvalBlock *blocks;
+  int n_blocks;
+  const float *link_min;   // [MB] {within a zone, between zones}, egress
+  float *rows;             // [group][2][DP]
+  GroupSum *sums;          // [group]
+};
+
+__host__ __device__ inline size_t group_lds_bytes(int GX, int MB, int DP) {
+  return (size_t)3 * GX * MB * (2 * sizeof(float4) + sizeof(uint32_t)) + (size_t)MB * DP * sizeof(float);
+}
+
+__global__ __launch_bounds__(kGroupThreads) void k_group_bounds(DevPlan pl, GroupArgs a) {
+  extern __shared__ uint4 lds_raw[];
+  __shared__ uint32_t s_row[2 * kMaxDP], s_seg2[4];
+  const int GX = pl.GX, MB = pl.MB, DP = pl.DP, TP = pl.TP, Z = pl.Z, t = threadIdx.x, nt = blockDim.x;
+  int blk = 0;
+  for (int i = 1; i < a.n_blocks; ++i)
+    if (blockIdx.x >= a.blocks[i].first_group) blk = i;
+  const uint32_t per_shape = a.blocks[blk].groups, in_block = blockIdx.x - a.blocks[blk].first_group;
+  const uint32_t shape = a.blocks[blk].first_shape + in_block / per_shape;
+  const ShapeRec sh = pl.shapes[shape];
+  const int S = sh.s;
+  int k[3];  // tp index of each segment
+  {
+    uint32_t kk = in_block % per_shape;
+    k[0] = (int)(kk % (uint32_t)TP);
+    kk /= (uint32_t)TP;
+    k[1] = pl.pst ? (int)(kk % (uint32_t)TP) : k[0];
+    k[2] = pl.pst ? (int)(kk / (uint32_t)TP) : k[0];
+  }
+  float4 *const lo = reinterpret_cast<float4 *>(lds_raw), *const hi = lo + 3 * GX * MB;  // [S][GX][MB]
+  uint32_t *const bits = reinterpret_cast<uint32_t *>(hi + 3 * GX * MB);
+  float *const nbm1 = reinterpret_cast<float *>(bits + 3 * GX * MB);  // [MB][DP]
+  uint32_t even = 0;  // degrees that can be halved
+  for (int d = 0; d < DP; ++d) even |= pl.dpv[d] % 2 == 0 ? 1u << d : 0u;
+  for (int i = t; i < S * GX * MB; i += nt) {
+    const int m = i % MB, x = i / MB % GX, seg = i / (MB * GX);
+    const int kt = at3(k, seg), n = at3(sh.n, seg);
+    const uint32_t sl = (shape * (uint32_t)TP + (uint32_t)kt) * 3u + (uint32_t)seg, gi = (sl * (uint32_t)GX + (uint32_t)x) * (uint32_t)MB + (uint32_t)m;
+    float sync = pl.syncz[sl * Z];
+    for (int z = 1; z < Z; ++z) sync = fminf(sync, pl.syncz[sl * Z + z]);
+    uint32_t b = pl.memok[gi] & pl.divis[m];
+    if ((pl.xt[x] & 255) != pl.xt[x] >> 8) b &= even;
+    if ((pl.h1m[x] >> kt) & 1u) b = 0;  // (pool x: type x in the first zone)
+    rec_store(lo, hi, bits, i, make_rec(pl.ta[gi], sync, pl.upd[sl * GX + x], pl.price_f[x], a.link_min[2 * m], n, pl.vals[DP + kt], b));
+  }
+  for (int i = t; i < MB * DP; i += nt) nbm1[i] = pl.nbm1_f[i];
+  if (t < 2 * DP) s_row[t] = __float_as_uint(kPosInf);
+  if (t < 4) s_seg2[t] = S >= 2 ? 0u : ~0u;
+  __syncthreads();
+  const float eg_out = Z > 1 ? a.link_min[2 * MB] : 0.f;
+  float low_t[kMaxDP], low_c[kMaxDP];
+#pragma unroll
+  for (int d = 0; d < kMaxDP; ++d) low_t[d] = low_c[d] = kPosInf;
+  const uint32_t n_items = (uint32_t)MB * (uint32_t)GX * (S >= 2 ? (uint32_t)GX : 1u) * (S == 3 ? (uint32_t)GX : 1u);
+  for (uint32_t e = t; e < n_items; e += nt) {
+    const uint32_t r1 = fast_div(e, pl.mg_mb), m = e - r1 * (uint32_t)MB;
+    const uint32_t r2 = fast_div(r1, pl.mg_g), x0 = r1 - r2 * (uint32_t)GX;
+    const uint32_t x2 = fast_div(r2, pl.mg_g), x1 = r2 - x2 * (uint32_t)GX;
+    const uint32_t i0 = x0 * MB + m, i1 = (GX + x1) * MB + m, i2 = (2 * GX + x2) * MB + m;
+    uint32_t b = bits[i0];
+    if (S >= 2) b &= (Z > 1 || x0 != x1) ? bits[i1] : 0u;  // neighbours lie on different pools
+    if (S == 3) b &= (Z > 1 || x1 != x2) ? bits[i2] : 0u;
+    if (!wave_any(b != 0)) continue;
+    const float t_in = a.link_min[2 * m], t_out = Z > 1 ? a.link_min[2 * m + 1] : t_in, t_any = fminf(t_in, t_out);
+    Acc p = acc_begin(rec_load(lo, hi, (int)i0));
+    if (S >= 2) {
+      const float w = x0 == x1 ? t_out : t_any;
+      p = acc_cross(p, rec_load(lo, hi, (int)i1), w, w, x0 == x1 ? eg_out : 0.f, sh.n[0] == 1, true);
+    }
+    if (S == 3) {
+      const float w = x1 == x2 ? t_out : t_any;
+      p = acc_cross(p, rec_load(lo, hi, (int)i2), w, w, x1 == x2 ? eg_out : 0.f, sh.n[1] == 1, false);
+    }
+    LaneC lc;
+    lc.xb = pl.xb_f[m];
+#pragma unroll
+    for (int d = 0; d < kMaxDP; ++d) {
+      if (d < DP) {  // uniform
+        lc.nbm1 = nbm1[m * DP + d];
+        lc.cd = pl.cd_f[d];
+        lc.dph = pl.dph_f[d];
+        float T, C;
+        acc_finish(p, lc, T, C);
+        const bool ok = (b >> d) & 1u;
+        low_t[d] = fminf(low_t[d], ok ? T : kPosInf);
+        low_c[d] = fminf(low_c[d], ok ? C : kPosInf);
+      }
+    }
+    if (S >= 2 && b != 0) atomicOr(&s_seg2[x1 >> 5], 1u << (x1 & 31u));
+  }
+#pragma unroll
+  for (int d = 0; d < kMaxDP; ++d) {
+    if (d < DP) {
+      const uint32_t mt = wave_min_u32(__float_as_uint(low_t[d])), mc = wave_min_u32(__float_as_uint(low_c[d]));
+      if ((t & 63) == 0) {
+        atomicMin(&s_row[d], mt);
+        atomicMin(&s_row[DP + d], mc);
+      }
+    }
+  }
+  __syncthreads();
+  if (t < 2 * DP) a.rows[(size_t)blockIdx.x * 2 * DP + t] = __uint_as_float(s_row[t]);
+  if (t == 0) {
+    uint32_t mt = s_row[0], mc = s_row[DP];
+    for (int d = 1; d < DP; ++d) { mt = min(mt, s_row[d]); mc = min(mc, s_row[DP + d]); }
+    a.sums[blockIdx.x] = GroupSum{__uint_as_float(mt), __uint_as_float(mc), {s_seg2[0], s_seg2[1], s_seg2[2], s_seg2[3]}};
+  }
+}
+
 // The lanes of a workgroup own the (mb, pool of segment 1, dp) triples; the pools of the
 // later segments are walked in uniform loops, so their record addresses, zones and
 // transfer terms are the same for the whole wave.
@@ -761,34 +911,24 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   const bool single0 = u.n[0] == 1, single1 = u.n[1] == 1;
   const int tp = u.tp[0];
   const uint64_t ubase = u.base;
-  // the limits in force: SCAN the smallest strict key so far, BOUNDS the smallest time and cost
-  // so far, COLLECT the threshold
-  auto limits = [&](float &l0, float &l1) {
-    l0 = tau;
-    l1 = kPosInf;
-    if (MODE != MODE_COLLECT)
-      l0 = __uint_as_float(__hip_atomic_load(&s_min[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-    if (MODE == MODE_BOUNDS)
-      l1 = __uint_as_float(__hip_atomic_load(&s_min[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  // the limit in force: the smallest strict key so far, COLLECT the threshold
+  auto limit = [&]() {
+    if (MODE == MODE_COLLECT) return tau;
+    return __uint_as_float(__hip_atomic_load(s_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
   };
   // can a plan that starts like this still matter?
-  auto alive = [&](const Acc &p, const LaneC &lc, float l0, float l1) {
+  auto alive = [&](const Acc &p, const LaneC &lc, float l0) {
     float T, C;
     acc_finish(p, lc, T, C);
     const float key = OBJ == 0 ? T : C, con = OBJ == 0 ? C : T;
-    if (MODE == MODE_BOUNDS) return key <= l0 || con <= l1;
     return key <= l0 && (!HASB || con <= a.lim_l);
   };
   // (one thread of the waves that improve on what the workgroup has)
-  auto report = [&](float l0, float l1) {
+  auto report = [&](float l0) {
     if (MODE == MODE_COLLECT || (MODE == MODE_SCAN && a.ucost)) return;
     if (wave_any(ms < l0)) {
       const float m = wave_min(ms);
-      if (lane == 0) atomicMin(&s_min[0], __float_as_uint(m));
-    }
-    if (MODE == MODE_BOUNDS && wave_any(ml < l1)) {
-      const float m = wave_min(ml);
-      if (lane == 0) atomicMin(&s_min[1], __float_as_uint(m));
+      if (lane == 0) atomicMin(s_min, __float_as_uint(m));
     }
   };
   if (S <= 2) {
@@ -812,9 +952,8 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         visit<MODE, OBJ, HASB>(a, T, C, b0 != 0, tau, idx0, u.shape, ms, ml);
         continue;
       }
-      float l0, l1;
-      limits(l0, l1);
-      if (!alive(A0, it.lc, l0, l1)) b0 = 0;
+      const float l0 = limit();
+      if (!alive(A0, it.lc, l0)) b0 = 0;
       if (!wave_any(b0 != 0)) continue;
       int z2 = u.o_lo / G, g2 = u.o_lo % G;
       for (int a2 = u.o_lo; a2 < u.o_lo + u.o_cnt; ++a2) {
@@ -835,7 +974,7 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         }
         if (++g2 == G) { g2 = 0; ++z2; }
       }
-      report(l0, l1);
+      report(l0);
     }
   } else {
     const int nin = MB * DP * (ZG - 1);
@@ -856,9 +995,8 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         const float4 *pairm = pair + it.mb * Z * Z;
         const float4 p12 = pairm[z1 * Z + z2];
         const Acc A1 = acc_cross(acc_begin(r0), r1, p12.x, p12.y, p12.z, single0, true);
-        float l0, l1;
-        limits(l0, l1);
-        if (!alive(A1, it.lc, l0, l1)) b1 = 0;
+        const float l0 = limit();
+        if (!alive(A1, it.lc, l0)) b1 = 0;
         if (!wave_any(b1 != 0)) continue;
         const uint32_t q13a = MIXED ? 0u : q13[a1];
         int rel2 = a2 - a1 - 1;
@@ -890,7 +1028,7 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
           }
           if (++g3 == G) { g3 = 0; ++z3; }
         }
-        report(l0, l1);
+        report(l0);
       }
       if (++g2 == G) { g2 = 0; ++z2; }
     }
@@ -966,9 +1104,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   uint32_t *q13 = reinterpret_cast<uint32_t *>(isect + 2 * ZG);       // [ZG]
   __shared__ float red[2][kMaxUnitThreads / 64];
   __shared__ uint32_t s_any[kMaxUnitThreads / 64];  // per wave, bit j: a pool can host segment j
-  __shared__ uint32_t s_min[2];  // what the workgroup has found so far (see unit_body)
+  __shared__ uint32_t s_min;  // the smallest key the workgroup has found so far (see unit_body)
   const int t = threadIdx.x;
-  if (MODE != MODE_COLLECT && t < 2) s_min[t] = __float_as_uint(t == 0 ? key_limit : kPosInf);
+  if (MODE != MODE_COLLECT && t == 0) s_min = __float_as_uint(key_limit);
 
   const int n0 = u.n[0], n1 = u.n[1], n2 = u.n[2];
   const int k0 = u.tp[0], k1 = u.tp[1], k2 = u.tp[2];            // tp index of each segment
@@ -993,7 +1131,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     const uint32_t gi = (sl * (uint32_t)G + (uint32_t)g) * (uint32_t)MB + mb;
     const float4 ta = pl.ta[gi];
     uint32_t q = 0xFFFFFFFFu;
-    if (!a.ignore_quota && !fresh) q = pl.qw[w * ZG + p];
+    if (!fresh) q = pl.qw[w * ZG + p];
     if constexpr (kAvailRides<MODE, MIXED>)
       if (fresh) q = quota_bits(pl, avail.v[p], w);
     if ((pl.h1m[p] >> k) & 1u) q = 0;  // H1: tensor parallelism stays inside a node
@@ -1013,7 +1151,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   if (S == 3 && !MIXED)
     for (int p = t; p < ZG; p += blockDim.x) {
       uint32_t q = 0xFFFFFFFFu;
-      if (!a.ignore_quota && !fresh) q = pl.qw[(w0 + w2) * ZG + p];
+      if (!fresh) q = pl.qw[(w0 + w2) * ZG + p];
       if constexpr (kAvailRides<MODE, MIXED>)
         if (fresh) q = quota_bits(pl, avail.v[p], w0 + w2);
       q13[p] = q;
@@ -1023,8 +1161,8 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
         else if (uq[p] != q) { uq[p] = q; any_here |= 8u; }
       }
     }
-  if (MIXED)  // under ignore_quota no pool counts as shared
-    for (int p = t; p < 2 * ZG; p += blockDim.x) isect[p] = a.ignore_quota ? 0ull : pl.isect[p];
+  if (MIXED)
+    for (int p = t; p < 2 * ZG; p += blockDim.x) isect[p] = pl.isect[p];
   for (int i = t; i < MB * Z * Z; i += blockDim.x) {  // per mb: transfer a -> b, b -> a, egress
     const int m = i / (Z * Z), ab = i - m * Z * Z, za = ab / Z, zb = ab % Z;
     pair[i] = make_float4(pl.tsec_f[i], pl.tsec_f[(m * Z + zb) * Z + za], pl.egs_f[ab], 0.f);
@@ -1066,14 +1204,14 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   const int share = sub * (int)u.n_parts + (int)u.part, n_shares = (int)u.n_parts * (int)n_sub;
   auto walk = [&](auto mode) {
     constexpr int M = decltype(mode)::value;
-    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
-    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
-    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, s_min, ms, ml);
+    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, &s_min, ms, ml);
+    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, &s_min, ms, ml);
+    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, &s_min, ms, ml);
   };
   walk(std::integral_constant<int, MODE>());
 
   if (MODE != MODE_COLLECT) {
-    if (!HASB && MODE != MODE_BOUNDS) ml = ms;
+    if (!HASB) ml = ms;
     ms = wave_min(ms);
     ml = wave_min(ml);
     if ((t & 63) == 0) { red[0][t >> 6] = ms; red[1][t >> 6] = ml; }
@@ -1083,9 +1221,8 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
         ms = fminf(ms, red[0][w]);
         ml = fminf(ml, red[1][w]);
       }
-      float keep = -1.0f;
-      if (MODE != MODE_BOUNDS) keep = unit_publish(a, ms, ml);
-      if (MODE == MODE_BEST) s_min[0] = __float_as_uint(keep);
+      const float keep = unit_publish(a, ms, ml);
+      if (MODE == MODE_BEST) s_min = __float_as_uint(keep);
       if (!(MODE == MODE_BEST && a.direct)) {  // (several workgroups share a listed unit)
         a.umin_s[uidx] = ms;
         a.umin_l[uidx] = ml;
@@ -1102,7 +1239,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     // being listed for a kernel of their own (8 to 10 us of a query of 35 to 55): with the threshold
     // known nearly all of it falls to the bounds.
     __syncthreads();
-    tau = __uint_as_float(s_min[0]);
+    tau = __uint_as_float(s_min);
     if (tau >= 0.0f) walk(std::integral_constant<int, MODE_COLLECT>());  // uniform
   }
 }
@@ -1151,20 +1288,6 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
 // The form that looks for the k-th value by rank (k_select_kth, RANK) is taken for more values than the
 // other one keeps in registers and k up to kKthByRank; beyond kKthRanked candidates it, too, takes the digits.
 constexpr uint32_t kKthByRank = 128, kKthByRankFrom = 8192, kKthRanked = 512;
-
-// The smallest value of a wave, in every lane.
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-  auto below = [&](auto ctrl) {  // (lanes without a source keep their own value)
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xF, 0xF, false));
-  };
-  below(std::integral_constant<int, 0x111>());  // row_shr:1, 2, 4, 8
-  below(std::integral_constant<int, 0x112>());
-  below(std::integral_constant<int, 0x114>());
-  below(std::integral_constant<int, 0x118>());
-  below(std::integral_constant<int, 0x142>());  // row_bcast:15, 31
-  below(std::integral_constant<int, 0x143>());
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
 
 // Radix select (11 + 11 + 10 bits) of the k-th smallest non-negative float among
 // n = min(*count, cap) values read with a stride; +inf entries are ignored and fewer than
@@ -1384,13 +1507,6 @@ struct Cand {
   int a[3];
   int k1, k2;
 };
-
-// Element j of a three-element array by selects (a lane-dependent subscript would move the
-// array to scratch memory).
-template <typename T>
-__device__ __forceinline__ int at3(const T *v, int j) {
-  return j == 0 ? (int)v[0] : (j == 1 ? (int)v[1] : (int)v[2]);
-}
 
 // The digits of candidate idx, which lies in the given shape.
 __device__ __forceinline__ void decode_in_shape(const DevPlan &pl, uint32_t shape, uint64_t idx,
