@@ -25,9 +25,11 @@ constexpr uint32_t kDefaultRefCap = 1u << 18;
 // candidates per scan workgroup: large enough to amortise the staging of a unit, small
 // enough to leave about ten workgroups per compute unit
 constexpr uint64_t kUnitTargetMin = 4096, kUnitTargetMax = 65536, kUnitsWanted = 2560;
-constexpr uint32_t kCollectSub = 4;      // workgroups that share one unit in the collect pass
-constexpr uint32_t kListSub = 8;         // the same when the pass walks a list of units,
-constexpr uint32_t kListUnits = 256;     // and the units it visits per round
+constexpr uint32_t kCollectSub = 8;      // workgroups that share one unit in the collect pass,
+constexpr uint32_t kCollectUnits = 256;  // and the units it visits per round
+constexpr size_t kChipWaves = 8192;      // 256 compute units of 32 waves
+constexpr uint32_t kSeedTicks = 800;     // 8 us: what the first units of a scan take from launch to result
+constexpr uint32_t kKthLive = 128;       // largest k whose running bound guides the scan (half the key slots)
 // A query whose constraint leaves at most this many units alive skips the scan: one pass
 // keeps every valid candidate of those units (see run_selection_impl)
 constexpr uint32_t kDirectUnits = 128;
@@ -36,10 +38,6 @@ constexpr uint32_t kFreshWorkgroups = 16;       // that bring the quota table up
 constexpr uint32_t kDirectManySurvivors = 8192;  // more than the select kernel holds in registers
                                                 // (or than half the survivor buffer): the query
                                                 // goes back to the scan from then on
-// a scan unit that takes more than kSplitAbove x the average load of a workgroup slot (and
-// kSplitAboveMean x the mean unit) is cut into parts of about kSplitTo x that load
-constexpr double kSplitAbove = 0.9, kSplitAboveMean = 1.5, kSplitTo = 0.7, kSplitToMean = 1.1;
-constexpr float kStagingTicks = 270.f;  // ticks (100 MHz) of a unit that its staging takes: 2.7 us
 constexpr uint32_t kRankOneWorkgroup = 128;  // largest k whose final ranking runs as one workgroup
 constexpr uint32_t kEvalUnitTarget = 16384;  // candidates per workgroup of the range evaluation
 constexpr unsigned kEvalRowsThreads = 512;
@@ -193,7 +191,7 @@ struct sailor_plan {
   bool avail_dirty = false;        // h_avail is newer than the device copy
   // scratch of the selection pipeline
   float *umin_s = nullptr, *umin_l = nullptr;
-  float *lb_time = nullptr, *lb_cost = nullptr;  // per unit: smallest time / cost with availability ignored
+  float *rows = nullptr;  // [unit][2][DP] bounds by degree, of the time and of the cost (k_group_bounds)
   // the units in ascending order of either bound (device), and the sorted bounds (host)
   uint32_t *order_time = nullptr, *order_cost = nullptr;
   std::vector<float> lb_time_sorted, lb_cost_sorted;
@@ -482,17 +480,6 @@ sailor_status build_space(const sailor_problem *p, sailor_plan *pl, std::vector<
     pl->n_eunits += e.per_shape * b.n_shapes;
   }
   if (pl->n_groups != group) return SAILOR_EINVAL;
-  // Largest units first, so that the small ones fill the tail of the launch (the order is
-  // refined by a timed pass once the tables are on the device).
-  {
-    std::vector<float> cost;  // candidates of the unit / innerp: whole numbers below 2^24
-    cost.reserve(pl->units.size());
-    for (const UnitRec &u : pl->units) cost.push_back((float)((uint32_t)u.o_cnt * (u.s == 3 ? (uint32_t)(ZG - 1) : 1u)));
-    std::vector<UnitRec> sorted;
-    sorted.reserve(pl->units.size());
-    for (uint32_t i : order_by(cost.data(), cost.size(), true)) sorted.push_back(pl->units[i]);
-    pl->units.swap(sorted);
-  }
   // Waves per workgroup: the lanes of a unit cover MB*DP*ZG triples in chunks of 64; pick
   // the wave count (2..8) that leaves the fewest idle wave slots in the last round.
   const uint64_t chunks = (innerp + 63) / 64;
@@ -610,6 +597,11 @@ sailor_status refresh_avail(sailor_plan *pl, hipStream_t st) {
   return SAILOR_OK;
 }
 
+// ScanArgs::most: half of the replicas of a pair of types lie on either pool.
+uint64_t most_replicas(const sailor_plan *pl) {
+  return (uint64_t)*std::max_element(pl->h_avail, pl->h_avail + pl->dev.ZGr) * (pl->dev.mixed ? 2u : 1u);
+}
+
 // Plain launch, or a launch whose own start / stop timestamps are recorded in two events.
 template <typename K, typename... A>
 void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t e0,
@@ -637,9 +629,8 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
                   hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const unsigned n_units = (unsigned)pl->units.size();
   const dim3 grid((a.direct               ? a.n_list_host * a.n_sub
-                   : MODE != MODE_COLLECT ? n_units
-                   : a.ulist              ? std::min(n_units, kListUnits) * a.n_sub
-                                          : n_units * a.n_sub) + a.fresh),
+                   : MODE != MODE_COLLECT ? (a.n_seeds ? a.n_seeds * a.n_sub + scan_workgroups(n_units - a.n_seeds, pl->unit_threads / 64) : n_units)
+                                          : std::min(n_units, kCollectUnits) * a.n_sub) + a.fresh),
       block(pl->unit_threads);
   const size_t lds = pl->lds_bytes;
   if (pl->dev.mixed) launch_units_m<MODE, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
@@ -703,8 +694,8 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   }
   // two counter sets: this call's set was reset by the final kernel of the previous call
   const uint32_t call = pl->calls++;
-  uint32_t *cnt = pl->counters + (call & 1u) * CNT_COUNT;
-  uint32_t *cnt_next = pl->counters + (~call & 1u) * CNT_COUNT;
+  uint32_t *cnt = pl->counters + (call & 1u) * kSetWords;
+  uint32_t *cnt_next = pl->counters + (~call & 1u) * kSetWords;
   sa.umin_s = pl->umin_s;
   sa.umin_l = pl->umin_l;
   sa.counters = cnt;
@@ -724,7 +715,10 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
                     pl->cache_lim_l == sa.lim_l) ? 1 : 0;
   const bool was_incremental = sa.incremental != 0;
   // (the constrained quantity is the cost when throughput is the objective, and the time otherwise)
-  if (has_bound) sa.ulb_con = obj == SAILOR_MAX_THROUGHPUT ? pl->lb_cost : pl->lb_time;
+  sa.rows_con = obj == SAILOR_MAX_THROUGHPUT ? pl->rows + pl->dev.DP : pl->rows;
+  // (what is kept for later calls must not depend on this call's results, nor on the availability alone)
+  if (!pl->incremental) sa.rows_key = obj == SAILOR_MAX_THROUGHPUT ? pl->rows : pl->rows + pl->dev.DP;
+  sa.most = pl->incremental ? ~0ull : most_replicas(pl);
   pl->cache_ok = false;  // until this call has succeeded
   pl->cache_obj = (int)obj;
   pl->cache_hasb = has_bound;
@@ -792,13 +786,20 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
       sa.n_sub = kDirectSub;
     }
   }
+  // units that do not fit on the chip at once: the first of the order guide the others (scan_workgroups)
+  auto guide = [&]() {
+    if (!sa.rows_key || (size_t)n_units * (pl->unit_threads / 64) <= kChipWaves) return;
+    sa.n_seeds = best ? kBestSeeds : kKthSeeds;
+    sa.n_sub = best ? kBestSeedSub : kKthSeedSub;
+    sa.wait_ticks = kSeedTicks;
+    if (obj == SAILOR_MIN_COST) sa.ulist = pl->order_cost;  // (their own order is by time)
+  };
   if (best && !sa.incremental && first_try) {
     // The scan keeps the candidates near the minimum itself (ScanArgs::near_band), so one kernel
     // is left behind it.  (Not when minima are reused: units that are not evaluated again report at
     // once, before any running minimum exists, and would have to stage their records again.)
     sa.near_band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
-    // (minima kept for later calls must not depend on this call's running minimum)
-    if (!pl->incremental) sa.ulb_key = obj == SAILOR_MAX_THROUGHPUT ? pl->lb_time : pl->lb_cost;
+    if (!sa.direct) guide();
     launch_units<MODE_BEST>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr, t_scan ? pl->ev[1] : nullptr);
     rc = run_tail(hdr_out, true);
     if (rc != SAILOR_OK) return rc;
@@ -840,8 +841,39 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     return SAILOR_OK;
   }
   sa.direct = 0;
+  sa.ulist = nullptr;
+  // A scan for the k smallest keys leaves out what a running upper bound of the k-th rules out, and ends
+  // with that bound as the threshold.  (Not for minima that are kept, nor for a k that is a large share of
+  // the bound's slots: with 256 of them it lies about 1.4 k keys up for k = 128.)
+  const bool by_slots = !best && first_try && !pl->incremental && k <= kKthLive;
+  sa.band = sa.near_band = 1.0f + 3.0f * kEvalEps;
+  if (by_slots) {
+    sa.kth = k;
+    guide();
+  }
+  const float *const rows_key = sa.rows_key;
+  if (!by_slots) sa.rows_key = nullptr;
   launch_units<MODE_SCAN>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr,
                           t_scan ? pl->ev[1] : nullptr);
+  sa.rows_key = rows_key;
+  sa.n_seeds = 0;
+  sa.wait_ticks = 0;
+  sa.ulist = nullptr;
+  sa.tau_src = cnt + CNT_TAU0;  // (not by_slots)
+  sa.n_sub = kCollectSub;
+  if (by_slots) {
+    rc = run_tail(hdr_out, false);
+    if (rc != SAILOR_OK) return rc;
+    pl->total_timed = t_all;
+    pl->scan_timed = t_scan;
+    if (hdr_out->surv_count > pl->surv_cap || hdr_out->ref_count > pl->ref_cap) {
+      *again = true;  // the exact k-th smallest minimum may admit fewer
+      return SAILOR_OK;
+    }
+    pl->last_incremental = false;
+    pl->last_scan_seq = sa.call_seq;
+    return SAILOR_OK;
+  }
   // an upper bound of the k-th smallest key: the k-th smallest unit minimum (the best plan's: the
   // smallest, and its tie band).  The same kernel lists the units whose loose minimum lies under it.
   sa.band = best ? (float)(1.0 + kTieTol) + 3.0f * kEvalEps : 1.0f + 3.0f * kEvalEps;
@@ -849,9 +881,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   const auto select = n_units > kKthByRankFrom && k_units_min <= kKthByRank ? k_select_kth<1024, true> : k_select_kth<1024, false>;
   select<<<1, 1024, 0, st>>>(pl->umin_s, 1, nullptr, n_units, k_units_min, cnt + CNT_TAU0, pl->umin_l, n_units, sa.band,
                              pl->ulist, cnt + CNT_NLIST);
-  sa.tau_src = cnt + CNT_TAU0;
   sa.ulist = pl->ulist;
-  sa.n_sub = kListSub;
   rc = run_tail(hdr_out, false);
   if (rc != SAILOR_OK) return rc;
   pl->total_timed = t_all;
@@ -866,7 +896,6 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     sa.use_tau_host = 1;
     sa.count_only = 1;
     sa.ulist = nullptr;  // the list belongs to the first threshold
-    sa.n_sub = kCollectSub;
     auto count_at = [&](float tau, uint32_t *n_loose, uint32_t *n_strict) -> sailor_status {
       k_zero_counters<<<1, 64, 0, st>>>(cnt, (1u << CNT_NLOOSE) | (1u << CNT_NSTRICT));
       sa.tau_host = tau;
@@ -1067,7 +1096,8 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   const long forced_parts = g_forced_unit_parts.load(std::memory_order_relaxed);
   const size_t unit_cap = pl->units.size() * (size_t)std::max(1L, forced_parts);
   char *per_unit = nullptr;  // the tables that creation fills last, in one copy: records, bounds, orders
-  slab.table(&per_unit, unit_cap * (sizeof(UnitRec) + 4 * sizeof(float)));
+  slab.table(&per_unit, unit_cap * (sizeof(UnitRec) + 2 * sizeof(uint32_t)));
+  slab.table(&pl->rows, unit_cap * 2 * DP);
   const EvalBlock *d_eblocks = nullptr;
   slab.input(&d_eblocks, pl->eblocks.data(), pl->eblocks.size());
   slab.table(&pl->d_eunits, (size_t)pl->n_eunits);
@@ -1112,7 +1142,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&ga.sums, (size_t)pl->n_groups);
   // selection scratch (umin_l lies behind umin_s: creation reads both back in one copy)
   slab.table(&pl->umin_s, 2 * unit_cap);
-  slab.table(&pl->counters, (size_t)2 * CNT_COUNT);
+  slab.table(&pl->counters, (size_t)2 * kSetWords);
   slab.table(&pl->ulist, unit_cap);
   slab.zeroed(&pl->unit_gen, unit_cap);
   slab.zeroed(&pl->unit_seq, unit_cap);
@@ -1123,9 +1153,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   pl->d_avail = const_cast<int32_t *>(d.avail);
   pl->umin_l = pl->umin_s + unit_cap;
   d.units = reinterpret_cast<UnitRec *>(per_unit);
-  pl->lb_time = reinterpret_cast<float *>(per_unit + unit_cap * sizeof(UnitRec));
-  pl->lb_cost = pl->lb_time + unit_cap;
-  pl->order_time = reinterpret_cast<uint32_t *>(pl->lb_cost + unit_cap);
+  pl->order_time = reinterpret_cast<uint32_t *>(per_unit + unit_cap * sizeof(UnitRec));
   pl->order_cost = pl->order_time + unit_cap;
   k_init_counters<<<1, 64>>>(pl->counters, pl->calls);
   k_quota_table<<<quota_grid(d), 256>>>(d, avail_table(p->avail, ZGr), nullptr, pl->d_avail, 0u);
@@ -1136,26 +1164,17 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   k_shape_agg<<<(unsigned)NS, kShapeAggThreads, (size_t)3 * TP * (Z + GX) * sizeof(float)>>>(d, pl->direct_mem);
   CREATE_TRY(hipGetLastError());
   {
-    // The units' bounds, which let a query pass over a unit whatever the availability becomes.  A unit
-    // without a plan that memory, node size and batch divisibility allow is dropped for good.  Units of equal
-    // size still differ widely in cost, because invalid plans are pruned early, so a timed
-    // pass records how long each remaining unit takes -- with every valid plan evaluated, since what
-    // a query can leave out depends on its objective and its bound (timed with what the fastest plan
-    // leaves out, units that are long for the cheapest one stayed whole: 144 us instead of 77 on
-    // 2.7e8 plans with pairs of types); they are launched longest first, which also deals them
-    // evenly to the hardware's dispatch queues.
+    // The units' bounds, which let a query pass over a unit, or some of its degrees, whatever the
+    // availability becomes.  A unit without a plan that memory, node size and batch divisibility allow is
+    // dropped for good.  The others are launched in ascending order of the smallest time that the present
+    // availability leaves them: what lies far behind then falls to the running limits.  (A timed pass over
+    // the space ordered them, longest first, and cut long ones into parts: 254 of the 1 755 us of a new job
+    // on 1.1e9 plans with pairs of types.  With limits by degree it is the order that shortens a scan.)
     size_t NU = pl->units.size();
-    const size_t n_units_alloc = unit_cap;  // entries of the per-unit tables on the device
-    UnitRec *d_units = const_cast<UnitRec *>(d.units);
-    float *d_cost = reinterpret_cast<float *>(pl->order_time);  // (filled behind this)
-    ScanArgs ca{};
-    ca.umin_s = pl->umin_s;
-    ca.umin_l = pl->umin_l;
-    ca.counters = pl->counters;
-    ca.lim_s = ca.lim_l = kPosInf;
     ga.blocks = d_eblocks;
     ga.n_blocks = (int)pl->eblocks.size();
     ga.link_min = link_min;
+    ga.most = (uint64_t)*std::max_element(p->avail, p->avail + ZGr) * (d.mixed ? 2u : 1u);
     // (a lane takes a microbatch size and a type per segment)
     k_group_bounds<<<pl->n_groups, GX * GX * MB <= 256 ? 64 : kGroupThreads, group_lds_bytes(GX, MB, DP)>>>(d, ga);
     CREATE_TRY(hipGetLastError());
@@ -1178,7 +1197,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     CREATE_TRY(hipGetLastError());
     std::vector<GroupSum> sums(pl->n_groups);
     CREATE_TRY(hipMemcpy(sums.data(), ga.sums, sums.size() * sizeof(GroupSum), hipMemcpyDeviceToHost));
-    std::vector<float> val(NU), lb_time(NU), lb_cost(NU);
+    std::vector<float> val(NU), lb_now(NU), lb_time(NU), lb_cost(NU);
     size_t n_kept = 0;
     for (size_t i = 0; i < NU; ++i) {
       const UnitRec &u = pl->units[i];
@@ -1187,6 +1206,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
       for (int a2 = u.o_lo; u.s >= 2 && a2 < u.o_lo + u.o_cnt && !holds; ++a2)
         holds = (g.seg2[(a2 % GX) >> 5] >> ((a2 % GX) & 31)) & 1u;
       if (!holds && !(n_kept == 0 && i + 1 == NU)) continue;  // launches need a non-empty grid
+      lb_now[n_kept] = g.time_now;
       lb_time[n_kept] = g.time;
       lb_cost[n_kept] = g.cost;
       pl->units[n_kept] = u;
@@ -1194,95 +1214,44 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     }
     pl->units.resize(NU = n_kept);
     d.n_units = (int)NU;
-    CREATE_TRY(hipMemcpy(d_units, pl->units.data(), NU * sizeof(UnitRec), hipMemcpyHostToDevice));
-    ca.ucost = d_cost;
-    launch_units<MODE_SCAN>(pl, SAILOR_MAX_THROUGHPUT, 0, ca, nullptr, nullptr, nullptr);
-    CREATE_TRY(hipGetLastError());
-    CREATE_TRY(hipMemcpy(val.data(), d_cost, NU * sizeof(float), hipMemcpyDeviceToHost));
-    // With the longest units first the launch ends about when the average load of a
-    // workgroup slot is done, unless a unit on its own takes longer than that: such a unit is
-    // cut into parts -- every part keeps the unit's records and takes a share of its lane
-    // space -- within the room the dropped units left in the tables.  A part is taken to last its
-    // share of the unit's time beyond the staging, and keeps the unit's bounds: its own would take
-    // as long as the whole pass behind them (five parts of a space of 1.1e9 plans: 150 of 3 200 us)
-    // and tell few parts apart.  (Cutting units that are merely above the mean costs more in
-    // staging than it gains: spaces with far more units than slots ran 4 % slower that way.)
-    {
-      double total = 0.0;
-      for (size_t i = 0; i < NU; ++i) total += val[i];
-      const double mean = total / (double)NU;
-      int per_cu = 0, cus = 0;
-      const void *scan_kernel = d.mixed ? (const void *)k_units<MODE_SCAN, 0, true, true>
-                                        : (const void *)k_units<MODE_SCAN, 0, true, false>;
-      CREATE_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_kernel,
-                                                              (int)pl->unit_threads, pl->lds_bytes));
-      CREATE_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device));
-      const double slots = (double)std::max(1, per_cu) * (double)std::max(1, cus);
-      const double load = total / std::min((double)NU, slots);  // average load of a slot
-      const double above = std::max(kSplitAbove * load, kSplitAboveMean * mean);
-      const double target = std::max(kSplitTo * load, kSplitToMean * mean);
-      const size_t waves = pl->unit_threads / 64;
-      // 64-lane chunks of a unit's lane space (three segments: pool 1 skips segment 2's pool)
-      const size_t chunks_of_unit = ((size_t)d.MB * d.DP * (size_t)std::max(1, d.ZG - 1) + 63) / 64;
-      const size_t most = std::max<size_t>(1, std::min<size_t>(255, chunks_of_unit / waves));
-      size_t room = n_units_alloc - NU;
-      std::vector<UnitRec> cut;  // the parts, which go behind the units that stay whole
-      std::vector<float> cut_val, cut_time, cut_cost;
-      size_t n_whole = 0;
-      for (size_t i = 0; i < NU; ++i) {
-        UnitRec u = pl->units[i];
-        size_t parts = 1;
-        if (forced_parts > 0) parts = std::min<size_t>((size_t)forced_parts, room + 1);
-        else if (val[i] > above)
-          parts = std::min<size_t>({most, (size_t)std::ceil(val[i] / target), room + 1});
-        u.n_parts = (uint8_t)parts;
-        if (parts == 1) {
-          pl->units[n_whole] = u;
-          val[n_whole] = val[i];
-          lb_time[n_whole] = lb_time[i];
-          lb_cost[n_whole] = lb_cost[i];
-          ++n_whole;
-          continue;
-        }
-        for (size_t c = 0; c < parts; ++c) {
-          u.part = (uint8_t)c;
-          cut.push_back(u);
-          cut_val.push_back(std::min(val[i], kStagingTicks) + std::max(0.f, val[i] - kStagingTicks) / (float)parts);
-          cut_time.push_back(lb_time[i]);
-          cut_cost.push_back(lb_cost[i]);
-        }
-        room -= parts - 1;
-      }
-      const auto behind = [n_whole](auto &whole, const auto &parts) {
-        whole.resize(n_whole);
-        whole.insert(whole.end(), parts.begin(), parts.end());
+    if (forced_parts > 1) {  // every unit's lane space cut into parts
+      const auto repeat = [&](auto &v) {
+        auto whole = v;
+        whole.resize(NU);
+        v.clear();
+        for (size_t i = 0; i < NU; ++i) v.insert(v.end(), (size_t)forced_parts, whole[i]);
       };
-      behind(pl->units, cut);
-      behind(val, cut_val);
-      behind(lb_time, cut_time);
-      behind(lb_cost, cut_cost);
+      repeat(pl->units);
+      repeat(lb_now);
+      repeat(lb_time);
+      repeat(lb_cost);
+      for (size_t i = 0; i < pl->units.size(); ++i) {
+        pl->units[i].n_parts = (uint8_t)forced_parts;
+        pl->units[i].part = (uint8_t)(i % (size_t)forced_parts);
+      }
       d.n_units = (int)(NU = pl->units.size());
+      val.resize(NU);
     }
     // the bounds in the units' final order, and the units sorted by either bound: the host then
     // knows how many units a limit leaves alive, and the device which
-    const std::vector<uint32_t> final_order = order_by(val.data(), NU, true);
+    const std::vector<uint32_t> final_order = order_by(lb_now.data(), NU, false);
     std::vector<UnitRec> sorted(NU);
     for (size_t i = 0; i < NU; ++i) sorted[i] = pl->units[final_order[i]];
     pl->units.swap(sorted);
-    std::vector<char> tables(unit_cap * (sizeof(UnitRec) + 4 * sizeof(float)));  // as they lie in `per_unit`
+    std::vector<char> tables(unit_cap * (sizeof(UnitRec) + 2 * sizeof(uint32_t)));  // as they lie in `per_unit`
     std::memcpy(tables.data(), pl->units.data(), NU * sizeof(UnitRec));
-    float *const words = reinterpret_cast<float *>(&tables[unit_cap * sizeof(UnitRec)]);
+    char *const orders = &tables[unit_cap * sizeof(UnitRec)];
     for (int which = 0; which < 2; ++which) {
       const std::vector<float> &lb = which ? lb_cost : lb_time;
       for (size_t i = 0; i < NU; ++i) val[i] = lb[final_order[i]];
-      std::memcpy(words + which * unit_cap, val.data(), NU * sizeof(float));
       const std::vector<uint32_t> order = order_by(val.data(), NU, false);
-      std::memcpy(words + (2 + which) * unit_cap, order.data(), NU * sizeof(uint32_t));
+      std::memcpy(orders + which * unit_cap * sizeof(uint32_t), order.data(), NU * sizeof(uint32_t));
       std::vector<float> &sorted_lb = which ? pl->lb_cost_sorted : pl->lb_time_sorted;
       sorted_lb.resize(NU);
       for (size_t i = 0; i < NU; ++i) sorted_lb[i] = val[order[i]];
     }
     CREATE_TRY(hipMemcpy(per_unit, tables.data(), tables.size(), hipMemcpyHostToDevice));
+    k_unit_rows<<<(unsigned)std::min<size_t>(1024, (NU * 2 * DP + 255) / 256), 256>>>(d.units, ga.rows, (uint32_t)NU, 2u * (uint32_t)DP, pl->rows);
     k_init_counters<<<1, 64>>>(pl->counters, pl->calls);
     CREATE_TRY(hipDeviceSynchronize());
   }

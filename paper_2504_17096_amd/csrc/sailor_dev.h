@@ -68,6 +68,7 @@ struct EvalBlock {      // a block's shapes are divided alike: into units of the
 };
 
 struct GroupSum {       // what k_group_bounds tells the host of a group of units
+  float time_now;       // smallest over the degrees that the availability at creation leaves
   float time, cost;     // smallest over all degrees, infinite if it holds no plan
   uint32_t seg2[4];     // the types that segment 2 has in its plans, a bit each
 };

@@ -26,24 +26,55 @@ namespace sailor {
 
 // ------------------------------------------------------------------ helpers
 
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fminf(v, __shfl_xor(v, off));
-  return v;
+// op over a wave's values, in every lane, for an op that may take a value twice (minima, maxima).  By moves
+// between lanes within the registers: six trips through the LDS, which __shfl_xor makes, are 0.2 us where a
+// wave has nothing else to do.  (Lanes without a source combine their value with itself.)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_word(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
 }
-
-// The smallest value of a wave, in every lane.
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_value(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, dpp_word<CTRL>(__builtin_bit_cast(uint32_t, v)));
+  } else {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(T, (uint64_t)dpp_word<CTRL>((uint32_t)(x >> 32)) << 32 | dpp_word<CTRL>((uint32_t)x));
+  }
+}
+template <typename T, typename OP>
+__device__ __forceinline__ T wave_fold(T v, OP op) {
+  v = op(v, dpp_value<0x111>(v));  // row_shr:1, 2, 4, 8
+  v = op(v, dpp_value<0x112>(v));
+  v = op(v, dpp_value<0x114>(v));
+  v = op(v, dpp_value<0x118>(v));
+  v = op(v, dpp_value<0x142>(v));  // row_bcast:15, 31
+  v = op(v, dpp_value<0x143>(v));
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+  } else {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(T, (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), 63) << 32 |
+                                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63));
+  }
+}
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-  auto below = [&](auto ctrl) {  // (lanes without a source keep their own value)
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, decltype(ctrl)::value, 0xF, 0xF, false));
-  };
-  below(std::integral_constant<int, 0x111>());  // row_shr:1, 2, 4, 8
-  below(std::integral_constant<int, 0x112>());
-  below(std::integral_constant<int, 0x114>());
-  below(std::integral_constant<int, 0x118>());
-  below(std::integral_constant<int, 0x142>());  // row_bcast:15, 31
-  below(std::integral_constant<int, 0x143>());
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+  return wave_fold(v, [](uint32_t a, uint32_t b) { return min(a, b); });
+}
+__device__ __forceinline__ float wave_min(float v) {
+  return wave_fold(v, [](float a, float b) { return fminf(a, b); });
+}
+__device__ __forceinline__ double wave_min_f64(double v) {
+  return wave_fold(v, [](double a, double b) { return fmin(a, b); });
+}
+__device__ __forceinline__ double wave_max_f64(double v) {
+  return wave_fold(v, [](double a, double b) { return fmax(a, b); });
+}
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
+  return wave_fold(v, [](uint64_t a, uint64_t b) { return a < b ? a : b; });
+}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+  return wave_fold(v, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
 }
 
 // Element j of a three-element array by selects (a lane-dependent subscript would move the
@@ -593,14 +624,13 @@ struct ScanArgs {
   float tau_host;           // ... or, when use_tau_host is set, this threshold
   int use_tau_host;
   int count_only;           // COLLECT: count the candidates under the threshold, keep none
-  uint32_t n_sub;           // COLLECT: workgroups that share one unit
+  uint32_t n_sub;           // workgroups that share one unit
   float lim_s, lim_l;       // constraint limits (strict, loose) on cost or on time
   SurvRec *surv;
   uint32_t surv_cap;
-  float *ucost;             // SCAN, optional: ticks of the 100 MHz clock each unit took, nothing
-                            // left out for the minimum found so far
   const uint32_t *ulist;    // COLLECT, optional: the units to visit and, in counters[CNT_NLIST],
-                            // how many; the grid then strides over the list
+                            // how many; the grid then strides over the list.  SCAN, BEST: the order
+                            // in which the units are launched, if it is not their own
   uint32_t *unit_gen;       // SCAN, optional: per unit, the availability generation its minima
   uint32_t cur_gen;         // were computed at; a scan stamps what it computes with cur_gen
   uint32_t *unit_seq;       // SCAN, with unit_gen: per unit, the call that evaluated it last
@@ -612,20 +642,26 @@ struct ScanArgs {
   float near_band;          // BEST: the tie band.  A unit whose loose minimum lies within near_band of
                             // the smallest strict key seen so far appends its candidates up to there;
                             // the running minimum only falls, so every candidate within the band of
-                            // the final one is among them
-  const float *ulb_con;     // SCAN, optional, with a constraint: per unit, the smallest value the
-                            // constrained quantity takes on any plan of the unit that memory, node
-                            // size and batch allow (availability ignored; the same fp32 arithmetic,
-                            // so an exact bound): a unit whose bound fails the loose limit holds
-                            // nothing and is not staged at all (Sec. 4.2.1, H3, applied to a unit)
+                            // the final one is among them.  SCAN with kth: what its keys may err by
+  uint32_t kth;             // SCAN, if not 0: only units among which the kth smallest key lies matter; COLLECT
+                            // behind it: the threshold is what SCAN's slots give for it (kth_of_slots)
+  // Bounds of a unit's plans by data-parallel degree (k_group_bounds), [unit][2][DP]:
+  const float *rows_con;    // with a constraint, of the constrained quantity: a degree beyond the loose limit
+                            // holds nothing, and a unit without a degree left is not staged at all
+                            // (Sec. 4.2.1, H3, applied to a part of the space)
+  const float *rows_key;    // optional, of the objective: the same against what is known of the result -- the
+                            // running minimum (BEST) or running kth smallest key (SCAN), COLLECT the threshold
+  uint32_t n_seeds;         // SCAN, BEST with rows_key: so many units at the front of the order are shared by n_sub
+                            // workgroups each
+  uint32_t wait_ticks;      // the others wait for what these find, no longer than so many ticks (100 MHz)
+  uint64_t most;            // the most replicas of one GPU that any pool holds: a degree D whose largest segment
+                            // takes w GPUs a replica needs D w <= most
   int direct;               // COLLECT without a scan before it, BEST: ulist names the only units
   uint32_t n_list_host;     // whose bound meets the limit (n_list_host of them).  COLLECT: every
                             // candidate of theirs that is valid and within the loose limit is kept
   uint32_t fresh;           // BEST: the availability is new and travels with this launch (plain pools only): units
                             // take their quotas from it, and the `fresh` workgroups behind theirs
   int32_t *avail_copy;      // bring the quota table and the device's copy up to date
-  const float *ulb_key;     // BEST, optional: the same bound for the objective; a unit that cannot
-                            // come within near_band of the running minimum is passed over
 };
 
 // Two sets, which a plan's calls use in turn; the final kernel of a call resets the next call's.
@@ -635,12 +671,17 @@ enum Counter { CNT_SURV = 0, CNT_OWNER = 1,      // number of the call the set b
                CNT_NLIST = 9,                    // length of the collect pass's unit list
                CNT_DONE = 10,                    // workgroups of the final kernel that have finished
                CNT_COUNT = 16 };
+// Behind a set's counters: the smallest keys that SCAN has come across, a word for the waves that share it;
+// and copies of the running limit, a cache line each, of which a workgroup reads one (thousands of workgroups
+// that ask for one word, and the atomics that lower it, wait for one another: 8 us of a scan of 15).
+constexpr uint32_t kKeySlots = 256, kLimitCopies = 16, kLimitStride = 32,
+                   kSetWords = CNT_COUNT + kKeySlots + kLimitCopies * kLimitStride;
 static_assert(CNT_SURV % 2 == 0 && CNT_OWNER == CNT_SURV + 1 && CNT_COUNT % 2 == 0, "one 8-byte word");
 
 // c: a counter of the set that belongs to `call`
 __device__ __forceinline__ uint32_t counter_reset_value(int c, uint32_t call) {
   if (c == CNT_OWNER) return call;
-  return (c >= CNT_GMIN && c <= CNT_TAU1) ? 0x7f800000u : 0u;  // thresholds start at +inf
+  return (c >= CNT_GMIN && c <= CNT_TAU1) || c >= CNT_COUNT ? 0x7f800000u : 0u;  // thresholds start at +inf
 }
 
 // zeroes the counters selected by mask (a fill kernel, usable under stream capture)
@@ -650,8 +691,8 @@ __global__ void k_zero_counters(uint32_t *c, uint32_t mask) {
 
 // both sets, before `call`
 __global__ void k_init_counters(uint32_t *c, uint32_t call) {
-  for (int i = threadIdx.x; i < 2 * CNT_COUNT; i += blockDim.x)
-    c[i] = counter_reset_value(i % CNT_COUNT, call + (((uint32_t)(i / CNT_COUNT) ^ call) & 1u));
+  for (uint32_t i = threadIdx.x; i < 2 * kSetWords; i += blockDim.x)
+    c[i] = counter_reset_value((int)(i % kSetWords), call + ((i / kSetWords ^ call) & 1u));
 }
 
 // One candidate of the scan: update the running minima, or append it to the survivors.
@@ -719,15 +760,15 @@ struct LaneItem {  // what a lane owns for one chunk of the lane space
   uint32_t dpbit;
 };
 
-// Lane item e of a lane space laid out as mb + MB * (a1 + n_a1 * dp): the dp digit is the
-// slowest, so a wave holds one or two dp values and whole waves drop out together when
-// their data-parallel degree cannot be placed.  mg = ceil(2^32 / (MB * n_a1)).
+// Lane item e of a lane space laid out as mb + MB * (a1 + n_a1 * i), with i the position of its dp in the
+// list s_dp: the dp digit is the slowest, so a wave holds one or two dp values and whole waves drop out
+// together when their data-parallel degree cannot be placed.  mg = ceil(2^32 / (MB * n_a1)).
 __device__ __forceinline__ LaneItem lane_item(const DevPlan &pl, int e, int n_items, int n_a1,
-                                              uint32_t mg) {
+                                              uint32_t mg, const uint8_t *s_dp) {
   LaneItem it;
   it.active = e < n_items;
   const uint32_t ee = it.active ? (uint32_t)e : 0u;
-  const uint32_t dp = fast_div(ee, mg), rem = ee - dp * (uint32_t)(pl.MB * n_a1);
+  const uint32_t i = fast_div(ee, mg), rem = ee - i * (uint32_t)(pl.MB * n_a1), dp = s_dp[i];
   const uint32_t a1 = fast_div(rem, pl.mg_mb);
   it.a1 = (int)a1;
   it.dp = (int)dp;
@@ -763,6 +804,7 @@ struct GroupArgs {
   const EvalBlock *blocks;
   int n_blocks;
   const float *link_min;   // [MB] {within a zone, between zones}, egress
+  uint64_t most;           // ScanArgs::most of the availability at creation
   float *rows;             // [group][2][DP]
   GroupSum *sums;          // [group]
 };
@@ -864,11 +906,71 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_bounds(DevPlan pl, Grou
   __syncthreads();
   if (t < 2 * DP) a.rows[(size_t)blockIdx.x * 2 * DP + t] = __uint_as_float(s_row[t]);
   if (t == 0) {
-    uint32_t mt = s_row[0], mc = s_row[DP];
-    for (int d = 1; d < DP; ++d) { mt = min(mt, s_row[d]); mc = min(mc, s_row[DP + d]); }
-    a.sums[blockIdx.x] = GroupSum{__uint_as_float(mt), __uint_as_float(mc), {s_seg2[0], s_seg2[1], s_seg2[2], s_seg2[3]}};
+    uint64_t w = 0;
+    for (int seg = 0; seg < S; ++seg) w = max(w, (uint64_t)at3(sh.n, seg) * (uint64_t)pl.vals[DP + at3(k, seg)]);
+    uint32_t mt = 0x7f800000u, mc = 0x7f800000u, now = 0x7f800000u;
+    for (int d = 0; d < DP; ++d) {
+      mt = min(mt, s_row[d]);
+      mc = min(mc, s_row[DP + d]);
+      if ((uint64_t)pl.dpv[d] * w <= a.most) now = min(now, s_row[d]);
+    }
+    a.sums[blockIdx.x] = GroupSum{__uint_as_float(now), __uint_as_float(mt), __uint_as_float(mc), {s_seg2[0], s_seg2[1], s_seg2[2], s_seg2[3]}};
   }
 }
+
+// An upper bound of the k-th smallest of a set's key slots, by one wave: the leading bits of that value,
+// the others set.  (+inf while fewer than k slots hold a key.)
+__device__ __forceinline__ uint32_t kth_of_slots(const uint32_t *slots, uint32_t k) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t v[kKeySlots / 64];
+#pragma unroll
+  for (uint32_t i = 0; i < kKeySlots / 64; ++i)
+    v[i] = __hip_atomic_load(&slots[lane + 64 * i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto below = [&](uint32_t x) {  // how many are
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kKeySlots / 64; ++i) n += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(v[i] < x));
+    return n;
+  };
+  constexpr int kCoarse = 10;  // (13 bits of mantissa: 1e-4 above the value at most)
+  if (below(0x7f800000u) < k) return 0x7f800000u;
+  uint32_t at = 0;
+  for (int bit = 30; bit >= kCoarse; --bit)
+    if (below(at | 1u << bit) < k) at |= 1u << bit;
+  return at | ((1u << kCoarse) - 1u);
+}
+
+// What a launch knows of the result while it runs.  BEST: the smallest strict key so far.  SCAN with kth: a
+// key that at least kth candidates do not exceed.  Keys go to slots, each candidate's to one, and as every
+// slot keeps its smallest, kth slots that hold a key up to some value are as many candidates up to it.
+__device__ __forceinline__ uint32_t *limit_copy(const ScanArgs &a, uint32_t i) {
+  return &a.counters[CNT_COUNT + kKeySlots + i % kLimitCopies * kLimitStride];
+}
+__device__ __forceinline__ uint32_t running_limit(const ScanArgs &a) {
+  return __hip_atomic_load(limit_copy(a, blockIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// (a wave) the copies, and the smallest key for the kernels behind this one
+template <int MODE>
+__device__ __forceinline__ void lower_limit(const ScanArgs &a, uint32_t to) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t *const word = lane < kLimitCopies ? limit_copy(a, lane) : &a.counters[CNT_GMIN];
+  if (lane < kLimitCopies + (MODE == MODE_BEST ? 1u : 0u)) atomicMin(word, to);
+}
+
+// The rows of the units' groups, unit by unit, so that a workgroup asks for them together with its record.
+__global__ __launch_bounds__(256) void k_unit_rows(const UnitRec *units, const float *rows, uint32_t n_units, uint32_t width,
+                                                   float *out) {
+  const size_t n = (size_t)n_units * width;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
+    out[i] = rows[(size_t)units[i / width].group * width + i % width];
+}
+
+// What a workgroup walks of its unit: the degrees listed in s_dp, and its share of the lane space's chunks and
+// of the innermost loop.
+struct Walk {
+  const uint8_t *s_dp;
+  int n_dp, chunk, n_chunk, inner, n_inner;
+};
 
 // The lanes of a workgroup own the (mb, pool of segment 1, dp) triples; the pools of the
 // later segments are walked in uniform loops, so their record addresses, zones and
@@ -892,30 +994,39 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_bounds(DevPlan pl, Grou
 // the caller knows, or above the loose limit.  For the fastest plan the lane space is walked from the
 // largest data-parallel degrees down, for the cheapest from the smallest up: what is small early prunes
 // most (cheapest of 1.9e7 plans with a TP degree per segment: 59 us down, 53 up).
-// The scan is bound by vector instructions (70 of its 92 us on 9.2e8 plans with a TP degree per
-// segment); without the bound it took 107 us, and 257 us instead of 156 on 1.1e9 plans with pairs
-// of types.
+//
+// live: what other workgroups have found counts as well.  The first wave asks for the running limit
+// once per round, and takes the answer to the question before, so that no round waits for it; a degree
+// whose bound (s_rows) lies above it falls without a record read.
 template <int S, int MODE, int OBJ, bool HASB, bool MIXED>
 __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, const UnitRec &u,
                                           const float4 *rec_lo, const float4 *rec_hi,
                                           const uint32_t *rbits, const float4 *pair,
                                           const uint32_t *q13, const uint64_t *isect, int w0,
-                                          int w1, int w2, float tau, int sub, int n_sub,
+                                          int w1, int w2, float tau, const Walk &wk,
+                                          const float *s_rows, bool live,
                                           uint32_t *s_min, float &ms, float &ml) {
-  // the chunks of the lane space are dealt round-robin to the waves of the n_sub
-  // workgroups that share the unit
+  // the chunks of the lane space are dealt round-robin to the waves of the workgroups that share the unit
   const int ZG = pl.ZG, G = pl.GX, MB = pl.MB, DP = pl.DP, Z = pl.Z;
   const int lane = threadIdx.x & 63;
-  const int wave = (int)(threadIdx.x >> 6) + (int)(blockDim.x >> 6) * sub;
-  const int nwave = (int)(blockDim.x >> 6) * n_sub;
+  const int wave = (int)(threadIdx.x >> 6) + (int)(blockDim.x >> 6) * wk.chunk;
+  const int nwave = (int)(blockDim.x >> 6) * wk.n_chunk;
   const bool single0 = u.n[0] == 1, single1 = u.n[1] == 1;
   const int tp = u.tp[0];
   const uint64_t ubase = u.base;
   // the limit in force: the smallest strict key so far, COLLECT the threshold
+  uint32_t asked = 0x7f800000u;
+  auto ask = [&]() {  // (in front of a loop without loads from memory: they would wait for it)
+    if (MODE != MODE_COLLECT && live && threadIdx.x < 64)
+      asked = running_limit(a);
+  };
   auto limit = [&]() {
     if (MODE == MODE_COLLECT) return tau;
+    if (live && threadIdx.x == 0) atomicMin(s_min, __float_as_uint(__uint_as_float(asked) * a.near_band));
     return __uint_as_float(__hip_atomic_load(s_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
   };
+  // can plans of this degree still matter?
+  auto alive_row = [&](int dp, float l0) { return MODE == MODE_COLLECT || !live || s_rows[dp] <= l0; };
   // can a plan that starts like this still matter?
   auto alive = [&](const Acc &p, const LaneC &lc, float l0) {
     float T, C;
@@ -925,20 +1036,22 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   };
   // (one thread of the waves that improve on what the workgroup has)
   auto report = [&](float l0) {
-    if (MODE == MODE_COLLECT || (MODE == MODE_SCAN && a.ucost)) return;
+    if (MODE == MODE_COLLECT) return;
     if (wave_any(ms < l0)) {
       const float m = wave_min(ms);
       if (lane == 0) atomicMin(s_min, __float_as_uint(m));
     }
   };
   if (S <= 2) {
-    const int nin = MB * DP * ZG;
+    const int nin = S == 1 && wk.inner != 0 ? 0 : MB * wk.n_dp * ZG;
+    const int o_from = u.o_lo + u.o_cnt * wk.inner / wk.n_inner, o_to = u.o_lo + u.o_cnt * (wk.inner + 1) / wk.n_inner;
     const int rounds = (nin - 1 - wave * 64 + nwave * 64) / (nwave * 64);  // (0 for waves beyond the lane space)
     for (int i = 0; i < rounds; ++i) {
       const int e0 = (wave + (OBJ == 0 ? rounds - 1 - i : i) * nwave) * 64;
-      const LaneItem it = lane_item(pl, e0 + lane, nin, ZG, pl.mg_mbzg);
+      const LaneItem it = lane_item(pl, e0 + lane, nin, ZG, pl.mg_mbzg, wk.s_dp);
       const int a1 = it.a1;
-      uint32_t b0 = rbits[a1 * MB + it.mb] & it.dpbit;
+      const float l0 = limit();
+      uint32_t b0 = alive_row(it.dp, l0) ? rbits[a1 * MB + it.mb] & it.dpbit : 0u;
       if (!wave_any(b0 != 0)) continue;
       const Rec r0 = rec_load(rec_lo, rec_hi, a1 * MB + it.mb);
       const int z1 = (int)fast_div((uint32_t)a1, pl.mg_g);
@@ -952,11 +1065,11 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         visit<MODE, OBJ, HASB>(a, T, C, b0 != 0, tau, idx0, u.shape, ms, ml);
         continue;
       }
-      const float l0 = limit();
       if (!alive(A0, it.lc, l0)) b0 = 0;
       if (!wave_any(b0 != 0)) continue;
-      int z2 = u.o_lo / G, g2 = u.o_lo % G;
-      for (int a2 = u.o_lo; a2 < u.o_lo + u.o_cnt; ++a2) {
+      ask();
+      int z2 = o_from / G, g2 = o_from % G;
+      for (int a2 = o_from; a2 < o_to; ++a2) {
         const int i1 = (ZG + a2) * MB + it.mb;
         uint32_t b1 = (a1 != a2) ? (b0 & rbits[i1]) : 0u;
         if (MIXED && b1 != 0 && pool_bit(isect, a2, a1))
@@ -977,17 +1090,18 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
       report(l0);
     }
   } else {
-    const int nin = MB * DP * (ZG - 1);
+    const int nin = MB * wk.n_dp * (ZG - 1);
+    const int p_from = ZG * wk.inner / wk.n_inner, p_to = ZG * (wk.inner + 1) / wk.n_inner;
     const int rounds = (nin - 1 - wave * 64 + nwave * 64) / (nwave * 64);
     int z2 = u.o_lo / G, g2 = u.o_lo % G;
     for (int a2 = u.o_lo; a2 < u.o_lo + u.o_cnt; ++a2) {
-
       for (int i = 0; i < rounds; ++i) {
         const int e0 = (wave + (OBJ == 0 ? rounds - 1 - i : i) * nwave) * 64;
-        const LaneItem it = lane_item(pl, e0 + lane, nin, ZG - 1, pl.mg_mbzg1);
+        const LaneItem it = lane_item(pl, e0 + lane, nin, ZG - 1, pl.mg_mbzg1, wk.s_dp);
         const int a1 = it.a1 + (it.a1 >= a2 ? 1 : 0);  // skip the pool of segment 2
         const int i0 = a1 * MB + it.mb, i1 = (ZG + a2) * MB + it.mb;
-        uint32_t b1 = rbits[i0] & it.dpbit & rbits[i1];
+        const float l0 = limit();
+        uint32_t b1 = alive_row(it.dp, l0) ? rbits[i0] & it.dpbit & rbits[i1] : 0u;
         if (!wave_any(b1 != 0)) continue;
         const Rec r0 = rec_load(rec_lo, rec_hi, i0);
         const Rec r1 = rec_load(rec_lo, rec_hi, i1);
@@ -995,7 +1109,6 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         const float4 *pairm = pair + it.mb * Z * Z;
         const float4 p12 = pairm[z1 * Z + z2];
         const Acc A1 = acc_cross(acc_begin(r0), r1, p12.x, p12.y, p12.z, single0, true);
-        const float l0 = limit();
         if (!alive(A1, it.lc, l0)) b1 = 0;
         if (!wave_any(b1 != 0)) continue;
         const uint32_t q13a = MIXED ? 0u : q13[a1];
@@ -1003,8 +1116,9 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         if (rel2 < 0) rel2 += ZG;
         const uint64_t idx0 = ubase + (uint64_t)(it.mb + MB * (tp + pl.TP * (it.dp + DP * a1))) +
                               (uint64_t)pl.inner * (uint64_t)rel2;
-        int z3 = 0, g3 = 0;
-        for (int a3 = 0; a3 < ZG; ++a3) {
+        ask();
+        int z3 = p_from / G, g3 = p_from % G;
+        for (int a3 = p_from; a3 < p_to; ++a3) {
           if (a3 != a2) {  // uniform
             const int i2 = (2 * ZG + a3) * MB + it.mb;
             uint32_t b2 = b1 & rbits[i2];
@@ -1035,14 +1149,20 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   }
 }
 
-// Folds a scanned unit's minima into the global minimum.  One thread.  Returns (best plan) the
+// The smallest strict key so far, by the way that a call's workgroups make it known.
+__device__ __forceinline__ uint32_t smallest_key(const ScanArgs &a, bool live) {
+  return live ? running_limit(a) : __hip_atomic_load(&a.counters[CNT_GMIN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Folds a scanned unit's minima into the global minimum.  One wave.  Returns (best plan) the
 // threshold up to which the unit's candidates are kept, or -1 if it has none that near.
-__device__ __forceinline__ float unit_publish(const ScanArgs &a, float ms, float ml) {
+__device__ __forceinline__ float unit_publish(const ScanArgs &a, bool live, uint32_t seen, float ms, float ml) {
   // keys are non-negative, so their bit patterns order like unsigned integers
-  // (a stale read only costs a redundant atomic; most units lose and skip theirs)
-  const uint32_t seen = __hip_atomic_load(&a.counters[CNT_GMIN], __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-  if (__float_as_uint(ms) < seen) atomicMin(&a.counters[CNT_GMIN], __float_as_uint(ms));
+  // (a stale `seen` only costs redundant atomics; most units lose and skip theirs)
+  if (__float_as_uint(ms) < seen) {
+    if (live) lower_limit<MODE_BEST>(a, __float_as_uint(ms));
+    else if ((threadIdx.x & 63u) == 0) atomicMin(&a.counters[CNT_GMIN], __float_as_uint(ms));
+  }
   // (a stale `seen` is larger than the true running minimum: more is kept, nothing is lost)
   const float tau = fminf(__uint_as_float(seen), ms) * a.near_band;
   return ml < kPosInf && ml <= tau ? tau : -1.0f;
@@ -1054,44 +1174,121 @@ __host__ __device__ inline size_t unit_lds_records(int ZG, int MB) {
   return ((size_t)3 * ZG * MB + 3) & ~(size_t)3;  // a multiple of 4, so that what follows stays 16-byte aligned
 }
 
+// What a pass leaves behind for a unit.  One thread (sub: of the first of the workgroups that share the
+// unit).  The minima are read where a pass follows that visits units by them: a shared unit, whose
+// workgroups each know a part of it, is visited in any case.  What the constraint or the running minimum rules
+// out is not counted as evaluated; what falls to the availability or to a k-th key is.
+template <int MODE>
+__device__ __forceinline__ void unit_done(const ScanArgs &a, uint32_t uidx, int sub, uint32_t n_sub, float ms, float ml, bool counts) {
+  if (MODE == MODE_COLLECT || (MODE == MODE_BEST && a.direct) || sub != 0) return;
+  const bool shared = n_sub > 1;
+  a.umin_s[uidx] = shared ? 0.f : ms;
+  a.umin_l[uidx] = shared ? 0.f : ml;
+  if (a.unit_gen) {
+    a.unit_gen[uidx] = a.cur_gen;
+    if (counts) a.unit_seq[uidx] = a.call_seq;
+  }
+}
+
+// A lane's test of a unit: is there a degree that can matter?  (unit_work finds out which, and asks for the
+// limit once more.)
+template <int MODE, bool HASB>
+__device__ __forceinline__ bool unit_test(const DevPlan &pl, const ScanArgs &a, uint32_t uidx, float key_limit) {
+  const UnitRec &u = pl.units[uidx];
+  const float *const con = a.rows_con + (size_t)uidx * 2 * pl.DP, *const key = a.rows_key + (size_t)uidx * 2 * pl.DP;
+  uint64_t w = 0;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) w = max(w, (uint64_t)u.n[j] * (uint32_t)pl.vals[pl.DP + u.tp[j]]);
+  bool any = false, meets = false, near = false;
+#pragma unroll 4
+  for (int d = 0; d < pl.DP; ++d) {
+    const bool m = !HASB || con[d] <= a.lim_l, n = key[d] <= key_limit;
+    any |= m && n && (uint64_t)pl.dpv[d] * w <= a.most;
+    meets |= m;
+    near |= n;
+  }
+  if (!any) unit_done<MODE>(a, uidx, 0, 1u, kPosInf, kPosInf, meets && (MODE != MODE_BEST || near));
+  return any;
+}
+
 // One workgroup per unit: stage the unit's segment records in LDS, then every lane walks
 // its (mb, dp, pool 1) triple over the unit's outer pool digits.  Everything the staging
 // needs comes from the unit record and tables that do not depend on one another, so all of
 // its global loads are in flight together and one barrier ends it.
 template <int MODE, int OBJ, bool HASB, bool MIXED>
 __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, const AvailArg<MODE, MIXED> &avail,
-                                          uint32_t uidx, int sub, uint32_t n_sub, uint4 *lds_raw) {
-  const unsigned long long t_begin = (MODE == MODE_SCAN && a.ucost) ? wall_clock64() : 0ull;
+                                          uint32_t uidx, int sub, uint32_t n_sub, float tau, uint4 *lds_raw) {
   const UnitRec u = pl.units[uidx];
   const bool fresh = kAvailRides<MODE, MIXED> && a.fresh != 0;
-  float tau = kPosInf, key_limit = kPosInf;
-  if ((MODE == MODE_SCAN || MODE == MODE_BEST) && (a.ulb_con || a.ulb_key)) {
-    bool dead = false;  // must come out the same in every wave of the workgroup
-    if (HASB && a.ulb_con) dead = !(a.ulb_con[uidx] <= a.lim_l);
-    if (MODE == MODE_BEST && a.ulb_key) {
-      // the running minimum changes while the workgroup reads it: one thread reads, all follow
-      __shared__ uint32_t s_seen;
-      if (threadIdx.x == 0)
-        s_seen = __hip_atomic_load(&a.counters[CNT_GMIN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool live = MODE != MODE_COLLECT && a.rows_key != nullptr;
+  const int n0 = u.n[0], n1 = u.n[1], n2 = u.n[2];
+  const int k0 = u.tp[0], k1 = u.tp[1], k2 = u.tp[2];            // tp index of each segment
+  const int tv0 = pl.tpv[k0], tv1 = pl.tpv[k1], tv2 = pl.tpv[k2];
+  const int w0 = n0 * tv0, w1 = n1 * tv1, w2 = n2 * tv2;        // GPUs of one replica
+  // The degrees that can matter, the same in every wave: the running limit changes while the workgroup
+  // reads it, so one thread reads and all follow.
+  __shared__ float s_rows[kMaxDP];
+  uint32_t degrees, fixed;  // (fixed: those that the workgroups which share a unit agree on)
+  bool counts;  // not ruled out by the constraint or the running minimum
+  float key_limit = tau;
+  {
+    __shared__ uint32_t s_seen;
+    const int d = threadIdx.x & 63;
+    const bool have = d < pl.DP;
+    const float con = HASB && have ? a.rows_con[(size_t)uidx * 2 * pl.DP + d] : 0.f;
+    const float key = a.rows_key && have ? a.rows_key[(size_t)uidx * 2 * pl.DP + d] : 0.f;
+    const uint64_t replicas = have ? (uint64_t)(uint32_t)pl.vals[d] : 0u;
+    if (live) {
+      if (threadIdx.x < 64) {
+        uint32_t seen = running_limit(a);
+        if (n_sub == 1 && a.wait_ticks != 0 && !(__uint_as_float(seen) < kPosInf)) {
+          const unsigned long long until = wall_clock64() + a.wait_ticks;
+          do {
+            __builtin_amdgcn_s_sleep(12);
+            seen = running_limit(a);
+          } while (!(__uint_as_float(seen) < kPosInf) && wall_clock64() < until);
+          if (MODE == MODE_SCAN) {  // (the first bound comes from the quickest of them)
+            __builtin_amdgcn_s_sleep(64);
+            seen = running_limit(a);
+          }
+        }
+        if (threadIdx.x == 0) s_seen = seen;
+      }
+      if ((int)threadIdx.x < pl.DP) s_rows[threadIdx.x] = key;
       __syncthreads();
       key_limit = __uint_as_float(s_seen) * a.near_band;  // (nothing above it matters to the query)
-      dead = dead || a.ulb_key[uidx] > key_limit;
     }
-    if (dead) {
-      if (threadIdx.x == 0 && !(MODE == MODE_BEST && a.direct)) {
-        a.umin_s[uidx] = kPosInf;
-        a.umin_l[uidx] = kPosInf;
-        if (a.unit_gen) a.unit_gen[uidx] = a.cur_gen;  // (not counted as evaluated: unit_seq stays)
-        if (a.ucost) a.ucost[uidx] = 0.f;
-      }
-      return;
-    }
+    const uint64_t w = (uint64_t)max(w0, max(w1, w2));
+    const bool meets = have && (!HASB || con <= a.lim_l), near = have && key <= key_limit;
+    fixed = (uint32_t)__builtin_amdgcn_ballot_w64(meets && (near || MODE != MODE_COLLECT) && replicas * w <= a.most);
+    degrees = fixed & (uint32_t)__builtin_amdgcn_ballot_w64(near);
+    counts = wave_any(meets) && (MODE != MODE_BEST || wave_any(near));
   }
-  if (MODE == MODE_COLLECT) {
-    tau = a.use_tau_host ? a.tau_host : __uint_as_float(*a.tau_src) * a.band;
-    if (!a.direct) {  // (without a scan before this pass there are no minima to consult)
-      const float um = a.umin_l[uidx];
-      if (!(um < kPosInf && um <= tau)) return;  // uniform over the workgroup
+  if (degrees == 0) {
+    if (threadIdx.x == 0) unit_done<MODE>(a, uidx, sub, n_sub, kPosInf, kPosInf, counts);
+    return;
+  }
+  // The lane space holds the degrees that matter only: with two of nine a unit takes a quarter of the rounds.
+  // Workgroups that share the unit divide its chunks first, a round for each of their waves, and then the
+  // innermost loop.  (A part of a unit that was cut has all degrees: chunk c goes to part c / waves mod n_parts,
+  // and the collect pass must visit exactly what the scan saw.)
+  __shared__ uint8_t s_dp[kMaxDP];
+  Walk wk{s_dp, 0, 0, 1, 0, 1};
+  {
+    const uint32_t dps = u.n_parts > 1 ? (1u << pl.DP) - 1u : (n_sub > 1 ? fixed : degrees);
+    wk.n_dp = __popc(dps);
+    const uint32_t d = threadIdx.x;
+    if (d < (uint32_t)pl.DP && ((dps >> d) & 1u)) s_dp[__popc(dps & ((1u << d) - 1u))] = (uint8_t)d;
+    if (u.n_parts > 1) {
+      wk.chunk = sub * (int)u.n_parts + (int)u.part;
+      wk.n_chunk = (int)(u.n_parts * n_sub);
+    } else if (n_sub > 1) {
+      const uint32_t rounds = ((uint32_t)(pl.MB * wk.n_dp * pl.ZG) + blockDim.x - 1u) / blockDim.x;
+      wk.n_chunk = (int)min(n_sub, rounds);
+      wk.n_inner = (int)n_sub / wk.n_chunk;
+      wk.chunk = sub % wk.n_chunk;
+      wk.inner = sub / wk.n_chunk;
+      if (wk.inner >= wk.n_inner) return;  // (the rest of the division; never the first)
     }
   }
   const int ZG = pl.ZG, G = pl.GX, MB = pl.MB, Z = pl.Z, S = u.s;
@@ -1108,10 +1305,6 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   const int t = threadIdx.x;
   if (MODE != MODE_COLLECT && t == 0) s_min = __float_as_uint(key_limit);
 
-  const int n0 = u.n[0], n1 = u.n[1], n2 = u.n[2];
-  const int k0 = u.tp[0], k1 = u.tp[1], k2 = u.tp[2];            // tp index of each segment
-  const int tv0 = pl.tpv[k0], tv1 = pl.tpv[k1], tv2 = pl.tpv[k2];
-  const int w0 = n0 * tv0, w1 = n1 * tv1, w2 = n2 * tv2;        // GPUs of one replica
   // Re-planning after an availability change: the unit is staged as always, and if every
   // validity word comes out as at its last evaluation its minima still hold.  With pairs of
   // types the shared-pool table is read during the evaluation, not the staging: a unit of two
@@ -1139,10 +1332,10 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     rec_store(rec_lo, rec_hi, rbits, i,
               make_rec(ta, pl.syncz[sl * Z + z], pl.upd[sl * G + g], pl.price_f[g],
                        pl.tsec_f[(mb * Z + z) * Z + z], seg == 0 ? n0 : (seg == 1 ? n1 : n2),
-                       seg == 0 ? tv0 : (seg == 1 ? tv1 : tv2), bits));
+                       seg == 0 ? tv0 : (seg == 1 ? tv1 : tv2), bits & degrees));
     // a segment that no pool can host validly rules the whole unit out
     const bool counts = seg != 1 || (p >= (int)u.o_lo && p < (int)(u.o_lo + u.o_cnt));
-    if (bits != 0 && counts) any_here |= 1u << seg;
+    if ((bits & degrees) != 0 && counts) any_here |= 1u << seg;
     if (keep_bits && counts) {  // (segment 2's pools outside the unit's range do not concern it)
       if (!a.incremental) ub[i] = bits;
       else if (ub[i] != bits) { ub[i] = bits; any_here |= 8u; }
@@ -1179,59 +1372,51 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   for (int w = 0; w < (int)(blockDim.x >> 6); ++w) any_all |= s_any[w];
   if (MODE == MODE_SCAN && a.incremental && !(any_all & 8u) && !joint_changed) {
     // every validity bit is what it was: the minima still hold (uniform over the workgroup)
-    if (t == 0) unit_publish(a, a.umin_s[uidx], a.umin_l[uidx]);
+    if (t < 64) unit_publish(a, false, smallest_key(a, false), a.umin_s[uidx], a.umin_l[uidx]);
     return;
   }
   any_all &= 7u;
   if (any_all != (1u << S) - 1u) {  // uniform over the workgroup
-    if (MODE != MODE_COLLECT && t == 0 && !(MODE == MODE_BEST && a.direct)) {
-      a.umin_s[uidx] = kPosInf;
-      a.umin_l[uidx] = kPosInf;
-      if (a.unit_gen) {
-        a.unit_gen[uidx] = a.cur_gen;
-        a.unit_seq[uidx] = a.call_seq;  // evaluated by this call
-      }
-      if (a.ucost) a.ucost[uidx] = (float)(wall_clock64() - t_begin);
-    }
+    if (t == 0) unit_done<MODE>(a, uidx, sub, n_sub, kPosInf, kPosInf, true);
     return;
   }
 
   float ms = kPosInf, ml = kPosInf;
-  // The unit's own share of the lane space, divided further among the n_sub workgroups.
-  // Chunk c of the lane space goes to wave c mod (waves * n_shares), so with the part as the
-  // fast digit of the share a part keeps the same chunks ((c / waves) mod n_parts == part)
-  // whatever n_sub is: the collect pass must visit exactly what the scan saw.
-  const int share = sub * (int)u.n_parts + (int)u.part, n_shares = (int)u.n_parts * (int)n_sub;
   auto walk = [&](auto mode) {
     constexpr int M = decltype(mode)::value;
-    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, &s_min, ms, ml);
-    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, &s_min, ms, ml);
-    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, share, n_shares, &s_min, ms, ml);
+    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, ms, ml);
+    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, ms, ml);
+    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, ms, ml);
   };
   walk(std::integral_constant<int, MODE>());
 
   if (MODE != MODE_COLLECT) {
+    const bool folds = !(MODE == MODE_SCAN && live);  // (a scan for the kth smallest key has no use for the smallest one)
+    const uint32_t seen = folds && t < 64 ? smallest_key(a, live) : 0u;  // (on its way during the reduction)
     if (!HASB) ml = ms;
     ms = wave_min(ms);
     ml = wave_min(ml);
     if ((t & 63) == 0) { red[0][t >> 6] = ms; red[1][t >> 6] = ml; }
     __syncthreads();
-    if (t == 0) {
-      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-        ms = fminf(ms, red[0][w]);
-        ml = fminf(ml, red[1][w]);
+    if (t < 64) {
+      const bool has = t < (int)(blockDim.x >> 6);
+      ms = wave_min(has ? red[0][t] : kPosInf);
+      ml = wave_min(has ? red[1][t] : kPosInf);
+      if (folds) {
+        const float keep = unit_publish(a, live, seen, ms, ml);
+        if (MODE == MODE_BEST && t == 0) s_min = __float_as_uint(keep);
       }
-      const float keep = unit_publish(a, ms, ml);
-      if (MODE == MODE_BEST) s_min = __float_as_uint(keep);
-      if (!(MODE == MODE_BEST && a.direct)) {  // (several workgroups share a listed unit)
-        a.umin_s[uidx] = ms;
-        a.umin_l[uidx] = ml;
-        if (a.unit_gen) {
-          a.unit_gen[uidx] = a.cur_gen;
-          a.unit_seq[uidx] = a.call_seq;  // evaluated by this call
-        }
+      if (t == 0) unit_done<MODE>(a, uidx, sub, n_sub, ms, ml, true);
+    }
+    if (MODE == MODE_SCAN && live && t < 64) {  // the waves' minima are keys of as many candidates
+      const uint32_t m = __float_as_uint(t < (int)(blockDim.x >> 6) ? red[0][t] : kPosInf);
+      if (m < 0x7f800000u)
+        atomicMin(&a.counters[CNT_COUNT + (blockIdx.x * (blockDim.x >> 6) + (uint32_t)t) % kKeySlots], m);
+      // (by all workgroups this would cost more than it prunes: they would wait for one another)
+      if (a.n_seeds != 0 && blockIdx.x % 4u == 0u) {
+        const uint32_t at = kth_of_slots(a.counters + CNT_COUNT, a.kth);
+        if (at < running_limit(a)) lower_limit<MODE>(a, at);
       }
-      if (a.ucost) a.ucost[uidx] = (float)(wall_clock64() - t_begin);
     }
   }
   if (MODE == MODE_BEST) {
@@ -1244,9 +1429,25 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   }
 }
 
-// SCAN: one workgroup per unit.  COLLECT: n_sub workgroups share a unit; with a unit list
-// the grid strides over the list instead of covering every unit.  BEST: as SCAN, or n_sub workgroups
-// for each of a few listed units.
+// How a running limit is used where the units do not fit on the chip at once.  The units at the front of the
+// order, which lower it, are short because workgroups share them; the other workgroups wait for what these
+// find (a bounded time: about what that takes) and take several units each, so that the waves of all of them
+// are launched while the first ones work (a wave costs the dispatcher about a nanosecond: 16 000 workgroups
+// 48 us).  Nearly all units then fall in one test of their bounds.  Bound by the chain of a shared unit
+// (record, staging, walk, limit: 8 us) and that of the units left alive (10 us).  Scan for the 64
+// fastest of 9.2e8 plans with a TP degree per segment 86 -> 28 us, fastest of 1.0e8 28 -> 18, cheapest of
+// 1.1e9 with pairs of types 167 -> 19.  Units that do fit at once gain nothing by waiting (1 632 of them: 19
+// us, and 15.5 as they come).
+constexpr uint32_t kScanWaves = 6144, kScanPerWg = 32, kBestSeeds = 16, kBestSeedSub = 16, kKthSeeds = 64, kKthSeedSub = 8;
+__host__ __device__ inline uint32_t scan_workgroups(uint32_t n_units, uint32_t waves) {
+  uint32_t per = (n_units * waves + kScanWaves - 1) / kScanWaves;
+  per = per < kScanPerWg ? per : kScanPerWg;
+  return per ? (n_units + per - 1) / per : 0u;
+}
+
+// SCAN: a workgroup for every unit or every few.  COLLECT: n_sub workgroups share a unit; the grid strides over a list of
+// units, or over all of them, of which it visits those whose minimum is within the threshold.  BEST: as SCAN,
+// or n_sub workgroups for each of a few listed units.
 //
 // A new availability rides on the call's first launch (ScanArgs::fresh): a quota table made by a kernel
 // of its own in front of it cost 6 of the 44 us that a new table and its fastest plan took on 6.8e6
@@ -1265,20 +1466,50 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
       return;
     }
   }
-  if (MODE == MODE_BEST && a.direct) {
-    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist[blockIdx.x / a.n_sub], (int)(blockIdx.x % a.n_sub), a.n_sub, lds_raw);
-  } else if (MODE != MODE_COLLECT) {
-    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, blockIdx.x, 0, 1u, lds_raw);
-  } else if (!a.ulist) {
-    unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, blockIdx.x / a.n_sub, (int)(blockIdx.x % a.n_sub), a.n_sub,
-                               lds_raw);
-  } else {
-    const uint32_t n_list = a.direct ? a.n_list_host : a.counters[CNT_NLIST];
-    const uint32_t per_round = gridDim.x / a.n_sub;
-    const int sub = (int)(blockIdx.x % a.n_sub);
-    for (uint32_t e = blockIdx.x / a.n_sub; e < n_list; e += per_round) {  // uniform
-      unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist[e], sub, a.n_sub, lds_raw);
+  if (MODE != MODE_COLLECT) {
+    const uint32_t n_shared = MODE == MODE_BEST && a.direct ? a.n_list_host : a.n_seeds;
+    const bool shared = blockIdx.x < n_shared * a.n_sub;
+    const uint32_t n_sub = shared ? a.n_sub : 1u, sub = shared ? blockIdx.x % n_sub : 0u;
+    const uint32_t first = shared ? blockIdx.x / n_sub : blockIdx.x - n_shared * (a.n_sub - 1u);  // in the order
+    const uint32_t step = gridDim.x - a.fresh - n_shared * a.n_sub, n = (uint32_t)pl.n_units;  // workgroups behind the shared units'
+    uint32_t hits = 1;
+    for (bool more = !shared && first + step < n; hits != 0;) {  // uniform
+      const uint32_t e = first + (uint32_t)__builtin_ctz(hits) * step;
+      unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist ? a.ulist[e] : e, (int)sub, n_sub, kPosInf, lds_raw);
+      hits &= hits - 1;
+      if (!more && hits == 0) break;
       __syncthreads();  // the staging area is reused
+      if (more) {       // of the units behind the first, `step` apart: those that are alive by now
+        __shared__ uint32_t s_hits;
+        if (threadIdx.x < 64) {
+          const uint32_t mine = first + threadIdx.x * step;
+          const bool alive = threadIdx.x > 0 && threadIdx.x < kScanPerWg && mine < n &&
+                             unit_test<MODE, HASB>(pl, a, a.ulist ? a.ulist[mine] : mine, __uint_as_float(running_limit(a)) * a.near_band);
+          const uint64_t all = __builtin_amdgcn_ballot_w64(alive);
+          if (threadIdx.x == 0) s_hits = (uint32_t)all;
+        }
+        __syncthreads();
+        hits = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_hits);
+        more = false;
+      }
+    }
+  } else {
+    const float tau = a.use_tau_host ? a.tau_host
+                      : __uint_as_float(a.kth ? kth_of_slots(a.counters + CNT_COUNT, a.kth) : *a.tau_src) * a.band;
+    const uint32_t per_round = gridDim.x / a.n_sub, lane = threadIdx.x & 63u;
+    const uint32_t n = !a.ulist ? (uint32_t)pl.n_units : a.direct ? a.n_list_host : a.counters[CNT_NLIST];
+    for (uint32_t e = blockIdx.x / a.n_sub; e < n; e += (a.ulist ? 1u : 64u) * per_round) {  // uniform
+      uint64_t hits = 1;
+      if (!a.ulist) {  // 64 units, a lane each: which of them hold a candidate under the threshold
+        const uint32_t mine = e + lane * per_round;
+        const float um = mine < n ? a.umin_l[mine] : kPosInf;
+        hits = __builtin_amdgcn_ballot_w64(um < kPosInf && um <= tau);
+      }
+      for (; hits != 0; hits &= hits - 1) {  // uniform
+        const uint32_t at = e + (uint32_t)__builtin_ctzll(hits) * per_round;
+        unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist ? a.ulist[at] : at, (int)(blockIdx.x % a.n_sub), a.n_sub, tau, lds_raw);
+        __syncthreads();  // the staging area is reused
+      }
     }
   }
 }
@@ -1559,12 +1790,6 @@ struct RefineLds {  // per-wave staging of the per-stage terms that are summed i
   double t[kMaxStages], dol[kMaxStages], comm[kMaxStages];
 };
 
-__device__ __forceinline__ double wave_max_f64(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  return v;
-}
-
 // The two real types a | b << 8 of extended type x (the plain ones, then the pairs a < b in
 // lexicographic order), by arithmetic: what DevPlan::xt holds, without the trip to memory
 // in front of the loads that depend on it.
@@ -1691,11 +1916,7 @@ __device__ __forceinline__ void eval_exact_wave(const DevPlan &pl, const Cand &c
     lds.comm[i] = comm;
   }
   if (__builtin_amdgcn_ballot_w64(oom != 0) != 0) mask |= 1u;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint64_t o = __shfl_xor((unsigned long long)peak, off);
-    peak = o > peak ? o : peak;
-  }
+  peak = wave_max_u64(peak);
   max_t = wave_max_f64(max_t);
   t_sync = wave_max_f64(t_sync);
   t_upd = wave_max_f64(t_upd);
@@ -1861,7 +2082,7 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
     n_ref = __hip_atomic_load(&a.counters[CNT_REF], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     n_feas = __hip_atomic_load(&a.counters[CNT_FEAS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (t < CNT_COUNT) next_counters[t] = counter_reset_value(t, owner + 1);  // for the next call
+  for (int c = t; c < (int)kSetWords; c += kBestWaves * 64) next_counters[c] = counter_reset_value(c, owner + 1);  // for the next call
   const RefRec *const ref = alone ? s_ref : a.ref;
   const uint32_t stored = alone ? n_ref : min(n_ref, a.ref_cap);
   if (alone) {
@@ -1869,8 +2090,7 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
   }
   double best = __builtin_huge_val();
   for (uint32_t i = t; i < stored; i += kBestWaves * 64) best = fmin(best, key_of(ref[i]));
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) best = fmin(best, __shfl_xor(best, off));
+  best = wave_min_f64(best);
   if (lane == 0) s_key[wv] = best;
   __syncthreads();
 #pragma unroll
@@ -1880,11 +2100,10 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
   uint32_t bp = 0;
   for (uint32_t i = t; i < stored; i += kBestWaves * 64)
     if (ref[i].mask == 0 && key_of(ref[i]) <= limit && ref[i].idx < bi) { bi = ref[i].idx; bp = i; }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned long long oi = __shfl_xor(bi, off);
-    const uint32_t op = __shfl_xor(bp, off);
-    if (oi < bi) { bi = oi; bp = op; }
+  {
+    const unsigned long long lowest = wave_min_u64(bi);
+    bp = (uint32_t)__builtin_amdgcn_readlane((int)bp, __builtin_ctzll(__builtin_amdgcn_ballot_w64(bi == lowest)));
+    bi = lowest;
   }
   if (lane == 0) { s_idx[wv] = bi; s_pos[wv] = bp; }
   __syncthreads();
@@ -1932,8 +2151,9 @@ __global__ __launch_bounds__(kRankLds) void k_rank_topk(const RefRec *ref, uint3
   const uint32_t n = min(n_ref, ref_cap);
   const uint32_t f = counters[CNT_FEAS], call = counters[CNT_OWNER];  // valid stored records (requested with the count)
   const bool overflow = n_ref > ref_cap;  // uniform: the list is incomplete, nothing is ranked
-  if (blockIdx.x == 0 && threadIdx.x < CNT_COUNT)
-    next_counters[threadIdx.x] = counter_reset_value(threadIdx.x, call + 1);  // for the next call
+  if (blockIdx.x == 0)
+    for (uint32_t c = threadIdx.x; c < kSetWords; c += blockDim.x)
+      next_counters[c] = counter_reset_value((int)c, call + 1);  // for the next call
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     hdr->n_found = overflow ? 0u : (f < k ? f : k);
     hdr->surv_count = counters[CNT_SURV];

@@ -963,3 +963,44 @@ def test_threshold_among_more_units_than_a_workgroup_keeps(torch_cuda, form):
         assert plan.last_scan()[1] > (8192 if form == "scarce" else 16384)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("mixed, zones", [(False, 1), (False, 2), (True, 1), (True, 2)])
+def test_scan_guided_by_a_running_limit(torch_cuda, mixed, zones):
+    # More units than fit on the chip at once: the first of their order are shared by workgroups, the others
+    # wait for them and take several units each.  The order is that of the availability at creation, so it is
+    # set to one that rules the best units out (and nothing, and everything); one zone, where neighbouring
+    # segments cannot share a type; degrees that pairs of types cannot halve (1, 3); k on both sides of
+    # what the running k-th key is kept for (128), and of the plans there are.  Against the oracle, whole numbers
+    # and indices the same.
+    from dataclasses import replace
+    from paper_2504_17096_amd.binding import set_scan_unit_parts
+    stream = torch_cuda.cuda.current_stream().cuda_stream
+    prob = replace(W.tiny_problem(73, n_layers=8, n_zones=zones, seg3_max_pp=8), global_batch=768,
+                   dp_values=np.array([1, 2, 3, 4, 8], np.int32)).with_per_segment_tp(True).with_mixed_types(mixed)
+    set_scan_unit_parts(40)
+    try:
+        plan = _plan(prob.with_avail(np.minimum(prob.avail, 2)))
+    finally:
+        set_scan_unit_parts(0)
+    try:
+        for avail in (np.minimum(prob.avail, 2), prob.avail * 4, np.zeros_like(prob.avail), prob.avail):
+            plan.set_avail(avail)
+            orc = Oracle(prob.with_avail(avail))
+            t, c, _, mask = orc.eval_batch(n_threads=THREADS)
+            ok = mask == 0
+            for objective in (MAX_THROUGHPUT, MIN_COST):
+                val = (c if objective == MAX_THROUGHPUT else 1.0 / t)[ok]
+                for bound in (None, off_data(float(np.median(val))) if ok.any() else 1.0):
+                    best = plan.best_plan(objective=objective, bound=bound, stream=stream)
+                    want = orc.best(objective=objective, bound=bound, n_threads=THREADS)
+                    assert (best is None) == (want is None)
+                    if want is not None:
+                        check_result(best, want, orc)
+                    for k in (1, 128, 129):
+                        check_topk(plan.topk(k, objective=objective, bound=bound, stream=stream),
+                                   orc.topk(k, objective=objective, bound=bound, n_threads=THREADS),
+                                   objective, orc, bound)
+        assert plan.last_scan()[1] > 4096  # of two or more waves each: more than the chip's 8 192
+    finally:
+        plan.destroy()
