@@ -226,6 +226,8 @@ struct sailor_plan {
   // search over per-stage placements: tables and scratch, created by the first call
   std::vector<SearchPP> search_pps;
   const SearchPP *d_search_pps = nullptr;
+  std::vector<int32_t> row_layers;    // layers per stage of every layer split
+  const uint32_t *search_alike = nullptr;
   uint32_t n_sub = 0, n_sub_t = 0;  // sub-problems with TP in them / with a TP degree per stage
   double *search_states = nullptr;    // frontiers and histories that do not fit LDS (wide beams), and
   uint32_t *search_history = nullptr; // how many words of them there are
@@ -990,6 +992,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     delete pl;
     return rc != SAILOR_OK ? rc : SAILOR_EINVAL;
   }
+  pl->row_layers = st_n;
   DevPlan &d = pl->dev;
   d.G = p->n_types; d.Z = p->n_zones;
   d.mixed = p->mixed_types ? 1 : 0;
@@ -1467,6 +1470,7 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
   if (!pl->d_search_pps) {
     pl->search_pps.clear();
     uint32_t sub = 0, sub_t = 0;
+    std::vector<uint32_t> alike;  // SearchArgs::alike
     for (size_t ip = 0; ip < pl->ppv.size(); ++ip) {
       SearchPP e{};
       e.P = pl->ppv[ip];
@@ -1484,10 +1488,26 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
       e.sub_off_t = sub_t;
       sub += (uint32_t)e.n_part * (uint32_t)(pl->dev.TP * pl->dev.DP * pl->dev.MB);
       sub_t += (uint32_t)e.n_part * (uint32_t)(pl->dev.DP * pl->dev.MB);
+      e.part0 = (uint32_t)alike.size();
+      // equal splits side by side, the first of them in front
+      const int32_t *const rows = &pl->row_layers[e.rs0];
+      const size_t P = (size_t)e.P;
+      std::vector<uint32_t> order((size_t)e.n_part);
+      for (uint32_t q = 0; q < order.size(); ++q) order[q] = q;
+      auto row = [&](uint32_t q) { return rows + q * P; };
+      std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) {
+        return std::lexicographical_compare(row(x), row(x) + P, row(y), row(y) + P);
+      });
+      alike.resize(alike.size() + order.size(), 0);
+      for (size_t i = 0, first = 0; i < order.size(); ++i) {
+        if (!std::equal(row(order[i]), row(order[i]) + P, row(order[first]))) first = i;
+        ++alike[e.part0 + order[first]];
+      }
       pl->search_pps.push_back(e);
     }
     pl->n_sub = sub;
     pl->n_sub_t = sub_t;
+    if (pl->arena.upload(&pl->search_alike, alike.data(), alike.size()) != hipSuccess) return SAILOR_ENOMEM;
     if (pl->arena.upload(&pl->d_search_pps, pl->search_pps.data(), pl->search_pps.size()) != hipSuccess)
       return SAILOR_ENOMEM;
   }
@@ -1638,6 +1658,7 @@ sailor_status sailor_search(sailor_plan *pl, sailor_objective objective,
   const bool split = opt->allow_split != 0, stp = opt->stage_tp != 0;
   const size_t W = (size_t)a.W, ZG = (size_t)pl->dev.ZGr, TPn = stp ? (size_t)pl->dev.TP : 1;
   a.pps = pl->d_search_pps;
+  a.alike = pl->search_alike;
   a.n_pp = (int)pl->search_pps.size();
   a.n_sub = stp ? pl->n_sub_t : pl->n_sub;
   a.list = pl->search_list;

@@ -31,9 +31,11 @@
 // inputs are requested a level ahead, appending candidates takes no barrier, the W smallest come
 // from a histogram and (up to 512 of them) a count of predecessors instead of a sort of everything, and a wide choice
 // (second pool, TP degree) is first reduced to the best of each (state, pool).  On the 48-layer,
-// 20-pool problem a search with beam 64 takes 0.63 ms where states in device memory, paths copied
+// 20-pool problem a search with beam 64 takes 0.51 ms where states in device memory, paths copied
 // level by level and a bitonic sort of every level took 2.9 ms; with two pools and a TP degree per
-// stage (1 600 choices, beam 8) 1.06 ms against 9.3 ms.
+// stage (1 600 choices, beam 8) 0.84 ms against 9.3 ms.  (0.60 and 1.05 ms with equal layer splits gone
+// through one by one: a depth of as many stages as layers has one split, however often it is listed,
+// and its sub-problems, 576 of 1 078, shared the compute units with the 8 that take longest.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -59,7 +61,8 @@ struct SearchPP {      // one pipeline depth
   uint32_t sub_off;    // first sub-problem of this depth
   int32_t n_part;
   uint32_t sub_off_t;  // the same when TP is not part of the sub-problem
-  uint32_t pad[3];
+  uint32_t part0;      // its first entry of SearchArgs::alike
+  uint32_t pad[2];
 };
 
 enum : int { SEARCH_PLAIN = 0, SEARCH_SPLIT = 1, SEARCH_STAGE_TP = 2, SEARCH_SPLIT_TP = 3 };
@@ -106,6 +109,9 @@ struct SearchArgs {
   int objective, has_bound, has_inc, W, max_runs;
   double bound, inc;
   const SearchPP *pps;
+  const uint32_t *alike;  // per layer split: how many splits of its depth are the same, 0 if an earlier one is.
+                          // The sub-problems of equal splits take the same course: the first is gone through
+                          // and counted for all of them, and on ties it is the one that wins
   int n_pp;
   uint32_t n_sub;
   uint32_t *list;         // [n_sub] surviving sub-problems, those of a depth together
@@ -228,7 +234,7 @@ __device__ __forceinline__ uint32_t search_magic(int d) {
 struct SearchSub {     // a sub-problem
   int ip, q, it, id, im, P, nb;
   int64_t D;
-  uint32_t rs;
+  uint32_t rs, alike;
   double nbm1, ringf;  // N_b - 1; 2 (D - 1) / D
 };
 
@@ -246,6 +252,7 @@ __device__ __forceinline__ SearchSub search_sub(const DevPlan &pl, const SearchA
   s.q = STP ? (int)rem : (int)(rem / (uint32_t)pl.TP);
   s.P = pp.P;
   s.rs = pp.rs0 + (uint32_t)s.q * (uint32_t)pp.P;
+  s.alike = a.alike[pp.part0 + (uint32_t)s.q];
   s.nb = pl.nb[s.im * pl.DP + s.id];
   s.D = pl.vals[s.id];
   s.nbm1 = (double)(s.nb - 1);
@@ -517,7 +524,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
   unsigned long long expanded = 0;
   for (uint32_t sid = blockIdx.x * n_waves + wv; sid < a.n_sub; sid += gridDim.x * n_waves) {
     const SearchSub s = search_sub<STP>(pl, a, sid);
-    if (s.nb == 0) continue;  // (uniform over the wave, like what follows)
+    if (s.nb == 0 || s.alike == 0) continue;  // (uniform over the wave, like what follows)
     wave_lds_fence();         // the tables are reused
     for (int i = lane; i < TPn * (int)pl.row_w; i += 64) L.raw[i] = search_row<STP>(pl, s, 0)[i];
     const bool fine = search_tables<MODE, true>(pl, s, L, lane, 64);
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
     } else {
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
-      expanded += mine;
+      expanded += (unsigned long long)mine * s.alike;
     }
   }
   if (lane == 0) s_exp[wv] = expanded;
@@ -761,7 +768,8 @@ __device__ __forceinline__ int search_select(const SearchLds &L, SelectShared &s
 // smallest choices lie in the W items with the smallest bests.
 // (Two waves per SIMD for split stages, four else.  At four, the code for split stages spills so much
 // that it takes 1.19 ms against 1.05; the other forms spill too -- 54 registers with a pool per stage,
-// 121 with a degree per stage -- but at two they lose a workgroup per compute unit, 0.72 ms against 0.62.)
+// 121 with a degree per stage -- but at two they lose a workgroup per compute unit, 0.72 ms against 0.62
+// where 1 078 sub-problems survive their first level; 0.39 against 0.40 where 574 do.)
 // FORM: where the frontiers are, and how all-reduce seconds are kept.
 template <int MODE, int FORM>
 __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_beam(DevPlan pl, SearchArgs a) {
@@ -1087,7 +1095,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
           __syncthreads();
         }
       }
-      my_total += expanded;
+      my_total += (unsigned long long)expanded * s.alike;
       if (last) {
         // the smallest (key, id) of the workgroup
 #pragma unroll
@@ -1171,7 +1179,8 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
               (unsigned long long)(runs & 255) << 16 | (unsigned long long)pk << 24 | z << 32 | zb << 40;
         }
       }
-      search_level<MODE, false, ZONES>(pl, s, L, j + 1, layers, tp1, tb ^ 1, t, kSearchThreads);
+      // (from the last wave on: the first ones write the frontier)
+      search_level<MODE, false, ZONES>(pl, s, L, j + 1, layers, tp1, tb ^ 1, kSearchThreads - 1 - t, kSearchThreads);
       n_cur = n;
     }
     if (truncated) wg_trunc = 1;

@@ -1186,3 +1186,38 @@ def test_lists_of_placements_of_every_length_match_the_oracle(torch_cuda, count,
             np.testing.assert_allclose(c, np.array([e.cost for e in want])[at], rtol=1e-12)
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("objective", OBJECTIVES)
+def test_equal_layer_splits_are_searched_once_and_counted_as_often(torch_cuda, objective):
+    # rows that repeat side by side, apart, and all of them; others that differ in the last stage only: the
+    # winner is the first of its kind and the placements of every row are counted, as the oracle, which
+    # goes through them all, does.  A bound first levels fail at (they are counted elsewhere).
+    from dataclasses import replace
+    prob = _tiny(74, n_layers=6, n_zones=2)
+    rows = {1: [[6], [6], [6]], 2: [[4, 2], [2, 4], [4, 2], [4, 2]],
+            3: [[2, 2, 2], [2, 3, 1], [2, 2, 2], [2, 3, 1]], 6: [[1] * 6, [1] * 6]}
+    prob = replace(prob, pp_values=np.array(sorted(rows), np.int32),
+                   n_partitions=np.array([len(rows[p]) for p in sorted(rows)], np.int32),
+                   partition_layers=np.array([n for p in sorted(rows) for r in rows[p] for n in r], np.int32))
+    plan, orc = _plan(prob), Oracle(prob)
+    stream = torch_cuda.cuda.current_stream().cuda_stream
+    try:
+        for kw in (dict(), dict(allow_split=True), dict(stage_tp=True), dict(allow_split=True, stage_tp=True)):
+            for width in (1, 16):
+                want = orc.search_beam(width, objective, **kw)
+                assert want is not None
+                inc = 1.5 * want.key
+                for extra in (dict(), dict(incumbent=inc), dict(incumbent=0.999 * want.key)):
+                    want = orc.search_beam(width, objective, **extra, **kw)
+                    truncated, expanded = orc.last_search
+                    got = plan.search(width, objective, stream=stream, **extra, **kw)
+                    assert got.found == (want is not None)
+                    assert (got.expanded, got.exact) == (expanded, not truncated)
+                    if want is not None:
+                        assert (got.pp_index, got.partition, got.dp_index, got.mb_index) == \
+                               (want.pp_idx, want.partition, want.dp_idx, want.mb_idx)
+                        assert got.pools == want.pools
+                        assert (got.iter_time_s, got.cost_per_iter) == (want.iter_time, want.cost)
+    finally:
+        plan.destroy()
