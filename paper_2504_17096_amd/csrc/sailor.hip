@@ -612,17 +612,17 @@ void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEven
   else kernel<<<grid, block, lds, st>>>(args...);
 }
 
-template <int MODE, bool MIXED>
+template <int MODE, bool MIXED, bool GUIDED>
 void launch_units_m(sailor_plan *pl, sailor_objective obj, int has_bound, const ScanArgs &a,
                     dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   AvailArg<MODE, MIXED> avail{};
   if constexpr (kAvailRides<MODE, MIXED>) avail = avail_table(pl);
   if (obj == SAILOR_MAX_THROUGHPUT) {
-    if (has_bound) launch(k_units<MODE, 0, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
-    else launch(k_units<MODE, 0, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
+    if (has_bound) launch(k_units<MODE, 0, true, MIXED, GUIDED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
+    else launch(k_units<MODE, 0, false, MIXED, GUIDED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
   } else {
-    if (has_bound) launch(k_units<MODE, 1, true, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
-    else launch(k_units<MODE, 1, false, MIXED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
+    if (has_bound) launch(k_units<MODE, 1, true, MIXED, GUIDED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
+    else launch(k_units<MODE, 1, false, MIXED, GUIDED>, grid, block, lds, st, e0, e1, pl->dev, a, avail);
   }
 }
 
@@ -635,8 +635,14 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
                                           : std::min(n_units, kCollectUnits) * a.n_sub) + a.fresh),
       block(pl->unit_threads);
   const size_t lds = pl->lds_bytes;
-  if (pl->dev.mixed) launch_units_m<MODE, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
-  else launch_units_m<MODE, false>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
+  if constexpr (MODE != MODE_COLLECT)
+    if (a.n_seeds) {
+      if (pl->dev.mixed) launch_units_m<MODE, true, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
+      else launch_units_m<MODE, false, true>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
+      return;
+    }
+  if (pl->dev.mixed) launch_units_m<MODE, true, false>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
+  else launch_units_m<MODE, false, false>(pl, obj, has_bound, a, grid, block, lds, st, e0, e1);
 }
 
 struct SearchLaunch {
@@ -732,6 +738,10 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
 
   // collect -> [k-th smallest survivor key] -> fp64 refine -> final selection -> sync
   // kept: the best plan's scan has kept its candidates already
+  // tail_by_slots: a bound from 256 slots takes the place of a kernel that selects the k-th smallest key.  It
+  // lies 74 keys up for k = 64 and 178 for k = 128, so a few more candidates are re-evaluated; where they do
+  // not fit, the call starts over without it.
+  bool tail_by_slots = false;
   auto run_tail = [&](ResultHeader *hdr, bool kept) -> sailor_status {
     // (a direct pass is the call's pass over the space: the scan's timing events ride on it)
     if (!kept)
@@ -752,11 +762,15 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
       ra.band = (float)(1.0 + kTieTol) + 3.0f * kEvalEps;
       k_refine_best<<<kBestWorkgroups, kBestWaves * 64, 0, st>>>(pl->dev, ra, cnt_next, pl->d_hdr, pl->d_out, ++pl->seq, call);
     } else {
-      // the exact k-th smallest fp32 key among the survivors, then only its neighbourhood
-      k_select_kth<256><<<1, 256, 0, st>>>(&pl->surv[0].key, (int)(sizeof(SurvRec) / 4),
-                                       cnt + CNT_SURV, pl->surv_cap, k, cnt + CNT_TAU1,
-                                       nullptr, 0u, 0.f, nullptr, nullptr);
-      ra.tau_src = cnt + CNT_TAU1;
+      // a bound of the k-th smallest fp32 key among the survivors, or the key itself, then only what lies up to it
+      if (tail_by_slots) {
+        ra.kth = k;
+      } else {
+        k_select_kth<256><<<1, 256, 0, st>>>(reinterpret_cast<const float *>(&pl->surv[0].key), (int)(sizeof(SurvRec) / 4),
+                                         cnt + CNT_SURV, pl->surv_cap, k, cnt + CNT_TAU1,
+                                         nullptr, 0u, 0.f, nullptr, nullptr);
+        ra.tau_src = cnt + CNT_TAU1;
+      }
       k_refine<<<256, kRefineWaves * 64, 0, st>>>(pl->dev, ra);
       // few records expected (about k, plus ties): one workgroup ranks them from LDS
       const bool one = k <= kRankOneWorkgroup;
@@ -824,6 +838,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   if (sa.direct && !(pl->direct_declined && pl->declined_obj == (int)obj && pl->declined_lim == sa.lim_l)) {
     sa.use_tau_host = 1;
     sa.tau_host = kPosInf;
+    tail_by_slots = k <= kKthLive;
     rc = run_tail(hdr_out, false);
     if (rc != SAILOR_OK) return rc;
     pl->total_timed = t_all;
@@ -864,6 +879,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   sa.tau_src = cnt + CNT_TAU0;  // (not by_slots)
   sa.n_sub = kCollectSub;
   if (by_slots) {
+    tail_by_slots = true;
     rc = run_tail(hdr_out, false);
     if (rc != SAILOR_OK) return rc;
     pl->total_timed = t_all;
@@ -1107,7 +1123,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   // derived tables, filled by the set-up kernels
   d.n_bw_coef = p->n_bw_coef;
   if (p->n_bw_coef > 0) slab.input(&d.bw_poly, p->bw_poly, (size_t)Z * Z * p->n_bw_coef);
-  slab.table(&d.bwp, (size_t)MB * Z * Z);
   slab.table(&d.xsec, (size_t)MB * Z * Z);
   if (!d.mixed) slab.table(&d.list_tables, list_copy_words(d));  // (not for problems with pairs of types)
   slab.table(&d.direct_tables, direct_copy_words(d));
@@ -1470,7 +1485,7 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
   if (!pl->d_search_pps) {
     pl->search_pps.clear();
     uint32_t sub = 0, sub_t = 0;
-    std::vector<uint32_t> alike;  // SearchArgs::alike
+    uint32_t parts = 0;
     for (size_t ip = 0; ip < pl->ppv.size(); ++ip) {
       SearchPP e{};
       e.P = pl->ppv[ip];
@@ -1488,7 +1503,18 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
       e.sub_off_t = sub_t;
       sub += (uint32_t)e.n_part * (uint32_t)(pl->dev.TP * pl->dev.DP * pl->dev.MB);
       sub_t += (uint32_t)e.n_part * (uint32_t)(pl->dev.DP * pl->dev.MB);
-      e.part0 = (uint32_t)alike.size();
+      e.part0 = parts;
+      parts += (uint32_t)e.n_part;
+      pl->search_pps.push_back(e);
+    }
+    pl->n_sub = sub;
+    pl->n_sub_t = sub_t;
+    if (pl->arena.upload(&pl->d_search_pps, pl->search_pps.data(), pl->search_pps.size()) != hipSuccess)
+      return SAILOR_ENOMEM;
+  }
+  if (search && !pl->search_alike) {
+    std::vector<uint32_t> alike;
+    for (const SearchPP &e : pl->search_pps) {
       // equal splits side by side, the first of them in front
       const int32_t *const rows = &pl->row_layers[e.rs0];
       const size_t P = (size_t)e.P;
@@ -1503,13 +1529,8 @@ static sailor_status search_setup(sailor_plan *pl, bool search) {
         if (!std::equal(row(order[i]), row(order[i]) + P, row(order[first]))) first = i;
         ++alike[e.part0 + order[first]];
       }
-      pl->search_pps.push_back(e);
     }
-    pl->n_sub = sub;
-    pl->n_sub_t = sub_t;
     if (pl->arena.upload(&pl->search_alike, alike.data(), alike.size()) != hipSuccess) return SAILOR_ENOMEM;
-    if (pl->arena.upload(&pl->d_search_pps, pl->search_pps.data(), pl->search_pps.size()) != hipSuccess)
-      return SAILOR_ENOMEM;
   }
   if (search && !pl->search_results) {
     DeviceArena &ar = pl->arena;

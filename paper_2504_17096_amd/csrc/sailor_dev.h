@@ -74,13 +74,16 @@ struct GroupSum {       // what k_group_bounds tells the host of a group of unit
 };
 static_assert(kMaxPools <= 128, "a bit per type");
 
-struct SurvRec {        // candidate kept for the fp64 re-evaluation
+// Candidate kept for the fp64 re-evaluation.  Its digits, which the pass that kept it knows, and its
+// unit's segments come with it: from its index they took two 64-bit divisions and a trip to the shape's record.
+struct SurvRec {
   uint64_t idx;
-  float key;            // fp32 key; +inf when only loosely inside the constraint
-  float key_loose;      // fp32 key
-  uint32_t shape;       // the candidate's shape, known to the pass that kept it
-  uint32_t pad;
+  uint32_t key;        // bits of the fp32 key; sign set: only loosely inside the constraint
+  uint32_t row_stage;  // of its shape
+  uint32_t where;      // pools of the segments, mb, dp and segment 1's tp: 7, 7, 7, 3, 5, 3 bits
+  uint32_t segs;       // stages per segment, less one (8 bits each), segments, tp of segments 2, 3: 2, 3, 3 bits
 };
+static_assert(kMaxPools <= 128 && kMaxMB <= 8 && kMaxDP <= 32 && kMaxTP <= 8 && kMaxStages <= 256, "the fields' bits");
 
 struct RefRec {         // fp64 re-evaluation of one candidate
   uint64_t idx, mem;
@@ -133,7 +136,6 @@ struct DevPlan {
   uint64_t *isect;             // [ZG][2] bit q: pools p and q draw on a common real pool
   int n_bw_coef;               // 0: constant link bandwidth
   const double *bw_poly;       // [Z][Z][n_bw_coef] bandwidth over log2(message bytes)
-  double *bwp;                 // [MB][Z][Z] bandwidth seen by one activation transfer
   double *xsec;                // [MB][Z][Z] seconds of one activation transfer a -> b
   float *tsec_f;               // the same, rounded once
   float *egs_f;                // [Z][Z] egress both ways

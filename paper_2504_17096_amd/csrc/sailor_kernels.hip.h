@@ -84,6 +84,19 @@ __device__ __forceinline__ int at3(const T *v, int j) {
   return j == 0 ? (int)v[0] : (j == 1 ? (int)v[1] : (int)v[2]);
 }
 
+// Brings a kernel's arguments into the scalar cache at once.  They lie in device memory that no cache holds
+// when a kernel starts, and are read where they are used: every line of 64 bytes a trip of its own, one behind
+// the other (half a microsecond each, five of them in front of a re-evaluation's first stage).
+template <typename T>
+__device__ __forceinline__ void touch_arguments(const T &args) {
+  const uint32_t *const w = reinterpret_cast<const uint32_t *>(&args);
+  constexpr int kLines = (int)(sizeof(T) / 64);
+  static_assert(kLines <= 16, "");
+  auto line = [&](int i) { return w[16 * (i < kLines ? i : kLines) < (int)(sizeof(T) / 4) ? 16 * (i < kLines ? i : kLines) : 0]; };
+  asm volatile("" ::"s"(line(0)), "s"(line(1)), "s"(line(2)), "s"(line(3)), "s"(line(4)), "s"(line(5)), "s"(line(6)), "s"(line(7)),
+               "s"(line(8)), "s"(line(9)), "s"(line(10)), "s"(line(11)), "s"(line(12)), "s"(line(13)), "s"(line(14)), "s"(line(15)));
+}
+
 // 24-bit multiply (full rate, unlike the 32-bit one), for table offsets
 __device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return __umul24(a, b); }
 
@@ -127,7 +140,6 @@ __global__ void k_small_tables(DevPlan pl, float *link_min) {
     int a = i / Z, b = i % Z;
     for (int m = 0; m < pl.MB; ++m) {
       const double bytes = (double)pl.p2p[m], bwv = link_bw(pl, a, b, bytes);
-      pl.bwp[m * Z * Z + i] = bwv;
       pl.xsec[m * Z * Z + i] = bytes / bwv;
       pl.tsec_f[m * Z * Z + i] = (float)(bytes / bwv);
       atomicMin(reinterpret_cast<uint32_t *>(&link_min[2 * m + (a != b)]), __float_as_uint((float)(bytes / bwv)));
@@ -236,15 +248,6 @@ __global__ void k_stage_tables(DevPlan pl, StageArgs a) {
     r[G] = __longlong_as_double((long long)(shard * (uint64_t)pl.bpp));
     r[G + 1] = (double)shard * (double)pl.gb;
   }
-}
-
-// model + activation bytes of a worker of stage i of P (Sec. 4.3) from the stage's parameter
-// and layer counts; reserved bytes are added where the GPU type is known
-__device__ __forceinline__ uint64_t stage_bytes_of(uint64_t params, int32_t layers, uint32_t bpp,
-                                                   int i, int P, int tp, int64_t nb, uint64_t act) {
-  const uint64_t shard = (params + (uint64_t)tp - 1) / (uint64_t)tp;
-  const int64_t inflight = (int64_t)(P - i) < nb ? (int64_t)(P - i) : nb;
-  return shard * (uint64_t)bpp + (uint64_t)inflight * (uint64_t)layers * act;
 }
 
 // activation bytes of a worker: microbatches in flight x layers x bytes of one (validated < 2^62)
@@ -672,10 +675,11 @@ enum Counter { CNT_SURV = 0, CNT_OWNER = 1,      // number of the call the set b
                CNT_DONE = 10,                    // workgroups of the final kernel that have finished
                CNT_COUNT = 16 };
 // Behind a set's counters: the smallest keys that SCAN has come across, a word for the waves that share it;
-// and copies of the running limit, a cache line each, of which a workgroup reads one (thousands of workgroups
+// the same of the candidates that COLLECT keeps, a word for those whose index leads to it; and copies of the running limit, a cache line each, of which a workgroup reads one (thousands of workgroups
 // that ask for one word, and the atomics that lower it, wait for one another: 8 us of a scan of 15).
 constexpr uint32_t kKeySlots = 256, kLimitCopies = 16, kLimitStride = 32,
-                   kSetWords = CNT_COUNT + kKeySlots + kLimitCopies * kLimitStride;
+                   kKeptSlots = CNT_COUNT + kKeySlots, kCopies = kKeptSlots + kKeySlots,
+                   kSetWords = kCopies + kLimitCopies * kLimitStride;
 static_assert(CNT_SURV % 2 == 0 && CNT_OWNER == CNT_SURV + 1 && CNT_COUNT % 2 == 0, "one 8-byte word");
 
 // c: a counter of the set that belongs to `call`
@@ -695,14 +699,54 @@ __global__ void k_init_counters(uint32_t *c, uint32_t call) {
     c[i] = counter_reset_value((int)(i % kSetWords), call + ((i / kSetWords ^ call) & 1u));
 }
 
-// One candidate of the scan: update the running minima, or append it to the survivors.
 struct NoAvail {};
 template <int MODE, bool MIXED> constexpr bool kAvailRides = MODE == MODE_BEST && !MIXED;
 template <int MODE, bool MIXED> using AvailArg = std::conditional_t<kAvailRides<MODE, MIXED>, AvailTable, NoAvail>;
 
+// The candidates a workgroup keeps of a unit, gathered in LDS and appended to the survivors when the unit has
+// been walked: one trip to the counter, where every wave made one for every chunk and pool at
+// which it kept something, and waited for it.
+constexpr uint32_t kKeptHere = 256;
+struct Kept {
+  unsigned long long idx[kKeptHere];
+  uint32_t key[kKeptHere], where[kKeptHere];  // as in SurvRec (where: without the tp)
+  uint32_t n, full, base;
+};
+
+__device__ __forceinline__ void survivor(const DevPlan &pl, const ScanArgs &a, const UnitRec &u, uint32_t slot,
+                                         unsigned long long idx, uint32_t key, uint32_t where) {
+  if (slot >= a.surv_cap) return;
+  SurvRec sv;
+  sv.idx = idx;
+  sv.key = key;
+  sv.row_stage = pl.shapes[u.shape].row_stage;
+  sv.where = where | (uint32_t)u.tp[0] << 29;
+  sv.segs = ((uint32_t)(u.n[0] - 1) & 255u) | ((uint32_t)(u.n[1] - 1) & 255u) << 8 | ((uint32_t)(u.n[2] - 1) & 255u) << 16 |
+            (uint32_t)u.s << 24 | (uint32_t)u.tp[1] << 26 | (uint32_t)u.tp[2] << 29;
+  a.surv[slot] = sv;
+}
+
+// (the workgroup, behind its walk of the unit)  A wave that found the list full has left its place empty
+// there: the list ends before it.
+__device__ __forceinline__ void keep_flush(const DevPlan &pl, const ScanArgs &a, const UnitRec &u, Kept &kept) {
+  __syncthreads();
+  uint32_t n = kept.n;
+  if (n == 0) return;  // uniform
+  if (n > kKeptHere) n = kept.full;
+  if (threadIdx.x == 0) kept.base = atomicAdd(&a.counters[CNT_SURV], n);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+    const uint32_t key = kept.key[i], idx = (uint32_t)kept.idx[i];
+    if (!(key >> 31)) atomicMin(&a.counters[kKeptSlots + (idx * 0x9E3779B1u >> 24)], key);
+    survivor(pl, a, u, kept.base + i, kept.idx[i], key, kept.where[i]);
+  }
+}
+static_assert(kKeySlots == 256, "eight bits of a hash");
+
+// One candidate of the scan: update the running minima, or keep it.
 template <int MODE, int OBJ, bool HASB>
-__device__ __forceinline__ void visit(const ScanArgs &a, float T, float C, bool feas, float tau,
-                                      uint64_t idx, uint32_t shape, float &ms, float &ml) {
+__device__ __forceinline__ void visit(const DevPlan &pl, const ScanArgs &a, const UnitRec &u, float T, float C, bool feas,
+                                      float tau, uint64_t idx, uint32_t where, Kept &kept, float &ms, float &ml) {
   const float key = OBJ == 0 ? T : C;
   const float con = OBJ == 0 ? C : T;
   if (MODE != MODE_COLLECT) {
@@ -724,25 +768,32 @@ __device__ __forceinline__ void visit(const ScanArgs &a, float T, float C, bool 
         if (m_strict != 0) atomicAdd(&a.counters[CNT_NSTRICT], (uint32_t)__popcll(m_strict));
       }
     } else {
-      // one atomic per wave: the first lane that keeps its candidate reserves the slots of all
+      // the first lane that keeps its candidate reserves the places of all: in the workgroup's list, or, when
+      // that is full, among the survivors at once
       const bool take = loose && key <= tau;
       const uint64_t m_take = __builtin_amdgcn_ballot_w64(take);
       if (m_take == 0) return;
-      const int lane = (int)(threadIdx.x & 63u), leader = __builtin_ctzll(m_take);
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(&a.counters[CNT_SURV], (uint32_t)__popcll(m_take));
-      base = (uint32_t)__shfl((int)base, leader);
-      if (!take) return;
+      const uint32_t lane = threadIdx.x & 63u, n = (uint32_t)__popcll(m_take);
+      const int leader = __builtin_ctzll(m_take);
       const bool strict = !HASB || con <= a.lim_s;
+      uint32_t base = 0;
+      if ((int)lane == leader) base = atomicAdd(&kept.n, n);
+      base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
+      const bool here = base + n <= kKeptHere;  // uniform over the wave
+      if (!here) {
+        if ((int)lane == leader && base <= kKeptHere) kept.full = base;  // (the one that crosses the end)
+        if ((int)lane == leader) base = atomicAdd(&a.counters[CNT_SURV], n);
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
+      }
+      if (!take) return;
       const uint32_t slot = base + (uint32_t)__popcll(m_take & ((1ull << lane) - 1ull));
-      if (slot < a.surv_cap) {
-        SurvRec sv;
-        sv.idx = idx;
-        sv.key = strict ? key : kPosInf;
-        sv.key_loose = key;
-        sv.shape = shape;
-        sv.pad = 0;
-        a.surv[slot] = sv;
+      const uint32_t bits = __float_as_uint(key) | (strict ? 0u : 1u << 31);
+      if (here) {
+        kept.idx[slot] = idx;
+        kept.key[slot] = bits;
+        kept.where[slot] = where;
+      } else {
+        survivor(pl, a, u, slot, idx, bits, where);
       }
     }
   }
@@ -944,7 +995,7 @@ __device__ __forceinline__ uint32_t kth_of_slots(const uint32_t *slots, uint32_t
 // key that at least kth candidates do not exceed.  Keys go to slots, each candidate's to one, and as every
 // slot keeps its smallest, kth slots that hold a key up to some value are as many candidates up to it.
 __device__ __forceinline__ uint32_t *limit_copy(const ScanArgs &a, uint32_t i) {
-  return &a.counters[CNT_COUNT + kKeySlots + i % kLimitCopies * kLimitStride];
+  return &a.counters[kCopies + i % kLimitCopies * kLimitStride];
 }
 __device__ __forceinline__ uint32_t running_limit(const ScanArgs &a) {
   return __hip_atomic_load(limit_copy(a, blockIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1005,7 +1056,7 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
                                           const uint32_t *q13, const uint64_t *isect, int w0,
                                           int w1, int w2, float tau, const Walk &wk,
                                           const float *s_rows, bool live,
-                                          uint32_t *s_min, float &ms, float &ml) {
+                                          uint32_t *s_min, Kept &kept, float &ms, float &ml) {
   // the chunks of the lane space are dealt round-robin to the waves of the workgroups that share the unit
   const int ZG = pl.ZG, G = pl.GX, MB = pl.MB, DP = pl.DP, Z = pl.Z;
   const int lane = threadIdx.x & 63;
@@ -1059,10 +1110,11 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
       const Acc A0 = acc_begin(r0);
       // index of the candidate whose outer digits are all zero
       const uint64_t idx0 = ubase + (uint64_t)(it.mb + MB * (tp + pl.TP * (it.dp + DP * a1)));
+      const uint32_t where0 = (uint32_t)a1 | (uint32_t)it.mb << 21 | (uint32_t)it.dp << 24;
       if (S == 1) {
         float T, C;
         acc_finish(A0, it.lc, T, C);
-        visit<MODE, OBJ, HASB>(a, T, C, b0 != 0, tau, idx0, u.shape, ms, ml);
+        visit<MODE, OBJ, HASB>(pl, a, u, T, C, b0 != 0, tau, idx0, where0, kept, ms, ml);
         continue;
       }
       if (!alive(A0, it.lc, l0)) b0 = 0;
@@ -1082,8 +1134,8 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
           if (rel2 < 0) rel2 += ZG;
           float T, C;
           acc_finish(A1, it.lc, T, C);
-          visit<MODE, OBJ, HASB>(a, T, C, b1 != 0, tau,
-                                 idx0 + (uint64_t)pl.inner * (uint64_t)rel2, u.shape, ms, ml);
+          visit<MODE, OBJ, HASB>(pl, a, u, T, C, b1 != 0, tau,
+                                 idx0 + (uint64_t)pl.inner * (uint64_t)rel2, where0 | (uint32_t)a2 << 7, kept, ms, ml);
         }
         if (++g2 == G) { g2 = 0; ++z2; }
       }
@@ -1116,6 +1168,7 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
         if (rel2 < 0) rel2 += ZG;
         const uint64_t idx0 = ubase + (uint64_t)(it.mb + MB * (tp + pl.TP * (it.dp + DP * a1))) +
                               (uint64_t)pl.inner * (uint64_t)rel2;
+        const uint32_t where0 = (uint32_t)a1 | (uint32_t)a2 << 7 | (uint32_t)it.mb << 21 | (uint32_t)it.dp << 24;
         ask();
         int z3 = p_from / G, g3 = p_from % G;
         for (int a3 = p_from; a3 < p_to; ++a3) {
@@ -1136,8 +1189,8 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
               if (rel3 < 0) rel3 += ZG;
               float T, C;
               acc_finish(A2, it.lc, T, C);
-              visit<MODE, OBJ, HASB>(a, T, C, b2 != 0, tau,
-                                     idx0 + pl.stride3 * (uint64_t)rel3, u.shape, ms, ml);
+              visit<MODE, OBJ, HASB>(pl, a, u, T, C, b2 != 0, tau,
+                                     idx0 + pl.stride3 * (uint64_t)rel3, where0 | (uint32_t)a3 << 14, kept, ms, ml);
             }
           }
           if (++g3 == G) { g3 = 0; ++z3; }
@@ -1215,7 +1268,7 @@ __device__ __forceinline__ bool unit_test(const DevPlan &pl, const ScanArgs &a, 
 // its (mb, dp, pool 1) triple over the unit's outer pool digits.  Everything the staging
 // needs comes from the unit record and tables that do not depend on one another, so all of
 // its global loads are in flight together and one barrier ends it.
-template <int MODE, int OBJ, bool HASB, bool MIXED>
+template <int MODE, int OBJ, bool HASB, bool MIXED, bool GUIDED>
 __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, const AvailArg<MODE, MIXED> &avail,
                                           uint32_t uidx, int sub, uint32_t n_sub, float tau, uint4 *lds_raw) {
   const UnitRec u = pl.units[uidx];
@@ -1241,7 +1294,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     if (live) {
       if (threadIdx.x < 64) {
         uint32_t seen = running_limit(a);
-        if (n_sub == 1 && a.wait_ticks != 0 && !(__uint_as_float(seen) < kPosInf)) {
+        if (GUIDED && n_sub == 1 && a.wait_ticks != 0 && !(__uint_as_float(seen) < kPosInf)) {
           const unsigned long long until = wall_clock64() + a.wait_ticks;
           do {
             __builtin_amdgcn_s_sleep(12);
@@ -1302,7 +1355,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   __shared__ float red[2][kMaxUnitThreads / 64];
   __shared__ uint32_t s_any[kMaxUnitThreads / 64];  // per wave, bit j: a pool can host segment j
   __shared__ uint32_t s_min;  // the smallest key the workgroup has found so far (see unit_body)
+  __shared__ Kept kept;
   const int t = threadIdx.x;
+  if (MODE != MODE_SCAN && t == 0) kept.n = 0;
   if (MODE != MODE_COLLECT && t == 0) s_min = __float_as_uint(key_limit);
 
   // Re-planning after an availability change: the unit is staged as always, and if every
@@ -1384,11 +1439,12 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   float ms = kPosInf, ml = kPosInf;
   auto walk = [&](auto mode) {
     constexpr int M = decltype(mode)::value;
-    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, ms, ml);
-    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, ms, ml);
-    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, ms, ml);
+    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
+    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
+    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
   };
   walk(std::integral_constant<int, MODE>());
+  if (MODE == MODE_COLLECT && !a.count_only) keep_flush(pl, a, u, kept);
 
   if (MODE != MODE_COLLECT) {
     const bool folds = !(MODE == MODE_SCAN && live);  // (a scan for the kth smallest key has no use for the smallest one)
@@ -1413,7 +1469,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
       if (m < 0x7f800000u)
         atomicMin(&a.counters[CNT_COUNT + (blockIdx.x * (blockDim.x >> 6) + (uint32_t)t) % kKeySlots], m);
       // (by all workgroups this would cost more than it prunes: they would wait for one another)
-      if (a.n_seeds != 0 && blockIdx.x % 4u == 0u) {
+      if (GUIDED && blockIdx.x % 4u == 0u) {
         const uint32_t at = kth_of_slots(a.counters + CNT_COUNT, a.kth);
         if (at < running_limit(a)) lower_limit<MODE>(a, at);
       }
@@ -1425,7 +1481,10 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     // known nearly all of it falls to the bounds.
     __syncthreads();
     tau = __uint_as_float(s_min);
-    if (tau >= 0.0f) walk(std::integral_constant<int, MODE_COLLECT>());  // uniform
+    if (tau >= 0.0f) {  // uniform
+      walk(std::integral_constant<int, MODE_COLLECT>());
+      keep_flush(pl, a, u, kept);
+    }
   }
 }
 
@@ -1454,9 +1513,14 @@ __host__ __device__ inline uint32_t scan_workgroups(uint32_t n_units, uint32_t w
 // candidates.  Only the best plan's pass takes it along: 512 bytes of arguments and the registers of the
 // second source of quotas cost a top-64 query, in its scan and its collect pass, 2 to 3 of its 33 to 61 us.
 // (Not with pairs of types, whose joint quotas are looked up per plan.)
-template <int MODE, int OBJ, bool HASB, bool MIXED>
+//
+// GUIDED: see scan_workgroups.  (A kernel of its own: what a workgroup keeps over several units made it
+// spill 140 scalar registers instead of 20, 9.1 instead of 8 us for the 180 units of a small space.)
+template <int MODE, int OBJ, bool HASB, bool MIXED, bool GUIDED>
 __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs a, AvailArg<MODE, MIXED> avail) {
   extern __shared__ uint4 lds_raw[];
+  touch_arguments(pl);
+  touch_arguments(a);
   if constexpr (kAvailRides<MODE, MIXED>) {
     const uint32_t n_wgs = gridDim.x - a.fresh;
     if (blockIdx.x >= n_wgs) {
@@ -1466,8 +1530,11 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
       return;
     }
   }
-  if (MODE != MODE_COLLECT) {
-    const uint32_t n_shared = MODE == MODE_BEST && a.direct ? a.n_list_host : a.n_seeds;
+  if (MODE != MODE_COLLECT && !GUIDED) {
+    const uint32_t n_sub = MODE == MODE_BEST && a.direct ? a.n_sub : 1u, e = blockIdx.x / n_sub;
+    unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, MODE == MODE_BEST && a.direct ? a.ulist[e] : e, (int)(blockIdx.x % n_sub), n_sub, kPosInf, lds_raw);
+  } else if (MODE != MODE_COLLECT) {
+    const uint32_t n_shared = a.n_seeds;
     const bool shared = blockIdx.x < n_shared * a.n_sub;
     const uint32_t n_sub = shared ? a.n_sub : 1u, sub = shared ? blockIdx.x % n_sub : 0u;
     const uint32_t first = shared ? blockIdx.x / n_sub : blockIdx.x - n_shared * (a.n_sub - 1u);  // in the order
@@ -1475,7 +1542,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
     uint32_t hits = 1;
     for (bool more = !shared && first + step < n; hits != 0;) {  // uniform
       const uint32_t e = first + (uint32_t)__builtin_ctz(hits) * step;
-      unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist ? a.ulist[e] : e, (int)sub, n_sub, kPosInf, lds_raw);
+      unit_work<MODE, OBJ, HASB, MIXED, true>(pl, a, avail, a.ulist ? a.ulist[e] : e, (int)sub, n_sub, kPosInf, lds_raw);
       hits &= hits - 1;
       if (!more && hits == 0) break;
       __syncthreads();  // the staging area is reused
@@ -1507,7 +1574,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
       }
       for (; hits != 0; hits &= hits - 1) {  // uniform
         const uint32_t at = e + (uint32_t)__builtin_ctzll(hits) * per_round;
-        unit_work<MODE, OBJ, HASB, MIXED>(pl, a, avail, a.ulist ? a.ulist[at] : at, (int)(blockIdx.x % a.n_sub), a.n_sub, tau, lds_raw);
+        unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, a.ulist ? a.ulist[at] : at, (int)(blockIdx.x % a.n_sub), a.n_sub, tau, lds_raw);
         __syncthreads();  // the staging area is reused
       }
     }
@@ -1732,21 +1799,45 @@ __global__ __launch_bounds__(THREADS) void k_select_kth(const float *vals, int s
 // ------------------------------------------------------------------ fp64 re-evaluation
 
 struct Cand {
-  uint32_t shape;
+  uint32_t row_stage;
   int P, s, mb, dp;          // indices into the value lists
   int tp[3];                 // tp index of each segment
   int a[3];
-  int k1, k2;
+  int n[3], k1, k2;          // stages per segment, cut points (P when unused)
 };
+
+// Of a kept candidate.
+__device__ __forceinline__ Cand candidate(const SurvRec &sv) {
+  Cand c;
+  c.row_stage = sv.row_stage;
+  c.s = (int)((sv.segs >> 24) & 3u);
+  c.mb = (int)((sv.where >> 21) & 7u);
+  c.dp = (int)((sv.where >> 24) & 31u);
+  c.tp[0] = (int)(sv.where >> 29);
+  c.tp[1] = (int)((sv.segs >> 26) & 7u);
+  c.tp[2] = (int)(sv.segs >> 29);
+  c.P = 0;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    c.a[j] = j < c.s ? (int)((sv.where >> (7 * j)) & 127u) : -1;
+    c.n[j] = j < c.s ? (int)((sv.segs >> (8 * j)) & 255u) + 1 : 0;
+    c.P += c.n[j];
+  }
+  c.k1 = c.n[0];
+  c.k2 = c.n[0] + c.n[1];
+  return c;
+}
 
 // The digits of candidate idx, which lies in the given shape.
 __device__ __forceinline__ void decode_in_shape(const DevPlan &pl, uint32_t shape, uint64_t idx,
                                                 Cand &c) {
   const ShapeRec sh = pl.shapes[shape];
   const uint64_t rem = idx - sh.base;
-  c.shape = shape;
+  c.row_stage = sh.row_stage;
   c.P = sh.P;
   c.s = sh.s;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) c.n[j] = sh.n[j];
   c.k1 = sh.k1;
   c.k2 = sh.k2;
   uint32_t o = (uint32_t)(rem / pl.inner);
@@ -1810,63 +1901,46 @@ __device__ __forceinline__ void eval_exact_wave(const DevPlan &pl, const Cand &c
                                                 uint32_t &mask) {
   const int G = pl.G, GX = pl.GX, Z = pl.Z, MB = pl.MB, TP = pl.TP, DP = pl.DP, P = c.P;
   const int lane = threadIdx.x & 63;
-  const ShapeRec sh = pl.shapes[c.shape];
-  const uint32_t rs = sh.row_stage;
+  const uint32_t rs = c.row_stage;
   const int64_t D = pl.vals[c.dp];
-  int xs[3];  // real types of each segment's pool
-#pragma unroll
-  for (int j = 0; j < 3; ++j) xs[j] = j < c.s ? type_pair(c.a[j] % GX, G) : 0;
-  mask = 0;
-  peak = 0;
   const int64_t nb = pl.nb[c.mb * DP + c.dp];
   const double p2p = (double)pl.p2p[c.mb];
-  const double *bwp = pl.bwp + c.mb * Z * Z;  // bandwidth seen by a transfer of p2p bytes
-  // quota per pool (GPUs of one replica there, times D) and H1
-  // (counted in halves: a segment on a pair of types takes half of its replicas from each).
-  // Everything read from memory is requested first, for all three segments at once: the
-  // loads do not depend on one another, and a loop that fetched them as it went paid a trip
-  // to memory for each.
-  int zj[3], ga[3], gb[3];
-  int64_t tpj[3], wj[3], av_a[3], av_b[3], nd_a[3], nd_b[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const bool used = j < c.s;
-    ga[j] = xs[j] & 255;
-    gb[j] = xs[j] >> 8;
-    zj[j] = used ? c.a[j] / GX : 0;
-    tpj[j] = used ? (int64_t)pl.vals[pl.DP + c.tp[j]] : 0;
-    av_a[j] = used ? (int64_t)pl.avail[zj[j] * G + ga[j]] : 0;
-    av_b[j] = used ? (int64_t)pl.avail[zj[j] * G + gb[j]] : 0;
-    nd_a[j] = used ? (int64_t)pl.node[ga[j]] : 0;
-    nd_b[j] = used ? (int64_t)pl.node[gb[j]] : 0;
-  }
-  if (nb == 0) {  // uniform over the wave (tested only now: the loads above need not wait for it)
-    mask = 4u;    // batch not divisible
-    T = C = __builtin_huge_val();
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < 3; ++j) wj[j] = (int64_t)sh.n[j] * tpj[j];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    if (j >= c.s) continue;
-#pragma unroll
-    for (int slot = 0; slot < 2; ++slot) {
-      if (slot == 1 && ga[j] == gb[j]) continue;
-      const int g = slot == 0 ? ga[j] : gb[j];
-      int64_t halves = 0;
-#pragma unroll
-      for (int j2 = 0; j2 < 3; ++j2) {
-        if (j2 >= c.s || zj[j2] != zj[j]) continue;
-        if (ga[j2] == gb[j2]) halves += ga[j2] == g ? 2 * wj[j2] : 0;
-        else halves += (ga[j2] == g || gb[j2] == g) ? wj[j2] : 0;
-      }
-      if (halves * D > 2 * (slot == 0 ? av_a[j] : av_b[j])) mask |= 2u;
+  const double *xsec = pl.xsec + c.mb * Z * Z;  // seconds of a transfer of p2p bytes
+  // quota per pool (GPUs of one replica there, times D; counted in halves: a segment on a pair of types
+  // takes half of its replicas from each) and H1, a lane for every segment and real type of its pool.  (One
+  // behind the other this was a third of the kernel's instructions, which a kernel of one wave fetches
+  // as it goes.)
+  int xs[3], zj[3], tpj[3];  // real types of each segment's pool, its zone, tp
+  mask = 0;
+  peak = 0;
+  {
+    const int j = lane >= 6 ? 0 : lane >> 1, n_j = at3(c.n, j);
+    const bool used = lane < 6 && j < c.s;
+    const int a = used ? at3(c.a, j) : 0, z = (int)fast_div((uint32_t)a, pl.mg_g), x = type_pair(a - z * GX, G);
+    const int ga = x & 255, gb = x >> 8, g = (lane & 1) ? gb : ga;
+    const int tp = pl.vals[DP + at3(c.tp, j)];
+    const int64_t av = pl.avail[z * G + g], nd = pl.node[g];
+    const int w = used ? n_j * tp : 0;  // (a replica's GPUs there: at most 2^20, validated)
+    if (nb == 0) {  // uniform over the wave (tested only now: the loads above need not wait for it)
+      mask = 4u;    // batch not divisible
+      T = C = __builtin_huge_val();
+      return;
     }
-    if (ga[j] != gb[j] && D % 2 != 0) mask |= 2u;  // D replicas cannot be halved
-    if (tpj[j] > nd_a[j] || tpj[j] > nd_b[j]) mask |= 8u;
+    int64_t halves = 0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      xs[q] = __builtin_amdgcn_readlane(x, 2 * q);
+      zj[q] = __builtin_amdgcn_readlane(z, 2 * q);
+      tpj[q] = __builtin_amdgcn_readlane(tp, 2 * q);
+      const int wq = __builtin_amdgcn_readlane(w, 2 * q), qa = xs[q] & 255, qb = xs[q] >> 8;  // (0 for a segment that is not there)
+      if (zj[q] == z) halves += (qa == g ? wq : 0) + (qb == g ? wq : 0);
+    }
+    const bool counts = used && ((lane & 1) == 0 || ga != gb);
+    if (wave_any(counts && (halves * D > 2 * av || (ga != gb && D % 2 != 0)))) mask |= 2u;  // (D replicas halved)
+    if (wave_any(counts && tp > nd)) mask |= 8u;
   }
   double max_t = 0.0, t_sync = 0.0, t_upd = 0.0;
+  const double ring = 2.0 * (double)(D - 1) / (double)D;
   uint32_t oom = 0;
   for (int i = lane; i < P; i += 64) {
     const int seg = i < c.k1 ? 0 : (i < c.k2 ? 1 : 2);
@@ -1877,38 +1951,32 @@ __device__ __forceinline__ void eval_exact_wave(const DevPlan &pl, const Cand &c
     const int sn = (i + 1) < c.k1 ? 0 : ((i + 1) < c.k2 ? 1 : 2);
     const int sp = (i - 1) < c.k1 ? 0 : ((i - 1) < c.k2 ? 1 : 2);
     const int zn = i < P - 1 ? at3(zj, sn) : z, zp = i > 0 ? at3(zj, sp) : z;
-    // everything the stage reads from memory, requested together
-    const size_t si = (size_t)rs + i;
-    const uint64_t params = pl.st_params[si];
-    const int32_t layers = pl.st_n[si];
+    // everything the stage reads from memory, requested together.  Its record (st_row) holds what follows
+    // from the layer split: with the shard sizes, transfers and gradient buffers divided out anew this was
+    // 2 500 instructions of one wave, most of what a re-evaluation takes
+    const double *const row = pl.st_row + ((size_t)(rs + (uint32_t)i) * (uint32_t)(MB * TP) + (uint32_t)(c.mb * TP + k)) * pl.row_w;
+    const int32_t layers = pl.st_n[rs + (uint32_t)i];
     const uint64_t act = pl.act[c.mb * TP + k];
     const uint64_t res1 = pl.res[g], res2 = pl.res[g2], cap1 = pl.cap[g], cap2 = pl.cap[g2];
-    const double c1 = pl.st_c[((si * G + g) * MB + c.mb) * TP + k];
-    const double c2 = pl.st_c[((si * G + g2) * MB + c.mb) * TP + k];
-    const double u1 = pl.st_u[(si * G + g) * TP + k], u2 = pl.st_u[(si * G + g2) * TP + k];
+    const double c1 = row[g], c2 = row[g2], u1 = row[G + g], u2 = row[G + g2], shard = row[2 * G], grads = row[2 * G + 1];
     const double price1 = pl.price[g], price2 = pl.price[g2];
-    const double bw_n = bwp[z * Z + zn], bw_p = bwp[z * Z + zp];
+    const double x_n = xsec[z * Z + zn], x_p = xsec[z * Z + zp];
     const double eg = pl.egress ? pl.egress[z * Z + zn] + pl.egress[zn * Z + z] : 0.0;
-    const uint64_t bytes_i = stage_bytes_of(params, layers, pl.bpp, i, P, (int)tp, nb, act);
+    const uint64_t bytes_i = (uint64_t)__double_as_longlong(shard) + act_bytes((int)((int64_t)(P - i) < nb ? (int64_t)(P - i) : nb), layers, act);
     const uint64_t m = bytes_i + res1, m2 = bytes_i + res2;  // both replica types
     if (m > cap1 || m2 > cap2) oom = 1u;
     peak = m > peak ? m : peak;
     peak = m2 > peak ? m2 : peak;
     double x = 0.0, comm = 0.0;
     if (i < P - 1) {
-      x += p2p / bw_n;
+      x += x_n;
       if (pl.egress && zn != z) comm = (double)nb * (double)D * p2p * eg;
     }
-    if (i > 0) x += p2p / bw_p;
+    if (i > 0) x += x_p;
     // the slower replica type sets the stage's pace (straggler, Sec. 4.3)
     const double t = fmax(c1, c2) + x;
     max_t = fmax(max_t, t);
-    if (D > 1) {
-      const uint64_t shard = (params + (uint64_t)tp - 1) / (uint64_t)tp;
-      const double bytes = (double)shard * (double)pl.gb;
-      const double sync = 2.0 * (double)(D - 1) / (double)D * bytes / link_bw(pl, z, z, bytes);
-      t_sync = fmax(t_sync, sync);
-    }
+    if (D > 1) t_sync = fmax(t_sync, ring * grads / link_bw(pl, z, z, grads));
     t_upd = fmax(t_upd, u1);
     t_upd = fmax(t_upd, u2);
     lds.t[i] = t;
@@ -1945,7 +2013,8 @@ struct RefineArgs {
   const SurvRec *surv;
   uint32_t surv_cap;
   uint32_t *counters;
-  const uint32_t *tau_src;  // NULL: take every survivor
+  uint32_t kth;             // if not 0: the threshold is what COLLECT's slots give for the kth smallest key, else
+  const uint32_t *tau_src;  // this; NULL: take every survivor
   float band;
   RefRec *ref;
   uint32_t ref_cap;
@@ -1962,13 +2031,15 @@ __global__ __launch_bounds__(kRefineWaves * 64) void k_refine(DevPlan pl, Refine
   // records, so the address is valid whatever the count turns out to be)
   SurvRec first{};
   if (wave < a.surv_cap) first = a.surv[wave];
+  touch_arguments(pl);
   const uint32_t n = min(a.counters[CNT_SURV], a.surv_cap);
-  const float tau = a.tau_src ? __uint_as_float(*a.tau_src) * a.band : kPosInf;
+  float tau = kPosInf;
+  if (a.kth) tau = __uint_as_float(kth_of_slots(a.counters + kKeptSlots, a.kth)) * a.band;
+  else if (a.tau_src) tau = __uint_as_float(*a.tau_src) * a.band;
   for (uint32_t i = wave; i < n; i += n_waves) {
     const SurvRec sv = i == wave ? first : a.surv[i];
-    if (!(sv.key_loose <= tau)) continue;
-    Cand c;
-    decode_in_shape(pl, sv.shape, sv.idx, c);
+    if (!(__uint_as_float(sv.key & 0x7fffffffu) <= tau)) continue;
+    const Cand c = candidate(sv);
     RefRec r;
     r.idx = sv.idx;
     r.pad = 0;
@@ -2033,38 +2104,69 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
   const uint64_t count_owner = __hip_atomic_load(reinterpret_cast<const uint64_t *>(a.counters + CNT_SURV),
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t gmin = a.counters[CNT_GMIN];
+  touch_arguments(pl);  // (while these are on their way)
   const uint32_t n_surv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)count_owner),
                  owner = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(count_owner >> 32));
   const uint32_t n = min(n_surv, a.surv_cap);
   const float tau = __uint_as_float(gmin) * a.band;
   const bool alone = n <= kBestAlone;  // uniform over the call's grid
   if (blockIdx.x != 0 && (alone || owner != call)) return;
-  auto evaluate = [&](uint64_t idx, uint32_t shape) {
-    Cand c;
-    decode_in_shape(pl, shape, idx, c);
+  auto evaluate = [&](const SurvRec &sv) {
+    const Cand c = candidate(sv);
     RefRec r;
-    r.idx = idx;
+    r.idx = sv.idx;
     r.pad = 0;
     eval_exact_wave(pl, c, a.objective, a.has_bound, a.bound, lds[wv], r.T, r.C, r.mem, r.mask);
     return r;
   };
+  auto within = [&](const SurvRec &sv) { return __uint_as_float(sv.key & 0x7fffffffu) <= tau; };
   auto key_of = [&](const RefRec &r) { return r.mask != 0 ? __builtin_huge_val() : (a.objective == 0 ? r.T : r.C); };
   uint32_t n_ref, n_feas = 0;
+  auto reset_next = [&](uint32_t from) {  // for the next call
+    for (uint32_t c = (uint32_t)t - from; c < kSetWords; c += kBestWaves * 64 - from) next_counters[c] = counter_reset_value((int)c, owner + 1);
+  };
   if (alone) {
-    const unsigned long long near = __builtin_amdgcn_ballot_w64((uint32_t)lane < n && mine.key_loose <= tau);
+    const unsigned long long near = __builtin_amdgcn_ballot_w64((uint32_t)lane < n && within(mine));
     const uint32_t rank = (uint32_t)__popcll(near & ((1ull << lane) - 1ull));
     n_ref = (uint32_t)__popcll(near);
     for (uint32_t w = wv; w < n_ref; w += kBestWaves) {  // uniform over the wave
       const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(((near >> lane) & 1ull) != 0 && rank == w));
-      const RefRec r = evaluate(__shfl((unsigned long long)mine.idx, from), (uint32_t)__shfl((int)mine.shape, from));
+      SurvRec sv;
+      auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, from); };
+      sv.idx = (uint64_t)of((uint32_t)(mine.idx >> 32)) << 32 | of((uint32_t)mine.idx);
+      sv.key = 0;
+      sv.row_stage = of(mine.row_stage);
+      sv.where = of(mine.where);
+      sv.segs = of(mine.segs);
+      const RefRec r = evaluate(sv);
       if (lane == 0) s_ref[w] = r;
     }
+    if (wv != 0) reset_next(64);
     __syncthreads();
+    if (wv != 0) return;
+    // a lane each: no more barriers
+    const bool valid = (uint32_t)lane < n_ref && s_ref[lane].mask == 0;
+    const double key = valid ? key_of(s_ref[lane]) : __builtin_huge_val(), limit = wave_min_f64(key) * (1.0 + kTieTol);
+    const unsigned long long idx = valid && key <= limit ? s_ref[lane].idx : ~0ull, lowest = wave_min_u64(idx);
+    const bool found = lowest != ~0ull;
+    const uint32_t at = (uint32_t)__builtin_ctzll(__builtin_amdgcn_ballot_w64(idx == lowest));
+    if (found && lane < (int)(sizeof(RefRec) / 8))
+      reinterpret_cast<unsigned long long *>(out)[lane] = reinterpret_cast<const unsigned long long *>(&s_ref[at])[lane];
+    n_feas = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(valid));
+    if (lane == 0) {
+      hdr->n_found = found ? 1u : 0u;
+      hdr->surv_count = n_surv;
+      hdr->ref_count = n_ref;
+      hdr->feasible_count = n_feas;
+      hdr->gmin_bits = gmin;
+      publish(hdr, seq);
+    }
+    return;
   } else {
     for (uint32_t i = blockIdx.x * kBestWaves + wv; i < n; i += gridDim.x * kBestWaves) {
       const SurvRec sv = a.surv[i];
-      if (!(sv.key_loose <= tau)) continue;
-      const RefRec r = evaluate(sv.idx, sv.shape);
+      if (!within(sv)) continue;
+      const RefRec r = evaluate(sv);
       if (lane == 0) {
         const uint32_t slot = atomicAdd(&a.counters[CNT_REF], 1u);
         if (slot < a.ref_cap) {  // (what does not fit is counted only: the host reports it)
@@ -2082,12 +2184,9 @@ __global__ __launch_bounds__(kBestWaves * 64) void k_refine_best(DevPlan pl, Ref
     n_ref = __hip_atomic_load(&a.counters[CNT_REF], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     n_feas = __hip_atomic_load(&a.counters[CNT_FEAS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  for (int c = t; c < (int)kSetWords; c += kBestWaves * 64) next_counters[c] = counter_reset_value(c, owner + 1);  // for the next call
-  const RefRec *const ref = alone ? s_ref : a.ref;
-  const uint32_t stored = alone ? n_ref : min(n_ref, a.ref_cap);
-  if (alone) {
-    n_feas = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((uint32_t)lane < stored && s_ref[lane].mask == 0));
-  }
+  reset_next(0);
+  const RefRec *const ref = a.ref;
+  const uint32_t stored = min(n_ref, a.ref_cap);
   double best = __builtin_huge_val();
   for (uint32_t i = t; i < stored; i += kBestWaves * 64) best = fmin(best, key_of(ref[i]));
   best = wave_min_f64(best);
@@ -2374,9 +2473,8 @@ __device__ __forceinline__ void sim_plan(const DevPlan &pl, const SimArgs &a, ui
                                          double *s_t) {
   const int P = c.P, G = pl.G, GX = pl.GX, Z = pl.Z, MB = pl.MB, TP = pl.TP;
   const int lane = threadIdx.x & 63;
-  const uint32_t rs = pl.shapes[c.shape].row_stage;
-  const double p2p = (double)pl.p2p[c.mb];
-  const double *bwp = pl.bwp + c.mb * Z * Z;
+  const uint32_t rs = c.row_stage;
+  const double *xsec = pl.xsec + c.mb * Z * Z;
   double fd[SPL], bd[SPL];
 #pragma unroll
   for (int s = 0; s < SPL; ++s) {
@@ -2390,11 +2488,11 @@ __device__ __forceinline__ void sim_plan(const DevPlan &pl, const SimArgs &a, ui
     double send_f = 0.0, send_b = 0.0;
     if (i < P - 1) {
       const int sn = (i + 1) < c.k1 ? 0 : ((i + 1) < c.k2 ? 1 : 2);
-      send_f = p2p / bwp[z * Z + at3(c.a, sn) / GX];
+      send_f = xsec[z * Z + at3(c.a, sn) / GX];
     }
     if (i > 0) {
       const int sp = (i - 1) < c.k1 ? 0 : ((i - 1) < c.k2 ? 1 : 2);
-      send_b = p2p / bwp[z * Z + at3(c.a, sp) / GX];
+      send_b = xsec[z * Z + at3(c.a, sp) / GX];
     }
     double f = pl.st_f[at], b = pl.st_b[at];
     if (g2 != g && pl.st_f[at2] + pl.st_b[at2] > f + b) {  // the pipeline through the slower type
