@@ -294,8 +294,8 @@ sailor_status sailor_topk(sailor_plan *plan, sailor_objective objective,
                           int32_t *n_found, void *hip_stream);
 
 /* Resize the device scratch of the selection: the list of candidates that survive the fp32
- * scan (24 B each, default 4 Mi entries) and the list re-evaluated in fp64 (40 B each,
- * default 256 Ki entries).  sailor_topk searches for a tighter threshold when the first
+ * scan (24 B each) and the list re-evaluated in fp64 (40 B each).  Until then a plan has 64 Ki and
+ * 16 Ki entries, and takes 4 Mi and 256 Ki when a query first keeps more.  sailor_topk searches for a tighter threshold when the first
  * list would overflow; a call fails with SAILOR_ENOMEM only when more candidates than fit
  * lie within the rounding band of the k-th key (or, for sailor_best_plan, within the tie
  * tolerance of the minimum).  Waits for the device.  SAILOR_EINVAL for a zero size. */

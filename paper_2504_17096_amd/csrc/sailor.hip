@@ -22,6 +22,10 @@ namespace {
 
 constexpr uint32_t kDefaultSurvCap = 1u << 22;  // 96 MiB of survivors
 constexpr uint32_t kDefaultRefCap = 1u << 18;
+// What a plan starts with (2 MiB): a query keeps some hundreds, and the few that keep more enlarge the
+// buffers to the above.  (A plan's destruction took 0.55 ms, most of it the release of the 96 MiB, and 4.3 ms
+// for minutes when the driver was behind with such releases.)
+constexpr uint32_t kFirstSurvCap = 1u << 16, kFirstRefCap = 1u << 14;
 // candidates per scan workgroup: large enough to amortise the staging of a unit, small
 // enough to leave about ten workgroups per compute unit
 constexpr uint64_t kUnitTargetMin = 4096, kUnitTargetMax = 65536, kUnitsWanted = 2560;
@@ -205,7 +209,8 @@ struct sailor_plan {
   uint32_t *ulist = nullptr;   // units the collect pass has to visit
   SurvRec *surv = nullptr;
   RefRec *ref = nullptr;
-  uint32_t surv_cap = kDefaultSurvCap, ref_cap = kDefaultRefCap;
+  uint32_t surv_cap = kFirstSurvCap, ref_cap = kFirstRefCap;
+  bool scratch_grows = true;   // they are what the plan started with
   // host-mapped result area: header + SAILOR_MAX_K records
   void *h_result = nullptr;
   ResultHeader *d_hdr = nullptr;
@@ -821,8 +826,9 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     if (rc != SAILOR_OK) return rc;
     pl->total_timed = t_all;
     pl->scan_timed = t_scan;
-    if (hdr_out->surv_count > pl->surv_cap) {
-      *again = true;  // a running minimum admits more than the final one: the scan's minimum decides
+    // (a running minimum admits more than the final one: the scan's minimum decides)
+    if (hdr_out->surv_count > pl->surv_cap || (pl->scratch_grows && hdr_out->ref_count > pl->ref_cap)) {
+      *again = true;
       return SAILOR_OK;
     }
     pl->last_direct = sa.direct != 0;
@@ -904,6 +910,10 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   if (rc != SAILOR_OK) return rc;
   pl->total_timed = t_all;
   pl->scan_timed = t_scan;
+  if (pl->scratch_grows && (hdr_out->surv_count > pl->surv_cap || hdr_out->ref_count > pl->ref_cap)) {
+    *again = true;
+    return SAILOR_OK;
+  }
   if (!best && hdr_out->surv_count > pl->surv_cap) {
     // The unit minima gave too loose a bound (few units hold valid plans, or none of them
     // strictly inside the constraint).  Search for a threshold that keeps at least k strict
@@ -958,10 +968,36 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   return SAILOR_OK;
 }
 
+// New survivor and re-evaluation buffers (the old ones stay if there is no memory).
+sailor_status resize_scratch(sailor_plan *pl, uint32_t max_survivors, uint32_t max_refined) {
+  HIP_TRY(hipSetDevice(pl->device));
+  HIP_TRY(hipDeviceSynchronize());
+  SurvRec *surv = nullptr;
+  RefRec *ref = nullptr;
+  if (pl->arena.alloc(&surv, (size_t)max_survivors) != hipSuccess) return SAILOR_ENOMEM;
+  if (pl->arena.alloc(&ref, (size_t)max_refined) != hipSuccess) {
+    pl->arena.free_one(surv);
+    return SAILOR_ENOMEM;
+  }
+  pl->arena.free_one(pl->surv);
+  pl->arena.free_one(pl->ref);
+  pl->surv = surv;
+  pl->ref = ref;
+  pl->surv_cap = max_survivors;
+  pl->ref_cap = max_refined;
+  pl->scratch_grows = false;
+  return SAILOR_OK;
+}
+
 sailor_status run_selection(sailor_plan *pl, sailor_objective obj, const sailor_constraint *con,
                             uint32_t k, hipStream_t st, ResultHeader *hdr_out) {
   bool again = false;
   sailor_status rc = run_selection_impl(pl, obj, con, k, st, hdr_out, true, &again);
+  if (rc == SAILOR_OK && again && pl->scratch_grows) {  // what was kept did not fit: once more with room for more
+    again = false;
+    try { rc = resize_scratch(pl, kDefaultSurvCap, kDefaultRefCap); } catch (...) { rc = SAILOR_ENOMEM; }
+    if (rc == SAILOR_OK) rc = run_selection_impl(pl, obj, con, k, st, hdr_out, true, &again);
+  }
   if (rc == SAILOR_OK && again) rc = run_selection_impl(pl, obj, con, k, st, hdr_out, false, &again);
   if (rc == SAILOR_EDEVICE) pl->counters_dirty = true;
   if (rc == SAILOR_OK) { pl->last_hdr = *hdr_out; pl->have_hdr = true; }
@@ -1165,7 +1201,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.zeroed(&pl->unit_gen, unit_cap);
   slab.zeroed(&pl->unit_seq, unit_cap);
   pl->ubits_stride = (uint32_t)(unit_lds_records(ZG, MB) + (size_t)ZG);
-  slab.table(&pl->ubits, unit_cap * (size_t)pl->ubits_stride);
   slab.table(&pl->staged, (size_t)SAILOR_MAX_K);
   CREATE_TRY(slab.commit(pl->arena));
   pl->d_avail = const_cast<int32_t *>(d.avail);
@@ -1407,22 +1442,7 @@ sailor_status sailor_topk(sailor_plan *pl, sailor_objective objective,
 sailor_status sailor_plan_set_scratch(sailor_plan *pl, uint32_t max_survivors,
                                       uint32_t max_refined) {
   if (!pl || max_survivors < 1 || max_refined < 1) return SAILOR_EINVAL;
-  HIP_TRY(hipSetDevice(pl->device));
-  HIP_TRY(hipDeviceSynchronize());
-  SurvRec *surv = nullptr;
-  RefRec *ref = nullptr;
-  if (pl->arena.alloc(&surv, (size_t)max_survivors) != hipSuccess) return SAILOR_ENOMEM;
-  if (pl->arena.alloc(&ref, (size_t)max_refined) != hipSuccess) {
-    pl->arena.free_one(surv);
-    return SAILOR_ENOMEM;
-  }
-  pl->arena.free_one(pl->surv);
-  pl->arena.free_one(pl->ref);
-  pl->surv = surv;
-  pl->ref = ref;
-  pl->surv_cap = max_survivors;
-  pl->ref_cap = max_refined;
-  return SAILOR_OK;
+  try { return resize_scratch(pl, max_survivors, max_refined); } catch (...) { return SAILOR_ENOMEM; }
 }
 
 sailor_status sailor_plan_set_timing(sailor_plan *pl, int32_t mode) {
@@ -1826,6 +1846,12 @@ sailor_status sailor_set_scan_unit_parts(int32_t n) {
 
 sailor_status sailor_plan_set_incremental(sailor_plan *pl, int32_t on) {
   if (!pl || (on != 0 && on != 1)) return SAILOR_EINVAL;
+  if (on && !pl->ubits) {  // (45 MB for the 14 000 units of 1.1e9 plans: allocated where it is used)
+    HIP_TRY(hipSetDevice(pl->device));
+    try {
+      if (pl->arena.alloc(&pl->ubits, pl->units.size() * (size_t)pl->ubits_stride) != hipSuccess) return SAILOR_ENOMEM;
+    } catch (...) { return SAILOR_ENOMEM; }
+  }
   if (pl->incremental != (on != 0)) pl->cache_ok = false;  // what a scan keeps depends on it
   pl->incremental = on != 0;
   return SAILOR_OK;

@@ -1004,3 +1004,24 @@ def test_scan_guided_by_a_running_limit(torch_cuda, mixed, zones):
         assert plan.last_scan()[1] > 4096  # of two or more waves each: more than the chip's 8 192
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("objective", [MAX_THROUGHPUT, MIN_COST])
+def test_more_ties_than_the_first_survivor_buffers_hold(torch_cuda, objective):
+    # 16 zones that do not differ: 77 296 placements of eight stages in up to three segments tie for the best,
+    # and the buffers a plan starts with (64 Ki kept, 16 Ki re-evaluated) are enlarged by the first query
+    Z = 16
+    prob = make_problem(n_layers=8, n_zones=Z, mb_list=(1,), tp_list=(1,), dp_list=(1, 2), pp_list=[8], max_segments=3,
+                        seg3_max_pp=8, global_batch=32, avail=np.full((Z, 1), 64), bw=np.full((Z, Z), 1e10), p2p=1_000_000)
+    orc = Oracle(prob)
+    for first in ("best", "topk"):
+        plan = _plan(prob)
+        try:
+            for call in (("best", "topk") if first == "best" else ("topk", "best")):
+                if call == "best":
+                    check_result(plan.best_plan(objective=objective), orc.best(objective, n_threads=4), orc)
+                else:
+                    check_topk(plan.topk(64, objective=objective), orc.topk(64, objective, n_threads=4), objective, orc)
+                assert plan.last_counts()[0] > 1 << 16
+        finally:
+            plan.destroy()
