@@ -2520,6 +2520,7 @@ __device__ __forceinline__ void sim_plan(const DevPlan &pl, const SimArgs &a, ui
 }
 
 __global__ __launch_bounds__(64) void k_sim_1f1b(DevPlan pl, SimArgs a) {
+  touch_arguments(pl);
   __shared__ double s_t[kMaxStages];
   const uint64_t ci = blockIdx.x;
   if (ci >= a.count) return;
