@@ -31,9 +31,9 @@
 // inputs are requested a level ahead, appending candidates takes no barrier, the W smallest come
 // from a histogram and (up to 512 of them) a count of predecessors instead of a sort of everything, and a wide choice
 // (second pool, TP degree) is first reduced to the best of each (state, pool).  On the 48-layer,
-// 20-pool problem a search with beam 64 takes 0.51 ms where states in device memory, paths copied
+// 20-pool problem a search with beam 64 takes 0.48 ms where states in device memory, paths copied
 // level by level and a bitonic sort of every level took 2.9 ms; with two pools and a TP degree per
-// stage (1 600 choices, beam 8) 0.84 ms against 9.3 ms.  (0.60 and 1.05 ms with equal layer splits gone
+// stage (1 600 choices, beam 8) 0.74 ms against 9.3 ms.  (0.1 and 0.2 ms more with equal layer splits gone
 // through one by one: a depth of as many stages as layers has one split, however often it is listed,
 // and its sub-problems, 576 of 1 078, shared the compute units with the 8 that take longest.)
 #pragma once
@@ -549,8 +549,7 @@ __global__ __launch_bounds__(kRootWaves * 64) void k_search_root(DevPlan pl, Sea
       if (lane == 0)
         a.list[(STP ? a.pps[s.ip].sub_off_t : a.pps[s.ip].sub_off) + atomicAdd(&a.counters[s.ip], 1u)] = sid;
     } else {
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
+      mine = wave_sum(mine);
       expanded += (unsigned long long)mine * s.alike;
     }
   }
@@ -700,12 +699,7 @@ __device__ __forceinline__ int search_select(const SearchLds &L, SelectShared &s
     uint32_t h[kPer], sum = 0;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) { h[q] = L.hist[lane * kPer + q]; sum += h[q]; }
-    uint32_t incl = sum;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t v = __shfl_up(incl, off);
-      if (lane >= off) incl += v;
-    }
+    const uint32_t incl = wave_prefix_sum(sum);
     uint32_t excl = (uint32_t)below + incl - sum;
     const unsigned long long here = __builtin_amdgcn_ballot_w64(excl < (uint32_t)W && (uint32_t)W <= excl + sum);
     const int owner = __builtin_ctzll(here);
@@ -1053,8 +1047,7 @@ __global__ __launch_bounds__(kSearchThreads, (MODE & 1) ? 2 : 4) void k_search_b
           }
           const bool done = i0 >= n_all;
           if (done && phase == 0) {  // how many were kept in all
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) kept += __shfl_xor(kept, off);
+            kept = wave_sum(kept);
             if (lane == 0 && kept) atomicAdd(&s_kept[cur], kept);
           }
           __syncthreads();
@@ -1527,14 +1520,9 @@ __global__ __launch_bounds__(kPlaceThreads) void k_eval_placements(DevPlan pl, P
         p.rs = pp.rs0 + (uint32_t)d.split * (uint32_t)pp.P;
         p.it = (uint8_t)d.it; p.id = (uint8_t)d.id; p.im = (uint8_t)d.im;
       }
-      int end = p.P;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(end, off);
-        if (lane >= off) end += v;
-      }
+      const int end = (int)wave_prefix_sum(p.P);
       const int n = __popcll(__builtin_amdgcn_ballot_w64(next + lane < c_end && end <= kPlaceStages));
-      const int stages = __shfl(end, max(n - 1, 0));
+      const int stages = __builtin_amdgcn_readlane(end, max(n - 1, 0));
       if (lane < n) {
         p.end = (uint16_t)end;
         S.plan[b][lane] = p;
@@ -1826,12 +1814,8 @@ __device__ __forceinline__ ReplicaSums replica_pairs(const DevPlan &pl, const Re
     if (THREADS == 64) wave_lds_fence();  // the next tile's times come after these reads
     else __syncthreads();
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint64_t o = __shfl_xor((unsigned long long)s.peak, off);
-    s.peak = o > s.peak ? o : s.peak;
-    s.flags |= __shfl_xor(s.flags, off);
-  }
+  s.peak = wave_max_u64(s.peak);
+  s.flags = wave_fold(s.flags, [](uint32_t x, uint32_t y) { return x | y; });
   s.t_pipe = wave_max_f64(s.t_pipe);
   s.t_sync = wave_max_f64(s.t_sync);
   s.t_upd = wave_max_f64(s.t_upd);
