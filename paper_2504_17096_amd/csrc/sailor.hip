@@ -33,7 +33,14 @@ constexpr uint64_t kUnitTargetMin = 4096, kUnitTargetMax = 65536, kUnitsWanted =
 // 14.5 us with 8 and 256, where two units fall to one group more often; 12.7 with these)
 constexpr uint32_t kCollectSub = 4, kCollectUnits = 512;
 constexpr size_t kChipWaves = 8192;      // 256 compute units of 32 waves
-constexpr uint32_t kSeedTicks = 800;     // 8 us: what the first units of a scan take from launch to result
+// A running k-th key takes longer to be found than a running minimum and rules out less: spaces up to twice the
+// chip's waves are scanned unguided for it (k = 26 of 3 600 units of four waves with pairs of types 74 -> 64 us, k = 53
+// of 5 580 units of two waves, 706 of them within a budget, 58 -> 38; cheapest of 2 806 units of three waves 40, unguided 99)
+constexpr size_t kGuidedKthWaves = 2 * kChipWaves;
+// What the first units of a scan take from launch to a result, at 100 MHz.  (Where a constraint leaves the first units
+// nothing, the wait is for nothing: cheapest of 7 296 units at 0.87 of the largest throughput 41 us with 8 us, 37 with 5;
+// those that find something have by then.)
+constexpr uint32_t kBestSeedTicks = 500, kKthSeedTicks = 800;
 constexpr uint32_t kKthLive = 128;       // largest k whose running bound guides the scan (half the key slots)
 // A query whose constraint leaves at most this many units alive skips the scan: one pass
 // keeps every valid candidate of those units (see run_selection_impl)
@@ -810,10 +817,10 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   }
   // units that do not fit on the chip at once: the first of the order guide the others (scan_workgroups)
   auto guide = [&]() {
-    if (!sa.rows_key || (size_t)n_units * (pl->unit_threads / 64) <= kChipWaves) return;
+    if (!sa.rows_key || (size_t)n_units * (pl->unit_threads / 64) <= (best ? kChipWaves : kGuidedKthWaves)) return;
     sa.n_seeds = best ? kBestSeeds : kKthSeeds;
     sa.n_sub = best ? kBestSeedSub : kKthSeedSub;
-    sa.wait_ticks = kSeedTicks;
+    sa.wait_ticks = best ? kBestSeedTicks : kKthSeedTicks;
     if (obj == SAILOR_MIN_COST) sa.ulist = pl->order_cost;  // (their own order is by time)
   };
   if (best && !sa.incremental && first_try) {

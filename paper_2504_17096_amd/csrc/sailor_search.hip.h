@@ -1871,7 +1871,7 @@ __device__ __forceinline__ void replica_write(const ReplicaArgs &a, const ListTa
 // 512 pairs; a larger one, of which one can hold as many pairs as hundreds of small plans, is
 // shared by the four waves.  With a lane per pipeline that fetched stage after stage (most lanes
 // idle at D < 64, a chain of memory trips per stage) 10 007 plans of 1-48 stages and 1-32 replicas
-// took 225 us; they take 45 us now, half of the workgroups being done after 12 us: what is left is
+// took 225 us; they take 44 us now, half of the workgroups being done after 12 us: what is left is
 // the chain of trips in front of a plan and the workgroups that hold several large plans.
 __global__ __launch_bounds__(kReplicaWaves * 64) void k_eval_replicas(DevPlan pl, ReplicaArgs a) {
   extern __shared__ ulonglong2 rep_lds[];

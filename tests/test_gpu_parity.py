@@ -1001,7 +1001,7 @@ def test_scan_guided_by_a_running_limit(torch_cuda, mixed, zones):
                         check_topk(plan.topk(k, objective=objective, bound=bound, stream=stream),
                                    orc.topk(k, objective=objective, bound=bound, n_threads=THREADS),
                                    objective, orc, bound)
-        assert plan.last_scan()[1] > 4096  # of two or more waves each: more than the chip's 8 192
+        assert plan.last_scan()[1] > 16384  # units: more than the chip's 8 192 waves, and twice that for a k-th key
     finally:
         plan.destroy()
 
