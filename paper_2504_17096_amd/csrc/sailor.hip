@@ -37,9 +37,12 @@ constexpr size_t kChipWaves = 8192;      // 256 compute units of 32 waves
 // chip's waves are scanned unguided for it (k = 26 of 3 600 units of four waves with pairs of types 74 -> 64 us, k = 53
 // of 5 580 units of two waves, 706 of them within a budget, 58 -> 38; cheapest of 2 806 units of three waves 40, unguided 99)
 constexpr size_t kGuidedKthWaves = 2 * kChipWaves;
+// Pairs of types make a unit long enough that the best plan's scan is guided wherever there is a unit to wait
+// (fastest of 2 295 units of three waves 114 us as they come and 37 guided, of 1 464 86 and 37, of 324 39 and 27).
+constexpr size_t kGuidedMixedWaves = 512;
 // What the first units of a scan take from launch to a result, at 100 MHz.  (Where a constraint leaves the first units
 // nothing, the wait is for nothing: cheapest of 7 296 units at 0.87 of the largest throughput 41 us with 8 us, 37 with 5;
-// those that find something have by then.)
+// those that find something have by then.  With 3 us that query takes 34, but pairs of types 68 instead of 31.)
 constexpr uint32_t kBestSeedTicks = 500, kKthSeedTicks = 800;
 constexpr uint32_t kKthLive = 128;       // largest k whose running bound guides the scan (half the key slots)
 // A query whose constraint leaves at most this many units alive skips the scan: one pass
@@ -817,7 +820,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   }
   // units that do not fit on the chip at once: the first of the order guide the others (scan_workgroups)
   auto guide = [&]() {
-    if (!sa.rows_key || (size_t)n_units * (pl->unit_threads / 64) <= (best ? kChipWaves : kGuidedKthWaves)) return;
+    if (!sa.rows_key || (size_t)n_units * (pl->unit_threads / 64) <= (!best ? kGuidedKthWaves : pl->dev.mixed ? kGuidedMixedWaves : kChipWaves)) return;
     sa.n_seeds = best ? kBestSeeds : kKthSeeds;
     sa.n_sub = best ? kBestSeedSub : kKthSeedSub;
     sa.wait_ticks = best ? kBestSeedTicks : kKthSeedTicks;
@@ -1179,7 +1182,6 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&d.dph_f, DP);
   slab.table(&d.nb, (size_t)MB * DP);
   slab.table(&d.divis, MB);
-  slab.table(&d.st_params, RS);
   // a stage record does not straddle cache lines (128 bytes): the evaluators of listed plans
   // fetch one per stage from anywhere in the table, and lines are what that costs
   d.row_w = 2u * (uint32_t)G + 2u;

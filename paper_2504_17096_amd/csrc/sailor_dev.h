@@ -151,7 +151,7 @@ struct DevPlan {
   // per-stage tables, one entry per stage of every partition row
   const int32_t *st_n;         // layers
   const int32_t *st_first;     // first layer
-  uint64_t *st_params;         // parameters incl. embedding / head
+  uint64_t unused_too;         // (for the same reason)
   // one record per stage, microbatch size and TP degree, of row_w words: compute seconds per
   // type [G], update seconds per type [G], bytes of weights, gradients and optimizer state of
   // the shard (as an integer), bytes of its gradient buffer

@@ -3,7 +3,7 @@
 // Set-up kernels (once per plan): k_small_tables, k_stage_tables, k_shape_agg, k_group_bounds;
 //            k_quota_table    again whenever the availability changes.
 // Hot path:  k_units<SCAN>    full-space fp32 evaluation + per-unit minima, early pruning
-//            k_select_kth     radix select of the k-th smallest fp32 key
+//            k_select_kth     radix select of the k-th smallest fp32 key (k > 128, or minima kept for later calls)
 //            k_units<COLLECT> re-evaluates the few units that can hold a winner
 //            k_refine, k_rank_topk   fp64 / exact-integer stage-by-stage re-evaluation, ranking
 //            k_units<BEST>, k_refine_best   the best plan: the same in two kernels
@@ -228,7 +228,6 @@ __global__ void k_stage_tables(DevPlan pl, StageArgs a) {
     for (int l = first; l < first + n; ++l) p += a.layer_params[l];
     if (a.st_flags[rs] & 1) p += a.embed;
     if (a.st_flags[rs] & 2) p += a.head;
-    pl.st_params[rs] = p;
     s_params = p;
   }
   double *const row = pl.st_row + (size_t)rs * MB * TP * pl.row_w;  // [MB][TP][row_w]
@@ -1515,7 +1514,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
 // (record, staging, walk, limit: 8 us) and that of the units left alive (10 us).  Scan for the 64
 // fastest of 9.2e8 plans with a TP degree per segment 86 -> 28 us, fastest of 1.0e8 28 -> 18, cheapest of
 // 1.1e9 with pairs of types 167 -> 19.  Units that do fit at once gain nothing by waiting (1 632 of them: 19
-// us, and 15.5 as they come).
+// us, and 15.5 as they come), those with pairs of types apart, which are longer.
 constexpr uint32_t kScanWaves = 6144, kScanPerWg = 32, kBestSeeds = 16, kBestSeedSub = 16, kKthSeeds = 64, kKthSeedSub = 8;
 __host__ __device__ inline uint32_t scan_workgroups(uint32_t n_units, uint32_t waves) {
   uint32_t per = (n_units * waves + kScanWaves - 1) / kScanWaves;
@@ -1614,7 +1613,7 @@ constexpr uint32_t kKthByRank = 128, kKthByRankFrom = 8192, kKthRanked = 512;
 // With a list (1024 threads only): also writes the positions i < n_list_src whose list_src[i] is finite and at
 // most result * band to list, and their number to *list_count (in no particular order).
 //
-// Thousands of values for a small k (the units' minima) take no radix pass: every wave names the
+// Thousands of values for a small k (the units' minima, where a call keeps them or starts over) take no radix pass: every wave names the
 // ceil(k / waves) smallest of its lanes' minima, and the largest value so named has at least k values up
 // to it.  Those -- hundreds, units being dealt to lanes by their place in the launch order -- go to LDS,
 // where each counts its rank.  The 64th of the minima of 9.2e8 plans' units, and the list: 15.7 -> 9.7 us, of
