@@ -965,20 +965,21 @@ def test_threshold_among_more_units_than_a_workgroup_keeps(torch_cuda, form):
         plan.destroy()
 
 
-@pytest.mark.parametrize("mixed, zones", [(False, 1), (False, 2), (True, 1), (True, 2)])
-def test_scan_guided_by_a_running_limit(torch_cuda, mixed, zones):
+@pytest.mark.parametrize("mixed, zones, parts", [(False, 1, 40), (False, 2, 40), (True, 1, 40), (True, 2, 40), (True, 1, 1),
+                                                 (True, 2, 1)])
+def test_scan_guided_by_a_running_limit(torch_cuda, mixed, zones, parts):
     # More units than fit on the chip at once: the first of their order are shared by workgroups, the others
     # wait for them and take several units each.  The order is that of the availability at creation, so it is
     # set to one that rules the best units out (and nothing, and everything); one zone, where neighbouring
     # segments cannot share a type; degrees that pairs of types cannot halve (1, 3); k on both sides of
-    # what the running k-th key is kept for (128), and of the plans there are.  Against the oracle, whole numbers
-    # and indices the same.
+    # what the running k-th key is kept for (128), and of the plans there are.  Whole units of pairs of types: fewer,
+    # which do fit, and guide the best plan's scan only.  Against the oracle, whole numbers and indices the same.
     from dataclasses import replace
     from paper_2504_17096_amd.binding import set_scan_unit_parts
     stream = torch_cuda.cuda.current_stream().cuda_stream
     prob = replace(W.tiny_problem(73, n_layers=8, n_zones=zones, seg3_max_pp=8), global_batch=768,
                    dp_values=np.array([1, 2, 3, 4, 8], np.int32)).with_per_segment_tp(True).with_mixed_types(mixed)
-    set_scan_unit_parts(40)
+    set_scan_unit_parts(parts)
     try:
         plan = _plan(prob.with_avail(np.minimum(prob.avail, 2)))
     finally:
@@ -1001,7 +1002,8 @@ def test_scan_guided_by_a_running_limit(torch_cuda, mixed, zones):
                         check_topk(plan.topk(k, objective=objective, bound=bound, stream=stream),
                                    orc.topk(k, objective=objective, bound=bound, n_threads=THREADS),
                                    objective, orc, bound)
-        assert plan.last_scan()[1] > 16384  # units: more than the chip's 8 192 waves, and twice that for a k-th key
+        # units: more than the chip's 8 192 waves, and twice that for a k-th key; pairs of types: more than 512 waves
+        assert plan.last_scan()[1] > 16384 if parts > 1 else 512 < plan.last_scan()[1] < 8192
     finally:
         plan.destroy()
 
