@@ -295,8 +295,8 @@ sailor_status sailor_topk(sailor_plan *plan, sailor_objective objective,
 
 /* Resize the device scratch of the selection: the list of candidates that survive the fp32
  * scan (24 B each) and the list re-evaluated in fp64 (40 B each).  Until then a plan has 64 Ki and
- * 16 Ki entries, and takes 4 Mi and 256 Ki when a query first keeps more.  sailor_topk searches for a tighter threshold when the first
- * list would overflow; a call fails with SAILOR_ENOMEM only when more candidates than fit
+ * 16 Ki entries; a query that would keep more takes 4 Mi and 256 Ki, without waiting for
+ * other streams, or goes on with what there is if the device has no memory for them.  sailor_topk searches for a tighter threshold when the first list would overflow; a call fails with SAILOR_ENOMEM only when more candidates than fit
  * lie within the rounding band of the k-th key (or, for sailor_best_plan, within the tie
  * tolerance of the minimum).  Waits for the device.  SAILOR_EINVAL for a zero size. */
 sailor_status sailor_plan_set_scratch(sailor_plan *plan, uint32_t max_survivors,

@@ -921,7 +921,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   if (rc != SAILOR_OK) return rc;
   pl->total_timed = t_all;
   pl->scan_timed = t_scan;
-  if (pl->scratch_grows && (hdr_out->surv_count > pl->surv_cap || hdr_out->ref_count > pl->ref_cap)) {
+  if (first_try && pl->scratch_grows && (hdr_out->surv_count > pl->surv_cap || hdr_out->ref_count > pl->ref_cap)) {
     *again = true;
     return SAILOR_OK;
   }
@@ -979,19 +979,18 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   return SAILOR_OK;
 }
 
-// New survivor and re-evaluation buffers (the old ones stay if there is no memory).
-sailor_status resize_scratch(sailor_plan *pl, uint32_t max_survivors, uint32_t max_refined) {
-  HIP_TRY(hipSetDevice(pl->device));
-  HIP_TRY(hipDeviceSynchronize());
+// New survivor and re-evaluation buffers; the old ones stay the plan's if there is no memory, and are not given
+// back here.
+sailor_status new_scratch(sailor_plan *pl, uint32_t max_survivors, uint32_t max_refined) {
   SurvRec *surv = nullptr;
   RefRec *ref = nullptr;
-  if (pl->arena.alloc(&surv, (size_t)max_survivors) != hipSuccess) return SAILOR_ENOMEM;
-  if (pl->arena.alloc(&ref, (size_t)max_refined) != hipSuccess) {
-    pl->arena.free_one(surv);
+  const bool got = pl->arena.alloc(&surv, (size_t)max_survivors) == hipSuccess &&
+                   pl->arena.alloc(&ref, (size_t)max_refined) == hipSuccess;
+  if (!got) {
+    (void)hipGetLastError();  // (reported here: not for the launch behind this to find)
+    if (surv) pl->arena.free_one(surv);
     return SAILOR_ENOMEM;
   }
-  pl->arena.free_one(pl->surv);
-  pl->arena.free_one(pl->ref);
   pl->surv = surv;
   pl->ref = ref;
   pl->surv_cap = max_survivors;
@@ -1004,10 +1003,19 @@ sailor_status run_selection(sailor_plan *pl, sailor_objective obj, const sailor_
                             uint32_t k, hipStream_t st, ResultHeader *hdr_out) {
   bool again = false;
   sailor_status rc = run_selection_impl(pl, obj, con, k, st, hdr_out, true, &again);
-  if (rc == SAILOR_OK && again && pl->scratch_grows) {  // what was kept did not fit: once more with room for more
-    again = false;
-    try { rc = resize_scratch(pl, kDefaultSurvCap, kDefaultRefCap); } catch (...) { rc = SAILOR_ENOMEM; }
-    if (rc == SAILOR_OK) rc = run_selection_impl(pl, obj, con, k, st, hdr_out, true, &again);
+  if (rc == SAILOR_OK && again && pl->scratch_grows) {
+    // What was kept did not fit: once more with room for more, or, where there is no memory, the longer way with
+    // what there is.  The first buffers (2 MiB) stay until the plan is destroyed: nothing has to be waited for,
+    // neither other streams' work nor this call's last workgroups, which may still read them.
+    bool grown = false;
+    try {
+      grown = new_scratch(pl, kDefaultSurvCap, kDefaultRefCap) == SAILOR_OK;
+    } catch (...) {
+    }
+    if (grown) {
+      again = false;
+      rc = run_selection_impl(pl, obj, con, k, st, hdr_out, true, &again);
+    }
   }
   if (rc == SAILOR_OK && again) rc = run_selection_impl(pl, obj, con, k, st, hdr_out, false, &again);
   if (rc == SAILOR_EDEVICE) pl->counters_dirty = true;
@@ -1452,7 +1460,17 @@ sailor_status sailor_topk(sailor_plan *pl, sailor_objective objective,
 sailor_status sailor_plan_set_scratch(sailor_plan *pl, uint32_t max_survivors,
                                       uint32_t max_refined) {
   if (!pl || max_survivors < 1 || max_refined < 1) return SAILOR_EINVAL;
-  try { return resize_scratch(pl, max_survivors, max_refined); } catch (...) { return SAILOR_ENOMEM; }
+  HIP_TRY(hipSetDevice(pl->device));
+  HIP_TRY(hipDeviceSynchronize());
+  SurvRec *const surv = pl->surv;
+  RefRec *const ref = pl->ref;
+  try {
+    const sailor_status rc = new_scratch(pl, max_survivors, max_refined);
+    if (rc != SAILOR_OK) return rc;
+    pl->arena.free_one(surv);
+    pl->arena.free_one(ref);
+    return SAILOR_OK;
+  } catch (...) { return SAILOR_ENOMEM; }
 }
 
 sailor_status sailor_plan_set_timing(sailor_plan *pl, int32_t mode) {

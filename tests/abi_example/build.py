@@ -1,4 +1,5 @@
-"""Builds the C program that drives the C ABI (tests/abi_example/abi_example.c) with gcc."""
+"""Builds the C program that drives the C ABI (tests/abi_example/abi_example.c) and the library that refuses
+device allocations (refuse_malloc.c) with gcc."""
 import os
 import subprocess
 
@@ -6,6 +7,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 SRC = os.path.join(HERE, "abi_example.c")
 EXE = os.path.join(HERE, "abi_example")
+REFUSAL_SRC = os.path.join(HERE, "refuse_malloc.c")
+REFUSAL = os.path.join(HERE, "librefuse_malloc.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
@@ -29,5 +32,13 @@ def build(force: bool = True) -> str:
     return EXE
 
 
+def build_refusal(force: bool = True) -> str:
+    if force or not os.path.exists(REFUSAL) or os.path.getmtime(REFUSAL_SRC) > os.path.getmtime(REFUSAL):
+        subprocess.check_call(["gcc", "-std=c99", "-O1", "-Wall", "-shared", "-fPIC", REFUSAL_SRC, "-o", REFUSAL,
+                               "-L" + os.path.join(ROCM, "lib"), "-Wl,--no-as-needed", "-lamdhip64", "-ldl",
+                               "-Wl,-rpath," + os.path.join(ROCM, "lib")])
+    return REFUSAL
+
+
 if __name__ == "__main__":
-    print(build())
+    print(build(), build_refusal())
