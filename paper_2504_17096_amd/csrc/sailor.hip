@@ -75,6 +75,14 @@ constexpr size_t kScanMaxLds = 160 * 1024;     // a scan workgroup stages its re
 
 std::atomic<int> g_forced_unit_parts{0};         // sailor_set_scan_unit_parts
 
+// Lets its thread allocate while a graph is captured: an allocation is refused otherwise, and the capture lost.
+class BesideCaptures {
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;  // (the calls exchange it with the thread's own)
+ public:
+  BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  ~BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+};
+
 struct DeviceArena {  // every device allocation of a plan, freed together
   std::vector<void *> ptrs;
   template <typename T>
@@ -1877,7 +1885,12 @@ sailor_status sailor_plan_set_incremental(sailor_plan *pl, int32_t on) {
   if (on && !pl->ubits) {  // (45 MB for the 14 000 units of 1.1e9 plans: allocated where it is used)
     HIP_TRY(hipSetDevice(pl->device));
     try {
-      if (pl->arena.alloc(&pl->ubits, pl->units.size() * (size_t)pl->ubits_stride) != hipSuccess) return SAILOR_ENOMEM;
+      const BesideCaptures beside;
+      if (pl->arena.alloc(&pl->ubits, pl->units.size() * (size_t)pl->ubits_stride) != hipSuccess) {
+        (void)hipGetLastError();  // (reported here)
+        pl->ubits = nullptr;
+        return SAILOR_ENOMEM;
+      }
     } catch (...) { return SAILOR_ENOMEM; }
   }
   if (pl->incremental != (on != 0)) pl->cache_ok = false;  // what a scan keeps depends on it

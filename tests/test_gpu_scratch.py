@@ -1,5 +1,5 @@
-"""The selection's buffers when a first query keeps more than they hold: beside work on other streams,
-and where there is no memory for larger ones."""
+"""What a plan allocates after its creation: larger selection buffers, beside work on other streams
+and where there is no memory for them, and what kept minima take."""
 import os
 import subprocess
 import sys
@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 from oracle.oracle import MAX_THROUGHPUT, MIN_COST, Oracle
+from paper_2504_17096_amd import workloads as W
 from tests.helpers import make_problem
 
 pytestmark = pytest.mark.gpu
@@ -72,13 +73,41 @@ def test_buffers_grow_beside_work_on_other_streams(torch_cuda, objective):
         plan.destroy()
 
 
+def test_minima_kept_from_within_a_capture_on(torch_cuda):
+    from paper_2504_17096_amd.binding import Plan
+    torch = torch_cuda
+    prob = W.config2()
+    plan, other = Plan(prob), Plan(prob)
+    try:
+        n = other.num_candidates()
+        t = torch.zeros(n, dtype=torch.float32, device="cuda:0")
+        side = torch.cuda.Stream()
+        other.eval_batch(0, n, d_time=t)
+        torch.cuda.synchronize()
+        want = t.cpu().numpy()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            plan.set_incremental(True)
+            other.eval_batch(0, n, d_time=t, stream=side.cuda_stream)
+        assert plan.best_plan().index == plan.best_plan().index == Oracle(prob).best().index
+        assert plan.last_scan()[0] == 0  # the second call found the first one's minima
+        for _ in range(3):
+            t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(t.cpu().numpy(), want)
+    finally:
+        plan.destroy()
+        other.destroy()
+
+
 def refused_queries():
     """(in a process of its own, see below)"""
     import ctypes
     from tests.abi_example import build
     refusal = ctypes.CDLL(build.build_refusal(force=False), ctypes.RTLD_GLOBAL)
     refusal.refuse_from.argtypes = [ctypes.c_size_t]
-    from paper_2504_17096_amd.binding import Plan
+    from paper_2504_17096_amd.binding import SAILOR_ENOMEM, Plan, SailorError
     prob = crowded_problem()
     orc, plan = Oracle(prob), Plan(prob)
     refusal.refuse_from(4 << 20)  # the first buffers have 2 MiB, the larger ones 106
@@ -91,6 +120,18 @@ def refused_queries():
     refusal.refuse_from((1 << 64) - 1)  # there is memory again
     check_top(plan.topk(128), orc.topk(128, n_threads=4))
     assert plan.last_counts()[0] > 1 << 16
+    plan.destroy()
+    plan = Plan(prob)
+    refusal.refuse_from(50_000)  # 9 pieces of 6 400 bytes: nothing is kept without memory for them, and no error is left
+    try:
+        plan.set_incremental(True)
+        raise AssertionError("not refused")
+    except SailorError as e:
+        assert e.status == SAILOR_ENOMEM
+    assert plan.best_plan().index == plan.best_plan().index == orc.best().index
+    refusal.refuse_from((1 << 64) - 1)
+    plan.set_incremental(True)
+    assert plan.best_plan().index == plan.best_plan().index == orc.best().index and plan.last_scan()[0] == 0
     plan.destroy()
     print("refused_queries: OK")
 
