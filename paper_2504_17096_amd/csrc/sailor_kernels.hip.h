@@ -1485,7 +1485,8 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     if (MODE == MODE_SCAN && live && t < 64) {  // the waves' minima are keys of as many candidates
       const uint32_t m = __float_as_uint(t < (int)(blockDim.x >> 6) ? red[0][t] : kPosInf);
       if (m < 0x7f800000u)
-        atomicMin(&a.counters[CNT_COUNT + (blockIdx.x * (blockDim.x >> 6) + (uint32_t)t) % kKeySlots], m);
+        // (one wave alone reaches every slot: with a degree left, the others of each workgroup often have nothing)
+        atomicMin(&a.counters[CNT_COUNT + (blockIdx.x + (uint32_t)t * (kKeySlots / (blockDim.x >> 6))) % kKeySlots], m);
       // (by all workgroups this would cost more than it prunes: they would wait for one another)
       if (GUIDED && blockIdx.x % 4u == 0u) {
         const uint32_t at = kth_of_slots(a.counters + CNT_COUNT, a.kth);

@@ -1027,3 +1027,36 @@ def test_more_ties_than_the_first_survivor_buffers_hold(torch_cuda, objective):
                 assert plan.last_counts()[0] > 1 << 16
         finally:
             plan.destroy()
+
+
+@pytest.mark.parametrize("k", [65, 128])
+def test_one_degree_left_to_a_budget_fills_the_slots_of_the_kth_key(torch_cuda, k):
+    # 416 pieces of four waves each; the batch leaves one data-parallel degree of eight, so 60 plans of a piece's
+    # lane space, all of them the first wave's.  Whatever wave they lie in, 416 pieces name 256 keys, of which the
+    # k-th bounds what is kept: some thousands at most, of 120 000 valid plans.  (64 of the slots were within reach.)
+    rng = np.random.default_rng(31)
+    G, Z, L, mb = 3, 4, 12, (1, 2, 4, 8, 16)
+    splits = {p: [np.diff([0, *sorted(rng.choice(np.arange(1, L), p - 1, replace=False)), L]).tolist() for _ in range(8)]
+              for p in (2, 3, 4, 6)}
+    bw = rng.uniform(0.5e9, 2e9, (Z, Z))
+    np.fill_diagonal(bw, rng.uniform(0.8e10, 1.2e10, Z))
+    prob = make_problem(
+        n_layers=L, n_types=G, n_zones=Z, mb_list=mb, tp_list=(1, 2), dp_list=(7, 8, 9, 11, 13, 17, 19, 23),
+        pp_list=[2, 3, 4, 6], partitions=splits, global_batch=128, max_segments=2,
+        t_fwd=rng.uniform(0.5e-3, 3e-3, (G, 5, 2, 1)), t_bwd=rng.uniform(1e-3, 5e-3, (G, 5, 2, 1)),
+        p2p=rng.integers(1_000_000, 9_000_000, 5).astype(np.uint64), cap=1 << 40, price=rng.uniform(0.5, 4.0, G),
+        avail=10_000, bw=bw)
+    orc, plan = Oracle(prob), _plan(prob)
+    try:
+        t, c, _, mask = orc.eval_batch(n_threads=THREADS)
+        ok = mask == 0
+        assert ok.sum() > 100_000
+        for objective in (MAX_THROUGHPUT, MIN_COST):
+            # a bound that all plans meet
+            bound = 2.0 * float(c[ok].max()) if objective == MAX_THROUGHPUT else 0.5 / float(t[ok].max())
+            check_topk(plan.topk(k, objective=objective, bound=bound), orc.topk(k, objective, bound=bound, n_threads=THREADS),
+                       objective, orc, bound)
+            assert plan.last_scan()[1] == 416
+            assert k <= plan.last_counts()[0] < ok.sum() // 8
+    finally:
+        plan.destroy()
