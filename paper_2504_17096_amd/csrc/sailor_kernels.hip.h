@@ -1285,10 +1285,11 @@ __device__ __forceinline__ bool unit_test(const DevPlan &pl, const ScanArgs &a, 
 // One workgroup per unit: stage the unit's segment records in LDS, then every lane walks
 // its (mb, dp, pool 1) triple over the unit's outer pool digits.  Everything the staging
 // needs comes from the unit record and tables that do not depend on one another, so all of
-// its global loads are in flight together and one barrier ends it.
+// its global loads are in flight together and one barrier ends it.  may_wait: for the running limit, if there is
+// none yet (GUIDED) and the unit has a degree that could matter.
 template <int MODE, int OBJ, bool HASB, bool MIXED, bool GUIDED>
 __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, const AvailArg<MODE, MIXED> &avail,
-                                          uint32_t uidx, int sub, uint32_t n_sub, float tau, uint4 *lds_raw) {
+                                          uint32_t uidx, int sub, uint32_t n_sub, float tau, bool may_wait, uint4 *lds_raw) {
   const UnitRec u = pl.units[uidx];
   const bool fresh = kAvailRides<MODE, MIXED> && a.fresh != 0;
   const bool live = MODE != MODE_COLLECT && a.rows_key != nullptr;
@@ -1309,10 +1310,11 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     const float con = HASB && have ? a.rows_con[(size_t)uidx * 2 * pl.DP + d] : 0.f;
     const float key = a.rows_key && have ? a.rows_key[(size_t)uidx * 2 * pl.DP + d] : 0.f;
     const uint64_t replicas = have ? (uint64_t)(uint32_t)pl.vals[d] : 0u;
+    const bool meets = have && (!HASB || con <= a.lim_l), fits = replicas * (uint64_t)max(w0, max(w1, w2)) <= a.most;
     if (live) {
       if (threadIdx.x < 64) {
         uint32_t seen = running_limit(a);
-        if (GUIDED && n_sub == 1 && a.wait_ticks != 0 && !(__uint_as_float(seen) < kPosInf)) {
+        if (GUIDED && may_wait && wave_any(meets && fits) && !(__uint_as_float(seen) < kPosInf)) {
           const unsigned long long until = wall_clock64() + a.wait_ticks;
           do {
             __builtin_amdgcn_s_sleep(12);
@@ -1329,9 +1331,8 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
       __syncthreads();
       key_limit = __uint_as_float(s_seen) * a.near_band;  // (nothing above it matters to the query)
     }
-    const uint64_t w = (uint64_t)max(w0, max(w1, w2));
-    const bool meets = have && (!HASB || con <= a.lim_l), near = have && key <= key_limit;
-    fixed = (uint32_t)__builtin_amdgcn_ballot_w64(meets && (near || MODE != MODE_COLLECT) && replicas * w <= a.most);
+    const bool near = have && key <= key_limit;
+    fixed = (uint32_t)__builtin_amdgcn_ballot_w64(meets && (near || MODE != MODE_COLLECT) && fits);
     degrees = fixed & (uint32_t)__builtin_amdgcn_ballot_w64(near);
     counts = wave_any(meets) && (MODE != MODE_BEST || wave_any(near));
   }
@@ -1551,7 +1552,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
   }
   if (MODE != MODE_COLLECT && !GUIDED) {
     const uint32_t n_sub = MODE == MODE_BEST && a.direct ? a.n_sub : 1u, e = blockIdx.x / n_sub;
-    unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, MODE == MODE_BEST && a.direct ? a.ulist[e] : e, (int)(blockIdx.x % n_sub), n_sub, kPosInf, lds_raw);
+    unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, MODE == MODE_BEST && a.direct ? a.ulist[e] : e, (int)(blockIdx.x % n_sub), n_sub, kPosInf, false, lds_raw);
   } else if (MODE != MODE_COLLECT) {
     const uint32_t n_shared = a.n_seeds;
     const bool shared = blockIdx.x < n_shared * a.n_sub;
@@ -1559,9 +1560,11 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
     const uint32_t first = shared ? blockIdx.x / n_sub : blockIdx.x - n_shared * (a.n_sub - 1u);  // in the order
     const uint32_t step = gridDim.x - a.fresh - n_shared * a.n_sub, n = (uint32_t)pl.n_units;  // workgroups behind the shared units'
     uint32_t hits = 1;
+    bool may_wait = !shared && a.wait_ticks != 0;  // (once: what the shared units find is there by then, or they found nothing)
     for (bool more = !shared && first + step < n; hits != 0;) {  // uniform
       const uint32_t e = first + (uint32_t)__builtin_ctz(hits) * step;
-      unit_work<MODE, OBJ, HASB, MIXED, true>(pl, a, avail, a.ulist ? a.ulist[e] : e, (int)sub, n_sub, kPosInf, lds_raw);
+      unit_work<MODE, OBJ, HASB, MIXED, true>(pl, a, avail, a.ulist ? a.ulist[e] : e, (int)sub, n_sub, kPosInf, may_wait, lds_raw);
+      may_wait = false;
       hits &= hits - 1;
       if (!more && hits == 0) break;
       __syncthreads();  // the staging area is reused
@@ -1593,7 +1596,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
       }
       for (; hits != 0; hits &= hits - 1) {  // uniform
         const uint32_t at = e + (uint32_t)__builtin_ctzll(hits) * per_round;
-        unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, a.ulist ? a.ulist[at] : at, (int)(blockIdx.x % a.n_sub), a.n_sub, tau, lds_raw);
+        unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, a.ulist ? a.ulist[at] : at, (int)(blockIdx.x % a.n_sub), a.n_sub, tau, false, lds_raw);
         __syncthreads();  // the staging area is reused
       }
     }

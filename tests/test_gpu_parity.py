@@ -1060,3 +1060,28 @@ def test_one_degree_left_to_a_budget_fills_the_slots_of_the_kth_key(torch_cuda, 
             assert k <= plan.last_counts()[0] < ok.sum() // 8
     finally:
         plan.destroy()
+
+
+@pytest.mark.parametrize("objective", [MAX_THROUGHPUT, MIN_COST])
+def test_a_guided_scan_that_finds_nothing_waits_once(torch_cuda, objective):
+    # 9.2e8 plans; what is available is of a type that holds no stage, which no bound of a piece knows.  A
+    # workgroup takes eight pieces, and eight waits of 8 us would be 64 us.
+    from dataclasses import replace
+    prob = W.config4()
+    reserved = prob.mem_reserved.copy()
+    reserved[-1] = prob.mem_capacity[-1]
+    prob = replace(prob, mem_reserved=reserved).with_per_segment_tp(True)
+    avail = prob.avail * (np.arange(prob.n_types) == prob.n_types - 1)
+    plan = _plan(prob)
+    try:
+        assert plan.best_plan(objective=objective) is not None
+        plan.set_avail(avail)
+        plan.set_timing(1)
+        times = []
+        for _ in range(12):
+            assert plan.topk(64, objective=objective) == []
+            times.append(plan.last_timing()[1])
+        assert plan.best_plan(objective=objective) is None
+        assert min(times) < 0.064, times
+    finally:
+        plan.destroy()
