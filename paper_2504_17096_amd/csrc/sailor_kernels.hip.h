@@ -1009,6 +1009,11 @@ __device__ __forceinline__ uint32_t kth_of_slots(const uint32_t *slots, uint32_t
   return at | ((1u << kCoarse) - 1u);
 }
 
+// The slot of a workgroup's wave: where those of the first waves would come round to the same ones, they move on by one.
+__device__ __forceinline__ uint32_t key_slot(uint32_t workgroup, uint32_t waves, uint32_t wave) {
+  return (workgroup * waves + workgroup * (waves & (0u - waves)) / kKeySlots + wave) % kKeySlots;
+}
+
 // What a launch knows of the result while it runs.  BEST: the smallest strict key so far.  SCAN with kth: a
 // key that at least kth candidates do not exceed.  Keys go to slots, each candidate's to one, and as every
 // slot keeps its smallest, kth slots that hold a key up to some value are as many candidates up to it.
@@ -1486,8 +1491,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     if (MODE == MODE_SCAN && live && t < 64) {  // the waves' minima are keys of as many candidates
       const uint32_t m = __float_as_uint(t < (int)(blockDim.x >> 6) ? red[0][t] : kPosInf);
       if (m < 0x7f800000u)
-        // (one wave alone reaches every slot: with a degree left, the others of each workgroup often have nothing)
-        atomicMin(&a.counters[CNT_COUNT + (blockIdx.x + (uint32_t)t * (kKeySlots / (blockDim.x >> 6))) % kKeySlots], m);
+        // (One wave alone reaches every slot: with a degree left, the others of each workgroup often have nothing.  And
+        // a workgroup's waves lie side by side, in one trip to memory: 64 best of 9.2e8 plans 79 us if they do not, 74.)
+        atomicMin(&a.counters[CNT_COUNT + key_slot(blockIdx.x, blockDim.x >> 6, (uint32_t)t)], m);
       // (by all workgroups this would cost more than it prunes: they would wait for one another)
       if (GUIDED && blockIdx.x % 4u == 0u) {
         const uint32_t at = kth_of_slots(a.counters + CNT_COUNT, a.kth);
