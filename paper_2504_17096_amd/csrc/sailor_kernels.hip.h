@@ -745,14 +745,15 @@ __device__ __forceinline__ void survivor(const DevPlan &pl, const ScanArgs &a, c
 }
 
 // (the workgroup, behind its walk of the unit)  A wave that found the list full has left its place empty
-// there: the list ends before it.
-__device__ __forceinline__ void keep_flush(const DevPlan &pl, const ScanArgs &a, const UnitRec &u, Kept &kept) {
+// there: the list ends before it.  drop (the first wave's word counts): none of it matters any more.
+__device__ __forceinline__ void keep_flush(const DevPlan &pl, const ScanArgs &a, const UnitRec &u, Kept &kept, bool drop) {
   __syncthreads();
   uint32_t n = kept.n;
   if (n == 0) return;  // uniform
   if (n > kKeptHere) n = kept.full;
-  if (threadIdx.x == 0) kept.base = atomicAdd(&a.counters[CNT_SURV], n);
+  if (threadIdx.x == 0) kept.base = drop ? ~0u : atomicAdd(&a.counters[CNT_SURV], n);
   __syncthreads();
+  if (kept.base == ~0u) return;  // uniform
   for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
     const uint32_t key = kept.key[i], idx = (uint32_t)kept.idx[i];
     if (!(key >> 31)) atomicMin(&a.counters[kKeptSlots + (idx * 0x9E3779B1u >> 24)], key);
@@ -1468,7 +1469,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
   };
   walk(std::integral_constant<int, MODE>());
-  if (MODE == MODE_COLLECT && !a.count_only) keep_flush(pl, a, u, kept);
+  if (MODE == MODE_COLLECT && !a.count_only) keep_flush(pl, a, u, kept, false);
 
   if (MODE != MODE_COLLECT) {
     const bool folds = !(MODE == MODE_SCAN && live);  // (a scan for the kth smallest key has no use for the smallest one)
@@ -1508,8 +1509,11 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     __syncthreads();
     tau = __uint_as_float(s_min);
     if (tau >= 0.0f) {  // uniform
+      // (What comes near is walked at about the same time: a second look at the limit, on its way during the walk,
+      // leaves a query some tens of candidates, which one workgroup re-evaluates, where it had 70 to 140.)
+      const uint32_t now = t < 64 ? smallest_key(a, live) : 0u;
       walk(std::integral_constant<int, MODE_COLLECT>());
-      keep_flush(pl, a, u, kept);
+      keep_flush(pl, a, u, kept, ml > __uint_as_float(now) * a.near_band);
     }
   }
 }
