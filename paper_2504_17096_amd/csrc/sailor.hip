@@ -884,8 +884,8 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   }
   sa.direct = 0;
   sa.ulist = nullptr;
-  // A scan for the k smallest keys leaves out what a running upper bound of the k-th rules out, and ends
-  // with that bound as the threshold.  (Not for minima that are kept, nor for a k that is a large share of
+  // A scan for the k smallest keys ends with an upper bound of the k-th as the threshold; a guided one leaves out
+  // what that rules out while it runs.  (Not for minima that are kept, nor for a k that is a large share of
   // the bound's slots: with 256 of them it lies about 1.4 k keys up for k = 128.)
   const bool by_slots = !best && first_try && !pl->incremental && k <= kKthLive;
   sa.band = sa.near_band = 1.0f + 3.0f * kEvalEps;

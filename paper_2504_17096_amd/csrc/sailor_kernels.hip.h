@@ -1070,16 +1070,16 @@ struct Walk {
 // largest data-parallel degrees down, for the cheapest from the smallest up: what is small early prunes
 // most (cheapest of 1.9e7 plans with a TP degree per segment: 59 us down, 53 up).
 //
-// live: what other workgroups have found counts as well.  The first wave asks for the running limit
-// once per round, and takes the answer to the question before, so that no round waits for it; a degree
-// whose bound (s_rows) lies above it falls without a record read.
+// live: a degree whose bound (s_rows) lies above the limit falls without a record read.  follows: what other
+// workgroups have found counts as well.  The first wave asks for the running limit once per round, and takes
+// the answer to the question before, so that no round waits for it.
 template <int S, int MODE, int OBJ, bool HASB, bool MIXED>
 __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, const UnitRec &u,
                                           const float4 *rec_lo, const float4 *rec_hi,
                                           const uint32_t *rbits, const float4 *pair,
                                           const uint32_t *q13, const uint64_t *isect, int w0,
                                           int w1, int w2, float tau, const Walk &wk,
-                                          const float *s_rows, bool live,
+                                          const float *s_rows, bool live, bool follows,
                                           uint32_t *s_min, Kept &kept, float &ms, float &ml) {
   // the chunks of the lane space are dealt round-robin to the waves of the workgroups that share the unit
   const int ZG = pl.ZG, G = pl.GX, MB = pl.MB, DP = pl.DP, Z = pl.Z;
@@ -1092,12 +1092,12 @@ __device__ __forceinline__ void unit_body(const DevPlan &pl, const ScanArgs &a, 
   // the limit in force: the smallest strict key so far, COLLECT the threshold
   uint32_t asked = 0x7f800000u;
   auto ask = [&]() {  // (in front of a loop without loads from memory: they would wait for it)
-    if (MODE != MODE_COLLECT && live && threadIdx.x < 64)
+    if (MODE != MODE_COLLECT && follows && threadIdx.x < 64)
       asked = running_limit(a);
   };
   auto limit = [&]() {
     if (MODE == MODE_COLLECT) return tau;
-    if (live && threadIdx.x == 0) atomicMin(s_min, __float_as_uint(__uint_as_float(asked) * a.near_band));
+    if (follows && threadIdx.x == 0) atomicMin(s_min, __float_as_uint(__uint_as_float(asked) * a.near_band));
     return __uint_as_float(__hip_atomic_load(s_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
   };
   // can plans of this degree still matter?
@@ -1299,6 +1299,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   const UnitRec u = pl.units[uidx];
   const bool fresh = kAvailRides<MODE, MIXED> && a.fresh != 0;
   const bool live = MODE != MODE_COLLECT && a.rows_key != nullptr;
+  const bool follows = live && (MODE == MODE_BEST || GUIDED);  // a k-th key has a running limit where seeds find it only
   const int n0 = u.n[0], n1 = u.n[1], n2 = u.n[2];
   const int k0 = u.tp[0], k1 = u.tp[1], k2 = u.tp[2];            // tp index of each segment
   const int tv0 = pl.tpv[k0], tv1 = pl.tpv[k1], tv2 = pl.tpv[k2];
@@ -1318,7 +1319,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     const uint64_t replicas = have ? (uint64_t)(uint32_t)pl.vals[d] : 0u;
     const bool meets = have && (!HASB || con <= a.lim_l), fits = replicas * (uint64_t)max(w0, max(w1, w2)) <= a.most;
     if (live) {
-      if (threadIdx.x < 64) {
+      if (follows && threadIdx.x < 64) {
         uint32_t seen = running_limit(a);
         if (GUIDED && may_wait && wave_any(meets && fits) && !(__uint_as_float(seen) < kPosInf)) {
           const unsigned long long until = wall_clock64() + a.wait_ticks;
@@ -1334,8 +1335,10 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
         if (threadIdx.x == 0) s_seen = seen;
       }
       if ((int)threadIdx.x < pl.DP) s_rows[threadIdx.x] = key;
-      __syncthreads();
-      key_limit = __uint_as_float(s_seen) * a.near_band;  // (nothing above it matters to the query)
+      if (follows) {
+        __syncthreads();
+        key_limit = __uint_as_float(s_seen) * a.near_band;  // (nothing above it matters to the query)
+      }
     }
     const bool near = have && key <= key_limit;
     fixed = (uint32_t)__builtin_amdgcn_ballot_w64(meets && (near || MODE != MODE_COLLECT) && fits);
@@ -1464,9 +1467,9 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
   float ms = kPosInf, ml = kPosInf;
   auto walk = [&](auto mode) {
     constexpr int M = decltype(mode)::value;
-    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
-    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
-    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, &s_min, kept, ms, ml);
+    if (S == 1) unit_body<1, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, follows, &s_min, kept, ms, ml);
+    else if (S == 2) unit_body<2, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, follows, &s_min, kept, ms, ml);
+    else unit_body<3, M, OBJ, HASB, MIXED>(pl, a, u, rec_lo, rec_hi, rbits, pair, q13, isect, w0, w1, w2, tau, wk, s_rows, live, follows, &s_min, kept, ms, ml);
   };
   walk(std::integral_constant<int, MODE>());
   if (MODE == MODE_COLLECT && !a.count_only) keep_flush(pl, a, u, kept, false);
