@@ -32,14 +32,14 @@ constexpr uint64_t kUnitTargetMin = 4096, kUnitTargetMax = 65536, kUnitsWanted =
 // workgroups that share one unit in the collect pass, and the units it visits per round (64 best of 9.2e8 plans:
 // 14.5 us with 8 and 256, where two units fall to one group more often; 12.7 with these)
 constexpr uint32_t kCollectSub = 4, kCollectUnits = 512;
-constexpr size_t kChipWaves = 8192;      // 256 compute units of 32 waves
 // A running k-th key takes longer to be found than a running minimum and rules out less: spaces up to twice the
-// chip's waves are scanned unguided for it (k = 26 of 3 600 units of four waves with pairs of types 74 -> 64 us, k = 53
+// chip's waves (8 192) are scanned unguided for it (k = 26 of 3 600 units of four waves with pairs of types 74 -> 64 us, k = 53
 // of 5 580 units of two waves, 706 of them within a budget, 58 -> 38; cheapest of 2 806 units of three waves 40, unguided 99)
-constexpr size_t kGuidedKthWaves = 2 * kChipWaves;
+constexpr size_t kCuWaves = 32;
+constexpr size_t kGuidedKthChips = 2;
 // Pairs of types make a unit long enough that the best plan's scan is guided wherever there is a unit to wait
 // (fastest of 2 295 units of three waves 114 us as they come and 37 guided, of 1 464 86 and 37, of 324 39 and 27).
-constexpr size_t kGuidedMixedWaves = 512;
+constexpr size_t kGuidedMixedWavesPerCu = 2;
 // What the first units of a scan take from launch to a result, at 100 MHz.  (Where a constraint leaves the first units
 // nothing, the wait is for nothing: cheapest of 7 296 units at 0.87 of the largest throughput 41 us with 8 us, 37 with 5;
 // those that find something have by then.  With 3 us that query takes 34, but pairs of types 68 instead of 31.)
@@ -197,6 +197,7 @@ struct sailor_plan {
   std::vector<UnitRec> units;
   std::vector<EvalBlock> eblocks;  // range evaluation: a block's units (laid out on the device)
   uint64_t n_eunits = 0;
+  size_t cus = 0;                  // compute units of the device
   uint32_t n_groups = 0;           // units of one shape and tp per segment are a group: see k_group_bounds
   EvalUnit *d_eunits = nullptr;    // ascending idx_lo
   size_t eval_lds_bytes = 0;
@@ -655,7 +656,7 @@ void launch_units(sailor_plan *pl, sailor_objective obj, int has_bound, const Sc
                   hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const unsigned n_units = (unsigned)pl->units.size();
   const dim3 grid((a.direct               ? a.n_list_host * a.n_sub
-                   : MODE != MODE_COLLECT ? (a.n_seeds ? a.n_seeds * a.n_sub + scan_workgroups(n_units - a.n_seeds, pl->unit_threads / 64) : n_units)
+                   : MODE != MODE_COLLECT ? (a.n_seeds ? a.n_seeds * a.n_sub + scan_workgroups(n_units - a.n_seeds, pl->unit_threads / 64, (uint32_t)(pl->cus * kCuWaves)) : n_units)
                                           : std::min(n_units, kCollectUnits) * a.n_sub) + a.fresh),
       block(pl->unit_threads);
   const size_t lds = pl->lds_bytes;
@@ -828,7 +829,7 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
   }
   // units that do not fit on the chip at once: the first of the order guide the others (scan_workgroups)
   auto guide = [&]() {
-    if (!sa.rows_key || (size_t)n_units * (pl->unit_threads / 64) <= (!best ? kGuidedKthWaves : pl->dev.mixed ? kGuidedMixedWaves : kChipWaves)) return;
+    if (!sa.rows_key || n_units <= (best ? kBestSeeds : kKthSeeds) || (size_t)n_units * (pl->unit_threads / 64) <= pl->cus * (!best ? kGuidedKthChips * kCuWaves : pl->dev.mixed ? kGuidedMixedWavesPerCu : kCuWaves)) return;
     sa.n_seeds = best ? kBestSeeds : kKthSeeds;
     sa.n_sub = best ? kBestSeedSub : kKthSeedSub;
     sa.wait_ticks = best ? kBestSeedTicks : kKthSeedTicks;
@@ -1124,6 +1125,9 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   } while (0)
 
   CREATE_TRY(hipGetDevice(&pl->device));
+  int cus = 0;
+  CREATE_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device));
+  pl->cus = (size_t)std::max(1, cus);
   TableSlab slab;
   const int G = d.G, GX = d.GX, Z = d.Z, ZG = d.ZG, ZGr = d.ZGr, MB = d.MB, TP = d.TP, DP = d.DP,
             L = p->n_layers;

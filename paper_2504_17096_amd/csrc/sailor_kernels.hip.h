@@ -18,6 +18,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "sailor_dev.h"
@@ -1530,11 +1531,13 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
 // fastest of 9.2e8 plans with a TP degree per segment 86 -> 28 us, fastest of 1.0e8 28 -> 18, cheapest of
 // 1.1e9 with pairs of types 167 -> 19.  Units that do fit at once gain nothing by waiting (1 632 of them: 19
 // us, and 15.5 as they come), those with pairs of types apart, which are longer.
-constexpr uint32_t kScanWaves = 6144, kScanPerWg = 32, kBestSeeds = 16, kBestSeedSub = 16, kKthSeeds = 64, kKthSeedSub = 8;
-__host__ __device__ inline uint32_t scan_workgroups(uint32_t n_units, uint32_t waves) {
-  uint32_t per = (n_units * waves + kScanWaves - 1) / kScanWaves;
-  per = per < kScanPerWg ? per : kScanPerWg;
-  return per ? (n_units + per - 1) / per : 0u;
+// As many each as leave no more than the chip's waves.  (Of 1.1e9 plans with pairs of types: 64 fastest where one pool
+// in five is available, which the limit rules out little of, 135 us with 6 144 waves, 121 with 8 192 and 117 with
+// 12 288; the cheapest, which it rules out nearly all of, 30, 31 and 34.)
+constexpr uint32_t kScanPerWg = 32, kBestSeeds = 16, kBestSeedSub = 16, kKthSeeds = 64, kKthSeedSub = 8;
+inline uint32_t scan_workgroups(uint32_t n_units, uint32_t waves, uint32_t chip_waves) {
+  const uint64_t per = std::min<uint64_t>(((uint64_t)n_units * waves + chip_waves - 1) / chip_waves, kScanPerWg);
+  return (uint32_t)((n_units + per - 1) / per);
 }
 
 // SCAN: a workgroup for every unit or every few.  COLLECT: n_sub workgroups share a unit; the grid strides over a list of
