@@ -218,6 +218,9 @@ struct sailor_plan {
   float *rows = nullptr;  // [unit][2][DP] bounds by degree, of the time and of the cost (k_group_bounds)
   // the units in ascending order of either bound (device), and the sorted bounds (host)
   uint32_t *order_time = nullptr, *order_cost = nullptr;
+  uint32_t *order_work = nullptr;  // the longest first, once a scan without a limit has had it made
+  uint8_t *work_bucket = nullptr;
+  bool work_ordered = false;
   std::vector<float> lb_time_sorted, lb_cost_sorted;
   // the last query whose direct pass kept too many candidates (it is not tried again)
   bool direct_declined = false;
@@ -895,7 +898,19 @@ sailor_status run_selection_impl(sailor_plan *pl, sailor_objective obj,
     guide();
   }
   const float *const rows_key = sa.rows_key;
-  if (!by_slots) sa.rows_key = nullptr;
+  if (!by_slots) {
+    // Nothing known of the result shortens this scan (k above kKthLive, minima that are kept, second tries): where the
+    // units do not fit on the chip at once, the longest go first.
+    sa.rows_key = nullptr;
+    if ((size_t)n_units * (pl->unit_threads / 64) > pl->cus * kCuWaves) {
+      if (!pl->work_ordered) {
+        k_unit_work<<<(unsigned)std::min<size_t>(pl->cus * 8, (n_units + 3) / 4), 256, 0, st>>>(pl->dev, pl->work_bucket);
+        k_work_order<<<1, 1024, 0, st>>>(pl->work_bucket, n_units, pl->order_work);
+        pl->work_ordered = true;  // (whatever the availability becomes)
+      }
+      sa.ulist = pl->order_work;
+    }
+  }
   launch_units<MODE_SCAN>(pl, obj, has_bound, sa, st, t_scan ? pl->ev[3] : nullptr,
                           t_scan ? pl->ev[1] : nullptr);
   sa.rows_key = rows_key;
@@ -1228,6 +1243,8 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&pl->umin_s, 2 * unit_cap);
   slab.table(&pl->counters, (size_t)2 * kSetWords);
   slab.table(&pl->ulist, unit_cap);
+  slab.table(&pl->order_work, unit_cap);
+  slab.table(&pl->work_bucket, unit_cap);
   slab.zeroed(&pl->unit_gen, unit_cap);
   slab.zeroed(&pl->unit_seq, unit_cap);
   pl->ubits_stride = (uint32_t)(unit_lds_records(ZG, MB) + (size_t)ZG);

@@ -1041,6 +1041,69 @@ __global__ __launch_bounds__(256) void k_unit_rows(const UnitRec *units, const f
     out[i] = rows[(size_t)units[i / width].group * width + i % width];
 }
 
+// How long each unit takes, roughly, where nothing rules out the plans that are valid under the present
+// availability; as a bucket, an eighth of an octave wide, the longest first.  A wave a unit: per segment and degree
+// how many pools hold the segment, with any microbatch size; of the lane space that leaves so many chunks alive, each
+// of which goes through the pools of the next segments, at four times the price where those hold theirs.  (Bound by
+// trips to memory; with the kernel behind it 31 us for 16 037 units and 17 for 7 797, once a plan.  129 cheapest of the
+// latter's 1.1e9 plans 335 us in the order of the units' bounds, 243 in this one, 257 in that of a timed pass over
+// the space at creation, which took 254.)
+constexpr int kWorkBuckets = 256;
+
+__global__ __launch_bounds__(256) void k_unit_work(DevPlan pl, uint8_t *bucket) {
+  const int lane = threadIdx.x & 63, ZG = pl.ZG, G = pl.GX, MB = pl.MB;
+  const float most_chunks = (float)((MB * ZG + 63) / 64);
+  for (uint32_t uidx = blockIdx.x * 4u + (threadIdx.x >> 6); uidx < (uint32_t)pl.n_units; uidx += gridDim.x * 4u) {  // uniform
+    const UnitRec &u = pl.units[uidx];
+    float holds[3] = {0.f, 0.f, 0.f};  // of degree `lane`
+#pragma unroll
+    for (int seg = 0; seg < 3; ++seg) {
+      if (seg >= u.s) continue;
+      const int k = at3(u.tp, seg), w = at3(u.n, seg) * pl.vals[pl.DP + k];
+      const uint32_t sl = (u.shape * (uint32_t)pl.TP + (uint32_t)k) * 3u + (uint32_t)seg;
+      const int from = seg == 1 ? (int)u.o_lo : 0, to = seg == 1 ? (int)u.o_lo + (int)u.o_cnt : ZG;
+      for (int p0 = from; p0 < to; p0 += 64) {
+        const int p = p0 + lane;
+        uint32_t bits = 0;
+        if (p < to) {
+          const uint32_t g = (uint32_t)p - fast_div((uint32_t)p, pl.mg_g) * (uint32_t)G;
+          for (int mb = 0; mb < MB; ++mb) bits |= pl.memok[(sl * (uint32_t)G + g) * (uint32_t)MB + (uint32_t)mb] & pl.divis[mb];
+          bits &= pl.qw[w * ZG + p];
+          if ((pl.h1m[p] >> k) & 1u) bits = 0;
+        }
+        for (int d = 0; d < pl.DP; ++d) {
+          const float n = (float)__popcll(__builtin_amdgcn_ballot_w64((bits >> d) & 1u));
+          if (lane == d) holds[seg] += n;
+        }
+      }
+    }
+    float work = fminf(most_chunks, holds[0]);
+    if (u.s == 2) work *= holds[1] > 0.f ? (float)u.o_cnt + 4.f * holds[1] : 0.f;
+    if (u.s == 3) work *= holds[2] > 0.f ? holds[1] * ((float)ZG + 4.f * holds[2]) : 0.f;
+    for (int off = 32; off >= 1; off >>= 1) work += __shfl_xor(work, off);
+    const int at = (int)(__float_as_uint(1.f + work) >> 20) - (127 << 3);
+    if (lane == 0) bucket[uidx] = (uint8_t)(kWorkBuckets - 1 - min(at, kWorkBuckets - 1));
+  }
+}
+
+// The units by bucket.  One workgroup.
+__global__ __launch_bounds__(1024) void k_work_order(const uint8_t *bucket, uint32_t n, uint32_t *order) {
+  __shared__ uint32_t s_at[kWorkBuckets];
+  const uint32_t t = threadIdx.x;
+  if (t < (uint32_t)kWorkBuckets) s_at[t] = 0;
+  __syncthreads();
+  for (uint32_t i = t; i < n; i += 1024) atomicAdd(&s_at[bucket[i]], 1u);
+  __syncthreads();
+  if (t < 64) {
+    uint32_t mine[kWorkBuckets / 64], sum = 0;
+    for (int j = 0; j < kWorkBuckets / 64; ++j) { mine[j] = s_at[t * (kWorkBuckets / 64) + (uint32_t)j]; sum += mine[j]; }
+    uint32_t at = wave_prefix_sum(sum) - sum;
+    for (int j = 0; j < kWorkBuckets / 64; ++j) { s_at[t * (kWorkBuckets / 64) + (uint32_t)j] = at; at += mine[j]; }
+  }
+  __syncthreads();
+  for (uint32_t i = t; i < n; i += 1024) order[atomicAdd(&s_at[bucket[i]], 1u)] = i;
+}
+
 // What a workgroup walks of its unit: the degrees listed in s_dp, and its share of the lane space's chunks and
 // of the innermost loop.
 struct Walk {
@@ -1568,7 +1631,7 @@ __global__ __launch_bounds__(kMaxUnitThreads) void k_units(DevPlan pl, ScanArgs 
   }
   if (MODE != MODE_COLLECT && !GUIDED) {
     const uint32_t n_sub = MODE == MODE_BEST && a.direct ? a.n_sub : 1u, e = blockIdx.x / n_sub;
-    unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, MODE == MODE_BEST && a.direct ? a.ulist[e] : e, (int)(blockIdx.x % n_sub), n_sub, kPosInf, false, lds_raw);
+    unit_work<MODE, OBJ, HASB, MIXED, false>(pl, a, avail, a.ulist ? a.ulist[e] : e, (int)(blockIdx.x % n_sub), n_sub, kPosInf, false, lds_raw);
   } else if (MODE != MODE_COLLECT) {
     const uint32_t n_shared = a.n_seeds;
     const bool shared = blockIdx.x < n_shared * a.n_sub;

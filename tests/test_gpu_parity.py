@@ -1096,3 +1096,38 @@ def test_a_guided_scan_that_finds_nothing_waits_once(torch_cuda, objective):
             plan.destroy()
     assert pieces[1] >= pieces[0] + 12
     assert took[1] - took[0] < (pieces[1] - pieces[0]) * 0.008, (pieces, took)
+
+
+@pytest.mark.parametrize("make, parts", [
+    (lambda: wide_problem(5), 40),   # 64 pools, 24 degrees; one and two segments
+    (lambda: W.tiny_problem(75, n_layers=3, n_types=4, n_zones=7, seg3_max_pp=3, partitions_per_pp=1).with_mixed_types(), 60),  # 70 pools
+])
+def test_scans_without_a_limit_take_the_longest_units_first(torch_cuda, make, parts):
+    # more units than fit on the chip at once, in an order of their own: every one is scanned, once.  k above
+    # what a running key is kept for, a k behind which nothing valid is left, and minima that are kept while the
+    # availability, by which they were ordered, changes.
+    from paper_2504_17096_amd.binding import set_scan_unit_parts
+    prob = make()
+    set_scan_unit_parts(parts)
+    try:
+        plan = _plan(prob)
+    finally:
+        set_scan_unit_parts(0)
+    try:
+        for avail in (np.minimum(prob.avail, 3), prob.avail):
+            plan.set_avail(avail)
+            orc = Oracle(prob.with_avail(avail))
+            t, c, _, mask = orc.eval_batch(n_threads=THREADS)
+            for objective in (MAX_THROUGHPUT, MIN_COST):
+                val = (c if objective == MAX_THROUGHPUT else 1.0 / t)[mask == 0]
+                for bound in (None, off_data(float(np.median(val)))):
+                    for k in (129, 4096) if bound is None else (129,):
+                        check_topk(plan.topk(k, objective=objective, bound=bound),
+                                   orc.topk(k, objective=objective, bound=bound, n_threads=THREADS), objective, orc, bound)
+                    assert plan.last_scan()[1] * 2 > 8192
+                want = orc.best(objective=objective, n_threads=THREADS)
+                for on in (True, True, False):
+                    plan.set_incremental(on)
+                    check_result(plan.best_plan(objective=objective), want, orc)
+    finally:
+        plan.destroy()
