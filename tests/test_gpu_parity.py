@@ -1131,3 +1131,54 @@ def test_scans_without_a_limit_take_the_longest_units_first(torch_cuda, make, pa
                     check_result(plan.best_plan(objective=objective), want, orc)
     finally:
         plan.destroy()
+
+
+def _many_small_units(n_zones, mixed, max_segments):
+    """More whole units of two waves than twice the chip's 8 192 waves, of few plans each: a TP degree per segment, and
+    many layer splits of one depth.  With two segments the lane space takes three rounds of a workgroup (eight
+    microbatch sizes, 24 degrees, two pools), with three it is less than a wave."""
+    rng = np.random.default_rng(100 + max_segments)
+    L, G, tp = 24, 2 if max_segments == 3 else 1, (1, 2, 4, 8)
+    P, n_splits = (8, 8) if max_segments == 3 else (12, 48)
+    mb, dp = ((1,), (1, 2)) if max_segments == 3 else (
+        (1, 2, 3, 4, 6, 8, 12, 24), (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16, 18, 20, 21, 24, 28, 30, 35, 36, 40, 42))
+    splits = set()
+    while len(splits) < n_splits:
+        splits.add(tuple(np.diff([0, *sorted(rng.choice(np.arange(1, L), P - 1, replace=False)), L]).tolist()))
+    bw = rng.uniform(0.5e9, 2e9, (n_zones, n_zones))
+    np.fill_diagonal(bw, rng.uniform(0.8e10, 1.2e10, n_zones))
+    prob = make_problem(
+        n_layers=L, n_types=G, n_zones=n_zones, mb_list=mb, tp_list=tp, dp_list=dp, pp_list=[P],
+        partitions={P: [list(s) for s in sorted(splits)]}, global_batch=24 * 5040, max_segments=max_segments,
+        seg3_max_pp=P, uniform_layers=False, t_fwd=rng.uniform(0.5e-3, 3e-3, (G, len(mb), 4, L)),
+        t_bwd=rng.uniform(1e-3, 5e-3, (G, len(mb), 4, L)), t_upd=rng.uniform(1e-4, 3e-4, (G, 4, L)),
+        act=rng.integers(10_000_000, 400_000_000, (len(mb), 4)).astype(np.uint64),
+        p2p=rng.integers(1_000_000, 9_000_000, len(mb)).astype(np.uint64), price=rng.uniform(0.5, 4.0, G),
+        avail=rng.integers(40, 120, (n_zones, G)) * (1 if max_segments == 3 else 8), bw=bw)
+    return prob.with_per_segment_tp(True).with_mixed_types(mixed)
+
+
+@pytest.mark.parametrize("n_zones, mixed, max_segments", [(2, False, 3), (2, True, 3), (2, False, 2)])
+def test_whole_units_guided_by_a_running_limit(torch_cuda, n_zones, mixed, max_segments):
+    # the first units of the order are shared by workgroups, which divide the rounds of the lane space first and then
+    # the innermost loop; the others have the degrees that a bound leaves only.  In the order of the availability at
+    # creation, of which the second table leaves little.
+    prob = _many_small_units(n_zones, mixed, max_segments)
+    plan = _plan(prob)
+    try:
+        for avail in (prob.avail, prob.avail * 2 // 5):
+            plan.set_avail(avail)
+            orc = Oracle(prob.with_avail(avail))
+            t, c, _, mask = orc.eval_batch(n_threads=THREADS)
+            assert (mask == 0).sum() > 1000
+            for objective in (MAX_THROUGHPUT, MIN_COST):
+                val = (c if objective == MAX_THROUGHPUT else 1.0 / t)[mask == 0]
+                for bound in (None, off_data(float(np.median(val)))):
+                    check_result(plan.best_plan(objective=objective, bound=bound),
+                                 orc.best(objective=objective, bound=bound, n_threads=THREADS), orc)
+                    for k in (1, 64, 128):
+                        check_topk(plan.topk(k, objective=objective, bound=bound),
+                                   orc.topk(k, objective=objective, bound=bound, n_threads=THREADS), objective, orc, bound)
+        assert plan.last_scan()[1] * 2 > 16384  # (two waves or more each, and none of them cut)
+    finally:
+        plan.destroy()
