@@ -136,8 +136,6 @@ struct DevPlan {
   uint64_t *isect;             // [ZG][2] bit q: pools p and q draw on a common real pool
   int n_bw_coef;               // 0: constant link bandwidth
   const double *bw_poly;       // [Z][Z][n_bw_coef] bandwidth over log2(message bytes)
-  uint64_t unused;             // (keeps what follows where it lies in the arguments' cache lines: 11 739 listed
-                               // plans 9.2 us without it, 9.0 with it)
   double *xsec;                // [MB][Z][Z] seconds of one activation transfer a -> b
   float *tsec_f;               // the same, rounded once
   float *egs_f;                // [Z][Z] egress both ways
@@ -151,7 +149,6 @@ struct DevPlan {
   // per-stage tables, one entry per stage of every partition row
   const int32_t *st_n;         // layers
   const int32_t *st_first;     // first layer
-  uint64_t unused_too;         // (for the same reason)
   // one record per stage, microbatch size and TP degree, of row_w words: compute seconds per
   // type [G], update seconds per type [G], bytes of weights, gradients and optimizer state of
   // the shard (as an integer), bytes of its gradient buffer
