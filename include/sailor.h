@@ -188,17 +188,18 @@ typedef struct {
 /* The planner's inputs (Sec. 4: job profile, quotas and current availability, prices; Sec. 4.1:
  * per-layer times and memory per GPU type, link bandwidths) become a plan object.
  * Build a plan: validate, copy the problem to the current HIP device, build the static
- * per-stage and per-segment tables there, and run three to four passes over the space that
- * decide how later scans are launched (which pieces of the space can never hold a valid plan,
- * how long the others take); results do not depend on that.  *out receives the plan.
- * (sailor_set_scan_unit_parts overrides how the pieces are cut.)
+ * per-stage and per-segment tables there, and work out, piece by piece of the space and from the
+ * GPU types alone, the smallest iteration time and cost at every data-parallel degree.  Pieces that
+ * can never hold a valid plan are dropped; later scans visit the others in the order of the smallest
+ * time that the availability given here leaves them.  Results do not depend on that order.  *out
+ * receives the plan.
  * Errors: SAILOR_EINVAL (see limits and field comments), SAILOR_ENOMEM, SAILOR_EDEVICE. */
 sailor_status sailor_plan_create(const sailor_problem *problem, sailor_plan **out);
 
-/* Tuning and testing, process-wide, for plans created afterwards: n = 0 (default) lets the
- * times measured at plan creation decide which pieces of the space are cut into parts for the
- * scan; n = 1..255 cuts every piece into n parts instead.  Results never depend on it.
- * SAILOR_EINVAL outside 0..255. */
+/* Testing, process-wide, for plans created afterwards: n = 2..255 cuts every piece of the space into
+ * n parts for the scan, which gives small problems as many pieces as large ones have; n = 0
+ * (default) and 1 leave the pieces whole.  Results never depend on it.  SAILOR_EINVAL outside
+ * 0..255. */
 sailor_status sailor_set_scan_unit_parts(int32_t n);
 
 /* Free everything the plan owns (host and device).  NULL is accepted. */
@@ -231,10 +232,10 @@ sailor_status sailor_plan_set_avail(sailor_plan *plan, const int32_t *avail);
  * changes nothing.
  * What it buys depends on the stream: the pieces whose validity changes are mostly the ones
  * that hold many valid plans, and those set the duration of a pass over the space, while a
- * pass that reuses minima can neither keep its candidates as it goes nor take the availability
- * along, and needs four more small kernels for that.  On the synthetic streams measured here a
- * re-plan takes 37 to 40 % longer with it on spaces of 10^7 to 10^8 plans and the same time on
- * 9 * 10^8. */
+ * pass that keeps minima can neither leave pieces out for what the call has found so far, nor keep
+ * its candidates as it goes, nor take the availability along, and needs four more small kernels for
+ * that.  On the synthetic streams measured here a re-plan takes 1.0 to 2.9 times as long with it
+ * on spaces of 10^7 to 10^8 plans, and 1.4 to 6 times on 10^9. */
 sailor_status sailor_plan_set_incremental(sailor_plan *plan, int32_t on);
 
 /* Pieces of the space the last successful sailor_best_plan / sailor_topk evaluated, and how

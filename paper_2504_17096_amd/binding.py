@@ -268,7 +268,7 @@ def _constraint(bound: Optional[float]):
 
 
 def set_scan_unit_parts(n: int) -> None:
-    """sailor_set_scan_unit_parts: 0 = cut scan pieces by measured time, n = into n parts each."""
+    """sailor_set_scan_unit_parts: n = cut every scan piece into n parts (tests), 0 = leave them whole."""
     rc = load_library().sailor_set_scan_unit_parts(n)
     if rc != SAILOR_OK:
         raise SailorError(rc, "sailor_set_scan_unit_parts")

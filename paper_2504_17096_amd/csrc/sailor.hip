@@ -1191,9 +1191,8 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
     shape_n.push_back((uint32_t)((sh.n[0] - 1) & 255) | (uint32_t)((sh.n[1] - 1) & 255) << 8 | (uint32_t)((sh.n[2] - 1) & 255) << 16);
   slab.input(&pl->direct_mem.shape_n, shape_n.data(), NS);
   slab.input(&d.blocks, pl->blocks.data(), pl->blocks.size());
-  // per-unit tables: one entry per unit as laid out (units dropped later leave room for the
-  // parts of units that are cut); sailor_set_scan_unit_parts(n) cuts every unit into n parts
-  // whatever the timing says and needs n times the room
+  // per-unit tables: one entry per unit as laid out, dropped ones included;
+  // sailor_set_scan_unit_parts(n) cuts every unit into n parts and needs n times the room
   const long forced_parts = g_forced_unit_parts.load(std::memory_order_relaxed);
   const size_t unit_cap = pl->units.size() * (size_t)std::max(1L, forced_parts);
   char *per_unit = nullptr;  // the tables that creation fills last, in one copy: records, bounds, orders
@@ -1239,7 +1238,7 @@ static sailor_status create_impl(const sailor_problem *p, sailor_plan **out, sai
   slab.table(&link_min, (size_t)2 * MB + 1);
   slab.table(&ga.rows, (size_t)pl->n_groups * 2 * DP);
   slab.table(&ga.sums, (size_t)pl->n_groups);
-  // selection scratch (umin_l lies behind umin_s: creation reads both back in one copy)
+  // selection scratch
   slab.table(&pl->umin_s, 2 * unit_cap);
   slab.table(&pl->counters, (size_t)2 * kSetWords);
   slab.table(&pl->ulist, unit_cap);

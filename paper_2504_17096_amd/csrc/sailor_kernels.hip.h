@@ -1,7 +1,8 @@
 // HIP kernels of the batched plan evaluator (gfx950, wave64).
 //
 // Set-up kernels (once per plan): k_small_tables, k_stage_tables, k_shape_agg, k_group_bounds;
-//            k_quota_table    again whenever the availability changes.
+//            k_quota_table    again whenever the availability changes;
+//            k_unit_work, k_work_order   in front of the first scan without a running limit.
 // Hot path:  k_units<SCAN>    full-space fp32 evaluation + per-unit minima, early pruning
 //            k_select_kth     radix select of the k-th smallest fp32 key (k > 128, or minima kept for later calls)
 //            k_units<COLLECT> re-evaluates the few units that can hold a winner
@@ -80,8 +81,7 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
 
 // The sum of a wave's values up to and including the lane's own (in the last lane: of all).  Six additions that
 // take their operand from another lane, where a shuffle is an LDS operation that is waited for: a search's levels
-// (histogram and counts of each) 0.51 -> 0.48 and 0.84 -> 0.74 ms, 11 739 listed plans 9.0 -> 8.7 us, with the
-// folds of k_eval_replicas 10 007 plans of replicas 46.8 -> 44.4.
+// (histogram and counts of each) 0.51 -> 0.48 and 0.84 -> 0.74 ms.
 __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
   auto from = [&](auto ctrl, auto rows) {  // (0 without a source; rows that a broadcast does not reach keep their sum)
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
