@@ -1380,10 +1380,7 @@ __device__ __forceinline__ void unit_work(const DevPlan &pl, const ScanArgs &a, 
     const bool have = d < pl.DP;
     const float con = HASB && have ? a.rows_con[(size_t)uidx * 2 * pl.DP + d] : 0.f;
     const float key = a.rows_key && have ? a.rows_key[(size_t)uidx * 2 * pl.DP + d] : 0.f;
-    // (Where minima are kept nothing falls to the largest pool, and a unit that kept them waits for no such load: re-plans
-    // of 1.1e9 plans with pairs of types 190 -> 185 us, of 9.2e8 117 -> 114.)
-    uint64_t replicas = 0;
-    if (a.most != ~0ull) replicas = have ? (uint64_t)(uint32_t)pl.vals[d] : 0u;
+    const uint64_t replicas = have ? (uint64_t)(uint32_t)pl.vals[d] : 0u;
     const bool meets = have && (!HASB || con <= a.lim_l), fits = replicas * (uint64_t)max(w0, max(w1, w2)) <= a.most;
     if (live) {
       if (follows && threadIdx.x < 64) {
